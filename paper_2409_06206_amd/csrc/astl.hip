@@ -8,6 +8,7 @@
 #include "staged_kernels.h"
 #include "astl_mlp.h"
 #include "fused.h"
+#include "window_layer.h"
 
 namespace gswa {
 
@@ -368,6 +369,8 @@ struct Plan {
     size_t reps;                  // bytes of the kGradReplicas copies
     size_t pack;                  // bytes of the MLP's repacked weights at the end of `saved` (fused MLP)
     bool fused_mlp, fused_mlp_bwd;
+    bool window;                  // both passes with one workgroup per window
+    Geom g;                       // (filled with `window`)
     bool wide_mlp;                // forward of the MLP half by the streaming kernel for wide layers
 };
 
@@ -402,6 +405,16 @@ int make_plan(const astl_desc *d, Plan *p)
     // backward: xn | dn | dx1 | max(pre | h | dh, attention scratch) | copies of the gradients
     const size_t hid_b = p->fused_mlp_bwd ? astl_mlp_bwd_ws_bytes(p->T, p->C, p->Hd) : 3 * p->hid;
     p->bwd_ws = 3 * p->act + (p->at_bws > hid_b ? p->at_bws : hid_b) + p->reps;
+    p->window = false;
+    if (d->attn.dtype == GSWA_F32 && !(d->attn.flags & GSWA_FORCE_STAGED)) {
+        rc = make_geom(&d->attn, &p->g);
+        if (rc != GSWA_OK) return rc;
+        p->window = window_layer_supported(p->g, true, p->Hd);
+    }
+    if (p->window) {
+        const size_t need = align256(window_layer_bwd_ws_bytes(p->g, p->Hd));
+        if (need > p->bwd_ws) p->bwd_ws = need;
+    }
     return GSWA_OK;
 }
 
@@ -415,6 +428,40 @@ int make_plan(const astl_desc *d, Plan *p)
         int rc_ = (expr);              \
         if (rc_ != GSWA_OK) return rc_; \
     } while (0)
+
+// The whole layer in one launch per direction (window_layer.h).
+WindowLayerArgs window_args(const astl_desc *d, const Plan &pl, const void *x, const astl_params *p)
+{
+    WindowLayerArgs a{};
+    a.g = pl.g; a.eps = d->eps; a.x = x;
+    a.w_qkv = p->w_qkv; a.b_qkv = p->b_qkv; a.w_proj = p->w_proj; a.b_proj = p->b_proj; a.table = p->bias_table;
+    a.ln1_w = p->ln1_w; a.ln1_b = p->ln1_b; a.ln2_w = p->ln2_w; a.ln2_b = p->ln2_b;
+    a.w_fc1 = p->w_fc1; a.b_fc1 = p->b_fc1; a.w_fc2 = p->w_fc2; a.b_fc2 = p->b_fc2;
+    return a;
+}
+
+int forward_window(const astl_desc *d, const Plan &pl, const void *x, const astl_params *p, void *y, char *saved, hipStream_t st)
+{
+    WindowLayerArgs a = window_args(d, pl, x, p);
+    a.y = y;
+    a.x1 = saved; a.attn = saved ? saved + pl.act : nullptr;
+    ASTL_HIP(launch_window_layer_fwd(a, d->attn.dtype == GSWA_F32, pl.Hd, st));
+    return GSWA_OK;
+}
+
+int backward_window(const astl_desc *d, const Plan &pl, const void *x, const void *dy, const astl_params *p, const char *saved,
+                    void *dx, const astl_grads *g, void *ws, hipStream_t st)
+{
+    WindowLayerArgs a = window_args(d, pl, x, p);
+    a.x1 = const_cast<char *>(saved); a.attn = const_cast<char *>(saved) + pl.act;
+    a.dy = dy; a.dx = dx; a.part = static_cast<float *>(ws);
+    WindowLayerGrads gr{};
+    gr.w_qkv = g->w_qkv; gr.b_qkv = g->b_qkv; gr.w_proj = g->w_proj; gr.b_proj = g->b_proj; gr.table = g->bias_table;
+    gr.w_fc1 = g->w_fc1; gr.b_fc1 = g->b_fc1; gr.w_fc2 = g->w_fc2; gr.b_fc2 = g->b_fc2;
+    gr.ln1_w = g->ln1_w; gr.ln1_b = g->ln1_b; gr.ln2_w = g->ln2_w; gr.ln2_b = g->ln2_b;
+    ASTL_HIP(launch_window_layer_bwd(a, d->attn.dtype == GSWA_F32, pl.Hd, gr, (d->attn.flags & GSWA_ACCUM_WGRAD) ? 1 : 0, st));
+    return GSWA_OK;
+}
 
 // What a sequence of layers hands from one forward call to the next: all layers of a sequence
 // use the same scratch, whose first slot holds LN_1(x) of the running layer.
@@ -799,6 +846,10 @@ int forward_checked(const astl_desc *desc, const void *x, const astl_params *p, 
     if (!x || !p || !y || !ws || !params_ok(p)) return GSWA_EINVAL;
     if (x == y || (reinterpret_cast<uintptr_t>(ws) & 255) || !aligned16(x, y, saved)) return GSWA_EINVAL;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
+    if (pl.window) {
+        if (link) link->emitted = false;
+        return forward_window(desc, pl, x, p, y, (char *)saved, st);
+    }
     if (desc->attn.dtype == GSWA_F32)
         return forward_t<float>(desc, pl, (const float *)x, p, (float *)y, (char *)saved, (char *)ws, st, link);
     return forward_t<bf16_t>(desc, pl, (const bf16_t *)x, p, (bf16_t *)y, (char *)saved, (char *)ws, st, link);
@@ -830,6 +881,7 @@ int backward_checked(const astl_desc *desc, const void *x, const void *dy, const
     if (dx == x || dx == dy || dx == saved || (reinterpret_cast<uintptr_t>(ws) & 255)) return GSWA_EINVAL;
     if (!aligned16(x, dy, saved, dx)) return GSWA_EINVAL;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
+    if (pl.window) return backward_window(desc, pl, x, dy, p, (const char *)saved, dx, g, ws, st);
     if (desc->attn.dtype == GSWA_F32)
         return backward_t<float>(desc, pl, (const float *)x, (const float *)dy, p, (const char *)saved, (float *)dx,
                                  g, (char *)ws, st, link);

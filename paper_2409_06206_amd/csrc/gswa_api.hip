@@ -4,6 +4,7 @@
 #include "common.h"
 #include "staged_kernels.h"
 #include "fused.h"
+#include "window_layer.h"
 
 #include <map>
 #include <mutex>
@@ -35,6 +36,45 @@ int gswa::report_hip_error(hipError_t e)
 {
     g_hip_error = hipGetErrorString(e);
     return GSWA_EHIP;
+}
+
+// Checks the descriptor (divisibility rules of the window partition and of the head groups)
+// and derives the geometry.
+int gswa::make_geom(const gswa_desc *d, Geom *g)
+{
+    if (!d) return GSWA_EINVAL;
+    if (d->B <= 0 || d->H <= 0 || d->W <= 0 || d->C <= 0) return GSWA_EINVAL;
+    if (d->heads <= 0 || d->groups <= 0 || d->window <= 0) return GSWA_EINVAL;
+    if (d->C % d->heads || d->heads % d->groups) return GSWA_EINVAL;
+    if (d->H % d->window || d->W % d->window) return GSWA_EINVAL;
+    if (d->shift < 0 || d->shift >= d->window) return GSWA_EINVAL;
+    if (d->dqk < 0) return GSWA_EINVAL;
+    if (d->dtype != GSWA_F32 && d->dtype != GSWA_BF16) return GSWA_EINVAL;
+    if (d->flags & ~(uint32_t)(GSWA_NO_CASCADE | GSWA_ACCUM_WGRAD | GSWA_FORCE_STAGED | GSWA_DETERMINISTIC))
+        return GSWA_EINVAL;
+    const long T = (long)d->B * d->H * d->W;
+    const long nW = T / ((long)d->window * d->window);
+    if (d->window > 64 || d->dqk > 4096) return GSWA_EUNSUPPORTED;
+    const int dq = d->dqk > 0 ? d->dqk : d->C / d->heads;
+    if (T * (2L * d->heads * dq + d->C) >= (1L << 40) || nW > 0x7fffffffL) return GSWA_EUNSUPPORTED;
+    g->B = d->B; g->H = d->H; g->W = d->W; g->C = d->C;
+    g->heads = d->heads; g->groups = d->groups; g->M = d->window; g->shift = d->shift;
+    g->N = d->window * d->window;
+    g->Cg = d->C / d->groups;
+    g->hg = d->heads / d->groups;
+    g->d = d->C / d->heads;
+    g->dq = dq;
+    g->Qg = g->hg * dq;
+    g->Rg = 2 * g->Qg + g->Cg;
+    g->nwi = d->H / d->window; g->nwj = d->W / d->window;
+    g->nW = (int)nW;
+    g->T = T;
+    g->cascade = (d->flags & GSWA_NO_CASCADE) ? 0 : 1;
+    int rs_f = 0, rs_b = 0;
+    attn_fwd_lds_bytes(*g, &rs_f);
+    attn_bwd_lds_bytes(*g, &rs_b);
+    if (rs_f == 0 || rs_b == 0) return GSWA_EUNSUPPORTED;
+    return GSWA_OK;
 }
 
 namespace {
@@ -84,45 +124,6 @@ size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
 // true when every pointer is 16-byte aligned (the kernels use vector loads and stores)
 template <typename... P> bool aligned16(P... p) { return (((reinterpret_cast<uintptr_t>(p)) | ...) & 15) == 0; }
 
-// Checks the descriptor (divisibility rules of the window partition and of the head groups)
-// and derives the geometry.
-int make_geom(const gswa_desc *d, Geom *g)
-{
-    if (!d) return GSWA_EINVAL;
-    if (d->B <= 0 || d->H <= 0 || d->W <= 0 || d->C <= 0) return GSWA_EINVAL;
-    if (d->heads <= 0 || d->groups <= 0 || d->window <= 0) return GSWA_EINVAL;
-    if (d->C % d->heads || d->heads % d->groups) return GSWA_EINVAL;
-    if (d->H % d->window || d->W % d->window) return GSWA_EINVAL;
-    if (d->shift < 0 || d->shift >= d->window) return GSWA_EINVAL;
-    if (d->dqk < 0) return GSWA_EINVAL;
-    if (d->dtype != GSWA_F32 && d->dtype != GSWA_BF16) return GSWA_EINVAL;
-    if (d->flags & ~(uint32_t)(GSWA_NO_CASCADE | GSWA_ACCUM_WGRAD | GSWA_FORCE_STAGED | GSWA_DETERMINISTIC))
-        return GSWA_EINVAL;
-    const long T = (long)d->B * d->H * d->W;
-    const long nW = T / ((long)d->window * d->window);
-    if (d->window > 64 || d->dqk > 4096) return GSWA_EUNSUPPORTED;
-    const int dq = d->dqk > 0 ? d->dqk : d->C / d->heads;
-    if (T * (2L * d->heads * dq + d->C) >= (1L << 40) || nW > 0x7fffffffL) return GSWA_EUNSUPPORTED;
-    g->B = d->B; g->H = d->H; g->W = d->W; g->C = d->C;
-    g->heads = d->heads; g->groups = d->groups; g->M = d->window; g->shift = d->shift;
-    g->N = d->window * d->window;
-    g->Cg = d->C / d->groups;
-    g->hg = d->heads / d->groups;
-    g->d = d->C / d->heads;
-    g->dq = dq;
-    g->Qg = g->hg * dq;
-    g->Rg = 2 * g->Qg + g->Cg;
-    g->nwi = d->H / d->window; g->nwj = d->W / d->window;
-    g->nW = (int)nW;
-    g->T = T;
-    g->cascade = (d->flags & GSWA_NO_CASCADE) ? 0 : 1;
-    int rs_f = 0, rs_b = 0;
-    attn_fwd_lds_bytes(*g, &rs_f);
-    attn_bwd_lds_bytes(*g, &rs_b);
-    if (rs_f == 0 || rs_b == 0) return GSWA_EUNSUPPORTED;
-    return GSWA_OK;
-}
-
 size_t elem_size(const gswa_desc *d) { return d->dtype == GSWA_F32 ? 4 : 2; }
 
 // A device buffer as a byte range, for the overlap rules of the entry points.
@@ -143,6 +144,7 @@ struct Sizes {
     size_t reps, tpart;  // bytes of the gradient copies and of the per-window bias-table gradients
     int nreps;           // gradient copies of the staged backward
     bool fused_fwd, fused_bwd;
+    bool window;         // fp32: one workgroup per window, both passes
 };
 
 bool use_fused_fwd(const gswa_desc *d, const Geom &g)
@@ -179,6 +181,12 @@ Sizes make_sizes(const gswa_desc *d, const Geom &g)
         // training needs no scratch; inference keeps the pack (and, when the forward is split,
         // the group outputs) in ws, which the caller sizes as fwd_ws + saved
         s.fwd_ws = 0;
+    }
+    s.window = !s.fused_fwd && d->dtype == GSWA_F32 && !(d->flags & GSWA_FORCE_STAGED) && window_layer_supported(g, true, 0);
+    if (s.window) {
+        // (never less than the one-kernel-per-step path asks for: GSWA_FORCE_STAGED changes no size)
+        const size_t need = align256(window_layer_bwd_ws_bytes(g, 0));
+        if (need > s.bwd_ws) s.bwd_ws = need;
     }
     if (s.fused_bwd) {
         s.fused_bwd_ws = align256(fused_bwd_ws_bytes(g));
@@ -392,6 +400,14 @@ int gswa_forward(const gswa_desc *desc, const void *x, const void *w_qkv, const 
         if (overlaps_any(rws, rx, rwq, rbq, rwp, rbp, rtb)) return GSWA_EINVAL;
     }
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
+    if (s.window) {
+        WindowLayerArgs a{};
+        a.g = g;
+        a.x = x; a.w_qkv = w_qkv; a.b_qkv = b_qkv; a.w_proj = w_proj; a.b_proj = b_proj; a.table = bias_table;
+        a.y = y; a.attn = saved;
+        GSWA_HIP(launch_window_layer_fwd(a, true, 0, st));
+        return GSWA_OK;
+    }
     if (desc->dtype == GSWA_F32)
         return forward_staged<float>(g, s, (const float *)x, (const float *)w_qkv, (const float *)b_qkv,
                                      (const float *)w_proj, (const float *)b_proj,
@@ -453,6 +469,17 @@ int gswa_backward(const gswa_desc *desc, const void *x, const void *dy, const vo
         if (overlaps_any(gtb, rx, rdy, rsv, rwq, rbq, rwp, rbp, rtb)) return GSWA_EINVAL;
     }
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
+    if (s.window) {
+        WindowLayerArgs a{};
+        a.g = g;
+        a.x = x; a.w_qkv = w_qkv; a.b_qkv = b_qkv; a.w_proj = w_proj; a.b_proj = b_proj; a.table = bias_table;
+        a.attn = const_cast<void *>(saved); a.dy = dy; a.dx = dx; a.part = static_cast<float *>(ws);
+        WindowLayerGrads gr{};
+        gr.w_qkv = (float *)dw_qkv; gr.b_qkv = (float *)db_qkv; gr.w_proj = (float *)dw_proj; gr.b_proj = (float *)db_proj;
+        gr.table = (float *)dbias_table;
+        GSWA_HIP(launch_window_layer_bwd(a, true, 0, gr, (desc->flags & GSWA_ACCUM_WGRAD) ? 1 : 0, st));
+        return GSWA_OK;
+    }
     if (desc->dtype == GSWA_F32)
         return backward_staged<float>(g, s, desc->flags, (const float *)x, (const float *)dy,
                                       (const float *)w_qkv, (const float *)b_qkv, (const float *)w_proj,

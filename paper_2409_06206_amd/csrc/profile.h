@@ -42,6 +42,9 @@ enum KernelId {
     K_LN_FWD_REDUCE, // LayerNorm of every token and that sum in one launch
     K_WIDE_ATTN_BWD, // wide layers: adjoint of one group's attention, one wavefront per window
     K_WIDE_WGRAD,    // wide layers: a group's dx slice and weight gradients from d(q|k|v)
+    K_WINDOW_BWD,    // whole backward of an attention layer, one workgroup per window
+    K_LAYER_FWD,     // a whole layer (Eq. 4-5), one workgroup per window
+    K_LAYER_BWD,     // its adjoint
     K_COUNT
 };
 

@@ -515,3 +515,16 @@ def test_random_layers_fp32(case):
 def test_random_layers_bf16(case):
     print("case", case, flush=True)
     parity.check_block(astl_oracle, dtype="bf16", **case)
+
+
+@pytest.mark.parametrize("groups,shape,shift,cascade", [
+    (1, (1, 24, 16), 0, True), (2, (4, 64, 72), 4, True), (3, (2, 8, 24), 5, True), (6, (1, 16, 8), 3, True),
+    (3, (1, 16, 16), 4, False),
+])
+def test_fp32_whole_layers_one_workgroup_per_window(groups, shape, shift, cascade):
+    """A whole fp32 layer of 60 channels, hidden 120, is one launch per direction: every group count, with and without
+    the cascade, more windows (288) than vectors of parameter gradients (256)."""
+    B, H, W = shape
+    case = dict(B=B, H=H, W=W, C=60, heads=6, groups=groups, window=8, shift=shift, dtype="f32", hidden=120)
+    print("case", case, flush=True)
+    parity.check_block(astl_oracle, cascade=cascade, **case)

@@ -446,3 +446,15 @@ def test_training_forward_on_the_fused_path_needs_no_scratch(oracle):
     with pytest.raises(gswa.GswaError):   # inference keeps its state in the scratch: NULL is an error there
         gswa.gswa_forward(layer.desc, layer.x, q["w_qkv"], q["b_qkv"], q["w_proj"], q["b_proj"], q["table"],
                           layer.y, None, None)
+
+
+@pytest.mark.parametrize("groups,shape,shift", [
+    (1, (4, 64, 72), 3),      # 288 windows: more than the 256 vectors of parameter gradients, so some workgroups take two
+    (2, (4, 64, 72), 4),
+    (3, (1, 8, 8), 5),        # one window, cut by the shift in both directions
+    (6, (33, 8, 64), 7),      # 264 windows of one window row
+])
+def test_fp32_layers_one_workgroup_per_window(oracle, groups, shape, shift):
+    """fp32 layers of 60 channels and 8x8 windows run one workgroup per window: every group count, workgroups with
+    one and with two windows, windows cut by the shift in every way."""
+    parity.check_case(oracle, *shape, 60, 6, groups, 8, shift, "f32", regime="stress")
