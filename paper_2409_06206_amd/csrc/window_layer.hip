@@ -32,9 +32,9 @@ constexpr float kLog2e = 1.4426950408889634f;
 // The lane's place in an operand, made afresh where it is used: otherwise the compiler computes the lane's addresses
 // of every phase at the start of the kernel, runs out of registers and spills them.
 #define FRESH_LANE                            \
-    int fresh_ = (int)threadIdx.x & 63;       \
+    int fresh_ = (int)threadIdx.x;            \
     asm volatile("" : "+v"(fresh_));          \
-    const int l16 = fresh_ & 15, q = fresh_ >> 4
+    const int l16 = fresh_ & 15, q = (fresh_ >> 4) & 3
 
 // Row pitch (elements): a multiple of four that is not a multiple of eight, so that 16 rows read at the same column
 // fall on different banks.
@@ -52,6 +52,9 @@ template <typename T_, int C_, int HEADS_, int G_, int M_, int DQ_, int HID_, in
     static constexpr int RQ = HG * HSQ, RV = HG * HSV, RP = 2 * RQ + RV;
     static constexpr int NFT = up(RP, 16), KUG = up(CG, 16), KUC = up(C, 16), KUR = up(RP, 16), CTC = up(C, 16), CTG = up(CG, 16);
     static constexpr int HFT = up(HID, 16), NVT = up(RV, 16);
+    // token tiles that share one reading of the weights: the loads of weights, 16 short pieces of rows each, are
+    // what the vector memory pipe of a compute unit spends its time on otherwise
+    static constexpr int TT = NT % 3 == 0 ? 3 : 2, TU = NT / TT;
     static constexpr int PC = pitch_of(16 * up(C + 1, 16)), PR = pitch_of(RP), PD = pitch_of(RV), PH = pitch_of(16 * up(HID + 1, 16));
     static constexpr int PF = N + 4; // pitch of a head's matrix of score gradients
     static constexpr int NTB = 2 * M - 1, NTBL = NTB * NTB, TBP = (NTBL + 3) & ~3;
@@ -73,7 +76,8 @@ template <typename T_, int C_, int HEADS_, int G_, int M_, int DQ_, int HID_, in
     static constexpr size_t SZ_DO = sizeof(E) * N * PD, SZ_F = sizeof(E) * N * PF;
     static constexpr size_t SZ_ST = sizeof(float) * 2 * HG * N, SZ_RED = sizeof(float) * WAVES * 2 * 16 * up(C, 16);
     static constexpr size_t B_R = 3 * SZ_ROW, B_U = B_R + SZ_R;
-    static constexpr size_t FIXED = B_U + SZ_TB + SZ_ST + SZ_RED;
+    static constexpr size_t SZ_SR = SZ_ST > SZ_RED ? SZ_ST : SZ_RED; // (row sums and softmax statistics take turns)
+    static constexpr size_t FIXED = B_U + SZ_TB + SZ_SR;
     static constexpr int fit_heads()
     {
         int n = HG;
@@ -83,7 +87,7 @@ template <typename T_, int C_, int HEADS_, int G_, int M_, int DQ_, int HID_, in
     static constexpr int NF = fit_heads(), ROUNDS = up(HG, NF);
     static constexpr size_t SZ_U = SZ_DO > NF * SZ_F ? SZ_DO : NF * SZ_F;
     static constexpr size_t bwd_tb(bool layer) { return layer && 2 * SZ_H > SZ_R + SZ_U ? B_R + 2 * SZ_H : B_U + SZ_U; }
-    static constexpr size_t bwd_lds(bool layer) { return bwd_tb(layer) + SZ_TB + SZ_ST + SZ_RED; }
+    static constexpr size_t bwd_lds(bool layer) { return bwd_tb(layer) + SZ_TB + SZ_SR; }
     static_assert(fwd_lds(true) <= 160 * 1024 && bwd_lds(true) <= 160 * 1024, "LDS budget");
 };
 
@@ -188,7 +192,14 @@ template <class S> struct Window {
         return ((last_r && r >= S::M - s) ? 1 : 0) | ((last_c && c >= S::M - s) ? 2 : 0);
     }
 };
+// offset of a token in the bias table: the entry of (query, key) is key_offset(query) - key_offset(key) + a constant;
+// of tokens 16 tile + 4q + i, which are neighbours in a window row (M is a multiple of four), it is that of i = 0 plus i
 template <class S> __device__ __forceinline__ int key_offset(int n) { const int r = n / S::M; return r * S::NTB + (n - r * S::M); }
+template <class S> __device__ __forceinline__ int key_offset4(int tile, int q)
+{
+    if (S::M == 8) return 2 * S::NTB * tile + S::NTB * (q >> 1) + 4 * (q & 1);
+    return key_offset<S>(16 * tile + 4 * q);
+}
 
 // feature of the padded q|k|v rows -> row of the group's weight block [q: QG | k: QG | v: CG], -1 for padding
 template <class S> __device__ __forceinline__ int weight_row(int f)
@@ -200,21 +211,85 @@ template <class S> __device__ __forceinline__ int weight_row(int f)
     const int r = f - 2 * S::RQ, h = r / S::HSV, e = r - h * S::HSV;
     return (r < S::RV && e < S::D) ? 2 * S::QG + h * S::D + e : -1;
 }
-
-// k-slots 16 s + 4q .. of row `row` of a row-major matrix with K columns (K even), zero beyond K and for row < 0
-template <typename E> __device__ __forceinline__ typename Op<E>::F weight_n(const E *w, int row, int ld, int k, int K)
+// the same for features f .. f + 3, f a multiple of four (all in one head): rows row .. row + n - 1, the rest is padding
+struct Rows4 { int row, n; };
+template <class S> __device__ __forceinline__ Rows4 weight_rows4(int f)
 {
-    const bool lo = row >= 0 && k < K, hi = row >= 0 && k + 2 < K;
-    const E *p = w + (long)(row < 0 ? 0 : row) * ld;
-    const f32x2 a = *reinterpret_cast<const f32x2 *>(p + (lo ? k : 0)), b = *reinterpret_cast<const f32x2 *>(p + (hi ? k + 2 : 0));
-    return f32x4{lo ? a[0] : 0.f, lo ? a[1] : 0.f, hi ? b[0] : 0.f, hi ? b[1] : 0.f};
+    const bool v = f >= 2 * S::RQ;
+    const int part = f >= S::RQ ? 1 : 0;
+    const int rq = f - part * S::RQ, hq = rq / S::HSQ, eq = rq - hq * S::HSQ;
+    const int rv = f - 2 * S::RQ, hv = (v ? rv : 0) / S::HSV, ev = rv - hv * S::HSV;
+    Rows4 r;
+    r.row = v ? 2 * S::QG + hv * S::D + ev : part * S::QG + hq * S::DQ + eq;
+    r.n = v ? S::D - ev : S::DQ - eq;
+    if (f >= S::RP) r.row = r.n = 0;
+    return r;
 }
+
+// Weights as operands, straight from memory.  All loads of a tile are issued before the first product (the compiler,
+// left alone, keeps four in flight: five trips to L2 per tile of 16 loads instead of one), so the values are masked
+// where they are used.  Only the k-slots beyond the matrix are masked; rows beyond it are the caller's to drop.
+// WeightsN: row `row` of a row-major matrix, k-slots along it (K and ld even).  WeightsT: column, k-slots down it.
+template <typename E, int K> struct WeightsN;
+template <typename E, int K> struct WeightsT;
+template <int K> struct WeightsN<float, K> {
+    static constexpr int KU = up(K, 16);
+    f32x4 v[KU];
+    __device__ __forceinline__ void load(const float *row, int q)
+    {
+#pragma unroll
+        for (int s = 0; s < KU; ++s) {
+            const int k = 16 * s + 4 * q;
+            if (K % 4 == 0) { // (rows of a multiple of 16 bytes)
+                v[s] = *reinterpret_cast<const f32x4 *>(row + (16 * s + 16 <= K || k < K ? k : 0));
+            } else {
+                const f32x2 lo = *reinterpret_cast<const f32x2 *>(row + (16 * s + 16 <= K || k < K ? k : 0));
+                const f32x2 hi = *reinterpret_cast<const f32x2 *>(row + (16 * s + 16 <= K || k + 2 < K ? k + 2 : 0));
+                v[s] = f32x4{lo[0], lo[1], hi[0], hi[1]};
+            }
+        }
+    }
+    __device__ __forceinline__ f32x4 op(int s, int q) const
+    {
+        const int k = 16 * s + 4 * q;
+        if (16 * s + 16 <= K) return v[s];
+        return f32x4{k < K ? v[s][0] : 0.f, k < K ? v[s][1] : 0.f, k + 2 < K ? v[s][2] : 0.f, k + 2 < K ? v[s][3] : 0.f};
+    }
+};
+template <int K> struct WeightsT<float, K> {
+    static constexpr int KU = up(K, 16);
+    float v[KU][4];
+    __device__ __forceinline__ void load(const float *col, int ld, int q)
+    {
+#pragma unroll
+        for (int s = 0; s < KU; ++s)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int k = 16 * s + 4 * q + i;
+                v[s][i] = col[(16 * s + 16 <= K || k < K ? k : 0) * ld];
+            }
+    }
+    __device__ __forceinline__ f32x4 op(int s, int q) const
+    {
+        f32x4 r;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) r[i] = (16 * s + 16 <= K || 16 * s + 4 * q + i < K) ? v[s][i] : 0.f;
+        return r;
+    }
+};
+__device__ __forceinline__ void loads_issued() { __builtin_amdgcn_sched_barrier(0); }
 
 // The row phases: 16 lanes hold a token, four channels each; a wave takes four tokens at a time.
 template <class S> struct Rows {
     static constexpr int UNITS = S::N / 4, PER = up(UNITS, S::WAVES);
 };
 __device__ __forceinline__ f32x4 load4(const float *p) { return *reinterpret_cast<const f32x4 *>(p); }
+// the same, or zeros (a load that no branch guards is not waited for before its value is used)
+template <typename T> __device__ __forceinline__ f32x4 load4_if(bool ok, const T *base, long at)
+{
+    const f32x4 v = load4(base + (ok ? at : 0));
+    return f32x4{ok ? v[0] : 0.f, ok ? v[1] : 0.f, ok ? v[2] : 0.f, ok ? v[3] : 0.f};
+}
 __device__ __forceinline__ void store4(float *p, f32x4 v) { *reinterpret_cast<f32x4 *>(p) = v; }
 
 // mean and 1 / sqrt(var + eps) of a token; lanes beyond the channels hold zeros
@@ -236,7 +311,7 @@ template <class S> __device__ __forceinline__ void load_table(float *tb, const t
 }
 
 // q|k|v of group gi from X (+ the output of the group before it, A) into the padded rows R
-template <class S> __device__ __forceinline__ void qkv_unit(const WindowLayerArgs &a, int gi, int ft, int tt, const typename S::E *X,
+template <class S> __device__ __forceinline__ void qkv_unit(const WindowLayerArgs &a, int gi, int ft, int tu, const typename S::E *X,
                                                             const typename S::E *A, typename S::E *R)
 {
     FRESH_LANE;
@@ -244,32 +319,32 @@ template <class S> __device__ __forceinline__ void qkv_unit(const WindowLayerArg
     const auto *w = static_cast<const typename S::T *>(a.w_qkv) + (long)gi * S::RG * S::CG;
     const auto *bias = static_cast<const typename S::T *>(a.b_qkv) + gi * S::RG;
     const int row = weight_row<S>(16 * ft + l16);
-    typename O::F wf[S::KUG];
+    WeightsN<typename S::E, S::CG> wf;
+    wf.load(w + (row < 0 ? 0 : row) * S::CG, q);
+    const Rows4 rows = weight_rows4<S>(16 * ft + 4 * q);
+    float bf[4];
 #pragma unroll
-    for (int s = 0; s < S::KUG; ++s) wf[s] = weight_n(w, row, S::CG, 16 * s + 4 * q, S::CG);
-    f32x4 acc;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int r = weight_row<S>(16 * ft + 4 * q + i);
-        acc[i] = r >= 0 ? to_f32(bias[r]) : 0.f;
-    }
-    const int t = 16 * tt + l16;
+    for (int i = 0; i < 4; ++i) bf[i] = to_f32(bias[i < rows.n ? rows.row + i : 0]);
+    loads_issued();
     const bool casc = gi > 0 && a.g.cascade;
 #pragma unroll
-    for (int s = 0; s < S::KUG; ++s) {
-        typename O::F f = O::ld_half(X + t * S::PC + gi * S::CG + 16 * s + 4 * q);
-        if (casc) f = O::add(f, O::ld_half(A + t * S::PC + (gi - 1) * S::CG + 16 * s + 4 * q));
-        acc = mma(wf[s], f, acc);
+    for (int tt = 0; tt < S::TT; ++tt) {
+        const int t = 16 * (tu * S::TT + tt) + l16;
+        typename O::F f[S::KUG];
+#pragma unroll
+        for (int s = 0; s < S::KUG; ++s) f[s] = O::ld_half(X + t * S::PC + gi * S::CG + 16 * s + 4 * q);
+        if (casc) {
+#pragma unroll
+            for (int s = 0; s < S::KUG; ++s) f[s] = O::add(f[s], O::ld_half(A + t * S::PC + (gi - 1) * S::CG + 16 * s + 4 * q));
+        }
+        f32x4 acc = O::zero();
+#pragma unroll
+        for (int s = 0; s < S::KUG; ++s) acc = mma(wf.op(s, q), f[s], acc);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[i] = i < rows.n ? acc[i] + bf[i] : 0.f;
+        if (16 * ft + 4 * q < S::RP) O::st(R + t * S::PR + 16 * ft + 4 * q, acc);
     }
-    if (16 * ft + 4 * q < S::RP) O::st(R + t * S::PR + 16 * ft + 4 * q, acc);
 }
-
-// base-2 scores of 16 keys (rows) against 16 queries (columns), bias and mask included
-template <class S> struct Scores {
-    float scale;
-    const float *tb;
-    __device__ __forceinline__ float bias(int oq, int ok) const { return tb[oq - ok + (S::M - 1) * (S::NTB + 1)]; }
-};
 
 template <class S, bool LAYER>
 __global__ __launch_bounds__(S::NTH) void window_layer_fwd_kernel(WindowLayerArgs a)
@@ -277,7 +352,6 @@ __global__ __launch_bounds__(S::NTH) void window_layer_fwd_kernel(WindowLayerArg
     using E = typename S::E;
     using T = typename S::T;
     using O = Op<E>;
-    using F = typename O::F;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     E *X = reinterpret_cast<E *>(lds + S::F_X), *A = reinterpret_cast<E *>(lds + S::F_A), *R = reinterpret_cast<E *>(lds + S::F_R);
     float *tb = reinterpret_cast<float *>(lds + S::fwd_tb(LAYER));
@@ -295,15 +369,15 @@ __global__ __launch_bounds__(S::NTH) void window_layer_fwd_kernel(WindowLayerArg
             const bool in = 4 * l16 < S::C;
             f32x4 gam, bet;
             if (LAYER) {
-                gam = in ? load4(static_cast<const T *>(a.ln1_w) + 4 * l16) : O::zero();
-                bet = in ? load4(static_cast<const T *>(a.ln1_b) + 4 * l16) : O::zero();
+                gam = load4_if(in, static_cast<const T *>(a.ln1_w), 4 * l16);
+                bet = load4_if(in, static_cast<const T *>(a.ln1_b), 4 * l16);
             }
             f32x4 f[Rows<S>::PER];
 #pragma unroll
             for (int k = 0; k < Rows<S>::PER; ++k) {
                 FRESH_LANE;
                 const int t = 4 * (wv + k * S::WAVES) + q;
-                f[k] = (in && t < S::N) ? load4(x + win.token(t < S::N ? t : 0) * S::C + 4 * l16) : O::zero();
+                f[k] = load4_if(in && t < S::N, x, win.token(t < S::N ? t : 0) * S::C + 4 * l16);
             }
 #pragma unroll
             for (int k = 0; k < Rows<S>::PER; ++k) {
@@ -334,7 +408,7 @@ __global__ __launch_bounds__(S::NTH) void window_layer_fwd_kernel(WindowLayerArg
 #pragma unroll 1
         for (int gi = 0; gi < S::G; ++gi) {
 #pragma unroll 1
-            for (int u = wv; u < S::NFT * S::NT; u += S::WAVES) qkv_unit<S>(a, gi, u / S::NT, u % S::NT, X, A, R);
+            for (int u = wv; u < S::NFT * S::TU; u += S::WAVES) qkv_unit<S>(a, gi, u / S::TU, u % S::TU, X, A, R);
             __syncthreads();
 #pragma unroll 1
             for (int u = wv; u < S::HG * S::NT; u += S::WAVES) {
@@ -351,15 +425,19 @@ __global__ __launch_bounds__(S::NTH) void window_layer_fwd_kernel(WindowLayerArg
                     HeadOp<E, S::HSQ> kf;
                     kf.load(R + (16 * kt + l16) * S::PR + S::RQ + hl * S::HSQ, q);
                     f32x4 s = mma(kf, qf, O::zero());
+                    const float *bias = tbh + oq - key_offset4<S>(kt, q);
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const int tk = 16 * kt + 4 * q + i;
-                        s[i] = fmaf(s[i], scale, tbh[oq - key_offset<S>(tk)]);
-                        if (masked) s[i] += win.region(tk) != rq ? maskv : 0.f;
-                        mx = fmaxf(mx, s[i]);
-                    }
+                    for (int i = 0; i < 4; ++i) s[i] = fmaf(s[i], scale, bias[-i]);
                     st[kt] = s;
                 }
+                if (masked) {
+#pragma unroll
+                    for (int kt = 0; kt < S::NT; ++kt)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) st[kt][i] += win.region(16 * kt + 4 * q + i) != rq ? maskv : 0.f;
+                }
+#pragma unroll
+                for (int kt = 0; kt < S::NT; ++kt) mx = fmaxf(mx, fmaxf(fmaxf(st[kt][0], st[kt][1]), fmaxf(st[kt][2], st[kt][3])));
                 mx = qgroup_max(mx);
                 float sum = 0.f;
 #pragma unroll
@@ -388,15 +466,18 @@ __global__ __launch_bounds__(S::NTH) void window_layer_fwd_kernel(WindowLayerArg
             FRESH_LANE;
             const int ct = u / S::NT, tt = u - ct * S::NT, t = 16 * tt + l16, c = 16 * ct + 4 * q;
             const long tok = win.token(t);
-            F wf[S::KUC];
-#pragma unroll
-            for (int s = 0; s < S::KUC; ++s)
-                wf[s] = weight_n(static_cast<const T *>(a.w_proj), 16 * ct + l16 < S::C ? 16 * ct + l16 : -1, S::C, 16 * s + 4 * q, S::C);
+            WeightsN<E, S::C> wf;
+            wf.load(static_cast<const T *>(a.w_proj) + (16 * ct + l16 < S::C ? 16 * ct + l16 : 0) * S::C, q);
             const bool in = c < S::C;
-            f32x4 acc = in ? load4(static_cast<const T *>(a.b_proj) + c) : O::zero();
-            if (LAYER && in) acc += load4(x + tok * S::C + c);
+            const f32x4 b = load4(static_cast<const T *>(a.b_proj) + (in ? c : 0));
+            f32x4 skip = O::zero();
+            if (LAYER) skip = load4(x + tok * S::C + (in ? c : 0));
+            loads_issued();
+            f32x4 acc = O::zero();
 #pragma unroll
-            for (int s = 0; s < S::KUC; ++s) acc = mma(wf[s], O::ld(A + t * S::PC + 16 * s + 4 * q), acc);
+            for (int s = 0; s < S::KUC; ++s) acc = mma(wf.op(s, q), O::ld(A + t * S::PC + 16 * s + 4 * q), acc);
+            acc += b;
+            if (LAYER) acc += skip;
             if (in) {
                 if (LAYER) {
                     O::st(X + t * S::PC + c, acc);
@@ -411,8 +492,8 @@ __global__ __launch_bounds__(S::NTH) void window_layer_fwd_kernel(WindowLayerArg
             // ---- LN_2 (over the group outputs), the MLP and its skip (Eq. 5) ----
             {
                 const bool in = 4 * l16 < S::C;
-                const f32x4 gam = in ? load4(static_cast<const T *>(a.ln2_w) + 4 * l16) : O::zero();
-                const f32x4 bet = in ? load4(static_cast<const T *>(a.ln2_b) + 4 * l16) : O::zero();
+                const f32x4 gam = load4_if(in, static_cast<const T *>(a.ln2_w), 4 * l16);
+                const f32x4 bet = load4_if(in, static_cast<const T *>(a.ln2_b), 4 * l16);
 #pragma unroll
                 for (int k = 0; k < Rows<S>::PER; ++k) {
                     FRESH_LANE;
@@ -429,33 +510,39 @@ __global__ __launch_bounds__(S::NTH) void window_layer_fwd_kernel(WindowLayerArg
             }
             __syncthreads();
 #pragma unroll 1
-            for (int u = wv; u < S::HFT * S::NT; u += S::WAVES) {
+            for (int u = wv; u < S::HFT * S::TU; u += S::WAVES) {
                 FRESH_LANE;
-                const int ft = u / S::NT, tt = u - ft * S::NT, t = 16 * tt + l16;
-                F wf[S::KUC];
+                const int ft = u / S::TU, tu = u - ft * S::TU;
+                const bool in = 16 * ft + 4 * q < S::HID;
+                WeightsN<E, S::C> wf;
+                wf.load(static_cast<const T *>(a.w_fc1) + (16 * ft + l16 < S::HID ? 16 * ft + l16 : 0) * S::C, q);
+                const f32x4 b = load4(static_cast<const T *>(a.b_fc1) + (in ? 16 * ft + 4 * q : 0));
+                loads_issued();
 #pragma unroll
-                for (int s = 0; s < S::KUC; ++s)
-                    wf[s] = weight_n(static_cast<const T *>(a.w_fc1), 16 * ft + l16 < S::HID ? 16 * ft + l16 : -1, S::C, 16 * s + 4 * q, S::C);
-                f32x4 acc = 16 * ft + 4 * q < S::HID ? load4(static_cast<const T *>(a.b_fc1) + 16 * ft + 4 * q) : O::zero();
+                for (int tt = 0; tt < S::TT; ++tt) {
+                    const int t = 16 * (tu * S::TT + tt) + l16;
+                    f32x4 acc = O::zero();
 #pragma unroll
-                for (int s = 0; s < S::KUC; ++s) acc = mma(wf[s], O::ld(A + t * S::PC + 16 * s + 4 * q), acc);
+                    for (int s = 0; s < S::KUC; ++s) acc = mma(wf.op(s, q), O::ld(A + t * S::PC + 16 * s + 4 * q), acc);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) acc[i] = gelu_f(acc[i]);
-                O::st(R + t * S::PH + 16 * ft + 4 * q, acc);
+                    for (int i = 0; i < 4; ++i) acc[i] = in ? gelu_f(acc[i] + b[i]) : 0.f;
+                    O::st(R + t * S::PH + 16 * ft + 4 * q, acc);
+                }
             }
             __syncthreads();
 #pragma unroll 1
             for (int u = wv; u < S::CTC * S::NT; u += S::WAVES) {
                 FRESH_LANE;
                 const int ct = u / S::NT, tt = u - ct * S::NT, t = 16 * tt + l16, c = 16 * ct + 4 * q;
-                F wf[S::HFT];
-#pragma unroll
-                for (int s = 0; s < S::HFT; ++s)
-                    wf[s] = weight_n(static_cast<const T *>(a.w_fc2), 16 * ct + l16 < S::C ? 16 * ct + l16 : -1, S::HID, 16 * s + 4 * q, S::HID);
+                WeightsN<E, S::HID> wf;
+                wf.load(static_cast<const T *>(a.w_fc2) + (16 * ct + l16 < S::C ? 16 * ct + l16 : 0) * S::HID, q);
                 const bool in = c < S::C;
-                f32x4 acc = in ? load4(static_cast<const T *>(a.b_fc2) + c) + O::wide(O::ld(X + t * S::PC + c)) : O::zero();
+                const f32x4 b = load4(static_cast<const T *>(a.b_fc2) + (in ? c : 0));
+                loads_issued();
+                f32x4 acc = O::zero();
 #pragma unroll
-                for (int s = 0; s < S::HFT; ++s) acc = mma(wf[s], O::ld(R + t * S::PH + 16 * s + 4 * q), acc);
+                for (int s = 0; s < S::HFT; ++s) acc = mma(wf.op(s, q), O::ld(R + t * S::PH + 16 * s + 4 * q), acc);
+                acc += b + O::wide(O::ld(X + t * S::PC + c));
                 if (in) store4(static_cast<T *>(a.y) + win.token(t) * S::C + c, acc);
             }
         }
@@ -469,14 +556,11 @@ __device__ __forceinline__ void put_grad(float *p, float v, bool first) { *p = f
 // result tile [16 rows of `rows`][16 columns] of a weight gradient: column `cols` is the bias gradient
 __device__ __forceinline__ void put_tile(float *dw, float *db, int ld, int row0, int rows, int col, int cols, f32x4 v, bool first)
 {
+    if (row0 >= rows || col > cols) return; // (rows is a multiple of four)
+    float *p = col < cols ? dw + row0 * ld + col : db + row0;
+    const int step = col < cols ? ld : 1;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int r = row0 + i;
-        if (r < rows) {
-            if (col < cols) put_grad(dw + r * ld + col, v[i], first);
-            else if (col == cols) put_grad(db + r, v[i], first);
-        }
-    }
+    for (int i = 0; i < 4; ++i) put_grad(p + i * step, v[i], first);
 }
 
 template <class S, bool LAYER>
@@ -492,7 +576,7 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
     E *Hh = R, *DP = reinterpret_cast<E *>(lds + S::B_R + S::SZ_H);
     float *tb = reinterpret_cast<float *>(lds + S::bwd_tb(LAYER));
     float *lse = tb + S::HEADS * S::TBP, *delta = lse + S::HG * S::N;
-    float *red = delta + S::HG * S::N;  // [WAVES][2][CP]
+    float *red = lse;  // [WAVES][2][CP]
     constexpr int CP = 16 * up(S::C, 16);
     const int l16 = threadIdx.x & 15, q = (threadIdx.x >> 4) & 3;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -534,16 +618,16 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
         if (LAYER) {
             // ---- Eq. 5 backwards.  A: LN_2(x1), DX: dy ----
             {
-                const f32x4 gam = in ? load4(static_cast<const T *>(a.ln2_w) + 4 * l16) : O::zero();
-                const f32x4 bet = in ? load4(static_cast<const T *>(a.ln2_b) + 4 * l16) : O::zero();
+                const f32x4 gam = load4_if(in, static_cast<const T *>(a.ln2_w), 4 * l16);
+                const f32x4 bet = load4_if(in, static_cast<const T *>(a.ln2_b), 4 * l16);
 #pragma unroll
                 for (int k = 0; k < Rows<S>::PER; ++k) {
                     FRESH_LANE;
                     const int t = 4 * (wv + k * S::WAVES) + q;
                     if (t < S::N) {
                         const long tok = win.token(t) * S::C + 4 * l16;
-                        f32x4 f = in ? load4(static_cast<const T *>(a.x1) + tok) : O::zero();
-                        const f32x4 d = in ? load4(static_cast<const T *>(a.dy) + tok) : O::zero();
+                        f32x4 f = load4_if(in, static_cast<const T *>(a.x1), tok);
+                        const f32x4 d = load4_if(in, static_cast<const T *>(a.dy), tok);
                         float mean, rstd;
                         stats<S>(f, in, a.eps, mean, rstd);
 #pragma unroll
@@ -556,80 +640,82 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
             __syncthreads();
             // ---- hidden layer, its gradient through the GELU ----
 #pragma unroll 1
-            for (int u = wv; u < S::HFT * S::NT; u += S::WAVES) {
+            for (int u = wv; u < S::HFT * S::TU; u += S::WAVES) {
                 FRESH_LANE;
-                const int ft = u / S::NT, tt = u - ft * S::NT, t = 16 * tt + l16, f = 16 * ft + l16;
-                F w1[S::KUC], w2[S::KUC];
+                const int ft = u / S::TU, tu = u - ft * S::TU, f = 16 * ft + l16;
+                const bool inf = 16 * ft + 4 * q < S::HID;
+                WeightsN<E, S::C> w1;
+                WeightsT<E, S::C> w2;
+                w1.load(static_cast<const T *>(a.w_fc1) + (f < S::HID ? f : 0) * S::C, q);
+                w2.load(static_cast<const T *>(a.w_fc2) + (f < S::HID ? f : 0), S::HID, q);
+                const f32x4 b = load4(static_cast<const T *>(a.b_fc1) + (inf ? 16 * ft + 4 * q : 0));
+                loads_issued();
 #pragma unroll
-                for (int s = 0; s < S::KUC; ++s) {
-                    w1[s] = weight_n(static_cast<const T *>(a.w_fc1), f < S::HID ? f : -1, S::C, 16 * s + 4 * q, S::C);
-                    const T *p2 = static_cast<const T *>(a.w_fc2) + (f < S::HID ? f : 0);
-                    float v[4];
+                for (int tt = 0; tt < S::TT; ++tt) {
+                    const int t = 16 * (tu * S::TT + tt) + l16;
+                    f32x4 pre = O::zero(), dh = O::zero();
+#pragma unroll
+                    for (int s = 0; s < S::KUC; ++s) {
+                        pre = mma(w1.op(s, q), O::ld(A + t * S::PC + 16 * s + 4 * q), pre);
+                        dh = mma(w2.op(s, q), O::ld(DX + t * S::PC + 16 * s + 4 * q), dh);
+                    }
+                    f32x4 h;
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        const int c = 16 * s + 4 * q + i;
-                        const bool ok = f < S::HID && c < S::C;
-                        v[i] = to_f32(p2[(c < S::C ? c : 0) * S::HID]);
-                        v[i] = ok ? v[i] : 0.f;
+                        pre[i] += b[i];
+                        h[i] = inf ? gelu_f(pre[i]) : 0.f;
+                        dh[i] = inf ? dh[i] * gelu_df(pre[i]) : 0.f;
                     }
-                    w2[s] = O::gather(v[0], v[1], v[2], v[3]);
+                    if (16 * ft + 4 * q == S::HID) h = one_pad;
+                    O::st(Hh + t * S::PH + 16 * ft + 4 * q, h);
+                    O::st(DP + t * S::PH + 16 * ft + 4 * q, dh);
                 }
-                f32x4 pre = 16 * ft + 4 * q < S::HID ? load4(static_cast<const T *>(a.b_fc1) + 16 * ft + 4 * q) : O::zero();
-                f32x4 dh = O::zero();
-#pragma unroll
-                for (int s = 0; s < S::KUC; ++s) {
-                    pre = mma(w1[s], O::ld(A + t * S::PC + 16 * s + 4 * q), pre);
-                    dh = mma(w2[s], O::ld(DX + t * S::PC + 16 * s + 4 * q), dh);
-                }
-                f32x4 h;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    h[i] = gelu_f(pre[i]);
-                    dh[i] *= gelu_df(pre[i]);
-                }
-                if (16 * ft + 4 * q == S::HID) h = one_pad;
-                O::st(Hh + t * S::PH + 16 * ft + 4 * q, h);
-                O::st(DP + t * S::PH + 16 * ft + 4 * q, dh);
             }
             __syncthreads();
             // ---- dn = dpre W1 (into X);  d Wfc1 = dpre^T LN_2(x1);  d Wfc2 = dy^T h ----
-            constexpr int U0 = S::CTC * S::NT, U1 = U0 + S::HFT * S::CTC, U2 = U1 + S::CTC * S::HFT;
+            // (weight gradients two column tiles at a time: they share the reading of the row tile)
+            constexpr int U0 = S::CTC * S::TU, U1 = U0 + S::HFT * up(S::CTC, 2), U2 = U1 + S::CTC * up(S::HFT, 2);
+            static_assert(S::CTC % 2 == 0 && S::HFT % 2 == 0, "pairs of column tiles");
 #pragma unroll 1
             for (int u = wv; u < U2; u += S::WAVES) {
                 FRESH_LANE;
                 if (u < U0) {
-                    const int ct = u / S::NT, tt = u - ct * S::NT, t = 16 * tt + l16, c = 16 * ct + l16;
-                    f32x4 acc = O::zero();
-                    F wf[S::HFT];
-                    const T *p1 = static_cast<const T *>(a.w_fc1) + (c < S::C ? c : 0);
+                    const int ct = u / S::TU, tu = u - ct * S::TU, c = 16 * ct + l16;
+                    WeightsT<E, S::HID> wf;
+                    wf.load(static_cast<const T *>(a.w_fc1) + (c < S::C ? c : 0), S::C, q);
+                    loads_issued();
 #pragma unroll
-                    for (int s = 0; s < S::HFT; ++s) {
-                        float v[4];
+                    for (int tt = 0; tt < S::TT; ++tt) {
+                        const int t = 16 * (tu * S::TT + tt) + l16;
+                        f32x4 acc = O::zero();
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            const int f = 16 * s + 4 * q + i;
-                            v[i] = to_f32(p1[(f < S::HID ? f : 0) * S::C]);
-                            v[i] = (f < S::HID && c < S::C) ? v[i] : 0.f;
-                        }
-                        wf[s] = O::gather(v[0], v[1], v[2], v[3]);
+                        for (int s = 0; s < S::HFT; ++s) acc = mma(wf.op(s, q), O::ld(DP + t * S::PH + 16 * s + 4 * q), acc);
+                        O::st(X + t * S::PC + 16 * ct + 4 * q, acc);
+                    }
+                } else if (u < U1) {
+                    const int v = u - U0, ft = v / (S::CTC / 2), ct = 2 * (v - ft * (S::CTC / 2));
+                    f32x4 acc[2] = {O::zero(), O::zero()};
+#pragma unroll
+                    for (int s = 0; s < S::NT; ++s) {
+                        const F r = O::ld_t(DP + 16 * s * S::PH + 16 * ft, S::PH, q, l16);
+#pragma unroll
+                        for (int p = 0; p < 2; ++p) acc[p] = mma(r, O::ld_t(A + 16 * s * S::PC + 16 * (ct + p), S::PC, q, l16), acc[p]);
                     }
 #pragma unroll
-                    for (int s = 0; s < S::HFT; ++s) acc = mma(wf[s], O::ld(DP + t * S::PH + 16 * s + 4 * q), acc);
-                    O::st(X + t * S::PC + 16 * ct + 4 * q, acc);
-                } else if (u < U1) {
-                    const int v = u - U0, ft = v / S::CTC, ct = v - ft * S::CTC;
-                    f32x4 acc = O::zero();
-#pragma unroll
-                    for (int s = 0; s < S::NT; ++s)
-                        acc = mma(O::ld_t(DP + 16 * s * S::PH + 16 * ft, S::PH, q, l16), O::ld_t(A + 16 * s * S::PC + 16 * ct, S::PC, q, l16), acc);
-                    put_tile(part + S::P_W1, part + S::P_B1, S::C, 16 * ft + 4 * q, S::HID, 16 * ct + l16, S::C, acc, first);
+                    for (int p = 0; p < 2; ++p)
+                        put_tile(part + S::P_W1, part + S::P_B1, S::C, 16 * ft + 4 * q, S::HID, 16 * (ct + p) + l16, S::C, acc[p], first);
                 } else {
-                    const int v = u - U1, ft = v / S::CTC, ct = v - ft * S::CTC;
-                    f32x4 acc = O::zero();
+                    const int v = u - U1, ct = v / (S::HFT / 2), ft = 2 * (v - ct * (S::HFT / 2));
+                    f32x4 acc[2] = {O::zero(), O::zero()};
 #pragma unroll
-                    for (int s = 0; s < S::NT; ++s)
-                        acc = mma(O::ld_t(DX + 16 * s * S::PC + 16 * ct, S::PC, q, l16), O::ld_t(Hh + 16 * s * S::PH + 16 * ft, S::PH, q, l16), acc);
-                    put_tile(part + S::P_W2, part + S::P_B2, S::HID, 16 * ct + 4 * q, S::C, 16 * ft + l16, S::HID, acc, first);
+                    for (int s = 0; s < S::NT; ++s) {
+                        const F r = O::ld_t(DX + 16 * s * S::PC + 16 * ct, S::PC, q, l16);
+#pragma unroll
+                        for (int p = 0; p < 2; ++p) acc[p] = mma(r, O::ld_t(Hh + 16 * s * S::PH + 16 * (ft + p), S::PH, q, l16), acc[p]);
+                    }
+#pragma unroll
+                    for (int p = 0; p < 2; ++p)
+                        put_tile(part + S::P_W2, part + S::P_B2, S::HID, 16 * ct + 4 * q, S::C, 16 * (ft + p) + l16, S::HID, acc[p], first);
                 }
             }
             __syncthreads();
@@ -638,9 +724,9 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
         {
             f32x4 gam1, bet1, gam2, sg = O::zero(), sb = O::zero();
             if (LAYER) {
-                gam1 = in ? load4(static_cast<const T *>(a.ln1_w) + 4 * l16) : O::zero();
-                bet1 = in ? load4(static_cast<const T *>(a.ln1_b) + 4 * l16) : O::zero();
-                gam2 = in ? load4(static_cast<const T *>(a.ln2_w) + 4 * l16) : O::zero();
+                gam1 = load4_if(in, static_cast<const T *>(a.ln1_w), 4 * l16);
+                bet1 = load4_if(in, static_cast<const T *>(a.ln1_b), 4 * l16);
+                gam2 = load4_if(in, static_cast<const T *>(a.ln2_w), 4 * l16);
             }
 #pragma unroll
             for (int k = 0; k < Rows<S>::PER; ++k) {
@@ -648,12 +734,12 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
                 const int t = 4 * (wv + k * S::WAVES) + q;
                 if (t < S::N) {
                     const long tok = win.token(t) * S::C + 4 * l16;
-                    f32x4 f = in ? load4(x + tok) : O::zero();
-                    f32x4 at = in ? load4(static_cast<const T *>(a.attn) + tok) : O::zero();
+                    f32x4 f = load4_if(in, x, tok);
+                    f32x4 at = load4_if(in, static_cast<const T *>(a.attn), tok);
                     E *xr = X + t * S::PC + 4 * l16, *dr = DX + t * S::PC + 4 * l16;
                     float mean, rstd;
                     if (LAYER) {
-                        const f32x4 u = in ? load4(static_cast<const T *>(a.x1) + tok) : O::zero();
+                        const f32x4 u = load4_if(in, static_cast<const T *>(a.x1), tok);
                         stats<S>(u, in, a.eps, mean, rstd);
                         f32x4 d = O::wide(O::ld(xr)), xh;
                         float s1 = 0.f, s2 = 0.f;
@@ -677,7 +763,7 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
 #pragma unroll
                         for (int i = 0; i < 4; ++i) f[i] = in ? (f[i] - mean) * rstd * gam1[i] + bet1[i] : 0.f;
                     } else {
-                        O::st(dr, in ? load4(static_cast<const T *>(a.dy) + tok) : O::zero());
+                        O::st(dr, load4_if(in, static_cast<const T *>(a.dy), tok));
                     }
                     O::st(xr, f);
                     O::st(A + t * S::PC + 4 * l16, 4 * l16 == S::C ? one_pad : at);
@@ -697,48 +783,48 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
         for (int gi = S::G - 1; gi >= 0; --gi) {
             const bool casc = gi > 0 && a.g.cascade;
             // ---- q|k|v of the group, dO = dY Wproj slice + the cascade gradient; once: d Wproj ----
-            constexpr int U0 = S::NVT * S::NT, U1 = U0 + S::NFT * S::NT;
-            const int U2 = gi == S::G - 1 ? U1 + S::CTC * S::CTC : U1;
+            constexpr int U0 = S::NVT * S::TU, U1 = U0 + S::NFT * S::TU;
+            const int U2 = gi == S::G - 1 ? U1 + S::CTC * S::CTC / 2 : U1;
 #pragma unroll 1
             for (int u = wv; u < U2; u += S::WAVES) {
                 FRESH_LANE;
                 if (u < U0) {
-                    const int vt = u / S::NT, tt = u - vt * S::NT, t = 16 * tt + l16;
+                    const int vt = u / S::TU, tu = u - vt * S::TU;
                     const int fr = 16 * vt + l16, hr = fr / S::HSV, er = fr - hr * S::HSV;
                     const bool okr = fr < S::RV && er < S::D;
-                    const T *pw = static_cast<const T *>(a.w_proj) + (okr ? gi * S::CG + hr * S::D + er : 0);
-                    F wf[S::KUC];
+                    WeightsT<E, S::C> wf;
+                    wf.load(static_cast<const T *>(a.w_proj) + (okr ? gi * S::CG + hr * S::D + er : 0), S::C, q);
+                    loads_issued();
+                    const int fo = 16 * vt + 4 * q, h = fo / S::HSV, e = fo - h * S::HSV; // (four features of one head)
+                    const bool prev = gi < S::G - 1 && a.g.cascade;
 #pragma unroll
-                    for (int s = 0; s < S::KUC; ++s) {
-                        float v[4];
+                    for (int tt = 0; tt < S::TT; ++tt) {
+                        const int t = 16 * (tu * S::TT + tt) + l16;
+                        f32x4 acc = O::zero();
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            const int o = 16 * s + 4 * q + i;
-                            v[i] = to_f32(pw[(o < S::C ? o : 0) * S::C]);
-                            v[i] = (okr && o < S::C) ? v[i] : 0.f;
-                        }
-                        wf[s] = O::gather(v[0], v[1], v[2], v[3]);
-                    }
-                    f32x4 acc = O::zero();
-                    if (gi < S::G - 1 && a.g.cascade) {
+                        for (int s = 0; s < S::KUC; ++s) acc = mma(wf.op(s, q), O::ld(DX + t * S::PC + 16 * s + 4 * q), acc);
+                        const E *xp = X + t * S::PC + (gi + 1) * S::CG + h * S::D + e;
 #pragma unroll
                         for (int i = 0; i < 4; ++i) {
-                            const int f = 16 * vt + 4 * q + i, h = f / S::HSV, e = f - h * S::HSV;
-                            if (f < S::RV && e < S::D) acc[i] = O::get(X + t * S::PC + (gi + 1) * S::CG + h * S::D + e);
+                            if (prev) acc[i] += O::get(xp + i);
+                            acc[i] = e + i < S::D ? acc[i] : 0.f;
                         }
+                        if (fo < S::RV) O::st(DO + t * S::PD + fo, acc);
                     }
-#pragma unroll
-                    for (int s = 0; s < S::KUC; ++s) acc = mma(wf[s], O::ld(DX + t * S::PC + 16 * s + 4 * q), acc);
-                    if (16 * vt + 4 * q < S::RV) O::st(DO + t * S::PD + 16 * vt + 4 * q, acc);
                 } else if (u < U1) {
-                    qkv_unit<S>(a, gi, (u - U0) / S::NT, (u - U0) % S::NT, X, A, R);
+                    qkv_unit<S>(a, gi, (u - U0) / S::TU, (u - U0) % S::TU, X, A, R);
                 } else {
-                    const int ot = (u - U1) / S::CTC, ct = (u - U1) - ot * S::CTC;
-                    f32x4 acc = O::zero();
+                    const int v = u - U1, ot = v / (S::CTC / 2), ct = 2 * (v - ot * (S::CTC / 2));
+                    f32x4 acc[2] = {O::zero(), O::zero()};
 #pragma unroll
-                    for (int s = 0; s < S::NT; ++s)
-                        acc = mma(O::ld_t(DX + 16 * s * S::PC + 16 * ot, S::PC, q, l16), O::ld_t(A + 16 * s * S::PC + 16 * ct, S::PC, q, l16), acc);
-                    put_tile(part + S::P_WP, part + S::P_BP, S::C, 16 * ot + 4 * q, S::C, 16 * ct + l16, S::C, acc, first);
+                    for (int s = 0; s < S::NT; ++s) {
+                        const F r = O::ld_t(DX + 16 * s * S::PC + 16 * ot, S::PC, q, l16);
+#pragma unroll
+                        for (int p = 0; p < 2; ++p) acc[p] = mma(r, O::ld_t(A + 16 * s * S::PC + 16 * (ct + p), S::PC, q, l16), acc[p]);
+                    }
+#pragma unroll
+                    for (int p = 0; p < 2; ++p)
+                        put_tile(part + S::P_WP, part + S::P_BP, S::C, 16 * ot + 4 * q, S::C, 16 * (ct + p) + l16, S::C, acc[p], first);
                 }
             }
             __syncthreads();
@@ -769,15 +855,19 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
                     vf.load(R + (16 * kt + l16) * S::PR + 2 * S::RQ + hl * S::HSV, q);
                     f32x4 s = mma(kf, qf, O::zero());
                     dp[kt] = mma(vf, of, O::zero());
+                    const float *bias = tbh + oq - key_offset4<S>(kt, q);
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const int tk = 16 * kt + 4 * q + i;
-                        s[i] = fmaf(s[i], scale, tbh[oq - key_offset<S>(tk)]);
-                        if (masked) s[i] += win.region(tk) != rq ? maskv : 0.f;
-                        mx = fmaxf(mx, s[i]);
-                    }
+                    for (int i = 0; i < 4; ++i) s[i] = fmaf(s[i], scale, bias[-i]);
                     st[kt] = s;
                 }
+                if (masked) {
+#pragma unroll
+                    for (int kt = 0; kt < S::NT; ++kt)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) st[kt][i] += win.region(16 * kt + 4 * q + i) != rq ? maskv : 0.f;
+                }
+#pragma unroll
+                for (int kt = 0; kt < S::NT; ++kt) mx = fmaxf(mx, fmaxf(fmaxf(st[kt][0], st[kt][1]), fmaxf(st[kt][2], st[kt][3])));
                 mx = qgroup_max(mx);
                 float sum = 0.f, dl = 0.f;
 #pragma unroll
@@ -831,12 +921,16 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
                     const f32x4 ls = *reinterpret_cast<const f32x4 *>(lse + hl * S::N + 16 * nt + 4 * q);
                     const f32x4 dl = *reinterpret_cast<const f32x4 *>(delta + hl * S::N + 16 * nt + 4 * q);
                     f32x4 p, d;
+                    const float *bias = tbh + ok + key_offset4<S>(nt, q);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) p[i] = fmaf(s[i], scale, bias[i]) - ls[i];
+                    if (masked) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) p[i] += win.region(16 * nt + 4 * q + i) != rk ? maskv : 0.f;
+                    }
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        const int tq = 16 * nt + 4 * q + i;
-                        float v = fmaf(s[i], scale, tbh[key_offset<S>(tq) + ok]);
-                        if (masked) v += win.region(tq) != rk ? maskv : 0.f;
-                        p[i] = __builtin_amdgcn_exp2f(v - ls[i]);
+                        p[i] = __builtin_amdgcn_exp2f(p[i]);
                         d[i] = p[i] * (dp[i] - dl[i]);
                     }
                     ds[k][nt] = O::from(d);
@@ -912,51 +1006,79 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
             leave_scores(0);
             __syncthreads();
             // ---- table gradient, dF = d(q|k|v) Wqkv, d Wqkv = d(q|k|v)^T F ----
-            constexpr int UF = S::CTG * S::NT, PX = up(UF, S::WAVES), V0 = S::NF * FP, V1 = V0 + S::NFT * S::CTG;
-            f32x4 df[PX];
+            constexpr int UF = S::CTG * S::TU, PX = up(UF, S::WAVES), CP2 = up(S::CTG, 2), V0 = S::NF * FP, V1 = V0 + S::NFT * CP2;
+            f32x4 df[PX][S::TT];
             const T *wq = static_cast<const T *>(a.w_qkv) + (long)gi * S::RG * S::CG;
 #pragma unroll
             for (int k = 0; k < PX; ++k) {
                 FRESH_LANE;
                 const int u = wv + k * S::WAVES;
-                df[k] = O::zero();
+#pragma unroll
+                for (int tt = 0; tt < S::TT; ++tt) df[k][tt] = O::zero();
                 if (u >= UF) continue;
-                const int ct = u / S::NT, tt = u - ct * S::NT, t = 16 * tt + l16, c = 16 * ct + l16;
+                const int ct = u / S::TU, tu = u - ct * S::TU, c = 16 * ct + l16;
+                const T *wc = wq + (c < S::CG ? c : 0);
+                constexpr int KB = S::KUR > 8 ? up(S::KUR, 2) : S::KUR; // (in two batches where the registers ask for it)
 #pragma unroll
-                for (int s = 0; s < S::KUR; ++s) {
-                    float v[4];
+                for (int s0 = 0; s0 < S::KUR; s0 += KB) {
+                    T v[KB][4];
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const int r = weight_row<S>(16 * s + 4 * q + i);
-                        v[i] = to_f32(wq[(r < 0 ? 0 : r) * S::CG + (c < S::CG ? c : 0)]);
-                        v[i] = (r >= 0 && c < S::CG) ? v[i] : 0.f;
+                    for (int s = s0; s < s0 + KB && s < S::KUR; ++s) {
+                        const Rows4 rows = weight_rows4<S>(16 * s + 4 * q);
+                        const T *wr = wc + rows.row * S::CG;
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) v[s - s0][i] = wr[i < rows.n ? i * S::CG : 0];
                     }
-                    const bool okk = 16 * s + 16 <= S::RP || 16 * s + 4 * q < S::RP;
-                    df[k] = mma(O::gather(v[0], v[1], v[2], v[3]), O::pick(okk, O::ld(R + t * S::PR + (okk ? 16 * s + 4 * q : 0))), df[k]);
+                    loads_issued();
+#pragma unroll
+                    for (int s = s0; s < s0 + KB && s < S::KUR; ++s) {
+                        const Rows4 rows = weight_rows4<S>(16 * s + 4 * q);
+                        const bool okk = 16 * s + 16 <= S::RP || 16 * s + 4 * q < S::RP;
+                        float m[4];
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) m[i] = i < rows.n ? to_f32(v[s - s0][i]) : 0.f;
+                        const F wf = O::gather(m[0], m[1], m[2], m[3]);
+#pragma unroll
+                        for (int tt = 0; tt < S::TT; ++tt) {
+                            const E *r = R + (16 * (tu * S::TT + tt) + l16) * S::PR;
+                            df[k][tt] = mma(wf, O::pick(okk, O::ld(r + (okk ? 16 * s + 4 * q : 0))), df[k][tt]);
+                        }
+                    }
+                    loads_issued();
                 }
             }
-            // (the wavefronts without a tile of dF take the first of the other units)
+            // (the wavefronts without tiles of dF take the first of the other units)
 #pragma unroll 1
             for (int u = (wv + S::WAVES - UF % S::WAVES) % S::WAVES; u < V1; u += S::WAVES) {
                 FRESH_LANE;
                 if (u < V0) {
                     fold(u / FP, u / FP, u % FP);
                 } else {
-                    const int ft = (u - V0) / S::CTG, ct = (u - V0) - ft * S::CTG, c = 16 * ct + l16;
-                    f32x4 acc = O::zero();
+                    constexpr int P = S::CTG > 1 ? 2 : 1;
+                    const int ft = (u - V0) / CP2, ct = P * ((u - V0) - ft * CP2);
+                    f32x4 acc[P];
+#pragma unroll
+                    for (int p = 0; p < P; ++p) acc[p] = O::zero();
 #pragma unroll
                     for (int s = 0; s < S::NT; ++s) {
-                        F b = O::ld_t(X + 16 * s * S::PC + gi * S::CG + 16 * ct, S::PC, q, l16);
-                        if (casc) b = O::add(b, O::ld_t(A + 16 * s * S::PC + (gi - 1) * S::CG + 16 * ct, S::PC, q, l16));
-                        if (c == S::CG) b = O::ones();
-                        acc = mma(O::ld_t(R + 16 * s * S::PR + 16 * ft, S::PR, q, l16), b, acc);
-                    }
+                        const F r = O::ld_t(R + 16 * s * S::PR + 16 * ft, S::PR, q, l16);
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const int r = weight_row<S>(16 * ft + 4 * q + i);
-                        if (r < 0 || 16 * ft + 4 * q + i >= S::RP) continue;
-                        if (c < S::CG) put_grad(part + S::P_WQ + (gi * S::RG + r) * S::CG + c, acc[i], first);
-                        else if (c == S::CG) put_grad(part + S::P_BQ + gi * S::RG + r, acc[i], first);
+                        for (int p = 0; p < P; ++p) {
+                            F b = O::ld_t(X + 16 * s * S::PC + gi * S::CG + 16 * (ct + p), S::PC, q, l16);
+                            if (casc) b = O::add(b, O::ld_t(A + 16 * s * S::PC + (gi - 1) * S::CG + 16 * (ct + p), S::PC, q, l16));
+                            if (16 * (ct + p) + l16 == S::CG) b = O::ones();
+                            acc[p] = mma(r, b, acc[p]);
+                        }
+                    }
+                    const Rows4 rows = weight_rows4<S>(16 * ft + 4 * q);
+#pragma unroll
+                    for (int p = 0; p < P; ++p) {
+                        const int c = 16 * (ct + p) + l16;
+                        float *pw = part + (c < S::CG ? S::P_WQ + (gi * S::RG + rows.row) * S::CG + c : S::P_BQ + gi * S::RG + rows.row);
+                        const int step = c < S::CG ? S::CG : 1;
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            if (i < rows.n && c <= S::CG) put_grad(pw + i * step, acc[p][i], first);
                     }
                 }
             }
@@ -966,10 +1088,14 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
                 FRESH_LANE;
                 const int u = wv + k * S::WAVES;
                 if (u >= UF) continue;
-                const int ct = u / S::NT, tt = u - ct * S::NT, t = 16 * tt + l16;
+                const int ct = u / S::TU, tu = u - ct * S::TU;
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    if (16 * ct + 4 * q + i < S::CG) O::put(X + t * S::PC + gi * S::CG + 16 * ct + 4 * q + i, df[k][i]);
+                for (int tt = 0; tt < S::TT; ++tt) {
+                    E *xr = X + (16 * (tu * S::TT + tt) + l16) * S::PC + gi * S::CG + 16 * ct + 4 * q;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (16 * ct + 4 * q + i < S::CG) O::put(xr + i, df[k][tt][i]);
+                }
             }
 #pragma unroll
             for (int round = 1; round < S::ROUNDS; ++round) {
@@ -984,7 +1110,7 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
         // ---- X is the gradient of the attention layer's input: out, or through LN_1's adjoint and the skip of Eq. 4 ----
         {
             f32x4 gam1, sg = O::zero(), sb = O::zero();
-            if (LAYER) gam1 = in ? load4(static_cast<const T *>(a.ln1_w) + 4 * l16) : O::zero();
+            if (LAYER) gam1 = load4_if(in, static_cast<const T *>(a.ln1_w), 4 * l16);
 #pragma unroll
             for (int k = 0; k < Rows<S>::PER; ++k) {
                 FRESH_LANE;
@@ -993,7 +1119,7 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
                     const long tok = win.token(t) * S::C + 4 * l16;
                     f32x4 d = in ? O::wide(O::ld(X + t * S::PC + 4 * l16)) : O::zero();
                     if (LAYER) {
-                        const f32x4 f = in ? load4(x + tok) : O::zero(), r = O::wide(O::ld(DX + t * S::PC + 4 * l16));
+                        const f32x4 f = load4_if(in, x, tok), r = O::wide(O::ld(DX + t * S::PC + 4 * l16));
                         float mean, rstd, s1 = 0.f, s2 = 0.f;
                         stats<S>(f, in, a.eps, mean, rstd);
                         f32x4 xh;
@@ -1061,7 +1187,8 @@ hipError_t launch_bwd(const WindowLayerArgs &a, const WindowLayerGrads &gr, int 
 }
 
 // The fp32 layers of 60 channels and 8x8 windows.
-template <int G> using F32Shape = WinShape<float, 60, 6, G, 8, 10, 120, 16>;
+// (one group: a wavefront holds two score-gradient tiles of 64x16, for which 128 registers are too few)
+template <int G> using F32Shape = WinShape<float, 60, 6, G, 8, 10, 120, G == 1 ? 12 : 16>;
 #define GSWA_F32_SHAPES(X) X(F32Shape<1>) X(F32Shape<2>) X(F32Shape<3>) X(F32Shape<6>)
 
 } // namespace
