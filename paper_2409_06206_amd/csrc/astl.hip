@@ -369,7 +369,7 @@ struct Plan {
     size_t reps;                  // bytes of the kGradReplicas copies
     size_t pack;                  // bytes of the MLP's repacked weights at the end of `saved` (fused MLP)
     bool fused_mlp, fused_mlp_bwd;
-    bool window;                  // both passes with one workgroup per window
+    const WindowLayerOps *window; // both passes with one workgroup per window (null: not for this layer)
     Geom g;                       // (filled with `window`)
     bool wide_mlp;                // forward of the MLP half by the streaming kernel for wide layers
 };
@@ -405,14 +405,14 @@ int make_plan(const astl_desc *d, Plan *p)
     // backward: xn | dn | dx1 | max(pre | h | dh, attention scratch) | copies of the gradients
     const size_t hid_b = p->fused_mlp_bwd ? astl_mlp_bwd_ws_bytes(p->T, p->C, p->Hd) : 3 * p->hid;
     p->bwd_ws = 3 * p->act + (p->at_bws > hid_b ? p->at_bws : hid_b) + p->reps;
-    p->window = false;
-    if (d->attn.dtype == GSWA_F32 && !(d->attn.flags & GSWA_FORCE_STAGED)) {
+    p->window = nullptr;
+    if (!(d->attn.flags & GSWA_FORCE_STAGED) && (d->attn.dtype == GSWA_F32 || d->attn.window == 12)) {
         rc = make_geom(&d->attn, &p->g);
         if (rc != GSWA_OK) return rc;
-        p->window = window_layer_supported(p->g, true, p->Hd);
+        p->window = window_layer_ops(p->g, d->attn.dtype == GSWA_F32, p->Hd);
     }
     if (p->window) {
-        const size_t need = align256(window_layer_bwd_ws_bytes(p->g, p->Hd));
+        const size_t need = align256(window_layer_bwd_ws_bytes(*p->window, p->g, true));
         if (need > p->bwd_ws) p->bwd_ws = need;
     }
     return GSWA_OK;
@@ -445,7 +445,7 @@ int forward_window(const astl_desc *d, const Plan &pl, const void *x, const astl
     WindowLayerArgs a = window_args(d, pl, x, p);
     a.y = y;
     a.x1 = saved; a.attn = saved ? saved + pl.act : nullptr;
-    ASTL_HIP(launch_window_layer_fwd(a, d->attn.dtype == GSWA_F32, pl.Hd, st));
+    ASTL_HIP(pl.window->fwd[1](a, st));
     return GSWA_OK;
 }
 
@@ -459,7 +459,7 @@ int backward_window(const astl_desc *d, const Plan &pl, const void *x, const voi
     gr.w_qkv = g->w_qkv; gr.b_qkv = g->b_qkv; gr.w_proj = g->w_proj; gr.b_proj = g->b_proj; gr.table = g->bias_table;
     gr.w_fc1 = g->w_fc1; gr.b_fc1 = g->b_fc1; gr.w_fc2 = g->w_fc2; gr.b_fc2 = g->b_fc2;
     gr.ln1_w = g->ln1_w; gr.ln1_b = g->ln1_b; gr.ln2_w = g->ln2_w; gr.ln2_b = g->ln2_b;
-    ASTL_HIP(launch_window_layer_bwd(a, d->attn.dtype == GSWA_F32, pl.Hd, gr, (d->attn.flags & GSWA_ACCUM_WGRAD) ? 1 : 0, st));
+    ASTL_HIP(pl.window->bwd[1](a, gr, (d->attn.flags & GSWA_ACCUM_WGRAD) ? 1 : 0, st));
     return GSWA_OK;
 }
 

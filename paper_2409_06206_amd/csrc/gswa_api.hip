@@ -144,12 +144,19 @@ struct Sizes {
     size_t reps, tpart;  // bytes of the gradient copies and of the per-window bias-table gradients
     int nreps;           // gradient copies of the staged backward
     bool fused_fwd, fused_bwd;
-    bool window;         // fp32: one workgroup per window, both passes
+    const WindowLayerOps *window; // one workgroup per window, both passes (null: not for this layer)
 };
 
 bool use_fused_fwd(const gswa_desc *d, const Geom &g)
 {
     return d->dtype == GSWA_BF16 && !(d->flags & GSWA_FORCE_STAGED) && g.dq == g.d && fused_fwd_supported(g);
+}
+
+// One workgroup per window (window_layer.h): fp32, and bf16 layers with 12x12 windows.
+const WindowLayerOps *use_window(const gswa_desc *d, const Geom &g)
+{
+    if ((d->flags & GSWA_FORCE_STAGED) || (d->dtype == GSWA_BF16 && g.M != 12)) return nullptr;
+    return window_layer_ops(g, d->dtype == GSWA_F32, 0);
 }
 
 Sizes make_sizes(const gswa_desc *d, const Geom &g)
@@ -182,10 +189,10 @@ Sizes make_sizes(const gswa_desc *d, const Geom &g)
         // the group outputs) in ws, which the caller sizes as fwd_ws + saved
         s.fwd_ws = 0;
     }
-    s.window = !s.fused_fwd && d->dtype == GSWA_F32 && !(d->flags & GSWA_FORCE_STAGED) && window_layer_supported(g, true, 0);
+    s.window = use_window(d, g);
     if (s.window) {
         // (never less than the one-kernel-per-step path asks for: GSWA_FORCE_STAGED changes no size)
-        const size_t need = align256(window_layer_bwd_ws_bytes(g, 0));
+        const size_t need = align256(window_layer_bwd_ws_bytes(*s.window, g, false));
         if (need > s.bwd_ws) s.bwd_ws = need;
     }
     if (s.fused_bwd) {
@@ -405,7 +412,7 @@ int gswa_forward(const gswa_desc *desc, const void *x, const void *w_qkv, const 
         a.g = g;
         a.x = x; a.w_qkv = w_qkv; a.b_qkv = b_qkv; a.w_proj = w_proj; a.b_proj = b_proj; a.table = bias_table;
         a.y = y; a.attn = saved;
-        GSWA_HIP(launch_window_layer_fwd(a, true, 0, st));
+        GSWA_HIP(s.window->fwd[0](a, st));
         return GSWA_OK;
     }
     if (desc->dtype == GSWA_F32)
@@ -477,7 +484,7 @@ int gswa_backward(const gswa_desc *desc, const void *x, const void *dy, const vo
         WindowLayerGrads gr{};
         gr.w_qkv = (float *)dw_qkv; gr.b_qkv = (float *)db_qkv; gr.w_proj = (float *)dw_proj; gr.b_proj = (float *)db_proj;
         gr.table = (float *)dbias_table;
-        GSWA_HIP(launch_window_layer_bwd(a, true, 0, gr, (desc->flags & GSWA_ACCUM_WGRAD) ? 1 : 0, st));
+        GSWA_HIP(s.window->bwd[0](a, gr, (desc->flags & GSWA_ACCUM_WGRAD) ? 1 : 0, st));
         return GSWA_OK;
     }
     if (desc->dtype == GSWA_F32)

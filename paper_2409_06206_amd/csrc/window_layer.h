@@ -29,12 +29,27 @@ struct WindowLayerGrads {
 // Checks a descriptor and derives its geometry (GSWA_OK or an error code).
 int make_geom(const gswa_desc *d, Geom *g);
 
-// hidden == 0 asks for the attention layer alone
-bool window_layer_supported(const Geom &g, bool f32, int hidden);
+// Vectors of parameter gradients a backward launch leaves at most (= its workgroups).
+constexpr int kWindowLayerVectors = 256;
+
+// What a shape brings; index 0: the attention layer alone, 1: the whole layer (hidden = 2 C).
+struct WindowLayerOps {
+    size_t vector[2]; // floats of a workgroup's vector
+    hipError_t (*fwd[2])(const WindowLayerArgs &, hipStream_t);
+    hipError_t (*bwd[2])(const WindowLayerArgs &, const WindowLayerGrads &, int accumulate, hipStream_t);
+};
+// the shapes of each file that instantiates the kernels (null: none fits)
+const WindowLayerOps *window_layer_f32(const Geom &g);
+const WindowLayerOps *window_layer_bf16_w8(const Geom &g);
+const WindowLayerOps *window_layer_bf16_w12h4(const Geom &g);
+const WindowLayerOps *window_layer_bf16_w12h6(const Geom &g);
+
+// The kernels that serve a layer, or null.  hidden == 0 asks for the attention layer alone.
+const WindowLayerOps *window_layer_ops(const Geom &g, bool f32, int hidden);
 // scratch of the backward: the workgroups' vectors
-size_t window_layer_bwd_ws_bytes(const Geom &g, int hidden);
-hipError_t launch_window_layer_fwd(const WindowLayerArgs &a, bool f32, int hidden, hipStream_t s);
-hipError_t launch_window_layer_bwd(const WindowLayerArgs &a, bool f32, int hidden, const WindowLayerGrads &gr,
-                                   int accumulate, hipStream_t s);
+inline size_t window_layer_bwd_ws_bytes(const WindowLayerOps &ops, const Geom &g, bool layer)
+{
+    return (size_t)(g.nW < kWindowLayerVectors ? g.nW : kWindowLayerVectors) * ops.vector[layer] * sizeof(float);
+}
 
 } // namespace gswa
