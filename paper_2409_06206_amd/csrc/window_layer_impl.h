@@ -35,7 +35,7 @@ constexpr float kLog2e = 1.4426950408889634f;
 #define FRESH_LANE                            \
     int fresh_ = (int)threadIdx.x;            \
     asm volatile("" : "+v"(fresh_));          \
-    const int l16 = fresh_ & 15, q = (fresh_ >> 4) & 3
+    [[maybe_unused]] const int l16 = fresh_ & 15, q = (fresh_ >> 4) & 3
 
 // Row pitch (elements): a multiple of four that is not a multiple of eight, so that 16 rows read at the same column
 // fall on different banks.
@@ -56,13 +56,16 @@ template <typename T_, int C_, int HEADS_, int G_, int M_, int DQ_, int HID_, in
     // token tiles that share one reading of the weights: the loads of weights, 16 short pieces of rows each, are
     // what the vector memory pipe of a compute unit spends its time on otherwise
     static constexpr int TT = NT % 3 == 0 ? 3 : 2, TU = NT / TT;
+    static constexpr int TP = NT % 3 == 0 ? 3 : 1, PU = NT / TP; // (products with C outputs: as many units as wavefronts)
     // Rows of C channels that group slices are read from keep every group at a stride of a multiple of four channels
     // (CGP), so that slices are aligned; OC is their first pad column.
     static constexpr int CGP = (CG + 3) & ~3, XW = G * CGP, OC = CG < CGP ? CG : XW;
     static constexpr int KUX = up(XW, 16), CTX = up(OC < XW ? XW : XW + 1, 16);
     static __device__ __forceinline__ int xcol(int c) { return CGP == CG ? c : c / CG * CGP + c % CG; }
     // (a slice's last k-slots and column tiles may run into the next row: numbers that meet zero weights or are dropped)
-    static constexpr int PC = pitch_of(imax(16 * up(C + 1, 16), XW)), PR = pitch_of(RP), PD = pitch_of(RV), PH = pitch_of(16 * up(HID + 1, 16));
+    static constexpr int PC = pitch_of(imax(16 * up(C + 1, 16), XW)), PR = pitch_of(RP + 8), PD = pitch_of(RV), PH = pitch_of(16 * up(HID + 1, 16));
+    // (behind q|k|v a row holds its token's part of the shift mask: as a key, as a query)
+    static constexpr int MK = RP, MQ = RP + 4;
     static constexpr int PF = N + 4; // pitch of a head's matrix of score gradients
     static constexpr int NTB = 2 * M - 1, NTBL = NTB * NTB, TBP = (NTBL + 3) & ~3;
     static_assert(M * M % 16 == 0 && C % 4 == 0 && D <= 16 && DQ <= 16 && C % 16 != 0 && CG % 16 != 0 && HID % 16 != 0, "shape");
@@ -119,11 +122,16 @@ template <> struct Op<float> {
     using F = f32x4;
     static __device__ __forceinline__ F ones() { return f32x4{1.f, 1.f, 1.f, 1.f}; }
     static __device__ __forceinline__ F ld(const float *p) { return *reinterpret_cast<const f32x4 *>(p); }
-    // element (row 4q + i, column l16), i < 4: `p` points at row 0, column 0
+    // element (row 4q + i, column l16), i < 4: `p` points at row 0, column 0; ld_tr: row 15 - 4q - i
     static __device__ __forceinline__ F ld_t(const float *p, int pitch, int q, int l16)
     {
         const float *r = p + 4 * q * pitch + l16;
         return f32x4{r[0], r[pitch], r[2 * pitch], r[3 * pitch]};
+    }
+    static __device__ __forceinline__ F ld_tr(const float *p, int pitch, int q, int l16)
+    {
+        const float *r = p + (12 - 4 * q) * pitch + l16;
+        return f32x4{r[3 * pitch], r[2 * pitch], r[pitch], r[0]};
     }
     static __device__ __forceinline__ F gather(float a, float b, float c, float d) { return f32x4{a, b, c, d}; }
     static __device__ __forceinline__ F from(f32x4 v) { return v; }
@@ -150,6 +158,12 @@ template <> struct Op<bf16_t> {
         const s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(r));
         return __builtin_bit_cast(uint2, v);
     }
+    static __device__ __forceinline__ F ld_tr(const bf16_t *p, int pitch, int q, int l16)
+    {
+        const bf16_t *r = p + (15 - 4 * q - (l16 >> 2)) * pitch + 4 * (l16 & 3);
+        const s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(r));
+        return __builtin_bit_cast(uint2, v);
+    }
     static __device__ __forceinline__ F gather(float a, float b, float c, float d) { return make_uint2(pack_bf16x2(a, b), pack_bf16x2(c, d)); }
     static __device__ __forceinline__ F from(f32x4 v) { return pack_bf16x4(v); }
     static __device__ __forceinline__ f32x4 wide(F v) { return f32x4{bf16_lo(v.x), bf16_hi(v.x), bf16_lo(v.y), bf16_hi(v.y)}; }
@@ -168,6 +182,12 @@ template <> struct Op<bf16_t> {
 };
 
 // One head's slice of a row as an operand: HS channels (a multiple of four, at most 16).
+//
+// Q and K operands (HS <= 12) carry the shift mask with them.  With r, c = "past the wrap in the last window row, column"
+// of a token, [regions of n and m differ] = (r_n|c_n) + (1-2 r_n)(1-c_n) r_m + (1-2 c_n)(1-r_n) c_m
+// - (1-2 r_n)(1-2 c_n) r_m c_m: four more k-slots, (1, r, c, rc) of the key against those coefficients of the query
+// times -100 log2(e).  In bf16 they take the slots 12 .. 15 that no head uses, at no cost; in fp32 they are one more
+// product, taken in masked windows only.
 template <typename E, int HS> struct HeadOp;
 template <int HS> struct HeadOp<float, HS> { // product i takes channels 4i .. 4i+3: HS / 4 products instead of four
     float v[HS / 4];
@@ -178,17 +198,41 @@ template <int HS> struct HeadOp<float, HS> { // product i takes channels 4i .. 4
     }
     __device__ __forceinline__ void mask(int) {}
 };
+template <int HS> __device__ __forceinline__ f32x4 mma(const HeadOp<float, HS> &a, const HeadOp<float, HS> &b, f32x4 c)
+{
+#pragma unroll
+    for (int i = 0; i < HS / 4; ++i) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[i], b.v[i], c, 0, 0, 0);
+    return c;
+}
 template <int HS> struct HeadOp<bf16_t, HS> { // (slots beyond the head: any number on one side, zeros on the masked one)
     uint2 v;
     __device__ __forceinline__ void load(const bf16_t *p, int q) { v = *reinterpret_cast<const uint2 *>(p + (4 * q < HS ? 4 * q : 0)); }
     __device__ __forceinline__ void mask(int q) { v = make_uint2(4 * q < HS ? v.x : 0u, 4 * q < HS ? v.y : 0u); }
 };
 template <int HS> __device__ __forceinline__ f32x4 mma(const HeadOp<bf16_t, HS> &a, const HeadOp<bf16_t, HS> &b, f32x4 c) { return mma16(a.v, b.v, c); }
-template <int HS> __device__ __forceinline__ f32x4 mma(const HeadOp<float, HS> &a, const HeadOp<float, HS> &b, f32x4 c)
+// q or k of a head: `row` is the token's row, `col` the head's column, `mcol` the column of the mask's part
+template <class S> struct QkOp : HeadOp<typename S::E, S::HSQ> {
+    static constexpr bool SLOTS = sizeof(typename S::E) == 2;
+    static_assert(!SLOTS || S::HSQ <= 12, "slots 12 .. 15 are the mask's");
+    __device__ __forceinline__ void load(const typename S::E *row, int col, int mcol, int q)
+    {
+        if constexpr (SLOTS) this->v = *reinterpret_cast<const uint2 *>(row + (q == 3 ? mcol : col + (4 * q < S::HSQ ? 4 * q : 0)));
+        else HeadOp<typename S::E, S::HSQ>::load(row + col, q);
+    }
+    __device__ __forceinline__ void mask(int q)
+    {
+        if constexpr (SLOTS) { // (which of the four slot groups count, as bits)
+            const uint32_t m = 0u - (((8u | ((1u << S::HSQ / 4) - 1u)) >> q) & 1u);
+            this->v = make_uint2(this->v.x & m, this->v.y & m);
+        }
+    }
+};
+// fp32: the mask's product on top of the scores of rows `rows` (their parts at column ra) against the lane's token `row`
+template <class S> __device__ __forceinline__ f32x4 add_mask(const typename S::E *rows, int ra, const typename S::E *row, int rb, f32x4 s, int l16, int q)
 {
-#pragma unroll
-    for (int i = 0; i < HS / 4; ++i) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[i], b.v[i], c, 0, 0, 0);
-    return c;
+    if constexpr (sizeof(typename S::E) == 4)
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(rows[l16 * S::PR + ra + q], row[rb + q], s, 0, 0, 0);
+    return s;
 }
 
 // sum over the 16 lanes of a row, left in all of them
@@ -211,9 +255,9 @@ template <class S> struct Window {
     __device__ __forceinline__ Window(const Geom &g, int w)
     {
         const int per = g.nwi * g.nwj;
-        b = w / per;
+        b = __builtin_amdgcn_readfirstlane(w / per); // (uniform, but divided on the vector ALU)
         const int r = w - b * per;
-        wi = r / g.nwj;
+        wi = __builtin_amdgcn_readfirstlane(r / g.nwj);
         wj = r - wi * g.nwj;
         H = g.H; W = g.W; s = g.shift;
         last_r = s > 0 && wi == g.nwi - 1;
@@ -240,6 +284,7 @@ template <class S> __device__ __forceinline__ int key_offset(int n) { const int 
 template <class S> __device__ __forceinline__ int key_offset4(int tile, int q)
 {
     if (S::M == 8) return 2 * S::NTB * tile + S::NTB * (q >> 1) + 4 * (q & 1);
+    if (S::M == 12) return 4 * S::NTB * (tile / 3) + key_offset<S>(16 * (tile % 3) + 4 * q); // (three tiles are four window rows)
     return key_offset<S>(16 * tile + 4 * q);
 }
 
@@ -396,6 +441,9 @@ template <class S> struct WeightsX {
 };
 __device__ __forceinline__ void loads_issued() { __builtin_amdgcn_sched_barrier(0); }
 
+// Scores with a query per column are taken of the keys of a tile in descending order (row 4q + i is key 15 - 4q - i), so
+// that a lane's four bias entries ascend in memory and enter the product as they are read.
+
 // The row phases: 16 lanes hold a token, four channels each; a wave takes four tokens at a time.
 template <class S> struct Rows {
     static constexpr int UNITS = S::N / 4, PER = up(UNITS, S::WAVES);
@@ -440,6 +488,18 @@ template <class S> __device__ __forceinline__ f32x4 get_row(const typename S::E 
     return v;
 }
 
+// the shift mask's parts of a token, behind its q|k|v
+template <class S> __device__ __forceinline__ void put_mask(const Window<S> &win, typename S::E *R)
+{
+    using O = Op<typename S::E>;
+    for (int t = threadIdx.x; t < S::N; t += S::NTH) {
+        const int reg = win.region(t);
+        const float r = reg & 1 ? 1.f : 0.f, c = reg & 2 ? 1.f : 0.f, m = -100.f * kLog2e;
+        O::st(R + t * S::PR + S::MK, f32x4{1.f, r, c, r * c});
+        O::st(R + t * S::PR + S::MQ, f32x4{m * (r + c - r * c), m * (1.f - 2.f * r) * (1.f - c), m * (1.f - 2.f * c) * (1.f - r), -m * (1.f - 2.f * r) * (1.f - 2.f * c)});
+    }
+}
+
 // mean and 1 / sqrt(var + eps) of a token; lanes beyond the channels hold zeros
 template <class S> __device__ __forceinline__ void stats(f32x4 f, bool in, float eps, float &mean, float &rstd)
 {
@@ -452,13 +512,22 @@ template <class S> __device__ __forceinline__ void stats(f32x4 f, bool in, float
 
 template <class S> __device__ __forceinline__ void load_table(float *tb, const typename S::T *table)
 {
-    for (int e = threadIdx.x; e < S::NTBL * S::HEADS; e += S::NTH) {
-        const int i = e / S::HEADS, h = e - i * S::HEADS;
-        tb[h * S::TBP + i] = to_f32(table[e]) * kLog2e;
+    constexpr int PER = up(S::NTBL * S::HEADS, S::NTH);
+    typename S::T v[PER];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int e = threadIdx.x + k * S::NTH;
+        v[k] = table[e < S::NTBL * S::HEADS ? e : 0];
+    }
+    loads_issued();
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int e = threadIdx.x + k * S::NTH, i = e / S::HEADS, h = e - i * S::HEADS;
+        if (e < S::NTBL * S::HEADS) tb[h * S::TBP + i] = to_f32(v[k]) * kLog2e;
     }
 }
 
-// q|k|v of group gi from X (+ the output of the group before it, A) into the padded rows R
+// q|k|v of group gi from X (+ the output of the group before it, A) into the padded rows R; q times log2(e) / sqrt(d)
 template <class S> __device__ __forceinline__ void qkv_unit(const WindowLayerArgs &a, int gi, int ft, int tu, const typename S::E *X,
                                                             const typename S::E *A, typename S::E *R)
 {
@@ -475,6 +544,8 @@ template <class S> __device__ __forceinline__ void qkv_unit(const WindowLayerArg
     for (int i = 0; i < 4; ++i) bf[i] = to_f32(bias[i < rows.n ? rows.row + i : 0]);
     loads_issued();
     const bool casc = gi > 0 && a.g.cascade;
+    const float pad = 16 * ft + 4 * q >= 2 * S::RQ ? 1.f : 0.f; // (v is one in the first pad feature: see window_layer_fwd_kernel)
+    const float sc = 16 * ft + 4 * q < S::RQ ? kLog2e / sqrtf((float)S::DQ) : 1.f; // (scores come in base 2)
 #pragma unroll
     for (int tt = 0; tt < S::TT; ++tt) {
         const int t = 16 * (tu * S::TT + tt) + l16;
@@ -489,7 +560,7 @@ template <class S> __device__ __forceinline__ void qkv_unit(const WindowLayerArg
 #pragma unroll
         for (int s = 0; s < S::KUG; ++s) acc = mma(wf.op(s, q), f[s], acc);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) acc[i] = i < rows.n ? acc[i] + bf[i] : 0.f;
+        for (int i = 0; i < 4; ++i) acc[i] = i < rows.n ? (acc[i] + bf[i]) * sc : (i == rows.n ? pad : 0.f);
         if (16 * ft + 4 * q < S::RP) O::st(R + t * S::PR + 16 * ft + 4 * q, acc);
     }
 }
@@ -500,48 +571,51 @@ __global__ __launch_bounds__(S::NTH) void window_layer_fwd_kernel(WindowLayerArg
     using E = typename S::E;
     using T = typename S::T;
     using O = Op<E>;
+    using F = typename O::F;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     E *X = reinterpret_cast<E *>(lds + S::F_X), *A = reinterpret_cast<E *>(lds + S::F_A), *R = reinterpret_cast<E *>(lds + S::F_R);
     float *tb = reinterpret_cast<float *>(lds + S::fwd_tb(LAYER));
-    const int l16 = threadIdx.x & 15;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const T *x = static_cast<const T *>(a.x);
-    const float scale = kLog2e / sqrtf((float)S::DQ), maskv = -100.f * kLog2e;
-    load_table<S>(tb, static_cast<const T *>(a.table));
 
     for (int w = blockIdx.x; w < a.g.nW; w += gridDim.x) {
         const Window<S> win(a.g, w);
-        const bool masked = win.last_r || win.last_c;
+        [[maybe_unused]] const bool masked = win.last_r || win.last_c;
         // ---- the window's rows (through LN_1) ----
         {
+            FRESH_LANE;
             const bool in = 4 * l16 < S::C;
             f32x4 gam, bet;
             if (LAYER) {
                 gam = load4_if(in, static_cast<const T *>(a.ln1_w), 4 * l16);
                 bet = load4_if(in, static_cast<const T *>(a.ln1_b), 4 * l16);
             }
-            f32x4 f[Rows<S>::PER];
+            typename O::F raw[Rows<S>::PER];
 #pragma unroll
             for (int k = 0; k < Rows<S>::PER; ++k) {
                 FRESH_LANE;
                 const int t = 4 * (wv + k * S::WAVES) + q;
-                f[k] = load4_if(in && t < S::N, x, win.token(t < S::N ? t : 0) * S::C + 4 * l16);
+                raw[k] = O::ld(x + win.token(t < S::N ? t : 0) * S::C + (4 * l16 < S::C ? 4 * l16 : 0));
             }
+            loads_issued();
+            if (w == (int)blockIdx.x) load_table<S>(tb, static_cast<const T *>(a.table));
 #pragma unroll
             for (int k = 0; k < Rows<S>::PER; ++k) {
                 FRESH_LANE;
                 const int t = 4 * (wv + k * S::WAVES) + q;
+                f32x4 f = O::wide(O::pick(in, raw[k]));
                 if (LAYER) {
                     float mean, rstd;
-                    stats<S>(f[k], in, a.eps, mean, rstd);
+                    stats<S>(f, in, a.eps, mean, rstd);
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) f[k][i] = in ? (f[k][i] - mean) * rstd * gam[i] + bet[i] : 0.f;
+                    for (int i = 0; i < 4; ++i) f[i] = in ? (f[i] - mean) * rstd * gam[i] + bet[i] : 0.f;
                 }
-                if (t < S::N) put_row<S>(X + t * S::PC, l16, f[k]);
+                if (t < S::N) put_row<S>(X + t * S::PC, l16, f);
             }
         }
         // (columns of the group outputs that no head has written yet meet zero weights, but must be numbers)
         for (int e = 4 * threadIdx.x; e < S::N * S::PC; e += 4 * S::NTH) O::st(A + e, zero4());
+        put_mask<S>(win, R);
         __syncthreads();
 #pragma unroll 1
         for (int gi = 0; gi < S::G; ++gi) {
@@ -553,41 +627,37 @@ __global__ __launch_bounds__(S::NTH) void window_layer_fwd_kernel(WindowLayerArg
                 FRESH_LANE;
                 const int hl = u / S::NT, nt = u - hl * S::NT, tq = 16 * nt + l16;
                 const float *tbh = tb + (gi * S::HG + hl) * S::TBP;
-                HeadOp<E, S::HSQ> qf;
-                qf.load(R + tq * S::PR + hl * S::HSQ, q);
+                QkOp<S> qf;
+                qf.load(R + tq * S::PR, hl * S::HSQ, S::MQ, q);
                 qf.mask(q);
-                const int oq = key_offset<S>(tq) + (S::M - 1) * (S::NTB + 1), rq = win.region(tq);
+                const int oq = key_offset<S>(tq) + (S::M - 1) * (S::NTB + 1);
                 f32x4 st[S::NT];
                 float mx = -INFINITY;
 #pragma unroll
                 for (int kt = 0; kt < S::NT; ++kt) {
-                    HeadOp<E, S::HSQ> kf;
-                    kf.load(R + (16 * kt + l16) * S::PR + S::RQ + hl * S::HSQ, q);
-                    f32x4 s = mma(kf, qf, zero4());
-                    const float *bias = tbh + oq - key_offset4<S>(kt, q);
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) s[i] = fmaf(s[i], scale, bias[-i]);
-                    st[kt] = s;
+                    QkOp<S> kf;
+                    kf.load(R + (16 * kt + 15 - l16) * S::PR, S::RQ + hl * S::HSQ, S::MK, q);
+                    const float *bias = tbh + oq - key_offset4<S>(kt, 3 - q) - 3;
+                    st[kt] = mma(kf, qf, f32x4{bias[0], bias[1], bias[2], bias[3]});
                 }
-                if (masked) {
+                if (sizeof(E) == 4 && masked) {
 #pragma unroll
-                    for (int kt = 0; kt < S::NT; ++kt)
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) st[kt][i] += win.region(16 * kt + 4 * q + i) != rq ? maskv : 0.f;
+                    for (int kt = 0; kt < S::NT; ++kt) st[kt] = add_mask<S>(R + 16 * kt * S::PR, S::MK, R + tq * S::PR, S::MQ, st[kt], 15 - l16, q);
                 }
 #pragma unroll
                 for (int kt = 0; kt < S::NT; ++kt) mx = fmaxf(mx, fmaxf(fmaxf(st[kt][0], st[kt][1]), fmaxf(st[kt][2], st[kt][3])));
                 mx = qgroup_max(mx);
-                float sum = 0.f;
 #pragma unroll
                 for (int kt = 0; kt < S::NT; ++kt)
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) { st[kt][i] = __builtin_amdgcn_exp2f(st[kt][i] - mx); sum += st[kt][i]; }
-                const float inv = 1.f / qgroup_sum(sum);
+                    for (int i = 0; i < 4; ++i) st[kt][i] = __builtin_amdgcn_exp2f(st[kt][i] - mx);
                 f32x4 o = zero4();
 #pragma unroll
                 for (int kt = 0; kt < S::NT; ++kt)
-                    o = mma(O::ld_t(R + 16 * kt * S::PR + 2 * S::RQ + hl * S::HSV, S::PR, q, l16), O::from(st[kt]), o);
+                    o = mma(O::ld_tr(R + 16 * kt * S::PR + 2 * S::RQ + hl * S::HSV, S::PR, q, l16), O::from(st[kt]), o);
+                // (v is one in feature D, so row D of the product is the softmax's denominator)
+                static_assert(S::D % 4 != 0, "a pad feature");
+                const float inv = 1.f / qgroup_sum(q == S::D / 4 ? o[S::D % 4] : 0.f);
                 E *ar = A + tq * S::PC + gi * S::CGP + hl * S::D;
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
@@ -605,28 +675,35 @@ __global__ __launch_bounds__(S::NTH) void window_layer_fwd_kernel(WindowLayerArg
             }
         }
 #pragma unroll 1
-        for (int u = wv; u < S::CTC * S::NT; u += S::WAVES) {
+        for (int u = wv; u < S::CTC * S::PU; u += S::WAVES) {
             FRESH_LANE;
-            const int ct = u / S::NT, tt = u - ct * S::NT, t = 16 * tt + l16, c = 16 * ct + 4 * q;
-            const long tok = win.token(t);
+            const int ct = u / S::PU, tu = u - ct * S::PU, c = 16 * ct + 4 * q;
+            const bool in = c < S::C;
             WeightsX<S> wf;
             wf.load(static_cast<const T *>(a.w_proj) + (16 * ct + l16 < S::C ? 16 * ct + l16 : 0) * S::C, q);
-            const bool in = c < S::C;
             const f32x4 b = load4(static_cast<const T *>(a.b_proj) + (in ? c : 0));
-            f32x4 skip = zero4();
-            if (LAYER) skip = load4(x + tok * S::C + (in ? c : 0));
-            loads_issued();
-            f32x4 acc = zero4();
+            F skip[S::TP];
+            if (LAYER) {
 #pragma unroll
-            for (int s = 0; s < S::KUX; ++s) acc = mma(wf.op(s, q), O::ld(A + t * S::PC + 16 * s + 4 * q), acc);
-            acc += b;
-            if (LAYER) acc += skip;
-            if (in) {
-                if (LAYER) {
-                    O::st(X + t * S::PC + c, acc);
-                    if (a.x1) store4(static_cast<T *>(a.x1) + tok * S::C + c, acc);
-                } else {
-                    store4(static_cast<T *>(a.y) + tok * S::C + c, acc);
+                for (int tt = 0; tt < S::TP; ++tt) skip[tt] = O::ld(x + win.token(16 * (tu * S::TP + tt) + l16) * S::C + (in ? c : 0));
+            }
+            loads_issued();
+#pragma unroll
+            for (int tt = 0; tt < S::TP; ++tt) {
+                const int t = 16 * (tu * S::TP + tt) + l16;
+                f32x4 acc = zero4();
+#pragma unroll
+                for (int s = 0; s < S::KUX; ++s) acc = mma(wf.op(s, q), O::ld(A + t * S::PC + 16 * s + 4 * q), acc);
+                acc += b;
+                if (LAYER) acc += O::wide(skip[tt]);
+                if (in) {
+                    const long at = win.token(t) * S::C + c;
+                    if (LAYER) {
+                        O::st(X + t * S::PC + c, acc);
+                        if (a.x1) store4(static_cast<T *>(a.x1) + at, acc);
+                    } else {
+                        store4(static_cast<T *>(a.y) + at, acc);
+                    }
                 }
             }
         }
@@ -634,6 +711,7 @@ __global__ __launch_bounds__(S::NTH) void window_layer_fwd_kernel(WindowLayerArg
             __syncthreads();
             // ---- LN_2 (over the group outputs), the MLP and its skip (Eq. 5) ----
             {
+                FRESH_LANE;
                 const bool in = 4 * l16 < S::C;
                 const f32x4 gam = load4_if(in, static_cast<const T *>(a.ln2_w), 4 * l16);
                 const f32x4 bet = load4_if(in, static_cast<const T *>(a.ln2_b), 4 * l16);
@@ -674,19 +752,23 @@ __global__ __launch_bounds__(S::NTH) void window_layer_fwd_kernel(WindowLayerArg
             }
             __syncthreads();
 #pragma unroll 1
-            for (int u = wv; u < S::CTC * S::NT; u += S::WAVES) {
+            for (int u = wv; u < S::CTC * S::PU; u += S::WAVES) {
                 FRESH_LANE;
-                const int ct = u / S::NT, tt = u - ct * S::NT, t = 16 * tt + l16, c = 16 * ct + 4 * q;
+                const int ct = u / S::PU, tu = u - ct * S::PU, c = 16 * ct + 4 * q;
+                const bool in = c < S::C;
                 WeightsN<E, S::HID> wf;
                 wf.load(static_cast<const T *>(a.w_fc2) + (16 * ct + l16 < S::C ? 16 * ct + l16 : 0) * S::HID, q);
-                const bool in = c < S::C;
                 const f32x4 b = load4(static_cast<const T *>(a.b_fc2) + (in ? c : 0));
                 loads_issued();
-                f32x4 acc = zero4();
 #pragma unroll
-                for (int s = 0; s < S::HFT; ++s) acc = mma(wf.op(s, q), O::ld(R + t * S::PH + 16 * s + 4 * q), acc);
-                acc += b + O::wide(O::ld(X + t * S::PC + c));
-                if (in) store4(static_cast<T *>(a.y) + win.token(t) * S::C + c, acc);
+                for (int tt = 0; tt < S::TP; ++tt) {
+                    const int t = 16 * (tu * S::TP + tt) + l16;
+                    f32x4 acc = zero4();
+#pragma unroll
+                    for (int s = 0; s < S::HFT; ++s) acc = mma(wf.op(s, q), O::ld(R + t * S::PH + 16 * s + 4 * q), acc);
+                    acc += b + O::wide(O::ld(X + t * S::PC + c));
+                    if (in) store4(static_cast<T *>(a.y) + win.token(t) * S::C + c, acc);
+                }
             }
         }
         if (w + (int)gridDim.x < a.g.nW) __syncthreads(); // (the next window's rows go where this one's are read)
@@ -718,16 +800,13 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
     E *R = reinterpret_cast<E *>(lds + S::B_R), *DO = reinterpret_cast<E *>(lds + S::B_DO), *FO = reinterpret_cast<E *>(lds + S::B_FO);
     E *Hh = reinterpret_cast<E *>(lds + S::B_H), *DP = reinterpret_cast<E *>(lds + S::B_H + S::SZ_H);
     float *tb = reinterpret_cast<float *>(lds + S::bwd_tb(LAYER));
-    float *lse = tb + S::HEADS * S::TBP, *delta = lse + S::HG * S::N;
+    float *lse = tb + S::HEADS * S::TBP, *delta = lse + S::HG * S::N; // (delta: negative)
     float *red = lse;  // [WAVES][2][CP]
     constexpr int CP = 16 * up(S::C, 16);
-    const int l16 = threadIdx.x & 15, q = (threadIdx.x >> 4) & 3;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const T *x = static_cast<const T *>(a.x);
-    const float qscale = 1.f / sqrtf((float)S::DQ), scale = kLog2e * qscale, maskv = -100.f * kLog2e;
+    const float qscale = 1.f / sqrtf((float)S::DQ);
     float *part = a.part + (long)blockIdx.x * S::stride(LAYER);
-    const bool in = 4 * l16 < S::C;
-    load_table<S>(tb, static_cast<const T *>(a.table));
     if (S::stride(LAYER) > (LAYER ? S::P_ALL : S::P_ATTN) && threadIdx.x < 4u) {
         const int e = (LAYER ? S::P_ALL : S::P_ATTN) + threadIdx.x;
         if (e < S::stride(LAYER)) part[e] = 0.f;
@@ -735,6 +814,7 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
 
     // gamma / beta sums over the tokens of a row phase: the four tokens of a wave here, the waves by finish_row_sums
     auto leave_row_sums = [&](f32x4 sg, f32x4 sb) {
+        FRESH_LANE;
 #pragma unroll
         for (int i = 0; i < 4; ++i) { sg[i] = qgroup_sum(sg[i]); sb[i] = qgroup_sum(sb[i]); }
         if (q == 0) {
@@ -755,22 +835,35 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
 
     for (int w = blockIdx.x; w < a.g.nW; w += gridDim.x) {
         const Window<S> win(a.g, w);
-        const bool masked = win.last_r || win.last_c, first = w == (int)blockIdx.x;
+        const bool first = w == (int)blockIdx.x;
+        [[maybe_unused]] const bool masked = win.last_r || win.last_c;
         const f32x4 one_pad = {1.f, 0.f, 0.f, 0.f};
         if (!first) __syncthreads();
         if (LAYER) {
             // ---- Eq. 5 backwards.  A: LN_2(x1), DX: dy ----
             {
+                FRESH_LANE;
+                const bool in = 4 * l16 < S::C;
                 const f32x4 gam = load4_if(in, static_cast<const T *>(a.ln2_w), 4 * l16);
                 const f32x4 bet = load4_if(in, static_cast<const T *>(a.ln2_b), 4 * l16);
+                F rx[Rows<S>::PER], rd[Rows<S>::PER];
+#pragma unroll
+                for (int k = 0; k < Rows<S>::PER; ++k) {
+                    FRESH_LANE;
+                    const int t = 4 * (wv + k * S::WAVES) + q;
+                    const long tok = win.token(t < S::N ? t : 0) * S::C + (4 * l16 < S::C ? 4 * l16 : 0);
+                    rx[k] = O::ld(static_cast<const T *>(a.x1) + tok);
+                    rd[k] = O::ld(static_cast<const T *>(a.dy) + tok);
+                }
+                loads_issued();
+                if (first) load_table<S>(tb, static_cast<const T *>(a.table));
 #pragma unroll
                 for (int k = 0; k < Rows<S>::PER; ++k) {
                     FRESH_LANE;
                     const int t = 4 * (wv + k * S::WAVES) + q;
                     if (t < S::N) {
-                        const long tok = win.token(t) * S::C + 4 * l16;
-                        f32x4 f = load4_if(in, static_cast<const T *>(a.x1), tok);
-                        const f32x4 d = load4_if(in, static_cast<const T *>(a.dy), tok);
+                        f32x4 f = O::wide(O::pick(in, rx[k]));
+                        const f32x4 d = O::wide(O::pick(in, rd[k]));
                         float mean, rstd;
                         stats<S>(f, in, a.eps, mean, rstd);
 #pragma unroll
@@ -866,24 +959,38 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
         }
         // ---- rows: with the whole layer LN_2's adjoint and the skip of Eq. 5 (DX: dx1), LN_1(x) (X); A: group outputs ----
         {
+            FRESH_LANE;
+            const bool in = 4 * l16 < S::C;
             f32x4 gam1, bet1, gam2, sg = zero4(), sb = zero4();
             if (LAYER) {
                 gam1 = load4_if(in, static_cast<const T *>(a.ln1_w), 4 * l16);
                 bet1 = load4_if(in, static_cast<const T *>(a.ln1_b), 4 * l16);
                 gam2 = load4_if(in, static_cast<const T *>(a.ln2_w), 4 * l16);
             }
+            F rx[Rows<S>::PER], ra[Rows<S>::PER], ru[Rows<S>::PER]; // x, group outputs, and x1 or dy
+#pragma unroll
+            for (int k = 0; k < Rows<S>::PER; ++k) {
+                FRESH_LANE;
+                const int t = 4 * (wv + k * S::WAVES) + q;
+                const long tok = win.token(t < S::N ? t : 0) * S::C + (4 * l16 < S::C ? 4 * l16 : 0);
+                rx[k] = O::ld(x + tok);
+                ra[k] = O::ld(static_cast<const T *>(a.attn) + tok);
+                ru[k] = O::ld(static_cast<const T *>(LAYER ? a.x1 : a.dy) + tok);
+            }
+            loads_issued();
+            if (!LAYER && first) load_table<S>(tb, static_cast<const T *>(a.table));
 #pragma unroll
             for (int k = 0; k < Rows<S>::PER; ++k) {
                 FRESH_LANE;
                 const int t = 4 * (wv + k * S::WAVES) + q;
                 if (t < S::N) {
                     const long tok = win.token(t) * S::C + 4 * l16;
-                    f32x4 f = load4_if(in, x, tok);
-                    f32x4 at = load4_if(in, static_cast<const T *>(a.attn), tok);
+                    f32x4 f = O::wide(O::pick(in, rx[k]));
+                    const f32x4 at = O::wide(O::pick(in, ra[k]));
                     E *xr = X + t * S::PC + 4 * l16, *dr = DX + t * S::PC + 4 * l16;
                     float mean, rstd;
                     if (LAYER) {
-                        const f32x4 u = load4_if(in, static_cast<const T *>(a.x1), tok);
+                        const f32x4 u = O::wide(O::pick(in, ru[k]));
                         stats<S>(u, in, a.eps, mean, rstd);
                         f32x4 d = O::wide(O::ld(xr)), xh;
                         float s1 = 0.f, s2 = 0.f;
@@ -908,13 +1015,14 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
 #pragma unroll
                         for (int i = 0; i < 4; ++i) f[i] = in ? (f[i] - mean) * rstd * gam1[i] + bet1[i] : 0.f;
                     } else {
-                        O::st(dr, load4_if(in, static_cast<const T *>(a.dy), tok));
+                        O::st(dr, O::wide(O::pick(in, ru[k])));
                     }
                     put_row<S>(X + t * S::PC, l16, f);
                     put_row<S>(A + t * S::PC, l16, at);
                 }
             }
             if (LAYER) leave_row_sums(sg, sb);
+            put_mask<S>(win, R);
         }
         __syncthreads();
         if (LAYER) finish_row_sums(S::P_G2, S::P_E2, first);
@@ -989,33 +1097,28 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
                 if (u >= UA) continue;
                 const int hl = u / S::NT, nt = u - hl * S::NT, tq = 16 * nt + l16;
                 const float *tbh = tb + (gi * S::HG + hl) * S::TBP;
-                HeadOp<E, S::HSQ> qf;
+                QkOp<S> qf;
                 HeadOp<E, S::HSV> of;
-                qf.load(R + tq * S::PR + hl * S::HSQ, q);
+                qf.load(R + tq * S::PR, hl * S::HSQ, S::MQ, q);
                 of.load(DO + tq * S::PD + hl * S::HSV, q);
                 qf.mask(q);
                 of.mask(q);
-                const int oq = key_offset<S>(tq) + (S::M - 1) * (S::NTB + 1), rq = win.region(tq);
+                const int oq = key_offset<S>(tq) + (S::M - 1) * (S::NTB + 1);
                 f32x4 st[S::NT], dp[S::NT];
                 float mx = -INFINITY;
 #pragma unroll
                 for (int kt = 0; kt < S::NT; ++kt) {
-                    HeadOp<E, S::HSQ> kf;
+                    QkOp<S> kf;
                     HeadOp<E, S::HSV> vf;
-                    kf.load(R + (16 * kt + l16) * S::PR + S::RQ + hl * S::HSQ, q);
-                    vf.load(R + (16 * kt + l16) * S::PR + 2 * S::RQ + hl * S::HSV, q);
-                    f32x4 s = mma(kf, qf, zero4());
+                    kf.load(R + (16 * kt + 15 - l16) * S::PR, S::RQ + hl * S::HSQ, S::MK, q);
+                    vf.load(R + (16 * kt + 15 - l16) * S::PR + 2 * S::RQ + hl * S::HSV, q);
+                    const float *bias = tbh + oq - key_offset4<S>(kt, 3 - q) - 3;
+                    st[kt] = mma(kf, qf, f32x4{bias[0], bias[1], bias[2], bias[3]});
                     dp[kt] = mma(vf, of, zero4());
-                    const float *bias = tbh + oq - key_offset4<S>(kt, q);
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) s[i] = fmaf(s[i], scale, bias[-i]);
-                    st[kt] = s;
                 }
-                if (masked) {
+                if (sizeof(E) == 4 && masked) {
 #pragma unroll
-                    for (int kt = 0; kt < S::NT; ++kt)
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) st[kt][i] += win.region(16 * kt + 4 * q + i) != rq ? maskv : 0.f;
+                    for (int kt = 0; kt < S::NT; ++kt) st[kt] = add_mask<S>(R + 16 * kt * S::PR, S::MK, R + tq * S::PR, S::MQ, st[kt], 15 - l16, q);
                 }
 #pragma unroll
                 for (int kt = 0; kt < S::NT; ++kt) mx = fmaxf(mx, fmaxf(fmaxf(st[kt][0], st[kt][1]), fmaxf(st[kt][2], st[kt][3])));
@@ -1034,15 +1137,16 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
                 dl = qgroup_sum(dl) * inv;
                 if (q == 0) {
                     lse[hl * S::N + tq] = mx + __log2f(sum);
-                    delta[hl * S::N + tq] = dl;
+                    delta[hl * S::N + tq] = -dl;
                 }
 #pragma unroll
                 for (int kt = 0; kt < S::NT; ++kt) {
                     f32x4 ds;
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) ds[i] = st[kt][i] * inv * (dp[kt][i] - dl);
-                    dq[k] = mma(O::ld_t(R + 16 * kt * S::PR + S::RQ + hl * S::HSQ, S::PR, q, l16), O::from(ds), dq[k]);
+                    for (int i = 0; i < 4; ++i) ds[i] = st[kt][i] * (dp[kt][i] - dl);
+                    dq[k] = mma(O::ld_tr(R + 16 * kt * S::PR + S::RQ + hl * S::HSQ, S::PR, q, l16), O::from(ds), dq[k]);
                 }
+                dq[k] *= inv * qscale;
             }
             __syncthreads();
             // The bias-table gradient of a head.  A lane owns the offset (dr, dc), 0 <= dr, dc < M, of a query from its key,
@@ -1107,34 +1211,29 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
                 const int kt = u - slot * S::NT, tk = 16 * kt + l16;
                 E *fo = FO + (slot * S::N + tk) * S::PF;
                 const float *tbh = tb + (gi * S::HG + hl) * S::TBP;
-                HeadOp<E, S::HSQ> kf;
+                QkOp<S> kf;
                 HeadOp<E, S::HSV> vf;
-                kf.load(R + tk * S::PR + S::RQ + hl * S::HSQ, q);
+                kf.load(R + tk * S::PR, S::RQ + hl * S::HSQ, S::MK, q);
                 vf.load(R + tk * S::PR + 2 * S::RQ + hl * S::HSV, q);
                 kf.mask(q);
                 vf.mask(q);
-                const int ok = (S::M - 1) * (S::NTB + 1) - key_offset<S>(tk), rk = win.region(tk);
+                const int ok = (S::M - 1) * (S::NTB + 1) - key_offset<S>(tk);
 #pragma unroll
                 for (int nt = 0; nt < S::NT; ++nt) {
-                    HeadOp<E, S::HSQ> qf;
+                    QkOp<S> qf;
                     HeadOp<E, S::HSV> of;
-                    qf.load(R + (16 * nt + l16) * S::PR + hl * S::HSQ, q);
+                    qf.load(R + (16 * nt + l16) * S::PR, hl * S::HSQ, S::MQ, q);
                     of.load(DO + (16 * nt + l16) * S::PD + hl * S::HSV, q);
-                    f32x4 s = mma(qf, kf, zero4()), dp = mma(of, vf, zero4());
                     const f32x4 ls = *reinterpret_cast<const f32x4 *>(lse + hl * S::N + 16 * nt + 4 * q);
                     const f32x4 dl = *reinterpret_cast<const f32x4 *>(delta + hl * S::N + 16 * nt + 4 * q);
-                    f32x4 p, d;
                     const float *bias = tbh + ok + key_offset4<S>(nt, q);
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) p[i] = fmaf(s[i], scale, bias[i]) - ls[i];
-                    if (masked) {
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) p[i] += win.region(16 * nt + 4 * q + i) != rk ? maskv : 0.f;
-                    }
+                    f32x4 p = mma(qf, kf, f32x4{bias[0], bias[1], bias[2], bias[3]}), d;
+                    const f32x4 dp = mma(of, vf, dl); // dP - delta
+                    if (sizeof(E) == 4 && masked) p = add_mask<S>(R + 16 * nt * S::PR, S::MQ, R + tk * S::PR, S::MK, p, l16, q);
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        p[i] = __builtin_amdgcn_exp2f(p[i]);
-                        d[i] = p[i] * (dp[i] - dl[i]);
+                        p[i] = __builtin_amdgcn_exp2f(p[i] - ls[i]);
+                        d[i] = p[i] * dp[i];
                     }
                     ds[j][nt] = O::from(d);
                     if (DIRECT) *reinterpret_cast<F *>(fo + 16 * nt + 4 * q) = ds[j][nt]; // [key][query]: four queries of a key
@@ -1167,7 +1266,7 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
                 FRESH_LANE;
                 const int u = wv + k * S::WAVES, hl = u / S::NT, tt = u - hl * S::NT, t = 16 * tt + l16;
                 if (u >= UA) continue;
-                if (4 * q < S::HSQ) O::st(R + t * S::PR + hl * S::HSQ + 4 * q, dq[k] * qscale);
+                if (4 * q < S::HSQ) O::st(R + t * S::PR + hl * S::HSQ + 4 * q, dq[k]);
             }
 #pragma unroll
             for (int k = 0; k < S::ROUNDS * PR_; ++k) {
@@ -1175,7 +1274,7 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
                 const int round = k / PR_, u = wv + (k - round * PR_) * S::WAVES, slot = u / S::NT, hl = round * S::NF + slot;
                 if (u >= UR || hl >= S::HG) continue;
                 const int t = 16 * (u - slot * S::NT) + l16;
-                if (4 * q < S::HSQ) O::st(R + t * S::PR + S::RQ + hl * S::HSQ + 4 * q, dk[k] * qscale);
+                if (4 * q < S::HSQ) O::st(R + t * S::PR + S::RQ + hl * S::HSQ + 4 * q, dk[k] * (1.f / kLog2e));
                 if (4 * q < S::HSV) O::st(R + t * S::PR + 2 * S::RQ + hl * S::HSV + 4 * q, dv[k]);
             }
             __syncthreads();
@@ -1275,6 +1374,8 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
         }
         // ---- X is the gradient of the attention layer's input: out, or through LN_1's adjoint and the skip of Eq. 4 ----
         {
+            FRESH_LANE;
+            const bool in = 4 * l16 < S::C;
             f32x4 gam1, sg = zero4(), sb = zero4();
             if (LAYER) gam1 = load4_if(in, static_cast<const T *>(a.ln1_w), 4 * l16);
 #pragma unroll
