@@ -63,7 +63,7 @@ template <typename T_, int C_, int HEADS_, int G_, int M_, int DQ_, int HID_, in
     static constexpr int KUX = up(XW, 16), CTX = up(OC < XW ? XW : XW + 1, 16);
     static __device__ __forceinline__ int xcol(int c) { return CGP == CG ? c : c / CG * CGP + c % CG; }
     // (a slice's last k-slots and column tiles may run into the next row: numbers that meet zero weights or are dropped)
-    static constexpr int PC = pitch_of(imax(16 * up(C + 1, 16), XW)), PR = pitch_of(RP + 8), PD = pitch_of(RV), PH = pitch_of(16 * up(HID + 1, 16));
+    static constexpr int PC = pitch_of(imax(16 * up(C + 1, 16), XW)), PR = pitch_of(sizeof(E) == 2 ? RP + 8 : RP), PD = pitch_of(RV), PH = pitch_of(16 * up(HID + 1, 16));
     // (behind q|k|v a row holds its token's part of the shift mask: as a key, as a query)
     static constexpr int MK = RP, MQ = RP + 4;
     static constexpr int PF = N + 4; // pitch of a head's matrix of score gradients
@@ -186,8 +186,8 @@ template <> struct Op<bf16_t> {
 // Q and K operands (HS <= 12) carry the shift mask with them.  With r, c = "past the wrap in the last window row, column"
 // of a token, [regions of n and m differ] = (r_n|c_n) + (1-2 r_n)(1-c_n) r_m + (1-2 c_n)(1-r_n) c_m
 // - (1-2 r_n)(1-2 c_n) r_m c_m: four more k-slots, (1, r, c, rc) of the key against those coefficients of the query
-// times -100 log2(e).  In bf16 they take the slots 12 .. 15 that no head uses, at no cost; in fp32 they are one more
-// product, taken in masked windows only.
+// times -100 log2(e).  In bf16 they take the slots 12 .. 15 that no head uses, at no cost.  In fp32, where adding and
+// taking away 144 would cost the scores their last bits, masked windows add the mask on the vector ALU.
 template <typename E, int HS> struct HeadOp;
 template <int HS> struct HeadOp<float, HS> { // product i takes channels 4i .. 4i+3: HS / 4 products instead of four
     float v[HS / 4];
@@ -227,14 +227,6 @@ template <class S> struct QkOp : HeadOp<typename S::E, S::HSQ> {
         }
     }
 };
-// fp32: the mask's product on top of the scores of rows `rows` (their parts at column ra) against the lane's token `row`
-template <class S> __device__ __forceinline__ f32x4 add_mask(const typename S::E *rows, int ra, const typename S::E *row, int rb, f32x4 s, int l16, int q)
-{
-    if constexpr (sizeof(typename S::E) == 4)
-        return __builtin_amdgcn_mfma_f32_16x16x4f32(rows[l16 * S::PR + ra + q], row[rb + q], s, 0, 0, 0);
-    return s;
-}
-
 // sum over the 16 lanes of a row, left in all of them
 __device__ __forceinline__ float row16_sum(float v)
 {
@@ -488,10 +480,25 @@ template <class S> __device__ __forceinline__ f32x4 get_row(const typename S::E 
     return v;
 }
 
+// fp32: the mask on top of scores; the lane's column is token `col`, its rows are tokens row0 + i (`up`) or row0 + 3 - i,
+// row0 a multiple of four
+template <class S> __device__ __forceinline__ f32x4 add_mask(const Window<S> &win, f32x4 s, int row0, bool up, int col)
+{
+    const int reg = win.region(col), r = row0 / S::M, c = row0 - r * S::M;
+    const bool rows = ((reg & 1) != 0) != (win.last_r && r >= S::M - win.s);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const bool cols = ((reg & 2) != 0) != (win.last_c && c + (up ? i : 3 - i) >= S::M - win.s);
+        s[i] += (rows || cols) ? -100.f * kLog2e : 0.f;
+    }
+    return s;
+}
+
 // the shift mask's parts of a token, behind its q|k|v
 template <class S> __device__ __forceinline__ void put_mask(const Window<S> &win, typename S::E *R)
 {
     using O = Op<typename S::E>;
+    if (!QkOp<S>::SLOTS) return;
     for (int t = threadIdx.x; t < S::N; t += S::NTH) {
         const int reg = win.region(t);
         const float r = reg & 1 ? 1.f : 0.f, c = reg & 2 ? 1.f : 0.f, m = -100.f * kLog2e;
@@ -642,7 +649,7 @@ __global__ __launch_bounds__(S::NTH) void window_layer_fwd_kernel(WindowLayerArg
                 }
                 if (sizeof(E) == 4 && masked) {
 #pragma unroll
-                    for (int kt = 0; kt < S::NT; ++kt) st[kt] = add_mask<S>(R + 16 * kt * S::PR, S::MK, R + tq * S::PR, S::MQ, st[kt], 15 - l16, q);
+                    for (int kt = 0; kt < S::NT; ++kt) st[kt] = add_mask<S>(win, st[kt], 16 * kt + 12 - 4 * q, false, tq);
                 }
 #pragma unroll
                 for (int kt = 0; kt < S::NT; ++kt) mx = fmaxf(mx, fmaxf(fmaxf(st[kt][0], st[kt][1]), fmaxf(st[kt][2], st[kt][3])));
@@ -1118,7 +1125,7 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
                 }
                 if (sizeof(E) == 4 && masked) {
 #pragma unroll
-                    for (int kt = 0; kt < S::NT; ++kt) st[kt] = add_mask<S>(R + 16 * kt * S::PR, S::MK, R + tq * S::PR, S::MQ, st[kt], 15 - l16, q);
+                    for (int kt = 0; kt < S::NT; ++kt) st[kt] = add_mask<S>(win, st[kt], 16 * kt + 12 - 4 * q, false, tq);
                 }
 #pragma unroll
                 for (int kt = 0; kt < S::NT; ++kt) mx = fmaxf(mx, fmaxf(fmaxf(st[kt][0], st[kt][1]), fmaxf(st[kt][2], st[kt][3])));
@@ -1229,7 +1236,7 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
                     const float *bias = tbh + ok + key_offset4<S>(nt, q);
                     f32x4 p = mma(qf, kf, f32x4{bias[0], bias[1], bias[2], bias[3]}), d;
                     const f32x4 dp = mma(of, vf, dl); // dP - delta
-                    if (sizeof(E) == 4 && masked) p = add_mask<S>(R + 16 * nt * S::PR, S::MQ, R + tk * S::PR, S::MK, p, l16, q);
+                    if (sizeof(E) == 4 && masked) p = add_mask<S>(win, p, 16 * nt + 4 * q, true, tk);
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
                         p[i] = __builtin_amdgcn_exp2f(p[i] - ls[i]);

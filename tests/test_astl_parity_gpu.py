@@ -528,3 +528,18 @@ def test_fp32_whole_layers_one_workgroup_per_window(groups, shape, shift, cascad
     case = dict(B=B, H=H, W=W, C=60, heads=6, groups=groups, window=8, shift=shift, dtype="f32", hidden=120)
     print("case", case, flush=True)
     parity.check_block(astl_oracle, cascade=cascade, **case)
+
+
+@pytest.mark.parametrize("heads,groups,dqk,shape,shift", [
+    (4, 1, 4, (1, 24, 36), 6), (4, 4, 4, (2, 12, 24), 5), (4, 1, 8, (1, 36, 12), 6), (4, 2, 8, (1, 24, 24), 0),
+    (4, 4, 8, (1, 12, 12), 7), (6, 1, 4, (1, 24, 24), 6), (6, 2, 4, (1, 24, 12), 3), (6, 3, 4, (17, 48, 48), 6),
+    (6, 6, 4, (1, 24, 24), 6),
+])
+def test_12x12_window_layers_one_workgroup_per_window(heads, groups, dqk, shape, shift):
+    """Whole bf16 layers with 12x12 windows and narrow q / k are one launch per direction: every organisation of the
+    heads, one window, windows cut by the shift in both directions, more windows (272) than vectors of parameter
+    gradients (256)."""
+    B, H, W = shape
+    case = dict(B=B, H=H, W=W, C=60, heads=heads, groups=groups, window=12, shift=shift, dtype="bf16", hidden=120, dqk=dqk)
+    print("case", case, flush=True)
+    parity.check_block(astl_oracle, **case)

@@ -458,3 +458,12 @@ def test_fp32_layers_one_workgroup_per_window(oracle, groups, shape, shift):
     """fp32 layers of 60 channels and 8x8 windows run one workgroup per window: every group count, workgroups with
     one and with two windows, windows cut by the shift in every way."""
     parity.check_case(oracle, *shape, 60, 6, groups, 8, shift, "f32", regime="stress")
+
+
+@pytest.mark.parametrize("heads,groups,dqk,shape,shift", [
+    (4, 1, 4, (1, 24, 36), 6), (4, 1, 8, (1, 12, 12), 3), (4, 2, 8, (1, 24, 24), 0), (4, 4, 4, (2, 12, 24), 5),
+    (6, 1, 4, (1, 24, 24), 6), (6, 6, 4, (29, 36, 36), 6),
+])
+def test_12x12_windows_one_workgroup_per_window(oracle, heads, groups, dqk, shape, shift):
+    """bf16 attention layers with 12x12 windows: the organisations of the heads that no other test runs."""
+    parity.check_case(oracle, *shape, 60, heads, groups, 12, shift, "bf16", regime="stress", dqk=dqk)
