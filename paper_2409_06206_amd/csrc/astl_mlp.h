@@ -12,12 +12,13 @@ bool astl_mlp_supported(int C, int hidden);
 size_t astl_mlp_pack_bytes();
 
 // x1 = x + a (stored);  y = MLP(LN_2(x1)) + x1.  rows tokens of C channels.  `pack` receives the
-// repacked weights (astl_mlp_pack_bytes() bytes, 16-byte aligned).  With next_ln_out non-null the
+// repacked weights (astl_mlp_pack_bytes() bytes, 16-byte aligned), or holds them already (`packed`).  y may be x: a
+// wavefront stores rows that it has read and nobody else reads.  With next_ln_out non-null the
 // kernel also writes LN(y) with the given gamma and beta there: the first step of a layer that
 // follows (Eq. 4), of y as stored, at the same eps.
 hipError_t launch_astl_mlp_fwd(long rows, int C, int hidden, float eps, const bf16_t *x, const bf16_t *a,
                                const bf16_t *ln_w, const bf16_t *ln_b, const bf16_t *w_fc1, const bf16_t *b_fc1,
-                               const bf16_t *w_fc2, const bf16_t *b_fc2, bf16_t *x1, bf16_t *y, void *pack,
+                               const bf16_t *w_fc2, const bf16_t *b_fc2, bf16_t *x1, bf16_t *y, void *pack, bool packed,
                                const bf16_t *next_ln_w, const bf16_t *next_ln_b, bf16_t *next_ln_out, hipStream_t s);
 
 // The same forward for wide layers (64 < C <= 192, hidden <= 384): the weights are streamed through LDS in
@@ -29,7 +30,7 @@ size_t astl_mlp_wide_pack_bytes();
 hipError_t launch_astl_mlp_wide_fwd(long rows, int C, int hidden, float eps, const bf16_t *x, const bf16_t *a,
                                     const bf16_t *ln_w, const bf16_t *ln_b, const bf16_t *w_fc1, const bf16_t *b_fc1,
                                     const bf16_t *w_fc2, const bf16_t *b_fc2, bf16_t *x1, bf16_t *y, void *pack,
-                                    void *bwd_pack, const bf16_t *next_ln_w, const bf16_t *next_ln_b,
+                                    void *bwd_pack, bool packed, const bf16_t *next_ln_w, const bf16_t *next_ln_b,
                                     bf16_t *next_ln_out, hipStream_t s);
 
 // Backward of the same layers between the two LayerNorm adjoints, one launch: from x1 and dy it writes

@@ -589,9 +589,9 @@ unsigned bwd_blocks(long rows)
     return (unsigned)(b < 1 ? 1 : b);
 }
 
-template <int KSC, int KSF> hipError_t launch_fwd_t(const MlpArgs &a, hipStream_t s)
+template <int KSC, int KSF> hipError_t launch_fwd_t(const MlpArgs &a, bool packed, hipStream_t s)
 {
-    {
+    if (!packed) {
         KernelTimer kt(K_MLP_PACK, s);
         hipLaunchKernelGGL((astl_mlp_pack_kernel<KSC, KSF>), dim3(32), dim3(kMlpThreads), 0, s, a);
         hipError_t e = hipGetLastError();
@@ -626,7 +626,7 @@ bool astl_mlp_supported(int C, int hidden)
 
 hipError_t launch_astl_mlp_fwd(long rows, int C, int hidden, float eps, const bf16_t *x, const bf16_t *a,
                                const bf16_t *ln_w, const bf16_t *ln_b, const bf16_t *w_fc1, const bf16_t *b_fc1,
-                               const bf16_t *w_fc2, const bf16_t *b_fc2, bf16_t *x1, bf16_t *y, void *pack,
+                               const bf16_t *w_fc2, const bf16_t *b_fc2, bf16_t *x1, bf16_t *y, void *pack, bool packed,
                                const bf16_t *next_ln_w, const bf16_t *next_ln_b, bf16_t *next_ln_out, hipStream_t s)
 {
     if (!astl_mlp_supported(C, hidden)) return hipErrorInvalidValue;
@@ -637,8 +637,8 @@ hipError_t launch_astl_mlp_fwd(long rows, int C, int hidden, float eps, const bf
     if (next_ln_out && next_ln_w && next_ln_b) {
         m.nxt_w = next_ln_w; m.nxt_b = next_ln_b; m.xn_out = next_ln_out;
     }
-    if (C <= 32) return hidden <= 64 ? launch_fwd_t<1, 2>(m, s) : launch_fwd_t<1, 4>(m, s);
-    return hidden <= 64 ? launch_fwd_t<2, 2>(m, s) : launch_fwd_t<2, 4>(m, s);
+    if (C <= 32) return hidden <= 64 ? launch_fwd_t<1, 2>(m, packed, s) : launch_fwd_t<1, 4>(m, packed, s);
+    return hidden <= 64 ? launch_fwd_t<2, 2>(m, packed, s) : launch_fwd_t<2, 4>(m, packed, s);
 }
 
 size_t astl_mlp_pack_bytes() { return align256(PackLayout<2, 4>::bytes); }

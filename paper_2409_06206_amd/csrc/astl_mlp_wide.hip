@@ -760,11 +760,11 @@ __global__ __launch_bounds__(256) void astl_mlp_wide_pack_kernel(WideMlpArgs a, 
     if (b.pack) wide_bwd_pack_body<KSC, KSF>(b, nub);
 }
 
-template <int KSC, int KSF> hipError_t launch_wide_t(const WideMlpArgs &a, hipStream_t s)
+template <int KSC, int KSF> hipError_t launch_wide_t(const WideMlpArgs &a, bool packed, hipStream_t s)
 {
     using L = WideMlp<KSC, KSF>;
     const int nu = ((a.Hd + 31) / 32 + L::HU - 1) / L::HU; // stream units
-    {
+    if (!packed) {
         KernelTimer kt(K_MLP_PACK, s);
         WideMlpBwdArgs b{};
         b.C = a.C; b.Hd = a.Hd; b.ln_w = a.ln_w; b.ln_b = a.ln_b; b.w_fc1 = a.w_fc1; b.b_fc1 = a.b_fc1; b.w_fc2 = a.w_fc2;
@@ -971,7 +971,7 @@ size_t astl_mlp_wide_pack_bytes() { return (WideMlp<6, 12>::P_BYTES + 255) & ~si
 hipError_t launch_astl_mlp_wide_fwd(long rows, int C, int hidden, float eps, const bf16_t *x, const bf16_t *a,
                                     const bf16_t *ln_w, const bf16_t *ln_b, const bf16_t *w_fc1, const bf16_t *b_fc1,
                                     const bf16_t *w_fc2, const bf16_t *b_fc2, bf16_t *x1, bf16_t *y, void *pack,
-                                    void *bwd_pack, const bf16_t *next_ln_w, const bf16_t *next_ln_b,
+                                    void *bwd_pack, bool packed, const bf16_t *next_ln_w, const bf16_t *next_ln_b,
                                     bf16_t *next_ln_out, hipStream_t s)
 {
     if (!astl_mlp_wide_supported(C, hidden) || rows <= 0) return hipErrorInvalidValue;
@@ -983,8 +983,8 @@ hipError_t launch_astl_mlp_wide_fwd(long rows, int C, int hidden, float eps, con
     if (next_ln_out && next_ln_w && next_ln_b) {
         m.nxt_w = next_ln_w; m.nxt_b = next_ln_b; m.xn_out = next_ln_out;
     }
-    if (C <= 128) return launch_wide_t<4, 12>(m, s);
-    return launch_wide_t<6, 12>(m, s);
+    if (C <= 128) return launch_wide_t<4, 12>(m, packed, s);
+    return launch_wide_t<6, 12>(m, packed, s);
 }
 
 size_t astl_mlp_wide_bwd_pack_bytes() { return (WideMlpBwd<6, 12>::P_BYTES + 255) & ~size_t(255); }

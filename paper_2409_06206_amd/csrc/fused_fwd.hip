@@ -748,10 +748,10 @@ hipError_t launch_attn_chunks(const Geom &g, const bf16_t *x, const uint8_t *pac
 template <class Cf>
 hipError_t run_fwd(const Geom &g, const bf16_t *x, const bf16_t *w_qkv, const bf16_t *b_qkv,
                    const bf16_t *w_proj, const bf16_t *b_proj, const bf16_t *table, bf16_t *y,
-                   bf16_t *attn, void *ws, int training, hipStream_t s)
+                   bf16_t *attn, void *ws, int training, bool packed, hipStream_t s)
 {
     uint8_t *pack = static_cast<uint8_t *>(ws);
-    {
+    if (!packed) {
         constexpr int entries =
             (Cf::N_WQH + Cf::N_WP2 + Cf::N_BF + Cf::N_WQ + Cf::N_WPT + Cf::N_WQT + Cf::N_WPK) * 64 + 4 * Cf::C;
         constexpr int wide_entries = (Cf::N_WQW + Cf::N_WPW + Cf::N_WQX + Cf::N_WQN) * 64 + Cf::HEADS * Cf::TBW_PITCH;
@@ -830,11 +830,11 @@ size_t fused_pack_bytes(const Geom &g)
 
 hipError_t launch_fused_fwd(const Geom &g, const bf16_t *x, const bf16_t *w_qkv, const bf16_t *b_qkv,
                             const bf16_t *w_proj, const bf16_t *b_proj, const bf16_t *table,
-                            bf16_t *y, bf16_t *attn_out, void *pack, int training, hipStream_t s)
+                            bf16_t *y, bf16_t *attn_out, void *pack, int training, bool packed, hipStream_t s)
 {
 #define X(C_, H_, G_)                                                  \
     if (g.C == C_ && g.heads == H_ && g.groups == G_)                  \
-        return run_fwd<FusedCfg<C_, H_, G_>>(g, x, w_qkv, b_qkv, w_proj, b_proj, table, y, attn_out, pack, training, s);
+        return run_fwd<FusedCfg<C_, H_, G_>>(g, x, w_qkv, b_qkv, w_proj, b_proj, table, y, attn_out, pack, training, packed, s);
     GSWA_FUSED_SHAPES(X)
 #undef X
     return hipErrorInvalidValue;

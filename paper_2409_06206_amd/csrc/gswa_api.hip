@@ -354,38 +354,9 @@ int backward_fused(const Geom &g, const Sizes &sz, uint32_t flags, const bf16_t 
 
 } // namespace
 
-extern "C" {
-
-int gswa_query_bytes(const gswa_desc *desc, size_t *saved_bytes, size_t *fwd_ws_bytes,
-                     size_t *bwd_ws_bytes)
-{
-    Geom g;
-    int rc = make_geom(desc, &g);
-    if (rc != GSWA_OK) return rc;
-    Sizes s = make_sizes(desc, g);
-    if (saved_bytes) *saved_bytes = s.saved;
-    if (fwd_ws_bytes) *fwd_ws_bytes = s.fwd_ws;
-    if (bwd_ws_bytes) *bwd_ws_bytes = s.bwd_ws;
-    return GSWA_OK;
-}
-
-int gswa_query_path(const gswa_desc *desc, int *forward_path, int *backward_path)
-{
-    Geom g;
-    int rc = make_geom(desc, &g);
-    if (rc != GSWA_OK) return rc;
-    const Sizes s = make_sizes(desc, g); // (the same decisions gswa_forward and gswa_backward take)
-    int fwd = GSWA_PATH_STAGED;
-    if (s.fused_fwd) fwd = GSWA_PATH_FUSED;
-    else if (desc->dtype == GSWA_BF16 && !(desc->flags & GSWA_FORCE_STAGED) && window_fwd_supported(g)) fwd = GSWA_PATH_WINDOW_FWD;
-    if (forward_path) *forward_path = fwd;
-    if (backward_path) *backward_path = s.fused_bwd ? GSWA_PATH_FUSED : GSWA_PATH_STAGED;
-    return GSWA_OK;
-}
-
-int gswa_forward(const gswa_desc *desc, const void *x, const void *w_qkv, const void *b_qkv,
+int gswa::attn_forward(const gswa_desc *desc, const void *x, const void *w_qkv, const void *b_qkv,
                  const void *w_proj, const void *b_proj, const void *bias_table, void *y,
-                 void *saved, void *ws, void *hip_stream)
+                 void *saved, void *ws, bool packed, void *hip_stream)
 {
     Geom g;
     int rc = make_geom(desc, &g);
@@ -425,7 +396,7 @@ int gswa_forward(const gswa_desc *desc, const void *x, const void *w_qkv, const 
         if (!saved && fused_fwd_needs_attn(g)) attn = static_cast<char *>(ws) + s.pack;
         hipError_t e = launch_fused_fwd(g, (const bf16_t *)x, (const bf16_t *)w_qkv, (const bf16_t *)b_qkv,
                                         (const bf16_t *)w_proj, (const bf16_t *)b_proj,
-                                        (const bf16_t *)bias_table, (bf16_t *)y, (bf16_t *)attn, pack, saved ? 1 : 0, st);
+                                        (const bf16_t *)bias_table, (bf16_t *)y, (bf16_t *)attn, pack, saved ? 1 : 0, packed, st);
         return e == hipSuccess ? GSWA_OK : hip_fail(e);
     }
     if (!(desc->flags & GSWA_FORCE_STAGED) && window_fwd_supported(g)) {
@@ -437,6 +408,42 @@ int gswa_forward(const gswa_desc *desc, const void *x, const void *w_qkv, const 
     return forward_staged<bf16_t>(g, s, (const bf16_t *)x, (const bf16_t *)w_qkv, (const bf16_t *)b_qkv,
                                   (const bf16_t *)w_proj, (const bf16_t *)b_proj,
                                   (const bf16_t *)bias_table, (bf16_t *)y, (bf16_t *)saved, (char *)ws, st);
+}
+
+extern "C" {
+
+int gswa_query_bytes(const gswa_desc *desc, size_t *saved_bytes, size_t *fwd_ws_bytes,
+                     size_t *bwd_ws_bytes)
+{
+    Geom g;
+    int rc = make_geom(desc, &g);
+    if (rc != GSWA_OK) return rc;
+    Sizes s = make_sizes(desc, g);
+    if (saved_bytes) *saved_bytes = s.saved;
+    if (fwd_ws_bytes) *fwd_ws_bytes = s.fwd_ws;
+    if (bwd_ws_bytes) *bwd_ws_bytes = s.bwd_ws;
+    return GSWA_OK;
+}
+
+int gswa_query_path(const gswa_desc *desc, int *forward_path, int *backward_path)
+{
+    Geom g;
+    int rc = make_geom(desc, &g);
+    if (rc != GSWA_OK) return rc;
+    const Sizes s = make_sizes(desc, g); // (the same decisions gswa_forward and gswa_backward take)
+    int fwd = GSWA_PATH_STAGED;
+    if (s.fused_fwd) fwd = GSWA_PATH_FUSED;
+    else if (desc->dtype == GSWA_BF16 && !(desc->flags & GSWA_FORCE_STAGED) && window_fwd_supported(g)) fwd = GSWA_PATH_WINDOW_FWD;
+    if (forward_path) *forward_path = fwd;
+    if (backward_path) *backward_path = s.fused_bwd ? GSWA_PATH_FUSED : GSWA_PATH_STAGED;
+    return GSWA_OK;
+}
+
+int gswa_forward(const gswa_desc *desc, const void *x, const void *w_qkv, const void *b_qkv,
+                 const void *w_proj, const void *b_proj, const void *bias_table, void *y,
+                 void *saved, void *ws, void *hip_stream)
+{
+    return attn_forward(desc, x, w_qkv, b_qkv, w_proj, b_proj, bias_table, y, saved, ws, false, hip_stream);
 }
 
 int gswa_backward(const gswa_desc *desc, const void *x, const void *dy, const void *w_qkv,

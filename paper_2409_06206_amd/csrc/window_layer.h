@@ -29,6 +29,11 @@ struct WindowLayerGrads {
 // Checks a descriptor and derives its geometry (GSWA_OK or an error code).
 int make_geom(const gswa_desc *d, Geom *g);
 
+// gswa_forward; `packed`: ws holds this layer's repacked parameters from an earlier inference call of the same descriptor
+// (layers of the kernels that read them repacked; the others take no notice).
+int attn_forward(const gswa_desc *d, const void *x, const void *w_qkv, const void *b_qkv, const void *w_proj, const void *b_proj,
+                 const void *bias_table, void *y, void *saved, void *ws, bool packed, void *hip_stream);
+
 // Vectors of parameter gradients a backward launch leaves at most (= its workgroups).
 constexpr int kWindowLayerVectors = 256;
 
