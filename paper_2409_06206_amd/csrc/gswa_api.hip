@@ -155,7 +155,7 @@ bool use_fused_fwd(const gswa_desc *d, const Geom &g)
 // One workgroup per window (window_layer.h): fp32, and bf16 layers with 12x12 windows.
 const WindowLayerOps *use_window(const gswa_desc *d, const Geom &g)
 {
-    if ((d->flags & GSWA_FORCE_STAGED) || (d->dtype == GSWA_BF16 && g.M != 12)) return nullptr;
+    if (d->flags & GSWA_FORCE_STAGED) return nullptr;
     return window_layer_ops(g, d->dtype == GSWA_F32, 0);
 }
 

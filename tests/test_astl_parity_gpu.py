@@ -543,3 +543,23 @@ def test_12x12_window_layers_one_workgroup_per_window(heads, groups, dqk, shape,
     case = dict(B=B, H=H, W=W, C=60, heads=heads, groups=groups, window=12, shift=shift, dtype="bf16", hidden=120, dqk=dqk)
     print("case", case, flush=True)
     parity.check_block(astl_oracle, **case)
+
+
+@pytest.mark.parametrize("groups,shape,shift,every", [
+    (1, (1, 8, 8), 5, 0), (1, (8, 64, 64), 4, 1), (2, (1, 16, 24), 3, 0), (2, (1, 8, 8 * 257), 4, 1),
+    (2, (1, 72, 456), 4, 0), (3, (2, 24, 16), 4, 1), (3, (8, 64, 64), 7, 0),
+    (3, (1, 8, 8 * 513), 4, 0),
+])
+def test_small_bf16_sequences_one_workgroup_per_window(groups, shape, shift, every):
+    """Sequences of bf16 layers of 60 channels with 8x8 windows on both sides of the number of windows up to which a
+    layer is one launch per direction (512): one window, workgroups with one and with two windows."""
+    B, H, W = shape
+    case = dict(B=B, H=H, W=W, C=60, heads=6, groups=groups, window=8, shift=shift, dtype="bf16", hidden=120, n_layers=2)
+    gswa.gswa_profile_enable(True)
+    gswa.gswa_profile_collect()
+    test_stack_matches_oracle_with_and_without_checkpointing(case, every)
+    names, dropped = gswa.gswa_profile_collect()
+    gswa.gswa_profile_enable(False)
+    assert dropped == 0
+    one_launch = B * (H // 8) * (W // 8) <= 512
+    assert ("layer_fwd" in names and "layer_bwd" in names) == one_launch and ("mlp_fwd" in names) != one_launch, names
