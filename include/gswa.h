@@ -125,7 +125,10 @@ int gswa_query_bytes(const gswa_desc *desc, size_t *saved_bytes, size_t *fwd_ws_
  * Returns GSWA_OK, or the error gswa_query_bytes would return for desc.
  */
 enum {
-    GSWA_PATH_STAGED = 0,     /* one kernel per step of Eq. 6-8 and head group (every shape, both types) */
+    GSWA_PATH_STAGED = 0,     /* one kernel per step of Eq. 6-8 and head group (every shape, both types).
+                                 The values name the general organisations: fp32 layers with C = 60, six
+                                 heads and 8x8 windows, and bf16 layers with C = 60 and 12x12 windows, run
+                                 one workgroup per window in both passes and report as they would without */
     GSWA_PATH_FUSED = 1,      /* the whole pass in one kernel, or one per head chunk (bf16, 8x8 or 16x16
                                  windows, six heads, C = 60 or 180; backward: 8x8 windows only)          */
     GSWA_PATH_WINDOW_FWD = 2  /* forward in one launch per layer, one workgroup per window (bf16 layers
