@@ -374,9 +374,7 @@ struct Plan {
     bool wide_mlp;                // forward of the MLP half by the streaming kernel for wide layers
 };
 
-// `sequence`: the layer is one of a sequence's whole-map calls.  (Not of its bands, whose kernels may not depend on how
-// many windows the band has: every band size gives the same bits.)
-int make_plan(const astl_desc *d, Plan *p, bool sequence = false)
+int make_plan(const astl_desc *d, Plan *p)
 {
     if (!d) return GSWA_EINVAL;
     int rc = gswa_query_bytes(&d->attn, &p->at_saved, &p->at_fws, &p->at_bws);
@@ -411,7 +409,7 @@ int make_plan(const astl_desc *d, Plan *p, bool sequence = false)
     if (!(d->attn.flags & GSWA_FORCE_STAGED)) {
         rc = make_geom(&d->attn, &p->g);
         if (rc != GSWA_OK) return rc;
-        p->window = window_layer_ops(p->g, d->attn.dtype == GSWA_F32, p->Hd, sequence);
+        p->window = window_layer_ops(p->g, d->attn.dtype == GSWA_F32, p->Hd);
     }
     if (p->window) {
         const size_t need = align256(window_layer_bwd_ws_bytes(*p->window, p->g, true));
@@ -475,7 +473,6 @@ struct LayerLink {
     // first .. first + count - 1 only, and y is the row of the first of them; y may lie over x there, because a
     // wavefront stores no row before it has read it.  count == 0: all tokens.
     long first, count;
-    bool band;                 // in: the call is a band of a map
     bool packed;               // in: the scratch holds this layer's repacked weights (an earlier band of the same size)
 };
 
@@ -852,7 +849,7 @@ int forward_checked(const astl_desc *desc, const void *x, const astl_params *p, 
                     void *hip_stream, LayerLink *link)
 {
     Plan pl;
-    int rc = make_plan(desc, &pl, link && !link->band);
+    int rc = make_plan(desc, &pl);
     if (rc != GSWA_OK) return rc;
     if (!x || !p || !y || !ws || !params_ok(p)) return GSWA_EINVAL;
     if ((x == y && !(link && link->count)) || (reinterpret_cast<uintptr_t>(ws) & 255) || !aligned16(x, y, saved)) return GSWA_EINVAL;
@@ -886,7 +883,7 @@ int backward_checked(const astl_desc *desc, const void *x, const void *dy, const
                      void *dx, const astl_grads *g, void *ws, void *hip_stream, BackLink *link)
 {
     Plan pl;
-    int rc = make_plan(desc, &pl, link != nullptr);
+    int rc = make_plan(desc, &pl);
     if (rc != GSWA_OK) return rc;
     if (!x || !dy || !p || !saved || !dx || !g || !ws || !params_ok(p) || !grads_ok(g)) return GSWA_EINVAL;
     if (dx == x || dx == dy || dx == saved || (reinterpret_cast<uintptr_t>(ws) & 255)) return GSWA_EINVAL;
@@ -922,9 +919,9 @@ int make_stack_plan(const astl_stack_desc *d, StackPlan *sp)
     sp->even = d->layer; sp->even.attn.shift = 0;
     sp->odd = d->layer; sp->odd.attn.shift = d->shift;
     Plan pe, po;
-    int rc = make_plan(&sp->even, &pe, true);
+    int rc = make_plan(&sp->even, &pe);
     if (rc != GSWA_OK) return rc;
-    rc = make_plan(&sp->odd, &po, true);
+    rc = make_plan(&sp->odd, &po);
     if (rc != GSWA_OK) return rc;
     sp->S = pe.saved > po.saved ? pe.saved : po.saved;
     sp->F = pe.fwd_ws > po.fwd_ws ? pe.fwd_ws : po.fwd_ws;
@@ -1089,7 +1086,7 @@ int astl_stack_forward_tiled(const astl_stack_desc *desc, const void *x, const a
         auto layer_call = [&](const astl_desc &sd, const char *src, char *dst, long first, long count) -> int {
             const int wr = sd.attn.H / M; // (where they lie is a function of the band's size)
             LayerLink link{};
-            link.first = first; link.count = count; link.band = true;
+            link.first = first; link.count = count;
             link.packed = tp.direct && packed_rows == wr;
             packed_rows = wr;
             return forward_checked(&sd, src, params + l, dst, nullptr, layer_ws, hip_stream, &link);

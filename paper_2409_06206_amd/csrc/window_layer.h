@@ -45,13 +45,11 @@ struct WindowLayerOps {
 };
 // the shapes of each file that instantiates the kernels (null: none fits)
 const WindowLayerOps *window_layer_f32(const Geom &g);
-const WindowLayerOps *window_layer_bf16_w8(const Geom &g);
 const WindowLayerOps *window_layer_bf16_w12h4(const Geom &g);
 const WindowLayerOps *window_layer_bf16_w12h6(const Geom &g);
 
-// The kernels that serve a layer, or null.  hidden == 0 asks for the attention layer alone; `sequence`: the
-// layer is one of a sequence's (astl_stack_*).
-const WindowLayerOps *window_layer_ops(const Geom &g, bool f32, int hidden, bool sequence = false);
+// The kernels that serve a layer, or null.  hidden == 0 asks for the attention layer alone.
+const WindowLayerOps *window_layer_ops(const Geom &g, bool f32, int hidden);
 // scratch of the backward: the workgroups' vectors
 inline size_t window_layer_bwd_ws_bytes(const WindowLayerOps &ops, const Geom &g, bool layer)
 {

@@ -13,25 +13,12 @@ const WindowLayerOps *window_layer_f32(const Geom &g)
     return nullptr;
 }
 
-// Sequences of bf16 layers with 8x8 windows.  Their other kernels take a window per wavefront (fused.h, astl_mlp.h):
-// four launches per layer and forward, a dozen per backward, each as long as a wavefront takes alone with its window.
-// While every window has a compute unit of its own, one workgroup per window is about twice as fast, whatever their
-// number; every further round of workgroups costs as much again.  Four layers, us per pass, window per wavefront /
-// per workgroup, inference and training:
-//   two groups   256 windows  123 /  65   464 / 233      512 windows  136 / 120   534 / 426     768  162 / 175   643 / 620
-//   one group    256          131 /  62   464 / 227      512          148 /  85   566 / 399
-//   three groups 256          121 /  65   481 / 241      512          138 / 116   555 / 443
-// Errors against fp64 (64 windows, one layer): 0.82 to 1.17 times those of the other kernels, most of them smaller.
-// (Six groups gain least, 1.3 times up to 256 windows and a loss behind, and keep the other kernels.)
-constexpr int kSmallLayerWindows = 512;
-
-const WindowLayerOps *window_layer_ops(const Geom &g, bool f32, int hidden, bool sequence)
+const WindowLayerOps *window_layer_ops(const Geom &g, bool f32, int hidden)
 {
     if (g.T * g.C >= (1L << 40) || (hidden != 0 && hidden != 2 * g.C)) return nullptr;
     if (f32) return window_layer_f32(g);
     if (const WindowLayerOps *o = window_layer_bf16_w12h4(g)) return o;
-    if (const WindowLayerOps *o = window_layer_bf16_w12h6(g)) return o;
-    return hidden != 0 && sequence && g.nW <= kSmallLayerWindows ? window_layer_bf16_w8(g) : nullptr;
+    return window_layer_bf16_w12h6(g);
 }
 
 } // namespace gswa

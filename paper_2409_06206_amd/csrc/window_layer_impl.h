@@ -276,8 +276,8 @@ template <class S> __device__ __forceinline__ int key_offset(int n) { const int 
 template <class S> __device__ __forceinline__ int key_offset4(int tile, int q)
 {
     if (S::M == 8) return 2 * S::NTB * tile + S::NTB * (q >> 1) + 4 * (q & 1);
-    if (S::M == 12) return 4 * S::NTB * (tile / 3) + key_offset<S>(16 * (tile % 3) + 4 * q); // (three tiles are four window rows)
-    return key_offset<S>(16 * tile + 4 * q);
+    static_assert(S::M == 8 || S::M == 12, "window size");
+    return 4 * S::NTB * (tile / 3) + key_offset<S>(16 * (tile % 3) + 4 * q); // (12: three tiles are four window rows)
 }
 
 // feature of the padded q|k|v rows -> row of the group's weight block [q: QG | k: QG | v: CG], -1 for padding

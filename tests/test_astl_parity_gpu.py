@@ -545,21 +545,35 @@ def test_12x12_window_layers_one_workgroup_per_window(heads, groups, dqk, shape,
     parity.check_block(astl_oracle, **case)
 
 
-@pytest.mark.parametrize("groups,shape,shift,every", [
-    (1, (1, 8, 8), 5, 0), (1, (8, 64, 64), 4, 1), (2, (1, 16, 24), 3, 0), (2, (1, 8, 8 * 257), 4, 1),
-    (2, (1, 72, 456), 4, 0), (3, (2, 24, 16), 4, 1), (3, (8, 64, 64), 7, 0),
-    (3, (1, 8, 8 * 513), 4, 0),
-])
-def test_small_bf16_sequences_one_workgroup_per_window(groups, shape, shift, every):
-    """Sequences of bf16 layers of 60 channels with 8x8 windows on both sides of the number of windows up to which a
-    layer is one launch per direction (512): one window, workgroups with one and with two windows."""
-    B, H, W = shape
-    case = dict(B=B, H=H, W=W, C=60, heads=6, groups=groups, window=8, shift=shift, dtype="bf16", hidden=120, n_layers=2)
-    gswa.gswa_profile_enable(True)
-    gswa.gswa_profile_collect()
-    test_stack_matches_oracle_with_and_without_checkpointing(case, every)
-    names, dropped = gswa.gswa_profile_collect()
-    gswa.gswa_profile_enable(False)
-    assert dropped == 0
-    one_launch = B * (H // 8) * (W // 8) <= 512
-    assert ("layer_fwd" in names and "layer_bwd" in names) == one_launch and ("mlp_fwd" in names) != one_launch, names
+@pytest.mark.parametrize("case,copies", [
+    (dict(H=16, W=24, heads=6, groups=1, window=8, shift=4, dtype="bf16"), 90),
+    (dict(H=16, W=24, heads=6, groups=2, window=8, shift=3, dtype="bf16"), 90),
+    (dict(H=24, W=16, heads=6, groups=3, window=8, shift=4, dtype="bf16"), 90),
+    (dict(H=24, W=36, heads=4, groups=2, window=12, shift=6, dtype="bf16", dqk=4), 90),
+    (dict(H=24, W=16, heads=6, groups=2, window=8, shift=4, dtype="f32"), 90),
+], ids=lambda v: _id(v) if isinstance(v, dict) else str(v))
+def test_an_image_gives_the_same_bits_alone_and_in_a_batch(case, copies):
+    """Every (image, window) is computed on its own, by kernels that are chosen without a look at the number of
+    images: the output and the input gradient of an image through a sequence of layers have the same bits whether the
+    call holds that image alone (6 windows) or with 89 others (540)."""
+    import torch
+    from paper_2409_06206_amd import runner
+    c = dict(C=60, hidden=120, n_layers=2, **case)
+    print("case", c, flush=True)
+    ps = [synth.astl_params(60, c["heads"], c["groups"], c["window"], 120, 300 + l, "stress", c.get("dqk", 0)) for l in range(2)]
+    ps = [{k: synth.quantize(v, c["dtype"]) for k, v in p.items()} for p in ps]
+    x, dy = synth.activations(copies, c["H"], c["W"], 60, 2)
+    got = []
+    for B in (1, copies):
+        st = runner.DeviceStack(B, checkpoint_every=1, **c)
+        st.set_params(ps)
+        st.set_inputs(x[:B], dy[:B])
+        st.forward(keep=False)
+        torch.cuda.synchronize()
+        y = st.y[:1].clone()
+        st.forward()
+        st.backward()
+        torch.cuda.synchronize()
+        got.append((y, st.y[:1].clone(), st.dx[:1].clone()))
+    for name, alone, batch in zip(("inference y", "y", "dx"), *got):
+        assert torch.equal(alone, batch), name
