@@ -440,8 +440,12 @@ WindowLayerArgs window_args(const astl_desc *d, const Plan &pl, const void *x, c
     return a;
 }
 
-int forward_window(const astl_desc *d, const Plan &pl, const void *x, const astl_params *p, void *y, char *saved, hipStream_t st)
+// (The attention layer's buffers lie where forward_t and backward_t have them, and may overlap no more than there.)
+int forward_window(const astl_desc *d, const Plan &pl, const void *x, const astl_params *p, void *y, char *saved, const char *ws,
+                   hipStream_t st)
 {
+    ASTL_RC(attn_forward_check(&d->attn, ws, p->w_qkv, p->b_qkv, p->w_proj, p->b_proj, p->bias_table, ws + pl.act,
+                               saved ? saved + pl.act : nullptr, ws + 2 * pl.act));
     WindowLayerArgs a = window_args(d, pl, x, p);
     a.y = y;
     a.x1 = saved; a.attn = saved ? saved + pl.act : nullptr;
@@ -450,11 +454,14 @@ int forward_window(const astl_desc *d, const Plan &pl, const void *x, const astl
 }
 
 int backward_window(const astl_desc *d, const Plan &pl, const void *x, const void *dy, const astl_params *p, const char *saved,
-                    void *dx, const astl_grads *g, void *ws, hipStream_t st)
+                    void *dx, const astl_grads *g, char *ws, hipStream_t st)
 {
+    ASTL_RC(attn_backward_check(&d->attn, ws, ws + 2 * pl.act, p->w_qkv, p->b_qkv, p->w_proj, p->b_proj, p->bias_table,
+                                saved + pl.act, ws + pl.act, g->w_qkv, g->b_qkv, g->w_proj, g->b_proj, g->bias_table,
+                                ws + 3 * pl.act));
     WindowLayerArgs a = window_args(d, pl, x, p);
     a.x1 = const_cast<char *>(saved); a.attn = const_cast<char *>(saved) + pl.act;
-    a.dy = dy; a.dx = dx; a.part = static_cast<float *>(ws);
+    a.dy = dy; a.dx = dx; a.part = reinterpret_cast<float *>(ws);
     WindowLayerGrads gr{};
     gr.w_qkv = g->w_qkv; gr.b_qkv = g->b_qkv; gr.w_proj = g->w_proj; gr.b_proj = g->b_proj; gr.table = g->bias_table;
     gr.w_fc1 = g->w_fc1; gr.b_fc1 = g->b_fc1; gr.w_fc2 = g->w_fc2; gr.b_fc2 = g->b_fc2;
@@ -856,7 +863,7 @@ int forward_checked(const astl_desc *desc, const void *x, const astl_params *p, 
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     if (pl.window) {
         if (link) link->emitted = false;
-        return forward_window(desc, pl, x, p, y, (char *)saved, st);
+        return forward_window(desc, pl, x, p, y, (char *)saved, (const char *)ws, st);
     }
     if (desc->attn.dtype == GSWA_F32)
         return forward_t<float>(desc, pl, (const float *)x, p, (float *)y, (char *)saved, (char *)ws, st, link);
@@ -889,7 +896,7 @@ int backward_checked(const astl_desc *desc, const void *x, const void *dy, const
     if (dx == x || dx == dy || dx == saved || (reinterpret_cast<uintptr_t>(ws) & 255)) return GSWA_EINVAL;
     if (!aligned16(x, dy, saved, dx)) return GSWA_EINVAL;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    if (pl.window) return backward_window(desc, pl, x, dy, p, (const char *)saved, dx, g, ws, st);
+    if (pl.window) return backward_window(desc, pl, x, dy, p, (const char *)saved, dx, g, (char *)ws, st);
     if (desc->attn.dtype == GSWA_F32)
         return backward_t<float>(desc, pl, (const float *)x, (const float *)dy, p, (const char *)saved, (float *)dx,
                                  g, (char *)ws, st, link);

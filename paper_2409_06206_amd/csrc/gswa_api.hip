@@ -352,19 +352,18 @@ int backward_fused(const Geom &g, const Sizes &sz, uint32_t flags, const bf16_t 
     return GSWA_OK;
 }
 
-} // namespace
-
-int gswa::attn_forward(const gswa_desc *desc, const void *x, const void *w_qkv, const void *b_qkv,
-                 const void *w_proj, const void *b_proj, const void *bias_table, void *y,
-                 void *saved, void *ws, bool packed, void *hip_stream)
+// The rules of gswa_forward's arguments: pointers, alignment, buffers that may not overlap.
+int check_forward(const gswa_desc *desc, const void *x, const void *w_qkv, const void *b_qkv, const void *w_proj,
+                  const void *b_proj, const void *bias_table, const void *y, const void *saved, const void *ws, Geom *geom,
+                  Sizes *sizes)
 {
-    Geom g;
+    Geom &g = *geom;
     int rc = make_geom(desc, &g);
     if (rc != GSWA_OK) return rc;
     if (!x || !w_qkv || !b_qkv || !w_proj || !b_proj || !bias_table || !y) return GSWA_EINVAL;
     if (reinterpret_cast<uintptr_t>(ws) & 255) return GSWA_EINVAL;
     if (!aligned16(x, w_qkv, b_qkv, w_proj, b_proj, bias_table, y, saved)) return GSWA_EINVAL;
-    Sizes s = make_sizes(desc, g);
+    const Sizes &s = *sizes = make_sizes(desc, g);
     {
         const size_t e = elem_size(desc), act = (size_t)g.T * g.C * e;
         const size_t ws_bytes = saved ? s.fwd_ws : s.fwd_ws + s.saved;
@@ -377,6 +376,77 @@ int gswa::attn_forward(const gswa_desc *desc, const void *x, const void *w_qkv, 
         if (overlaps_any(rsv, rx, rws, rwq, rbq, rwp, rbp, rtb)) return GSWA_EINVAL;
         if (overlaps_any(rws, rx, rwq, rbq, rwp, rbp, rtb)) return GSWA_EINVAL;
     }
+    return GSWA_OK;
+}
+
+// The same of gswa_backward's.
+int check_backward(const gswa_desc *desc, const void *x, const void *dy, const void *w_qkv, const void *b_qkv,
+                   const void *w_proj, const void *b_proj, const void *bias_table, const void *saved, const void *dx,
+                   const void *dw_qkv, const void *db_qkv, const void *dw_proj, const void *db_proj, const void *dbias_table,
+                   const void *ws, Geom *geom, Sizes *sizes)
+{
+    Geom &g = *geom;
+    int rc = make_geom(desc, &g);
+    if (rc != GSWA_OK) return rc;
+    if (!x || !dy || !w_qkv || !b_qkv || !w_proj || !b_proj || !bias_table || !saved || !dx ||
+        !dw_qkv || !db_qkv || !dw_proj || !db_proj || !dbias_table)
+        return GSWA_EINVAL;
+    if (reinterpret_cast<uintptr_t>(ws) & 255) return GSWA_EINVAL;
+    if (!aligned16(x, dy, w_qkv, b_qkv, w_proj, bias_table, saved, dx, dw_qkv, db_qkv, dw_proj, db_proj,
+                   dbias_table))
+        return GSWA_EINVAL;
+    const Sizes &s = *sizes = make_sizes(desc, g);
+    {
+        const size_t e = elem_size(desc), act = (size_t)g.T * g.C * e;
+        if (!ws && s.bwd_ws > 0) return GSWA_EINVAL;
+        const size_t n_wq = (size_t)g.groups * g.Rg * g.Cg, n_bq = (size_t)g.groups * g.Rg;
+        const size_t n_wp = (size_t)g.C * g.C, n_tb = (size_t)(2 * g.M - 1) * (2 * g.M - 1) * g.heads;
+        const Range rx(x, act), rdy(dy, act), rsv(saved, s.saved), rdx(dx, act), rws(ws, s.bwd_ws);
+        const Range rwq(w_qkv, n_wq * e), rbq(b_qkv, n_bq * e), rwp(w_proj, n_wp * e), rbp(b_proj, (size_t)g.C * e);
+        const Range rtb(bias_table, n_tb * e);
+        const Range gwq(dw_qkv, n_wq * 4), gbq(db_qkv, n_bq * 4), gwp(dw_proj, n_wp * 4), gbp(db_proj, (size_t)g.C * 4);
+        const Range gtb(dbias_table, n_tb * 4);
+        // every output and the scratch: disjoint from every input and from each other
+        if (overlaps_any(rdx, rx, rdy, rsv, rws, rwq, rbq, rwp, rbp, rtb, gwq, gbq, gwp, gbp, gtb)) return GSWA_EINVAL;
+        if (overlaps_any(rws, rx, rdy, rsv, rwq, rbq, rwp, rbp, rtb, gwq, gbq, gwp, gbp, gtb)) return GSWA_EINVAL;
+        if (overlaps_any(gwq, rx, rdy, rsv, rwq, rbq, rwp, rbp, rtb, gbq, gwp, gbp, gtb)) return GSWA_EINVAL;
+        if (overlaps_any(gbq, rx, rdy, rsv, rwq, rbq, rwp, rbp, rtb, gwp, gbp, gtb)) return GSWA_EINVAL;
+        if (overlaps_any(gwp, rx, rdy, rsv, rwq, rbq, rwp, rbp, rtb, gbp, gtb)) return GSWA_EINVAL;
+        if (overlaps_any(gbp, rx, rdy, rsv, rwq, rbq, rwp, rbp, rtb, gtb)) return GSWA_EINVAL;
+        if (overlaps_any(gtb, rx, rdy, rsv, rwq, rbq, rwp, rbp, rtb)) return GSWA_EINVAL;
+    }
+    return GSWA_OK;
+}
+
+} // namespace
+
+int gswa::attn_forward_check(const gswa_desc *desc, const void *x, const void *w_qkv, const void *b_qkv, const void *w_proj,
+                             const void *b_proj, const void *bias_table, const void *y, const void *saved, const void *ws)
+{
+    Geom g;
+    Sizes s;
+    return check_forward(desc, x, w_qkv, b_qkv, w_proj, b_proj, bias_table, y, saved, ws, &g, &s);
+}
+
+int gswa::attn_backward_check(const gswa_desc *desc, const void *x, const void *dy, const void *w_qkv, const void *b_qkv,
+                              const void *w_proj, const void *b_proj, const void *bias_table, const void *saved,
+                              const void *dx, const void *dw_qkv, const void *db_qkv, const void *dw_proj,
+                              const void *db_proj, const void *dbias_table, const void *ws)
+{
+    Geom g;
+    Sizes s;
+    return check_backward(desc, x, dy, w_qkv, b_qkv, w_proj, b_proj, bias_table, saved, dx, dw_qkv, db_qkv, dw_proj, db_proj,
+                          dbias_table, ws, &g, &s);
+}
+
+int gswa::attn_forward(const gswa_desc *desc, const void *x, const void *w_qkv, const void *b_qkv,
+                 const void *w_proj, const void *b_proj, const void *bias_table, void *y,
+                 void *saved, void *ws, bool packed, void *hip_stream)
+{
+    Geom g;
+    Sizes s;
+    int rc = check_forward(desc, x, w_qkv, b_qkv, w_proj, b_proj, bias_table, y, saved, ws, &g, &s);
+    if (rc != GSWA_OK) return rc;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     if (s.window) {
         WindowLayerArgs a{};
@@ -453,35 +523,10 @@ int gswa_backward(const gswa_desc *desc, const void *x, const void *dy, const vo
                   void *hip_stream)
 {
     Geom g;
-    int rc = make_geom(desc, &g);
+    Sizes s;
+    int rc = check_backward(desc, x, dy, w_qkv, b_qkv, w_proj, b_proj, bias_table, saved, dx, dw_qkv, db_qkv, dw_proj, db_proj,
+                            dbias_table, ws, &g, &s);
     if (rc != GSWA_OK) return rc;
-    if (!x || !dy || !w_qkv || !b_qkv || !w_proj || !b_proj || !bias_table || !saved || !dx ||
-        !dw_qkv || !db_qkv || !dw_proj || !db_proj || !dbias_table)
-        return GSWA_EINVAL;
-    if (reinterpret_cast<uintptr_t>(ws) & 255) return GSWA_EINVAL;
-    if (!aligned16(x, dy, w_qkv, b_qkv, w_proj, bias_table, saved, dx, dw_qkv, db_qkv, dw_proj, db_proj,
-                   dbias_table))
-        return GSWA_EINVAL;
-    Sizes s = make_sizes(desc, g);
-    {
-        const size_t e = elem_size(desc), act = (size_t)g.T * g.C * e;
-        if (!ws && s.bwd_ws > 0) return GSWA_EINVAL;
-        const size_t n_wq = (size_t)g.groups * g.Rg * g.Cg, n_bq = (size_t)g.groups * g.Rg;
-        const size_t n_wp = (size_t)g.C * g.C, n_tb = (size_t)(2 * g.M - 1) * (2 * g.M - 1) * g.heads;
-        const Range rx(x, act), rdy(dy, act), rsv(saved, s.saved), rdx(dx, act), rws(ws, s.bwd_ws);
-        const Range rwq(w_qkv, n_wq * e), rbq(b_qkv, n_bq * e), rwp(w_proj, n_wp * e), rbp(b_proj, (size_t)g.C * e);
-        const Range rtb(bias_table, n_tb * e);
-        const Range gwq(dw_qkv, n_wq * 4), gbq(db_qkv, n_bq * 4), gwp(dw_proj, n_wp * 4), gbp(db_proj, (size_t)g.C * 4);
-        const Range gtb(dbias_table, n_tb * 4);
-        // every output and the scratch: disjoint from every input and from each other
-        if (overlaps_any(rdx, rx, rdy, rsv, rws, rwq, rbq, rwp, rbp, rtb, gwq, gbq, gwp, gbp, gtb)) return GSWA_EINVAL;
-        if (overlaps_any(rws, rx, rdy, rsv, rwq, rbq, rwp, rbp, rtb, gwq, gbq, gwp, gbp, gtb)) return GSWA_EINVAL;
-        if (overlaps_any(gwq, rx, rdy, rsv, rwq, rbq, rwp, rbp, rtb, gbq, gwp, gbp, gtb)) return GSWA_EINVAL;
-        if (overlaps_any(gbq, rx, rdy, rsv, rwq, rbq, rwp, rbp, rtb, gwp, gbp, gtb)) return GSWA_EINVAL;
-        if (overlaps_any(gwp, rx, rdy, rsv, rwq, rbq, rwp, rbp, rtb, gbp, gtb)) return GSWA_EINVAL;
-        if (overlaps_any(gbp, rx, rdy, rsv, rwq, rbq, rwp, rbp, rtb, gtb)) return GSWA_EINVAL;
-        if (overlaps_any(gtb, rx, rdy, rsv, rwq, rbq, rwp, rbp, rtb)) return GSWA_EINVAL;
-    }
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     if (s.window) {
         WindowLayerArgs a{};

@@ -34,6 +34,15 @@ int make_geom(const gswa_desc *d, Geom *g);
 int attn_forward(const gswa_desc *d, const void *x, const void *w_qkv, const void *b_qkv, const void *w_proj, const void *b_proj,
                  const void *bias_table, void *y, void *saved, void *ws, bool packed, void *hip_stream);
 
+// The rules of gswa_forward's and gswa_backward's arguments alone (nothing is enqueued): for callers that run the
+// attention layer inside a kernel of their own.
+int attn_forward_check(const gswa_desc *d, const void *x, const void *w_qkv, const void *b_qkv, const void *w_proj,
+                       const void *b_proj, const void *bias_table, const void *y, const void *saved, const void *ws);
+int attn_backward_check(const gswa_desc *d, const void *x, const void *dy, const void *w_qkv, const void *b_qkv,
+                        const void *w_proj, const void *b_proj, const void *bias_table, const void *saved, const void *dx,
+                        const void *dw_qkv, const void *db_qkv, const void *dw_proj, const void *db_proj,
+                        const void *dbias_table, const void *ws);
+
 // Vectors of parameter gradients a backward launch leaves at most (= its workgroups).
 constexpr int kWindowLayerVectors = 256;
 

@@ -310,3 +310,36 @@ def test_fused_path_memory_does_not_grow_with_the_group_count():
     # narrow layers: strictly falling from one group to two and to three
     t = [sum(gswa.gswa_query_bytes(gswa.make_desc(32, 64, 64, 60, 6, G, 8, 4, "bf16"))[::2]) for G in (1, 2, 3)]
     assert t[0] > t[1] > t[2]
+
+
+@pytest.mark.parametrize("change", [dict(dtype="f32"), dict(H=24, W=24, window=12, shift=6, heads=4, dqk=4)],
+                         ids=["fp32 8x8", "bf16 12x12"])
+def test_whole_layers_reject_what_their_attention_layer_rejects(change):
+    """The attention layer's parameters and their gradients may overlap neither the scratch nor the saved state nor each
+    other, also where the whole layer runs in one launch and the attention entry points are not called."""
+    from paper_2409_06206_amd import astl
+    case = {**GOOD, "hidden": 120, **change}
+    desc = astl.make_desc(**case)
+    act = (case["B"] * case["H"] * case["W"] * case["C"] * (4 if case["dtype"] == "f32" else 2) + 255) // 256 * 256
+    addr = _spread(6 + 2 * len(astl.PARAM_FIELDS))
+    x, dy, y, dx, saved, ws = addr[:6]
+    params = dict(zip(astl.PARAM_FIELDS, addr[6:]))
+    grads = dict(zip(astl.PARAM_FIELDS, addr[6 + len(params):]))
+
+    def rejected(call, *args):
+        with pytest.raises(gswa.GswaError) as ei:
+            call(desc, *args, stream=0)
+        assert ei.value.status == gswa.GSWA_EINVAL
+
+    fwd = lambda p=params, s=saved, w=ws: rejected(astl.astl_forward, x, p, y, s, w)
+    fwd(p={**params, "w_proj": ws + act + 256})              # a weight inside the scratch
+    fwd(p={**params, "b_qkv": ws + 2 * act + 256}, s=None)  # the same at inference
+    fwd(p={**params, "bias_table": saved + act + 512})       # the bias table inside the saved state
+    fwd(s=ws + act)                                          # saved state over the scratch
+
+    bwd = lambda p=params, g=grads, s=saved, w=ws: rejected(astl.astl_backward, x, dy, p, s, dx, g, w)
+    bwd(g={**grads, "w_qkv": ws + 256})                      # a gradient inside the scratch
+    bwd(g={**grads, "b_proj": grads["w_proj"] + 60 * 60 * 4 - 16})  # two gradients share bytes
+    bwd(g={**grads, "bias_table": params["w_qkv"] + 16})     # a gradient over a weight
+    bwd(g={**grads, "w_proj": saved + act + 256})            # a gradient over the saved state
+    bwd(w=params["w_proj"] - 3 * act)                        # the scratch over a weight
