@@ -795,6 +795,14 @@ __device__ __forceinline__ void put_tile(float *dw, float *db, int ld, int row0,
     for (int i = 0; i < 4; ++i) put_grad(p + i * step, v[i], first);
 }
 
+// four channels (piece k of 16) of a token's row of dn, fp32; the pieces of a row are exchanged so that 16 rows written at
+// the same channels fall on different banks
+template <class S> __device__ __forceinline__ float *dn_piece(float *dn, int t, int k)
+{
+    static_assert(S::CTC == 4, "16 pieces a row");
+    return dn + (sizeof(typename S::E) == 4 ? S::PC : 64) * t + 4 * (k ^ (t & 15));
+}
+
 template <class S, bool LAYER>
 __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArgs a)
 {
@@ -806,6 +814,9 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
     E *X = reinterpret_cast<E *>(lds), *A = reinterpret_cast<E *>(lds + S::SZ_ROW), *DX = reinterpret_cast<E *>(lds + 2 * S::SZ_ROW);
     E *R = reinterpret_cast<E *>(lds + S::B_R), *DO = reinterpret_cast<E *>(lds + S::B_DO), *FO = reinterpret_cast<E *>(lds + S::B_FO);
     E *Hh = reinterpret_cast<E *>(lds + S::B_H), *DP = reinterpret_cast<E *>(lds + S::B_H + S::SZ_H);
+    constexpr bool DN_IN_X = sizeof(E) == 4;
+    float *DN = reinterpret_cast<float *>(DN_IN_X ? X : Hh);
+    static_assert(DN_IN_X || sizeof(float) * S::N * 16 * S::CTC <= S::SZ_H, "dn in the hidden layer's place");
     float *tb = reinterpret_cast<float *>(lds + S::bwd_tb(LAYER));
     float *lse = tb + S::HEADS * S::TBP, *delta = lse + S::HG * S::N; // (delta: negative)
     float *red = lse;  // [WAVES][2][CP]
@@ -916,26 +927,32 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
                 }
             }
             __syncthreads();
-            // ---- dn = dpre W1 (into X);  d Wfc1 = dpre^T LN_2(x1);  d Wfc2 = dy^T h ----
+            // ---- d Wfc1 = dpre^T LN_2(x1);  d Wfc2 = dy^T h;  dn = dpre W1 ----
             // (weight gradients two column tiles at a time: they share the reading of the row tile)
+            // dn is the start of LN_2's adjoint and its gamma / beta sums and stays in fp32.  X has the place for it where
+            // rows are fp32; otherwise it goes where the hidden layer was, when that has been read.
             constexpr int U0 = S::CTC * S::TU, U1 = U0 + S::HFT * up(S::CTC, 2), U2 = U1 + S::CTC * up(S::HFT, 2);
             static_assert(S::CTC % 2 == 0 && S::HFT % 2 == 0, "pairs of column tiles");
+            auto dn_unit = [&](int u) {
+                FRESH_LANE;
+                const int ct = u / S::TU, tu = u - ct * S::TU, c = 16 * ct + l16;
+                WeightsT<E, S::HID> wf;
+                wf.load(static_cast<const T *>(a.w_fc1) + (c < S::C ? c : 0), S::C, q);
+                loads_issued();
+#pragma unroll
+                for (int tt = 0; tt < S::TT; ++tt) {
+                    const int t = 16 * (tu * S::TT + tt) + l16;
+                    f32x4 acc = zero4();
+#pragma unroll
+                    for (int s = 0; s < S::HFT; ++s) acc = mma(wf.op(s, q), O::ld(DP + t * S::PH + 16 * s + 4 * q), acc);
+                    *reinterpret_cast<f32x4 *>(dn_piece<S>(DN, t, 4 * ct + q)) = acc;
+                }
+            };
 #pragma unroll 1
-            for (int u = wv; u < U2; u += S::WAVES) {
+            for (int u = DN_IN_X ? wv : U0 + wv; u < U2; u += S::WAVES) {
                 FRESH_LANE;
                 if (u < U0) {
-                    const int ct = u / S::TU, tu = u - ct * S::TU, c = 16 * ct + l16;
-                    WeightsT<E, S::HID> wf;
-                    wf.load(static_cast<const T *>(a.w_fc1) + (c < S::C ? c : 0), S::C, q);
-                    loads_issued();
-#pragma unroll
-                    for (int tt = 0; tt < S::TT; ++tt) {
-                        const int t = 16 * (tu * S::TT + tt) + l16;
-                        f32x4 acc = zero4();
-#pragma unroll
-                        for (int s = 0; s < S::HFT; ++s) acc = mma(wf.op(s, q), O::ld(DP + t * S::PH + 16 * s + 4 * q), acc);
-                        O::st(X + t * S::PC + 16 * ct + 4 * q, acc);
-                    }
+                    dn_unit(u);
                 } else if (u < U1) {
                     const int v = u - U0, ft = v / (S::CTC / 2), ct = 2 * (v - ft * (S::CTC / 2));
                     f32x4 acc[2] = {zero4(), zero4()};
@@ -963,6 +980,11 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
                 }
             }
             __syncthreads();
+            if (!DN_IN_X) {
+#pragma unroll 1
+                for (int u = wv; u < U0; u += S::WAVES) dn_unit(u);
+                __syncthreads();
+            }
         }
         // ---- rows: with the whole layer LN_2's adjoint and the skip of Eq. 5 (DX: dx1), LN_1(x) (X); A: group outputs ----
         {
@@ -994,12 +1016,12 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
                     const long tok = win.token(t) * S::C + 4 * l16;
                     f32x4 f = O::wide(O::pick(in, rx[k]));
                     const f32x4 at = O::wide(O::pick(in, ra[k]));
-                    E *xr = X + t * S::PC + 4 * l16, *dr = DX + t * S::PC + 4 * l16;
+                    E *dr = DX + t * S::PC + 4 * l16;
                     float mean, rstd;
                     if (LAYER) {
                         const f32x4 u = O::wide(O::pick(in, ru[k]));
                         stats<S>(u, in, a.eps, mean, rstd);
-                        f32x4 d = O::wide(O::ld(xr)), xh;
+                        f32x4 d = *reinterpret_cast<const f32x4 *>(dn_piece<S>(DN, t, l16)), xh;
                         float s1 = 0.f, s2 = 0.f;
 #pragma unroll
                         for (int i = 0; i < 4; ++i) {
@@ -1029,9 +1051,9 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
                 }
             }
             if (LAYER) leave_row_sums(sg, sb);
-            put_mask<S>(win, R);
         }
         __syncthreads();
+        put_mask<S>(win, R); // (not before: dn lies there)
         if (LAYER) finish_row_sums(S::P_G2, S::P_E2, first);
 
 #pragma unroll 1

@@ -577,3 +577,30 @@ def test_an_image_gives_the_same_bits_alone_and_in_a_batch(case, copies):
         got.append((y, st.y[:1].clone(), st.dx[:1].clone()))
     for name, alone, batch in zip(("inference y", "y", "dx"), *got):
         assert torch.equal(alone, batch), name
+
+
+def test_gradient_at_the_second_layer_norm_stays_in_fp32():
+    """A whole layer with 12x12 windows whose numbers up to d LN_2 are all exact: dy = 1, GELU' = 1 (b_fc1 = 16), and W1, W2
+    so that every entry of the gradient at LN_2's output is 1 + 15/4096, which bf16 rounds to 1.  Its sum over the
+    tokens is d ln2_b: fp32 keeps it to 208 additions of 2^-24 (1.3e-5) and GELU' in fp32, one rounding to bf16 costs
+    3.7e-3."""
+    from paper_2409_06206_amd import runner
+    import torch
+    C, hidden = 60, 120
+    p = synth.astl_params(C, 4, 2, 12, hidden, 300, "stress", 4)
+    eye = np.eye(C, dtype=np.float32)
+    p["w_fc1"] = np.concatenate([eye, eye * (15.0 / 4096.0)])
+    p["w_fc2"] = np.concatenate([eye, eye], axis=1)
+    p["b_fc1"] = np.full(hidden, 16.0, dtype=np.float32)
+    p["ln2_w"], p["ln2_b"] = np.ones(C, dtype=np.float32), np.zeros(C, dtype=np.float32)
+    p = {k: synth.quantize(v, "bf16") for k, v in p.items()}
+    blk = runner.DeviceBlock(1, 12, 12, C, 4, 2, 12, 6, "bf16", hidden, dqk=4)
+    blk.set_params(p)
+    x, _ = synth.activations(1, 12, 12, C, 3)
+    blk.set_inputs(synth.quantize(x, "bf16"), np.ones((1, 12, 12, C), dtype=np.float32))
+    print("forward, backward", flush=True)
+    blk.forward()
+    blk.backward()
+    torch.cuda.synchronize()
+    want = np.full(C, 144.0 * (1.0 + 15.0 / 4096.0))
+    assert parity.rel_err(blk.results()["dln2_b"], want) <= 2e-5
