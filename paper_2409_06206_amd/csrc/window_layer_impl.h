@@ -63,8 +63,8 @@ template <typename T_, int C_, int HEADS_, int G_, int M_, int DQ_, int HID_, in
     static constexpr int KUX = up(XW, 16), CTX = up(OC < XW ? XW : XW + 1, 16);
     static __device__ __forceinline__ int xcol(int c) { return CGP == CG ? c : c / CG * CGP + c % CG; }
     // (a slice's last k-slots and column tiles may run into the next row: numbers that meet zero weights or are dropped)
-    static constexpr int PC = pitch_of(imax(16 * up(C + 1, 16), XW)), PR = pitch_of(sizeof(E) == 2 ? RP + 8 : RP), PD = pitch_of(RV), PH = pitch_of(16 * up(HID + 1, 16));
-    // (behind q|k|v a row holds its token's part of the shift mask: as a key, as a query)
+    static constexpr int PC = pitch_of(imax(16 * up(C + 1, 16), XW)), PR = pitch_of(sizeof(E) == 2 ? RP + 12 : RP), PD = pitch_of(RV), PH = pitch_of(16 * up(HID + 1, 16));
+    // (behind q|k|v a row holds its token's part of the shift mask: as a key; as a query, the rounded factor and the rest)
     static constexpr int MK = RP, MQ = RP + 4;
     static constexpr int PF = N + 4; // pitch of a head's matrix of score gradients
     static constexpr int NTB = 2 * M - 1, NTBL = NTB * NTB, TBP = (NTBL + 3) & ~3;
@@ -183,10 +183,11 @@ template <> struct Op<bf16_t> {
 
 // One head's slice of a row as an operand: HS channels (a multiple of four, at most 16).
 //
-// Q and K operands (HS <= 12) carry the shift mask with them.  With r, c = "past the wrap in the last window row, column"
+// Q and K operands (HS <= 8) carry the shift mask with them.  With r, c = "past the wrap in the last window row, column"
 // of a token, [regions of n and m differ] = (r_n|c_n) + (1-2 r_n)(1-c_n) r_m + (1-2 c_n)(1-r_n) c_m
 // - (1-2 r_n)(1-2 c_n) r_m c_m: four more k-slots, (1, r, c, rc) of the key against those coefficients of the query
-// times -100 log2(e).  In bf16 they take the slots 12 .. 15 that no head uses, at no cost.  In fp32, where adding and
+// times -100 log2(e).  In bf16 they take the slots 12 .. 15 that no head uses, with the factor rounded to bf16 (144), and
+// the slots 8 .. 11 with what the rounding left (0.2695): together -100.00002, at no cost.  In fp32, where adding and
 // taking away 144 would cost the scores their last bits, masked windows add the mask on the vector ALU.
 template <typename E, int HS> struct HeadOp;
 template <int HS> struct HeadOp<float, HS> { // product i takes channels 4i .. 4i+3: HS / 4 products instead of four
@@ -210,19 +211,19 @@ template <int HS> struct HeadOp<bf16_t, HS> { // (slots beyond the head: any num
     __device__ __forceinline__ void mask(int q) { v = make_uint2(4 * q < HS ? v.x : 0u, 4 * q < HS ? v.y : 0u); }
 };
 template <int HS> __device__ __forceinline__ f32x4 mma(const HeadOp<bf16_t, HS> &a, const HeadOp<bf16_t, HS> &b, f32x4 c) { return mma16(a.v, b.v, c); }
-// q or k of a head: `row` is the token's row, `col` the head's column, `mcol` the column of the mask's part
+// q (`query`) or k of a head: `row` is the token's row, `col` the head's column
 template <class S> struct QkOp : HeadOp<typename S::E, S::HSQ> {
     static constexpr bool SLOTS = sizeof(typename S::E) == 2;
-    static_assert(!SLOTS || S::HSQ <= 12, "slots 12 .. 15 are the mask's");
-    __device__ __forceinline__ void load(const typename S::E *row, int col, int mcol, int q)
+    static_assert(!SLOTS || S::HSQ <= 8, "slots 8 .. 15 are the mask's");
+    __device__ __forceinline__ void load(const typename S::E *row, int col, bool query, int q)
     {
-        if constexpr (SLOTS) this->v = *reinterpret_cast<const uint2 *>(row + (q == 3 ? mcol : col + (4 * q < S::HSQ ? 4 * q : 0)));
+        if constexpr (SLOTS) this->v = *reinterpret_cast<const uint2 *>(row + (q < 2 ? col + (4 * q < S::HSQ ? 4 * q : 0) : query ? S::MQ + 4 * (3 - q) : S::MK));
         else HeadOp<typename S::E, S::HSQ>::load(row + col, q);
     }
     __device__ __forceinline__ void mask(int q)
     {
         if constexpr (SLOTS) { // (which of the four slot groups count, as bits)
-            const uint32_t m = 0u - (((8u | ((1u << S::HSQ / 4) - 1u)) >> q) & 1u);
+            const uint32_t m = 0u - (((12u | ((1u << S::HSQ / 4) - 1u)) >> q) & 1u);
             this->v = make_uint2(this->v.x & m, this->v.y & m);
         }
     }
@@ -501,9 +502,11 @@ template <class S> __device__ __forceinline__ void put_mask(const Window<S> &win
     if (!QkOp<S>::SLOTS) return;
     for (int t = threadIdx.x; t < S::N; t += S::NTH) {
         const int reg = win.region(t);
-        const float r = reg & 1 ? 1.f : 0.f, c = reg & 2 ? 1.f : 0.f, m = -100.f * kLog2e;
+        const float r = reg & 1 ? 1.f : 0.f, c = reg & 2 ? 1.f : 0.f, hi = -144.f, lo = -100.f * kLog2e - hi;
+        const f32x4 coef = {r + c - r * c, (1.f - 2.f * r) * (1.f - c), (1.f - 2.f * c) * (1.f - r), -(1.f - 2.f * r) * (1.f - 2.f * c)};
         O::st(R + t * S::PR + S::MK, f32x4{1.f, r, c, r * c});
-        O::st(R + t * S::PR + S::MQ, f32x4{m * (r + c - r * c), m * (1.f - 2.f * r) * (1.f - c), m * (1.f - 2.f * c) * (1.f - r), -m * (1.f - 2.f * r) * (1.f - 2.f * c)});
+        O::st(R + t * S::PR + S::MQ, hi * coef);
+        O::st(R + t * S::PR + S::MQ + 4, lo * coef);
     }
 }
 
@@ -635,7 +638,7 @@ __global__ __launch_bounds__(S::NTH) void window_layer_fwd_kernel(WindowLayerArg
                 const int hl = u / S::NT, nt = u - hl * S::NT, tq = 16 * nt + l16;
                 const float *tbh = tb + (gi * S::HG + hl) * S::TBP;
                 QkOp<S> qf;
-                qf.load(R + tq * S::PR, hl * S::HSQ, S::MQ, q);
+                qf.load(R + tq * S::PR, hl * S::HSQ, true, q);
                 qf.mask(q);
                 const int oq = key_offset<S>(tq) + (S::M - 1) * (S::NTB + 1);
                 f32x4 st[S::NT];
@@ -643,7 +646,7 @@ __global__ __launch_bounds__(S::NTH) void window_layer_fwd_kernel(WindowLayerArg
 #pragma unroll
                 for (int kt = 0; kt < S::NT; ++kt) {
                     QkOp<S> kf;
-                    kf.load(R + (16 * kt + 15 - l16) * S::PR, S::RQ + hl * S::HSQ, S::MK, q);
+                    kf.load(R + (16 * kt + 15 - l16) * S::PR, S::RQ + hl * S::HSQ, false, q);
                     const float *bias = tbh + oq - key_offset4<S>(kt, 3 - q) - 3;
                     st[kt] = mma(kf, qf, f32x4{bias[0], bias[1], bias[2], bias[3]});
                 }
@@ -1128,7 +1131,7 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
                 const float *tbh = tb + (gi * S::HG + hl) * S::TBP;
                 QkOp<S> qf;
                 HeadOp<E, S::HSV> of;
-                qf.load(R + tq * S::PR, hl * S::HSQ, S::MQ, q);
+                qf.load(R + tq * S::PR, hl * S::HSQ, true, q);
                 of.load(DO + tq * S::PD + hl * S::HSV, q);
                 qf.mask(q);
                 of.mask(q);
@@ -1139,7 +1142,7 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
                 for (int kt = 0; kt < S::NT; ++kt) {
                     QkOp<S> kf;
                     HeadOp<E, S::HSV> vf;
-                    kf.load(R + (16 * kt + 15 - l16) * S::PR, S::RQ + hl * S::HSQ, S::MK, q);
+                    kf.load(R + (16 * kt + 15 - l16) * S::PR, S::RQ + hl * S::HSQ, false, q);
                     vf.load(R + (16 * kt + 15 - l16) * S::PR + 2 * S::RQ + hl * S::HSV, q);
                     const float *bias = tbh + oq - key_offset4<S>(kt, 3 - q) - 3;
                     st[kt] = mma(kf, qf, f32x4{bias[0], bias[1], bias[2], bias[3]});
@@ -1242,7 +1245,7 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
                 const float *tbh = tb + (gi * S::HG + hl) * S::TBP;
                 QkOp<S> kf;
                 HeadOp<E, S::HSV> vf;
-                kf.load(R + tk * S::PR, S::RQ + hl * S::HSQ, S::MK, q);
+                kf.load(R + tk * S::PR, S::RQ + hl * S::HSQ, false, q);
                 vf.load(R + tk * S::PR + 2 * S::RQ + hl * S::HSV, q);
                 kf.mask(q);
                 vf.mask(q);
@@ -1251,7 +1254,7 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
                 for (int nt = 0; nt < S::NT; ++nt) {
                     QkOp<S> qf;
                     HeadOp<E, S::HSV> of;
-                    qf.load(R + (16 * nt + l16) * S::PR, hl * S::HSQ, S::MQ, q);
+                    qf.load(R + (16 * nt + l16) * S::PR, hl * S::HSQ, true, q);
                     of.load(DO + (16 * nt + l16) * S::PD + hl * S::HSV, q);
                     const f32x4 ls = *reinterpret_cast<const f32x4 *>(lse + hl * S::N + 16 * nt + 4 * q);
                     const f32x4 dl = *reinterpret_cast<const f32x4 *>(delta + hl * S::N + 16 * nt + 4 * q);

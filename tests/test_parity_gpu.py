@@ -467,3 +467,22 @@ def test_fp32_layers_one_workgroup_per_window(oracle, groups, shape, shift):
 def test_12x12_windows_one_workgroup_per_window(oracle, heads, groups, dqk, shape, shift):
     """bf16 attention layers with 12x12 windows: the organisations of the heads that no other test runs."""
     parity.check_case(oracle, *shape, 60, heads, groups, 12, shift, "bf16", regime="stress", dqk=dqk)
+
+
+@pytest.mark.parametrize("heads,groups,dqk", [(4, 1, 4), (4, 2, 8), (6, 3, 4)])
+def test_shift_mask_of_12x12_windows_is_minus_100(oracle, heads, groups, dqk):
+    """One 12x12 window cut in half by the shift, no queries or keys, a bias of 100 between tokens six and more rows
+    apart: they lie on both sides of the cut, so bias and mask cancel, and any other mask (-99.8 is what -100 log2(e)
+    becomes in bf16) gives them other weights than the tokens of the query's own side."""
+    B, H, W, C, window, shift = 1, 12, 12, 60, 12, 6
+    x, dy, p = parity.make_inputs(B, H, W, C, heads, groups, window, "bf16", synth.LAYER_SEED0, "stress", dqk)
+    hg = heads // groups
+    p["w_qkv"][:, :2 * hg * dqk], p["b_qkv"][:, :2 * hg * dqk] = 0.0, 0.0
+    rows = np.arange((2 * window - 1) ** 2) // (2 * window - 1) - (window - 1)
+    p["table"][:] = np.where(np.abs(rows) >= 6, 100.0, 0.0)[:, None]
+    x += np.where(np.arange(H) < 6, 1.0, -1.0)[None, :, None, None]
+    x = synth.quantize(x, "bf16")
+    want = parity.oracle_results(oracle, x, dy, p, heads, groups, window, shift, dqk=dqk)
+    got, _ = parity.gpu_results(x, dy, p, heads, groups, window, shift, "bf16", dqk=dqk)
+    errs = {k: parity.rel_err(got[k], want[k]) for k in ("y", "dx")}
+    assert max(errs.values()) <= parity.TOL["bf16"], errs
