@@ -562,11 +562,17 @@ template <class S> __device__ __forceinline__ void qkv_unit(const WindowLayerArg
         typename O::F f[S::KUG];
 #pragma unroll
         for (int s = 0; s < S::KUG; ++s) f[s] = O::ld(X + t * S::PC + gi * S::CGP + 16 * s + 4 * q);
-        if (casc) {
-#pragma unroll
-            for (int s = 0; s < S::KUG; ++s) f[s] = O::add(f[s], O::ld(A + t * S::PC + (gi - 1) * S::CGP + 16 * s + 4 * q));
-        }
         f32x4 acc = zero4();
+        if (casc) {
+            // (Groups of an odd number of channels: W x + W o instead of W (x + o), whose sum would be rounded.  The
+            // one-kernel-per-step path adds these in fp32; with the sum rounded four groups lose a fifth of their digits.)
+#pragma unroll
+            for (int s = 0; s < S::KUG; ++s) {
+                const typename O::F o = O::ld(A + t * S::PC + (gi - 1) * S::CGP + 16 * s + 4 * q);
+                if (sizeof(typename S::E) == 2 && S::CG % 2 != 0) acc = mma(wf.op(s, q), o, acc);
+                else f[s] = O::add(f[s], o);
+            }
+        }
 #pragma unroll
         for (int s = 0; s < S::KUG; ++s) acc = mma(wf.op(s, q), f[s], acc);
 #pragma unroll

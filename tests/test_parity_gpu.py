@@ -486,3 +486,24 @@ def test_shift_mask_of_12x12_windows_is_minus_100(oracle, heads, groups, dqk):
     got, _ = parity.gpu_results(x, dy, p, heads, groups, window, shift, "bf16", dqk=dqk)
     errs = {k: parity.rel_err(got[k], want[k]) for k in ("y", "dx")}
     assert max(errs.values()) <= parity.TOL["bf16"], errs
+
+
+@pytest.mark.parametrize("dqk", [4, 8])
+def test_cascade_of_odd_groups_is_added_in_fp32(oracle, dqk):
+    """12x12 windows, four groups of 15 channels, no queries or keys: group 0 puts out delta = 15/4096 everywhere, group 1
+    holds +1 and -1 by turns and its values are sums of a pair, so they are 2 delta; with x + O_0 rounded to bf16 on the
+    way they would be 2^-8, half as much.  What is left are the roundings of v, of the group's output and of y, 2^-9 each."""
+    C, groups, window, Cg = 60, 4, 12, 15
+    p = {k: np.zeros(s, dtype=np.float32) for k, s in synth.param_shapes(C, 4, groups, window, dqk).items()}
+    p["w_qkv"][0, 2 * dqk:] = np.eye(Cg)
+    for i in range(14):
+        p["w_qkv"][1, 2 * dqk + i, [i - i % 2, i - i % 2 + 1]] = 1.0
+    p["w_proj"][:] = np.eye(C)
+    x = np.zeros((1, 24, 24, C), dtype=np.float32)
+    x[..., :Cg] = 15.0 / 4096.0
+    x[..., Cg:2 * Cg - 1] = np.where(np.arange(14) % 2 == 0, 1.0, -1.0)
+    want = oracle.forward(x, p["w_qkv"], p["b_qkv"], p["w_proj"], p["b_proj"], p["table"], heads=4, groups=groups,
+                          window=window, shift=6, dqk=dqk)[..., Cg:2 * Cg]
+    got, _ = parity.gpu_results(x, None, p, 4, groups, window, 6, "bf16", backward=False, dqk=dqk)
+    assert abs(want.max() - 30.0 / 4096.0) <= 1e-9
+    assert parity.rel_err(got["y"][..., Cg:2 * Cg], want) <= 3 * parity.U_BF16
