@@ -1125,12 +1125,13 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
             __syncthreads();
             constexpr int UA = S::HG * S::NT, PA = up(UA, S::WAVES);
             // ---- query role: softmax, delta, dQ ----
-            f32x4 dq[PA];
+            F dq[PA]; // (held as what LDS gets of them: a wave of a layer with one group holds five, and six dK and dV)
 #pragma unroll
             for (int k = 0; k < PA; ++k) {
                 __builtin_amdgcn_sched_barrier(0);
                 FRESH_LANE;
-                dq[k] = zero4();
+                dq[k] = F{};
+                f32x4 acc = zero4();
                 const int u = wv + k * S::WAVES;
                 if (u >= UA) continue;
                 const int hl = u / S::NT, nt = u - hl * S::NT, tq = 16 * nt + l16;
@@ -1182,9 +1183,9 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
                     f32x4 ds;
 #pragma unroll
                     for (int i = 0; i < 4; ++i) ds[i] = st[kt][i] * (dp[kt][i] - dl);
-                    dq[k] = mma(O::ld_tr(R + 16 * kt * S::PR + S::RQ + hl * S::HSQ, S::PR, q, l16), O::from(ds), dq[k]);
+                    acc = mma(O::ld_tr(R + 16 * kt * S::PR + S::RQ + hl * S::HSQ, S::PR, q, l16), O::from(ds), acc);
                 }
-                dq[k] *= inv * qscale;
+                dq[k] = O::from(acc * (inv * qscale));
             }
             __syncthreads();
             // The bias-table gradient of a head.  A lane owns the offset (dr, dc), 0 <= dr, dc < M, of a query from its key,
@@ -1234,7 +1235,7 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
             // wavefronts without a tile do meanwhile. ----
             constexpr int UR = S::NF * S::NT, PR_ = up(UR, S::WAVES), SPARE = UR < S::WAVES ? S::WAVES - UR : S::WAVES;
             constexpr bool DIRECT = S::ROUNDS == 1;
-            f32x4 dk[S::ROUNDS * PR_], dv[S::ROUNDS * PR_];
+            F dk[S::ROUNDS * PR_], dv[S::ROUNDS * PR_];
 #pragma unroll
             for (int round = 0; round < S::ROUNDS; ++round) {
                 F ds[PR_][S::NT];
@@ -1243,7 +1244,8 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
                 __builtin_amdgcn_sched_barrier(0);
                 FRESH_LANE;
                 const int k = round * PR_ + j;
-                dk[k] = dv[k] = zero4();
+                dk[k] = dv[k] = F{};
+                f32x4 ak = zero4(), av = zero4();
                 const int u = wv + j * S::WAVES, slot = u / S::NT, hl = round * S::NF + slot;
                 if (u >= UR || hl >= S::HG) continue;
                 const int kt = u - slot * S::NT, tk = 16 * kt + l16;
@@ -1275,9 +1277,11 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
                     }
                     ds[j][nt] = O::from(d);
                     if (DIRECT) *reinterpret_cast<F *>(fo + 16 * nt + 4 * q) = ds[j][nt]; // [key][query]: four queries of a key
-                    dv[k] = mma(O::ld_t(DO + 16 * nt * S::PD + hl * S::HSV, S::PD, q, l16), O::from(p), dv[k]);
-                    dk[k] = mma(O::ld_t(R + 16 * nt * S::PR + hl * S::HSQ, S::PR, q, l16), ds[j][nt], dk[k]);
+                    av = mma(O::ld_t(DO + 16 * nt * S::PD + hl * S::HSV, S::PD, q, l16), O::from(p), av);
+                    ak = mma(O::ld_t(R + 16 * nt * S::PR + hl * S::HSQ, S::PR, q, l16), ds[j][nt], ak);
                 }
+                dk[k] = O::from(ak * (1.f / kLog2e));
+                dv[k] = O::from(av);
             }
                 if (!DIRECT) {
                     if (round > 0)
@@ -1304,7 +1308,7 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
                 FRESH_LANE;
                 const int u = wv + k * S::WAVES, hl = u / S::NT, tt = u - hl * S::NT, t = 16 * tt + l16;
                 if (u >= UA) continue;
-                if (4 * q < S::HSQ) O::st(R + t * S::PR + hl * S::HSQ + 4 * q, dq[k]);
+                if (4 * q < S::HSQ) *reinterpret_cast<F *>(R + t * S::PR + hl * S::HSQ + 4 * q) = dq[k];
             }
 #pragma unroll
             for (int k = 0; k < S::ROUNDS * PR_; ++k) {
@@ -1312,8 +1316,8 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
                 const int round = k / PR_, u = wv + (k - round * PR_) * S::WAVES, slot = u / S::NT, hl = round * S::NF + slot;
                 if (u >= UR || hl >= S::HG) continue;
                 const int t = 16 * (u - slot * S::NT) + l16;
-                if (4 * q < S::HSQ) O::st(R + t * S::PR + S::RQ + hl * S::HSQ + 4 * q, dk[k] * (1.f / kLog2e));
-                if (4 * q < S::HSV) O::st(R + t * S::PR + 2 * S::RQ + hl * S::HSV + 4 * q, dv[k]);
+                if (4 * q < S::HSQ) *reinterpret_cast<F *>(R + t * S::PR + S::RQ + hl * S::HSQ + 4 * q) = dk[k];
+                if (4 * q < S::HSV) *reinterpret_cast<F *>(R + t * S::PR + 2 * S::RQ + hl * S::HSV + 4 * q) = dv[k];
             }
             __syncthreads();
             // ---- table gradient, dF = d(q|k|v) Wqkv, d Wqkv = d(q|k|v)^T F ----

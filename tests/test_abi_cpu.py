@@ -343,3 +343,43 @@ def test_whole_layers_reject_what_their_attention_layer_rejects(change):
     bwd(g={**grads, "bias_table": params["w_qkv"] + 16})     # a gradient over a weight
     bwd(g={**grads, "w_proj": saved + act + 256})            # a gradient over the saved state
     bwd(w=params["w_proj"] - 3 * act)                        # the scratch over a weight
+
+
+def _kernels(path):
+    """Name and register facts of every gfx950 kernel in a shared library: the metadata note of each code object in it."""
+    import msgpack
+    import struct
+    with open(path, "rb") as f:
+        blob = f.read()
+    at = blob.find(b"\x7fELF", 4)
+    while at >= 0:
+        e = memoryview(blob)[at:]
+        at = blob.find(b"\x7fELF", at + 4)
+        if bytes(e[18:20]) != b"\xe0\x00":          # (machine: AMDGPU)
+            continue
+        shoff, = struct.unpack_from("<Q", e, 40)
+        size, count = struct.unpack_from("<HH", e, 58)
+        for i in range(count):
+            head = struct.unpack_from("<IIQQQQ", e, shoff + i * size)
+            if head[1] != 7:                        # (a section of notes)
+                continue
+            p, end = head[4], head[4] + head[5]
+            while p < end:
+                name, desc, kind = struct.unpack_from("<III", e, p)
+                p += 12 + (name + 3) // 4 * 4
+                if kind == 32:
+                    yield from msgpack.unpackb(bytes(e[p:p + desc]))["amdhsa.kernels"]
+                p += (desc + 3) // 4 * 4
+
+
+def test_kernels_do_not_spill_vector_registers():
+    """With matrix-core results kept in the architectural registers a spill costs scratch traffic, and the compiler's
+    handling of it has been wrong once.  These five hold more than fits and spill a few; no other kernel may."""
+    from paper_2409_06206_amd import build
+    known = {("wave_fwd_kernel", "Li60ELi6ELi1E"): 7, ("wgrad_mfma_kernel", ""): 4, ("window_fwd_kernel", "Li9ELi1ELi4E"): 8,
+             ("window_fwd_kernel", "Li9ELi2ELi3E"): 3, ("window_fwd_kernel", "Li9ELi2ELi4E"): 12}
+    kernels = list(_kernels(build.LIB_PATH))
+    assert len(kernels) > 100
+    for k in kernels:
+        most = max([n for (a, b), n in known.items() if a in k[".name"] and b in k[".name"]], default=0)
+        assert k[".vgpr_spill_count"] <= most, (k[".name"], k[".vgpr_spill_count"])
