@@ -75,7 +75,7 @@ enum {
                                     of the token range and every window adds into a copy of its own, one
                                     launch adds the copies) instead of with fp32 atomics; costs scratch
                                     (64 copies + one bias-table gradient per window) and some time.  The
-                                    fused path always sums in a fixed order                               */
+                                    other paths always sum in a fixed order                               */
 };
 
 typedef struct gswa_desc {
@@ -95,14 +95,15 @@ typedef struct gswa_desc {
  *                  [B*H*W, C] in desc->dtype and, on the fused path, the parameters repacked
  *                  for the matrix cores (tens of KB, independent of B, H, W).  Scores and
  *                  probabilities are never kept; backward recomputes them.
- *   *fwd_ws_bytes  scratch of gswa_forward when `saved` is given (staged path: one group's
- *                  q|k|v; fused path: nothing is used).  For inference (saved == NULL) the
+ *   *fwd_ws_bytes  scratch of gswa_forward when `saved` is given (staged and window paths: one
+ *                  group's q|k|v; fused path: nothing is used).  For inference (saved == NULL) the
  *                  scratch must hold *fwd_ws_bytes + *saved_bytes: what would have been saved is
  *                  then kept there for the duration of the call.
  *   *bwd_ws_bytes  scratch of gswa_backward.  Staged path: one group's q|k|v and its gradient, plus
  *                  16 fp32 copies of the five parameter gradients (workgroups spread their atomic
  *                  adds over the copies; one launch sums them at the end) and, for bf16 layers with
  *                  64- or 144-token windows, one bias-table gradient per window.
+ *                  GSWA_PATH_WINDOW: at least one gradient vector for each of up to 256 workgroups.
  *                  Fused path: one partial parameter-gradient vector per workgroup of ONE head-group
  *                  launch (each launch is followed by the fixed-order sum of its partials, and the next
  *                  reuses the buffer), so this size does not grow with the group count.  Layers of
@@ -125,14 +126,17 @@ int gswa_query_bytes(const gswa_desc *desc, size_t *saved_bytes, size_t *fwd_ws_
  * Returns GSWA_OK, or the error gswa_query_bytes would return for desc.
  */
 enum {
-    GSWA_PATH_STAGED = 0,     /* one kernel per step of Eq. 6-8 and head group (every shape, both types).
-                                 The values name the general organisations: fp32 layers with C = 60, six
-                                 heads and 8x8 windows, and bf16 layers with C = 60 and 12x12 windows, run
-                                 one workgroup per window in both passes and report as they would without */
+    GSWA_PATH_STAGED = 0,     /* one kernel per step of Eq. 6-8 and head group (every shape, both types)  */
     GSWA_PATH_FUSED = 1,      /* the whole pass in one kernel, or one per head chunk (bf16, 8x8 or 16x16
                                  windows, six heads, C = 60 or 180; backward: 8x8 windows only)          */
-    GSWA_PATH_WINDOW_FWD = 2  /* forward in one launch per layer, one workgroup per window (bf16 layers
+    GSWA_PATH_WINDOW_FWD = 2, /* forward in one launch per layer, one workgroup per window (bf16 layers
                                  with narrow q/k or 12x12 windows); their backward is GSWA_PATH_STAGED   */
+    GSWA_PATH_WINDOW = 3      /* each pass in one launch, one workgroup per window, and one more that sums
+                                 the parameter gradients in a fixed order (always bit-identical from run
+                                 to run).  C = 60 and any group count: GSWA_F32 with 6 heads, window 8,
+                                 dqk 0 or 10; GSWA_BF16 with window 12 and (heads, dqk) = (4, 4), (4, 8)
+                                 or (6, 4).  astl_forward and astl_backward run such a layer, with hidden
+                                 = 120, in one launch as well                                            */
 };
 int gswa_query_path(const gswa_desc *desc, int *forward_path, int *backward_path);
 
@@ -154,9 +158,10 @@ int gswa_forward(const gswa_desc *desc, const void *x, const void *w_qkv, const 
  * written by gswa_forward on the same desc, x and parameters.
  *   dx                    [B,H,W,C] in desc->dtype, overwritten.
  *   dw_qkv ... dbias_table fp32, overwritten, or added into with GSWA_ACCUM_WGRAD.
- *                         The fused path sums per-workgroup partials in a fixed order (same
- *                         bits every run); the staged path reduces with fp32 atomics, so its
- *                         last bits can differ between runs unless GSWA_DETERMINISTIC is set.
+ *                         GSWA_PATH_FUSED and GSWA_PATH_WINDOW sum per-workgroup partials in a
+ *                         fixed order (same bits every run); GSWA_PATH_STAGED reduces with fp32
+ *                         atomics, so its last bits can differ between runs unless
+ *                         GSWA_DETERMINISTIC is set.
  * dx, the five gradients and ws must each be disjoint, as byte ranges, from every other buffer of
  * the call (GSWA_EINVAL otherwise); ws may be NULL only if *bwd_ws_bytes is 0.
  */

@@ -152,7 +152,7 @@ bool use_fused_fwd(const gswa_desc *d, const Geom &g)
     return d->dtype == GSWA_BF16 && !(d->flags & GSWA_FORCE_STAGED) && g.dq == g.d && fused_fwd_supported(g);
 }
 
-// One workgroup per window (window_layer.h): fp32, and bf16 layers with 12x12 windows.
+// One workgroup per window in both passes (window_layer.h).
 const WindowLayerOps *use_window(const gswa_desc *d, const Geom &g)
 {
     if (d->flags & GSWA_FORCE_STAGED) return nullptr;
@@ -502,10 +502,11 @@ int gswa_query_path(const gswa_desc *desc, int *forward_path, int *backward_path
     if (rc != GSWA_OK) return rc;
     const Sizes s = make_sizes(desc, g); // (the same decisions gswa_forward and gswa_backward take)
     int fwd = GSWA_PATH_STAGED;
-    if (s.fused_fwd) fwd = GSWA_PATH_FUSED;
+    if (s.window) fwd = GSWA_PATH_WINDOW;
+    else if (s.fused_fwd) fwd = GSWA_PATH_FUSED;
     else if (desc->dtype == GSWA_BF16 && !(desc->flags & GSWA_FORCE_STAGED) && window_fwd_supported(g)) fwd = GSWA_PATH_WINDOW_FWD;
     if (forward_path) *forward_path = fwd;
-    if (backward_path) *backward_path = s.fused_bwd ? GSWA_PATH_FUSED : GSWA_PATH_STAGED;
+    if (backward_path) *backward_path = s.window ? GSWA_PATH_WINDOW : s.fused_bwd ? GSWA_PATH_FUSED : GSWA_PATH_STAGED;
     return GSWA_OK;
 }
 

@@ -42,7 +42,8 @@ enum KernelId {
     K_LN_FWD_REDUCE, // LayerNorm of every token and that sum in one launch
     K_WIDE_ATTN_BWD, // wide layers: adjoint of one group's attention, one wavefront per window
     K_WIDE_WGRAD,    // wide layers: a group's dx slice and weight gradients from d(q|k|v)
-    K_WINDOW_BWD,    // whole backward of an attention layer, one workgroup per window
+    K_WINDOW_ATTN_FWD, // whole forward of an attention layer, one workgroup per window (window_layer.h)
+    K_WINDOW_BWD,    // its backward
     K_LAYER_FWD,     // a whole layer (Eq. 4-5), one workgroup per window
     K_LAYER_BWD,     // its adjoint
     K_COUNT

@@ -28,7 +28,7 @@ const char *kernel_name(int id)
                                          "wproj_grad", "attn_core_fwd", "attn_core_bwd", "qkv+dO_linear", "window_fwd",
                                          "ln_fwd", "ln_bwd", "gelu_fwd", "gelu_bwd", "fc1_linear", "fc2_linear",
                                          "fc_dlinear", "fc_wgrad", "mlp_fwd", "mlp_bwd", "mlp_pack", "mlp_reduce", "ln_fwd+mlp_reduce",
-                                         "wide_attn_bwd", "wide_qkv_grad", "window_bwd", "layer_fwd", "layer_bwd"};
+                                         "wide_attn_bwd", "wide_qkv_grad", "window_attn_fwd", "window_bwd", "layer_fwd", "layer_bwd"};
     return (id >= 0 && id < K_COUNT) ? names[id] : "?";
 }
 

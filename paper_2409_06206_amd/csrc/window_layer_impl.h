@@ -1469,7 +1469,7 @@ template <class S, bool LAYER> hipError_t launch_fwd(const WindowLayerArgs &a, h
     auto kern = window_layer_fwd_kernel<S, LAYER>;
     if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(kern), S::fwd_lds(LAYER)); e != hipSuccess) return e;
     const int grid = a.g.nW < 4096 ? a.g.nW : 4096;
-    KernelTimer kt(LAYER ? K_LAYER_FWD : K_WINDOW_FWD, s);
+    KernelTimer kt(LAYER ? K_LAYER_FWD : K_WINDOW_ATTN_FWD, s);
     hipLaunchKernelGGL(kern, dim3(grid), dim3(S::NTH), S::fwd_lds(LAYER), s, a);
     return hipGetLastError();
 }

@@ -14,7 +14,7 @@ GSWA_OK, GSWA_EINVAL, GSWA_EUNSUPPORTED, GSWA_EHIP, GSWA_ETOOBIG = 0, -1, -2, -3
 GSWA_STATIC_SCRATCH_BYTES = 96 * 1024 * 1024
 GSWA_F32, GSWA_BF16 = 0, 1
 GSWA_NO_CASCADE, GSWA_ACCUM_WGRAD, GSWA_FORCE_STAGED, GSWA_DETERMINISTIC = 1, 2, 4, 8
-GSWA_PATH_STAGED, GSWA_PATH_FUSED, GSWA_PATH_WINDOW_FWD = 0, 1, 2
+GSWA_PATH_STAGED, GSWA_PATH_FUSED, GSWA_PATH_WINDOW_FWD, GSWA_PATH_WINDOW = 0, 1, 2, 3
 
 EXPORTS = ("gswa_query_bytes", "gswa_query_path", "gswa_forward", "gswa_backward", "gswa_backward_static", "gswa_strerror",
            "gswa_last_hip_error", "gswa_version", "gswa_profile_enable",

@@ -110,12 +110,25 @@ def test_fused_path_sizes():
 
 
 def test_query_path_names_the_organisation_that_serves_a_layer():
-    """gswa_query_path: the benchmark shapes take the fused kernels, fp32 and forced layers the per-step
-    path, narrow q/k and 12 x 12 windows the one-launch forward with a per-step backward."""
-    F, S, WF = gswa.GSWA_PATH_FUSED, gswa.GSWA_PATH_STAGED, gswa.GSWA_PATH_WINDOW_FWD
+    """gswa_query_path: the benchmark shapes take the fused kernels, forced layers the per-step path, narrow q/k and
+    12 x 12 windows the one-launch forward with a per-step backward, and the layers below one launch in both passes."""
+    F, S, WF, W = gswa.GSWA_PATH_FUSED, gswa.GSWA_PATH_STAGED, gswa.GSWA_PATH_WINDOW_FWD, gswa.GSWA_PATH_WINDOW
     assert gswa.gswa_query_path(gswa.make_desc(**GOOD)) == (F, F)
     assert gswa.gswa_query_path(gswa.make_desc(**{**GOOD, "C": 180})) == (F, F)
-    assert gswa.gswa_query_path(gswa.make_desc(**{**GOOD, "dtype": "f32"})) == (S, S)
+    path = lambda **kw: gswa.gswa_query_path(gswa.make_desc(**{**GOOD, **kw}))
+    for groups in (1, 2, 3, 6):
+        for dqk in (0, 10):
+            assert path(dtype="f32", groups=groups, dqk=dqk) == (W, W)
+            assert path(dtype="f32", groups=groups, dqk=dqk, flags=gswa.GSWA_FORCE_STAGED) == (S, S)
+        assert path(dtype="f32", groups=groups, dqk=4) == path(dtype="f32", groups=groups, window=4, shift=2) == (S, S)
+    assert path(dtype="f32", heads=4) == path(dtype="f32", C=180) == (S, S)
+    m12 = dict(H=24, W=24, window=12, shift=6)
+    for heads, dqk in ((4, 4), (4, 8), (6, 4)):
+        for groups in (g for g in (1, 2, 3, 4, 6) if heads % g == 0):
+            assert path(heads=heads, groups=groups, dqk=dqk, **m12) == (W, W)
+            assert path(heads=heads, groups=groups, dqk=dqk, flags=gswa.GSWA_FORCE_STAGED, **m12) == (S, S)
+            assert path(heads=heads, groups=groups, dqk=dqk, dtype="f32", **m12) == (S, S)
+    assert path(heads=6, dqk=8, **m12)[1] == path(heads=4, dqk=0, **m12)[1] == path(heads=4, dqk=5, **m12)[1] == S
     assert gswa.gswa_query_path(gswa.make_desc(**{**GOOD, "flags": gswa.GSWA_FORCE_STAGED})) == (S, S)
     assert gswa.gswa_query_path(gswa.make_desc(**{**GOOD, "C": 180, "H": 32, "W": 32, "window": 16, "shift": 8})) == (F, S)
     assert gswa.gswa_query_path(gswa.make_desc(**{**GOOD, "dqk": 4})) == (WF, S)
