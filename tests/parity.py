@@ -6,12 +6,32 @@ Tolerance (stated by the benchmark definition): per output tensor
 For bf16 the oracle is fed the bf16-rounded inputs, so the comparison measures the kernels'
 arithmetic and the rounding of their outputs only.
 """
+import contextlib
+
 import numpy as np
 
 from paper_2409_06206_amd import synth
 
 TOL = {"f32": 1e-5, "bf16": 2e-2}
 GRAD_NAMES = ("dx", "dw_qkv", "db_qkv", "dw_proj", "db_proj", "dtable")
+
+
+@contextlib.contextmanager
+def launched():
+    """Names of the kernels that the library launches inside the block (filled in when it ends without an error)."""
+    import torch
+    from paper_2409_06206_amd import gswa
+    names = set()
+    gswa.gswa_profile_enable(True)
+    try:
+        gswa.gswa_profile_collect()
+        yield names
+        torch.cuda.synchronize()
+        got, dropped = gswa.gswa_profile_collect()
+        assert dropped == 0
+        names.update(got)
+    finally:
+        gswa.gswa_profile_enable(False)
 
 
 def rel_err(got, want):

@@ -527,7 +527,9 @@ def test_fp32_whole_layers_one_workgroup_per_window(groups, shape, shift, cascad
     B, H, W = shape
     case = dict(B=B, H=H, W=W, C=60, heads=6, groups=groups, window=8, shift=shift, dtype="f32", hidden=120)
     print("case", case, flush=True)
-    parity.check_block(astl_oracle, cascade=cascade, **case)
+    with parity.launched() as names:
+        parity.check_block(astl_oracle, cascade=cascade, **case)
+    assert names == {"layer_fwd", "layer_bwd", "reduce_partials"}
 
 
 @pytest.mark.parametrize("heads,groups,dqk,shape,shift", [
@@ -542,7 +544,9 @@ def test_12x12_window_layers_one_workgroup_per_window(heads, groups, dqk, shape,
     B, H, W = shape
     case = dict(B=B, H=H, W=W, C=60, heads=heads, groups=groups, window=12, shift=shift, dtype="bf16", hidden=120, dqk=dqk)
     print("case", case, flush=True)
-    parity.check_block(astl_oracle, **case)
+    with parity.launched() as names:
+        parity.check_block(astl_oracle, **case)
+    assert names == {"layer_fwd", "layer_bwd", "reduce_partials"}
 
 
 @pytest.mark.parametrize("case,copies", [

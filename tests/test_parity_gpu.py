@@ -352,15 +352,19 @@ def test_narrow_query_key_and_window_12(oracle, B, H, W, C, heads, groups, windo
                cascade=False, seed=synth.LAYER_SEED0 + 3)
 
 
-def test_window_forward_inference_and_staged_forward_agree(oracle):
-    """12 x 12 windows, narrow q/k: the one-launch forward without a saved buffer gives the bits of the
-    training forward, and the one-kernel-per-step forward the same result within the tolerance."""
+@pytest.mark.parametrize("heads,dqk,kernel", [(4, 4, "window_attn_fwd"), (6, 0, "window_fwd")])
+def test_window_forward_inference_and_staged_forward_agree(oracle, heads, dqk, kernel):
+    """12 x 12 windows: the one-launch forward (of the kernels for both passes, and of the one for the forward alone)
+    without a saved buffer gives the bits of the training forward, and the one-kernel-per-step forward the same result
+    within the tolerance."""
     from paper_2409_06206_amd import gswa
-    shape = (2, 24, 24, 60, 4, 2, 12)
-    x, dy, p = parity.make_inputs(*shape, "bf16", synth.LAYER_SEED0, "stress", dqk=4)
-    a, _ = parity.gpu_results(x, dy, p, 4, 2, 12, 6, "bf16", backward=True, dqk=4)
-    b, _ = parity.gpu_results(x, dy, p, 4, 2, 12, 6, "bf16", backward=False, dqk=4)
-    c, _ = parity.gpu_results(x, dy, p, 4, 2, 12, 6, "bf16", backward=False, dqk=4,
+    shape = (2, 24, 24, 60, heads, 2, 12)
+    x, dy, p = parity.make_inputs(*shape, "bf16", synth.LAYER_SEED0, "stress", dqk=dqk)
+    a, _ = parity.gpu_results(x, dy, p, heads, 2, 12, 6, "bf16", backward=True, dqk=dqk)
+    with parity.launched() as names:
+        b, _ = parity.gpu_results(x, dy, p, heads, 2, 12, 6, "bf16", backward=False, dqk=dqk)
+    assert names == {kernel}
+    c, _ = parity.gpu_results(x, dy, p, heads, 2, 12, 6, "bf16", backward=False, dqk=dqk,
                               extra_flags=gswa.GSWA_FORCE_STAGED)
     assert np.array_equal(a["y"], b["y"])
     assert parity.rel_err(c["y"], a["y"].astype(np.float64)) <= parity.TOL["bf16"]
@@ -394,10 +398,12 @@ def test_random_shapes_bf16(oracle, shape):
 
 
 @pytest.mark.parametrize("dtype,shape,flags", [
-    ("f32", (4, 32, 32, 60, 6, 2, 8, 4), 0),                 # one-kernel-per-step path, vector ALUs
+    ("f32", (4, 32, 32, 60, 6, 2, 8, 4), 0),                 # one workgroup per window
+    ("f32", (4, 32, 32, 60, 6, 2, 8, 4), "staged"),          # one-kernel-per-step path, vector ALUs
     ("f32", (2, 32, 48, 180, 6, 3, 16, 8), 0),               # 256-token windows: strips of queries
     ("bf16", (4, 32, 32, 60, 6, 2, 8, 4), "staged"),         # the same path on the matrix cores
-    ("bf16", (2, 48, 48, 60, 4, 2, 12, 6), 0),               # 12 x 12 windows, narrow q/k
+    ("bf16", (2, 48, 48, 60, 4, 2, 12, 6), 0),               # 12 x 12 windows, narrow q/k: one workgroup per window
+    ("bf16", (2, 48, 48, 60, 4, 2, 12, 6), "staged"),        # the same, one-kernel-per-step backward
 ])
 def test_reproducible_mode_gives_the_same_bits_every_run(oracle, dtype, shape, flags):
     """GSWA_DETERMINISTIC: no gradient depends on the order in which workgroups finish."""
@@ -457,7 +463,9 @@ def test_training_forward_on_the_fused_path_needs_no_scratch(oracle):
 def test_fp32_layers_one_workgroup_per_window(oracle, groups, shape, shift):
     """fp32 layers of 60 channels and 8x8 windows run one workgroup per window: every group count, workgroups with
     one and with two windows, windows cut by the shift in every way."""
-    parity.check_case(oracle, *shape, 60, 6, groups, 8, shift, "f32", regime="stress")
+    with parity.launched() as names:
+        parity.check_case(oracle, *shape, 60, 6, groups, 8, shift, "f32", regime="stress")
+    assert names == {"window_attn_fwd", "window_bwd", "reduce_partials"}
 
 
 @pytest.mark.parametrize("heads,groups,dqk,shape,shift", [
@@ -466,7 +474,9 @@ def test_fp32_layers_one_workgroup_per_window(oracle, groups, shape, shift):
 ])
 def test_12x12_windows_one_workgroup_per_window(oracle, heads, groups, dqk, shape, shift):
     """bf16 attention layers with 12x12 windows: the organisations of the heads that no other test runs."""
-    parity.check_case(oracle, *shape, 60, heads, groups, 12, shift, "bf16", regime="stress", dqk=dqk)
+    with parity.launched() as names:
+        parity.check_case(oracle, *shape, 60, heads, groups, 12, shift, "bf16", regime="stress", dqk=dqk)
+    assert names == {"window_attn_fwd", "window_bwd", "reduce_partials"}
 
 
 @pytest.mark.parametrize("heads,groups,dqk", [(4, 1, 4), (4, 2, 8), (6, 3, 4)])
