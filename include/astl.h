@@ -87,7 +87,9 @@ int astl_forward(const astl_desc *desc, const void *x, const astl_params *params
  * Gradients of a scalar loss through the layer, given dy = dLoss/dy and `saved` as written by
  * astl_forward on the same desc, x and params.  dx [B,H,W,C] in the layer's element type,
  * overwritten; it may not overlap x, dy or saved.  The parameter gradients are reduced with
- * fp32 atomics on part of the path, so their last bits can differ between runs.
+ * fp32 atomics on part of the path, so their last bits can differ between runs, unless the attention
+ * layer is GSWA_PATH_WINDOW (gswa_query_path) and hidden = 120: then the pass is one launch and one sum
+ * in a fixed order.
  */
 int astl_backward(const astl_desc *desc, const void *x, const void *dy, const astl_params *params,
                   const void *saved, void *dx, const astl_grads *grads, void *ws, void *hip_stream);
@@ -127,8 +129,9 @@ int astl_stack_forward(const astl_stack_desc *desc, const void *x, const astl_pa
  * the map goes through each layer in bands of `band_windows` rows of windows of that layer's (shifted)
  * window grid, one image at a time.  A band of a shifted layer that does not reach the map's last window
  * row is a contiguous run of image rows and needs only the column part of the shift mask; the band that
- * ends the map also takes the map's first `shift` rows.  The result is the one astl_stack_forward gives
- * for inference, bit for bit.
+ * ends the map also takes the map's first `shift` rows.  The result has the same bits for every
+ * band_windows.  From astl_stack_forward's it differs by roundings: that call takes LayerNorm 1 of a layer
+ * inside the MLP kernel of the layer before, where there is one (bf16), which sums a row in another order.
  *
  * x [B,H,W,C] is read only; y [B,H,W,C] receives layer 0's output and is then updated in place by the
  * later layers; x and y must not overlap.  ws: *ws_bytes of astl_stack_tiled_query_bytes, 256-byte
