@@ -30,6 +30,13 @@ namespace gswa {
 namespace {
 
 constexpr float kLog2e = 1.4426950408889634f;
+// Scores: in bf16 base 2, with the factor and the scale in q and in the bias table.  In fp32 the roundings of these would
+// show, and so would the order of the sums: there a score is taken times the scale and with its bias at the end, the
+// exponentials are summed on the vector ALU, and the backward keeps maximum and denominator apart.  Against all of these
+// the bf16 way, error against fp64 over the one-kernel-per-step path's (attention layer, two groups, 16 layers): y 1.13 ->
+// 1.00, dx 1.12 -> 1.01, dtable 1.15 -> 0.99; a whole layer takes 86 us either way (three 48x56 patches).
+template <typename E> constexpr float score_unit = sizeof(E) == 2 ? kLog2e : 1.f; // (of bias and mask)
+template <typename E> __device__ __forceinline__ float prob(float d) { return __builtin_amdgcn_exp2f(sizeof(E) == 2 ? d : d * kLog2e); }
 
 // The lane's place in an operand, made afresh where it is used: otherwise the compiler computes the lane's addresses
 // of every phase at the start of the kernel, runs out of registers and spills them.
@@ -87,7 +94,7 @@ template <typename T_, int C_, int HEADS_, int G_, int M_, int DQ_, int HID_, in
     // over DX, whose last use (but for the skip, which goes by memory) is over by then.  The MLP's hidden layer and its
     // gradient lie over what follows DX.
     static constexpr size_t SZ_DO = sizeof(E) * N * PD, SZ_F = sizeof(E) * N * PF;
-    static constexpr size_t SZ_ST = sizeof(float) * 2 * HG * N, SZ_RED = sizeof(float) * WAVES * 2 * 16 * up(C, 16);
+    static constexpr size_t SZ_ST = sizeof(float) * (sizeof(E) == 4 ? 3 : 2) * HG * N, SZ_RED = sizeof(float) * WAVES * 2 * 16 * up(C, 16);
     static constexpr size_t SZ_SR = SZ_ST > SZ_RED ? SZ_ST : SZ_RED; // (row sums and softmax statistics take turns)
     static constexpr size_t FIXED = 2 * SZ_ROW + SZ_R + SZ_DO + SZ_TB + SZ_SR;
     static constexpr bool fits(int n, bool over) { return FIXED + (over ? (n * SZ_F > SZ_ROW ? n * SZ_F : SZ_ROW) : SZ_ROW + n * SZ_F) <= 160 * 1024; }
@@ -229,6 +236,16 @@ template <class S> struct QkOp : HeadOp<typename S::E, S::HSQ> {
         }
     }
 };
+// a tile of scores, from the four bias entries of the lane on: in bf16 they start the sum
+template <class S> __device__ __forceinline__ f32x4 scores(const QkOp<S> &a, const QkOp<S> &b, const float *bias)
+{
+    const f32x4 t = {bias[0], bias[1], bias[2], bias[3]};
+    if constexpr (sizeof(typename S::E) == 2) return mma(a, b, t);
+    f32x4 d = mma(a, b, zero4());
+#pragma unroll
+    for (int i = 0; i < 4; ++i) d[i] = fmaf(d[i], 1.f / sqrtf((float)S::DQ), t[i]);
+    return d;
+}
 // sum over the 16 lanes of a row, left in all of them
 __device__ __forceinline__ float row16_sum(float v)
 {
@@ -491,7 +508,7 @@ template <class S> __device__ __forceinline__ f32x4 add_mask(const Window<S> &wi
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const bool cols = ((reg & 2) != 0) != (win.last_c && c + (up ? i : 3 - i) >= S::M - win.s);
-        s[i] += (rows || cols) ? -100.f * kLog2e : 0.f;
+        s[i] += (rows || cols) ? -100.f * score_unit<float> : 0.f;
     }
     return s;
 }
@@ -534,7 +551,7 @@ template <class S> __device__ __forceinline__ void load_table(float *tb, const t
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
         const int e = threadIdx.x + k * S::NTH, i = e / S::HEADS, h = e - i * S::HEADS;
-        if (e < S::NTBL * S::HEADS) tb[h * S::TBP + i] = to_f32(v[k]) * kLog2e;
+        if (e < S::NTBL * S::HEADS) tb[h * S::TBP + i] = to_f32(v[k]) * score_unit<typename S::E>;
     }
 }
 
@@ -555,8 +572,8 @@ template <class S> __device__ __forceinline__ void qkv_unit(const WindowLayerArg
     for (int i = 0; i < 4; ++i) bf[i] = to_f32(bias[i < rows.n ? rows.row + i : 0]);
     loads_issued();
     const bool casc = gi > 0 && a.g.cascade;
-    const float pad = 16 * ft + 4 * q >= 2 * S::RQ ? 1.f : 0.f; // (v is one in the first pad feature: see window_layer_fwd_kernel)
-    const float sc = 16 * ft + 4 * q < S::RQ ? kLog2e / sqrtf((float)S::DQ) : 1.f; // (scores come in base 2)
+    const float pad = sizeof(typename S::E) == 2 && 16 * ft + 4 * q >= 2 * S::RQ ? 1.f : 0.f; // (bf16: v is one in the first pad feature: see window_layer_fwd_kernel)
+    const float sc = 16 * ft + 4 * q < S::RQ && sizeof(typename S::E) == 2 ? kLog2e / sqrtf((float)S::DQ) : 1.f;
 #pragma unroll
     for (int tt = 0; tt < S::TT; ++tt) {
         const int t = 16 * (tu * S::TT + tt) + l16;
@@ -655,7 +672,7 @@ __global__ __launch_bounds__(S::NTH) void window_layer_fwd_kernel(WindowLayerArg
                     QkOp<S> kf;
                     kf.load(R + (16 * kt + 15 - l16) * S::PR, S::RQ + hl * S::HSQ, false, q);
                     const float *bias = tbh + oq - key_offset4<S>(kt, 3 - q) - 3;
-                    st[kt] = mma(kf, qf, f32x4{bias[0], bias[1], bias[2], bias[3]});
+                    st[kt] = scores(kf, qf, bias);
                 }
                 if (sizeof(E) == 4 && masked) {
 #pragma unroll
@@ -664,20 +681,23 @@ __global__ __launch_bounds__(S::NTH) void window_layer_fwd_kernel(WindowLayerArg
 #pragma unroll
                 for (int kt = 0; kt < S::NT; ++kt) mx = fmaxf(mx, fmaxf(fmaxf(st[kt][0], st[kt][1]), fmaxf(st[kt][2], st[kt][3])));
                 mx = qgroup_max(mx);
+                f32x4 sum = zero4();
 #pragma unroll
-                for (int kt = 0; kt < S::NT; ++kt)
+                for (int kt = 0; kt < S::NT; ++kt) {
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) st[kt][i] = __builtin_amdgcn_exp2f(st[kt][i] - mx);
+                    for (int i = 0; i < 4; ++i) st[kt][i] = prob<E>(st[kt][i] - mx);
+                    if (sizeof(E) == 4) sum += st[kt];
+                }
                 f32x4 o = zero4();
 #pragma unroll
                 for (int kt = 0; kt < S::NT; ++kt)
                     o = mma(O::ld_tr(R + 16 * kt * S::PR + 2 * S::RQ + hl * S::HSV, S::PR, q, l16), O::from(st[kt]), o);
-                // (v is one in feature D, so row D of the product is the softmax's denominator.  In bf16 it is the sum of the
-                // exponentials as rounded for the product: numerator and denominator share the roundings.  Against the sum of
-                // the fp32 exponentials, error of y over 48 layers each: (heads, groups, dqk) = (4, 1, 4) 3.64e-3 either way,
-                // (6, 3, 4) 4.52e-3 and 4.53e-3, (6, 6, 4) 6.15e-3 and 6.21e-3.)
+                // The softmax's denominator.  In bf16 v is one in feature D, so it is row D of the product: the sum of the
+                // exponentials as rounded for the product; numerator and denominator share the roundings.  (Against the sum
+                // of the fp32 exponentials, error of y over 48 layers each: (heads, groups, dqk) = (4, 1, 4) 3.64e-3 either
+                // way, (6, 3, 4) 4.52e-3 and 4.53e-3, (6, 6, 4) 6.15e-3 and 6.21e-3.)
                 static_assert(S::D % 4 != 0, "a pad feature");
-                const float inv = 1.f / qgroup_sum(q == S::D / 4 ? o[S::D % 4] : 0.f);
+                const float inv = 1.f / qgroup_sum(sizeof(E) == 4 ? (sum[0] + sum[1]) + (sum[2] + sum[3]) : q == S::D / 4 ? o[S::D % 4] : 0.f);
                 E *ar = A + tq * S::PC + gi * S::CGP + hl * S::D;
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
@@ -831,7 +851,8 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
     float *DN = reinterpret_cast<float *>(DN_IN_X ? X : Hh);
     static_assert(DN_IN_X || sizeof(float) * S::N * 16 * S::CTC <= S::SZ_H, "dn in the hidden layer's place");
     float *tb = reinterpret_cast<float *>(lds + S::bwd_tb(LAYER));
-    float *lse = tb + S::HEADS * S::TBP, *delta = lse + S::HG * S::N; // (delta: negative)
+    // of every query: bf16 its base-2 log-sum-exp, fp32 its largest score and 1 / the sum of exponentials; minus sum P dP
+    float *lse = tb + S::HEADS * S::TBP, *delta = lse + S::HG * S::N, *rsum = delta + S::HG * S::N;
     float *red = lse;  // [WAVES][2][CP]
     constexpr int CP = 16 * up(S::C, 16);
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1156,7 +1177,7 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
                     kf.load(R + (16 * kt + 15 - l16) * S::PR, S::RQ + hl * S::HSQ, false, q);
                     vf.load(R + (16 * kt + 15 - l16) * S::PR + 2 * S::RQ + hl * S::HSV, q);
                     const float *bias = tbh + oq - key_offset4<S>(kt, 3 - q) - 3;
-                    st[kt] = mma(kf, qf, f32x4{bias[0], bias[1], bias[2], bias[3]});
+                    st[kt] = scores(kf, qf, bias);
                     dp[kt] = mma(vf, of, zero4());
                 }
                 if (sizeof(E) == 4 && masked) {
@@ -1171,7 +1192,7 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
                 for (int kt = 0; kt < S::NT; ++kt)
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        st[kt][i] = __builtin_amdgcn_exp2f(st[kt][i] - mx);
+                        st[kt][i] = prob<E>(st[kt][i] - mx);
                         sum += st[kt][i];
                         dl += st[kt][i] * dp[kt][i];
                     }
@@ -1179,7 +1200,8 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
                 const float inv = 1.f / sum;
                 dl = qgroup_sum(dl) * inv;
                 if (q == 0) {
-                    lse[hl * S::N + tq] = mx + __log2f(sum);
+                    lse[hl * S::N + tq] = sizeof(E) == 4 ? mx : mx + __log2f(sum);
+                    if (sizeof(E) == 4) rsum[hl * S::N + tq] = inv;
                     delta[hl * S::N + tq] = -dl;
                 }
 #pragma unroll
@@ -1271,12 +1293,14 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
                     const f32x4 ls = *reinterpret_cast<const f32x4 *>(lse + hl * S::N + 16 * nt + 4 * q);
                     const f32x4 dl = *reinterpret_cast<const f32x4 *>(delta + hl * S::N + 16 * nt + 4 * q);
                     const float *bias = tbh + ok + key_offset4<S>(nt, q);
-                    f32x4 p = mma(qf, kf, f32x4{bias[0], bias[1], bias[2], bias[3]}), d;
-                    const f32x4 dp = mma(of, vf, dl); // dP - delta
+                    f32x4 p = scores(qf, kf, bias), d;
+                    f32x4 dp = mma(of, vf, sizeof(E) == 4 ? zero4() : dl), rs; // dP - delta
+                    if (sizeof(E) == 4) { dp += dl; rs = *reinterpret_cast<const f32x4 *>(rsum + hl * S::N + 16 * nt + 4 * q); }
                     if (sizeof(E) == 4 && masked) p = add_mask<S>(win, p, 16 * nt + 4 * q, true, tk);
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        p[i] = __builtin_amdgcn_exp2f(p[i] - ls[i]);
+                        p[i] = prob<E>(p[i] - ls[i]);
+                        if (sizeof(E) == 4) p[i] *= rs[i];
                         d[i] = p[i] * dp[i];
                     }
                     ds[j][nt] = O::from(d);
@@ -1284,7 +1308,7 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
                     av = mma(O::ld_t(DO + 16 * nt * S::PD + hl * S::HSV, S::PD, q, l16), O::from(p), av);
                     ak = mma(O::ld_t(R + 16 * nt * S::PR + hl * S::HSQ, S::PR, q, l16), ds[j][nt], ak);
                 }
-                dk[k] = O::from(ak * (1.f / kLog2e));
+                dk[k] = O::from(ak * (sizeof(E) == 4 ? qscale : 1.f / kLog2e));
                 dv[k] = O::from(av);
             }
                 if (!DIRECT) {
