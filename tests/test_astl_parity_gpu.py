@@ -608,3 +608,25 @@ def test_gradient_at_the_second_layer_norm_stays_in_fp32():
     torch.cuda.synchronize()
     want = np.full(C, 144.0 * (1.0 + 15.0 / 4096.0))
     assert parity.rel_err(blk.results()["dln2_b"], want) <= 2e-5
+
+
+def test_fp32_channel_means_are_rounded_once():
+    """A whole fp32 layer on a map of 959 and 961: every token's mean is 960 and its variance 1, both exact, as long as the
+    sum is divided by 60 and not multiplied by the rounded 1/60 (5.2e-8 too much: 960.00006).  d ln1_w, the sum over the
+    tokens of a gradient times the normalised map, would be off by 6e-5."""
+    from paper_2409_06206_amd import runner
+    import torch
+    C = 60
+    p = synth.astl_params(C, 6, 2, 8, 120, 300, "stress")
+    p["ln1_w"], p["ln1_b"] = np.ones(C, dtype=np.float32), np.zeros(C, dtype=np.float32)
+    p["w_fc2"][:] = 0.0   # (nothing comes back through LN_2, whose input near 960 has an fp32 rounding of its own)
+    x = np.broadcast_to(np.where(np.arange(C) % 2 == 0, 961.0, 959.0), (1, 16, 16, C)).astype(np.float32)
+    _, dy = synth.activations(1, 16, 16, C, 3)
+    blk = runner.DeviceBlock(1, 16, 16, C, 6, 2, 8, 4, "f32", 120)
+    blk.set_params(p)
+    blk.set_inputs(x, dy)
+    blk.forward()
+    blk.backward()
+    torch.cuda.synchronize()
+    _, grads = astl_oracle.backward(x, dy, p, heads=6, groups=2, window=8, shift=4)
+    assert parity.rel_err(blk.results()["dln1_w"], grads["ln1_w"]) <= parity.TOL["f32"]
