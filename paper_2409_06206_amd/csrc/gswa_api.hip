@@ -191,7 +191,7 @@ Sizes make_sizes(const gswa_desc *d, const Geom &g)
     }
     s.window = use_window(d, g);
     if (s.window) {
-        // (never less than the one-kernel-per-step path asks for: GSWA_FORCE_STAGED changes no size)
+        // (never less than the one-kernel-per-step path asks for; more where 256 vectors outweigh a group's q|k|v)
         const size_t need = align256(window_layer_bwd_ws_bytes(*s.window, g, false));
         if (need > s.bwd_ws) s.bwd_ws = need;
     }
