@@ -99,6 +99,12 @@ size_t fused_pack_bytes(const Geom &g);
 // attn_out buffer (for inference the caller lends scratch).
 bool fused_fwd_needs_attn(const Geom &g);
 
+// LayerNorm in front of the layer, taken in the forward kernel's read of x (w null: none).
+struct FusedLn {
+    const bf16_t *w = nullptr, *b = nullptr;
+    float eps = 0.f;
+};
+
 // y = GSWA(x); attn_out receives the concatenated group outputs [T, C] (may be null unless
 // fused_fwd_needs_attn); `pack` receives the packed parameters (fused_pack_bytes, 256-byte aligned), or holds them already (`packed`).
 // `training`: attn_out is kept by the caller for the backward pass (otherwise it is scratch and a
@@ -204,12 +210,13 @@ __device__ __forceinline__ void wide_pack_entry(int i, const bf16_t *__restrict_
     }
 }
 
-// Wide layers (C = 180) with 8x8 windows: the whole forward in one launch, one wavefront per
-// window, the weights streamed through LDS (wide_fwd.hip).  `attn` receives the group outputs when
+// Wide layers (C = 180) with 8x8 or 16x16 windows: the whole forward in one launch, 32 tokens per
+// wavefront, the weights streamed through LDS (wide_fwd.hip).  `attn` receives the group outputs when
 // `training` (the caller keeps them for the backward pass); otherwise it is not touched.
+// With `ln` the layer's input is LayerNorm(x) (rounded to bf16), taken of the rows as they are loaded.
 bool wide_fwd_supported(const Geom &g);
-hipError_t launch_wide_fwd(const Geom &g, const bf16_t *x, const void *pack, bf16_t *y, bf16_t *attn,
-                           int training, hipStream_t s);
+hipError_t launch_wide_fwd(const Geom &g, const bf16_t *x, const void *pack, const bf16_t *table, bf16_t *y, bf16_t *attn,
+                           int training, const FusedLn &ln, hipStream_t s);
 
 // Sums the per-workgroup partial vectors of one launch and scatters their segments to the gradients
 // (fixed summation order).  Segment k covers entries [begin[k], begin[k+1]) of a partial vector and

@@ -764,8 +764,8 @@ hipError_t run_fwd(const Geom &g, const bf16_t *x, const bf16_t *w_qkv, const bf
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if constexpr (Cf::SPLIT) {
-        if (wide_fwd_supported(g)) { // 8x8 windows: the whole layer in one launch
-            return launch_wide_fwd(g, x, pack, y, attn, training, s);
+        if (wide_fwd_supported(g)) { // the whole layer in one launch (its byte offsets are 32 bits wide: larger maps go on below)
+            return launch_wide_fwd(g, x, pack, table, y, attn, training, FusedLn{}, s);
         }
         if (!attn) return hipErrorInvalidValue;
         e = g.M == 16 ? launch_attn_chunks<Cf, 16>(g, x, pack, table, attn, s)

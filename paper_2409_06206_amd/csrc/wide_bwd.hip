@@ -851,7 +851,7 @@ hipError_t run_wide_bwd(const Geom &g, const bf16_t *x, const bf16_t *dy, const 
 
 bool wide_bwd_supported(const Geom &g)
 {
-    if (!wide_fwd_supported(g)) return false; // (8x8 windows, q and k of the head's width; the forward fills the fragments)
+    if (g.M != 8 || !wide_fwd_supported(g)) return false; // (q and k of the head's width; the forward fills the fragments)
     if (g.shift % 2 != 0) return false;        // (the runs of a window's rows are fetched in 16-byte pieces)
     // 32-bit byte offsets into d(q|k|v)
     if ((size_t)g.nW * 4 * 9 * 1024 >= (size_t(1) << 32)) return false;

@@ -1,15 +1,24 @@
-// Forward of wide GSWA layers (C = 180, six heads of 30 channels, 8x8 windows) in one launch:
+// Forward of wide GSWA layers (C = 180, six heads of 30 channels, 8x8 or 16x16 windows) in one launch:
 // shift + partition + per-group QKV projection (Eq. 6) with the cascade add (Eq. 8) + scores with
 // relative bias and shift mask + softmax + PV + output projection (Eq. 7) + merge + reverse shift.
 //
-// One wavefront owns one window: its 64 tokens are four 16-token tiles, K, V and the
-// probabilities never leave the wave's registers.  A workgroup is four waves, one per SIMD (a
-// wave then has the SIMD's whole register file: x of all groups and all head outputs stay in
-// registers).  The weights of a wide layer (108 KB of QKV fragments, 72 KB of projection
-// fragments) do not fit LDS together, so they pass through it as a stream of equal units, double
-// buffered, one workgroup barrier per unit: the QKV fragments of one head (one group: of its q,
-// k or v), then the projection in pieces of the same size.  Every fragment read from LDS serves
-// the four token tiles of the wave.
+// A wavefront owns two 16-token tiles: two waves share an 8x8 window, eight a 16x16 one.  x of all groups
+// and all head outputs of its tokens stay in its registers, so do its probabilities; K and V of a head cross
+// the waves of a window through LDS, already in the operand layout of the products that read them (one
+// 16-byte write and read per lane and tile).  A workgroup is eight waves, two per SIMD (256 registers): one
+// wave's vector instructions run under the other's products, which one wave per SIMD with a whole window
+// (the organisation before, 512 registers) could not offer.  The weights of a wide layer (108 KB of QKV
+// fragments, 72 KB of projection fragments) do not fit LDS together, so they pass through it as a stream of
+// equal units: the QKV fragments of one head, then the projection in pieces of the same size.
+//
+// What bounds it: with 8x8 windows the steps between barriers, 1.4 to 2.2 k clocks of which 0.6 k are
+// products and 0.6 k the LDS reads of the fragments (each serves two tiles); with 16x16 windows the vector
+// instructions of the softmax.  Measured (one image of 512x512, two groups): 8x8 windows 121 -> 94 us a pass,
+// 16x16 windows 291 -> 150 us (there two attention launches and one of the projection before); one image of
+// 96x64 29.7 -> 20.2 us.  Taken one after the other at 8x8: two waves per window 130 -> 115 us, the next
+// window's rows loaded under the projection, a few per step (in one go they stall the wave for 8 k clocks
+// while memory serves the whole chip) and padded bias tables -> 111, windows of half the waves one step late
+// -> 100, operands of the next products read under the present ones -> 94.
 //
 // Everything is kept with rows = features and column = token (T-form, see fused_bwd.hip), and a
 // head of 30 channels is two 16-row tiles, i.e. exactly the 32 k-slots of one K=32 MFMA step in
@@ -27,30 +36,101 @@ namespace {
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kMaskLog2 = -100.0f * kLog2e; // the additive -100 of the shift mask, in base-2 units
 
-
-template <class Cf> struct WideFwdCfg {
-    // one wave per SIMD: a wave then has the whole register file of its SIMD (512 registers), which
-    // holds a window's x, all head outputs and the staging registers of the weight stream
-    static constexpr int NWAVES = 4, NTHREADS = 64 * NWAVES;
-    // The weights pass through LDS as a stream of equal units, double buffered: the QKV fragments of
-    // one head, then the projection fragments in pieces of the same size (whole output tiles).
-    // (one group: a head's fragments are 36 KB, so a unit is one of q, k, v of a head)
-    static constexpr int UPH = Cf::G == 1 ? 3 : 1;                 // units per head
-    static constexpr int FR_UNIT = 3 * Cf::ET * Cf::KSX / UPH;     // fragments (1 KB) of one unit
+// M: window side, TW: 16-token tiles a wave owns
+template <class Cf, int M_, int TW_> struct WideFwdCfg {
+    static constexpr int M = M_, TW = TW_, NT = M * M / 16; // tiles of a window
+    static constexpr int NWAVES = 8, NTHREADS = 64 * NWAVES;
+    static constexpr int WPW = NT / TW, WINS = NWAVES / WPW; // waves of a window, windows of a workgroup
+    static constexpr int RPT = 16 / M;                       // window rows a tile covers
+    static constexpr int NTBL = (2 * M - 1) * (2 * M - 1), TP = (NTBL + 7) & ~3; // bias table of a head, its pitch
+    static constexpr int NTB = M == 8 ? TW : 1;              // query tiles taken through the softmax together
+    // The weights pass through LDS as a stream of equal units: the QKV fragments of one head, then the projection
+    // fragments in pieces of the same size (whole output tiles).
+    static constexpr int FR_UNIT = 3 * Cf::ET * Cf::KSX;           // fragments (1 KB) of one unit
     static constexpr size_t UNIT_BYTES = (size_t)FR_UNIT * 1024;
     static constexpr int OT_UNIT = FR_UNIT / Cf::HEADS;            // output tiles of one projection unit
     static constexpr int NPU = Cf::OT / OT_UNIT;                   // projection units
-    static constexpr int NHU = Cf::HEADS * UPH;                    // head units
-    static constexpr int NU = NHU + NPU;                           // units per window
-    static constexpr size_t OFF_BIAS = 0;                          // fp32 b_qkv [3C], b_proj [C]
-    static constexpr size_t OFF_TBL = (size_t)16 * Cf::C;          // fp32 [HEADS][TBW_PITCH]
-    static constexpr size_t OFF_W = OFF_TBL + (size_t)Cf::HEADS * Cf::TBW_PITCH * 4;
-    static constexpr size_t LDS_BYTES = OFF_W + 2 * UNIT_BYTES;
-    static_assert(OFF_W % 16 == 0 && LDS_BYTES <= 160 * 1024, "LDS budget");
-    static_assert(FR_UNIT % Cf::HEADS == 0 && Cf::OT % OT_UNIT == 0 && NU % 2 == 0,
+    static constexpr int NU = Cf::HEADS + NPU;                     // units per window
+    // A round (one window per slot) is a sequence of steps: q, k, v of head 0, its scores .. PV, the same of head 1, ...,
+    // then the projection unit by unit.  Steps are grouped into times; a barrier ends a time.
+    //   LATE   windows of the second half of the workgroup's waves run one time behind the others, so that on every SIMD
+    //          one wave is in the vector instructions of a softmax while the other is in the products and LDS reads of
+    //          its q, k, v: needs windows that share no wave between the halves
+    //   MERGE  the scores of head h and q, k, v of head h + 1 make one time (k and v then need two buffers)
+    static constexpr int LATE = WINS > 1 ? 1 : 0;
+    static constexpr bool MERGE = !LATE && Cf::G > 1;
+    static constexpr int NS = 2 * Cf::HEADS + NPU;                 // steps
+    static constexpr int time_of(int step) { return !MERGE ? step : step < 2 * Cf::HEADS ? (step + 1) / 2 : step - Cf::HEADS; }
+    static constexpr int NTIME = time_of(NS - 1) + 1;
+    static constexpr int unit_time(int u) { return time_of(u < Cf::HEADS ? 2 * u : u + Cf::HEADS); } // first time unit u is read
+    static constexpr int unit_at(int time) // the unit first read at this time (its loads leave one time before), or -1
+    {
+        for (int u = 0; u < NU; ++u)
+            if (unit_time(u) == time) return u;
+        return -1;
+    }
+    // LDS buffer of a unit: read at times unit_time .. unit_time + LATE, written from one time before
+    static constexpr int NSLOT = 2 + LATE;
+    static constexpr int unit_slot(int u)
+    {
+        constexpr int late[3][12] = {{0, 1, 2, 0, 1, 2, 1, 2}, {0, 1, 0, 1, 0, 2, 1, 0, 2, 1}, {0, 1, 2, 0, 1, 2, 0, 1, 2, 0, 1, 2}};
+        return LATE ? late[Cf::G - 1][u] : u % 2;
+    }
+    // The rows of the next window are loaded a few operands at a time behind the steps of scores and projection (a burst
+    // stalls the wave until memory has served the whole chip's), into the registers of a group whose q, k, v are done:
+    // first operand of group gi that step `step` loads, or -1
+    static constexpr int KPM = Cf::G == 1 ? 2 : 1; // operands per step and tile
+    static constexpr int load_at(int step, int gi)
+    {
+        const int m = step < 2 * Cf::HEADS ? (step % 2 ? step / 2 : -1) : step - Cf::HEADS;
+        const int k = (m - ((gi + 1) * Cf::HG - 1)) * KPM;
+        return m >= 0 && k >= 0 && k < Cf::KSX ? k : -1;
+    }
+    // vector-memory instructions a wave issues in a step at least: loads of the next window, stores of y, of `attn`
+    static constexpr int loads_in(int step)
+    {
+        int n = 0;
+        for (int gi = 0; gi < Cf::G; ++gi) n += load_at(step, gi) >= 0 ? 2 * KPM * TW : 0;
+        return n;
+    }
+    static constexpr int stores_in(int step) { return step < 2 * Cf::HEADS ? 0 : (OT_UNIT / 2 + OT_UNIT % 2) * TW; }
+    static constexpr int keeps_in(int step) { return step < 2 * Cf::HEADS && step % 2 && step / 2 % Cf::HG == Cf::HG - 1 ? Cf::HG * TW : 0; }
+    static constexpr bool slots_free()
+    {
+        for (int u = 0; u < 2 * NU; ++u) // (u: this round's and the next one's)
+            for (int v = 0; v < u; ++v) {
+                const int tu = unit_time(u % NU) + u / NU * NTIME, tv = unit_time(v % NU) + v / NU * NTIME;
+                if (unit_slot(u % NU) == unit_slot(v % NU) && tu - 1 <= tv + LATE) return false;
+            }
+        return true;
+    }
+    // K and V of a head, all windows of the workgroup, as the operands they are read as (1 KB per tile and kind)
+    static constexpr int KVBUF = MERGE ? 2 : 1;
+    static constexpr size_t KV_WIN = (size_t)2 * NT * 1024, KV_BYTES = WINS * KV_WIN;
+    // fp32 linear biases padded to whole tiles: [HEADS][q, k, v][32] (q in the scores' base-2 units; v of feature D: 1,
+    // see below), then b_proj [16 OT]
+    static constexpr int N_BQKV = Cf::HEADS * 3 * 32;
+    static constexpr size_t OFF_BIAS = 0;
+    static constexpr size_t OFF_TBL = (size_t)(N_BQKV + 16 * Cf::OT) * 4; // fp32 [HEADS][TP]
+    static constexpr size_t OFF_LN = OFF_TBL + (size_t)Cf::HEADS * TP * 4; // fp32 [HEADS][32][gamma, beta], head-padded
+    static constexpr size_t OFF_KV = OFF_LN + (size_t)Cf::HEADS * 32 * 8;
+    static constexpr size_t OFF_W = OFF_KV + KVBUF * KV_BYTES;
+    static constexpr size_t LDS_BYTES = OFF_W + NSLOT * UNIT_BYTES;
+    static_assert(OFF_LN % 16 == 0 && OFF_KV % 16 == 0 && OFF_W % 16 == 0 && LDS_BYTES <= 160 * 1024, "LDS budget");
+    static_assert(FR_UNIT % Cf::HEADS == 0 && Cf::OT % OT_UNIT == 0 && NU % 2 == 0 && NU <= 12,
                   "units tile the projection");
+    static_assert(!LATE || (NWAVES / 2) % WPW == 0, "a window's waves run at the same time");
     static_assert(Cf::ET == 2 && Cf::D + 1 <= 32 && Cf::CG % Cf::D == 0, "heads of 17..31 channels: two tiles, a spare row");
+    static_assert(NT % TW == 0 && NWAVES % WPW == 0, "whole windows per workgroup");
+    static_assert(TW == 1 || TW == 2, "tiles of a wave");
 };
+
+// waits until at most N vector-memory operations are outstanding, and for everything in LDS
+template <int N> __device__ __forceinline__ void wait_vm()
+{
+    static_assert(N < 64, "six bits");
+    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4));
+}
 
 template <int Q0> __device__ __forceinline__ float qgroup_bcast(float v)
 {
@@ -61,335 +141,489 @@ template <int Q0> __device__ __forceinline__ float qgroup_bcast(float v)
     return __uint_as_float(r[Q0 & 1]);
 }
 
-template <class Cf>
-__global__ __launch_bounds__(256, 1) void wide_fwd_kernel(Geom g, const bf16_t *__restrict__ x,
-                                                          const uint8_t *__restrict__ pack,
-                                                          bf16_t *__restrict__ y, bf16_t *__restrict__ attn)
+// LayerNorm of the wave's rows, held as operands in head-padded order (xh[group][step][tile]; zero beyond a head's
+// D features), in place: a row is spread over the four lanes that share l16.  Mean first, then the squared distances
+// from it, result rounded to bf16, as the LayerNorm kernels do it.  gb: (gamma, beta) pairs [head][32], zero beyond D.
+template <int G, int KSX, int TW, int C, int D>
+__device__ __forceinline__ void layer_norm_operands(uint4 (&xh)[G][KSX][TW], const float4 *gb, int q, float eps)
 {
-    using W = WideFwdCfg<Cf>;
+    const bool hx = 16 + 4 * q < D, hy = 16 + 4 * q + 2 < D;
+    float mean[TW], rstd[TW];
+#pragma unroll
+    for (int t = 0; t < TW; ++t) {
+        float sum = 0.f;
+#pragma unroll
+        for (int k = 0; k < G * KSX; ++k) {
+            const uint4 v = xh[k / KSX][k % KSX][t];
+            sum += (bf16_lo(v.x) + bf16_hi(v.x)) + (bf16_lo(v.y) + bf16_hi(v.y));
+            sum += (bf16_lo(v.z) + bf16_hi(v.z)) + (bf16_lo(v.w) + bf16_hi(v.w));
+        }
+        mean[t] = qgroup_sum(sum) / (float)C;
+        float dev = 0.f;
+#pragma unroll
+        for (int k = 0; k < G * KSX; ++k) {
+            const uint4 v = xh[k / KSX][k % KSX][t];
+            auto sq = [&](uint32_t u) {
+                const float a = bf16_lo(u) - mean[t], b = bf16_hi(u) - mean[t];
+                return a * a + b * b;
+            };
+            dev += sq(v.x) + sq(v.y);
+            dev += (hx ? sq(v.z) : 0.f) + (hy ? sq(v.w) : 0.f);
+        }
+        rstd[t] = rsqrtf(qgroup_sum(dev) / (float)C + eps);
+    }
+#pragma unroll
+    for (int k = 0; k < G * KSX; ++k) {
+        const float4 *p = gb + k * 16 + 2 * q;
+        const float4 g0 = p[0], g1 = p[1], g2 = p[8], g3 = p[9];
+#pragma unroll
+        for (int t = 0; t < TW; ++t) {
+            uint4 &v = xh[k / KSX][k % KSX][t];
+            auto norm = [&](uint32_t u, const float4 &g) {
+                return pack_bf16x2((bf16_lo(u) - mean[t]) * rstd[t] * g.x + g.y, (bf16_hi(u) - mean[t]) * rstd[t] * g.z + g.w);
+            };
+            v = make_uint4(norm(v.x, g0), norm(v.y, g1), norm(v.z, g2), norm(v.w, g3));
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+template <class Cf, int M, int TW>
+__global__ __launch_bounds__(512, 2) void wide_fwd_kernel(Geom g, const bf16_t *__restrict__ x,
+                                                          const uint8_t *__restrict__ pack,
+                                                          const bf16_t *__restrict__ table,
+                                                          bf16_t *__restrict__ y, bf16_t *__restrict__ attn,
+                                                          const bf16_t *__restrict__ ln_w, const bf16_t *__restrict__ ln_b,
+                                                          float ln_eps)
+{
+    using W = WideFwdCfg<Cf, M, TW>;
     constexpr int C = Cf::C, D = Cf::D, CG = Cf::CG, HG = Cf::HG, HEADS = Cf::HEADS, G = Cf::G;
-    constexpr int KSX = Cf::KSX, TP = Cf::TBW_PITCH, NU = W::NU, OT_UNIT = W::OT_UNIT;
-    constexpr int M = 8, NTHREADS = W::NTHREADS;
+    constexpr int KSX = Cf::KSX, TP = W::TP, OT_UNIT = W::OT_UNIT, NT = W::NT, NTB = W::NTB;
+    constexpr int NTHREADS = W::NTHREADS, RPT = W::RPT, STEP = RPT * (2 * M - 1);
     constexpr int FPW = (W::FR_UNIT + W::NWAVES - 1) / W::NWAVES; // fragments a wave moves per unit
-    constexpr int NTB = 2; // query tiles taken through the softmax together
+    static_assert(W::slots_free(), "no unit is overwritten while it is read");
 
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
 
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, q = lane >> 4;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wslot = wv / W::WPW;          // window of the workgroup this wave works on
+    const int t0 = (wv % W::WPW) * TW;      // its first tile in the window
     const int s = g.shift;
-    const int cn = l16 & 7, rsub = l16 >> 3;
+    const int cn = l16 % M, rsub = l16 / M;
     const int per_img = g.nwi * g.nwj;
     const uint32_t tbytes = (uint32_t)g.T * (2u * C);
     const buf_t xbuf = make_buf(x, tbytes), ybuf = make_buf(y, tbytes), abuf = make_buf(attn, attn ? tbytes : 0u);
-    // second half of a head's k-slots: features 16+4q..16+4q+3, of which only those below D exist
-    const uint32_t m_hx = (16 + 4 * q < D) ? 0xffffffffu : 0u, m_hy = (16 + 4 * q + 2 < D) ? 0xffffffffu : 0u;
     const uint32_t c8 = 8u * q;
 
-    // ---- weight stream: unit u of a window = QKV fragments of a head (or of its q, k or v alone),
-    // then projection fragments of OT_UNIT output tiles.  A thread stages its 16-byte pieces of the
-    // next unit in registers while the current unit is computed with, and writes them to the other
-    // LDS buffer afterwards; one barrier per unit. ----
+    const bool late = W::LATE && wv >= W::NWAVES / 2;
+
+    // ---- weight stream ----
     // (the lane index as a round's address arithmetic sees it: opaque, re-made every round, so that per-lane
     // addresses are computed where they are used instead of being kept, and spilled, across the kernel)
-    int lane_r = lane;
-    auto unit_src = [&](int u) {
-        return pack + (u < W::NHU ? Cf::P_WQW + (size_t)u * W::UNIT_BYTES
-                                  : Cf::P_WPW + (size_t)(u - W::NHU) * W::UNIT_BYTES);
+    int lane_r = lane, wv_r = wv;
+    // second half of a head's k-slots: features 16+4q..16+4q+3, of which only those below D exist
+    auto keep_hi = [&](uint4 &v) {
+        if (16 + 4 * (lane_r >> 4) >= D) v.z = 0u;
+        if (16 + 4 * (lane_r >> 4) + 2 >= D) v.w = 0u;
     };
     // Loads that write LDS directly: one instruction moves one fragment (64 lanes x 16 bytes land at
-    // the wave-uniform LDS address + 16 * lane).  Wave w moves fragments w, w + 4, ... of the unit.
-    auto stream_unit = [&](int u, int slot) {
-        const uint8_t *src = unit_src(u) + 16 * lane_r;
-        uint8_t *dst = lds + W::OFF_W + (size_t)slot * W::UNIT_BYTES;
+    // the wave-uniform LDS address + 16 * lane).  Wave w moves fragments w, w + 8, ... of the unit.
+    const uint32_t lds_w = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)lds + (uint32_t)W::OFF_W;
+    auto stream_unit = [&](int u) {
+        const uint8_t *src = pack + (u < HEADS ? Cf::P_WQW + (size_t)u * W::UNIT_BYTES
+                                               : Cf::P_WPW + (size_t)(u - HEADS) * W::UNIT_BYTES) +
+                             16 * lane_r + 1024 * wv_r;
+        const uint32_t dst = __builtin_amdgcn_readfirstlane(lds_w + (uint32_t)(W::unit_slot(u) * W::UNIT_BYTES) + 1024 * wv_r);
 #pragma unroll
-        for (int k = 0; k < FPW; ++k) {
-            const int f = k * W::NWAVES + wv;
-            if (f < W::FR_UNIT) lds_dma16(src + (size_t)f * 1024, dst + (size_t)f * 1024);
-        }
+        for (int k = 0; k < FPW; ++k)
+            if (k * W::NWAVES + wv_r < W::FR_UNIT) lds_dma16_at(src + k * W::NWAVES * 1024, dst + k * W::NWAVES * 1024);
     };
 
-    // ---- the window of this wave: byte offsets of its tokens (tile t, this lane's column) and its x as
-    // MFMA operands (all groups, head-padded order: step ks of group gi, tile t) ----
-    const int stride = W::NWAVES * (int)gridDim.x;
+    // ---- the tokens of this wave: byte offsets (tile t, this lane's column) and their x as MFMA
+    // operands (all groups, head-padded order: step ks of group gi, tile t) ----
+    const int stride = W::WINS * (int)gridDim.x;
     const int rounds = (g.nW + stride - 1) / stride;
-    uint32_t tok[4];
-    bool lastrow = false, lastcol = false;
-    uint4 xh[G][KSX][4];
+    uint32_t tok[TW], tokn[TW]; // of the window in hand, of the one whose rows are on their way
+    bool lastrow = false, lastcol = false, lastrow_n = false, lastcol_n = false;
+    uint4 xh[G][KSX][TW];
     auto window_tokens = [&](int win) {
         const int b = win / per_img;
         const int wr = win - b * per_img;
         const int wi = wr / g.nwj, wj = wr - wi * g.nwj;
-        lastrow = s > 0 && wi == g.nwi - 1;
-        lastcol = s > 0 && wj == g.nwj - 1;
+        lastrow_n = s > 0 && wi == g.nwi - 1;
+        lastcol_n = s > 0 && wj == g.nwj - 1;
         int sj = wj * M + cn + s;
         if (sj >= g.W) sj -= g.W;
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            int si = wi * M + 2 * t + rsub + s;
+        for (int t = 0; t < TW; ++t) {
+            int si = wi * M + RPT * (t0 + t) + rsub + s;
             if (si >= g.H) si -= g.H;
-            tok[t] = (uint32_t)((((b * g.H + si) * g.W) + sj) * C) * 2u;
+            tokn[t] = (uint32_t)((((b * g.H + si) * g.W) + sj) * C) * 2u;
         }
     };
-    auto load_x = [&]() {
+    auto load_x = [&](int gi, int ks) {
 #pragma unroll
-        for (int gi = 0; gi < G; ++gi)
-#pragma unroll
-            for (int ks = 0; ks < KSX; ++ks)
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    const uint32_t off = tok[t] + c8 + 2u * (gi * CG + ks * D);
-                    const uint2 lo = bload64(xbuf, off, 0u);
-                    uint2 hi = bload64(xbuf, off + 32u, 0u);
-                    hi.x &= m_hx;
-                    hi.y &= m_hy;
-                    xh[gi][ks][t] = cat(lo, hi);
-                }
+        for (int t = 0; t < TW; ++t) {
+            const uint32_t off = tokn[t] + c8 + 2u * (gi * CG + ks * D);
+            xh[gi][ks][t] = cat(bload64(xbuf, off, 0u), bload64(xbuf, off + 32u, 0u));
+        }
     };
-    int win = wv * (int)gridDim.x + (int)blockIdx.x;
+    int win = wslot * (int)gridDim.x + (int)blockIdx.x;
     bool active = win < g.nW;
     if (active) {
         window_tokens(win);
-        load_x();
+#pragma unroll
+        for (int gi = 0; gi < G; ++gi)
+#pragma unroll
+            for (int ks = 0; ks < KSX; ++ks) load_x(gi, ks);
     }
 
-    // set-up: linear biases, bias table, first unit
-    stream_unit(0, 0);
-    for (int i = tid; i < C; i += NTHREADS)
-        reinterpret_cast<uint4 *>(lds + W::OFF_BIAS)[i] = reinterpret_cast<const uint4 *>(pack + Cf::P_BIAS)[i];
-    for (int i = tid; i < HEADS * TP / 4; i += NTHREADS)
-        reinterpret_cast<uint4 *>(lds + W::OFF_TBL)[i] = reinterpret_cast<const uint4 *>(pack + Cf::P_TBW)[i];
+    // set-up: linear biases, bias table (base-2 units; last entry first, so that a lane's four key rows are four
+    // consecutive floats), LayerNorm's vectors, first unit
+    stream_unit(0);
+    {
+        const float *pb = reinterpret_cast<const float *>(pack + Cf::P_BIAS); // b_qkv [3C], b_proj [C]
+        float *bias = reinterpret_cast<float *>(lds + W::OFF_BIAS);
+        for (int i = tid; i < W::N_BQKV; i += NTHREADS) {
+            const int e = i & 31, t3 = (i >> 5) % 3, hd = i / 96;
+            float v = e < D ? pb[(hd / HG) * 3 * CG + t3 * CG + (hd % HG) * D + e] : 0.f;
+            if (t3 == 0) v *= kLog2e;
+            if (t3 == 2 && e == D) v = 1.f;
+            bias[i] = v;
+        }
+        for (int i = tid; i < 16 * Cf::OT; i += NTHREADS) bias[W::N_BQKV + i] = i < C ? pb[3 * C + i] : 0.f;
+    }
+    for (int i = tid; i < W::NTBL * HEADS; i += NTHREADS)
+        reinterpret_cast<float *>(lds + W::OFF_TBL)[(i % HEADS) * TP + W::NTBL - 1 - i / HEADS] = to_f32(table[i]) * kLog2e;
+    if (ln_w)
+        for (int i = tid; i < HEADS * 32; i += NTHREADS) {
+            const int e = i & 31, c = (i >> 5) * D + e;
+            reinterpret_cast<float2 *>(lds + W::OFF_LN)[i] = e < D ? make_float2(to_f32(ln_w[c]), to_f32(ln_b[c])) : make_float2(0.f, 0.f);
+        }
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
 
-    // this lane's query column (rn = 2nt + rsub, cn) against key rows 4q+j of key tile kt:
-    // key (2kt + q/2, 4(q%2) + j); table entry = tb0 + 30(nt - kt) - j
-    const int tb0 = (rsub - (q >> 1) + M - 1) * (2 * M - 1) + (cn - 4 * (q & 1) + M - 1);
-    const bool qc_w = cn >= M - s;
-    bool kc_w[4], qr_w[4], kr_w[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) kc_w[j] = (4 * (q & 1) + j) >= M - s;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        qr_w[t] = (2 * t + rsub) >= M - s;
-        kr_w[t] = (2 * t + (q >> 1)) >= M - s;
-    }
+    // this lane's query column (rn = RPT (t0 + ni) + rsub, cn) against key rows 4q+j of key tile kt: key
+    // (RPT kt + 4q/M, 4q%M + j); reversed table entry = tb0 + STEP (kt + TW-1 - ni) + j
+    const int key_r0 = (4 * q) / M, key_c0 = (4 * q) % M;
+    const int tb0 = W::NTBL - 1 - STEP * (TW - 1) -
+                    ((RPT * t0 + rsub - key_r0 + M - 1) * (2 * M - 1) + (cn - key_c0 + M - 1));
     const f32x4 zero4 = f32x4{0.f, 0.f, 0.f, 0.f};
 
+    // (a late wave's share of the unit its first step's time would have sent off)
+    if (late) {
+        if (W::unit_at(1) >= 0) stream_unit(W::unit_at(1));
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+    }
     for (int round = 0; round < rounds; ++round) {
         const bool more = round + 1 < rounds;
-        if (active && round > 0) {
-            window_tokens(win);
-            load_x();
-        }
+        const bool next = win + stride < g.nW;
         // head outputs, packed tile pairs [head][token tile]: operand of the cascade and of the projection
-        uint4 Ob[HEADS][4];
-        uint2 Qb[2][4], Kb[2][4], Vb[2][4];
+        uint4 Ob[HEADS][TW];
+        uint2 Qb[2][TW]; // q of the head whose scores come next
 
         uint32_t lds0 = 0;
         asm volatile("" : "+v"(lds0)); // keeps the LDS reads of a round inside the round
         lane_r = lane;
-        asm volatile("" : "+v"(lane_r));
+        wv_r = wv;
+        asm volatile("" : "+v"(lane_r), "+s"(wv_r));
         const float *bqkv = reinterpret_cast<const float *>(lds + lds0 + W::OFF_BIAS);
-        const float *bproj = bqkv + 3 * C;
+        const float *bproj = bqkv + W::N_BQKV;
         const float *tbl = reinterpret_cast<const float *>(lds + lds0 + W::OFF_TBL);
+        uint4 *kv = reinterpret_cast<uint4 *>(lds + lds0 + W::OFF_KV + (size_t)wslot * W::KV_WIN);
+        if (active) {
+#pragma unroll
+            for (int t = 0; t < TW; ++t) tok[t] = tokn[t];
+            lastrow = lastrow_n;
+            lastcol = lastcol_n;
+#pragma unroll
+            for (int gi = 0; gi < G; ++gi)
+#pragma unroll
+                for (int ks = 0; ks < KSX; ++ks)
+#pragma unroll
+                    for (int t = 0; t < TW; ++t) keep_hi(xh[gi][ks][t]);
+            if (ln_w)
+                layer_norm_operands<G, KSX, TW, C, D>(xh, reinterpret_cast<const float4 *>(lds + lds0 + W::OFF_LN), q, ln_eps);
+        }
 
-        static_for<NU>([&](auto u_) {
-            constexpr int u = decltype(u_)::value;
-            const uint4 *wu = reinterpret_cast<const uint4 *>(lds + lds0 + W::OFF_W + (size_t)(u & 1) * W::UNIT_BYTES);
-            // next unit on its way into the other buffer (the first of the next window after the last):
-            // every wave has passed the previous barrier, i.e. finished reading that buffer
-            if (u + 1 < NU) stream_unit(u + 1, (u + 1) & 1);
-            else if (more) stream_unit(0, 0);
-
-            if constexpr (u < W::NHU) {
-                constexpr int hd = u / W::UPH, part = u % W::UPH, gi = hd / HG, hl = hd % HG;
-                constexpr int T3B = part * (3 / W::UPH), T3E = T3B + 3 / W::UPH; // of q, k, v: this unit's
-                if (active) {
-                    if (G > 1 && part == 0 && hl == 0 && gi > 0 && g.cascade) { // Eq. 8
+        // scores, softmax and PV of head hd (K and V of all tiles of the window from LDS)
+        auto attention = [&](auto hd_) {
+            constexpr int hd = decltype(hd_)::value, gi = hd / HG, hl = hd % HG;
+            const uint4 *kvh = kv + (size_t)(hd % W::KVBUF) * (W::KV_BYTES / 16);
+            const float *tb = tbl + hd * TP + tb0;
 #pragma unroll
-                        for (int ks = 0; ks < KSX; ++ks)
+            for (int n0 = 0; n0 < TW; n0 += NTB) {
+                // S^T tiles (base-2 units), accumulated onto the relative bias: rows = keys 16kt+4q+j, column = query
+                f32x4 st[NTB][NT];
+                constexpr int KC = NT == 4 ? 4 : 1; // key tiles whose operands are read together, one chunk ahead of the products
+                uint4 kop[2][KC];
+                auto fetch = [&](int c) {
 #pragma unroll
-                            for (int t = 0; t < 4; ++t) {
-                                const uint4 p = Ob[(gi > 0 ? gi - 1 : 0) * HG + ks][t];
-                                uint4 &xv = xh[gi][ks][t];
-                                xv.x = add_bf16x2(xv.x, p.x);
-                                xv.y = add_bf16x2(xv.y, p.y);
-                                xv.z = add_bf16x2(xv.z, p.z & m_hx);
-                                xv.w = add_bf16x2(xv.w, p.w & m_hy);
-                            }
-                    }
-                    // ---- Q^T, K^T (rows = head features) and V (rows = tokens): eight independent
-                    // accumulator tiles per kind, so that consecutive MFMAs never wait for each other ----
-#pragma unroll
-                    for (int t3 = T3B; t3 < T3E; ++t3) {
-                        f32x4 acc[2][4];
-#pragma unroll
-                        for (int et = 0; et < 2; ++et) {
-                            f32x4 b4;
-                            if (t3 < 2) {
-#pragma unroll
-                                for (int j = 0; j < 4; ++j) {
-                                    const int e = 16 * et + 4 * q + j;
-                                    const float bv = e < D ? bqkv[gi * 3 * CG + t3 * CG + hl * D + e] : 0.f;
-                                    b4[j] = t3 == 0 ? bv * kLog2e : bv;
-                                }
-                            } else {
-                                // column D of V is one: row D of the PV product is the sum of the probabilities
-                                const int e = 16 * et + l16;
-                                const float bv = e < D ? bqkv[gi * 3 * CG + 2 * CG + hl * D + e] : (e == D ? 1.f : 0.f);
-                                b4 = f32x4{bv, bv, bv, bv};
-                            }
-#pragma unroll
-                            for (int t = 0; t < 4; ++t) acc[et][t] = b4;
-                        }
-#pragma unroll
-                        for (int ks = 0; ks < KSX; ++ks) {
-                            const uint4 f0 = wu[(((t3 - T3B) * 2 + 0) * KSX + ks) * 64 + lane];
-                            const uint4 f1 = wu[(((t3 - T3B) * 2 + 1) * KSX + ks) * 64 + lane];
-#pragma unroll
-                            for (int t = 0; t < 4; ++t) {
-                                const uint4 xv = xh[gi][ks][t];
-                                acc[0][t] = t3 < 2 ? mma32(f0, xv, acc[0][t]) : mma32(xv, f0, acc[0][t]);
-                                acc[1][t] = t3 < 2 ? mma32(f1, xv, acc[1][t]) : mma32(xv, f1, acc[1][t]);
-                            }
-                        }
-#pragma unroll
-                        for (int et = 0; et < 2; ++et)
-#pragma unroll
-                            for (int t = 0; t < 4; ++t) {
-                                const uint2 pk = pack_bf16x4(acc[et][t]);
-                                if (t3 == 0) Qb[et][t] = pk;
-                                else if (t3 == 1) Kb[et][t] = pk;
-                                else Vb[et][t] = pk;
-                            }
-                        __builtin_amdgcn_sched_barrier(0); // (keeps the scheduler from stretching the next stage's loads over this one)
-                    }
-                }
-                if constexpr (part == W::UPH - 1) {
-                if (active) {
-                    // relative bias of score tile (kt, nt) depends on nt - kt only: seven register tiles
-                    f32x4 bt[7];
-#pragma unroll
-                    for (int dl = 0; dl < 7; ++dl)
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) bt[dl][j] = tbl[hd * TP + tb0 + 30 * (dl - 3) - j];
-
-                    // S^T tiles (base-2 units): rows = keys 16kt+4q+j, column = query 16nt+l16; two query
-                    // tiles are taken through every stage together (independent chains)
-#pragma unroll
-                    for (int n0 = 0; n0 < 4; n0 += NTB) {
-                        f32x4 st[NTB][4];
-#pragma unroll
-                        for (int ni = 0; ni < NTB; ++ni) {
-                            const uint4 qop = cat(Qb[0][n0 + ni], Qb[1][n0 + ni]);
-#pragma unroll
-                            for (int kt = 0; kt < 4; ++kt)
-                                st[ni][kt] = mma32(cat(Kb[0][kt], Kb[1][kt]), qop, bt[n0 + ni - kt + 3]);
-                        }
-                        if (lastrow || lastcol) {
-#pragma unroll
-                            for (int ni = 0; ni < NTB; ++ni)
-#pragma unroll
-                                for (int kt = 0; kt < 4; ++kt)
-#pragma unroll
-                                    for (int j = 0; j < 4; ++j)
-                                        if ((lastrow && qr_w[n0 + ni] != kr_w[kt]) || (lastcol && qc_w != kc_w[j]))
-                                            st[ni][kt][j] += kMaskLog2;
-                        }
-                        float mx[NTB];
-#pragma unroll
-                        for (int ni = 0; ni < NTB; ++ni) {
-                            float m0 = fmaxf(fmaxf(st[ni][0][0], st[ni][0][1]), fmaxf(st[ni][0][2], st[ni][0][3]));
-#pragma unroll
-                            for (int kt = 1; kt < 4; ++kt)
-#pragma unroll
-                                for (int j = 0; j < 4; j += 2) m0 = fmaxf(fmaxf(m0, st[ni][kt][j]), st[ni][kt][j + 1]);
-                            mx[ni] = m0;
-                        }
-#pragma unroll
-                        for (int ni = 0; ni < NTB; ++ni) mx[ni] = qgroup_max(mx[ni]);
-                        uint2 Pb[NTB][4];
+                    for (int k = 0; k < KC; ++k) {
+                        const int kt = c * KC + k;
+                        kop[c & 1][k] = kvh[kt * 64 + lane];
 #pragma unroll
                         for (int ni = 0; ni < NTB; ++ni)
 #pragma unroll
-                            for (int kt = 0; kt < 4; ++kt) {
-#pragma unroll
-                                for (int j = 0; j < 4; ++j) st[ni][kt][j] = __builtin_amdgcn_exp2f(st[ni][kt][j] - mx[ni]);
-                                Pb[ni][kt] = pack_bf16x4(st[ni][kt]);
-                            }
-                        // O^T = V^T P^T: rows = head features (row D = sum of the probabilities)
-                        f32x4 o0[NTB], o1[NTB];
-#pragma unroll
-                        for (int ni = 0; ni < NTB; ++ni) {
-                            o0[ni] = mma32(cat(Vb[0][0], Vb[0][1]), cat(Pb[ni][0], Pb[ni][1]), zero4);
-                            o1[ni] = mma32(cat(Vb[1][0], Vb[1][1]), cat(Pb[ni][0], Pb[ni][1]), zero4);
-                        }
-#pragma unroll
-                        for (int ni = 0; ni < NTB; ++ni) {
-                            o0[ni] = mma32(cat(Vb[0][2], Vb[0][3]), cat(Pb[ni][2], Pb[ni][3]), o0[ni]);
-                            o1[ni] = mma32(cat(Vb[1][2], Vb[1][3]), cat(Pb[ni][2], Pb[ni][3]), o1[ni]);
-                        }
-#pragma unroll
-                        for (int ni = 0; ni < NTB; ++ni) {
-                            const float inv = __builtin_amdgcn_rcpf(qgroup_bcast<(D - 16) / 4>(o1[ni][(D - 16) % 4]));
-                            o0[ni] *= inv;
-                            o1[ni] *= inv;
-                            Ob[hd][n0 + ni] = cat(pack_bf16x4(o0[ni]), pack_bf16x4(o1[ni]));
-                        }
-                        __builtin_amdgcn_sched_barrier(0);
+                            for (int j = 0; j < 4; ++j) st[ni][kt][j] = tb[STEP * (kt + TW - 1 - (n0 + ni)) + j];
                     }
-                    // the outputs of a group leave together when the caller keeps them for the backward
-                    // pass (pieces of a row then fill whole cache lines)
-                    if (attn && hl == HG - 1) {
+                };
+                fetch(0);
 #pragma unroll
-                        for (int nt = 0; nt < 4; ++nt)
+                for (int c = 0; c < NT / KC; ++c) {
+                    if (c + 1 < NT / KC) fetch(c + 1);
+                    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                            for (int h2 = gi * HG; h2 <= hd; ++h2) {
-                                // lane group q: features 8q .. 8q+7 of the head (16 contiguous bytes)
-                                const uint32_t off = tok[nt] + 16u * q + 2u * (h2 * D);
-                                const uint4 o = pair_rows(make_uint2(Ob[h2][nt].x, Ob[h2][nt].y),
-                                                          make_uint2(Ob[h2][nt].z, Ob[h2][nt].w));
-                                if (8 * q + 8 <= D) {
-                                    bstore128(abuf, off, 0u, o);
-                                } else {
-                                    if (8 * q + 4 <= D) bstore64(abuf, off, 0u, make_uint2(o.x, o.y));
-                                    if (8 * q + 6 <= D) bstore32(abuf, off + 8u, 0u, o.z);
+                    for (int k = 0; k < KC; ++k)
+#pragma unroll
+                        for (int ni = 0; ni < NTB; ++ni) {
+                            const int kt = c * KC + k;
+                            st[ni][kt] = mma32(kop[c & 1][k], cat(Qb[0][n0 + ni], Qb[1][n0 + ni]), st[ni][kt]);
+                        }
+                }
+                constexpr int VC = NT == 4 ? 2 : 1; // (V the same way, in pairs of tiles; with few tiles the first under the softmax)
+                uint4 vop[2][2 * VC];
+                auto fetch_v = [&](int c) {
+#pragma unroll
+                    for (int k = 0; k < 2 * VC; ++k) vop[c & 1][k] = kvh[(NT + 2 * VC * c + k) * 64 + lane];
+                };
+                if (NT == 4) fetch_v(0);
+                if (lastrow || lastcol) {
+                    int s_ = s; // (opaque: the conditions are made here, not kept over the head)
+                    asm volatile("" : "+s"(s_));
+                    float cm[4];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) cm[j] = (lastcol && (cn >= M - s_) != (key_c0 + j >= M - s_)) ? kMaskLog2 : 0.f;
+#pragma unroll
+                    for (int ni = 0; ni < NTB; ++ni) {
+                        const bool qr_w = RPT * (t0 + n0 + ni) + rsub >= M - s_;
+#pragma unroll
+                        for (int kt = 0; kt < NT; ++kt) {
+                            const bool rm = lastrow && qr_w != (RPT * kt + key_r0 >= M - s_);
+#pragma unroll
+                            for (int j = 0; j < 4; ++j) st[ni][kt][j] += rm ? kMaskLog2 : cm[j];
+                        }
+                    }
+                }
+                float mx[NTB];
+#pragma unroll
+                for (int ni = 0; ni < NTB; ++ni) {
+                    float m0 = fmaxf(fmaxf(st[ni][0][0], st[ni][0][1]), fmaxf(st[ni][0][2], st[ni][0][3]));
+#pragma unroll
+                    for (int kt = 1; kt < NT; ++kt)
+#pragma unroll
+                        for (int j = 0; j < 4; j += 2) m0 = fmaxf(fmaxf(m0, st[ni][kt][j]), st[ni][kt][j + 1]);
+                    mx[ni] = m0;
+                }
+#pragma unroll
+                for (int ni = 0; ni < NTB; ++ni) mx[ni] = qgroup_max(mx[ni]);
+                uint2 Pb[NTB][NT];
+#pragma unroll
+                for (int ni = 0; ni < NTB; ++ni)
+#pragma unroll
+                    for (int kt = 0; kt < NT; ++kt) {
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) st[ni][kt][j] = __builtin_amdgcn_exp2f(st[ni][kt][j] - mx[ni]);
+                        Pb[ni][kt] = pack_bf16x4(st[ni][kt]);
+                    }
+                // O^T = V^T P^T: rows = head features (row D = sum of the probabilities)
+                f32x4 o0[NTB], o1[NTB];
+#pragma unroll
+                for (int ni = 0; ni < NTB; ++ni) o0[ni] = o1[ni] = zero4;
+#pragma unroll
+                for (int c = 0; c < NT / (2 * VC); ++c) {
+                    if (NT > 4 && c == 0) fetch_v(0);
+                    if (c + 1 < NT / (2 * VC)) fetch_v(c + 1);
+                    if (NT > 4) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int k = 0; k < VC; ++k)
+#pragma unroll
+                        for (int ni = 0; ni < NTB; ++ni) {
+                            const int kt = 2 * (VC * c + k);
+                            const uint4 p = cat(Pb[ni][kt], Pb[ni][kt + 1]);
+                            o0[ni] = mma32(vop[c & 1][2 * k], p, o0[ni]);
+                            o1[ni] = mma32(vop[c & 1][2 * k + 1], p, o1[ni]);
+                        }
+                }
+#pragma unroll
+                for (int ni = 0; ni < NTB; ++ni) {
+                    const float inv = __builtin_amdgcn_rcpf(qgroup_bcast<(D - 16) / 4>(o1[ni][(D - 16) % 4]));
+                    o0[ni] *= inv;
+                    o1[ni] *= inv;
+                    Ob[hd][n0 + ni] = cat(pack_bf16x4(o0[ni]), pack_bf16x4(o1[ni]));
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            // the outputs of a group leave together when the caller keeps them for the backward
+            // pass (pieces of a row then fill whole cache lines)
+            if (attn && hl == HG - 1) {
+#pragma unroll
+                for (int nt = 0; nt < TW; ++nt)
+#pragma unroll
+                    for (int h2 = gi * HG; h2 <= hd; ++h2) {
+                        // lane group q: features 8q .. 8q+7 of the head (16 contiguous bytes)
+                        const uint32_t off = tok[nt] + 16u * q + 2u * (h2 * D);
+                        const uint4 o = pair_rows(make_uint2(Ob[h2][nt].x, Ob[h2][nt].y),
+                                                  make_uint2(Ob[h2][nt].z, Ob[h2][nt].w));
+                        if (8 * q + 8 <= D) {
+                            bstore128(abuf, off, 0u, o);
+                        } else {
+                            if (8 * q + 4 <= D) bstore64(abuf, off, 0u, make_uint2(o.x, o.y));
+                            if (8 * q + 6 <= D) bstore32(abuf, off + 8u, 0u, o.z);
+                        }
+                    }
+            }
+        };
+
+        static_for<W::NS>([&](auto i_) {
+            constexpr int i = decltype(i_)::value, time = W::time_of(i);
+            constexpr bool first = i == 0 || W::time_of(i - 1) != time, last = i == W::NS - 1 || W::time_of(i + 1) != time;
+            // the unit that the next time reads first, on its way into a buffer that every wave has finished reading
+            // (late waves are one time further on)
+            constexpr int ue = W::unit_at((time + 1) % W::NTIME), ul = W::unit_at((time + 1 + W::LATE) % W::NTIME);
+            constexpr bool we = time + 1 >= W::NTIME, wl = time + 1 + W::LATE >= W::NTIME; // (of the next round)
+            if constexpr (first) {
+                if (!late) {
+                    if (ue >= 0 && (!we || more)) stream_unit(ue);
+                } else {
+                    if (ul >= 0 && (!wl || more)) stream_unit(ul);
+                }
+            }
+            if (next) {
+                static_for<G>([&](auto g_) {
+                    constexpr int gi = decltype(g_)::value, k0 = W::load_at(i, gi);
+                    if constexpr (k0 >= 0) {
+                        if constexpr (gi == 0 && k0 == 0) window_tokens(win + stride);
+#pragma unroll
+                        for (int ks = k0; ks < k0 + W::KPM; ++ks) load_x(gi, ks);
+                    }
+                });
+            }
+            const uint4 *wu;
+            if constexpr (i < 2 * HEADS) {
+                constexpr int hd = i / 2, gi = hd / HG, hl = hd % HG;
+                if constexpr (i % 2) {
+                    if (active) attention(std::integral_constant<int, hd>{});
+                } else if (active) {
+                    wu = reinterpret_cast<const uint4 *>(lds + lds0 + W::OFF_W + (size_t)W::unit_slot(hd) * W::UNIT_BYTES);
+                    if (G > 1 && hl == 0 && gi > 0 && g.cascade) { // Eq. 8
+#pragma unroll
+                        for (int ks = 0; ks < KSX; ++ks)
+#pragma unroll
+                            for (int t = 0; t < TW; ++t) {
+                                uint4 p = Ob[(gi > 0 ? gi - 1 : 0) * HG + ks][t];
+                                keep_hi(p);
+                                uint4 &xv = xh[gi][ks][t];
+                                xv.x = add_bf16x2(xv.x, p.x);
+                                xv.y = add_bf16x2(xv.y, p.y);
+                                xv.z = add_bf16x2(xv.z, p.z);
+                                xv.w = add_bf16x2(xv.w, p.w);
+                            }
+                    }
+                    // ---- Q^T, K^T (rows = head features) and V (rows = tokens) ----
+                    uint4 *kvw = kv + (size_t)(hd % W::KVBUF) * (W::KV_BYTES / 16);
+                    // (fragments and bias of the next kind are read under the products of the one in hand: left alone the
+                    // compiler keeps two reads in flight and waits for each pair)
+                    constexpr int KH = KSX > 3 ? KSX / 2 : KSX, NC = KSX / KH; // K steps of a chunk, chunks of a kind
+                    uint4 fr[2][2 * KH];
+                    f32x4 acc[2][TW];
+                    f32x4 b4[2];
+                    auto fetch = [&](int c) {
+                        const int t3 = c / NC, k0 = c % NC * KH;
+                        if (k0 == 0) {
+                            const float *bh = bqkv + (hd * 3 + t3) * 32;
+#pragma unroll
+                            for (int et = 0; et < 2; ++et) {
+                                if (t3 < 2) {
+                                    b4[et] = *reinterpret_cast<const f32x4 *>(bh + 16 * et + 4 * q);
+                                } else { // (column D of V is one: row D of the PV product is the sum of the probabilities)
+                                    const float bv = bh[16 * et + l16];
+                                    b4[et] = f32x4{bv, bv, bv, bv};
                                 }
                             }
+                        }
+#pragma unroll
+                        for (int ks = 0; ks < KH; ++ks)
+#pragma unroll
+                            for (int et = 0; et < 2; ++et) fr[c & 1][2 * ks + et] = wu[((t3 * 2 + et) * KSX + k0 + ks) * 64 + lane];
+                    };
+                    fetch(0);
+#pragma unroll
+                    for (int c = 0; c < 3 * NC; ++c) {
+                        const int t3 = c / NC, k0 = c % NC * KH;
+                        if (k0 == 0) {
+#pragma unroll
+                            for (int et = 0; et < 2; ++et)
+#pragma unroll
+                                for (int t = 0; t < TW; ++t) acc[et][t] = b4[et];
+                        }
+                        if (c + 1 < 3 * NC) fetch(c + 1);
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int ks = 0; ks < KH; ++ks)
+#pragma unroll
+                            for (int et = 0; et < 2; ++et) {
+                                const uint4 f = fr[c & 1][2 * ks + et];
+#pragma unroll
+                                for (int t = 0; t < TW; ++t) {
+                                    const uint4 xv = xh[gi][k0 + ks][t];
+                                    acc[et][t] = t3 < 2 ? mma32(f, xv, acc[et][t]) : mma32(xv, f, acc[et][t]);
+                                }
+                            }
+                        if (k0 + KH < KSX) continue;
+                        // q stays with the wave; k and v go to LDS as the operands the scores and PV read:
+                        // k tile by tile, v by pairs of tiles and per half of the features
+#pragma unroll
+                        for (int t = 0; t < TW; ++t) {
+                            const uint2 p0 = pack_bf16x4(acc[0][t]), p1 = pack_bf16x4(acc[1][t]);
+                            if (t3 == 0) {
+                                Qb[0][t] = p0;
+                                Qb[1][t] = p1;
+                            } else if (t3 == 1) {
+                                kvw[(t0 + t) * 64 + lane] = cat(p0, p1);
+                            } else {
+                                uint2 *vw = reinterpret_cast<uint2 *>(kvw + (NT + ((t0 + t) & ~1)) * 64 + lane) + ((t0 + t) & 1);
+                                vw[0] = p0;
+                                vw[128] = p1;
+                            }
+                        }
                     }
                 }
-                }
             } else {
+                constexpr int pu = i - 2 * HEADS;
+                wu = reinterpret_cast<const uint4 *>(lds + lds0 + W::OFF_W + (size_t)W::unit_slot(HEADS + pu) * W::UNIT_BYTES);
                 // ---- Y^T = Wproj A^T + b for OT_UNIT output tiles: rows = output channels, column = token ----
-                constexpr int pu = u - W::NHU;
                 if (active) {
                     // two output tiles at a time: their packed results are regrouped so that a lane holds 16
                     // contiguous bytes of its token's row (a tile left over at the end goes out in 8-byte pieces)
-                    auto project = [&](int ot, f32x4(&acc)[4]) {
+                    uint4 wf[2][HEADS]; // (fragments of the next tile are read under the products of the one in hand)
+                    auto fetch = [&](int oi) {
 #pragma unroll
-                        for (int j = 0; j < 4; ++j) {
-                            const int o = 16 * ot + 4 * q + j;
-                            const float bv = o < C ? bproj[o] : 0.f;
-#pragma unroll
-                            for (int t = 0; t < 4; ++t) acc[t][j] = bv;
-                        }
-#pragma unroll
-                        for (int hd = 0; hd < HEADS; ++hd) {
-                            const uint4 wf = wu[((ot - pu * OT_UNIT) * HEADS + hd) * 64 + lane];
-#pragma unroll
-                            for (int t = 0; t < 4; ++t) acc[t] = mma32(wf, Ob[hd][t], acc[t]);
-                        }
+                        for (int hd = 0; hd < HEADS; ++hd) wf[oi & 1][hd] = wu[(oi * HEADS + hd) * 64 + lane];
                     };
+                    auto project = [&](int oi, f32x4(&acc)[TW]) {
+                        const f32x4 b4 = *reinterpret_cast<const f32x4 *>(bproj + 16 * (pu * OT_UNIT + oi) + 4 * q);
+                        if (oi + 1 < OT_UNIT) fetch(oi + 1);
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int t = 0; t < TW; ++t) acc[t] = b4;
+#pragma unroll
+                        for (int hd = 0; hd < HEADS; ++hd)
+#pragma unroll
+                            for (int t = 0; t < TW; ++t) acc[t] = mma32(wf[oi & 1][hd], Ob[hd][t], acc[t]);
+                    };
+                    fetch(0);
 #pragma unroll
                     for (int oi = 0; oi + 1 < OT_UNIT; oi += 2) {
                         const int ot = pu * OT_UNIT + oi;
-                        f32x4 acc0[4], acc1[4];
-                        project(ot, acc0);
-                        project(ot + 1, acc1);
+                        f32x4 acc0[TW], acc1[TW];
+                        project(oi, acc0);
+                        project(oi + 1, acc1);
                         const int o0 = 16 * ot + 8 * q; // first channel of this lane's eight
 #pragma unroll
-                        for (int t = 0; t < 4; ++t) {
+                        for (int t = 0; t < TW; ++t) {
                             const uint4 v = pair_rows(pack_bf16x4(acc0[t]), pack_bf16x4(acc1[t]));
                             const uint32_t off = tok[t] + 2u * o0;
                             if (o0 + 8 <= C) bstore128(ybuf, off, 0u, v);
@@ -399,39 +633,52 @@ __global__ __launch_bounds__(256, 1) void wide_fwd_kernel(Geom g, const bf16_t *
                     }
                     if (OT_UNIT % 2 == 1) {
                         const int ot = pu * OT_UNIT + OT_UNIT - 1;
-                        f32x4 acc[4];
-                        project(ot, acc);
+                        f32x4 acc[TW];
+                        project(OT_UNIT - 1, acc);
                         const int o0 = 16 * ot + 4 * q;
 #pragma unroll
-                        for (int t = 0; t < 4; ++t)
+                        for (int t = 0; t < TW; ++t)
                             if (o0 < C) bstore64(ybuf, tok[t] + c8 + 32u * ot, 0u, pack_bf16x4(acc[t]));
                         __builtin_amdgcn_sched_barrier(0);
                     }
                 }
             }
-            // the next unit has landed in LDS before any wave reads it
-            __builtin_amdgcn_s_waitcnt(0);
-            __syncthreads();
+            // Before the barrier: the wave's share of the next unit has landed in LDS, its k and v are written and read.
+            // Vector-memory operations complete in the order they were issued: "at most n outstanding" covers the
+            // stream loads when at least n were issued behind them.
+            if constexpr (last) {
+                constexpr int p = first ? i : i - 1; // the other step of this time
+                constexpr int NY = W::stores_in(i) + (first ? 0 : W::stores_in(p)), NX = W::loads_in(i) + (first ? 0 : W::loads_in(p)),
+                              NA = W::keeps_in(i) + (first ? 0 : W::keeps_in(p));
+                __builtin_amdgcn_sched_barrier(0);
+                if ((late ? ul : ue) < 0) wait_vm<63>();
+                else if (!active) wait_vm<0>();
+                else if (NA && attn) { if (next) wait_vm<NX + NY + NA>(); else wait_vm<NY + NA>(); }
+                else if (NX && next) wait_vm<NX + NY>();
+                else wait_vm<NY>();
+                __syncthreads();
+            }
         });
         win += stride;
-        active = win < g.nW;
+        active = next;
     }
+    if (W::LATE && !late) __syncthreads(); // (as many barriers for every wave)
 }
 
 #define GSWA_WIDE_SHAPES(X) X(180, 6, 1) X(180, 6, 2) X(180, 6, 3)
 
-template <class Cf>
-hipError_t run_wide_fwd(const Geom &g, const bf16_t *x, const uint8_t *pack, bf16_t *y, bf16_t *attn, int training,
-                        hipStream_t s)
+template <class Cf, int M, int TW>
+hipError_t run_wide_fwd(const Geom &g, const bf16_t *x, const uint8_t *pack, const bf16_t *table, bf16_t *y, bf16_t *attn,
+                        const FusedLn &ln, hipStream_t s)
 {
-    using W = WideFwdCfg<Cf>;
-    auto kern = wide_fwd_kernel<Cf>;
+    using W = WideFwdCfg<Cf, M, TW>;
+    auto kern = wide_fwd_kernel<Cf, M, TW>;
     if (hipError_t ea = allow_dynamic_lds(reinterpret_cast<const void *>(kern), W::LDS_BYTES); ea != hipSuccess) return ea;
-    // one window per wave: spread the windows over the compute units before filling a workgroup
+    // spread the windows over the compute units before filling a workgroup
     int grid = device_cu_count();
     if (grid > g.nW) grid = g.nW;
     KernelTimer kt(K_FUSED_FWD, s);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(W::NTHREADS), W::LDS_BYTES, s, g, x, pack, y, training ? attn : nullptr);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(W::NTHREADS), W::LDS_BYTES, s, g, x, pack, table, y, attn, ln.w, ln.b, ln.eps);
     return hipGetLastError();
 }
 
@@ -439,7 +686,7 @@ hipError_t run_wide_fwd(const Geom &g, const bf16_t *x, const uint8_t *pack, bf1
 
 bool wide_fwd_supported(const Geom &g)
 {
-    if (g.M != 8 || g.dq != g.d || (long)g.T * g.C >= (1L << 31)) return false;
+    if ((g.M != 8 && g.M != 16) || g.dq != g.d || (long)g.T * g.C >= (1L << 31)) return false;
 #define X(C_, H_, G_) \
     if (g.C == C_ && g.heads == H_ && g.groups == G_) return true;
     GSWA_WIDE_SHAPES(X)
@@ -447,13 +694,18 @@ bool wide_fwd_supported(const Geom &g)
     return false;
 }
 
-hipError_t launch_wide_fwd(const Geom &g, const bf16_t *x, const void *pack, bf16_t *y, bf16_t *attn, int training,
-                           hipStream_t s)
+hipError_t launch_wide_fwd(const Geom &g, const bf16_t *x, const void *pack, const bf16_t *table, bf16_t *y, bf16_t *attn,
+                           int training, const FusedLn &ln, hipStream_t s)
 {
     if (training && !attn) return hipErrorInvalidValue;
-#define X(C_, H_, G_)                                 \
-    if (g.C == C_ && g.heads == H_ && g.groups == G_) \
-        return run_wide_fwd<FusedCfg<C_, H_, G_>>(g, x, static_cast<const uint8_t *>(pack), y, attn, training, s);
+    const uint8_t *p = static_cast<const uint8_t *>(pack);
+    bf16_t *at = training ? attn : nullptr;
+#define X(C_, H_, G_)                                                                             \
+    if (g.C == C_ && g.heads == H_ && g.groups == G_) {                                           \
+        using Cf = FusedCfg<C_, H_, G_>;                                                          \
+        return g.M == 16 ? run_wide_fwd<Cf, 16, 2>(g, x, p, table, y, at, ln, s)                  \
+                         : run_wide_fwd<Cf, 8, 2>(g, x, p, table, y, at, ln, s);                  \
+    }
     GSWA_WIDE_SHAPES(X)
 #undef X
     return hipErrorInvalidValue;

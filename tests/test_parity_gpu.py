@@ -96,6 +96,34 @@ def test_accumulate_flag_on_wide_fused_path(oracle, groups):
         assert parity.rel_err(got[k] - 0.5, 2.0 * want[k]) <= parity.TOL["bf16"], k
 
 
+@pytest.mark.parametrize("groups", [1, 2, 3])
+@pytest.mark.parametrize("B,H,W,window,shift", [
+    (1, 8, 8, 8, 4),         # one window: three of four window slots of the workgroup empty
+    (3, 24, 328, 8, 3),      # 369 windows, odd shift: the second slot partly filled
+    (1, 328, 216, 8, 0),     # 1107 windows: a second round of a few slots
+    (1, 16, 16, 16, 8),
+    (1, 304, 224, 16, 5),    # 266 windows: a second round of a few workgroups
+])
+def test_wide_forward_in_one_launch(oracle, B, H, W, window, shift, groups):
+    """The forward of a wide layer: one launch besides the packing for both window sizes; training and inference
+    give the same bits."""
+    x, dy, p = parity.make_inputs(B, H, W, 180, 6, groups, window, "bf16", synth.LAYER_SEED0 + 3, "stress")
+    want = parity.oracle_results(oracle, x, dy, p, 6, groups, window, shift, backward=False)["y"]
+    with parity.launched() as names:
+        got, _ = parity.gpu_results(x, dy, p, 6, groups, window, shift, "bf16", backward=False)
+    assert names == {"pack_fwd", "fused_fwd"}
+    assert parity.rel_err(got["y"], want) <= parity.TOL["bf16"]
+    assert all(e <= parity.TOL["bf16"] for e in parity.border_errs({"y": got["y"]}, {"y": want}, window, shift).values())
+    from paper_2409_06206_amd import runner
+    import torch
+    layer = runner.DeviceLayer(B, H, W, 180, 6, groups, window, shift, "bf16")
+    layer.set_params(p)
+    layer.set_inputs(x, dy)
+    layer.forward(keep=True)
+    torch.cuda.synchronize()
+    assert np.array_equal(layer.results()["y"], got["y"])
+
+
 def test_kernel_timing_aid_reports_the_launched_kernels():
     """gswa_profile_*: per-kernel HIP-event totals for one forward + backward."""
     import torch
