@@ -107,11 +107,13 @@ struct FusedLn {
 
 // y = GSWA(x); attn_out receives the concatenated group outputs [T, C] (may be null unless
 // fused_fwd_needs_attn); `pack` receives the packed parameters (fused_pack_bytes, 256-byte aligned), or holds them already (`packed`).
+// `ln`: only where wide_fwd_supported.
 // `training`: attn_out is kept by the caller for the backward pass (otherwise it is scratch and a
 // kernel may leave out what only the backward would read).
 hipError_t launch_fused_fwd(const Geom &g, const bf16_t *x, const bf16_t *w_qkv, const bf16_t *b_qkv,
                             const bf16_t *w_proj, const bf16_t *b_proj, const bf16_t *table,
-                            bf16_t *y, bf16_t *attn_out, void *pack, int training, bool packed, hipStream_t s);
+                            bf16_t *y, bf16_t *attn_out, void *pack, int training, bool packed, const FusedLn &ln,
+                            hipStream_t s);
 
 // ---------------------------------------------------------------------------------------
 // Parameter packing for this kernel (layout: FusedCfg, WQW / WPW / TBW)

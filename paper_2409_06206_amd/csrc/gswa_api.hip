@@ -439,9 +439,15 @@ int gswa::attn_backward_check(const gswa_desc *desc, const void *x, const void *
                           dbias_table, ws, &g, &s);
 }
 
+bool gswa::attn_forward_takes_ln(const gswa_desc *desc)
+{
+    Geom g;
+    return make_geom(desc, &g) == GSWA_OK && use_fused_fwd(desc, g) && wide_fwd_supported(g);
+}
+
 int gswa::attn_forward(const gswa_desc *desc, const void *x, const void *w_qkv, const void *b_qkv,
                  const void *w_proj, const void *b_proj, const void *bias_table, void *y,
-                 void *saved, void *ws, bool packed, void *hip_stream)
+                 void *saved, void *ws, bool packed, const AttnLn *ln, void *hip_stream)
 {
     Geom g;
     Sizes s;
@@ -464,9 +470,11 @@ int gswa::attn_forward(const gswa_desc *desc, const void *x, const void *w_qkv, 
         void *pack = saved ? static_cast<void *>(static_cast<char *>(saved) + s.act) : ws;
         void *attn = saved;
         if (!saved && fused_fwd_needs_attn(g)) attn = static_cast<char *>(ws) + s.pack;
-        hipError_t e = launch_fused_fwd(g, (const bf16_t *)x, (const bf16_t *)w_qkv, (const bf16_t *)b_qkv,
+        FusedLn fl{};
+        if (ln) { fl.w = (const bf16_t *)ln->w; fl.b = (const bf16_t *)ln->b; fl.eps = ln->eps; }
+        hipError_t e = launch_fused_fwd(g, (const bf16_t *)(ln ? ln->x : x), (const bf16_t *)w_qkv, (const bf16_t *)b_qkv,
                                         (const bf16_t *)w_proj, (const bf16_t *)b_proj,
-                                        (const bf16_t *)bias_table, (bf16_t *)y, (bf16_t *)attn, pack, saved ? 1 : 0, packed, st);
+                                        (const bf16_t *)bias_table, (bf16_t *)y, (bf16_t *)attn, pack, saved ? 1 : 0, packed, fl, st);
         return e == hipSuccess ? GSWA_OK : hip_fail(e);
     }
     if (!(desc->flags & GSWA_FORCE_STAGED) && window_fwd_supported(g)) {
@@ -514,7 +522,7 @@ int gswa_forward(const gswa_desc *desc, const void *x, const void *w_qkv, const 
                  const void *w_proj, const void *b_proj, const void *bias_table, void *y,
                  void *saved, void *ws, void *hip_stream)
 {
-    return attn_forward(desc, x, w_qkv, b_qkv, w_proj, b_proj, bias_table, y, saved, ws, false, hip_stream);
+    return attn_forward(desc, x, w_qkv, b_qkv, w_proj, b_proj, bias_table, y, saved, ws, false, nullptr, hip_stream);
 }
 
 int gswa_backward(const gswa_desc *desc, const void *x, const void *dy, const void *w_qkv,

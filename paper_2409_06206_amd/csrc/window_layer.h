@@ -30,9 +30,15 @@ struct WindowLayerGrads {
 int make_geom(const gswa_desc *d, Geom *g);
 
 // gswa_forward; `packed`: ws holds this layer's repacked parameters from an earlier inference call of the same descriptor
-// (layers of the kernels that read them repacked; the others take no notice).
+// (layers of the kernels that read them repacked; the others take no notice).  `ln` (only where attn_forward_takes_ln):
+// the layer is applied to LayerNorm(ln->x); `x` then only names the memory that LayerNorm would have been written to.
+struct AttnLn {
+    const void *x, *w, *b;
+    float eps;
+};
+bool attn_forward_takes_ln(const gswa_desc *d);
 int attn_forward(const gswa_desc *d, const void *x, const void *w_qkv, const void *b_qkv, const void *w_proj, const void *b_proj,
-                 const void *bias_table, void *y, void *saved, void *ws, bool packed, void *hip_stream);
+                 const void *bias_table, void *y, void *saved, void *ws, bool packed, const AttnLn *ln, void *hip_stream);
 
 // The rules of gswa_forward's and gswa_backward's arguments alone (nothing is enqueued): for callers that run the
 // attention layer inside a kernel of their own.

@@ -447,6 +447,32 @@ def test_band_by_band_inference_is_the_whole_map_inference(case, bands):
     assert parity.rel_err(runner.to_host(st.y), runner.to_host(whole)) <= (1e-6 if dtype == "f32" else 2e-2)
 
 
+@pytest.mark.parametrize("groups,window,shift", [(1, 8, 4), (2, 8, 3), (3, 16, 8)])
+def test_wide_layers_take_ln1_in_the_attention_kernel(groups, window, shift):
+    """Wide layers with the streaming MLP kernels: no launch of LN_1, so that a sequence gives the bits of the banded
+    call and of single layer calls, kept state or not."""
+    import torch
+    from paper_2409_06206_amd import runner
+    B, H, W, L, hidden = 2, 3 * window, 5 * window, 3, 360
+    ps = [{k: synth.quantize(v, "bf16") for k, v in synth.astl_params(180, 6, groups, window, hidden, 500 + l, "stress").items()}
+          for l in range(L)]
+    x, dy = (synth.quantize(a, "bf16") for a in synth.activations(B, H, W, 180, 1))
+    st = runner.DeviceStack(B, H, W, 180, 6, groups, window, shift, "bf16", hidden, L, 0)
+    st.set_params(ps)
+    st.set_inputs(x)
+    with parity.launched() as names:
+        st.forward(keep=False)
+    assert "mlp_fwd" in names and "ln_fwd" not in names, names
+    whole = st.y.clone()
+    for run in (lambda: st.forward_tiled(1), lambda: st.forward(keep=True)):
+        st.y.fill_(float("nan"))
+        run()
+        torch.cuda.synchronize()
+        assert torch.equal(st.y, whole)
+    kw = dict(heads=6, groups=groups, window=window, shift=shift, store=lambda a: synth.quantize(a, "bf16"))
+    assert parity.rel_err(runner.to_host(whole), astl_oracle.stack_forward(x, ps, **kw)) <= parity.TOL["bf16"]
+
+
 def test_inference_sequence_at_the_benchmark_size():
     """astl_infer_stack6 as bench.py runs it (six whole layers, one 512x512 map, C = 180, hidden 360, in one
     call): every output element against the oracle's loop over the layers, and the band-by-band form on the
