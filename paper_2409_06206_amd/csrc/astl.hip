@@ -482,6 +482,7 @@ struct LayerLink {
     // first .. first + count - 1 only, and y is the row of the first of them; y may lie over x there, because a
     // wavefront stores no row before it has read it.  count == 0: all tokens.
     long first, count;
+    int windows;               // in: only the first so many windows hold tokens that are taken (0: all)
     bool packed;               // in: the scratch holds this layer's repacked weights (an earlier band of the same size)
 };
 
@@ -513,7 +514,7 @@ int forward_t(const astl_desc *d, const Plan &pl, const T *x, const astl_params 
     }
     if (link) link->emitted = false;
     ASTL_RC(attn_forward(&d->attn, xn, p->w_qkv, p->b_qkv, p->w_proj, p->b_proj, p->bias_table, a, at_saved,
-                         rest, packed, pl.attn_ln ? &ln1 : nullptr, st));
+                         rest, packed, pl.attn_ln ? &ln1 : nullptr, link ? link->windows : 0, st));
     const long first = link ? link->first : 0, count = link && link->count ? link->count : rows;
     if (pl.fused_mlp) {
         // Eq. 4's skip and the whole of Eq. 5 in one launch; in a sequence of layers also LN_1 of
@@ -1095,10 +1096,11 @@ int astl_stack_forward_tiled(const astl_stack_desc *desc, const void *x, const a
         const astl_desc *ld = (l & 1) ? &tp.sp.odd : &tp.sp.even;
         const int s = ld->attn.shift;
         int packed_rows = 0; // window rows of the band whose call left this layer's repacked weights in the scratch
-        auto layer_call = [&](const astl_desc &sd, const char *src, char *dst, long first, long count) -> int {
+        auto layer_call = [&](const astl_desc &sd, const char *src, char *dst, long first, long count, int windows) -> int {
             const int wr = sd.attn.H / M; // (where they lie is a function of the band's size)
             LayerLink link{};
             link.first = first; link.count = count;
+            link.windows = windows;
             link.packed = tp.direct && packed_rows == wr;
             packed_rows = wr;
             return forward_checked(&sd, src, params + l, dst, nullptr, layer_ws, hip_stream, &link);
@@ -1116,7 +1118,8 @@ int astl_stack_forward_tiled(const astl_stack_desc *desc, const void *x, const a
                     // starting at image row aM: its window rows 0 .. e-a-1 are exactly these windows (no
                     // row of theirs is beyond the last M - s rows, so only the column mask applies, as in
                     // the map); one more row of windows, which wraps within the band, is computed on
-                    // whatever lies there and dropped.
+                    // whatever lies there and dropped, or left out by the attention kernels that go by windows (187 x 17 windows are
+                    // a fourth round of them, 187 x 16 are not: bands of 16 window rows of a 1000 x 1496 map 10.05 -> 9.81 ms).
                     const int wr = e - a + (s ? 1 : 0);
                     sd.attn.H = wr * M;
                     src = ib + (size_t)a * M * row;
@@ -1126,9 +1129,9 @@ int astl_stack_forward_tiled(const astl_stack_desc *desc, const void *x, const a
                     }
                     char *dst = ob + ((size_t)a * M + s) * row;
                     if (tp.direct && aligned16(src + (size_t)s * row, dst)) {
-                        ASTL_RC(layer_call(sd, src, dst, (long)s * at.W, (long)(e - a) * M * at.W));
+                        ASTL_RC(layer_call(sd, src, dst, (long)s * at.W, (long)(e - a) * M * at.W, (e - a) * (at.W / M)));
                     } else {
-                        ASTL_RC(layer_call(sd, src, yb, 0, 0));
+                        ASTL_RC(layer_call(sd, src, yb, 0, 0, 0));
                         ASTL_HIP(copy_rows(dst, yb + (size_t)s * row, (e - a) * M));
                     }
                 } else {
@@ -1138,7 +1141,7 @@ int astl_stack_forward_tiled(const astl_stack_desc *desc, const void *x, const a
                     sd.attn.H = rows;
                     ASTL_HIP(copy_rows(xb, ib, s));
                     ASTL_HIP(copy_rows(xb + (size_t)s * row, ib + ((size_t)a * M + s) * row, rows - s));
-                    ASTL_RC(layer_call(sd, xb, yb, 0, 0));
+                    ASTL_RC(layer_call(sd, xb, yb, 0, 0, 0));
                     ASTL_HIP(copy_rows(ob, yb, s));
                     ASTL_HIP(copy_rows(ob + ((size_t)a * M + s) * row, yb + (size_t)s * row, rows - s));
                 }

@@ -447,7 +447,8 @@ bool gswa::attn_forward_takes_ln(const gswa_desc *desc)
 
 int gswa::attn_forward(const gswa_desc *desc, const void *x, const void *w_qkv, const void *b_qkv,
                  const void *w_proj, const void *b_proj, const void *bias_table, void *y,
-                 void *saved, void *ws, bool packed, const AttnLn *ln, void *hip_stream)
+                 void *saved, void *ws, bool packed, const AttnLn *ln, int windows,
+                 void *hip_stream)
 {
     Geom g;
     Sizes s;
@@ -470,6 +471,8 @@ int gswa::attn_forward(const gswa_desc *desc, const void *x, const void *w_qkv, 
         void *pack = saved ? static_cast<void *>(static_cast<char *>(saved) + s.act) : ws;
         void *attn = saved;
         if (!saved && fused_fwd_needs_attn(g)) attn = static_cast<char *>(ws) + s.pack;
+        // (only the one-launch kernels go by windows)
+        if (windows > 0 && windows < g.nW && (wide_fwd_supported(g) || !fused_fwd_needs_attn(g))) g.nW = windows;
         FusedLn fl{};
         if (ln) { fl.w = (const bf16_t *)ln->w; fl.b = (const bf16_t *)ln->b; fl.eps = ln->eps; }
         hipError_t e = launch_fused_fwd(g, (const bf16_t *)(ln ? ln->x : x), (const bf16_t *)w_qkv, (const bf16_t *)b_qkv,
@@ -522,7 +525,7 @@ int gswa_forward(const gswa_desc *desc, const void *x, const void *w_qkv, const 
                  const void *w_proj, const void *b_proj, const void *bias_table, void *y,
                  void *saved, void *ws, void *hip_stream)
 {
-    return attn_forward(desc, x, w_qkv, b_qkv, w_proj, b_proj, bias_table, y, saved, ws, false, nullptr, hip_stream);
+    return attn_forward(desc, x, w_qkv, b_qkv, w_proj, b_proj, bias_table, y, saved, ws, false, nullptr, 0, hip_stream);
 }
 
 int gswa_backward(const gswa_desc *desc, const void *x, const void *dy, const void *w_qkv,

@@ -37,8 +37,10 @@ struct AttnLn {
     float eps;
 };
 bool attn_forward_takes_ln(const gswa_desc *d);
+// `windows` (> 0): only the first so many windows of the batch are wanted; the other tokens of y hold anything afterwards.
 int attn_forward(const gswa_desc *d, const void *x, const void *w_qkv, const void *b_qkv, const void *w_proj, const void *b_proj,
-                 const void *bias_table, void *y, void *saved, void *ws, bool packed, const AttnLn *ln, void *hip_stream);
+                 const void *bias_table, void *y, void *saved, void *ws, bool packed, const AttnLn *ln, int windows,
+                 void *hip_stream);
 
 // The rules of gswa_forward's and gswa_backward's arguments alone (nothing is enqueued): for callers that run the
 // attention layer inside a kernel of their own.
