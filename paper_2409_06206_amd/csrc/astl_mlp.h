@@ -11,6 +11,28 @@ bool astl_mlp_supported(int C, int hidden);
 // Bytes of the weights repacked for the matrix cores (written by the forward, read by both passes).
 size_t astl_mlp_pack_bytes();
 
+// Weights of several layers of one shape repacked by one launch (all layers of a sequence: a launch of its own per layer
+// is 4 us of which the weights' way through the chip is a fraction).
+struct MlpPackJob {
+    const bf16_t *ln_w, *ln_b, *w_fc1, *b_fc1, *w_fc2, *b_fc2;
+    void *pack, *bwd_pack; // bwd_pack: wide layers only (may be null)
+};
+constexpr int kMaxPackJobs = 16;
+hipError_t launch_astl_mlp_pack(int C, int hidden, const MlpPackJob *jobs, int n, hipStream_t s);
+hipError_t launch_astl_mlp_wide_pack(int C, int hidden, const MlpPackJob *jobs, int n, hipStream_t s);
+
+// The part of the repacked weights that the forward reads, for 32 < C <= 64 and 64 < hidden <= 128 (units of 16 bytes):
+// W1 diag(gamma) fragments [FT][2 K steps][64], W2 fragments [channel tiles][KSF K steps][64], biases b1 + W1 beta, b2.
+struct NarrowMlpPack {
+    static constexpr int FT = 8, KSF = 4, W2 = 1024, FLOATS = 2048, SRC_FLOATS = 4096;
+    static constexpr size_t LDS_BYTES = (size_t)FLOATS * 16 + 192 * 4;
+    // into LDS, by n threads
+    static __device__ __forceinline__ void stage(uint4 *dst, const uint4 *src, int tid, int n)
+    {
+        for (int i = tid; i < FLOATS + 48; i += n) dst[i] = src[i < FLOATS ? i : i + SRC_FLOATS - FLOATS];
+    }
+};
+
 // x1 = x + a (stored);  y = MLP(LN_2(x1)) + x1.  rows tokens of C channels.  `pack` receives the
 // repacked weights (astl_mlp_pack_bytes() bytes, 16-byte aligned), or holds them already (`packed`).  y may be x: a
 // wavefront stores rows that it has read and nobody else reads.  With next_ln_out non-null the

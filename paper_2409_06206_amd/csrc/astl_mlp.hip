@@ -84,16 +84,24 @@ template <int KSC, int KSF> struct PackLayout {
     static constexpr int nfloats = (FT + CT) * 16;
     static constexpr size_t bytes = (size_t)4 * frag * 16 + (size_t)nfloats * 4;
 };
+static_assert(PackLayout<2, 4>::w2f == NarrowMlpPack::W2 && PackLayout<2, 4>::floats_at == NarrowMlpPack::SRC_FLOATS &&
+                  PackLayout<2, 4>::nfloats == 192 && PackLayout<2, 4>::FT == NarrowMlpPack::FT,
+              "the whole-layer kernel reads this layout");
 
+struct MlpPackJobs {
+    MlpPackJob j[kMaxPackJobs];
+    int C, Hd;
+};
 // Once per forward call: the MLP's weights into MFMA fragment order (gamma and beta of LN_2 folded
 // into the first layer); the backward pass reads the same pack.
 template <int KSC, int KSF>
-__global__ __launch_bounds__(kMlpThreads) void astl_mlp_pack_kernel(MlpArgs a)
+__global__ __launch_bounds__(kMlpThreads) void astl_mlp_pack_kernel(MlpPackJobs jobs)
 {
+    const MlpPackJob &a = jobs.j[blockIdx.y];
     using L = PackLayout<KSC, KSF>;
     constexpr int CT = L::CT, FT = L::FT;
     uint4 *pk = static_cast<uint4 *>(a.pack);
-    const int C = a.C, Hd = a.Hd;
+    const int C = jobs.C, Hd = jobs.Hd;
     build_frags(pk + L::w1f, FT, KSC, [&](int f, int c) { return (f < Hd && c < C) ? bf(a.w_fc1, (long)f * C + c) * bf(a.ln_w, c) : 0.f; });
     build_frags(pk + L::w2f, CT, KSF, [&](int c, int f) { return (f < Hd && c < C) ? bf(a.w_fc2, (long)c * Hd + f) : 0.f; });
     build_frags(pk + L::w2t, FT, KSC, [&](int f, int c) { return (f < Hd && c < C) ? bf(a.w_fc2, (long)c * Hd + f) : 0.f; });
@@ -589,13 +597,22 @@ unsigned bwd_blocks(long rows)
     return (unsigned)(b < 1 ? 1 : b);
 }
 
+template <int KSC, int KSF> hipError_t launch_pack_t(int C, int hidden, const MlpPackJob *jobs, int n, hipStream_t s)
+{
+    if (n < 1 || n > kMaxPackJobs) return hipErrorInvalidValue;
+    MlpPackJobs a{};
+    for (int i = 0; i < n; ++i) a.j[i] = jobs[i];
+    a.C = C; a.Hd = hidden;
+    KernelTimer kt(K_MLP_PACK, s);
+    hipLaunchKernelGGL((astl_mlp_pack_kernel<KSC, KSF>), dim3(32, n), dim3(kMlpThreads), 0, s, a);
+    return hipGetLastError();
+}
+
 template <int KSC, int KSF> hipError_t launch_fwd_t(const MlpArgs &a, bool packed, hipStream_t s)
 {
     if (!packed) {
-        KernelTimer kt(K_MLP_PACK, s);
-        hipLaunchKernelGGL((astl_mlp_pack_kernel<KSC, KSF>), dim3(32), dim3(kMlpThreads), 0, s, a);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
+        const MlpPackJob job = {a.ln_w, a.ln_b, a.w_fc1, a.b_fc1, a.w_fc2, a.b_fc2, a.pack, nullptr};
+        if (hipError_t e = launch_pack_t<KSC, KSF>(a.C, a.Hd, &job, 1, s); e != hipSuccess) return e;
     }
     auto kern = astl_mlp_fwd_kernel<KSC, KSF>;
     const size_t lds = fwd_lds<KSC, KSF>();
@@ -639,6 +656,13 @@ hipError_t launch_astl_mlp_fwd(long rows, int C, int hidden, float eps, const bf
     }
     if (C <= 32) return hidden <= 64 ? launch_fwd_t<1, 2>(m, packed, s) : launch_fwd_t<1, 4>(m, packed, s);
     return hidden <= 64 ? launch_fwd_t<2, 2>(m, packed, s) : launch_fwd_t<2, 4>(m, packed, s);
+}
+
+hipError_t launch_astl_mlp_pack(int C, int hidden, const MlpPackJob *jobs, int n, hipStream_t s)
+{
+    if (!astl_mlp_supported(C, hidden)) return hipErrorInvalidValue;
+    if (C <= 32) return hidden <= 64 ? launch_pack_t<1, 2>(C, hidden, jobs, n, s) : launch_pack_t<1, 4>(C, hidden, jobs, n, s);
+    return hidden <= 64 ? launch_pack_t<2, 2>(C, hidden, jobs, n, s) : launch_pack_t<2, 4>(C, hidden, jobs, n, s);
 }
 
 size_t astl_mlp_pack_bytes() { return align256(PackLayout<2, 4>::bytes); }

@@ -782,11 +782,42 @@ __global__ __launch_bounds__(kWideThreads) void astl_mlp_wide_bwd_kernel(WideMlp
     }
 }
 
+struct WidePackJobs {
+    MlpPackJob j[kMaxPackJobs];
+    const bf16_t *nxt_w, *nxt_b; // (single layers: the LayerNorm that follows)
+    int C, Hd;
+};
+
 template <int KSC, int KSF>
-__global__ __launch_bounds__(256) void astl_mlp_wide_pack_kernel(WideMlpArgs a, int nu, WideMlpBwdArgs b, int nub)
+__global__ __launch_bounds__(256) void astl_mlp_wide_pack_kernel(WidePackJobs jobs, int nu, int nub)
 {
+    const MlpPackJob &job = jobs.j[blockIdx.y];
+    WideMlpArgs a{};
+    a.C = jobs.C; a.Hd = jobs.Hd; a.ln_w = job.ln_w; a.ln_b = job.ln_b; a.w_fc1 = job.w_fc1; a.b_fc1 = job.b_fc1;
+    a.w_fc2 = job.w_fc2; a.b_fc2 = job.b_fc2; a.pack = job.pack; a.nxt_w = jobs.nxt_w; a.nxt_b = jobs.nxt_b;
     wide_fwd_pack_body<KSC, KSF>(a, nu);
-    if (b.pack) wide_bwd_pack_body<KSC, KSF>(b, nub);
+    if (job.bwd_pack) {
+        WideMlpBwdArgs b{};
+        b.C = a.C; b.Hd = a.Hd; b.ln_w = a.ln_w; b.ln_b = a.ln_b; b.w_fc1 = a.w_fc1; b.b_fc1 = a.b_fc1; b.w_fc2 = a.w_fc2;
+        b.pack = job.bwd_pack;
+        wide_bwd_pack_body<KSC, KSF>(b, nub);
+    }
+}
+
+template <int KSC, int KSF>
+hipError_t launch_wide_pack_t(int C, int hidden, const MlpPackJob *jobs, int n, const bf16_t *nxt_w, const bf16_t *nxt_b, hipStream_t s)
+{
+    if (n < 1 || n > kMaxPackJobs) return hipErrorInvalidValue;
+    using L = WideMlp<KSC, KSF>;
+    using LB = WideMlpBwd<KSC, KSF>;
+    const int steps = (hidden + 31) / 32;
+    WidePackJobs a{};
+    for (int i = 0; i < n; ++i) a.j[i] = jobs[i];
+    a.nxt_w = nxt_w; a.nxt_b = nxt_b; a.C = C; a.Hd = hidden;
+    KernelTimer kt(K_MLP_PACK, s);
+    hipLaunchKernelGGL((astl_mlp_wide_pack_kernel<KSC, KSF>), dim3(256, n), dim3(256), 0, s, a, (steps + L::HU - 1) / L::HU,
+                       (steps + LB::HU - 1) / LB::HU);
+    return hipGetLastError();
 }
 
 template <int KSC, int KSF> hipError_t launch_wide_t(const WideMlpArgs &a, bool packed, hipStream_t s)
@@ -794,15 +825,8 @@ template <int KSC, int KSF> hipError_t launch_wide_t(const WideMlpArgs &a, bool 
     using L = WideMlp<KSC, KSF>;
     const int nu = ((a.Hd + 31) / 32 + L::HU - 1) / L::HU; // stream units
     if (!packed) {
-        KernelTimer kt(K_MLP_PACK, s);
-        WideMlpBwdArgs b{};
-        b.C = a.C; b.Hd = a.Hd; b.ln_w = a.ln_w; b.ln_b = a.ln_b; b.w_fc1 = a.w_fc1; b.b_fc1 = a.b_fc1; b.w_fc2 = a.w_fc2;
-        b.pack = a.bwd_pack;
-        using LB = WideMlpBwd<KSC, KSF>;
-        const int nub = ((a.Hd + 31) / 32 + LB::HU - 1) / LB::HU;
-        hipLaunchKernelGGL((astl_mlp_wide_pack_kernel<KSC, KSF>), dim3(256), dim3(256), 0, s, a, nu, b, nub);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
+        const MlpPackJob job = {a.ln_w, a.ln_b, a.w_fc1, a.b_fc1, a.w_fc2, a.b_fc2, a.pack, a.bwd_pack};
+        if (hipError_t e = launch_wide_pack_t<KSC, KSF>(a.C, a.Hd, &job, 1, a.nxt_w, a.nxt_b, s); e != hipSuccess) return e;
     }
     auto kern = astl_mlp_wide_fwd_kernel<KSC, KSF>;
     if (hipError_t ea = allow_dynamic_lds(reinterpret_cast<const void *>(kern), L::LDS_BYTES); ea != hipSuccess) return ea;
@@ -996,6 +1020,13 @@ bool astl_mlp_wide_supported(int C, int hidden)
 }
 
 size_t astl_mlp_wide_pack_bytes() { return (WideMlp<6, 12>::P_BYTES + 255) & ~size_t(255); }
+
+hipError_t launch_astl_mlp_wide_pack(int C, int hidden, const MlpPackJob *jobs, int n, hipStream_t s)
+{
+    if (!astl_mlp_wide_supported(C, hidden)) return hipErrorInvalidValue;
+    return C <= 128 ? launch_wide_pack_t<4, 12>(C, hidden, jobs, n, nullptr, nullptr, s)
+                    : launch_wide_pack_t<6, 12>(C, hidden, jobs, n, nullptr, nullptr, s);
+}
 
 hipError_t launch_astl_mlp_wide_fwd(long rows, int C, int hidden, float eps, const bf16_t *x, const bf16_t *a,
                                     const bf16_t *ln_w, const bf16_t *ln_b, const bf16_t *w_fc1, const bf16_t *b_fc1,

@@ -105,6 +105,20 @@ struct FusedLn {
     float eps = 0.f;
 };
 
+// Parameters of several layers of one shape repacked by one launch.
+struct FusedPackJob {
+    const bf16_t *w_qkv, *b_qkv, *w_proj, *b_proj, *table;
+    uint8_t *pack;
+};
+constexpr int kMaxFusedPackJobs = 16;
+hipError_t launch_fused_pack(const Geom &g, const FusedPackJob *jobs, int n, hipStream_t s);
+
+// Narrow layers (C = 60, 8x8 windows): the whole layer (Eq. 4-5) in one launch, from the repacked parameters of both
+// halves; attn and x1 receive what the backward pass reads (null: inference).  y may be x.
+bool wave_layer_supported(const Geom &g, int hidden);
+hipError_t launch_wave_layer(const Geom &g, const bf16_t *x, const void *pack, const void *mlp_pack, const bf16_t *ln1_w,
+                             const bf16_t *ln1_b, float eps, bf16_t *y, bf16_t *attn, bf16_t *x1, hipStream_t s);
+
 // y = GSWA(x); attn_out receives the concatenated group outputs [T, C] (may be null unless
 // fused_fwd_needs_attn); `pack` receives the packed parameters (fused_pack_bytes, 256-byte aligned), or holds them already (`packed`).
 // `ln`: only where wide_fwd_supported.

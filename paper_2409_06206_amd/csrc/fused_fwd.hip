@@ -3,6 +3,8 @@
 // + window merge + reverse shift, one kernel, one pass over x and y.
 #include "fused.h"
 #include "mfma.h"
+#include "staged_kernels.h"
+#include "astl_mlp.h"
 
 namespace gswa {
 
@@ -13,6 +15,10 @@ constexpr float kLog2e = 1.4426950408889634f;
 // terms of the mask product cancel exactly (-144 / log2(e) = -99.8 in natural units).
 constexpr float kMaskLog2 = -144.0f;
 
+struct FusedPackJobs {
+    FusedPackJob j[kMaxFusedPackJobs];
+};
+
 // ---------------------------------------------------------------------------------------
 // Parameter packing (see FusedCfg): every thread assembles the operand of one (fragment, lane).
 // ---------------------------------------------------------------------------------------
@@ -22,13 +28,12 @@ __device__ __forceinline__ uint32_t bf16_scaled(bf16_t w, float sc)
 }
 
 template <class Cf>
-__global__ __launch_bounds__(256) void pack_params_kernel(const bf16_t *__restrict__ w_qkv,
-                                                          const bf16_t *__restrict__ b_qkv,
-                                                          const bf16_t *__restrict__ w_proj,
-                                                          const bf16_t *__restrict__ b_proj,
-                                                          const bf16_t *__restrict__ table,
-                                                          uint8_t *__restrict__ pack, int wide_first)
+__global__ __launch_bounds__(256) void pack_params_kernel(FusedPackJobs jobs, int wide_first)
 {
+    const FusedPackJob &job = jobs.j[blockIdx.y];
+    const bf16_t *__restrict__ w_qkv = job.w_qkv, *__restrict__ b_qkv = job.b_qkv, *__restrict__ w_proj = job.w_proj,
+                 *__restrict__ b_proj = job.b_proj, *__restrict__ table = job.table;
+    uint8_t *__restrict__ pack = job.pack;
     // blocks from wide_first on (if not negative): the layouts of the wide one-launch kernels, same launch
     if constexpr (Cf::SPLIT) {
         if (wide_first >= 0 && (int)blockIdx.x >= wide_first) {
@@ -213,6 +218,26 @@ template <class Cf> struct WaveFwdCfg {
     static constexpr size_t LDS_BYTES = OFF_COPY + COPY_BYTES;
 };
 
+// Four waves per window, a 16-token tile each, K and V exchanged through LDS; 16 waves, four windows per workgroup.
+// LAYER: the whole layer (LN_1 in front, skip, LN_2, MLP and skip behind; Eq. 4-5).
+template <class Cf, bool LAYER> struct Wave4FwdCfg {
+    static constexpr int NWAVES = 16, NTHREADS = 64 * NWAVES, WPW = 4, WINS = NWAVES / WPW;
+    // heads of a group whose K and V are exchanged together (LDS has no room for all six of one group)
+    static constexpr int HB = Cf::HG == 6 ? 1 : Cf::HG;
+    static constexpr size_t OFF_BIAS = 0;
+    static constexpr size_t OFF_COPY = (size_t)16 * Cf::C;
+    static constexpr size_t OFF_WQH = OFF_COPY + Cf::P_WQH, OFF_WP2 = OFF_COPY + Cf::P_WP2, OFF_BF = OFF_COPY + Cf::P_BF;
+    static constexpr size_t COPY_BYTES = Cf::P_WQ;
+    static constexpr int COPY_IT = (int)((COPY_BYTES / 16 + NTHREADS - 1) / NTHREADS);
+    // whole layer: LN_1's (gamma, beta) in head-padded order [HEADS][16], W1, W2 fragments and the MLP's biases
+    static constexpr size_t OFF_LN = OFF_COPY + COPY_BYTES;
+    static constexpr size_t OFF_MLP = OFF_LN + (LAYER ? (size_t)Cf::HEADS * 16 * 8 : 0);
+    static constexpr size_t OFF_KV = OFF_MLP + (LAYER ? NarrowMlpPack::LDS_BYTES : 0);
+    static constexpr size_t KV_WIN = (size_t)HB * 8 * 512; // K and V tiles of the heads of a batch
+    static constexpr size_t LDS_BYTES = OFF_KV + WINS * KV_WIN;
+    static_assert(OFF_LN % 16 == 0 && LDS_BYTES <= 160 * 1024, "LDS budget");
+};
+
 // the value of row-group Q0 (lanes 16*Q0 .. 16*Q0+15) copied to the lanes of all four groups
 template <int Q0> __device__ __forceinline__ float qgroup_broadcast(float v)
 {
@@ -352,11 +377,6 @@ __global__ __launch_bounds__(512, 1) void wave_fwd_kernel(Geom g, const bf16_t *
                     }
             }
             // ---- Q^T, K^T (rows = head features, then the mask terms) and V (rows = tokens) ----
-            uint4 wqf[3][NSTEP];
-#pragma unroll
-            for (int t3 = 0; t3 < 3; ++t3)
-#pragma unroll
-                for (int st = 0; st < NSTEP; ++st) wqf[t3][st] = wqh[((hd * 3 + t3) * NSTEP + st) * 64 + lane];
             f32x4 bq, bk;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
@@ -367,26 +387,54 @@ __global__ __launch_bounds__(512, 1) void wave_fwd_kernel(Geom g, const bf16_t *
             // column D of V is one: row D of the PV product is the sum of the probabilities
             const float bvs = l16 < D ? bqkv[gi * 3 * CG + 2 * CG + hl * D + l16] : (l16 == D ? 1.f : 0.f);
             uint2 Qb[4], Kb[4], Vb[4];
+            if constexpr (HG == 6) {
+                // (one group: the fragments of q, k and v one after the other; together they do not fit the registers:
+                // seven spilled, a 512x512 map 46.6 us against 45.0)
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                f32x4 qT = bq, kT = bk, vv = f32x4{bvs, bvs, bvs, bvs};
+                for (int t3 = 0; t3 < 3; ++t3) {
+                    uint4 wf[NSTEP];
 #pragma unroll
-                for (int st = 0; st < HG / 2; ++st) {
-                    const uint4 xb = cat(xh[gi * HG + 2 * st][t], xh[gi * HG + 2 * st + 1][t]);
-                    qT = mma32(wqf[0][st], xb, qT);
-                    kT = mma32(wqf[1][st], xb, kT);
-                    vv = mma32(xb, wqf[2][st], vv);
+                    for (int st = 0; st < (t3 < 2 ? NSTEP : HG / 2); ++st) wf[st] = wqh[((hd * 3 + t3) * NSTEP + st) * 64 + lane];
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        f32x4 acc = t3 == 0 ? bq : t3 == 1 ? bk : f32x4{bvs, bvs, bvs, bvs};
+#pragma unroll
+                        for (int st = 0; st < HG / 2; ++st) {
+                            const uint4 xb = cat(xh[2 * st][t], xh[2 * st + 1][t]);
+                            acc = t3 < 2 ? mma32(wf[st], xb, acc) : mma32(xb, wf[st], acc);
+                        }
+                        if (t3 < 2) acc = mma32(wf[NSTEP - 1], cat(make_uint2(0u, 0u), feat[t]), acc);
+                        (t3 == 0 ? Qb : t3 == 1 ? Kb : Vb)[t] = pack_bf16x4(acc);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
                 }
-                {
-                    const uint2 xodd = HG % 2 ? xh[gi * HG + HG - 1][t] : make_uint2(0u, 0u);
-                    const uint4 xb = cat(xodd, feat[t]);
-                    qT = mma32(wqf[0][NSTEP - 1], xb, qT);
-                    kT = mma32(wqf[1][NSTEP - 1], xb, kT);
-                    if (HG % 2) vv = mma32(xb, wqf[2][NSTEP - 1], vv);
+            } else {
+                uint4 wqf[3][NSTEP];
+#pragma unroll
+                for (int t3 = 0; t3 < 3; ++t3)
+#pragma unroll
+                    for (int st = 0; st < NSTEP; ++st) wqf[t3][st] = wqh[((hd * 3 + t3) * NSTEP + st) * 64 + lane];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    f32x4 qT = bq, kT = bk, vv = f32x4{bvs, bvs, bvs, bvs};
+#pragma unroll
+                    for (int st = 0; st < HG / 2; ++st) {
+                        const uint4 xb = cat(xh[gi * HG + 2 * st][t], xh[gi * HG + 2 * st + 1][t]);
+                        qT = mma32(wqf[0][st], xb, qT);
+                        kT = mma32(wqf[1][st], xb, kT);
+                        vv = mma32(xb, wqf[2][st], vv);
+                    }
+                    {
+                        const uint2 xodd = HG % 2 ? xh[gi * HG + HG - 1][t] : make_uint2(0u, 0u);
+                        const uint4 xb = cat(xodd, feat[t]);
+                        qT = mma32(wqf[0][NSTEP - 1], xb, qT);
+                        kT = mma32(wqf[1][NSTEP - 1], xb, kT);
+                        if (HG % 2) vv = mma32(xb, wqf[2][NSTEP - 1], vv);
+                    }
+                    Qb[t] = pack_bf16x4(qT);
+                    Kb[t] = pack_bf16x4(kT);
+                    Vb[t] = pack_bf16x4(vv);
                 }
-                Qb[t] = pack_bf16x4(qT);
-                Kb[t] = pack_bf16x4(kT);
-                Vb[t] = pack_bf16x4(vv);
             }
             uint2 bfh[NDLT];
 #pragma unroll
@@ -462,6 +510,459 @@ __global__ __launch_bounds__(512, 1) void wave_fwd_kernel(Geom g, const bf16_t *
         if (win + W::NWAVES * (int)gridDim.x < g.nW) {
             load_window(win + W::NWAVES * gridDim.x);
             load_group(0);
+        }
+    }
+}
+
+// What the whole layer adds to the attention layer's arguments.
+struct WaveLayerArgs {
+    const bf16_t *ln1_w, *ln1_b;
+    const uint4 *mlp; // weights of the MLP as its pack kernel left them (NarrowMlpPack)
+    bf16_t *x1;       // GSWA(LN_1(x)) + x, kept for the backward pass (null: not kept)
+    float eps;
+};
+
+// LayerNorm of rows of C channels spread over the four lanes that share l16, four channels per piece (NP pieces; a
+// piece's pairs count where `lo`, `hi`): mean first, then the squared distances from it.  Normalised row in `v`.
+template <int NP, int C, class Lo, class Hi>
+__device__ __forceinline__ void normalise_pieces(f32x4 (&v)[NP], float eps, Lo lo, Hi hi)
+{
+    float sum = 0.f;
+#pragma unroll
+    for (int p = 0; p < NP; ++p) sum += (v[p][0] + v[p][1]) + (v[p][2] + v[p][3]);
+    const float mean = qgroup_sum(sum) / (float)C;
+    float dev = 0.f;
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[p][j] = (j < 2 ? lo(p) : hi(p)) ? v[p][j] - mean : 0.f;
+        dev += (v[p][0] * v[p][0] + v[p][1] * v[p][1]) + (v[p][2] * v[p][2] + v[p][3] * v[p][3]);
+    }
+    const float rstd = rsqrtf(qgroup_sum(dev) / (float)C + eps);
+#pragma unroll
+    for (int p = 0; p < NP; ++p) v[p] *= rstd;
+}
+__device__ __forceinline__ f32x4 widen4(uint2 u) { return f32x4{bf16_lo(u.x), bf16_hi(u.x), bf16_lo(u.y), bf16_hi(u.y)}; }
+
+// ---------------------------------------------------------------------------------------
+// The same forward with a window in four waves, and around it, for whole layers, LN_1, the skips, LN_2 and the MLP.
+// A wave keeps its 16 tokens from x to y in registers (119 to 126 of them: four waves per SIMD); K and V of the heads of a
+// group cross the window's waves through LDS as the operands they are read as, two barriers per group.  The projection's
+// result tiles are the rows LN_2 and the MLP take (channels 16 ct + 4q .. of token l16, as in astl_mlp.hip), so the whole
+// second half of the layer needs no exchange.  With few windows the time is this chain of steps; six layers on a 72x88 map
+// (99 windows) went from 172 to 84 us (24 launches of packing, attention layer and MLP half to 8), six on 512x512 from 518
+// to 456 us, where it is bound by vector instructions and by LDS (every fragment serves one tile).
+// ---------------------------------------------------------------------------------------
+template <class Cf, bool LAYER>
+__global__ __launch_bounds__(1024) void wave4_fwd_kernel(Geom g, const bf16_t *__restrict__ x,
+                                                          const uint8_t *__restrict__ pack,
+                                                          bf16_t *__restrict__ y, bf16_t *__restrict__ attn,
+                                                          WaveLayerArgs la)
+{
+    using W = Wave4FwdCfg<Cf, LAYER>;
+    constexpr int C = Cf::C, D = Cf::D, CG = Cf::CG, HG = Cf::HG, HEADS = Cf::HEADS;
+    constexpr int OT = Cf::OT, NSTEP = Cf::NSTEP, NDLT = Cf::NDLT, WPW = W::WPW, HB = W::HB, TW = 1;
+    constexpr int M = 8, NTHREADS = W::NTHREADS;
+    static_assert(Cf::ET == 1 && D + 4 <= 16, "one 16-row tile per head with four spare rows");
+    static_assert(CG % 2 == 0 && D % 2 == 0 && C % 4 == 0 && HEADS % 2 == 0, "dword-granular loads and stores");
+
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+
+    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, q = lane >> 4;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wslot = wv / WPW, t0 = (wv % WPW) * TW; // window of the workgroup, this wave's first tile in it
+    const int s = g.shift;
+    const int cn = l16 & 7, rsub = l16 >> 3;
+    const int per_img = g.nwi * g.nwj;
+    // Global tensors as buffers (see make_buf).  This lane's four channels 4q .. 4q+3 of a 16-wide
+    // head tile are one 8-byte access; the pairs at or beyond D belong to the next head (or lie
+    // past the tensor): they are masked to zero when read and left out when written.
+    const uint32_t tbytes = (uint32_t)g.T * (2u * C);
+    const buf_t xbuf = make_buf(x, tbytes), ybuf = make_buf(y, tbytes), abuf = make_buf(attn, attn ? tbytes : 0u);
+    const bool lo_ok = 4 * q < D, hi_ok = 4 * q + 2 < D;
+    const uint32_t m_lo = lo_ok ? 0xffffffffu : 0u, m_hi = hi_ok ? 0xffffffffu : 0u;
+    const uint32_t c8 = 8u * q;
+
+    // x of a window in head-padded operand order: tile t, head hd: channels hd*D + 4q .. 4q+3 of
+    // token 16 (t0 + t) + l16; and the mask inputs (1, r, c, r*c) of the tokens, r / c = "past the wrap in
+    // the last window row / column"
+    uint32_t tok[TW]; // byte offset of the token's row (2*T*C fits 32 bits, checked on the host)
+    uint2 xh[HEADS][TW], feat[TW];
+    auto load_window = [&](int win) {
+        const int b = win / per_img;
+        const int wr = win - b * per_img;
+        const int wi = wr / g.nwj, wj = wr - wi * g.nwj;
+        const bool lastrow = s > 0 && wi == g.nwi - 1, lastcol = s > 0 && wj == g.nwj - 1;
+        int sj = wj * M + cn + s;
+        if (sj >= g.W) sj -= g.W;
+        const float c = (lastcol && cn >= M - s) ? 1.f : 0.f;
+#pragma unroll
+        for (int t = 0; t < TW; ++t) {
+            const int rn = 2 * (t0 + t) + rsub;
+            int si = wi * M + rn + s;
+            if (si >= g.H) si -= g.H;
+            tok[t] = (uint32_t)((((b * g.H + si) * g.W) + sj) * C) * 2u;
+            const float r = (lastrow && rn >= M - s) ? 1.f : 0.f;
+            feat[t] = make_uint2(pack_bf16x2(1.f, r), pack_bf16x2(c, r * c));
+        }
+    };
+    // the x slice of one group: a group is fetched while the previous one is being computed (whole layers: all
+    // groups at once, LN_1 needs whole rows)
+    auto load_group = [&, xbuf](int gi) {
+#pragma unroll
+        for (int t = 0; t < TW; ++t)
+#pragma unroll
+            for (int hl = 0; hl < HG; ++hl) {
+                const int hd = gi * HG + hl;
+                xh[hd][t] = bload64(xbuf, tok[t] + c8 + 2u * (hd * D), 0u);
+                xh[hd][t].x &= m_lo;
+                xh[hd][t].y &= m_hi;
+            }
+    };
+    auto load_first = [&]() {
+#pragma unroll
+        for (int gi = 0; gi < (LAYER ? Cf::G : 1); ++gi) load_group(gi);
+    };
+
+    const int stride = W::WINS * (int)gridDim.x;
+    const int rounds = (g.nW + stride - 1) / stride;
+    int win = wslot * (int)gridDim.x + (int)blockIdx.x;
+    if (win < g.nW) { // in flight during the set-up
+        load_window(win);
+        load_first();
+    }
+
+    // ---- set-up: packed weights, bias operands and linear biases into LDS (unrolled, so that the
+    // loads of a thread are all in flight together); the workgroups start at different offsets
+    // so that they do not all ask for the same cache lines at once ----
+    {
+        constexpr int N16 = (int)(W::COPY_BYTES / 16);
+        const int rot = (int)((blockIdx.x * 5u) % (unsigned)W::COPY_IT);
+#pragma unroll
+        for (int k = 0; k < W::COPY_IT; ++k) {
+            int kk = k + rot;
+            if (kk >= W::COPY_IT) kk -= W::COPY_IT;
+            const int i = kk * NTHREADS + tid;
+            if (i < N16) reinterpret_cast<uint4 *>(lds + W::OFF_COPY)[i] = reinterpret_cast<const uint4 *>(pack)[i];
+        }
+        if (tid < C)
+            reinterpret_cast<uint4 *>(lds + W::OFF_BIAS)[tid] = reinterpret_cast<const uint4 *>(pack + Cf::P_BIAS)[tid];
+        if constexpr (LAYER) {
+            NarrowMlpPack::stage(reinterpret_cast<uint4 *>(lds + W::OFF_MLP), la.mlp, tid, NTHREADS);
+            if (tid < HEADS * 16) {
+                const int e = tid & 15, c = (tid >> 4) * D + e;
+                reinterpret_cast<float2 *>(lds + W::OFF_LN)[tid] =
+                    e < D ? make_float2(to_f32(la.ln1_w[c]), to_f32(la.ln1_b[c])) : make_float2(0.f, 0.f);
+            }
+        }
+    }
+    __syncthreads();
+
+    // constant operands: identity rows (upper half of the score MFMA's A operand) and the column of
+    // ones that spreads -max over a score tile
+    const uint2 ident = make_uint2((4 * q == l16 ? 0x3F80u : 0u) | (4 * q + 1 == l16 ? 0x3F800000u : 0u),
+                                   (4 * q + 2 == l16 ? 0x3F80u : 0u) | (4 * q + 3 == l16 ? 0x3F800000u : 0u));
+    const uint2 ones0 = make_uint2(q == 0 ? 0x3F80u : 0u, 0u);
+    const f32x4 zero4 = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    for (int round = 0; round < rounds; ++round, win += stride) {
+        const bool active = win < g.nW; // (the same for all waves of a window)
+        // The LDS contents do not change from window to window, but their reads must stay inside
+        // this loop (hoisted out, the weights of all heads would sit in registers): the offset of
+        // LDS is made opaque once per window.
+        uint32_t lds0 = 0;
+        asm volatile("" : "+v"(lds0));
+        const uint4 *wqh = reinterpret_cast<const uint4 *>(lds + lds0 + W::OFF_WQH);
+        const uint4 *wp2 = reinterpret_cast<const uint4 *>(lds + lds0 + W::OFF_WP2);
+        const uint2 *bfr = reinterpret_cast<const uint2 *>(lds + lds0 + W::OFF_BF);
+        const float *bqkv = reinterpret_cast<const float *>(lds + lds0 + W::OFF_BIAS);
+        const float *bproj = bqkv + 3 * C;
+        uint2 *kv = reinterpret_cast<uint2 *>(lds + lds0 + W::OFF_KV + (size_t)wslot * W::KV_WIN);
+        if constexpr (LAYER) {
+            if (active) { // LN_1, rounded to bf16 as between two launches
+                const float4 *gb = reinterpret_cast<const float4 *>(lds + lds0 + W::OFF_LN) + 2 * q;
+#pragma unroll
+                for (int t = 0; t < TW; ++t) {
+                    f32x4 v[HEADS];
+#pragma unroll
+                    for (int hd = 0; hd < HEADS; ++hd) v[hd] = widen4(xh[hd][t]);
+                    normalise_pieces<HEADS, C>(v, la.eps, [&](int) { return lo_ok; }, [&](int) { return hi_ok; });
+#pragma unroll
+                    for (int hd = 0; hd < HEADS; ++hd) {
+                        const float4 g0 = gb[hd * 8], g1 = gb[hd * 8 + 1];
+                        xh[hd][t] = make_uint2(pack_bf16x2(v[hd][0] * g0.x + g0.y, v[hd][1] * g0.z + g0.w),
+                                               pack_bf16x2(v[hd][2] * g1.x + g1.y, v[hd][3] * g1.z + g1.w));
+                    }
+                }
+            }
+        }
+        uint2 Ob[HEADS][TW];
+        auto heads_from = [&](auto h0_) {
+            const int h0 = h0_, gi = h0 / HG;
+            uint2 Qb[HB][TW];
+            if (h0 % HG == 0 && gi > 0 && g.cascade && active) { // Eq. 8: the previous group's output joins this group's input
+#pragma unroll
+                for (int hlp = 0; hlp < HG; ++hlp)
+#pragma unroll
+                    for (int t = 0; t < TW; ++t) {
+                        const uint2 prev = Ob[(gi > 0 ? gi - 1 : 0) * HG + hlp][t];
+                        uint2 &xv = xh[gi * HG + hlp][t];
+                        xv.x = add_bf16x2(xv.x, prev.x);
+                        xv.y = add_bf16x2(xv.y, prev.y);
+                    }
+            }
+            if (active) {
+#pragma unroll
+                for (int i = 0; i < HB; ++i) {
+                    const int hd = h0 + i, hl = hd % HG;
+                    // ---- Q^T, K^T (rows = head features, then the mask terms) and V (rows = tokens) ----
+                    f32x4 bq, bk;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const int e = 4 * q + j;
+                        bq[j] = e < D ? bqkv[gi * 3 * CG + hl * D + e] * kLog2e : 0.f;
+                        bk[j] = e < D ? bqkv[gi * 3 * CG + CG + hl * D + e] : 0.f;
+                    }
+                    // column D of V is one: row D of the PV product is the sum of the probabilities
+                    const float bvs = l16 < D ? bqkv[gi * 3 * CG + 2 * CG + hl * D + l16] : (l16 == D ? 1.f : 0.f);
+                    uint2 Kb[TW], Vb[TW];
+                    if constexpr (HG == 6) {
+                        // (one group: the fragments of q, k and v one after the other, together they do not fit the registers)
+                        f32x4 acc[3][TW];
+#pragma unroll
+                        for (int t = 0; t < TW; ++t) {
+                            acc[0][t] = bq;
+                            acc[1][t] = bk;
+                            acc[2][t] = f32x4{bvs, bvs, bvs, bvs};
+                        }
+#pragma unroll
+                        for (int t3 = 0; t3 < 3; ++t3) {
+                            uint4 wqf[NSTEP];
+#pragma unroll
+                            for (int st = 0; st < (t3 < 2 ? NSTEP : HG / 2); ++st) wqf[st] = wqh[((hd * 3 + t3) * NSTEP + st) * 64 + lane];
+#pragma unroll
+                            for (int t = 0; t < TW; ++t) {
+#pragma unroll
+                                for (int st = 0; st < HG / 2; ++st) {
+                                    const uint4 xb = cat(xh[2 * st][t], xh[2 * st + 1][t]);
+                                    acc[t3][t] = t3 < 2 ? mma32(wqf[st], xb, acc[t3][t]) : mma32(xb, wqf[st], acc[t3][t]);
+                                }
+                                if (t3 < 2) acc[t3][t] = mma32(wqf[NSTEP - 1], cat(make_uint2(0u, 0u), feat[t]), acc[t3][t]);
+                            }
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+#pragma unroll
+                        for (int t = 0; t < TW; ++t) {
+                            Qb[i][t] = pack_bf16x4(acc[0][t]);
+                            Kb[t] = pack_bf16x4(acc[1][t]);
+                            Vb[t] = pack_bf16x4(acc[2][t]);
+                        }
+                    } else {
+                        uint4 wqf[3][NSTEP];
+#pragma unroll
+                        for (int t3 = 0; t3 < 3; ++t3)
+#pragma unroll
+                            for (int st = 0; st < NSTEP; ++st) wqf[t3][st] = wqh[((hd * 3 + t3) * NSTEP + st) * 64 + lane];
+#pragma unroll
+                        for (int t = 0; t < TW; ++t) {
+                            f32x4 qT = bq, kT = bk, vv = f32x4{bvs, bvs, bvs, bvs};
+#pragma unroll
+                            for (int st = 0; st < HG / 2; ++st) {
+                                const uint4 xb = cat(xh[gi * HG + 2 * st][t], xh[gi * HG + 2 * st + 1][t]);
+                                qT = mma32(wqf[0][st], xb, qT);
+                                kT = mma32(wqf[1][st], xb, kT);
+                                vv = mma32(xb, wqf[2][st], vv);
+                            }
+                            {
+                                const uint2 xodd = HG % 2 ? xh[gi * HG + HG - 1][t] : make_uint2(0u, 0u);
+                                const uint4 xb = cat(xodd, feat[t]);
+                                qT = mma32(wqf[0][NSTEP - 1], xb, qT);
+                                kT = mma32(wqf[1][NSTEP - 1], xb, kT);
+                                if (HG % 2) vv = mma32(xb, wqf[2][NSTEP - 1], vv);
+                            }
+                            Qb[i][t] = pack_bf16x4(qT);
+                            Kb[t] = pack_bf16x4(kT);
+                            Vb[t] = pack_bf16x4(vv);
+                        }
+                    }
+#pragma unroll
+                    for (int t = 0; t < TW; ++t) {
+                        kv[(i * 8 + t0 + t) * 64 + lane] = Kb[t];
+                        kv[(i * 8 + 4 + t0 + t) * 64 + lane] = Vb[t];
+                    }
+                }
+            }
+            __syncthreads();
+            if (active) {
+#pragma unroll
+                for (int i = 0; i < HB; ++i) {
+                    const int hd = h0 + i, hl = hd % HG;
+                    uint2 K4[4], V4[4]; // of all tiles of the window
+#pragma unroll
+                    for (int kt = 0; kt < 4; ++kt) {
+                        K4[kt] = kv[(i * 8 + kt) * 64 + lane];
+                        V4[kt] = kv[(i * 8 + 4 + kt) * 64 + lane];
+                    }
+                    uint2 bfh[TW + 3]; // bias operands of this wave's query tiles: key/query tile offsets t0 - 3 ..
+#pragma unroll
+                    for (int dlt = 0; dlt < TW + 3; ++dlt) bfh[dlt] = bfr[(hd * NDLT + t0 + dlt) * 64 + lane];
+                    if (!LAYER && hl == HG - 1 && gi + 1 < Cf::G) load_group(gi + 1); // this group's x is consumed
+
+#pragma unroll
+                    for (int nt = 0; nt < TW; ++nt) {
+                        // S^T tiles (base-2 units): rows = keys 16kt+4q+j, column = query 16(t0+nt)+l16
+                        f32x4 st[4];
+#pragma unroll
+                        for (int kt = 0; kt < 4; ++kt) st[kt] = mma16(ident, bfh[nt - kt + 3], zero4);
+#pragma unroll
+                        for (int kt = 0; kt < 4; ++kt) st[kt] = mma16(K4[kt], Qb[i][nt], st[kt]);
+                        float mx = fmaxf(fmaxf(st[0][0], st[0][1]), fmaxf(st[0][2], st[0][3]));
+#pragma unroll
+                        for (int kt = 1; kt < 4; ++kt)
+#pragma unroll
+                            for (int j = 0; j < 4; j += 2) mx = fmaxf(fmaxf(mx, st[kt][j]), st[kt][j + 1]);
+                        mx = qgroup_max(mx);
+                        const uint2 negmx = make_uint2(q == 0 ? pack_bf16x2(-mx, 0.f) : 0u, 0u);
+                        uint2 Pb[4];
+#pragma unroll
+                        for (int kt = 0; kt < 4; ++kt) {
+                            st[kt] = mma16(ones0, negmx, st[kt]); // every row of the tile: - max (to bf16)
+#pragma unroll
+                            for (int j = 0; j < 4; ++j) st[kt][j] = __builtin_amdgcn_exp2f(st[kt][j]);
+                            Pb[kt] = pack_bf16x4(st[kt]);
+                        }
+                        // O^T = V^T P^T: rows = head features (row D = sum of the probabilities)
+                        f32x4 oT = mma32(cat(V4[0], V4[1]), cat(Pb[0], Pb[1]), zero4);
+                        oT = mma32(cat(V4[2], V4[3]), cat(Pb[2], Pb[3]), oT);
+                        oT *= __builtin_amdgcn_rcpf(qgroup_broadcast<D / 4>(oT[D % 4]));
+                        Ob[hd][nt] = pack_bf16x4(oT);
+                    }
+                    if (attn && hl == HG - 1) { // the group's output, kept for the backward: its heads together,
+                                                // so that the pieces of a row reach memory as whole cache lines
+                        if (hi_ok) {
+#pragma unroll
+                            for (int nt = 0; nt < TW; ++nt)
+#pragma unroll
+                                for (int h2 = gi * HG; h2 <= hd; ++h2) bstore64(abuf, tok[nt] + c8 + 2u * (h2 * D), 0u, Ob[h2][nt]);
+                        } else if (lo_ok) {
+#pragma unroll
+                            for (int nt = 0; nt < TW; ++nt)
+#pragma unroll
+                                for (int h2 = gi * HG; h2 <= hd; ++h2) bstore32(abuf, tok[nt] + c8 + 2u * (h2 * D), 0u, Ob[h2][nt].x);
+                        }
+                    }
+                }
+            }
+            if (h0 + HB < HEADS) __syncthreads(); // (K and V are read before the next heads' are written)
+        };
+        // (one group: as constants; left to the loop's unrolling some of the registers end up in memory)
+        if constexpr (HG == 6) {
+            static_for<HEADS / HB>([&](auto b_) { heads_from(std::integral_constant<int, decltype(b_)::value * HB>{}); });
+        } else {
+#pragma unroll
+            for (int h0 = 0; h0 < HEADS; h0 += HB) heads_from(h0);
+        }
+
+        if (active) {
+            // x again, channels 16 ot + 4q .. + 3 of the lane's tokens (the skip of Eq. 4), on its way under the projection
+            [[maybe_unused]] uint2 xs[LAYER ? OT : 1][TW];
+            [[maybe_unused]] uint2 x1[LAYER ? OT : 1][TW]; // the layer's rows between its halves, as stored
+            if constexpr (LAYER) {
+#pragma unroll
+                for (int ot = 0; ot < OT; ++ot)
+#pragma unroll
+                    for (int t = 0; t < TW; ++t) xs[ot][t] = bload64(xbuf, tok[t] + c8 + 32u * ot, 0u);
+            }
+            // ---- Y^T = Wproj A^T + b: rows = output channels, column = token ----
+#pragma unroll
+            for (int ot = 0; ot < OT; ++ot) {
+                uint4 wpf[HEADS / 2];
+#pragma unroll
+                for (int pr = 0; pr < HEADS / 2; ++pr) wpf[pr] = wp2[(ot * (HEADS / 2) + pr) * 64 + lane];
+                f32x4 bp;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int o = 16 * ot + 4 * q + j;
+                    bp[j] = o < C ? bproj[o] : 0.f;
+                }
+                const int o0 = 16 * ot + 4 * q;
+#pragma unroll
+                for (int t = 0; t < TW; ++t) {
+                    f32x4 acc = bp;
+#pragma unroll
+                    for (int pr = 0; pr < HEADS / 2; ++pr) acc = mma32(wpf[pr], cat(Ob[2 * pr][t], Ob[2 * pr + 1][t]), acc);
+                    const uint2 a = pack_bf16x4(acc);
+                    if constexpr (LAYER) {
+                        // (both rounded where a launch of its own would store them)
+                        x1[ot][t] = make_uint2(o0 < C ? add_bf16x2(xs[ot][t].x, a.x) : 0u, o0 < C ? add_bf16x2(xs[ot][t].y, a.y) : 0u);
+                    } else if (o0 < C) {
+                        bstore64(ybuf, tok[t] + c8 + 32u * ot, 0u, a);
+                    }
+                }
+            }
+            if constexpr (LAYER) {
+                using P = NarrowMlpPack;
+                const uint4 *w1 = reinterpret_cast<const uint4 *>(lds + lds0 + W::OFF_MLP), *w2 = w1 + P::W2;
+                const float *b1s = reinterpret_cast<const float *>(w1 + P::FLOATS), *b2s = b1s + P::FT * 16;
+                if (la.x1) {
+                    const buf_t x1buf = make_buf(la.x1, tbytes);
+#pragma unroll
+                    for (int ot = 0; ot < OT; ++ot)
+#pragma unroll
+                        for (int t = 0; t < TW; ++t)
+                            if (16 * ot + 4 * q < C) bstore64(x1buf, tok[t] + c8 + 32u * ot, 0u, x1[ot][t]);
+                }
+                // ---- LN_2 (gamma and beta are folded into the first map), the MLP, the skip of Eq. 5 ----
+                {
+                    uint4 bx[2][TW];
+#pragma unroll
+                    for (int t = 0; t < TW; ++t) {
+                        f32x4 v[OT];
+#pragma unroll
+                        for (int ot = 0; ot < OT; ++ot) v[ot] = widen4(x1[ot][t]);
+                        auto in = [&](int ot) { return 16 * ot + 4 * q < C; };
+                        normalise_pieces<OT, C>(v, la.eps, in, in);
+#pragma unroll
+                        for (int s2 = 0; s2 < 2; ++s2) bx[s2][t] = cat(pack_bf16x4(v[2 * s2]), pack_bf16x4(v[2 * s2 + 1]));
+                    }
+                    uint2 hp[P::FT][TW];
+#pragma unroll
+                    for (int ft = 0; ft < P::FT; ++ft) {
+                        const uint4 f0 = w1[(ft * 2 + 0) * 64 + lane], f1 = w1[(ft * 2 + 1) * 64 + lane];
+                        const f32x4 b1 = *reinterpret_cast<const f32x4 *>(b1s + 16 * ft + 4 * q);
+#pragma unroll
+                        for (int t = 0; t < TW; ++t) {
+                            f32x4 acc = mma32(f1, bx[1][t], mma32(f0, bx[0][t], zero4)) + b1;
+#pragma unroll
+                            for (int j = 0; j < 4; ++j) {
+                                float Phi, phi;
+                                gauss(acc[j], Phi, phi);
+                                acc[j] *= Phi;
+                            }
+                            hp[ft][t] = pack_bf16x4(acc);
+                        }
+                    }
+#pragma unroll
+                    for (int ot = 0; ot < OT; ++ot) {
+                        uint4 wf[P::KSF];
+#pragma unroll
+                        for (int k = 0; k < P::KSF; ++k) wf[k] = w2[(ot * P::KSF + k) * 64 + lane];
+                        const f32x4 b2 = *reinterpret_cast<const f32x4 *>(b2s + 16 * ot + 4 * q);
+#pragma unroll
+                        for (int t = 0; t < TW; ++t) {
+                            f32x4 acc = zero4;
+#pragma unroll
+                            for (int k = 0; k < P::KSF; ++k) acc = mma32(wf[k], cat(hp[2 * k][t], hp[2 * k + 1][t]), acc);
+                            acc += b2 + widen4(x1[ot][t]);
+                            if (16 * ot + 4 * q < C) bstore64(ybuf, tok[t] + c8 + 32u * ot, 0u, pack_bf16x4(acc));
+                        }
+                    }
+                }
+            }
+        }
+        if (win + stride < g.nW) {
+            load_window(win + stride);
+            load_first();
         }
     }
 }
@@ -745,23 +1246,37 @@ hipError_t launch_attn_chunks(const Geom &g, const bf16_t *x, const uint8_t *pac
     return hipSuccess;
 }
 
+template <class Cf> hipError_t run_pack(const Geom &g, const FusedPackJob *jobs, int n, hipStream_t s)
+{
+    constexpr int entries =
+        (Cf::N_WQH + Cf::N_WP2 + Cf::N_BF + Cf::N_WQ + Cf::N_WPT + Cf::N_WQT + Cf::N_WPK) * 64 + 4 * Cf::C;
+    constexpr int wide_entries = (Cf::N_WQW + Cf::N_WPW + Cf::N_WQX + Cf::N_WQN) * 64 + Cf::HEADS * Cf::TBW_PITCH;
+    const int blocks = (entries + 255) / 256;
+    const bool wide = Cf::SPLIT && wide_fwd_supported(g);
+    if (n < 1 || n > kMaxFusedPackJobs) return hipErrorInvalidValue;
+    FusedPackJobs a{};
+    for (int i = 0; i < n; ++i) a.j[i] = jobs[i];
+    KernelTimer kt(K_PACK_FWD, s);
+    hipLaunchKernelGGL(pack_params_kernel<Cf>, dim3(blocks + (wide ? (wide_entries + 255) / 256 : 0), n), dim3(256), 0, s, a,
+                       wide ? blocks : -1);
+    return hipGetLastError();
+}
+
+template <class Cf, bool LAYER>
+hipError_t launch_wave(const Geom &g, const bf16_t *x, const uint8_t *pack, bf16_t *y, bf16_t *attn, const WaveLayerArgs &la,
+                       hipStream_t s);
+
 template <class Cf>
 hipError_t run_fwd(const Geom &g, const bf16_t *x, const bf16_t *w_qkv, const bf16_t *b_qkv,
                    const bf16_t *w_proj, const bf16_t *b_proj, const bf16_t *table, bf16_t *y,
                    bf16_t *attn, void *ws, int training, bool packed, const FusedLn &ln, hipStream_t s)
 {
     uint8_t *pack = static_cast<uint8_t *>(ws);
+    hipError_t e = hipSuccess;
     if (!packed) {
-        constexpr int entries =
-            (Cf::N_WQH + Cf::N_WP2 + Cf::N_BF + Cf::N_WQ + Cf::N_WPT + Cf::N_WQT + Cf::N_WPK) * 64 + 4 * Cf::C;
-        constexpr int wide_entries = (Cf::N_WQW + Cf::N_WPW + Cf::N_WQX + Cf::N_WQN) * 64 + Cf::HEADS * Cf::TBW_PITCH;
-        const int blocks = (entries + 255) / 256;
-        const bool wide = Cf::SPLIT && wide_fwd_supported(g);
-        KernelTimer kt(K_PACK_FWD, s);
-        hipLaunchKernelGGL(pack_params_kernel<Cf>, dim3(blocks + (wide ? (wide_entries + 255) / 256 : 0)), dim3(256), 0, s,
-                           w_qkv, b_qkv, w_proj, b_proj, table, pack, wide ? blocks : -1);
+        const FusedPackJob job = {w_qkv, b_qkv, w_proj, b_proj, table, pack};
+        e = run_pack<Cf>(g, &job, 1, s);
     }
-    hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if constexpr (Cf::SPLIT) {
         if (wide_fwd_supported(g)) { // the whole layer in one launch (its byte offsets are 32 bits wide: larger maps go on below)
@@ -781,17 +1296,35 @@ hipError_t run_fwd(const Geom &g, const bf16_t *x, const bf16_t *w_qkv, const bf
         hipLaunchKernelGGL(kern, dim3(grid), dim3(256), lds, s, g.T, attn, pack, y);
         return hipGetLastError();
     } else {
+        return launch_wave<Cf, false>(g, x, pack, y, attn, WaveLayerArgs{}, s);
+    }
+}
+
+template <class Cf, bool LAYER>
+hipError_t launch_wave(const Geom &g, const bf16_t *x, const uint8_t *pack, bf16_t *y, bf16_t *attn, const WaveLayerArgs &la,
+                       hipStream_t s)
+{
+    // spread the windows over the compute units before filling a workgroup
+    int grid = device_cu_count();
+    if (grid > g.nW) grid = g.nW;
+    KernelTimer kt(LAYER ? K_LAYER_FWD : K_FUSED_FWD, s);
+    // A window in four waves is the shorter chain (one window 17.0 -> 11.7 us, 512 windows 16.6 -> 14.0, 1024 18.7 ->
+    // 18.3); with more windows than fit the chip at once (four a compute unit) a window in one wave reads the weights from
+    // LDS a fourth as often: 1600 windows 25.6 / 23.9 us, 4096 windows 47.5 / 40.8.  The same bits either way.  Whole
+    // layers do not fit one wave's registers (12 to 19 spilled) and gain from four at every size.
+    if (LAYER || g.nW <= 4 * device_cu_count()) {
+        using W = Wave4FwdCfg<Cf, LAYER>;
+        auto kern = wave4_fwd_kernel<Cf, LAYER>;
+        if (hipError_t ea = allow_dynamic_lds(reinterpret_cast<const void *>(kern), W::LDS_BYTES); ea != hipSuccess) return ea;
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(W::NTHREADS), W::LDS_BYTES, s, g, x, pack, y, attn, la);
+    } else {
         using W = WaveFwdCfg<Cf>;
         static_assert(W::LDS_BYTES <= 160 * 1024, "LDS budget");
         auto kern = wave_fwd_kernel<Cf>;
         if (hipError_t ea = allow_dynamic_lds(reinterpret_cast<const void *>(kern), W::LDS_BYTES); ea != hipSuccess) return ea;
-        // one window per wave: spread the windows over the compute units before filling a workgroup
-        int grid = device_cu_count();
-        if (grid > g.nW) grid = g.nW;
-        KernelTimer kt(K_FUSED_FWD, s);
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * W::NWAVES), W::LDS_BYTES, s, g, x, pack, y, attn);
-        return hipGetLastError();
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(W::NTHREADS), W::LDS_BYTES, s, g, x, pack, y, attn);
     }
+    return hipGetLastError();
 }
 
 // instantiation table
@@ -826,6 +1359,34 @@ size_t fused_pack_bytes(const Geom &g)
     GSWA_FUSED_SHAPES(X)
 #undef X
     return 0;
+}
+
+hipError_t launch_fused_pack(const Geom &g, const FusedPackJob *jobs, int n, hipStream_t s)
+{
+#define X(C_, H_, G_) \
+    if (g.C == C_ && g.heads == H_ && g.groups == G_) return run_pack<FusedCfg<C_, H_, G_>>(g, jobs, n, s);
+    GSWA_FUSED_SHAPES(X)
+#undef X
+    return hipErrorInvalidValue;
+}
+
+#define GSWA_WAVE_SHAPES(X) X(60, 6, 1) X(60, 6, 2) X(60, 6, 3) X(60, 6, 6)
+
+bool wave_layer_supported(const Geom &g, int hidden)
+{
+    return g.C == 60 && g.dq == g.d && fused_fwd_supported(g) && astl_mlp_supported(g.C, hidden) && hidden > 64;
+}
+
+hipError_t launch_wave_layer(const Geom &g, const bf16_t *x, const void *pack, const void *mlp_pack, const bf16_t *ln1_w,
+                             const bf16_t *ln1_b, float eps, bf16_t *y, bf16_t *attn, bf16_t *x1, hipStream_t s)
+{
+    const WaveLayerArgs la = {ln1_w, ln1_b, static_cast<const uint4 *>(mlp_pack), x1, eps};
+#define X(C_, H_, G_)                                 \
+    if (g.C == C_ && g.heads == H_ && g.groups == G_) \
+        return launch_wave<FusedCfg<C_, H_, G_>, true>(g, x, static_cast<const uint8_t *>(pack), y, attn, la, s);
+    GSWA_WAVE_SHAPES(X)
+#undef X
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_fused_fwd(const Geom &g, const bf16_t *x, const bf16_t *w_qkv, const bf16_t *b_qkv,

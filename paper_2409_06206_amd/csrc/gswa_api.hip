@@ -445,10 +445,18 @@ bool gswa::attn_forward_takes_ln(const gswa_desc *desc)
     return make_geom(desc, &g) == GSWA_OK && use_fused_fwd(desc, g) && wide_fwd_supported(g);
 }
 
+size_t gswa::attn_pack_bytes(const gswa_desc *desc, size_t *saved_offset)
+{
+    Geom g;
+    if (make_geom(desc, &g) != GSWA_OK) return 0;
+    const Sizes s = make_sizes(desc, g);
+    *saved_offset = s.act;
+    return s.window ? 0 : s.pack;
+}
+
 int gswa::attn_forward(const gswa_desc *desc, const void *x, const void *w_qkv, const void *b_qkv,
                  const void *w_proj, const void *b_proj, const void *bias_table, void *y,
-                 void *saved, void *ws, bool packed, const AttnLn *ln, int windows,
-                 void *hip_stream)
+                 void *saved, void *ws, const AttnOpts &o, void *hip_stream)
 {
     Geom g;
     Sizes s;
@@ -468,16 +476,17 @@ int gswa::attn_forward(const gswa_desc *desc, const void *x, const void *w_qkv, 
                                      (const float *)w_proj, (const float *)b_proj,
                                      (const float *)bias_table, (float *)y, (float *)saved, (char *)ws, st);
     if (s.fused_fwd) {
-        void *pack = saved ? static_cast<void *>(static_cast<char *>(saved) + s.act) : ws;
+        void *pack = o.pack ? o.pack : saved ? static_cast<void *>(static_cast<char *>(saved) + s.act) : ws;
         void *attn = saved;
         if (!saved && fused_fwd_needs_attn(g)) attn = static_cast<char *>(ws) + s.pack;
         // (only the one-launch kernels go by windows)
-        if (windows > 0 && windows < g.nW && (wide_fwd_supported(g) || !fused_fwd_needs_attn(g))) g.nW = windows;
+        if (o.windows > 0 && o.windows < g.nW && (wide_fwd_supported(g) || !fused_fwd_needs_attn(g))) g.nW = o.windows;
         FusedLn fl{};
+        const AttnLn *ln = o.ln;
         if (ln) { fl.w = (const bf16_t *)ln->w; fl.b = (const bf16_t *)ln->b; fl.eps = ln->eps; }
         hipError_t e = launch_fused_fwd(g, (const bf16_t *)(ln ? ln->x : x), (const bf16_t *)w_qkv, (const bf16_t *)b_qkv,
                                         (const bf16_t *)w_proj, (const bf16_t *)b_proj,
-                                        (const bf16_t *)bias_table, (bf16_t *)y, (bf16_t *)attn, pack, saved ? 1 : 0, packed, fl, st);
+                                        (const bf16_t *)bias_table, (bf16_t *)y, (bf16_t *)attn, pack, saved ? 1 : 0, o.packed, fl, st);
         return e == hipSuccess ? GSWA_OK : hip_fail(e);
     }
     if (!(desc->flags & GSWA_FORCE_STAGED) && window_fwd_supported(g)) {
@@ -525,7 +534,7 @@ int gswa_forward(const gswa_desc *desc, const void *x, const void *w_qkv, const 
                  const void *w_proj, const void *b_proj, const void *bias_table, void *y,
                  void *saved, void *ws, void *hip_stream)
 {
-    return attn_forward(desc, x, w_qkv, b_qkv, w_proj, b_proj, bias_table, y, saved, ws, false, nullptr, 0, hip_stream);
+    return attn_forward(desc, x, w_qkv, b_qkv, w_proj, b_proj, bias_table, y, saved, ws, AttnOpts{}, hip_stream);
 }
 
 int gswa_backward(const gswa_desc *desc, const void *x, const void *dy, const void *w_qkv,

@@ -29,18 +29,23 @@ struct WindowLayerGrads {
 // Checks a descriptor and derives its geometry (GSWA_OK or an error code).
 int make_geom(const gswa_desc *d, Geom *g);
 
-// gswa_forward; `packed`: ws holds this layer's repacked parameters from an earlier inference call of the same descriptor
-// (layers of the kernels that read them repacked; the others take no notice).  `ln` (only where attn_forward_takes_ln):
-// the layer is applied to LayerNorm(ln->x); `x` then only names the memory that LayerNorm would have been written to.
-struct AttnLn {
+// gswa_forward with what a whole layer or a sequence of layers knows besides.
+struct AttnLn { // LayerNorm in front of the layer
     const void *x, *w, *b;
     float eps;
 };
+struct AttnOpts {
+    bool packed = false; // the repacked parameters are where this call would put them (kernels that read none take no notice)
+    void *pack = nullptr; // (with `packed`) they are here instead
+    const AttnLn *ln = nullptr; // only where attn_forward_takes_ln: the layer is applied to LayerNorm(ln->x); `x` then only
+                                // names the memory that LayerNorm would have been written to
+    int windows = 0;            // > 0: only the first so many windows are wanted, the other tokens of y may hold anything
+};
 bool attn_forward_takes_ln(const gswa_desc *d);
-// `windows` (> 0): only the first so many windows of the batch are wanted; the other tokens of y hold anything afterwards.
+// Bytes of the repacked parameters of kernels that read them repacked, and where they lie in `saved`; 0: there are none.
+size_t attn_pack_bytes(const gswa_desc *d, size_t *saved_offset);
 int attn_forward(const gswa_desc *d, const void *x, const void *w_qkv, const void *b_qkv, const void *w_proj, const void *b_proj,
-                 const void *bias_table, void *y, void *saved, void *ws, bool packed, const AttnLn *ln, int windows,
-                 void *hip_stream);
+                 const void *bias_table, void *y, void *saved, void *ws, const AttnOpts &o, void *hip_stream);
 
 // The rules of gswa_forward's and gswa_backward's arguments alone (nothing is enqueued): for callers that run the
 // attention layer inside a kernel of their own.

@@ -447,6 +447,48 @@ def test_band_by_band_inference_is_the_whole_map_inference(case, bands):
     assert parity.rel_err(runner.to_host(st.y), runner.to_host(whole)) <= (1e-6 if dtype == "f32" else 2e-2)
 
 
+@pytest.mark.parametrize("groups,hidden,shift", [(1, 120, 4), (2, 128, 3), (3, 68, 4), (6, 120, 7)])
+def test_narrow_layers_of_a_sequence_in_one_launch(groups, hidden, shift):
+    """Narrow layers of a sequence: one launch a layer and one each for all weights of both halves; the same bits for an
+    image alone, in a batch that takes several rounds, band by band (in place) and with the state kept."""
+    import torch
+    from paper_2409_06206_amd import runner
+    B, H, W, L = 41, 40, 48, 3
+    ps = [{k: synth.quantize(v, "bf16") for k, v in synth.astl_params(60, 6, groups, 8, hidden, 500 + l, "stress").items()}
+          for l in range(L)]
+    x, dy = (synth.quantize(a, "bf16") for a in synth.activations(B, H, W, 60, 1))
+
+    def stack(n, every=0):
+        st = runner.DeviceStack(n, H, W, 60, 6, groups, 8, shift, "bf16", hidden, L, every)
+        st.set_params(ps)
+        st.set_inputs(x[:n], dy[:n])
+        return st
+    one, many = stack(1), stack(B)
+    with parity.launched() as names:
+        one.forward(keep=False)
+    assert names == {"pack_fwd", "mlp_pack", "layer_fwd"}, names
+    alone = one.y.clone()
+    kw = dict(heads=6, groups=groups, window=8, shift=shift, store=lambda a: synth.quantize(a, "bf16"))
+    assert parity.rel_err(runner.to_host(alone), astl_oracle.stack_forward(x[:1], ps, **kw)) <= parity.TOL["bf16"]
+    many.forward(keep=False)
+    torch.cuda.synchronize()
+    assert torch.equal(many.y[:1], alone)
+    for nb in (1, 2, 5):
+        one.y.fill_(float("nan"))
+        one.forward_tiled(nb)
+        torch.cuda.synchronize()
+        assert torch.equal(one.y, alone), nb
+    grads = []
+    for every in (0, 2):
+        st = stack(1, every)
+        st.forward(keep=True)
+        st.backward()
+        torch.cuda.synchronize()
+        assert torch.equal(st.y, alone)
+        grads.append(st.dx.clone())
+    assert torch.equal(*grads)
+
+
 @pytest.mark.parametrize("groups,window,shift", [(1, 8, 4), (2, 8, 3), (3, 16, 8)])
 def test_wide_layers_take_ln1_in_the_attention_kernel(groups, window, shift):
     """Wide layers with the streaming MLP kernels: no launch of LN_1, so that a sequence gives the bits of the banded

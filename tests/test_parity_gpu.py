@@ -124,6 +124,32 @@ def test_wide_forward_in_one_launch(oracle, B, H, W, window, shift, groups):
     assert np.array_equal(layer.results()["y"], got["y"])
 
 
+@pytest.mark.parametrize("groups", [1, 2, 3, 6])
+@pytest.mark.parametrize("shift", [0, 3])
+def test_narrow_forward_in_four_waves_and_in_one(oracle, groups, shift):
+    """Up to four windows a compute unit a window is taken by four waves that exchange K and V, beyond by one: the
+    same bits (and the kept group outputs: the gradients of the same rows agree with the oracle in both)."""
+    import torch
+    from paper_2409_06206_amd import runner
+    x, dy, p = parity.make_inputs(41, 40, 48, 60, 6, groups, 8, "bf16", synth.LAYER_SEED0 + 5, "stress")  # 1230 windows
+
+    def run(n, keep):
+        layer = runner.DeviceLayer(n, 40, 48, 60, 6, groups, 8, shift, "bf16")
+        layer.set_params(p)
+        layer.set_inputs(x[:n], dy[:n])
+        layer.forward(keep=keep)
+        if keep:
+            layer.backward()
+        torch.cuda.synchronize()
+        return layer.results()
+    whole, alone, kept = run(41, True), run(1, False), run(1, True)
+    assert np.array_equal(whole["y"][:1], alone["y"]) and np.array_equal(alone["y"], kept["y"])
+    assert np.array_equal(whole["dx"][:1], kept["dx"])
+    want = parity.oracle_results(oracle, x[:1], dy[:1], p, 6, groups, 8, shift)
+    for k, w in want.items():
+        assert parity.rel_err(kept[k], w) <= parity.TOL["bf16"], k
+
+
 def test_kernel_timing_aid_reports_the_launched_kernels():
     """gswa_profile_*: per-kernel HIP-event totals for one forward + backward."""
     import torch
