@@ -124,6 +124,23 @@ def test_wide_forward_in_one_launch(oracle, B, H, W, window, shift, groups):
     assert np.array_equal(layer.results()["y"], got["y"])
 
 
+@pytest.mark.parametrize("groups", [1, 2, 3])
+def test_wide_forward_gives_an_image_the_same_bits_alone_and_in_a_batch(groups):
+    """Up to two windows a compute unit four waves take a window, beyond two."""
+    import torch
+    from paper_2409_06206_amd import runner
+    x, dy, p = parity.make_inputs(18, 40, 48, 180, 6, groups, 8, "bf16", synth.LAYER_SEED0 + 6, "stress")  # 540 windows
+    y = []
+    for n in (18, 1):
+        layer = runner.DeviceLayer(n, 40, 48, 180, 6, groups, 8, 4, "bf16")
+        layer.set_params(p)
+        layer.set_inputs(x[:n], dy[:n])
+        layer.forward(keep=False)
+        torch.cuda.synchronize()
+        y.append(layer.results()["y"][:1])
+    assert np.array_equal(*y)
+
+
 @pytest.mark.parametrize("groups", [1, 2, 3, 6])
 @pytest.mark.parametrize("shift", [0, 3])
 def test_narrow_forward_in_four_waves_and_in_one(oracle, groups, shift):
