@@ -109,7 +109,15 @@ template <typename T_, int C_, int HEADS_, int G_, int M_, int DQ_, int HID_, in
     static constexpr size_t SZ_DX = OVER && NF * SZ_F > SZ_ROW ? NF * SZ_F : SZ_ROW;
     static constexpr size_t B_DX = 2 * SZ_ROW, B_R = B_DX + SZ_DX, B_DO = B_R + SZ_R, B_FO = OVER ? B_DX : B_DO + SZ_DO;
     static constexpr size_t B_H = 3 * SZ_ROW, B_END = B_DO + SZ_DO + (OVER ? 0 : NF * SZ_F);
-    static constexpr size_t bwd_tb(bool layer) { return layer && B_H + 2 * SZ_H > B_END ? B_H + 2 * SZ_H : B_END; }
+    // Where there is room: sums of a head's score gradients over pairs of window rows at the same distance (see fold_blocks)
+    static constexpr size_t SZ_S = sizeof(float) * NTB * N;
+    static constexpr size_t tb_at(bool layer, bool blocks)
+    {
+        const size_t end = B_END + (blocks ? NF * SZ_S : 0);
+        return layer && B_H + 2 * SZ_H > end ? B_H + 2 * SZ_H : end;
+    }
+    static constexpr bool BLOCKS = sizeof(E) == 2 && tb_at(false, true) + SZ_TB + SZ_SR <= 160 * 1024 && tb_at(true, true) + SZ_TB + SZ_SR <= 160 * 1024;
+    static constexpr size_t bwd_tb(bool layer) { return tb_at(layer, BLOCKS); }
     static constexpr size_t bwd_lds(bool layer) { return bwd_tb(layer) + SZ_TB + SZ_SR; }
     static_assert(fwd_lds(true) <= 160 * 1024 && bwd_lds(true) <= 160 * 1024, "LDS budget");
 };
@@ -1263,6 +1271,54 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
                 if (dr > 0) put_grad(tg + e - S::M * S::NTB * S::HEADS, t10, first);
                 if (dr > 0 && dc > 0) put_grad(tg + e - S::M * (S::NTB + 1) * S::HEADS, t11, first);
             };
+            // The same in two steps where LDS has room for what lies between (BLOCKS).  First the blocks [keys of a window row]
+            // x [queries of a window row] at the same distance dr of the two rows are added up: a lane owns four
+            // neighbouring queries of one column of keys and the distances dr and dr - M, M blocks in all, read eight
+            // bytes at a time.  Then the diagonals of each sum.  `fold` reads two bytes at a time and is three wavefronts'
+            // work that the others wait for (8.2 k clocks under the second head's key role, 5.5 k behind the last head's);
+            // this is seven units of 2 k and nine of 1 k (32 48x48 patches, two groups, fwd + bwd: 113.0 -> 109.1 us; six
+            // groups of six heads, 4 patches: 94 -> 87).
+            constexpr int FB = up(S::M * S::M * S::M / 4, 64), FS = up(S::NTBL, 64);
+            float *SB = reinterpret_cast<float *>(lds + S::B_END);
+            auto fold_blocks = [&](int slot, int unit) {
+                FRESH_LANE;
+                const int task = unit * 64 + 16 * q + l16;
+                if (task >= S::M * S::M * S::M / 4) return;
+                const int cq = task % (S::M / 4), c = task / (S::M / 4) % S::M, dr = task / (S::M / 4 * S::M);
+                const E *fo = FO + slot * S::N * S::PF + c * S::PF + 4 * cq;
+                F v[S::M];
+#pragma unroll
+                for (int r = 0; r < S::M; ++r) v[r] = O::ld(fo + r * S::M * S::PF + (r + dr >= S::M ? r + dr - S::M : r + dr) * S::M);
+                loads_issued();
+                f32x4 near = zero4(), wrap = zero4(); // dr, dr - M
+#pragma unroll
+                for (int r = 0; r < S::M; ++r) {
+                    const f32x4 x = O::wide(v[r]);
+                    const float w = r + dr >= S::M ? 1.f : 0.f, n = 1.f - w;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        near[i] = fmaf(x[i], n, near[i]);
+                        wrap[i] = fmaf(x[i], w, wrap[i]);
+                    }
+                }
+                float *sb = SB + slot * S::NTB * S::N + c * S::M + 4 * cq;
+                *reinterpret_cast<f32x4 *>(sb + (dr + S::M - 1) * S::N) = near;
+                if (dr > 0) *reinterpret_cast<f32x4 *>(sb + (dr - 1) * S::N) = wrap;
+            };
+            auto fold_sums = [&](int hl, int slot, int unit) {
+                FRESH_LANE;
+                const int e = unit * 64 + 16 * q + l16;
+                if (e >= S::NTBL) return;
+                const int dri = e / S::NTB, dc = e - dri * S::NTB - (S::M - 1);
+                const float *sb = SB + slot * S::NTB * S::N + dri * S::N;
+                float v[S::M], sum = 0.f;
+#pragma unroll
+                for (int c = 0; c < S::M; ++c) v[c] = sb[c * S::M + (c + dc < 0 ? 0 : c + dc >= S::M ? S::M - 1 : c + dc)];
+                loads_issued();
+#pragma unroll
+                for (int c = 0; c < S::M; ++c) sum += c + dc >= 0 && c + dc < S::M ? v[c] : 0.f;
+                put_grad(part + S::P_TB + e * S::HEADS + gi * S::HG + hl, sum, first);
+            };
             // ---- key role, NF heads at a time: dV, dK, and the score gradients for the table gradient.  With one round they
             // go to LDS as they come; with more they wait in registers until the heads before have been folded, which the
             // wavefronts without a tile do meanwhile. ----
@@ -1321,9 +1377,14 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
                 if (!DIRECT) {
                     if (round > 0)
 #pragma unroll 1
-                        for (int u = UR < S::WAVES ? wv - UR : wv; u >= 0 && u < S::NF * FP; u += SPARE)
-                            fold((round - 1) * S::NF + u / FP, u / FP, u % FP);
+                        for (int u = UR < S::WAVES ? wv - UR : wv; u >= 0 && u < S::NF * (S::BLOCKS ? FB : FP); u += SPARE) {
+                            if constexpr (S::BLOCKS) fold_blocks(u / FB, u % FB);
+                            else fold((round - 1) * S::NF + u / FP, u / FP, u % FP);
+                        }
                     __syncthreads();
+                    if (S::BLOCKS && round > 0)
+#pragma unroll 1
+                        for (int u = S::WAVES - 1 - wv; u < S::NF * FS; u += S::WAVES) fold_sums((round - 1) * S::NF + u / FS, u / FS, u % FS);
 #pragma unroll
                     for (int j = 0; j < PR_; ++j) {
                         FRESH_LANE;
@@ -1356,7 +1417,7 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
             }
             __syncthreads();
             // ---- table gradient, dF = d(q|k|v) Wqkv, d Wqkv = d(q|k|v)^T F ----
-            constexpr int UF = S::CTG * S::TU, PX = up(UF, S::WAVES), CP2 = up(S::CTG, 2), V0 = S::NF * FP, V1 = V0 + S::NFT * CP2;
+            constexpr int UF = S::CTG * S::TU, PX = up(UF, S::WAVES), CP2 = up(S::CTG, 2), V0 = S::NF * (S::BLOCKS ? FB : FP), V1 = V0 + S::NFT * CP2;
             f32x4 df[PX][S::TT];
             const T *wq = static_cast<const T *>(a.w_qkv) + (long)gi * S::RG * S::CG;
 #pragma unroll
@@ -1402,7 +1463,8 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
             for (int u = (wv + S::WAVES - UF % S::WAVES) % S::WAVES; u < V1; u += S::WAVES) {
                 FRESH_LANE;
                 if (u < V0) {
-                    if ((S::ROUNDS - 1) * S::NF + u / FP < S::HG) fold((S::ROUNDS - 1) * S::NF + u / FP, u / FP, u % FP);
+                    if constexpr (S::BLOCKS) { if ((S::ROUNDS - 1) * S::NF + u / FB < S::HG) fold_blocks(u / FB, u % FB); }
+                    else { if ((S::ROUNDS - 1) * S::NF + u / FP < S::HG) fold((S::ROUNDS - 1) * S::NF + u / FP, u / FP, u % FP); }
                 } else {
                     constexpr int P = S::CTG > 1 ? 2 : 1;
                     const int ft = (u - V0) / CP2, ct = P * ((u - V0) - ft * CP2);
@@ -1433,6 +1495,10 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
                 }
             }
             __syncthreads();
+            if (S::BLOCKS)
+#pragma unroll 1
+                for (int u = (wv + S::WAVES - UF % S::WAVES) % S::WAVES; u < S::NF * FS; u += S::WAVES)
+                    if ((S::ROUNDS - 1) * S::NF + u / FS < S::HG) fold_sums((S::ROUNDS - 1) * S::NF + u / FS, u / FS, u % FS);
 #pragma unroll
             for (int k = 0; k < PX; ++k) {
                 FRESH_LANE;
