@@ -40,8 +40,8 @@ template <class Cf> struct WideBwdCfg {
     static constexpr int TILES_AU = FR_UNIT / Cf::KSC;             // (head, feature tile) pairs of dO per unit
     static_assert(Cf::HG * Cf::ET * Cf::KSC == NAU * FR_UNIT && FR_UNIT % Cf::KSC == 0, "dO units");
     static constexpr int FPW = (FR_UNIT + NWAVES - 1) / NWAVES;    // fragments a wave moves per unit
-    static constexpr size_t OFF_BIAS = 0;                          // fp32 b_qkv [3C] (b_proj [C] behind it)
-    static constexpr size_t OFF_TBL = (size_t)16 * Cf::C;          // fp32 [HG][TBW_PITCH], base-2 units: the group's heads
+    static constexpr size_t OFF_BIAS = 0;                          // fp32 b_qkv of the group, [HG][q, k, v][32]
+    static constexpr size_t OFF_TBL = (size_t)Cf::HG * 96 * 4;       // fp32 [HG][TBW_PITCH], base-2 units: the group's heads
     static constexpr size_t OFF_FOLD = OFF_TBL + (size_t)Cf::HG * Cf::TBW_PITCH * 4; // per wave 28 x 64 fp32
     static constexpr size_t FOLD_BYTES = (size_t)28 * 64 * 4;
     static constexpr size_t OFF_W = OFF_FOLD + NWAVES * FOLD_BYTES;
@@ -192,8 +192,12 @@ __global__ __launch_bounds__(256, 1) void wide_attn_bwd_kernel(Geom g, const bf1
     // set-up: dy of the first window, first unit, linear biases, the bias table of the group's heads
     if (active) fetch_dy(win);
     stream_unit(0, 0);
-    for (int i = tid; i < C; i += W::NTHREADS)
-        reinterpret_cast<uint4 *>(lds + W::OFF_BIAS)[i] = reinterpret_cast<const uint4 *>(pack + Cf::P_BIAS)[i];
+    // (the group's q|k|v bias, padded to whole tiles [head][q, k, v][32], q in base-2 units)
+    for (int i = tid; i < HG * 96; i += W::NTHREADS) {
+        const int e = i & 31, t3 = (i >> 5) % 3, hl = i / 96;
+        const float v = e < D ? reinterpret_cast<const float *>(pack + Cf::P_BIAS)[GI * 3 * CG + t3 * CG + hl * D + e] : 0.f;
+        reinterpret_cast<float *>(lds + W::OFF_BIAS)[i] = t3 == 0 ? v * kLog2e : v;
+    }
     for (int i = tid; i < HG * TP / 4; i += W::NTHREADS)
         reinterpret_cast<uint4 *>(lds + W::OFF_TBL)[i] =
             reinterpret_cast<const uint4 *>(pack + Cf::P_TBW + (size_t)GI * HG * TP * 4)[i];
@@ -283,30 +287,39 @@ __global__ __launch_bounds__(256, 1) void wide_attn_bwd_kernel(Geom g, const bf1
 #pragma unroll
                         for (int t = 0; t < 4; ++t) acc[i][t] = zero4;
                     const uint8_t *dyrow = stage + lds0 + (size_t)(rsub * M + cn) * (2 * C) + 16 * q;
-#pragma unroll
-                    for (int ks = 0; ks < KSC; ++ks) {
-                        uint4 dyf[4];
+                    // (operands of a K step are read under the products of the step before: left alone the compiler reads
+                    // a fragment and waits for it, twice the clocks of its four products.  Here and in the QKV step below:
+                    // 32 images of 64x64, fwd + bwd, 351.3 -> 346.7 us; 512x512 670 -> 660, three groups 652 -> 640)
+                    uint4 dyf[2][4], wf[2][W::TILES_AU];
+                    auto fetch = [&](int ks) {
 #pragma unroll
                         for (int t = 0; t < 4; ++t) {
                             const uint8_t *p = dyrow + (size_t)t * (2 * M * 2 * C) + 64 * ks;
-                            const uint2 lo = *reinterpret_cast<const uint2 *>(p);
-                            const uint2 hi = *reinterpret_cast<const uint2 *>(p + 8);
-                            uint4 v = cat(lo, hi);
+                            dyf[ks & 1][t] = cat(*reinterpret_cast<const uint2 *>(p), *reinterpret_cast<const uint2 *>(p + 8));
+                        }
+#pragma unroll
+                        for (int i = 0; i < W::TILES_AU; ++i) wf[ks & 1][i] = wu[(i * KSC + ks) * 64 + lane];
+                    };
+                    fetch(0);
+#pragma unroll
+                    for (int ks = 0; ks < KSC; ++ks) {
+                        if (ks + 1 < KSC) fetch(ks + 1);
+                        __builtin_amdgcn_sched_barrier(0);
+                        if (32 * ks + 32 > C) {
                             const int c0 = 32 * ks + 8 * q; // first channel of this lane's slots
-                            if (32 * ks + 32 > C) {
+#pragma unroll
+                            for (int t = 0; t < 4; ++t) {
+                                uint4 &v = dyf[ks & 1][t];
                                 v.x = c0 < C ? v.x : 0u;
                                 v.y = c0 + 2 < C ? v.y : 0u;
                                 v.z = c0 + 4 < C ? v.z : 0u;
                                 v.w = c0 + 6 < C ? v.w : 0u;
                             }
-                            dyf[t] = v;
                         }
 #pragma unroll
-                        for (int i = 0; i < W::TILES_AU; ++i) {
-                            const uint4 wf = wu[(i * KSC + ks) * 64 + lane];
+                        for (int i = 0; i < W::TILES_AU; ++i)
 #pragma unroll
-                            for (int t = 0; t < 4; ++t) acc[i][t] = mma32(wf, dyf[t], acc[i][t]);
-                        }
+                            for (int t = 0; t < 4; ++t) acc[i][t] = mma32(wf[ks & 1][i], dyf[ks & 1][t], acc[i][t]);
                     }
 #pragma unroll
                     for (int i = 0; i < W::TILES_AU; ++i) {
@@ -337,29 +350,35 @@ __global__ __launch_bounds__(256, 1) void wide_attn_bwd_kernel(Geom g, const bf1
                 if (active) {
                     // ---- Q^T, K^T, V^T exactly as the forward computes them (rows = head features) ----
                     uint2 Qb[2][4], Kb[2][4], Vb[2][4];
+                    // (the fragments of a K step are read under the products of the step before; vector instructions may cross
+                    // the barrier, so that the packing of one kind overlaps the products of the next)
+                    uint4 fr[2][2];
+                    f32x4 b4[2];
+                    auto fetch = [&](int i) { // i = 3 kinds x KS steps
+                        const int t3 = i / KS, ks = i % KS;
+#pragma unroll
+                        for (int et = 0; et < 2; ++et) {
+                            if (ks == 0) b4[et] = *reinterpret_cast<const f32x4 *>(bqkv + (hl * 3 + t3) * 32 + 16 * et + 4 * q);
+                            fr[i & 1][et] = wu[((t3 * 2 + et) * KS + ks) * 64 + lane];
+                        }
+                    };
+                    fetch(0);
 #pragma unroll
                     for (int t3 = 0; t3 < 3; ++t3) {
                         f32x4 acc[2][4];
 #pragma unroll
-                        for (int et = 0; et < 2; ++et) {
-                            f32x4 b4;
+                        for (int et = 0; et < 2; ++et)
 #pragma unroll
-                            for (int j = 0; j < 4; ++j) {
-                                const int e = 16 * et + 4 * q + j;
-                                const float bv = e < D ? bqkv[GI * 3 * CG + t3 * CG + hl * D + e] : 0.f;
-                                b4[j] = t3 == 0 ? bv * kLog2e : bv;
-                            }
-#pragma unroll
-                            for (int t = 0; t < 4; ++t) acc[et][t] = b4;
-                        }
+                            for (int t = 0; t < 4; ++t) acc[et][t] = b4[et];
 #pragma unroll
                         for (int ks = 0; ks < KS; ++ks) {
-                            const uint4 f0 = wu[((t3 * 2 + 0) * KS + ks) * 64 + lane];
-                            const uint4 f1 = wu[((t3 * 2 + 1) * KS + ks) * 64 + lane];
+                            const int i = t3 * KS + ks;
+                            if (i + 1 < 3 * KS) fetch(i + 1);
+                            __builtin_amdgcn_sched_barrier(0x6);
 #pragma unroll
                             for (int t = 0; t < 4; ++t) {
-                                acc[0][t] = mma32(f0, xh[ks][t], acc[0][t]);
-                                acc[1][t] = mma32(f1, xh[ks][t], acc[1][t]);
+                                acc[0][t] = mma32(fr[i & 1][0], xh[ks][t], acc[0][t]);
+                                acc[1][t] = mma32(fr[i & 1][1], xh[ks][t], acc[1][t]);
                             }
                         }
 #pragma unroll
