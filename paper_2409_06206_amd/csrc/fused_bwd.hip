@@ -47,7 +47,7 @@ template <class Cf, int HB_, int HE_, bool WPROJ_ = (HE_ == Cf::HEADS)> struct B
     static constexpr size_t SRC_WQT = Cf::P_WQT + (size_t)HB * 3 * ET * HG * ET * 512;
     static constexpr size_t OFF_WQ = 0;
     static constexpr size_t OFF_BIAS = OFF_WQ + (size_t)N_WQ * 1024;
-    static constexpr size_t OFF_WPT = OFF_BIAS + (size_t)16 * C;
+    static constexpr size_t OFF_WPT = OFF_BIAS + (size_t)NH * 3 * ET * 64; // fp32 b_qkv [head][q, k, v][16 ET]
     // two heads of a wide three-head group fit LDS only without the Wproj^T fragments: those are
     // then read from the packed buffer in memory (12 reads per wave, window and head)
     static constexpr bool WPT_LDS = !(Cf::SPLIT && NH > 1 && Cf::HG == 3);
@@ -103,8 +103,56 @@ template <class Cf> __device__ __forceinline__ constexpr int fqt(int hd, int t, 
     return ((((hd * 3 + t) * Cf::ET + et) * Cf::HG + hlp) * Cf::ET) + etp;
 }
 
+// Channels [c, c + 8) (c + 4) of a row of N channels, read in one piece from where it ends with the row at the
+// latest: nothing outside the row is touched.  piece4 / piece2 move what was read too early into place and put zeros
+// behind the row's end (first: the slot of quad 0; eight resp. four channels a quad).
+struct __attribute__((packed, aligned(4))) Piece4 { uint32_t v[4]; };
+struct __attribute__((packed, aligned(4))) Piece2 { uint32_t v[2]; };
+template <int N> __device__ __forceinline__ uint4 load_piece4(const bf16_t *row, int c)
+{
+    static_assert(N >= 8 && N % 2 == 0, "whole pieces");
+    const Piece4 p = *reinterpret_cast<const Piece4 *>(row + (c < N - 8 ? c : N - 8));
+    return make_uint4(p.v[0], p.v[1], p.v[2], p.v[3]);
+}
+template <int N> __device__ __forceinline__ uint2 load_piece2(const bf16_t *row, int c)
+{
+    static_assert(N >= 4 && N % 2 == 0, "whole pieces");
+    const Piece2 p = *reinterpret_cast<const Piece2 *>(row + (c < N - 4 ? c : N - 4));
+    return make_uint2(p.v[0], p.v[1]);
+}
+template <int N> __device__ __forceinline__ uint4 piece4(uint4 p, int first, int q)
+{
+    const int n = N - first; // channels from quad 0's first on; quad n / 8 holds the last n % 8 of them
+    if (n >= 32) return p;
+    const uint32_t w[4] = {p.x, p.y, p.z, p.w};
+    uint32_t o[4];
+    const int part = n / 8, sh = n % 8 == 0 ? 4 : 4 - n % 8 / 2;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        o[i] = q < part ? w[i] : 0u;
+        if (i + sh < 4) o[i] = q == part ? w[i + sh < 4 ? i + sh : 0] : o[i];
+    }
+    return make_uint4(o[0], o[1], o[2], o[3]);
+}
+template <int N> __device__ __forceinline__ uint2 piece2(uint2 p, int first, int q)
+{
+    const int n = N - first;
+    if (n >= 16) return p;
+    const int part = n / 4;
+    uint2 o = make_uint2(q < part ? p.x : 0u, q < part ? p.y : 0u);
+    if (n % 4) o.x = q == part ? p.y : o.x;
+    return o;
+}
+
 constexpr bool ranges_overlap(int a0, int a1, int b0, int b1) { return a0 < b1 && b0 < a1; }
 
+// What bounds it: chains, not rates.  A head is three steps of four wavefronts between barriers, each a few products
+// long, and a CU holds two workgroups: a read that is waited for where it is used costs more than its products.  So the
+// next window's rows are loaded a head before the window ends, in pieces of 16 bytes; a head's weights, biases (whole
+// padded tiles) and bias-table entries are read in front of the barrier before their use; the set-up's loads are all in
+// flight together; the table gradient of as many heads as LDS takes is folded at once.  fwd + bwd, 32 images of 64x64,
+// 60 channels: two groups 142.4 -> 127.0 us, one 198 -> 159, three 155 -> 135, six 143 -> 126.5; one image of 64x64
+// 58.8 -> 46.1; 180 channels with an odd shift, 8 images: two groups 230 -> 182, three 180 -> 143.
 template <class Cf, int HB, int HE, bool WPROJ>
 __global__ __launch_bounds__(256, (BwdCfg<Cf, HB, HE, WPROJ>::LDS_BYTES <= 80 * 1024 ? 2 : 1))
 void fused_bwd_kernel(Geom g, const bf16_t *__restrict__ x,
@@ -171,84 +219,100 @@ void fused_bwd_kernel(Geom g, const bf16_t *__restrict__ x,
         if (sj >= g.W) sj -= g.W;
         return ((long)b * g.H + si) * g.W + sj;
     };
-    uint4 xf[G][KS], af[G][KS], dyf[KSC];
-    uint2 cgrad[NH][ET]; // dF of the next group (Eq. 8) for the heads whose next group an earlier launch finished
+    constexpr auto need_x = [](int gi) { return gi >= GB && gi <= GE; };
+    constexpr auto need_a = [](int gi) { return WPROJ || (gi >= GB - 1 && gi < GE); };
+    // dF of the next group (Eq. 8) comes from the dx slice that an earlier launch finished
+    constexpr auto need_c = [](int hd) {
+        const int gi = hd / HG;
+        return gi < G - 1 && !(HB <= (gi + 1) * HG && HE >= (gi + 2) * HG);
+    };
+    constexpr int ROW_REGS = [&]() {
+        int n = 4 * KSC;
+        for (int gi = 0; gi < G; ++gi) n += 4 * KS * ((need_x(gi) ? 1 : 0) + (need_a(gi) ? 1 : 0));
+        return n;
+    }();
+    uint4 xf[G][KS], af[G][KS], dyf[KSC];    // a window's operands
+    uint4 rx[G][KS], ra[G][KS], rdy[KSC];    // as loaded: partial pieces still unshifted
+    uint2 cgrad[NH][ET], rc[NH][ET];
     auto load_rows = [&](int win) {
         const long tok = token_of(win);
 #pragma unroll
         for (int hx = 0; hx < NH; ++hx) {
             const int hd = HB + hx, gi = hd / HG, hl = hd % HG;
-            const bool in_regs = HB <= (gi + 1) * HG && HE >= (gi + 2) * HG;
 #pragma unroll
             for (int et = 0; et < ET; ++et) {
-                cgrad[hx][et] = make_uint2(0u, 0u);
-                if (gi < G - 1 && !in_regs && g.cascade) {
-                    const int e0 = 16 * et + 4 * q;
-                    const uint32_t *src = reinterpret_cast<const uint32_t *>(dx + tok * C + (gi + 1) * CG + hl * D + e0);
-                    if (e0 < D) cgrad[hx][et].x = src[0];
-                    if (e0 + 2 < D) cgrad[hx][et].y = src[1];
-                }
+                rc[hx][et] = make_uint2(0u, 0u);
+                if (need_c(hd) && g.cascade)
+                    rc[hx][et] = load_piece2<D>(dx + tok * C + (gi + 1) * CG + hl * D, 16 * et + 4 * q);
             }
         }
-        const uint32_t *xrow = reinterpret_cast<const uint32_t *>(x + tok * C);
-        const uint32_t *arow = reinterpret_cast<const uint32_t *>(attn + tok * C);
-        const uint32_t *dyrow = reinterpret_cast<const uint32_t *>(dy + tok * C);
 #pragma unroll
         for (int gi = 0; gi < G; ++gi)
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
-                uint32_t xv[4], av[4];
-                const bool need_x = gi >= GB && gi <= GE;
-                const bool need_a = WPROJ || (gi >= GB - 1 && gi < GE);
-#pragma unroll
-                for (int dw = 0; dw < 4; ++dw) {
-                    const int c = 32 * ks + 8 * q + 2 * dw;
-                    xv[dw] = (need_x && c < CG) ? xrow[(gi * CG + c) >> 1] : 0u;
-                    av[dw] = (need_a && c < CG) ? arow[(gi * CG + c) >> 1] : 0u;
-                }
-                xf[gi][ks] = make_uint4(xv[0], xv[1], xv[2], xv[3]);
-                af[gi][ks] = make_uint4(av[0], av[1], av[2], av[3]);
+                rx[gi][ks] = ra[gi][ks] = make_uint4(0u, 0u, 0u, 0u);
+                if (need_x(gi)) rx[gi][ks] = load_piece4<CG>(x + tok * C + gi * CG, 32 * ks + 8 * q);
+                if (need_a(gi)) ra[gi][ks] = load_piece4<CG>(attn + tok * C + gi * CG, 32 * ks + 8 * q);
             }
 #pragma unroll
-        for (int ks = 0; ks < KSC; ++ks) {
-            uint32_t dwv[4];
-#pragma unroll
-            for (int dw = 0; dw < 4; ++dw) {
-                const int o = 32 * ks + 8 * q + 2 * dw;
-                dwv[dw] = o < C ? dyrow[o >> 1] : 0u;
-            }
-            dyf[ks] = make_uint4(dwv[0], dwv[1], dwv[2], dwv[3]);
-        }
+        for (int ks = 0; ks < KSC; ++ks) rdy[ks] = load_piece4<C>(dy + tok * C, 32 * ks + 8 * q);
     };
-    // (with many groups the row registers are too many to hold two windows' worth at once)
-    constexpr bool PIPE = (2 * G * KS + KSC) * 4 <= 32;
+    auto take_rows = [&]() {
+#pragma unroll
+        for (int hx = 0; hx < NH; ++hx)
+#pragma unroll
+            for (int et = 0; et < ET; ++et) cgrad[hx][et] = piece2<D>(rc[hx][et], 16 * et, q);
+#pragma unroll
+        for (int gi = 0; gi < G; ++gi)
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                xf[gi][ks] = need_x(gi) ? piece4<CG>(rx[gi][ks], 32 * ks, q) : make_uint4(0u, 0u, 0u, 0u);
+                af[gi][ks] = need_a(gi) ? piece4<CG>(ra[gi][ks], 32 * ks, q) : make_uint4(0u, 0u, 0u, 0u);
+            }
+#pragma unroll
+        for (int ks = 0; ks < KSC; ++ks) dyf[ks] = piece4<C>(rdy[ks], 32 * ks, q);
+    };
+    // (the rows of the next window wait in registers from the last head of the window before on; where a launch needs
+    // too many of them they are loaded at the start of their own window)
+    constexpr bool PIPE = ROW_REGS <= 32;
     if (PIPE && (int)blockIdx.x < g.nW) load_rows(blockIdx.x);
 
     // set-up copies, unrolled so that a thread's loads are all in flight before its first store
     {
         constexpr int N_Q = (int)((B::OFF_BIAS - B::OFF_WQ) / 16), N_PT = (int)((B::OFF_WQT - B::OFF_WPT) / 16);
-        constexpr int N_QT = (int)((B::PACK_BYTES - B::OFF_WQT) / 16), N_T = NTBL * NH;
+        constexpr int N_QT = (int)((B::PACK_BYTES - B::OFF_WQT) / 16), N_T = NTBL * NH, N_B = NH * 3 * ET * 16;
         constexpr int I_Q = (N_Q + 255) / 256, I_PT = (N_PT + 255) / 256, I_QT = (N_QT + 255) / 256, I_T = (N_T + 255) / 256;
-        uint4 vq[I_Q], vpt[I_PT > 0 ? I_PT : 1], vqt[I_QT], vb = make_uint4(0u, 0u, 0u, 0u);
+        constexpr int I_B = (N_B + 255) / 256;
+        uint4 vq[I_Q], vpt[I_PT > 0 ? I_PT : 1], vqt[I_QT];
         uint16_t vt[I_T];
+        float vb[I_B];
+        // (threads behind a part's end copy its last piece once more: under a condition each load would sit, and be
+        // waited for, in the branch of its store)
+        auto at = [&](int k, int n) { const int i = 256 * k + tid; return i < n ? i : n - 1; };
 #pragma unroll
-        for (int k = 0; k < I_Q; ++k) { const int i = 256 * k + tid; vq[k] = reinterpret_cast<const uint4 *>(pack + B::SRC_WQ)[i < N_Q ? i : 0]; }
+        for (int k = 0; k < I_Q; ++k) vq[k] = reinterpret_cast<const uint4 *>(pack + B::SRC_WQ)[at(k, N_Q)];
 #pragma unroll
-        for (int k = 0; k < I_PT; ++k) { const int i = 256 * k + tid; vpt[k] = reinterpret_cast<const uint4 *>(pack + B::SRC_WPT)[i < N_PT ? i : 0]; }
+        for (int k = 0; k < I_PT; ++k) vpt[k] = reinterpret_cast<const uint4 *>(pack + B::SRC_WPT)[at(k, N_PT)];
 #pragma unroll
-        for (int k = 0; k < I_QT; ++k) { const int i = 256 * k + tid; vqt[k] = reinterpret_cast<const uint4 *>(pack + B::SRC_WQT)[i < N_QT ? i : 0]; }
-        if (tid < C) vb = reinterpret_cast<const uint4 *>(pack + Cf::P_BIAS)[tid];
+        for (int k = 0; k < I_QT; ++k) vqt[k] = reinterpret_cast<const uint4 *>(pack + B::SRC_WQT)[at(k, N_QT)];
 #pragma unroll
-        for (int k = 0; k < I_T; ++k) { const int i = 256 * k + tid; const int ii = i < N_T ? i : 0; vt[k] = table[(ii % NTBL) * HEADS + HB + ii / NTBL].bits; }
+        for (int k = 0; k < I_B; ++k) {
+            const int i = at(k, N_B), e = i % (16 * ET), t = i / (16 * ET) % 3, hd = HB + i / (48 * ET);
+            vb[k] = reinterpret_cast<const float *>(pack + Cf::P_BIAS)[hd / HG * 3 * CG + t * CG + hd % HG * D + (e < D ? e : 0)];
+            if (e >= D) vb[k] = 0.f;
+        }
 #pragma unroll
-        for (int k = 0; k < I_Q; ++k) { const int i = 256 * k + tid; if (i < N_Q) reinterpret_cast<uint4 *>(lds + B::OFF_WQ)[i] = vq[k]; }
+        for (int k = 0; k < I_T; ++k) { const int i = at(k, N_T); vt[k] = table[(i % NTBL) * HEADS + HB + i / NTBL].bits; }
 #pragma unroll
-        for (int k = 0; k < I_PT; ++k) { const int i = 256 * k + tid; if (i < N_PT) reinterpret_cast<uint4 *>(lds + B::OFF_WPT)[i] = vpt[k]; }
+        for (int k = 0; k < I_Q; ++k) reinterpret_cast<uint4 *>(lds + B::OFF_WQ)[at(k, N_Q)] = vq[k];
 #pragma unroll
-        for (int k = 0; k < I_QT; ++k) { const int i = 256 * k + tid; if (i < N_QT) reinterpret_cast<uint4 *>(lds + B::OFF_WQT)[i] = vqt[k]; }
-        if (tid < C) reinterpret_cast<uint4 *>(lds + B::OFF_BIAS)[tid] = vb;
+        for (int k = 0; k < I_PT; ++k) reinterpret_cast<uint4 *>(lds + B::OFF_WPT)[at(k, N_PT)] = vpt[k];
 #pragma unroll
-        for (int k = 0; k < I_T; ++k) { const int i = 256 * k + tid; if (i < N_T) tblf[i] = __uint_as_float((uint32_t)vt[k] << 16); }
+        for (int k = 0; k < I_QT; ++k) reinterpret_cast<uint4 *>(lds + B::OFF_WQT)[at(k, N_QT)] = vqt[k];
+#pragma unroll
+        for (int k = 0; k < I_B; ++k) reinterpret_cast<float *>(lds + B::OFF_BIAS)[at(k, N_B)] = vb[k];
+#pragma unroll
+        for (int k = 0; k < I_T; ++k) tblf[at(k, N_T)] = __uint_as_float((uint32_t)vt[k] << 16);
     }
 
     // this lane's token inside the window, and the bias-table row of its (query, key 4q) pair:
@@ -281,13 +345,38 @@ void fused_bwd_kernel(Geom g, const bf16_t *__restrict__ x,
 
     const uint2 ones2 = make_uint2(0x3f803f80u, 0x3f803f80u);
 
+    // A head's weights and biases.  Narrow layers read them before the barrier in front of their use, so that the
+    // wait there hides the reads' latency; wide ones, short of registers, where they are used.
+    constexpr bool AHEAD = !Cf::SPLIT;
+    struct HeadOps {
+        uint4 pt[ET][KSC], qkv[3][ET][KS];
+        f32x4 bT[3][ET];   // bias of the rows 4q + j
+        float bN[2][ET];   // bias of q, k of column l16
+    } ho;
     for (int win = blockIdx.x; win < g.nW; win += gridDim.x) {
         // (the lane index as this window's address arithmetic sees it: opaque, so that the many per-lane LDS and
         // memory addresses below are computed where they are used instead of being kept, and spilled, across windows)
         int lane_w = threadIdx.x & 63;
         asm volatile("" : "+v"(lane_w));
         const int lane = lane_w, l16 = lane & 15, q = lane >> 4;
+        auto read_head = [&](int hx) {
+#pragma unroll
+            for (int et = 0; et < ET; ++et) {
+#pragma unroll
+                for (int ks = 0; ks < KSC; ++ks) ho.pt[et][ks] = wpt[((hx * ET + et) * KSC + ks) * 64 + lane];
+#pragma unroll
+                for (int t = 0; t < 3; ++t) {
+                    const float *bias = bqkv + (hx * 3 + t) * (16 * ET) + 16 * et;
+#pragma unroll
+                    for (int ks = 0; ks < KS; ++ks) ho.qkv[t][et][ks] = wq[fq<Cf>(hx, t, et, ks) * 64 + lane];
+                    ho.bT[t][et] = *reinterpret_cast<const f32x4 *>(bias + 4 * q);
+                    if (t < 2) ho.bN[t][et] = bias[l16];
+                }
+            }
+        };
         if (!PIPE) load_rows(win);
+        if (AHEAD) read_head(NH - 1);
+        take_rows();
         // Eq. 8: the input of a group with a cascade term is F = x slice + previous group's output,
         // rounded to bf16 exactly as the forward kernels round it (it is the operand of their QKV
         // product), so that q, k, v and the probabilities are recomputed from the same values
@@ -334,8 +423,8 @@ void fused_bwd_kernel(Geom g, const bf16_t *__restrict__ x,
 #pragma unroll
         for (int k = 0; k < KTP; ++k) {
             const int ti = 4 * k + wv;
-            if (ti < NTP) {
-                const int ot = ti / CTP, ct = ti - ot * CTP;
+            if (4 * k + 3 < NTP || ti < NTP) {
+                const int ot = CTP == 4 ? k : ti / CTP, ct = CTP == 4 ? wv : ti - ot * CTP;
                 const uint16_t *ar = dybuf + (16 * ot + l16) * LW + 8 * q;
                 const uint16_t *br = abuf + (16 * ct + l16) * LW + 8 * q;
 #pragma unroll
@@ -366,6 +455,7 @@ void fused_bwd_kernel(Geom g, const bf16_t *__restrict__ x,
 #pragma unroll
                     for (int etp = 0; etp < ET; ++etp) dFT[hlp][etp] = f32x4{0.f, 0.f, 0.f, 0.f};
             }
+            if (!AHEAD) read_head(hx);
             // ---- dO^T of this head: adjoint of Eq. 7, plus the gradient arriving through Eq. 8 ----
             f32x4 dOT[ET];
 #pragma unroll
@@ -381,29 +471,21 @@ void fused_bwd_kernel(Geom g, const bf16_t *__restrict__ x,
                 }
 #pragma unroll
                 for (int ks = 0; ks < KSC; ++ks)
-                    dOT[et] = mma32(wpt[((hx * ET + et) * KSC + ks) * 64 + lane], dyf[ks], dOT[et]);
+                    dOT[et] = mma32(ho.pt[et][ks], dyf[ks], dOT[et]);
             }
             // ---- recompute q, k (both forms) and v (T-form) of this wave's tokens ----
             f32x4 qT[ET], qN[ET], kT[ET], kN[ET], vT[ET];
 #pragma unroll
             for (int et = 0; et < ET; ++et) {
-                const int ev = 16 * et + l16;
-                const float bqn = ev < D ? bqkv[gi * 3 * CG + hl * D + ev] : 0.f;
-                const float bkn = ev < D ? bqkv[gi * 3 * CG + CG + hl * D + ev] : 0.f;
+                qT[et] = ho.bT[0][et];
+                kT[et] = ho.bT[1][et];
+                vT[et] = ho.bT[2][et];
+                const float bqn = ho.bN[0][et], bkn = ho.bN[1][et];
                 qN[et] = f32x4{bqn, bqn, bqn, bqn};
                 kN[et] = f32x4{bkn, bkn, bkn, bkn};
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int e = 16 * et + 4 * q + j;
-                    qT[et][j] = e < D ? bqkv[gi * 3 * CG + hl * D + e] : 0.f;
-                    kT[et][j] = e < D ? bqkv[gi * 3 * CG + CG + hl * D + e] : 0.f;
-                    vT[et][j] = e < D ? bqkv[gi * 3 * CG + 2 * CG + hl * D + e] : 0.f;
-                }
-#pragma unroll
                 for (int ks = 0; ks < KS; ++ks) {
-                    const uint4 fq_ = wq[fq<Cf>(hx, 0, et, ks) * 64 + lane];
-                    const uint4 fk_ = wq[fq<Cf>(hx, 1, et, ks) * 64 + lane];
-                    const uint4 fv_ = wq[fq<Cf>(hx, 2, et, ks) * 64 + lane];
+                    const uint4 fq_ = ho.qkv[0][et][ks], fk_ = ho.qkv[1][et][ks], fv_ = ho.qkv[2][et][ks];
                     qT[et] = mma32(fq_, xf[gi][ks], qT[et]);
                     qN[et] = mma32(xf[gi][ks], fq_, qN[et]);
                     kT[et] = mma32(fk_, xf[gi][ks], kT[et]);
@@ -424,7 +506,16 @@ void fused_bwd_kernel(Geom g, const bf16_t *__restrict__ x,
                 *reinterpret_cast<uint2 *>(qtr + row) = pack_bf16x4(qN[et]);
                 store_tile_transposed(dotr + (16 * et + 4 * q) * LD + 16 * wv + (l16 & ~1), LD, dOb[et], lane);
             }
+            float tb[4][4]; // bias of (query, key 16kt+4q+j)
+            auto read_table = [&]() {
+#pragma unroll
+                for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) tb[kt][j] = tblf[hx * NTBL + idx0 - 30 * kt - j];
+            };
+            if (AHEAD) read_table();
             __syncthreads();
+            if (PIPE && hdr == NH - 1 && win + (int)gridDim.x < g.nW) load_rows(win + gridDim.x);
 
             // ---- query role: S^T, P^T, dP^T, dS^T for this wave's 16 queries, all 64 keys ----
             f32x4 st[4], dp[4];
@@ -438,11 +529,11 @@ void fused_bwd_kernel(Geom g, const bf16_t *__restrict__ x,
                     dp[kt] = mma16(vb[(kt * ET + et) * 64 + lane], dOb[et], dp[kt]);
                 }
             }
+            if (!AHEAD) read_table();
 #pragma unroll
             for (int kt = 0; kt < 4; ++kt)
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    st[kt][j] += tblf[hx * NTBL + idx0 - 30 * kt - j];
+                for (int j = 0; j < 4; ++j) st[kt][j] += tb[kt][j];
             if (lastrow || lastcol) {
 #pragma unroll
                 for (int kt = 0; kt < 4; ++kt)
@@ -509,6 +600,18 @@ void fused_bwd_kernel(Geom g, const bf16_t *__restrict__ x,
                 }
                 *reinterpret_cast<uint2 *>(gbuf + ((0 * ET + et) * 16 + l16) * LW + 16 * wv + 4 * q) = pack_bf16x4(dqN);
             }
+            uint2 wx[3][ET][HG][ET]; // the head's Wqkv^T tiles
+            auto read_wqt = [&]() {
+#pragma unroll
+                for (int t = 0; t < 3; ++t)
+#pragma unroll
+                    for (int et = 0; et < ET; ++et)
+#pragma unroll
+                        for (int hlp = 0; hlp < HG; ++hlp)
+#pragma unroll
+                            for (int etp = 0; etp < ET; ++etp) wx[t][et][hlp][etp] = wqt[fqt<Cf>(hx, t, et, hlp, etp) * 64 + lane];
+            };
+            if (AHEAD) read_wqt();
             __syncthreads();
 
             // ---- key role: dV = P^T dO, dK = scale * dS^T Q for this wave's 16 keys, both forms ----
@@ -561,6 +664,9 @@ void fused_bwd_kernel(Geom g, const bf16_t *__restrict__ x,
                 }
             }
             // ---- d(q|k|v) through Wqkv^T into dF of the group ----
+            auto w_at = [&](int t, int et, int hlp, int etp) {
+                return AHEAD ? wx[t][et][hlp][etp] : wqt[fqt<Cf>(hx, t, et, hlp, etp) * 64 + lane];
+            };
 #pragma unroll
             for (int et = 0; et < ET; ++et) {
                 const uint2 gq = pack_bf16x4(dqT[et]), gk = pack_bf16x4(dkT[et]), gv = pack_bf16x4(dvT[et]);
@@ -568,18 +674,19 @@ void fused_bwd_kernel(Geom g, const bf16_t *__restrict__ x,
                 for (int hlp = 0; hlp < HG; ++hlp)
 #pragma unroll
                     for (int etp = 0; etp < ET; ++etp) {
-                        dFT[hlp][etp] = mma16(wqt[fqt<Cf>(hx, 0, et, hlp, etp) * 64 + lane], gq, dFT[hlp][etp]);
-                        dFT[hlp][etp] = mma16(wqt[fqt<Cf>(hx, 1, et, hlp, etp) * 64 + lane], gk, dFT[hlp][etp]);
-                        dFT[hlp][etp] = mma16(wqt[fqt<Cf>(hx, 2, et, hlp, etp) * 64 + lane], gv, dFT[hlp][etp]);
+                        dFT[hlp][etp] = mma16(w_at(0, et, hlp, etp), gq, dFT[hlp][etp]);
+                        dFT[hlp][etp] = mma16(w_at(1, et, hlp, etp), gk, dFT[hlp][etp]);
+                        dFT[hlp][etp] = mma16(w_at(2, et, hlp, etp), gv, dFT[hlp][etp]);
                     }
             }
+            if (AHEAD && hdr + 1 < NH) read_head(hx - 1);
             __syncthreads();
 
             // ---- d w_qkv (and d b_qkv in the spare column) of this head: K = 64 tokens ----
 #pragma unroll
             for (int k = 0; k < KT; ++k) {
                 const int ti = 4 * k + wv;
-                if (ti < NT) {
+                if (4 * k + 3 < NT || ti < NT) {
                     const int r = ti / CT, ct = ti - r * CT;
                     const uint16_t *ar = gbuf + (16 * r + l16) * LW + 8 * q;
                     const uint16_t *br = fbuf + (16 * ct + l16) * LW + 8 * q;
@@ -611,7 +718,6 @@ void fused_bwd_kernel(Geom g, const bf16_t *__restrict__ x,
                     }
             }
         }
-        if (PIPE && win + (int)gridDim.x < g.nW) load_rows(win + gridDim.x);
     }
 
     // ---- flush: this workgroup's partial sums, in parameter order.  The packed query weights
@@ -624,15 +730,12 @@ void fused_bwd_kernel(Geom g, const bf16_t *__restrict__ x,
         const int ti = 4 * k + wv;
         if (ti < NTP) {
             const int ot = ti / CTP, ct = ti - ot * CTP;
-            const int c = 16 * ct + l16;
+            const int c = 16 * ct + l16, o = 16 * ot + 4 * q;
+            float *dst = mine + (c < C ? B::L_DWP + o * C + c : B::L_DBP + o);
+            const int step = c < C ? C : 1;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int o = 16 * ot + 4 * q + j;
-                if (o < C) {
-                    if (c < C) mine[B::L_DWP + o * C + c] = wpacc[k][j];
-                    else if (c == C) mine[B::L_DBP + o] = wpacc[k][j];
-                }
-            }
+            for (int j = 0; j < 4; ++j)
+                if (o + j < C && c <= C) dst[j * step] = wpacc[k][j];
         }
     }
     }
@@ -646,35 +749,36 @@ void fused_bwd_kernel(Geom g, const bf16_t *__restrict__ x,
             if (ti < NT) {
                 const int r = ti / CT, ct = ti - r * CT;
                 const int t = r / ET, et = r - t * ET;
-                const int c = 16 * ct + l16;
+                const int c = 16 * ct + l16, e = 16 * et + 4 * q;
+                const int row = ((gi - GB) * 3 + t) * B::RG + (hl - B::HL0) * D + e;
+                float *dst = mine + (c < CG ? B::L_DWQ + row * CG + c : B::L_DBQ + row);
+                const int step = c < CG ? CG : 1;
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int e = 16 * et + 4 * q + j;
-                    if (e < D) {
-                        const int row = ((gi - GB) * 3 + t) * B::RG + (hl - B::HL0) * D + e;
-                        const float v = t == 0 ? dwacc[hx][k][j] * scale : dwacc[hx][k][j];
-                        if (c < CG) mine[B::L_DWQ + row * CG + c] = v;
-                        else if (c == CG) mine[B::L_DBQ + row] = v;
-                    }
-                }
+                for (int j = 0; j < 4; ++j)
+                    if (e + j < D && c <= CG) dst[j * step] = t == 0 ? dwacc[hx][k][j] * scale : dwacc[hx][k][j];
             }
         }
     }
     // bias-table gradient: (query, key) accumulators -> table entries, summed in a fixed order
-    float *mat = reinterpret_cast<float *>(lds + B::OFF_P); // [64 queries][64 keys] of one head, rows 65 floats
-                                                            // apart (the 16 query rows a store touches then
-                                                            // fall on different banks)
-    constexpr int MP = 65;
-    static_assert((size_t)64 * MP * 4 <= 2 * B::SZ_SQ, "table flush aliases P and dS");
+    // [head][64 queries][64 keys], as many heads at a time as LDS takes; rows 65 floats apart (the 16 query rows a
+    // store touches then fall on different banks)
+    constexpr int MP = 65, SQ = 64 * MP;
+    constexpr int HP = (int)(B::LDS_BYTES / (4 * SQ)) < NH ? (int)(B::LDS_BYTES / (4 * SQ)) : NH;
+    static_assert(HP > 0, "the table flush takes LDS over");
+    float *mats = reinterpret_cast<float *>(lds);
 #pragma unroll
-    for (int hx = 0; hx < NH; ++hx) {
+    for (int h0 = 0; h0 < NH; h0 += HP) {
         __syncthreads();
 #pragma unroll
-        for (int kt = 0; kt < 4; ++kt)
+        for (int hx = h0; hx < h0 + HP && hx < NH; ++hx)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) mat[(16 * wv + l16) * MP + 16 * kt + 4 * q + j] = tblacc[hx][kt][j];
+            for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) mats[(hx - h0) * SQ + (16 * wv + l16) * MP + 16 * kt + 4 * q + j] = tblacc[hx][kt][j];
         __syncthreads();
-        {
+#pragma unroll
+        for (int hx = h0; hx < h0 + HP && hx < NH; ++hx) {
+            const float *mat = mats + (hx - h0) * SQ;
             // Four threads share the offsets (dr0, dc0), (dr0 - M, dc0), (dr0, dc0 - M), (dr0 - M, dc0 - M)
             // with 0 <= dr0, dc0 < M: for every query (rn, cn) exactly one of the four has its key
             // inside the window, key = ((rn - dr0) mod M, (cn - dc0) mod M), so the four entries take
