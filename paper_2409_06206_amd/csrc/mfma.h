@@ -189,4 +189,29 @@ template <int N, class F> __device__ __forceinline__ void static_for(F &&f)
     static_for_impl(static_cast<F &&>(f), std::make_integer_sequence<int, N>{});
 }
 
+// Channels [c, c + 8) of a row of N channels, read in one piece from where it ends with the row at the latest: nothing
+// outside the row is touched.  piece4 moves what was read too early into place and puts zeros behind the row's end
+// (first: the slot of quad 0; eight channels a quad).
+struct __attribute__((packed, aligned(4))) Piece4 { uint32_t v[4]; };
+template <int N> __device__ __forceinline__ uint4 load_piece4(const bf16_t *row, int c)
+{
+    static_assert(N >= 8 && N % 2 == 0, "whole pieces");
+    const Piece4 p = *reinterpret_cast<const Piece4 *>(row + (c < N - 8 ? c : N - 8));
+    return make_uint4(p.v[0], p.v[1], p.v[2], p.v[3]);
+}
+template <int N> __device__ __forceinline__ uint4 piece4(uint4 p, int first, int q)
+{
+    const int n = N - first; // channels from quad 0's first on; quad n / 8 holds the last n % 8 of them
+    if (n >= 32) return p;
+    const uint32_t w[4] = {p.x, p.y, p.z, p.w};
+    uint32_t o[4];
+    const int part = n / 8, sh = n % 8 == 0 ? 4 : 4 - n % 8 / 2;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        o[i] = q < part ? w[i] : 0u;
+        if (i + sh < 4) o[i] = q == part ? w[i + sh < 4 ? i + sh : 0] : o[i];
+    }
+    return make_uint4(o[0], o[1], o[2], o[3]);
+}
+
 } // namespace gswa

@@ -1183,35 +1183,29 @@ __global__ __launch_bounds__(512, 1) void wgrad_stream_kernel(long rows, WgradSt
 #pragma unroll
         for (int c = 0; c < CW; ++c) acc[r][c] = zero4;
 
+    // The rows of the next pass are on their way while this one's are computed with.  They are taken as loaded, from a
+    // valid row; the row's end and rows past the last count as zero where they are used (a select behind the load is a
+    // wait behind the load; whole layer of one group, 16 images of 64x64, fwd + bwd: 566.5 -> 553.0 us).
+    uint4 gn[KSN], an[KSK];
+    auto load_rows = [&](long tile) {
+        const long tok = tile * P::TOK + 16 * wv + l16, row = tok < rows ? tok : 0;
+#pragma unroll
+        for (int ks = 0; ks < KSN; ++ks) gn[ks] = load_piece4<NB>(dout + row * lddout, 32 * ks + 8 * q);
+#pragma unroll
+        for (int ks = 0; ks < KSK; ++ks) an[ks] = load_piece4<KB>(a + row * lda, 32 * ks + 8 * q);
+    };
+
     const long ntile = (rows + P::TOK - 1) / P::TOK;
+    if ((long)blockIdx.x < ntile) load_rows(blockIdx.x);
     for (long tile = blockIdx.x; tile < ntile; tile += gridDim.x) {
-        // this lane's token of the pass as operands: features 32 ks + 8 q .. + 7 of its row (a valid row is
-        // read unconditionally so that the dwords merge into wide loads; rows past the end count as zero)
-        const long tok = tile * P::TOK + 16 * wv + l16;
-        const bool ok = tok < rows;
-        const uint32_t *grow = reinterpret_cast<const uint32_t *>(dout + (ok ? tok : 0) * lddout);
-        const uint32_t *arow = reinterpret_cast<const uint32_t *>(a + (ok ? tok : 0) * lda);
+        // this lane's token of the pass as operands: features 32 ks + 8 q .. + 7 of its row
+        const bool ok = tile * P::TOK + 16 * wv + l16 < rows;
         uint4 gf[KSN], af[KSK];
 #pragma unroll
-        for (int ks = 0; ks < KSN; ++ks) {
-            uint32_t v[4];
+        for (int ks = 0; ks < KSN; ++ks) gf[ks] = ok ? piece4<NB>(gn[ks], 32 * ks, q) : make_uint4(0u, 0u, 0u, 0u);
 #pragma unroll
-            for (int dw = 0; dw < 4; ++dw) {
-                const int c = 32 * ks + 8 * q + 2 * dw;
-                v[dw] = c < NB ? grow[c >> 1] : 0u;
-            }
-            gf[ks] = ok ? make_uint4(v[0], v[1], v[2], v[3]) : make_uint4(0u, 0u, 0u, 0u);
-        }
-#pragma unroll
-        for (int ks = 0; ks < KSK; ++ks) {
-            uint32_t v[4];
-#pragma unroll
-            for (int dw = 0; dw < 4; ++dw) {
-                const int c = 32 * ks + 8 * q + 2 * dw;
-                v[dw] = c < KB ? arow[c >> 1] : 0u;
-            }
-            af[ks] = ok ? make_uint4(v[0], v[1], v[2], v[3]) : make_uint4(0u, 0u, 0u, 0u);
-        }
+        for (int ks = 0; ks < KSK; ++ks) af[ks] = ok ? piece4<KB>(an[ks], 32 * ks, q) : make_uint4(0u, 0u, 0u, 0u);
+        if (tile + (long)gridDim.x < ntile) load_rows(tile + gridDim.x);
         __syncthreads(); // the previous pass's rows are consumed
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {

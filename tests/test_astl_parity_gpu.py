@@ -122,6 +122,15 @@ def test_wide_layer_with_enough_tokens_for_the_streaming_weight_gradients(case):
     assert names["fc_wgrad"][1] == 1 and "fill_zero" not in names, names
 
 
+@pytest.mark.parametrize("groups", [1, 2])
+@pytest.mark.parametrize("H,W", [(40, 104), (136, 248)])
+def test_weight_gradients_of_a_last_pass_half_full(groups, H, W):
+    """65 and 527 windows of 64 tokens: the weight-gradient kernels take 128 tokens a pass, the last one's second half lies
+    past the last row (one group: both streaming gradients; two: the projection's); 527 also wraps the grid's rounds."""
+    print("case", groups, H, W, flush=True)
+    parity.check_block(astl_oracle, B=1, H=H, W=W, C=180, heads=6, groups=groups, window=8, shift=4, dtype="bf16", hidden=360)
+
+
 def test_wide_layer_with_few_tokens_keeps_the_gradient_copies():
     """2048 tokens: too few rows for the streaming weight-gradient kernel (it takes 4096 and more); the layer
     takes the kernels that add into 16 gradient copies (and still the streaming MLP kernels)."""
