@@ -27,11 +27,11 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0
 # the launch kinds of that kernel), valid only for the kernel source they were taken on:
 # {(workload, groups, kernel): (source file, sha256 of it, bytes per launch)}
 MEASURED_TRAFFIC = {
-    ("c4", 2, "wide_attn_bwd"): ("wide_bwd.hip", "9049b09287411286713757e150239f25eb4b0fc83b84015ac04c6c9f78170307", 229576312),
-    ("c3", 2, "wide_attn_bwd"): ("wide_bwd.hip", "9049b09287411286713757e150239f25eb4b0fc83b84015ac04c6c9f78170307", 116065640),
-    ("c2", 2, "fused_bwd"): ("fused_bwd.hip", "8aefb5890a71d6f6e8172a7992c221f0116de8d79eace3ae9662cfa534bd9b74", 74163908),
-    ("c5_m8", 2, "fused_fwd"): ("wide_fwd.hip", "2741dc20c76eea55b1b9254b569d5d7423fdfab82ee26444cc861f11740d1a99", 225001912),
-    ("c5_m16", 2, "fused_attn_fwd"): ("fused_fwd.hip", "fb20eb1f46acd89fc3898bd81bb6dcaaef9a8566d74eb9b3c773e5ab64968f98", 181130520),
+    ("c4", 2, "wide_attn_bwd"): ("wide_bwd.hip", "02d8cb1da0d072cd7c18004c5636e7947c841336354a7e72cca5488f4241a903", 229522842),
+    ("c3", 2, "wide_attn_bwd"): ("wide_bwd.hip", "02d8cb1da0d072cd7c18004c5636e7947c841336354a7e72cca5488f4241a903", 115178291),
+    ("c2", 2, "fused_bwd"): ("fused_bwd.hip", "045736001555f81e0501be67670f7af0f1ac71b801671cb1e812f83f53afcbf1", 74098790),
+    ("c5_m8", 2, "fused_fwd"): ("wide_fwd.hip", "b5f1b4eadff08b11b6d6efec42c205fd7c4ddfc20244cb89fd60ebece554519b", 238839398),
+    ("c5_m16", 2, "fused_fwd"): ("wide_fwd.hip", "b5f1b4eadff08b11b6d6efec42c205fd7c4ddfc20244cb89fd60ebece554519b", 240262861),
 }
 
 
