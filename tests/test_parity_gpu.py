@@ -96,6 +96,23 @@ def test_accumulate_flag_on_wide_fused_path(oracle, groups):
         assert parity.rel_err(got[k] - 0.5, 2.0 * want[k]) <= parity.TOL["bf16"], k
 
 
+@pytest.mark.parametrize("C,heads,dqk,window", [
+    (180, 6, 0, 8),   # 30 channels: the last four of a head's two tiles half full
+    (36, 2, 0, 8),    # 18: one pair behind a whole tile
+    (64, 2, 0, 8),    # 32: no remainder
+    (34, 2, 0, 8),    # 17: heads that begin between two dwords
+    (60, 2, 18, 12),  # 30 and 18, 12x12 windows
+    (60, 2, 5, 8),    # 30, and five channels of q and k
+])
+def test_attention_adjoint_by_pairs_of_channels(oracle, C, heads, dqk, window):
+    """The attention adjoint of the one-kernel-per-step path takes the channels of a head in pairs where heads and rows
+    begin on a dword, one by one where they do not."""
+    from paper_2409_06206_amd import gswa
+    print("case", C, heads, dqk, window, flush=True)
+    parity.check_case(oracle, 2, 2 * window, 3 * window, C, heads, 1, window, 3, "bf16", regime="stress", dqk=dqk,
+                      extra_flags=gswa.GSWA_FORCE_STAGED)
+
+
 @pytest.mark.parametrize("groups", [1, 2, 3])
 @pytest.mark.parametrize("B,H,W,window,shift", [
     (1, 8, 8, 8, 4),         # one window: three of four window slots of the workgroup empty
