@@ -547,7 +547,8 @@ __device__ __forceinline__ f32x4 widen4(uint2 u) { return f32x4{bf16_lo(u.x), bf
 // ---------------------------------------------------------------------------------------
 // The same forward with a window in four waves, and around it, for whole layers, LN_1, the skips, LN_2 and the MLP.
 // A wave keeps its 16 tokens from x to y in registers (119 to 126 of them: four waves per SIMD); K and V of the heads of a
-// group cross the window's waves through LDS as the operands they are read as, two barriers per group.  The projection's
+// batch (a group, or one head of a group of six) cross the window's waves through LDS as the operands they are read as, one
+// barrier between writing and reading them and one before the next batch, of this window or the next, is written.  The projection's
 // result tiles are the rows LN_2 and the MLP take (channels 16 ct + 4q .. of token l16, as in astl_mlp.hip), so the whole
 // second half of the layer needs no exchange.  With few windows the time is this chain of steps; six layers on a 72x88 map
 // (99 windows) went from 172 to 84 us (24 launches of packing, attention layer and MLP half to 8), six on 512x512 from 518
@@ -853,7 +854,8 @@ __global__ __launch_bounds__(1024) void wave4_fwd_kernel(Geom g, const bf16_t *_
                     }
                 }
             }
-            if (h0 + HB < HEADS) __syncthreads(); // (K and V are read before the next heads' are written)
+            // K and V are read before the next heads' are written, the next window's first heads among them
+            if (h0 + HB < HEADS || round + 1 < rounds) __syncthreads();
         };
         // (one group: as constants; left to the loop's unrolling some of the registers end up in memory)
         if constexpr (HG == 6) {

@@ -459,7 +459,7 @@ def test_band_by_band_inference_is_the_whole_map_inference(case, bands):
 @pytest.mark.parametrize("groups,hidden,shift", [(1, 120, 4), (2, 128, 3), (3, 68, 4), (6, 120, 7)])
 def test_narrow_layers_of_a_sequence_in_one_launch(groups, hidden, shift):
     """Narrow layers of a sequence: one launch a layer and one each for all weights of both halves; the same bits for an
-    image alone, in a batch that takes several rounds, band by band (in place) and with the state kept."""
+    image alone, first of a batch, band by band (in place) and with the state kept."""
     import torch
     from paper_2409_06206_amd import runner
     B, H, W, L = 41, 40, 48, 3
@@ -496,6 +496,41 @@ def test_narrow_layers_of_a_sequence_in_one_launch(groups, hidden, shift):
         assert torch.equal(st.y, alone)
         grads.append(st.dx.clone())
     assert torch.equal(*grads)
+
+
+@pytest.mark.parametrize("groups", [1, 2, 3, 6])
+def test_narrow_layers_of_a_sequence_in_several_rounds(groups):
+    """More windows than the workgroups of the one-launch layer hold at once (four each, one workgroup per compute unit):
+    every image of the batch, those of the second and third round among them, has the bits it has alone, in
+    inference and with the state kept, and so has its gradient."""
+    import torch
+    from paper_2409_06206_amd import runner
+    H, W, L, hidden = 40, 48, 3, 120
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    B = 8 * cus // 30 + 2  # images of 30 windows
+    ps = [{k: synth.quantize(v, "bf16") for k, v in synth.astl_params(60, 6, groups, 8, hidden, 500 + l, "stress").items()}
+          for l in range(L)]
+    x, dy = (synth.quantize(a, "bf16") for a in synth.activations(B, H, W, 60, 1))
+
+    def stack(n):
+        st = runner.DeviceStack(n, H, W, 60, 6, groups, 8, 4, "bf16", hidden, L)
+        st.set_params(ps)
+        return st
+    many, one = stack(B), stack(1)
+    many.set_inputs(x, dy)
+    many.forward(keep=False)
+    y = many.y.clone()
+    many.y.fill_(float("nan"))
+    many.forward(keep=True)
+    many.backward()
+    torch.cuda.synchronize()
+    for i in range(B):
+        one.set_inputs(x[i:i + 1], dy[i:i + 1])
+        one.forward(keep=True)
+        one.backward()
+        torch.cuda.synchronize()
+        assert torch.equal(y[i], one.y[0]) and torch.equal(many.y[i], one.y[0]), i
+        assert torch.equal(many.dx[i], one.dx[0]), i
 
 
 @pytest.mark.parametrize("groups,window,shift", [(1, 8, 4), (2, 8, 3), (3, 16, 8)])
