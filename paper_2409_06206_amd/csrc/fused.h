@@ -105,7 +105,8 @@ struct FusedLn {
     float eps = 0.f;
 };
 
-// Parameters of several layers of one shape repacked by one launch.
+// Parameters of several layers of one shape repacked by one launch (of `g` only the shape of the layer counts, not the
+// size of the map).
 struct FusedPackJob {
     const bf16_t *w_qkv, *b_qkv, *w_proj, *b_proj, *table;
     uint8_t *pack;

@@ -27,17 +27,26 @@ __device__ __forceinline__ uint32_t bf16_scaled(bf16_t w, float sc)
     return sc == 1.0f ? (uint32_t)w.bits : (uint32_t)f32_to_bf16_bits(to_f32(w) * sc);
 }
 
+// All layouts of a shape are written whatever the size of the map, so that weights packed once serve maps and bands of
+// any size.
+template <class Cf> struct PackGrid {
+    static constexpr int ENTRIES =
+        (Cf::N_WQH + Cf::N_WP2 + Cf::N_BF + Cf::N_WQ + Cf::N_WPT + Cf::N_WQT + Cf::N_WPK) * 64 + 4 * Cf::C;
+    static constexpr int WIDE_ENTRIES =
+        Cf::SPLIT ? (Cf::N_WQW + Cf::N_WPW + Cf::N_WQX + Cf::N_WQN) * 64 + Cf::HEADS * Cf::TBW_PITCH : 0;
+    static constexpr int WIDE_FIRST = (ENTRIES + 255) / 256; // first block of the wide one-launch kernels' layouts
+    static constexpr int BLOCKS = WIDE_FIRST + (WIDE_ENTRIES + 255) / 256;
+};
 template <class Cf>
-__global__ __launch_bounds__(256) void pack_params_kernel(FusedPackJobs jobs, int wide_first)
+__global__ __launch_bounds__(256) void pack_params_kernel(FusedPackJobs jobs)
 {
     const FusedPackJob &job = jobs.j[blockIdx.y];
     const bf16_t *__restrict__ w_qkv = job.w_qkv, *__restrict__ b_qkv = job.b_qkv, *__restrict__ w_proj = job.w_proj,
                  *__restrict__ b_proj = job.b_proj, *__restrict__ table = job.table;
     uint8_t *__restrict__ pack = job.pack;
-    // blocks from wide_first on (if not negative): the layouts of the wide one-launch kernels, same launch
     if constexpr (Cf::SPLIT) {
-        if (wide_first >= 0 && (int)blockIdx.x >= wide_first) {
-            wide_pack_entry<Cf>(((int)blockIdx.x - wide_first) * 256 + (int)threadIdx.x, w_qkv, w_proj, table, pack);
+        if ((int)blockIdx.x >= PackGrid<Cf>::WIDE_FIRST) {
+            wide_pack_entry<Cf>(((int)blockIdx.x - PackGrid<Cf>::WIDE_FIRST) * 256 + (int)threadIdx.x, w_qkv, w_proj, table, pack);
             return;
         }
     }
@@ -1248,19 +1257,13 @@ hipError_t launch_attn_chunks(const Geom &g, const bf16_t *x, const uint8_t *pac
     return hipSuccess;
 }
 
-template <class Cf> hipError_t run_pack(const Geom &g, const FusedPackJob *jobs, int n, hipStream_t s)
+template <class Cf> hipError_t run_pack(const FusedPackJob *jobs, int n, hipStream_t s)
 {
-    constexpr int entries =
-        (Cf::N_WQH + Cf::N_WP2 + Cf::N_BF + Cf::N_WQ + Cf::N_WPT + Cf::N_WQT + Cf::N_WPK) * 64 + 4 * Cf::C;
-    constexpr int wide_entries = (Cf::N_WQW + Cf::N_WPW + Cf::N_WQX + Cf::N_WQN) * 64 + Cf::HEADS * Cf::TBW_PITCH;
-    const int blocks = (entries + 255) / 256;
-    const bool wide = Cf::SPLIT && wide_fwd_supported(g);
     if (n < 1 || n > kMaxFusedPackJobs) return hipErrorInvalidValue;
     FusedPackJobs a{};
     for (int i = 0; i < n; ++i) a.j[i] = jobs[i];
     KernelTimer kt(K_PACK_FWD, s);
-    hipLaunchKernelGGL(pack_params_kernel<Cf>, dim3(blocks + (wide ? (wide_entries + 255) / 256 : 0), n), dim3(256), 0, s, a,
-                       wide ? blocks : -1);
+    hipLaunchKernelGGL(pack_params_kernel<Cf>, dim3(PackGrid<Cf>::BLOCKS, n), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
@@ -1277,7 +1280,7 @@ hipError_t run_fwd(const Geom &g, const bf16_t *x, const bf16_t *w_qkv, const bf
     hipError_t e = hipSuccess;
     if (!packed) {
         const FusedPackJob job = {w_qkv, b_qkv, w_proj, b_proj, table, pack};
-        e = run_pack<Cf>(g, &job, 1, s);
+        e = run_pack<Cf>(&job, 1, s);
     }
     if (e != hipSuccess) return e;
     if constexpr (Cf::SPLIT) {
@@ -1366,7 +1369,7 @@ size_t fused_pack_bytes(const Geom &g)
 hipError_t launch_fused_pack(const Geom &g, const FusedPackJob *jobs, int n, hipStream_t s)
 {
 #define X(C_, H_, G_) \
-    if (g.C == C_ && g.heads == H_ && g.groups == G_) return run_pack<FusedCfg<C_, H_, G_>>(g, jobs, n, s);
+    if (g.C == C_ && g.heads == H_ && g.groups == G_) return run_pack<FusedCfg<C_, H_, G_>>(jobs, n, s);
     GSWA_FUSED_SHAPES(X)
 #undef X
     return hipErrorInvalidValue;

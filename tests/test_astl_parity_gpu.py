@@ -533,6 +533,37 @@ def test_narrow_layers_of_a_sequence_in_several_rounds(groups):
         assert torch.equal(many.dx[i], one.dx[0]), i
 
 
+@pytest.mark.parametrize("C,groups,window,images", [(180, 2, 8, 8), (180, 1, 16, 8), (60, 2, 8, 24)])
+def test_band_by_band_inference_of_more_than_2_31_elements(C, groups, window, images):
+    """Bands are small whatever the input: a batch of 2^31 elements and more gives every image the bits it has alone
+    (the kernels that serve a whole map of that size are others, and read the weights repacked in another order)."""
+    import torch
+    from paper_2409_06206_amd import runner
+    H, W, L = 1008, 1504, 2
+    assert images * H * W * C >= 1 << 31
+    print("case", C, groups, window, images, flush=True)
+    ps = [{k: synth.quantize(v, "bf16") for k, v in synth.astl_params(C, 6, groups, window, 2 * C, 500 + l, "stress").items()}
+          for l in range(L)]
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(1)
+    x = torch.randn((images, H, W, C), generator=gen, device="cuda:0", dtype=torch.bfloat16)
+
+    def stack(n):
+        st = runner.DeviceStack(n, H, W, C, 6, groups, window, window // 2, "bf16", 2 * C, L, band_windows=16, inference_only=True)
+        st.set_params(ps)
+        st.ws.fill_(255)  # (NaN where nothing is written)
+        return st
+    many, one = stack(images), stack(1)
+    many.x = x
+    many.forward(keep=False)
+    for i in range(images):
+        one.x = x[i:i + 1]
+        one.forward(keep=False)
+        torch.cuda.synchronize()
+        finite, same = bool(torch.isfinite(one.y).all()), torch.equal(many.y[i], one.y[0])
+        assert finite and same, i
+
+
 @pytest.mark.parametrize("groups,window,shift", [(1, 8, 4), (2, 8, 3), (3, 16, 8)])
 def test_wide_layers_take_ln1_in_the_attention_kernel(groups, window, shift):
     """Wide layers with the streaming MLP kernels: no launch of LN_1, so that a sequence gives the bits of the banded
