@@ -1117,6 +1117,7 @@ struct TiledPlan {
     int nb;          // window rows per band
     int M, nwi;
     Plan pl;         // of a whole band of an unshifted layer
+    bool one_kind;   // every band is served by the same kernels: one place and layout of repacked weights fits all of them
     size_t min_act;  // bytes of the smallest band that occurs
     size_t band_act; // bytes of the largest band, [rows, W, C] (256-aligned)
     size_t layer_ws; // scratch of one layer call on the largest band (inference form)
@@ -1138,7 +1139,7 @@ int make_tiled_plan(const astl_stack_desc *d, int band_windows, TiledPlan *tp)
     const int kinds[3] = {tp->nb, tp->nb < tp->nwi ? tp->nb + 1 : tp->nb, rem ? rem : tp->nb};
     tp->band_act = tp->layer_ws = 0;
     tp->min_act = ~size_t(0);
-    tp->direct = true;
+    tp->direct = tp->one_kind = true;
     for (int k = 0; k < 3; ++k)
         for (int odd = 0; odd < 2; ++odd) {
             astl_desc sd = odd ? tp->sp.odd : tp->sp.even;
@@ -1150,6 +1151,10 @@ int make_tiled_plan(const astl_stack_desc *d, int band_windows, TiledPlan *tp)
             if (pl.act > tp->band_act) tp->band_act = pl.act;
             if (pl.act < tp->min_act) tp->min_act = pl.act;
             if (k == 0 && !odd) tp->pl = pl;
+            // (the one-launch kernels take up to 2^31 elements: a whole band may hold fewer, one with the dropped row more)
+            if (pl.wave_layer != tp->pl.wave_layer || pl.attn_ln != tp->pl.attn_ln || pl.attn_pack != tp->pl.attn_pack ||
+                pl.pack != tp->pl.pack)
+                tp->one_kind = false;
             if (pl.window || !(pl.fused_mlp || pl.wide_mlp)) tp->direct = false;
             if (pl.fwd_ws + pl.saved > tp->layer_ws) tp->layer_ws = pl.fwd_ws + pl.saved;
         }
@@ -1197,7 +1202,7 @@ int astl_stack_forward_tiled(const astl_stack_desc *desc, const void *x, const a
     const char *cur = static_cast<const char *>(x);
     char *out = static_cast<char *>(y);
     SequencePacks packs;
-    packs.plan(tp.pl, layer_ws, tp.pl.wave_layer ? tp.layer_ws : tp.min_act);
+    if (tp.one_kind) packs.plan(tp.pl, layer_ws, tp.pl.wave_layer ? tp.layer_ws : tp.min_act); // (else band by band, below)
     for (int l = 0; l < tp.sp.L; ++l) {
         const astl_desc *ld = (l & 1) ? &tp.sp.odd : &tp.sp.even;
         ASTL_RC(packs.ready(ld, tp.pl, params, l, tp.sp.L, [](int) -> char * { return nullptr; }, st));

@@ -564,6 +564,34 @@ def test_band_by_band_inference_of_more_than_2_31_elements(C, groups, window, im
         assert finite and same, i
 
 
+@pytest.mark.parametrize("C,W", [(180, 93200), (60, 279616)])
+def test_bands_on_both_sides_of_2_31_elements(C, W):
+    """Bands of 16 window rows just below 2^31 elements and, in the shifted layer, of 17 rows above: other kernels
+    serve them, and neither kind's scratch may lie over the weights the other repacked.  Against bands of four
+    rows, at the tolerance of two organisations of the same layers."""
+    import torch
+    from paper_2409_06206_amd import runner
+    H, L = 264, 3
+    assert 16 * 8 * W * C < 1 << 31 <= 17 * 8 * W * C
+    print("case", C, W, flush=True)
+    ps = [{k: synth.quantize(v, "bf16") for k, v in synth.astl_params(C, 6, 2, 8, 2 * C, 500 + l, "stress").items()}
+          for l in range(L)]
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(1)
+    st = runner.DeviceStack(1, H, W, C, 6, 2, 8, 4, "bf16", 2 * C, L, band_windows=16, inference_only=True)
+    st.set_params(ps)
+    st.x = torch.randn((1, H, W, C), generator=gen, device="cuda:0", dtype=torch.bfloat16)
+    st.ws.fill_(255)  # (NaN where nothing is written)
+    st.forward(keep=False)
+    got = st.y.clone()
+    st.forward_tiled(4)
+    torch.cuda.synchronize()
+    for r in range(0, H, 8):
+        a, b = got[0, r:r + 8].float(), st.y[0, r:r + 8].float()
+        err = float((a - b).abs().max() / b.abs().max())
+        assert err <= 2e-2, (r, err)
+
+
 @pytest.mark.parametrize("groups,window,shift", [(1, 8, 4), (2, 8, 3), (3, 16, 8)])
 def test_wide_layers_take_ln1_in_the_attention_kernel(groups, window, shift):
     """Wide layers with the streaming MLP kernels: no launch of LN_1, so that a sequence gives the bits of the banded
