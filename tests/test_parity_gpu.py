@@ -158,6 +158,45 @@ def test_wide_forward_gives_an_image_the_same_bits_alone_and_in_a_batch(groups):
     assert np.array_equal(*y)
 
 
+@pytest.mark.parametrize("groups", [1, 2, 3])
+@pytest.mark.parametrize("window,shift", [(8, 4), (8, 0), (16, 8), (16, 3)])
+def test_wide_forward_of_2_31_elements_and_more(window, shift, groups):
+    """The one-launch forward of wide layers addresses fewer than 2^31 elements; larger inputs take one launch per head
+    chunk and one of the projection.  Every image against itself alone, which the one-launch kernel computes, at the
+    tolerance of two organisations of the same layer; with and without the group outputs kept."""
+    import torch
+    from paper_2409_06206_amd import gswa, runner
+    B, H, W, C = 8, 1008, 1504, 180
+    assert (B - 1) * H * W * C < 1 << 31 <= B * H * W * C
+    print("case", window, shift, groups, flush=True)
+    _, _, p = parity.make_inputs(1, window, window, C, 6, groups, window, "bf16", synth.LAYER_SEED0 + 7, "stress")
+    one = runner.DeviceLayer(1, H, W, C, 6, groups, window, shift, "bf16")
+    one.set_params(p)
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(1)
+    x = torch.randn((B, H, W, C), generator=gen, device="cuda:0", dtype=torch.bfloat16)
+    desc = gswa.make_desc(B, H, W, C, 6, groups, window, shift, "bf16")
+    saved_bytes, fwd_bytes, _ = gswa.gswa_query_bytes(desc)
+    ws = torch.full((fwd_bytes + saved_bytes,), 255, dtype=torch.uint8, device="cuda:0")  # (NaN where nothing is written)
+    args = [one.params[k] for k in ("w_qkv", "b_qkv", "w_proj", "b_proj", "table")]
+    y = []
+    for saved in (None, torch.empty(saved_bytes, dtype=torch.uint8, device="cuda:0")):
+        y.append(torch.full_like(x, float("nan")))
+        with parity.launched() as names:
+            gswa.gswa_forward(desc, x, *args, y[-1], saved, ws)
+        assert names == {"pack_fwd", "fused_attn_fwd", "proj_gemm"}
+    assert torch.equal(*y)
+    for i in range(B):
+        one.x = x[i:i + 1]
+        with parity.launched() as names:
+            one.forward(keep=False)
+        assert names == {"pack_fwd", "fused_fwd"}
+        want, top = one.y[0], float(one.y.abs().max())
+        for r in range(0, H, 16):
+            err = float((y[0][i, r:r + 16].float() - want[r:r + 16].float()).abs().max()) / top
+            assert err <= parity.TOL["bf16"], (i, r, err)
+
+
 @pytest.mark.parametrize("groups", [1, 2, 3, 6])
 @pytest.mark.parametrize("shift", [0, 3])
 def test_narrow_forward_in_four_waves_and_in_one(oracle, groups, shift):
