@@ -27,11 +27,11 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0
 # the launch kinds of that kernel), valid only for the kernel source they were taken on:
 # {(workload, groups, kernel): (source file, sha256 of it, bytes per launch)}
 MEASURED_TRAFFIC = {
-    ("c4", 2, "wide_attn_bwd"): ("wide_bwd.hip", "02d8cb1da0d072cd7c18004c5636e7947c841336354a7e72cca5488f4241a903", 229522842),
-    ("c3", 2, "wide_attn_bwd"): ("wide_bwd.hip", "02d8cb1da0d072cd7c18004c5636e7947c841336354a7e72cca5488f4241a903", 115178291),
+    ("c4", 2, "wide_attn_bwd"): ("wide_bwd.hip", "352693d517081ee0c33c35060cc3f2ac5a2649ebcfd12444c2cc316d892ad1e2", 229522842),
+    ("c3", 2, "wide_attn_bwd"): ("wide_bwd.hip", "352693d517081ee0c33c35060cc3f2ac5a2649ebcfd12444c2cc316d892ad1e2", 115178291),
     ("c2", 2, "fused_bwd"): ("fused_bwd.hip", "045736001555f81e0501be67670f7af0f1ac71b801671cb1e812f83f53afcbf1", 74098790),
-    ("c5_m8", 2, "fused_fwd"): ("wide_fwd.hip", "b5f1b4eadff08b11b6d6efec42c205fd7c4ddfc20244cb89fd60ebece554519b", 238839398),
-    ("c5_m16", 2, "fused_fwd"): ("wide_fwd.hip", "b5f1b4eadff08b11b6d6efec42c205fd7c4ddfc20244cb89fd60ebece554519b", 240262861),
+    ("c5_m8", 2, "fused_fwd"): ("wide_fwd.hip", "98163ed852681e2c18862150cd6b51ab1f4d47b54d1aeb9a3572bef3389a5f4b", 238839398),
+    ("c5_m16", 2, "fused_fwd"): ("wide_fwd.hip", "98163ed852681e2c18862150cd6b51ab1f4d47b54d1aeb9a3572bef3389a5f4b", 240262861),
 }
 
 

@@ -130,8 +130,11 @@ int astl_stack_forward(const astl_stack_desc *desc, const void *x, const astl_pa
  * window grid, one image at a time.  A band of a shifted layer that does not reach the map's last window
  * row is a contiguous run of image rows and needs only the column part of the shift mask; the band that
  * ends the map also takes the map's first `shift` rows.  The result has the same bits for every
- * band_windows.  From astl_stack_forward's it differs by roundings: that call takes LayerNorm 1 of a layer
- * inside the MLP kernel of the layer before, where there is one (bf16), which sums a row in another order.
+ * band_windows (as long as a band of band_windows + 1 rows holds fewer than 2^31 elements; larger ones run other
+ * kernels).  They are astl_stack_forward's where a layer's attention or window kernel takes LayerNorm 1 itself (the
+ * bf16 layers of 60 and 180 channels with 8x8 or 16x16 windows and the layers of one workgroup per window); other
+ * results differ from that call's by roundings: it takes LayerNorm 1 of a layer inside the MLP kernel of the layer
+ * before, where there is one (bf16), which sums a row in another order.
  *
  * x [B,H,W,C] is read only; y [B,H,W,C] receives layer 0's output and is then updated in place by the
  * later layers; x and y must not overlap.  ws: *ws_bytes of astl_stack_tiled_query_bytes, 256-byte

@@ -835,7 +835,9 @@ int backward_t(const astl_desc *d, const Plan &pl, const T *x, const T *dy, cons
         ASTL_HIP(launch_ln_bwd<T>(n2, st));
     }
 
-    // Eq. 4 backwards: the attention layer on LN_1(x) (recomputed), then LN_1 and the skip
+    // Eq. 4 backwards: the attention layer on LN_1(x) (recomputed), then LN_1 and the skip.  (Where the forward took LN_1
+    // inside another kernel, that one sums a row in another order: about one element of LN_1(x) in 150000 is one bf16
+    // step from the forward's.)
     LnArgs l1{};
     l1.u = x; l1.gamma = p->ln1_w; l1.beta = p->ln1_b; l1.out = xn; l1.rows = rows; l1.C = C; l1.eps = d->eps;
     // (the fused MLP backward's final sum rides in the same launch)

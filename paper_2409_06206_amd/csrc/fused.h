@@ -1,12 +1,15 @@
 // Fused per-window GSWA kernels (bf16 storage, MFMA arithmetic).
 //
-// Activations stay in registers in MFMA operand / result layouts (see mfma.h).  Two ways of
+// Activations stay in registers in MFMA operand / result layouts (see mfma.h).  Three ways of
 // giving a window to the hardware are in use:
-//   * one wavefront per window (forward of narrow layers): the wave holds all 64 tokens as four
-//     16-token tiles, so nothing crosses waves and no barrier is needed after the set-up;
-//   * one workgroup per window, one wavefront per 16 tokens (split forward of wide layers, every
-//     fused backward): K and V of a head, and in the backward the transposed score gradients,
-//     cross waves through LDS.
+//   * one wavefront per window (forward of narrow layers with many windows, attention adjoint of wide layers): the wave
+//     holds all 64 tokens as four 16-token tiles, so nothing crosses waves and no barrier is needed for it;
+//   * a few wavefronts per window, several windows per workgroup (forward of narrow layers with few windows and of whole
+//     narrow layers: four waves of one tile; forward of wide layers: waves of one or two tiles, wide_fwd.hip): K and V of a
+//     head cross the window's waves through LDS, as the operands they are read as;
+//   * one workgroup per window, one wavefront per 16 tokens (backward of narrow layers; wide layers: backward with an odd
+//     shift, both passes of inputs of 2^31 elements and more): K and V of a head, and in the backward the transposed
+//     score gradients, cross waves through LDS.
 // The shift, the window partition and their inverses are the address computation of the
 // first load and the last store (Sec. "Patch Embedding", Sec. "Group Shifted Window Attention").
 #pragma once
@@ -32,9 +35,9 @@ namespace gswa {
 //   WP2  Wproj, K=32 steps over head pairs
 //   BF   relative-position bias times log2(e) as bf16 score-tile operands, one per head and
 //        key/query tile offset
-// Wide layers (C > 64) do not fit their weights in LDS at once: their forward runs per head
-// chunk (SPLIT), takes the cascade input from memory, and projects in a separate GEMM that
-// uses WPK; WQH, WP2 and BF are empty for them.
+// Wide layers (C > 64, SPLIT) do not fit their weights in LDS at once; WQH, WP2 and BF are empty for them.  Their forward
+// streams WQW and WPW (below) through LDS in one launch; from 2^31 elements on it runs per head chunk (WQ), takes the
+// cascade input from memory, and projects in a separate GEMM that uses WPK.
 template <int C_, int HEADS_, int G_> struct FusedCfg {
     static constexpr int C = C_, HEADS = HEADS_, G = G_;
     static constexpr int D = C / HEADS, CG = C / G, HG = HEADS / G;
@@ -60,14 +63,15 @@ template <int C_, int HEADS_, int G_> struct FusedCfg {
     static constexpr size_t P_WPT = P_BIAS + (size_t)16 * C;
     static constexpr size_t P_WQT = P_WPT + (size_t)N_WPT * 1024;
     static constexpr size_t P_WPK = P_WQT + (size_t)N_WQT * 512;
-    // Wide layers, forward with one wavefront per window (wide_fwd.hip): a head is 16*ET = 32
+    // Wide layers, forward in one launch (wide_fwd.hip): a head is 16*ET = 32
     // k-slots, so one K=32 step carries one head in "head-padded order": lane group q holds the
     // head's features 4q..4q+3 and 16+4q..16+4q+3 -- the rows of the two result tiles of a head
     // output, which makes a packed output tile pair the operand of the next product.
     //   WQW  Wqkv, input channels of the group in head-padded order, one K=32 step per input head:
     //        (hd, t, et, step); query rows carry log2(e)/sqrt(d)
     //   WPW  Wproj, one K=32 step per head: (ot, hd)
-    //   TBW  relative-position bias times log2(e), fp32, [head][TBW_PITCH]
+    //   TBW  relative-position bias times log2(e), fp32, [head][TBW_PITCH]; read by the attention adjoint (the
+    //        forward, which serves 16x16 windows too, fills its own from the table)
     static constexpr int KSX = CG / D;                            // input heads of a group = K=32 steps
     static constexpr int N_WQW = SPLIT ? HEADS * 3 * ET * KSX : 0;
     static constexpr int N_WPW = SPLIT ? OT * HEADS : 0;
@@ -95,8 +99,8 @@ bool fused_fwd_supported(const Geom &g);
 // Bytes of the packed parameters (both passes).
 size_t fused_pack_bytes(const Geom &g);
 
-// True when the forward of this geometry runs per head chunk and therefore always needs the
-// attn_out buffer (for inference the caller lends scratch).
+// True when the forward of this geometry may run per head chunk (wide layers, from 2^31 elements on) and is then handed the
+// attn_out buffer for inference too (the caller lends scratch; the one-launch kernel leaves it alone).
 bool fused_fwd_needs_attn(const Geom &g);
 
 // LayerNorm in front of the layer, taken in the forward kernel's read of x (w null: none).
@@ -227,8 +231,8 @@ __device__ __forceinline__ void wide_pack_entry(int i, const bf16_t *__restrict_
     }
 }
 
-// Wide layers (C = 180) with 8x8 or 16x16 windows: the whole forward in one launch, 32 tokens per
-// wavefront, the weights streamed through LDS (wide_fwd.hip).  `attn` receives the group outputs when
+// Wide layers (C = 180, fewer than 2^31 elements) with 8x8 or 16x16 windows: the whole forward in one launch, 16 or 32
+// tokens per wavefront, the weights streamed through LDS (wide_fwd.hip).  `attn` receives the group outputs when
 // `training` (the caller keeps them for the backward pass); otherwise it is not touched.
 // With `ln` the layer's input is LayerNorm(x) (rounded to bf16), taken of the rows as they are loaded.
 bool wide_fwd_supported(const Geom &g);

@@ -2,7 +2,7 @@
 // groups) through the attention and the QKV projection, group by group in reverse order (Eq. 8 hands
 // the gradient of a group's input to the output of the group before it).  Two launches per group:
 //
-// wide_attn_bwd_kernel: one wavefront per window, as in the forward (wide_fwd.hip): four waves per
+// wide_attn_bwd_kernel: one wavefront per window (the forward, wide_fwd.hip, has two): four waves per
 //   workgroup, one per SIMD, the weights streamed through LDS as equal units, double buffered, one
 //   workgroup barrier per unit.  Per window: dO of the group's heads = dy Wproj (adjoint of Eq. 7) plus
 //   the cascade gradient (the dx slice of the next group, already final); then per head q, k, v, the

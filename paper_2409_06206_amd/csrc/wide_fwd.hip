@@ -3,9 +3,8 @@
 // relative bias and shift mask + softmax + PV + output projection (Eq. 7) + merge + reverse shift.
 //
 // A wavefront owns two 16-token tiles: two waves share an 8x8 window, eight a 16x16 one (few 8x8 windows: one tile, four
-// waves).  x of all groups
-// and all head outputs of its tokens stay in its registers, so do its probabilities; K and V of a head cross
-// the waves of a window through LDS, already in the operand layout of the products that read them (one
+// waves).  x of all groups and all head outputs of its tokens stay in its registers, so do its probabilities; K and V of
+// a head cross the waves of a window through LDS, already in the operand layout of the products that read them (one
 // 16-byte write and read per lane and tile).  A workgroup is eight waves, two per SIMD (256 registers): one
 // wave's vector instructions run under the other's products, which one wave per SIMD with a whole window
 // (the organisation before, 512 registers) could not offer.  The weights of a wide layer (108 KB of QKV
@@ -14,12 +13,19 @@
 //
 // What bounds it: with 8x8 windows the steps between barriers, 1.4 to 2.2 k clocks of which 0.6 k are
 // products and 0.6 k the LDS reads of the fragments (each serves two tiles); with 16x16 windows the vector
-// instructions of the softmax.  Measured (one image of 512x512, two groups): 8x8 windows 121 -> 94 us a pass,
-// 16x16 windows 291 -> 150 us (there two attention launches and one of the projection before); one image of
-// 96x64 29.7 -> 20.2 us.  Taken one after the other at 8x8: two waves per window 130 -> 115 us, the next
-// window's rows loaded under the projection, a few per step (in one go they stall the wave for 8 k clocks
-// while memory serves the whole chip) and padded bias tables -> 111, windows of half the waves one step late
-// -> 100, operands of the next products read under the present ones -> 94.
+// instructions of the softmax.  Measured (one image of 512x512, two groups; a pass is the packing and this launch, passes
+// one after the other, both organisations in turn on one card): 8x8 windows 134.8 -> 97.7 us, 16x16 windows 305.6 -> 154.0
+// us (there two attention launches and one of the projection before); one image of 96x64 29.7 -> 20.2 us.  Steps at 8x8, as
+// they were taken, on another card: two waves per window 130 -> 115 us, the next window's rows loaded under the projection,
+// a few per step (in one go they stall the wave for 8 k clocks while memory serves the whole chip) and padded bias tables
+// -> 111, windows of half the waves one step late -> 100, operands of the next products read under the present ones -> 94.
+// The price is memory: 8x8 windows read 1.22 and write 1.31 times the map (1.12 and 1.26 with one wave per window), 239 MB
+// for 225.
+//
+// The softmax's denominator is the sum of the probabilities as they were rounded to bf16 for the PV product (fp32 sums;
+// row D of that product), and its reciprocal v_rcp_f32's; the organisation that 16x16 windows had before summed them
+// unrounded and divided.  Error of y against fp64 over three maps, one to three groups, 12 seeds: 0.5 to 1.2 % smaller
+// than that, or the same (64x64, two groups 3.904 -> 3.886e-3).
 //
 // Everything is kept with rows = features and column = token (T-form, see fused_bwd.hip), and a
 // head of 30 channels is two 16-row tiles, i.e. exactly the 32 k-slots of one K=32 MFMA step in
@@ -144,7 +150,7 @@ template <int Q0> __device__ __forceinline__ float qgroup_bcast(float v)
 
 // LayerNorm of the wave's rows, held as operands in head-padded order (xh[group][step][tile]; zero beyond a head's
 // D features), in place: a row is spread over the four lanes that share l16.  Mean first, then the squared distances
-// from it, result rounded to bf16, as the LayerNorm kernels do it.  gb: (gamma, beta) pairs [head][32], zero beyond D.
+// from it, result rounded to bf16, as the LayerNorm kernels do it (which sum a row in another order).  gb: (gamma, beta) pairs [head][32], zero beyond D.
 template <int G, int KSX, int TW, int C, int D>
 __device__ __forceinline__ void layer_norm_operands(uint4 (&xh)[G][KSX][TW], const float4 *gb, int q, float eps)
 {
