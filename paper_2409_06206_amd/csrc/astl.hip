@@ -533,8 +533,9 @@ struct SequencePacks {
         cap = fit < (size_t)kMaxPackJobs ? (int)fit : kMaxPackJobs;
         on = cap > 0;
     }
-    // before layer l (of L) runs; saved_of(l): its saved state (training)
-    template <class F> int ready(const astl_desc *d, const Plan &pl, const astl_params *params, int l, int L, F saved_of, hipStream_t st)
+    // before layer l (of L; `d`, `pl`: its call) runs in layer_ws; saved_of(l): its saved state (training)
+    template <class F>
+    int ready(const astl_desc *d, const Plan &pl, const astl_params *params, int l, int L, F saved_of, char *layer_ws, hipStream_t st)
     {
         if (!on || (l >= l0 && l < l0 + n)) return GSWA_OK;
         l0 = l;
@@ -542,6 +543,10 @@ struct SequencePacks {
         void *ap[kMaxPackJobs], *mp[kMaxPackJobs];
         for (int i = 0; i < n; ++i) {
             char *sv = base ? nullptr : saved_of(l + i);
+            const astl_params &p = params[l + i];
+            // (what the layer's call refuses is refused before anything is written into its saved state or the scratch)
+            ASTL_RC(attn_forward_check(&d->attn, layer_ws, p.w_qkv, p.b_qkv, p.w_proj, p.b_proj, p.bias_table, layer_ws + pl.act,
+                                       sv ? sv + pl.act : nullptr, layer_ws + (sv ? 2 : 3) * pl.act));
             ap[i] = base ? base + i * each : sv + pl.act + pl.attn_pack_at;
             mp[i] = base ? base + i * each + pl.attn_pack : sv + pl.saved - pl.pack;
         }
@@ -1089,7 +1094,7 @@ int astl_stack_forward(const astl_stack_desc *desc, const void *x, const astl_pa
     packs.plan(pl, keep ? nullptr : layer_ws, pl.wave_layer ? sp.F + sp.S : pl.act);
     for (int l = 0; l < sp.L; ++l) {
         const astl_desc *ld = (l & 1) ? &sp.odd : &sp.even;
-        ASTL_RC(packs.ready(ld, pl, params, l, sp.L, [&](int i) { return sv + (size_t)i * (sp.S + sp.A); },
+        ASTL_RC(packs.ready(ld, pl, params, l, sp.L, [&](int i) { return sv + (size_t)i * (sp.S + sp.A); }, layer_ws,
                             static_cast<hipStream_t>(hip_stream)));
         packs.give(link, l);
         void *out, *lsaved = nullptr;
@@ -1203,11 +1208,14 @@ int astl_stack_forward_tiled(const astl_stack_desc *desc, const void *x, const a
     // were the difference.)
     const char *cur = static_cast<const char *>(x);
     char *out = static_cast<char *>(y);
+    astl_desc band = tp.sp.even; // (the call that tp.pl describes)
+    band.attn.B = 1;
+    band.attn.H = nb * M;
     SequencePacks packs;
     if (tp.one_kind) packs.plan(tp.pl, layer_ws, tp.pl.wave_layer ? tp.layer_ws : tp.min_act); // (else band by band, below)
     for (int l = 0; l < tp.sp.L; ++l) {
         const astl_desc *ld = (l & 1) ? &tp.sp.odd : &tp.sp.even;
-        ASTL_RC(packs.ready(ld, tp.pl, params, l, tp.sp.L, [](int) -> char * { return nullptr; }, st));
+        ASTL_RC(packs.ready(&band, tp.pl, params, l, tp.sp.L, [](int) -> char * { return nullptr; }, layer_ws, st));
         const int s = ld->attn.shift;
         int packed_rows = 0; // window rows of the band whose call left this layer's repacked weights in the scratch
         auto layer_call = [&](const astl_desc &sd, const char *src, char *dst, long first, long count, int windows) -> int {
@@ -1314,7 +1322,7 @@ int astl_stack_backward(const astl_stack_desc *desc, const void *x, const void *
         packs.plan(pl, nullptr, 0);
         for (int l = l0; l < l1; ++l) {
             const astl_desc *ld = (l & 1) ? &sp.odd : &sp.even;
-            ASTL_RC(packs.ready(ld, pl, params, l, l1, [&](int i) { return region + (size_t)(i - l0) * slot; },
+            ASTL_RC(packs.ready(ld, pl, params, l, l1, [&](int i) { return region + (size_t)(i - l0) * slot; }, layer_ws,
                                 static_cast<hipStream_t>(hip_stream)));
             packs.give(link, l);
             char *st = region + (size_t)(l - l0) * slot;

@@ -358,6 +358,41 @@ def test_whole_layers_reject_what_their_attention_layer_rejects(change):
     bwd(w=params["w_proj"] - 3 * act)                        # the scratch over a weight
 
 
+@pytest.mark.parametrize("C,window", [(60, 8), (180, 8), (180, 16)])
+def test_sequences_reject_overlaps_before_they_repack_weights(C, window):
+    """The weights of a sequence are repacked ahead of its layers, into saved state or scratch: a later layer's parameter
+    that lies there is refused before (found without a device: nothing is launched, nothing written)."""
+    from paper_2409_06206_amd import astl
+    L, H, W = 4, 20 * window, 40 * window               # (large enough for the weights of all layers in the scratch)
+    base = dict(B=2, H=H, W=W, C=C, heads=6, groups=2, window=window, shift=window // 2, dtype="bf16", hidden=2 * C, n_layers=L)
+    act = 2 * H * W * C * 2
+    assert act % 256 == 0
+    layer = astl.astl_query_bytes(astl.make_desc(**{k: v for k, v in base.items() if k != "n_layers"}))
+    addr = _spread(6 + 2 * L * len(astl.PARAM_FIELDS), 1 << 34)
+    x, dy, y, dx, saved, ws = addr[:6]
+    n = len(astl.PARAM_FIELDS)
+    params = [dict(zip(astl.PARAM_FIELDS, addr[6 + l * n:])) for l in range(L)]
+    grads = [dict(zip(astl.PARAM_FIELDS, addr[6 + (L + l) * n:])) for l in range(L)]
+    last = lambda **change: params[:-1] + [{**params[-1], **change}]
+
+    def rejected(call, every, *args):
+        with pytest.raises(gswa.GswaError) as ei:
+            call(astl.make_stack_desc(**base, checkpoint_every=every), *args, stream=0)
+        assert ei.value.status == gswa.GSWA_EINVAL
+
+    kept = saved + (L - 1) * (layer[0] + act)          # the last layer's state: x1, the attention layer's, the MLP's weights
+    scratch = ws + 2 * act                              # a layer's scratch: LN_1(x), the attention layer's output, the rest
+    for name in ("w_qkv", "b_proj", "bias_table"):
+        rejected(astl.astl_stack_forward, 0, x, last(**{name: kept + 2 * act + 256}), y, saved, ws)
+        rejected(astl.astl_stack_forward, 0, x, last(**{name: scratch + act + 256}), y, saved, ws)
+        rejected(astl.astl_stack_forward, 0, x, last(**{name: scratch + act + 256}), y, None, ws)
+        rejected(astl.astl_stack_forward, 2, x, last(**{name: scratch + act + 256}), y, saved, ws)
+        # recomputed blocks of two layers: their states, then two gradients, then a layer's scratch, all in ws
+        rejected(astl.astl_stack_backward, 2, x, dy, last(**{name: ws + layer[0] + act + 2 * act + 256}), saved, dx, grads, ws)
+        # bands of ten window rows, eleven with the dropped one: two buffers of eleven, then a layer's scratch
+        rejected(astl.astl_stack_forward_tiled, 0, x, last(**{name: ws + 32 * window * W * C * 2 + 256}), y, 10, ws)
+
+
 def _kernels(path):
     """Name and register facts of every gfx950 kernel in a shared library: the metadata note of each code object in it."""
     import msgpack
