@@ -979,7 +979,8 @@ __global__ __launch_bounds__(1024) void wave4_fwd_kernel(Geom g, const bf16_t *_
 }
 
 // ---------------------------------------------------------------------------------------
-// Split forward for wide layers: attention of heads [HB, HE) (one group or part of one), the
+// Split forward for wide layers, inputs of 2^31 elements and more (wide_fwd.hip takes the others, whose byte offsets fit 32
+// bits): attention of heads [HB, HE) (one group or part of one), the
 // cascade input of Eq. 8 read back from the group outputs in memory, no projection.  Window side
 // M is 8 or 16: a workgroup has N/16 waves, wave w owns tokens 16w..16w+15 of the window and holds
 // the N keys of each of its queries as N/16 score tiles.
