@@ -262,29 +262,68 @@ __device__ __forceinline__ void store_piece(bf16_t *base, long t, bool ok, int C
     }
 }
 
-template <int KSC, int KSF>
-__global__ __launch_bounds__(kWideThreads) void astl_mlp_wide_fwd_kernel(WideMlpArgs a, int nu)
+// Rows through a buffer resource: the 16 rows of a tile start at a wave-uniform address, a lane's pieces lie at offsets
+// that are the same for every tile, and rows beyond the last one read zeros and are not written.
+template <int KSC> struct TileRows {
+    uint32_t off, off4, off5; // byte offsets of the lane's piece 0 and of its pieces KSC - 2 and KSC - 1 (as load_rows)
+    int C;
+    __device__ __forceinline__ TileRows(int C_, int tok, int q) : C(C_)
+    {
+        const int c4 = 32 * (KSC - 2) + 8 * q, c5 = 32 * (KSC - 1) + 8 * q;
+        off = (uint32_t)(2 * (tok * C + 8 * q));
+        off4 = (uint32_t)(2 * (tok * C + (c4 + 8 > C ? C - 8 : c4)));
+        off5 = (uint32_t)(2 * (tok * C + (c5 + 8 > C ? C - 8 : c5)));
+    }
+    __device__ __forceinline__ buf_t rsrc(const bf16_t *base, long tile, long rows) const
+    {
+        const long left = rows - tile * 16;
+        const int n = left <= 0 ? 0 : left < 16 ? (int)left : 16;
+        return make_buf(base + (n > 0 ? tile * 16 * C : 0), (uint32_t)(2 * n * C));
+    }
+    __device__ __forceinline__ u32x4 load(buf_t b, int p) const
+    {
+        return __builtin_amdgcn_raw_buffer_load_b128(b, (int)(p < KSC - 2 ? off + 64 * p : p == KSC - 2 ? off4 : off5), 0, 0);
+    }
+    __device__ __forceinline__ void store(bf16_t *base, long tile, long rows, int q, const uint32_t (&r)[KSC][4]) const
+    {
+        const buf_t b = rsrc(base, tile, rows);
+#pragma unroll
+        for (int p = 0; p < KSC; ++p) {
+            const int c0 = 32 * p + 8 * q;
+            const uint32_t at = off + 64 * p;
+            if (p < KSC - 2 || c0 + 8 <= C) bstore128(b, at, 0, make_uint4(r[p][0], r[p][1], r[p][2], r[p][3]));
+            else if (c0 + 4 == C) bstore64(b, at, 0, make_uint2(r[p][0], r[p][1]));
+        }
+    }
+};
+
+// nu stream units (the hidden features there are).
+// What bounds it (stamps of the clock, one band of 1000x1496: 191488 tokens): of the 34 k clocks of a round 25 k are the four
+// units, in which the two waves of a SIMD share its issue of vector instructions (an ordinary one every 4.4 clocks, an
+// exponential or reciprocal every 8, a product takes 8 of its 16), 8 k LN_2 and the rows' way in and out.  Six layers in
+// bands, us, as the steps were taken: 9100; the row unpacked once, both skips and biases as what sums start from 8660; a
+// unit's loads spread over its steps 8430; GELU two instructions shorter and turns at the priority 8360; the next rows in
+// shares 8010.  No gain: two tiles a wave (the fragments read once for both: LDS is no bound), products and GELU of
+// different steps interleaved one by one, y stored in the course of the next round.
+template <int KSC, int KSF, int nu>
+__global__ __launch_bounds__(kWideThreads) void astl_mlp_wide_fwd_kernel(WideMlpArgs a)
 {
     using L = WideMlp<KSC, KSF>;
     constexpr int CT = L::CT;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     const uint8_t *pack = static_cast<const uint8_t *>(a.pack);
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, tok = lane & 15, q = lane >> 4;
+    const int tid = threadIdx.x, lane = tid & 63, tok = lane & 15, q = lane >> 4;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int C = a.C;
+    const uint32_t lds_at = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)lds);
     int lane_r = lane;
 
     // One load instruction moves one fragment (64 lanes x 16 bytes land at the wave-uniform LDS address
-    // + 16 lane); wave w moves fragments w, w + 8, ... of the unit.
-    auto stream_unit = [&](int u, int slot) {
-        int ln = lane_r;
-        asm volatile("" : "+v"(ln)); // (the per-fragment addresses are made here, not kept over the unit loop)
-        const uint8_t *src = pack + (size_t)u * L::UNIT_BYTES + 16 * ln;
-        uint8_t *dst = lds + (size_t)slot * L::UNIT_BYTES;
-#pragma unroll 1
-        for (int k = 0; k < L::FPW; ++k) { // (not unrolled: one address in registers at a time)
-            const int f = k * kWideWaves + wv;
-            if (f < L::FR_UNIT) lds_dma16(src + (size_t)f * 1024, dst + (size_t)f * 1024);
-        }
+    // + 16 lane); wave w moves fragments w, w + 8, ... of the unit, the n-th of its share here.
+    auto stream = [&](int unit, int slot, int n) {
+        if (n >= L::FPW || (L::FR_UNIT % kWideWaves != 0 && n * kWideWaves + wv >= L::FR_UNIT)) return;
+        const uint32_t f = (n * kWideWaves + wv) * 1024;
+        lds_dma16_sv(pack + (size_t)unit * L::UNIT_BYTES + f, 16 * lane_r, lds_at + slot * L::UNIT_BYTES + f);
     };
 
     const long ntiles = (a.rows + 15) / 16;
@@ -293,10 +332,14 @@ __global__ __launch_bounds__(kWideThreads) void astl_mlp_wide_fwd_kernel(WideMlp
     long tile = (long)blockIdx.x * kWideWaves + wv;
 
     u32x4 rx[KSC], ra[KSC];
-    load_rows<KSC>(a.x, tile * 16 + tok, a.rows, C, q, rx);
-    load_rows<KSC>(a.a, tile * 16 + tok, a.rows, C, q, ra);
-
-    stream_unit(0, 0);
+    {
+        const TileRows<KSC> tr(C, tok, q);
+        const buf_t bx = tr.rsrc(a.x, tile, a.rows), ba = tr.rsrc(a.a, tile, a.rows);
+#pragma unroll
+        for (int p = 0; p < KSC; ++p) { rx[p] = tr.load(bx, p); ra[p] = tr.load(ba, p); }
+    }
+#pragma unroll
+    for (int n = 0; n < L::FPW; ++n) stream(0, 0, n);
     for (int i = tid; i < L::T_FLOATS / 4; i += kWideThreads)
         reinterpret_cast<uint4 *>(lds + L::OFF_TABLES)[i] = reinterpret_cast<const uint4 *>(pack + L::P_TABLES)[i];
     __builtin_amdgcn_s_waitcnt(0);
@@ -304,79 +347,139 @@ __global__ __launch_bounds__(kWideThreads) void astl_mlp_wide_fwd_kernel(WideMlp
 
     int slot = 0; // buffer the unit about to be used lies in
     for (int round = 0; round < rounds; ++round, tile += stride) {
-        const bool more = round + 1 < rounds;
-        const long t = tile * 16 + tok;
-        const bool ok = t < a.rows;
         uint32_t lds0 = 0;
         asm volatile("" : "+v"(lds0)); // keeps the LDS reads of a round inside the round
         lane_r = lane;
         asm volatile("" : "+v"(lane_r));
         const float *tb = reinterpret_cast<const float *>(lds + lds0 + L::OFF_TABLES);
+        const int qr = lane_r >> 4; // (offsets and masks are made per round: kept, they would take dozens of registers)
+        const TileRows<KSC> tr(C, lane_r & 15, qr);
 
         // Eq. 4's skip; the stored (rounded) sum is what LN_2 sees here and in the backward pass
         uint32_t x1[KSC][4];
         {
             uint32_t xv[KSC][4], av[KSC][4];
-            tidy_rows<KSC>(C, q, rx, xv);
-            tidy_rows<KSC>(C, q, ra, av);
+            tidy_rows<KSC>(C, qr, rx, xv);
+            tidy_rows<KSC>(C, qr, ra, av);
 #pragma unroll
             for (int p = 0; p < KSC; ++p)
 #pragma unroll
                 for (int dw = 0; dw < 4; ++dw)
                     x1[p][dw] = pack_bf16x2(bf16_lo(xv[p][dw]) + bf16_lo(av[p][dw]), bf16_hi(xv[p][dw]) + bf16_hi(av[p][dw]));
         }
-        if (a.x1) store_rows<KSC>(a.x1, t, ok, C, q, x1);
-        uint32_t bx[KSC][4];
-#pragma unroll
-        for (int p = 0; p < KSC; ++p)
-#pragma unroll
-            for (int dw = 0; dw < 4; ++dw) bx[p][dw] = x1[p][dw];
-        layer_norm_rows<KSC>(bx, C, q, a.eps, reinterpret_cast<const float2 *>(tb + L::T_GB));
+        if (a.x1) tr.store(a.x1, tile, a.rows, qr, x1);
 
+        // LN_2 as layer_norm_rows takes it.  The row lies in fp32 where the sums of the second product will be: with the
+        // second bias it is what they start from (the skip of Eq. 5).  Tiles 2p and 2p + 1 of the sums are the lane's
+        // channels 32 p + 8 q + 0..3 and + 4..7.
         f32x4 yacc[CT];
+        uint4 bx[KSC];
+        {
+            float sum = 0.f;
 #pragma unroll
-        for (int ct = 0; ct < CT; ++ct) yacc[ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int p = 0; p < KSC; ++p)
+#pragma unroll
+                for (int dw = 0; dw < 4; ++dw) {
+                    f32x4 &y = yacc[2 * p + (dw >> 1)];
+                    y[2 * (dw & 1)] = bf16_lo(x1[p][dw]);
+                    y[2 * (dw & 1) + 1] = bf16_hi(x1[p][dw]);
+                    sum += y[2 * (dw & 1)] + y[2 * (dw & 1) + 1];
+                }
+            const float mean = qgroup_sum(sum) / (float)C;
+            __builtin_amdgcn_sched_barrier(0);
+            float dev = 0.f;
+#pragma unroll
+            for (int p = 0; p < KSC; ++p)
+#pragma unroll
+                for (int dw = 0; dw < 4; ++dw) {
+                    const f32x4 y = yacc[2 * p + (dw >> 1)];
+                    float d0 = y[2 * (dw & 1)] - mean, d1 = y[2 * (dw & 1) + 1] - mean;
+                    if (p >= KSC - 2) { // (C > 32 (KSC - 2): only the last two steps can reach beyond the row)
+                        const bool in = 32 * p + 8 * qr + 2 * dw < C;
+                        d0 = in ? d0 : 0.f;
+                        d1 = in ? d1 : 0.f;
+                    }
+                    dev += d0 * d0 + d1 * d1;
+                }
+            const float rstd = rsqrtf(qgroup_sum(dev) / (float)C + a.eps);
+            const float2 *gb = reinterpret_cast<const float2 *>(tb + L::T_GB);
+#pragma unroll
+            for (int p = 0; p < KSC; ++p) {
+                uint32_t n[4];
+#pragma unroll
+                for (int dw = 0; dw < 4; ++dw) {
+                    const float4 g = *reinterpret_cast<const float4 *>(gb + 32 * p + 8 * qr + 2 * dw); // (gamma, beta) of two channels; zero beyond C
+                    const f32x4 y = yacc[2 * p + (dw >> 1)];
+                    n[dw] = pack_bf16x2((y[2 * (dw & 1)] - mean) * rstd * g.x + g.y, (y[2 * (dw & 1) + 1] - mean) * rstd * g.z + g.w);
+                }
+                asm volatile("" : "+v"(n[0]), "+v"(n[1]), "+v"(n[2]), "+v"(n[3])); // (made here, not where they are used)
+                bx[p] = make_uint4(n[0], n[1], n[2], n[3]);
+                yacc[2 * p] += *reinterpret_cast<const f32x4 *>(tb + L::T_B2 + 32 * p + 8 * qr);
+                yacc[2 * p + 1] += *reinterpret_cast<const f32x4 *>(tb + L::T_B2 + 32 * p + 8 * qr + 4);
+                asm volatile("" : "+v"(yacc[2 * p]), "+v"(yacc[2 * p + 1]));
+                __builtin_amdgcn_sched_barrier(0); // (one step's scale and shift in registers at a time)
+            }
+        }
 
-        // The steps of a unit, written out one after the other (the products of one step can run under the
-        // GELU of the step before).
-        auto unit_steps = [&](int unit) {
+        // The steps of a unit, written out one after the other.  A step's fragments are read in four groups of KSC, the next
+        // group under the products of the one in hand (left alone the compiler keeps one read in flight and every product
+        // waits for its own): the first half of the channels for both tiles of W1, the second half, then W2's channel tiles
+        // in two halves.  With each group a wave sends one fragment of the next unit on its way into the other buffer
+        // (every wave has passed the previous barrier, i.e. finished reading that buffer), behind the last unit's the next
+        // round's first (after the last round nobody reads it): all of them in one go, 72 KB at 64 bytes a clock, and no
+        // wave computes for 1 k of a unit's 7 k clocks.  The next round's rows come a share with each unit, behind every
+        // second of its first groups: the rows of the whole chip in one go fill the memory's queues for 4 k clocks, in which
+        // waves stand where they issue.
+        auto unit_steps = [&](auto unit_) {
+            constexpr int unit = decltype(unit_)::value, PER = (2 * KSC + nu - 1) / nu;
+            constexpr int nxt = unit + 1 < nu ? unit + 1 : 0;
+            const buf_t nx = tr.rsrc(a.x, tile + stride, a.rows), na = tr.rsrc(a.a, tile + stride, a.rows); // (no rows: nothing is read)
             const uint4 *wu = reinterpret_cast<const uint4 *>(lds + lds0 + (size_t)slot * L::UNIT_BYTES);
-            // A step's fragments are read in four groups of KSC, the next group under the products of the one in hand
-            // (left alone the compiler keeps one read in flight and every product waits for its own): the first half of
-            // the channels for both tiles of W1, the second half, then W2's channel tiles in two halves.  (Six layers,
-            // 512x512: 1622 -> 1599 us; the kernel is bound by vector instructions, two thirds of its time.  The same
-            // in the backward kernel: 0.8 % slower, not kept.)
+            constexpr int GROUPS = 4 * L::HU;
+            auto row = [&](int p) {
+                if (p < KSC) rx[p] = tr.load(nx, p);
+                else ra[p - KSC] = tr.load(na, p - KSC);
+            };
             uint4 fr[2][KSC];
-            auto fetch = [&](int hs, int g) {
-                const uint4 *ws = wu + hs * L::FR_STEP * 64;
+            auto fetch = [&](int n) {
+                const uint4 *ws = wu + (n >> 2) * L::FR_STEP * 64;
+                const int g = n & 3;
 #pragma unroll
                 for (int k = 0; k < KSC; ++k) {
                     const int f = g < 2 ? (k & 1) * KSC + g * (KSC / 2) + k / 2 : 2 * KSC + (g - 2) * KSC + k;
                     fr[g & 1][k] = ws[f * 64 + lane_r];
                 }
             };
-            fetch(0, 0);
+            auto issue = [&](int n) {
+                if (n + 1 < GROUPS) fetch(n + 1);
+                stream(nxt, slot ^ 1, n);
+                constexpr int EVERY = 2 * PER <= GROUPS ? 2 : 1;
+                static_assert(PER <= GROUPS, "a load with each group at most");
+                if (n % EVERY == 0 && n / EVERY < PER && unit * PER + n / EVERY < 2 * KSC) row(unit * PER + n / EVERY);
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            fetch(0);
 #pragma unroll
             for (int hs = 0; hs < L::HU; ++hs) {
+                // (The two waves of a SIMD take turns at going first: the older one otherwise always does, and the younger
+                // one is left with its vector instructions when nothing runs beside them.)
+                if ((wv >= kWideWaves / 2) == (((unit + hs) & 1) != 0)) __builtin_amdgcn_s_setprio(1);
+                else __builtin_amdgcn_s_setprio(0);
                 const int f0 = 32 * (L::HU * unit + hs); // hidden features f0 + 16 jt + 4 q + i of token tok
-                const float4 b10 = *reinterpret_cast<const float4 *>(tb + L::T_B1 + f0 + 4 * q);
-                const float4 b11 = *reinterpret_cast<const float4 *>(tb + L::T_B1 + f0 + 16 + 4 * q);
-                f32x4 h0 = f32x4{0.f, 0.f, 0.f, 0.f}, h1 = f32x4{0.f, 0.f, 0.f, 0.f};
+                f32x4 h0 = *reinterpret_cast<const f32x4 *>(tb + L::T_B1 + f0 + 4 * qr);
+                f32x4 h1 = *reinterpret_cast<const f32x4 *>(tb + L::T_B1 + f0 + 16 + 4 * qr);
 #pragma unroll
                 for (int g = 0; g < 2; ++g) {
-                    fetch(hs, g + 1);
-                    __builtin_amdgcn_sched_barrier(0);
+                    issue(4 * hs + g);
 #pragma unroll
                     for (int k = 0; k < KSC / 2; ++k) {
-                        const int s = g * (KSC / 2) + k;
-                        const uint4 b = make_uint4(bx[s][0], bx[s][1], bx[s][2], bx[s][3]);
-                        h0 = mma32(fr[g][2 * k], b, h0);
-                        h1 = mma32(fr[g][2 * k + 1], b, h1);
+                        h0 = mma32(fr[g][2 * k], bx[g * (KSC / 2) + k], h0);
+                        h1 = mma32(fr[g][2 * k + 1], bx[g * (KSC / 2) + k], h1);
                     }
                 }
                 // the pre-activation as the one-kernel-per-step path stores it (rounded), then the GELU
-                const uint32_t pp[4] = {pack_bf16x2(h0[0] + b10.x, h0[1] + b10.y), pack_bf16x2(h0[2] + b10.z, h0[3] + b10.w),
-                                        pack_bf16x2(h1[0] + b11.x, h1[1] + b11.y), pack_bf16x2(h1[2] + b11.z, h1[3] + b11.w)};
+                const uint32_t pp[4] = {pack_bf16x2(h0[0], h0[1]), pack_bf16x2(h0[2], h0[3]),
+                                        pack_bf16x2(h1[0], h1[1]), pack_bf16x2(h1[2], h1[3])};
                 uint32_t hp[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
@@ -389,65 +492,36 @@ __global__ __launch_bounds__(kWideThreads) void astl_mlp_wide_fwd_kernel(WideMlp
                 const uint4 hb = make_uint4(hp[0], hp[1], hp[2], hp[3]);
 #pragma unroll
                 for (int g = 2; g < 4; ++g) {
-                    if (g == 2) fetch(hs, 3);
-                    else if (hs + 1 < L::HU) fetch(hs + 1, 0);
-                    __builtin_amdgcn_sched_barrier(0);
+                    issue(4 * hs + g);
 #pragma unroll
-                    for (int k = 0; k < KSC; ++k) {
-                        const int ct = (g - 2) * KSC + k;
-                        yacc[ct] = mma32(fr[g & 1][k], hb, yacc[ct]);
-                    }
+                    for (int k = 0; k < KSC; ++k) yacc[(g - 2) * KSC + k] = mma32(fr[g & 1][k], hb, yacc[(g - 2) * KSC + k]);
                 }
             }
         };
 
-        // First unit of the round (written apart from the loop over the others, so that the compiler sees that
-        // the row loads below are not in flight when it runs): the second unit is sent on its way into the
-        // other buffer (every wave has passed the previous barrier, i.e. finished reading that buffer), and
-        // BEHIND its loads the next round's rows, which have until the end of the round.
-        if (nu > 1) stream_unit(1, slot ^ 1);
-        else if (more) stream_unit(0, slot ^ 1);
-        if (more) {
-            const long tn = t + stride * 16;
-            load_rows<KSC>(a.x, tn, a.rows, C, q, rx);
-            load_rows<KSC>(a.a, tn, a.rows, C, q, ra);
-        }
-        unit_steps(0);
-        // The next unit has landed in LDS before any wave reads it.  Vector-memory operations complete in the
-        // order they were issued, so "at most n outstanding" covers everything older than the n youngest: here
-        // those are the row loads (each of the KSC steps of the two tensors is one load instruction), which
-        // stay in flight.
-        if (more) __builtin_amdgcn_s_waitcnt(kWaitAllBut2Ksc<KSC>);
-        else __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
-        slot ^= 1;
-        for (int unit = 1; unit < nu; ++unit) {
-            if (unit + 1 < nu) stream_unit(unit + 1, slot ^ 1);
-            else if (more) stream_unit(0, slot ^ 1); // (the first unit of the next round)
+        // (the next unit has landed in LDS before any wave passes the barrier)
+        static_for<nu>([&](auto unit) {
             unit_steps(unit);
             __builtin_amdgcn_s_waitcnt(0);
             __syncthreads();
             slot ^= 1;
-        }
+        });
 
-        // bias and the skip of Eq. 5; tiles 2p and 2p + 1 hold the lane's channels 32 p + 8 q + 0..3 and + 4..7
         uint32_t yo[KSC][4];
 #pragma unroll
         for (int p = 0; p < KSC; ++p) {
-            const float4 b2a = *reinterpret_cast<const float4 *>(tb + L::T_B2 + 32 * p + 8 * q);
-            const float4 b2b = *reinterpret_cast<const float4 *>(tb + L::T_B2 + 32 * p + 8 * q + 4);
             const f32x4 lo = yacc[2 * p], hi = yacc[2 * p + 1];
-            yo[p][0] = pack_bf16x2(lo[0] + b2a.x + bf16_lo(x1[p][0]), lo[1] + b2a.y + bf16_hi(x1[p][0]));
-            yo[p][1] = pack_bf16x2(lo[2] + b2a.z + bf16_lo(x1[p][1]), lo[3] + b2a.w + bf16_hi(x1[p][1]));
-            yo[p][2] = pack_bf16x2(hi[0] + b2b.x + bf16_lo(x1[p][2]), hi[1] + b2b.y + bf16_hi(x1[p][2]));
-            yo[p][3] = pack_bf16x2(hi[2] + b2b.z + bf16_lo(x1[p][3]), hi[3] + b2b.w + bf16_hi(x1[p][3]));
+            yo[p][0] = pack_bf16x2(lo[0], lo[1]);
+            yo[p][1] = pack_bf16x2(lo[2], lo[3]);
+            yo[p][2] = pack_bf16x2(hi[0], hi[1]);
+            yo[p][3] = pack_bf16x2(hi[2], hi[3]);
         }
-        store_rows<KSC>(a.y, t, ok, C, q, yo);
+        tr.store(a.y, tile, a.rows, qr, yo);
         if (a.xn_out) {
             // the LayerNorm of the layer that follows, taken of y as stored (the padding channels of the lane
             // hold b2 = 0 plus x1 = 0 plus products with zero weight rows: zero)
-            layer_norm_rows<KSC>(yo, C, q, a.eps, reinterpret_cast<const float2 *>(tb + L::T_NGB));
-            store_rows<KSC>(a.xn_out, t, ok, C, q, yo);
+            layer_norm_rows<KSC>(yo, C, qr, a.eps, reinterpret_cast<const float2 *>(tb + L::T_NGB));
+            tr.store(a.xn_out, tile, a.rows, qr, yo);
         }
     }
 }
@@ -625,18 +699,17 @@ __global__ __launch_bounds__(kWideThreads) void astl_mlp_wide_bwd_kernel(WideMlp
             for (int hs = 0; hs < L::HU; ++hs) {
                 const uint4 *ws = wu + hs * L::FR_STEP * 64;
                 const int f0 = 32 * (L::HU * unit + hs) + 8 * q; // the lane's hidden features f0 + 0..7 of token tok
-                f32x4 p0 = f32x4{0.f, 0.f, 0.f, 0.f}, p1 = p0, d0 = p0, d1 = p0;
+                f32x4 p0 = *reinterpret_cast<const f32x4 *>(tb + L::T_B1 + f0), p1 = *reinterpret_cast<const f32x4 *>(tb + L::T_B1 + f0 + 4);
+                f32x4 d0 = f32x4{0.f, 0.f, 0.f, 0.f}, d1 = d0;
 #pragma unroll
                 for (int s = 0; s < KSC; ++s) {
                     const uint4 b = make_uint4(bx[s][0], bx[s][1], bx[s][2], bx[s][3]);
                     p0 = mma32(ws[s * 64 + lane_r], b, p0);
                     p1 = mma32(ws[(KSC + s) * 64 + lane_r], b, p1);
                 }
-                const float4 b10 = *reinterpret_cast<const float4 *>(tb + L::T_B1 + f0);
-                const float4 b11 = *reinterpret_cast<const float4 *>(tb + L::T_B1 + f0 + 4);
                 // pre and dh as the one-kernel-per-step path stores them (rounded)
-                const uint32_t pp[4] = {pack_bf16x2(p0[0] + b10.x, p0[1] + b10.y), pack_bf16x2(p0[2] + b10.z, p0[3] + b10.w),
-                                        pack_bf16x2(p1[0] + b11.x, p1[1] + b11.y), pack_bf16x2(p1[2] + b11.z, p1[3] + b11.w)};
+                const uint32_t pp[4] = {pack_bf16x2(p0[0], p0[1]), pack_bf16x2(p0[2], p0[3]),
+                                        pack_bf16x2(p1[0], p1[1]), pack_bf16x2(p1[2], p1[3])};
                 __builtin_amdgcn_sched_barrier(0); // (the first product's accumulators are packed before the second's are live)
 #pragma unroll
                 for (int s = 0; s < KSC; ++s) {
@@ -828,13 +901,15 @@ template <int KSC, int KSF> hipError_t launch_wide_t(const WideMlpArgs &a, bool 
         const MlpPackJob job = {a.ln_w, a.ln_b, a.w_fc1, a.b_fc1, a.w_fc2, a.b_fc2, a.pack, a.bwd_pack};
         if (hipError_t e = launch_wide_pack_t<KSC, KSF>(a.C, a.Hd, &job, 1, a.nxt_w, a.nxt_b, s); e != hipSuccess) return e;
     }
-    auto kern = astl_mlp_wide_fwd_kernel<KSC, KSF>;
+    auto kern = nu == 1 ? astl_mlp_wide_fwd_kernel<KSC, KSF, 1> : nu == 2 ? astl_mlp_wide_fwd_kernel<KSC, KSF, 2>
+              : nu == 3 ? astl_mlp_wide_fwd_kernel<KSC, KSF, 3> : astl_mlp_wide_fwd_kernel<KSC, KSF, 4>;
+    static_assert(KSF / L::HU == 4, "one to four units");
     if (hipError_t ea = allow_dynamic_lds(reinterpret_cast<const void *>(kern), L::LDS_BYTES); ea != hipSuccess) return ea;
     const long tiles = (a.rows + 15) / 16;
     long blocks = (tiles + kWideWaves - 1) / kWideWaves;
     if (blocks > device_cu_count()) blocks = device_cu_count(); // (one workgroup of eight waves per compute unit)
     KernelTimer kt(K_MLP_FWD, s);
-    hipLaunchKernelGGL(kern, dim3((unsigned)(blocks < 1 ? 1 : blocks)), dim3(kWideThreads), L::LDS_BYTES, s, a, nu);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(blocks < 1 ? 1 : blocks)), dim3(kWideThreads), L::LDS_BYTES, s, a);
     return hipGetLastError();
 }
 

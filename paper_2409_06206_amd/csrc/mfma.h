@@ -121,6 +121,11 @@ __device__ __forceinline__ void lds_dma16_at(const void *src, uint32_t ldsaddr)
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(ldsaddr), "v"(src) : "memory");
 }
+// the same from a wave-uniform address plus 32 bits per lane
+__device__ __forceinline__ void lds_dma16_sv(const void *base, uint32_t voff, uint32_t ldsaddr)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(ldsaddr), "v"(voff), "s"(base) : "memory");
+}
 __device__ __forceinline__ void lds_dma16(const void *src, void *dst)
 {
     lds_dma16_at(src, __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)dst));

@@ -52,8 +52,9 @@ __device__ __forceinline__ void gauss(float t, float &Phi, float &phi)
     const float e = __builtin_amdgcn_exp2f(t * t * -0.72134752044448170f);
     const float k = __builtin_amdgcn_rcpf(fmaf(fabsf(t), 0.23164190f, 1.f));
     const float poly = ((((0.5307027145f * k - 0.7265760135f) * k + 0.7107068705f) * k - 0.142248368f) * k + 0.127414796f) * k;
-    const float w = poly * e;
-    Phi = t >= 0.f ? 1.f - w : w;
+    // Phi = 1 - poly e for positive t, poly e for the others: |step(t) - poly e|, with the step a product clamped to 0..1
+    // (a comparison, a choice and a subtraction otherwise; fused into the next instruction the magnitude costs nothing)
+    Phi = fabsf(fmaf(-poly, e, __builtin_amdgcn_fmed3f(t * 3.4028234e38f, 0.f, 1.f)));
     phi = 0.39894228040143268f * e;
 }
 
