@@ -29,6 +29,10 @@ namespace {
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kMaskLog2 = -100.0f * kLog2e; // the additive -100 of the shift mask, in base-2 units
 
+// s_waitcnt immediate: everything in LDS, all vector-memory operations but the 12 youngest
+// (vmcnt in bits 3:0 and 15:14, expcnt 6:4, lgkmcnt 11:8)
+constexpr int kWaitAllBut12 = 12 | (7 << 4);
+
 template <class Cf> struct WideBwdCfg {
     static constexpr int NWAVES = 4, NTHREADS = 64 * NWAVES;
     static constexpr int NTBL = 15 * 15;
@@ -542,8 +546,11 @@ __global__ __launch_bounds__(256, 1) void wide_attn_bwd_kernel(Geom g, const bf1
                     }
                 }
             }
-            // the next unit has landed in LDS before any wave reads it
-            __builtin_amdgcn_s_waitcnt(0);
+            // The next unit has landed in LDS before any wave reads it.  Memory operations complete in the order they were
+            // issued: behind the unit's loads a wave with a window has issued at least the stores of dQ, dK and dV of the
+            // head, whose way to memory is nobody's to wait for.
+            if (u >= W::NAU && active) __builtin_amdgcn_s_waitcnt(kWaitAllBut12);
+            else __builtin_amdgcn_s_waitcnt(0);
             __syncthreads();
         });
         par = (par + NU) & 1;
@@ -634,9 +641,9 @@ __global__ __launch_bounds__(512, 1) void wide_qkv_grad_kernel(Geom g, const uin
 
     // the group's Wqkv^T fragments: (head of the group, q|k|v, channel tile)
     {
-        constexpr int N16 = HG * 3 * CTF * 64;
-        const uint4 *src = reinterpret_cast<const uint4 *>(pack + Cf::P_WQX + (size_t)GI * HG * 3 * CTF * 1024);
-        for (int i = tid; i < N16; i += 64 * NWV) reinterpret_cast<uint4 *>(lds + W::G_OFF_WQX)[i] = src[i];
+        constexpr int NF = HG * 3 * CTF;
+        const uint8_t *src = pack + Cf::P_WQX + (size_t)GI * NF * 1024 + 16 * lane;
+        for (int f = wv; f < NF; f += NWV) lds_dma16(src + (size_t)f * 1024, lds + W::G_OFF_WQX + (size_t)f * 1024);
     }
 
     // row tiles of d w_qkv this wave owns: rt = wv, wv + 8, ...
@@ -646,7 +653,24 @@ __global__ __launch_bounds__(512, 1) void wide_qkv_grad_kernel(Geom g, const uin
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct) acc[r][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
 
+    // A wave's fragments of the next pair are loaded into the registers of this pair's, each when its last product has
+    // been issued.  (Windows beyond the last one read the last one's; only the last pair can hold one, and there is none
+    // behind it.)
     const int npair = (g.nW + 1) / 2;
+    uint4 dq[HG * 3];
+    uint4 xf[KS];
+    const uint4 *dsrc, *fsrc;
+    auto source = [&](int pair) {
+        const int w = 2 * pair + slot < g.nW ? 2 * pair + slot : g.nW - 1;
+        dsrc = reinterpret_cast<const uint4 *>(dqkv + ((size_t)w * 4 + tt) * W::FR_TILE * 1024) + lane;
+        // F of these tokens as the first kernel used it (x slice + previous group's output, Eq. 8)
+        fsrc = reinterpret_cast<const uint4 *>(ffr + ((size_t)w * 4 + tt) * KS * 1024) + lane;
+    };
+    source(blockIdx.x);
+#pragma unroll
+    for (int i = 0; i < HG * 3; ++i) dq[i] = dsrc[i * 64];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) xf[ks] = fsrc[ks * 64];
     for (int pair = blockIdx.x; pair < npair; pair += gridDim.x) {
         const int win = 2 * pair + slot;
         const bool valid = win < g.nW;
@@ -657,24 +681,14 @@ __global__ __launch_bounds__(512, 1) void wide_qkv_grad_kernel(Geom g, const uin
         if (si >= g.H) si -= g.H;
         if (sj >= g.W) sj -= g.W;
         const uint32_t tok = (uint32_t)((((b * g.H + si) * g.W) + sj) * C) * 2u;
-
-        uint4 dq[HG * 3];
-        uint4 xf[KS];
-        if (valid) {
-            const uint4 *dsrc = reinterpret_cast<const uint4 *>(dqkv + ((size_t)win * 4 + tt) * W::FR_TILE * 1024) + lane;
-#pragma unroll
-            for (int i = 0; i < HG * 3; ++i) dq[i] = dsrc[i * 64];
-            // F of these tokens as the first kernel used it (x slice + previous group's output, Eq. 8)
-            const uint4 *fsrc = reinterpret_cast<const uint4 *>(ffr + ((size_t)win * 4 + tt) * KS * 1024) + lane;
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) xf[ks] = fsrc[ks * 64];
-        } else { // the odd window out: its columns of the row buffers are zero
+        if (!valid) { // the odd window out: its columns of the row buffers are zero
 #pragma unroll
             for (int i = 0; i < HG * 3; ++i) dq[i] = make_uint4(0u, 0u, 0u, 0u);
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) xf[ks] = make_uint4(0u, 0u, 0u, 0u);
         }
-        __syncthreads(); // the previous pair's rows are consumed (first pass: the weights are in place)
+        if (pair == (int)blockIdx.x) __builtin_amdgcn_s_waitcnt(0); // (the weights are in place)
+        __syncthreads(); // the previous pair's rows are consumed
         // F^T rows through a selector product; d(q|k|v)^T rows by a transposed store of the packed tiles
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct) {
@@ -692,15 +706,30 @@ __global__ __launch_bounds__(512, 1) void wide_qkv_grad_kernel(Geom g, const uin
             store_tile_transposed(gbuf + ((2 * i + 1) * 16 + 4 * q) * LW + col0 + (l16 & ~1), LW,
                                   make_uint2(dq[i].z, dq[i].w), lane);
         }
+        source(pair + (int)gridDim.x);
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) xf[ks] = fsrc[ks * 64];
         // ---- dx slice of this wave's 16 tokens: dF^T = Wqkv^T d(q|k|v)^T, rows = channels ----
         if (valid) {
             f32x4 df[CTF];
 #pragma unroll
             for (int ct = 0; ct < CTF; ++ct) df[ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+            // (a step's fragments are read under the products of the step before: one read and one product at a time, as the
+            // compiler has it by itself, waits for LDS most of the time)
+            uint4 wf[2][CTF];
+            auto fetch = [&](int i) {
 #pragma unroll
-            for (int i = 0; i < HG * 3; ++i)
+                for (int ct = 0; ct < CTF; ++ct) wf[i & 1][ct] = wqx[(i * CTF + ct) * 64 + lane];
+            };
+            fetch(0);
 #pragma unroll
-                for (int ct = 0; ct < CTF; ++ct) df[ct] = mma32(wqx[(i * CTF + ct) * 64 + lane], dq[i], df[ct]);
+            for (int i = 0; i < HG * 3; ++i) {
+                if (i + 1 < HG * 3) fetch(i + 1);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int ct = 0; ct < CTF; ++ct) df[ct] = mma32(wf[i & 1][ct], dq[i], df[ct]);
+                dq[i] = dsrc[i * 64];
+            }
             // tile ct = (input head hl', half et'): rows = channels hl' D + 16 et' + 4q ..
 #pragma unroll
             for (int ct = 0; ct < CTF; ++ct) {
@@ -719,22 +748,29 @@ __global__ __launch_bounds__(512, 1) void wide_qkv_grad_kernel(Geom g, const uin
         }
         __syncthreads();
         // ---- d w_qkv, d b_qkv: K = the pair's 128 tokens ----
-#pragma unroll
-        for (int kp = 0; kp < 4; ++kp) {
-            uint4 afr[RW];
+        uint4 afr[2][RW], bfr[2][CT];
+        auto fetch_rows = [&](int kp) {
 #pragma unroll
             for (int r = 0; r < RW; ++r) {
                 const int rt = wv + NWV * r;
                 const uint16_t *ar = gbuf + (16 * (rt < FT ? rt : 0) + l16) * LW + 32 * kp + 8 * q;
-                afr[r] = cat(*reinterpret_cast<const uint2 *>(ar), *reinterpret_cast<const uint2 *>(ar + 4));
+                afr[kp & 1][r] = cat(*reinterpret_cast<const uint2 *>(ar), *reinterpret_cast<const uint2 *>(ar + 4));
             }
 #pragma unroll
             for (int ct = 0; ct < CT; ++ct) {
                 const uint16_t *br = fbuf + (16 * ct + l16) * LW + 32 * kp + 8 * q;
-                const uint4 bf = cat(*reinterpret_cast<const uint2 *>(br), *reinterpret_cast<const uint2 *>(br + 4));
-#pragma unroll
-                for (int r = 0; r < RW; ++r) acc[r][ct] = mma32(afr[r], bf, acc[r][ct]);
+                bfr[kp & 1][ct] = cat(*reinterpret_cast<const uint2 *>(br), *reinterpret_cast<const uint2 *>(br + 4));
             }
+        };
+        fetch_rows(0);
+#pragma unroll
+        for (int kp = 0; kp < 4; ++kp) {
+            if (kp + 1 < 4) fetch_rows(kp + 1);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+                for (int r = 0; r < RW; ++r) acc[r][ct] = mma32(afr[kp & 1][r], bfr[kp & 1][ct], acc[r][ct]);
         }
     }
 
