@@ -518,11 +518,9 @@ void fused_bwd_kernel(Geom g, const bf16_t *__restrict__ x,
                     for (int j = 0; j < 4; ++j)
                         if ((lastrow && rmask[kt]) || (lastcol && cmask[j])) st[kt][j] += kMask;
             }
-            float mx = -INFINITY;
+            float mx = max4f(st[0]);
 #pragma unroll
-            for (int kt = 0; kt < 4; ++kt)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) mx = fmaxf(mx, st[kt][j]);
+            for (int kt = 1; kt < 4; ++kt) mx = max5f(mx, st[kt]);
             mx = qgroup_max(mx);
             const float mxl = mx * kLog2e;
             float sum = 0.f;

@@ -458,11 +458,9 @@ __global__ __launch_bounds__(512, 1) void wave_fwd_kernel(Geom g, const bf16_t *
                 for (int kt = 0; kt < 4; ++kt) st[kt] = mma16(ident, bfh[nt - kt + 3], zero4);
 #pragma unroll
                 for (int kt = 0; kt < 4; ++kt) st[kt] = mma16(Kb[kt], Qb[nt], st[kt]);
-                float mx = fmaxf(fmaxf(st[0][0], st[0][1]), fmaxf(st[0][2], st[0][3]));
+                float mx = max4f(st[0]);
 #pragma unroll
-                for (int kt = 1; kt < 4; ++kt)
-#pragma unroll
-                    for (int j = 0; j < 4; j += 2) mx = fmaxf(fmaxf(mx, st[kt][j]), st[kt][j + 1]);
+                for (int kt = 1; kt < 4; ++kt) mx = max5f(mx, st[kt]);
                 mx = qgroup_max(mx);
                 const uint2 negmx = make_uint2(q == 0 ? pack_bf16x2(-mx, 0.f) : 0u, 0u);
                 uint2 Pb[4];
@@ -826,11 +824,9 @@ __global__ __launch_bounds__(1024) void wave4_fwd_kernel(Geom g, const bf16_t *_
                         for (int kt = 0; kt < 4; ++kt) st[kt] = mma16(ident, bfh[nt - kt + 3], zero4);
 #pragma unroll
                         for (int kt = 0; kt < 4; ++kt) st[kt] = mma16(K4[kt], Qb[i][nt], st[kt]);
-                        float mx = fmaxf(fmaxf(st[0][0], st[0][1]), fmaxf(st[0][2], st[0][3]));
+                        float mx = max4f(st[0]);
 #pragma unroll
-                        for (int kt = 1; kt < 4; ++kt)
-#pragma unroll
-                            for (int j = 0; j < 4; j += 2) mx = fmaxf(fmaxf(mx, st[kt][j]), st[kt][j + 1]);
+                        for (int kt = 1; kt < 4; ++kt) mx = max5f(mx, st[kt]);
                         mx = qgroup_max(mx);
                         const uint2 negmx = make_uint2(q == 0 ? pack_bf16x2(-mx, 0.f) : 0u, 0u);
                         uint2 Pb[4];

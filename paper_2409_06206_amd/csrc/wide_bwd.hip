@@ -455,11 +455,9 @@ __global__ __launch_bounds__(256, 1) void wide_attn_bwd_kernel(Geom g, const bf1
                         float mx[2], sum[2], dlt[2];
 #pragma unroll
                         for (int ni = 0; ni < 2; ++ni) {
-                            float m0 = fmaxf(fmaxf(st[ni][0][0], st[ni][0][1]), fmaxf(st[ni][0][2], st[ni][0][3]));
+                            float m0 = max4f(st[ni][0]);
 #pragma unroll
-                            for (int kt = 1; kt < 4; ++kt)
-#pragma unroll
-                                for (int j = 0; j < 4; j += 2) m0 = fmaxf(fmaxf(m0, st[ni][kt][j]), st[ni][kt][j + 1]);
+                            for (int kt = 1; kt < 4; ++kt) m0 = max5f(m0, st[ni][kt]);
                             mx[ni] = m0;
                         }
 #pragma unroll

@@ -160,7 +160,12 @@ template <> struct Op<float> {
     }
     static __device__ __forceinline__ float get(const float *p) { return *p; }
     static __device__ __forceinline__ void put(float *p, float v) { *p = v; }
-    static __device__ __forceinline__ void gelu(float t, float &h, float &dh) { h = gelu_f(t); dh = gelu_df(t); }
+    static __device__ __forceinline__ void gelu(float t, float &h, float &dh)
+    {
+        const float Phi = gauss_cdf(t);
+        h = t * Phi;
+        dh = fmaf(t, 0.39894228040143268f * __builtin_amdgcn_exp2f(t * t * -0.72134752044448170f), Phi);
+    }
 };
 template <> struct Op<bf16_t> {
     using F = uint2;
@@ -206,12 +211,14 @@ template <> struct Op<bf16_t> {
 // the slots 8 .. 11 with what the rounding left (0.2695): together -100.00002, at no cost.  In fp32, where adding and
 // taking away 144 would cost the scores their last bits, masked windows add the mask on the vector ALU.
 template <typename E, int HS> struct HeadOp;
+// `at`: where in the head's slice a lane's part begins, `load` reads it from there
 template <int HS> struct HeadOp<float, HS> { // product i takes channels 4i .. 4i+3: HS / 4 products instead of four
     float v[HS / 4];
-    __device__ __forceinline__ void load(const float *p, int q)
+    static __device__ __forceinline__ int at(int q) { return q; }
+    __device__ __forceinline__ void load(const float *p)
     {
 #pragma unroll
-        for (int i = 0; i < HS / 4; ++i) v[i] = p[4 * i + q];
+        for (int i = 0; i < HS / 4; ++i) v[i] = p[4 * i];
     }
     __device__ __forceinline__ void mask(int) {}
 };
@@ -223,18 +230,19 @@ template <int HS> __device__ __forceinline__ f32x4 mma(const HeadOp<float, HS> &
 }
 template <int HS> struct HeadOp<bf16_t, HS> { // (slots beyond the head: any number on one side, zeros on the masked one)
     uint2 v;
-    __device__ __forceinline__ void load(const bf16_t *p, int q) { v = *reinterpret_cast<const uint2 *>(p + (4 * q < HS ? 4 * q : 0)); }
+    static __device__ __forceinline__ int at(int q) { return 4 * q < HS ? 4 * q : 0; }
+    __device__ __forceinline__ void load(const bf16_t *p) { v = *reinterpret_cast<const uint2 *>(p); }
     __device__ __forceinline__ void mask(int q) { v = make_uint2(4 * q < HS ? v.x : 0u, 4 * q < HS ? v.y : 0u); }
 };
 template <int HS> __device__ __forceinline__ f32x4 mma(const HeadOp<bf16_t, HS> &a, const HeadOp<bf16_t, HS> &b, f32x4 c) { return mma16(a.v, b.v, c); }
-// q (`query`) or k of a head: `row` is the token's row, `col` the head's column
+// q (`query`) or k of a head: `at` is where in a token's row the lane's part of the head at column `col` lies
 template <class S> struct QkOp : HeadOp<typename S::E, S::HSQ> {
     static constexpr bool SLOTS = sizeof(typename S::E) == 2;
     static_assert(!SLOTS || S::HSQ <= 8, "slots 8 .. 15 are the mask's");
-    __device__ __forceinline__ void load(const typename S::E *row, int col, bool query, int q)
+    static __device__ __forceinline__ int at(int col, bool query, int q)
     {
-        if constexpr (SLOTS) this->v = *reinterpret_cast<const uint2 *>(row + (q < 2 ? col + (4 * q < S::HSQ ? 4 * q : 0) : query ? S::MQ + 4 * (3 - q) : S::MK));
-        else HeadOp<typename S::E, S::HSQ>::load(row + col, q);
+        if constexpr (SLOTS) return q < 2 ? col + (4 * q < S::HSQ ? 4 * q : 0) : query ? S::MQ + 4 * (3 - q) : S::MK;
+        return col + HeadOp<typename S::E, S::HSQ>::at(q);
     }
     __device__ __forceinline__ void mask(int q)
     {
@@ -245,9 +253,8 @@ template <class S> struct QkOp : HeadOp<typename S::E, S::HSQ> {
     }
 };
 // a tile of scores, from the four bias entries of the lane on: in bf16 they start the sum
-template <class S> __device__ __forceinline__ f32x4 scores(const QkOp<S> &a, const QkOp<S> &b, const float *bias)
+template <class S> __device__ __forceinline__ f32x4 scores(const QkOp<S> &a, const QkOp<S> &b, f32x4 t)
 {
-    const f32x4 t = {bias[0], bias[1], bias[2], bias[3]};
     if constexpr (sizeof(typename S::E) == 2) return mma(a, b, t);
     f32x4 d = mma(a, b, zero4());
 #pragma unroll
@@ -306,6 +313,35 @@ template <class S> __device__ __forceinline__ int key_offset4(int tile, int q)
     static_assert(S::M == 8 || S::M == 12, "window size");
     return 4 * S::NTB * (tile / 3) + key_offset<S>(16 * (tile % 3) + 4 * q); // (12: three tiles are four window rows)
 }
+
+// A lane's place in LDS, kept in a register of its own: what a loop over tiles adds to it is then an offset of the read
+// instruction (two or three instructions per read otherwise, with which the units of scores spent a quarter of their
+// vector instructions).
+template <typename E> __device__ __forceinline__ const E *lane_base(const E *p, int off)
+{
+    asm volatile("" : "+v"(off));
+    return p + off;
+}
+// The lane's four bias entries of a score tile: with a query per column (keys of the tile in descending order), with a key
+// per column.  Tiles KB apart differ by KSTEP entries.
+template <class S> struct BiasOf {
+    static constexpr int KB = S::M == 8 ? 1 : 3, KSTEP = S::M == 8 ? 2 * S::NTB : 4 * S::NTB, KN = S::NT / KB;
+    static_assert(S::NT % KB == 0, "whole turns");
+    const float *p[KB];
+    bool query;
+    __device__ __forceinline__ BiasOf(const float *tbh, int token, bool query_, int q) : query(query_)
+    {
+        const int o = key_offset<S>(token), mid = (S::M - 1) * (S::NTB + 1);
+#pragma unroll
+        for (int r = 0; r < KB; ++r)
+            p[r] = lane_base(tbh, query ? mid + o - key_offset4<S>(r, 3 - q) - 3 - KSTEP * (KN - 1) : mid - o + key_offset4<S>(r, q));
+    }
+    __device__ __forceinline__ f32x4 tile(int t) const
+    {
+        const float *b = p[t % KB] + KSTEP * (query ? KN - 1 - t / KB : t / KB);
+        return f32x4{b[0], b[1], b[2], b[3]};
+    }
+};
 
 // feature of the padded q|k|v rows -> row of the group's weight block [q: QG | k: QG | v: CG], -1 for padding
 template <class S> __device__ __forceinline__ int weight_row(int f)
@@ -675,26 +711,25 @@ __global__ __launch_bounds__(S::NTH) void window_layer_fwd_kernel(WindowLayerArg
             for (int u = wv; u < S::HG * S::NT; u += S::WAVES) {
                 FRESH_LANE;
                 const int hl = u / S::NT, nt = u - hl * S::NT, tq = 16 * nt + l16;
-                const float *tbh = tb + (gi * S::HG + hl) * S::TBP;
+                const BiasOf<S> bias(tb + (gi * S::HG + hl) * S::TBP, tq, true, q);
+                const E *krow = lane_base(R, (15 - l16) * S::PR + QkOp<S>::at(S::RQ + hl * S::HSQ, false, q));
                 QkOp<S> qf;
-                qf.load(R + tq * S::PR, hl * S::HSQ, true, q);
+                qf.load(R + tq * S::PR + QkOp<S>::at(hl * S::HSQ, true, q));
                 qf.mask(q);
-                const int oq = key_offset<S>(tq) + (S::M - 1) * (S::NTB + 1);
                 f32x4 st[S::NT];
-                float mx = -INFINITY;
 #pragma unroll
                 for (int kt = 0; kt < S::NT; ++kt) {
                     QkOp<S> kf;
-                    kf.load(R + (16 * kt + 15 - l16) * S::PR, S::RQ + hl * S::HSQ, false, q);
-                    const float *bias = tbh + oq - key_offset4<S>(kt, 3 - q) - 3;
-                    st[kt] = scores(kf, qf, bias);
+                    kf.load(krow + 16 * kt * S::PR);
+                    st[kt] = scores<S>(kf, qf, bias.tile(kt));
                 }
                 if (sizeof(E) == 4 && masked) {
 #pragma unroll
                     for (int kt = 0; kt < S::NT; ++kt) st[kt] = add_mask<S>(win, st[kt], 16 * kt + 12 - 4 * q, false, tq);
                 }
+                float mx = max4f(st[0]);
 #pragma unroll
-                for (int kt = 0; kt < S::NT; ++kt) mx = fmaxf(mx, fmaxf(fmaxf(st[kt][0], st[kt][1]), fmaxf(st[kt][2], st[kt][3])));
+                for (int kt = 1; kt < S::NT; ++kt) mx = max5f(mx, st[kt]);
                 mx = qgroup_max(mx);
                 f32x4 sum = zero4();
 #pragma unroll
@@ -833,14 +868,43 @@ __global__ __launch_bounds__(S::NTH) void window_layer_fwd_kernel(WindowLayerArg
 // adds to (or, for the workgroup's first window, sets) an entry of the workgroup's vector of parameter gradients
 __device__ __forceinline__ void put_grad(float *p, float v, bool first) { *p = first ? v : *p + v; }
 
-// result tile [16 rows of `rows`][16 columns] of a weight gradient: column `cols` is the bias gradient
-__device__ __forceinline__ void put_tile(float *dw, float *db, int ld, int row0, int rows, int col, int cols, f32x4 v, bool first)
-{
-    if (row0 >= rows || col > cols) return; // (rows is a multiple of four)
-    float *p = col < cols ? dw + row0 * ld + col : db + row0;
-    const int step = col < cols ? ld : 1;
+// Four entries of the workgroup's vector of parameter gradients, `step` apart, the first n of them in use.  What earlier
+// windows left there is read ahead of the products whose sums are added (read behind them, every tile of the second window
+// of a workgroup waited for memory: 11 k of its 92 k clocks).
+struct GradTile {
+    float *p;
+    int step, n;
+    f32x4 old;
+    __device__ __forceinline__ void load(bool first)
+    {
+        old = zero4();
+        if (first) return;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) put_grad(p + i * step, v[i], first);
+        for (int i = 0; i < 4; ++i) old[i] = i < n ? p[i * step] : 0.f;
+    }
+    // (all sums before the first store: a wait for a load behind it waits for the store as well)
+    __device__ __forceinline__ f32x4 sum(f32x4 v, bool first) const
+    {
+        f32x4 r = first ? v : old + v;
+        asm volatile("" : "+v"(r));
+        return r;
+    }
+    __device__ __forceinline__ void store(f32x4 r) const
+    {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (i < n) p[i * step] = r[i];
+    }
+};
+// result tile [16 rows of `rows`][16 columns] of a weight gradient: column `cols` is the bias gradient
+__device__ __forceinline__ GradTile grad_tile(float *dw, float *db, int ld, int row0, int rows, int col, int cols, bool first)
+{
+    GradTile t;
+    t.n = row0 >= rows || col > cols ? 0 : 4; // (rows is a multiple of four)
+    t.p = t.n == 0 ? dw : col < cols ? dw + row0 * ld + col : db + row0;
+    t.step = col < cols ? ld : 1;
+    t.load(first);
+    return t;
 }
 
 // four channels (piece k of 16) of a token's row of dn, fp32; the pieces of a row are exchanged so that 16 rows written at
@@ -1004,6 +1068,9 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
                     dn_unit(u);
                 } else if (u < U1) {
                     const int v = u - U0, ft = v / (S::CTC / 2), ct = 2 * (v - ft * (S::CTC / 2));
+                    GradTile gt[2];
+#pragma unroll
+                    for (int p = 0; p < 2; ++p) gt[p] = grad_tile(part + S::P_W1, part + S::P_B1, S::C, 16 * ft + 4 * q, S::HID, 16 * (ct + p) + l16, S::C, first);
                     f32x4 acc[2] = {zero4(), zero4()};
 #pragma unroll
                     for (int s = 0; s < S::NT; ++s) {
@@ -1012,10 +1079,14 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
                         for (int p = 0; p < 2; ++p) acc[p] = mma(r, O::ld_t(A + 16 * s * S::PC + 16 * (ct + p), S::PC, q, l16), acc[p]);
                     }
 #pragma unroll
-                    for (int p = 0; p < 2; ++p)
-                        put_tile(part + S::P_W1, part + S::P_B1, S::C, 16 * ft + 4 * q, S::HID, 16 * (ct + p) + l16, S::C, acc[p], first);
+                    for (int p = 0; p < 2; ++p) acc[p] = gt[p].sum(acc[p], first);
+#pragma unroll
+                    for (int p = 0; p < 2; ++p) gt[p].store(acc[p]);
                 } else {
                     const int v = u - U1, ct = v / (S::HFT / 2), ft = 2 * (v - ct * (S::HFT / 2));
+                    GradTile gt[2];
+#pragma unroll
+                    for (int p = 0; p < 2; ++p) gt[p] = grad_tile(part + S::P_W2, part + S::P_B2, S::HID, 16 * ct + 4 * q, S::C, 16 * (ft + p) + l16, S::HID, first);
                     f32x4 acc[2] = {zero4(), zero4()};
 #pragma unroll
                     for (int s = 0; s < S::NT; ++s) {
@@ -1024,8 +1095,9 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
                         for (int p = 0; p < 2; ++p) acc[p] = mma(r, O::ld_t(Hh + 16 * s * S::PH + 16 * (ft + p), S::PH, q, l16), acc[p]);
                     }
 #pragma unroll
-                    for (int p = 0; p < 2; ++p)
-                        put_tile(part + S::P_W2, part + S::P_B2, S::HID, 16 * ct + 4 * q, S::C, 16 * (ft + p) + l16, S::HID, acc[p], first);
+                    for (int p = 0; p < 2; ++p) acc[p] = gt[p].sum(acc[p], first);
+#pragma unroll
+                    for (int p = 0; p < 2; ++p) gt[p].store(acc[p]);
                 }
             }
             __syncthreads();
@@ -1142,6 +1214,13 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
                     qkv_unit<S>(a, gi, (u - U0) / S::TU, (u - U0) % S::TU, X, A, R);
                 } else {
                     const int v = u - U1, ot = v / CX2, ct = 2 * (v - ot * CX2);
+                    GradTile gt[2];
+#pragma unroll
+                    for (int p = 0; p < 2; ++p) {
+                        const int col = 16 * (ct + p) + l16, g = col / S::CGP, o = col - g * S::CGP;
+                        const int c = col == S::OC ? S::C : (g < S::G && o < S::CG ? g * S::CG + o : S::C + 1);
+                        gt[p] = grad_tile(part + S::P_WP, part + S::P_BP, S::C, 16 * ot + 4 * q, S::C, c, S::C, first);
+                    }
                     f32x4 acc[2] = {zero4(), zero4()};
 #pragma unroll
                     for (int s = 0; s < S::NT; ++s) {
@@ -1155,11 +1234,9 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
                         }
                     }
 #pragma unroll
-                    for (int p = 0; p < 2; ++p) {
-                        const int col = 16 * (ct + p) + l16, g = col / S::CGP, o = col - g * S::CGP;
-                        const int c = col == S::OC ? S::C : (g < S::G && o < S::CG ? g * S::CG + o : S::C + 1);
-                        put_tile(part + S::P_WP, part + S::P_BP, S::C, 16 * ot + 4 * q, S::C, c, S::C, acc[p], first);
-                    }
+                    for (int p = 0; p < 2; ++p) acc[p] = gt[p].sum(acc[p], first);
+#pragma unroll
+                    for (int p = 0; p < 2; ++p) gt[p].store(acc[p]);
                 }
             }
             __syncthreads();
@@ -1175,32 +1252,32 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
                 const int u = wv + k * S::WAVES;
                 if (u >= UA) continue;
                 const int hl = u / S::NT, nt = u - hl * S::NT, tq = 16 * nt + l16;
-                const float *tbh = tb + (gi * S::HG + hl) * S::TBP;
+                const BiasOf<S> bias(tb + (gi * S::HG + hl) * S::TBP, tq, true, q);
+                const E *krow = lane_base(R, (15 - l16) * S::PR + QkOp<S>::at(S::RQ + hl * S::HSQ, false, q));
+                const E *vrow = lane_base(R, (15 - l16) * S::PR + 2 * S::RQ + hl * S::HSV + HeadOp<E, S::HSV>::at(q));
                 QkOp<S> qf;
                 HeadOp<E, S::HSV> of;
-                qf.load(R + tq * S::PR, hl * S::HSQ, true, q);
-                of.load(DO + tq * S::PD + hl * S::HSV, q);
+                qf.load(R + tq * S::PR + QkOp<S>::at(hl * S::HSQ, true, q));
+                of.load(DO + tq * S::PD + hl * S::HSV + HeadOp<E, S::HSV>::at(q));
                 qf.mask(q);
                 of.mask(q);
-                const int oq = key_offset<S>(tq) + (S::M - 1) * (S::NTB + 1);
                 f32x4 st[S::NT], dp[S::NT];
-                float mx = -INFINITY;
 #pragma unroll
                 for (int kt = 0; kt < S::NT; ++kt) {
                     QkOp<S> kf;
                     HeadOp<E, S::HSV> vf;
-                    kf.load(R + (16 * kt + 15 - l16) * S::PR, S::RQ + hl * S::HSQ, false, q);
-                    vf.load(R + (16 * kt + 15 - l16) * S::PR + 2 * S::RQ + hl * S::HSV, q);
-                    const float *bias = tbh + oq - key_offset4<S>(kt, 3 - q) - 3;
-                    st[kt] = scores(kf, qf, bias);
+                    kf.load(krow + 16 * kt * S::PR);
+                    vf.load(vrow + 16 * kt * S::PR);
+                    st[kt] = scores<S>(kf, qf, bias.tile(kt));
                     dp[kt] = mma(vf, of, zero4());
                 }
                 if (sizeof(E) == 4 && masked) {
 #pragma unroll
                     for (int kt = 0; kt < S::NT; ++kt) st[kt] = add_mask<S>(win, st[kt], 16 * kt + 12 - 4 * q, false, tq);
                 }
+                float mx = max4f(st[0]);
 #pragma unroll
-                for (int kt = 0; kt < S::NT; ++kt) mx = fmaxf(mx, fmaxf(fmaxf(st[kt][0], st[kt][1]), fmaxf(st[kt][2], st[kt][3])));
+                for (int kt = 1; kt < S::NT; ++kt) mx = max5f(mx, st[kt]);
                 mx = qgroup_max(mx);
                 float sum = 0.f, dl = 0.f;
 #pragma unroll
@@ -1266,10 +1343,15 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
                 }
                 float *tg = part + S::P_TB + gi * S::HG + hl;
                 const int e = ((dr + S::M - 1) * S::NTB + dc + S::M - 1) * S::HEADS;
-                put_grad(tg + e, t00, first);
-                if (dc > 0) put_grad(tg + e - S::M * S::HEADS, t01, first);
-                if (dr > 0) put_grad(tg + e - S::M * S::NTB * S::HEADS, t10, first);
-                if (dr > 0 && dc > 0) put_grad(tg + e - S::M * (S::NTB + 1) * S::HEADS, t11, first);
+                float *pt[4] = {tg + e, dc > 0 ? tg + e - S::M * S::HEADS : tg + e, dr > 0 ? tg + e - S::M * S::NTB * S::HEADS : tg + e,
+                                dr > 0 && dc > 0 ? tg + e - S::M * (S::NTB + 1) * S::HEADS : tg + e};
+                f32x4 t = {t00, t01, t10, t11};
+                if (!first) t += f32x4{*pt[0], *pt[1], *pt[2], *pt[3]};
+                asm volatile("" : "+v"(t)); // (as GradTile)
+                *pt[0] = t[0];
+                if (dc > 0) *pt[1] = t[1];
+                if (dr > 0) *pt[2] = t[2];
+                if (dr > 0 && dc > 0) *pt[3] = t[3];
             };
             // The same in two steps where LDS has room for what lies between (BLOCKS).  First the blocks [keys of a window row]
             // x [queries of a window row] at the same distance dr of the two rows are added up: a lane owns four
@@ -1311,13 +1393,15 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
                 if (e >= S::NTBL) return;
                 const int dri = e / S::NTB, dc = e - dri * S::NTB - (S::M - 1);
                 const float *sb = SB + slot * S::NTB * S::N + dri * S::N;
+                float *pt = part + S::P_TB + e * S::HEADS + gi * S::HG + hl;
+                const float old = first ? 0.f : *pt; // (as GradTile)
                 float v[S::M], sum = 0.f;
 #pragma unroll
                 for (int c = 0; c < S::M; ++c) v[c] = sb[c * S::M + (c + dc < 0 ? 0 : c + dc >= S::M ? S::M - 1 : c + dc)];
                 loads_issued();
 #pragma unroll
                 for (int c = 0; c < S::M; ++c) sum += c + dc >= 0 && c + dc < S::M ? v[c] : 0.f;
-                put_grad(part + S::P_TB + e * S::HEADS + gi * S::HG + hl, sum, first);
+                *pt = first ? sum : old + sum;
             };
             // ---- key role, NF heads at a time: dV, dK, and the score gradients for the table gradient.  With one round they
             // go to LDS as they come; with more they wait in registers until the heads before have been folded, which the
@@ -1339,26 +1423,27 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
                 if (u >= UR || hl >= S::HG) continue;
                 const int kt = u - slot * S::NT, tk = 16 * kt + l16;
                 E *fo = FO + (slot * S::N + tk) * S::PF;
-                const float *tbh = tb + (gi * S::HG + hl) * S::TBP;
+                const BiasOf<S> bias(tb + (gi * S::HG + hl) * S::TBP, tk, false, q);
+                const E *qrow = lane_base(R, l16 * S::PR + QkOp<S>::at(hl * S::HSQ, true, q));
+                const E *orow = lane_base(DO, l16 * S::PD + hl * S::HSV + HeadOp<E, S::HSV>::at(q));
+                const float *srow = lane_base(lse, hl * S::N + 4 * q); // (statistics: base-2 log-sum-exp or maximum; minus sum P dP; 1 / sum)
                 QkOp<S> kf;
                 HeadOp<E, S::HSV> vf;
-                kf.load(R + tk * S::PR, S::RQ + hl * S::HSQ, false, q);
-                vf.load(R + tk * S::PR + 2 * S::RQ + hl * S::HSV, q);
+                kf.load(R + tk * S::PR + QkOp<S>::at(S::RQ + hl * S::HSQ, false, q));
+                vf.load(R + tk * S::PR + 2 * S::RQ + hl * S::HSV + HeadOp<E, S::HSV>::at(q));
                 kf.mask(q);
                 vf.mask(q);
-                const int ok = (S::M - 1) * (S::NTB + 1) - key_offset<S>(tk);
 #pragma unroll
                 for (int nt = 0; nt < S::NT; ++nt) {
                     QkOp<S> qf;
                     HeadOp<E, S::HSV> of;
-                    qf.load(R + (16 * nt + l16) * S::PR, hl * S::HSQ, true, q);
-                    of.load(DO + (16 * nt + l16) * S::PD + hl * S::HSV, q);
-                    const f32x4 ls = *reinterpret_cast<const f32x4 *>(lse + hl * S::N + 16 * nt + 4 * q);
-                    const f32x4 dl = *reinterpret_cast<const f32x4 *>(delta + hl * S::N + 16 * nt + 4 * q);
-                    const float *bias = tbh + ok + key_offset4<S>(nt, q);
-                    f32x4 p = scores(qf, kf, bias), d;
+                    qf.load(qrow + 16 * nt * S::PR);
+                    of.load(orow + 16 * nt * S::PD);
+                    const f32x4 ls = *reinterpret_cast<const f32x4 *>(srow + 16 * nt);
+                    const f32x4 dl = *reinterpret_cast<const f32x4 *>(srow + S::HG * S::N + 16 * nt);
+                    f32x4 p = scores<S>(qf, kf, bias.tile(nt)), d;
                     f32x4 dp = mma(of, vf, sizeof(E) == 4 ? zero4() : dl), rs; // dP - delta
-                    if (sizeof(E) == 4) { dp += dl; rs = *reinterpret_cast<const f32x4 *>(rsum + hl * S::N + 16 * nt + 4 * q); }
+                    if (sizeof(E) == 4) { dp += dl; rs = *reinterpret_cast<const f32x4 *>(srow + 2 * S::HG * S::N + 16 * nt); }
                     if (sizeof(E) == 4 && masked) p = add_mask<S>(win, p, 16 * nt + 4 * q, true, tk);
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
@@ -1468,6 +1553,16 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
                 } else {
                     constexpr int P = S::CTG > 1 ? 2 : 1;
                     const int ft = (u - V0) / CP2, ct = P * ((u - V0) - ft * CP2);
+                    const Rows4 rows = weight_rows4<S>(16 * ft + 4 * q);
+                    GradTile gt[P];
+#pragma unroll
+                    for (int p = 0; p < P; ++p) {
+                        const int c = 16 * (ct + p) + l16;
+                        gt[p].n = c > S::CG ? 0 : rows.n < 4 ? rows.n : 4;
+                        gt[p].p = c < S::CG ? part + S::P_WQ + (gi * S::RG + rows.row) * S::CG + c : part + S::P_BQ + gi * S::RG + rows.row;
+                        gt[p].step = c < S::CG ? S::CG : 1;
+                        gt[p].load(first);
+                    }
                     f32x4 acc[P];
 #pragma unroll
                     for (int p = 0; p < P; ++p) acc[p] = zero4();
@@ -1482,16 +1577,10 @@ __global__ __launch_bounds__(S::NTH) void window_layer_bwd_kernel(WindowLayerArg
                             acc[p] = mma(r, b, acc[p]);
                         }
                     }
-                    const Rows4 rows = weight_rows4<S>(16 * ft + 4 * q);
 #pragma unroll
-                    for (int p = 0; p < P; ++p) {
-                        const int c = 16 * (ct + p) + l16;
-                        float *pw = part + (c < S::CG ? S::P_WQ + (gi * S::RG + rows.row) * S::CG + c : S::P_BQ + gi * S::RG + rows.row);
-                        const int step = c < S::CG ? S::CG : 1;
+                    for (int p = 0; p < P; ++p) acc[p] = gt[p].sum(acc[p], first);
 #pragma unroll
-                        for (int i = 0; i < 4; ++i)
-                            if (i < rows.n && c <= S::CG) put_grad(pw + i * step, acc[p][i], first);
-                    }
+                    for (int p = 0; p < P; ++p) gt[p].store(acc[p]);
                 }
             }
             __syncthreads();
