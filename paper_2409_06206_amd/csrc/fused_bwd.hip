@@ -848,16 +848,16 @@ __global__ __launch_bounds__(1024) void reduce_partials_kernel(const float *__re
     reduce_partials_block<V>(part, nparts, n, out, accumulate, (int)blockIdx.x, red);
 }
 
-// Two sums in one launch: blocks [0, blocks0) take the first (V entries per load), the others the second
-// (one entry per load: the short vectors of a bias-table gradient).
+// Two sums in one launch: blocks [0, blocks1) take the second (one entry per load: the short vectors of a bias-table
+// gradient, of which there may be many, so these blocks start first), the others the first (V entries per load).
 template <int V>
-__global__ __launch_bounds__(1024) void reduce_partials_pair_kernel(ReduceJob j0, int blocks0, ReduceJob j1)
+__global__ __launch_bounds__(1024) void reduce_partials_pair_kernel(ReduceJob j0, int blocks1, ReduceJob j1)
 {
     __shared__ float red[32 * (32 * V + 1)];
-    if ((int)blockIdx.x < blocks0)
-        reduce_partials_block<V>(j0.part, j0.nparts, j0.n, j0.out, j0.accumulate, (int)blockIdx.x, red);
+    if ((int)blockIdx.x < blocks1)
+        reduce_partials_block<1>(j1.part, j1.nparts, j1.n, j1.out, j1.accumulate, (int)blockIdx.x, red);
     else
-        reduce_partials_block<1>(j1.part, j1.nparts, j1.n, j1.out, j1.accumulate, (int)blockIdx.x - blocks0, red);
+        reduce_partials_block<V>(j0.part, j0.nparts, j0.n, j0.out, j0.accumulate, (int)blockIdx.x - blocks1, red);
 }
 
 // d w_proj, d b_proj of wide layers: dY^T [A | 1] over plain token rows, 128 tokens per pass of a workgroup
@@ -1046,9 +1046,9 @@ hipError_t launch_reduce_pair(const ReduceJob &a, const ReduceJob &b, hipStream_
     const int blocks0 = (a.n + 32 * v - 1) / (32 * v), blocks1 = (b.n + 31) / 32;
     const dim3 grid(blocks0 + blocks1);
     switch (v) {
-    case 4: hipLaunchKernelGGL(reduce_partials_pair_kernel<4>, grid, dim3(1024), 0, s, a, blocks0, b); break;
-    case 2: hipLaunchKernelGGL(reduce_partials_pair_kernel<2>, grid, dim3(1024), 0, s, a, blocks0, b); break;
-    default: hipLaunchKernelGGL(reduce_partials_pair_kernel<1>, grid, dim3(1024), 0, s, a, blocks0, b); break;
+    case 4: hipLaunchKernelGGL(reduce_partials_pair_kernel<4>, grid, dim3(1024), 0, s, a, blocks1, b); break;
+    case 2: hipLaunchKernelGGL(reduce_partials_pair_kernel<2>, grid, dim3(1024), 0, s, a, blocks1, b); break;
+    default: hipLaunchKernelGGL(reduce_partials_pair_kernel<1>, grid, dim3(1024), 0, s, a, blocks1, b); break;
     }
     return hipGetLastError();
 }

@@ -109,6 +109,7 @@ struct WgradArgs {
     // Where the caller knows that the streaming kernel will run (wgrad_pair_streams), dw / db may be the final
     // gradient arrays instead of a zeroed copy: `direct` nonzero, and the sum then writes (accumulate 0) or adds.
     int direct, accumulate;
+    const struct ReduceJob *also; // (with `direct`, may be null) another sum of partial vectors, in the same launch as this one's
 };
 
 template <typename T> hipError_t launch_linear(const LinearArgs &a, hipStream_t s);
