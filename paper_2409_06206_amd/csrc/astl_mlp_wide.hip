@@ -927,163 +927,214 @@ template <int KSC, int KSF> hipError_t launch_wide_bwd_t(const WideMlpBwdArgs &a
 
 
 // ---------------------------------------------------------------------------------------------------------
-// LayerNorm of bf16 rows in the lane pattern of this file: four lanes per row, 16 rows per wave, every load a
-// 16-byte piece that nothing touches until the whole tile of the NEXT iteration is on its way (2 KSC, or with
-// a second input 4 KSC, loads in flight per lane: what a streaming kernel needs to reach the memory's rate).
+// LayerNorm of bf16 rows and its adjoint, streaming kernels bound by memory.  Half a wavefront takes a row: lane l of 32
+// holds its dwords (two channels) l + 32 k, so that a load instruction reads whole cache lines of two neighbouring rows
+// and a lane keeps the same channels in every row: the adjoint's sums over rows stay in 2 x 2 NK registers until the end.
+// (With 16 rows to a load, four lanes each, an instruction touched 16 pieces of 64 bytes, a wavefront held 180 to 195
+// registers, two to a SIMD, and the sums over rows cost 16 lanes' additions per value and tile: 30.7 -> 19.4 and 15.4 -> 12.4 us for 65536 rows of 180, 4.9 and 3.8 TB/s.)
 // ---------------------------------------------------------------------------------------------------------
-constexpr int kLnRowsThreads = 256;
+constexpr int kLnRowsThreads = 256, kLnRowsWaves = kLnRowsThreads / 64;
+// pairs of rows a wavefront takes at a time; the next ones' loads are in flight meanwhile
+// (four pairs: the adjoint 143 registers and 33 us instead of 19, LayerNorm 13.2 instead of 12.4, 65536 rows of 180)
+constexpr int kLnRowsPairs = 2;
 
-template <int KSC>
+// sum over half a wavefront, in all its lanes
+__device__ __forceinline__ float half_sum(float v)
+{
+    v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0xB1, 0xf, 0xf, true));  // quad_perm [1,0,3,2]
+    v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x4E, 0xf, 0xf, true));  // quad_perm [2,3,0,1]
+    v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x141, 0xf, 0xf, true)); // row_half_mirror
+    v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x140, 0xf, 0xf, true)); // row_mirror
+    const unsigned u = __float_as_uint(v);
+    const u32x2 r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// Dwords l + 32 k of rows t0 + 2 r + half (rows beyond the last one: the last one; dwords beyond the row: its last one)
+template <int NK, int R> struct LnRows {
+    uint32_t v[R][NK];
+    __device__ __forceinline__ void load(const bf16_t *base, long t0, long rows, int C, int l, int half)
+    {
+        const uint32_t *b32 = reinterpret_cast<const uint32_t *>(base);
+        const int last = (C >> 1) - 1;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const long t = t0 + 2 * r + half;
+            const uint32_t *row = b32 + (t < rows ? t : rows - 1) * (C >> 1);
+#pragma unroll
+            for (int k = 0; k < NK; ++k) v[r][k] = row[k + 1 < NK || l + 32 * k <= last ? l + 32 * k : last];
+        }
+    }
+};
+
+// v / n with inv = 1 / n: the quotient rounded once, in three instructions instead of ten
+__device__ __forceinline__ float over(float v, float n, float inv)
+{
+    const float r = v * inv;
+    return fmaf(fmaf(-n, r, v), inv, r);
+}
+
+// mean and 1 / sqrt(var + eps) of a row, zero beyond C: the mean first, then the squared distances from it
+template <int NK> __device__ __forceinline__ float2 ln_row_stats(const uint32_t (&x)[NK], bool in, int C, float inv, float eps)
+{
+    float sum = 0.f, dev = 0.f;
+#pragma unroll
+    for (int k = 0; k < NK; ++k) sum += bf16_lo(x[k]) + bf16_hi(x[k]);
+    const float mean = over(half_sum(sum), (float)C, inv);
+#pragma unroll
+    for (int k = 0; k < NK; ++k) {
+        const float d0 = bf16_lo(x[k]) - mean, d1 = bf16_hi(x[k]) - mean;
+        if (k + 1 < NK || in) dev += d0 * d0 + d1 * d1;
+    }
+    return make_float2(mean, rsqrtf(over(half_sum(dev), (float)C, inv) + eps));
+}
+
+template <int NK>
 __global__ __launch_bounds__(kLnRowsThreads) void ln_rows_fwd_kernel(LnRowsArgs a)
 {
-    __shared__ float2 gb[32 * KSC];
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, tok = lane & 15, q = lane >> 4;
+    constexpr int R = kLnRowsPairs;
+    const int lane = threadIdx.x & 63, l = lane & 31, half = lane >> 5;
     const int C = a.C;
-    for (int c = tid; c < 32 * KSC; c += kLnRowsThreads)
-        gb[c] = c < C ? make_float2(bfv(a.gamma, c), bfv(a.beta, c)) : make_float2(0.f, 0.f);
-    const long ntiles = (a.rows + 15) / 16;
-    const long stride = (long)gridDim.x * (kLnRowsThreads / 64);
-    long tile = (long)blockIdx.x * (kLnRowsThreads / 64) + wv;
-    u32x4 ru[KSC], rv[KSC];
-    if (tile < ntiles) {
-        load_rows<KSC>(a.u, tile * 16 + tok, a.rows, C, q, ru);
-        if (a.add) load_rows<KSC>(a.add, tile * 16 + tok, a.rows, C, q, rv);
+    const float inv = 1.f / (float)C;
+    const bool in = l + 32 * (NK - 1) < (C >> 1); // (C > 64 (NK - 1): only a row's last dwords can be missing)
+    const long stride = (long)gridDim.x * kLnRowsWaves * 2 * R;
+    long t0 = ((long)blockIdx.x * kLnRowsWaves + (threadIdx.x >> 6)) * 2 * R;
+    LnRows<NK, R> u, v;
+    if (t0 < a.rows) {
+        u.load(a.u, t0, a.rows, C, l, half);
+        if (a.add) v.load(a.add, t0, a.rows, C, l, half);
     }
-    __syncthreads();
-    for (; tile < ntiles; tile += stride) {
-        const long t = tile * 16 + tok;
-        const bool ok = t < a.rows;
-        uint32_t x[KSC][4];
-        tidy_rows<KSC>(C, q, ru, x);
-        if (a.add) {
-            // the stored (rounded) sum is what gets normalised
-            uint32_t v[KSC][4];
-            tidy_rows<KSC>(C, q, rv, v);
+    float2 gam[NK], bet[NK];
 #pragma unroll
-            for (int p = 0; p < KSC; ++p)
+    for (int k = 0; k < NK; ++k) {
+        const int c = k + 1 < NK || in ? 2 * (l + 32 * k) : 0;
+        gam[k] = make_float2(bfv(a.gamma, c), bfv(a.gamma, c + 1));
+        bet[k] = make_float2(bfv(a.beta, c), bfv(a.beta, c + 1));
+    }
+    for (; t0 < a.rows; t0 += stride) {
+        uint32_t x[R][NK];
 #pragma unroll
-                for (int dw = 0; dw < 4; ++dw)
-                    x[p][dw] = pack_bf16x2(bf16_lo(x[p][dw]) + bf16_lo(v[p][dw]), bf16_hi(x[p][dw]) + bf16_hi(v[p][dw]));
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int k = 0; k < NK; ++k) {
+                x[r][k] = u.v[r][k];
+                // the stored (rounded) sum is what gets normalised
+                if (a.add) x[r][k] = pack_bf16x2(bf16_lo(x[r][k]) + bf16_lo(v.v[r][k]), bf16_hi(x[r][k]) + bf16_hi(v.v[r][k]));
+                if (k + 1 == NK && !in) x[r][k] = 0u;
+            }
+        if (t0 + stride < a.rows) {
+            u.load(a.u, t0 + stride, a.rows, C, l, half);
+            if (a.add) v.load(a.add, t0 + stride, a.rows, C, l, half);
         }
-        if (tile + stride < ntiles) { // the next tile's rows are on their way while this one is computed
-            load_rows<KSC>(a.u, t + stride * 16, a.rows, C, q, ru);
-            if (a.add) load_rows<KSC>(a.add, t + stride * 16, a.rows, C, q, rv);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const long t = t0 + 2 * r + half;
+            const float2 st = ln_row_stats<NK>(x[r], in, C, inv, a.eps);
+            if (t >= a.rows) continue;
+#pragma unroll
+            for (int k = 0; k < NK; ++k) {
+                if (k + 1 == NK && !in) continue;
+                const long at = t * (C >> 1) + l + 32 * k;
+                if (a.add && a.sum_out) reinterpret_cast<uint32_t *>(a.sum_out)[at] = x[r][k];
+                reinterpret_cast<uint32_t *>(a.out)[at] =
+                    pack_bf16x2((bf16_lo(x[r][k]) - st.x) * st.y * gam[k].x + bet[k].x, (bf16_hi(x[r][k]) - st.x) * st.y * gam[k].y + bet[k].y);
+            }
         }
-        if (a.add && a.sum_out) store_rows<KSC>(a.sum_out, t, ok, C, q, x);
-        layer_norm_rows<KSC>(x, C, q, a.eps, gb);
-        store_rows<KSC>(a.out, t, ok, C, q, x);
     }
 }
 
 
-// LayerNorm's adjoint of the same rows, same lane pattern: with xh = (u - mean) rstd and g = dout gamma,
+// LayerNorm's adjoint of the same rows: with xh = (u - mean) rstd and g = dout gamma,
 //   du = rstd (g - mean(g) - xh mean(g xh)) (+ res);   d gamma = sum_t dout xh;   d beta = sum_t dout.
-// The sums over rows as in the MLP backward kernel above (row shifts, per-wave sums in LDS); every workgroup
-// writes ONE vector [d gamma: C | d beta: C] of its own, which the caller sums in a fixed order: no atomics.
-template <int KSC>
+// Every workgroup writes ONE vector [d gamma: C | d beta: C] of its own, which the caller sums in a fixed order: no
+// atomics.
+template <int NK>
 __global__ __launch_bounds__(kLnRowsThreads) void ln_rows_bwd_kernel(LnRowsBwdArgs a)
 {
-    constexpr int NW = kLnRowsThreads / 64;
-    __shared__ float gam[32 * KSC];
-    __shared__ __attribute__((aligned(16))) float gsum_all[NW * 4 * 2 * 8 * KSC];
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, tok = lane & 15, q = lane >> 4;
+    constexpr int R = kLnRowsPairs;
+    __shared__ float2 sums[kLnRowsWaves][2][32 * NK];
+    const int lane = threadIdx.x & 63, l = lane & 31, half = lane >> 5, wv = threadIdx.x >> 6;
     const int C = a.C;
-    for (int c = tid; c < 32 * KSC; c += kLnRowsThreads) gam[c] = c < C ? bfv(a.gamma, c) : 0.f;
-    for (int i = tid; i < NW * 4 * 2 * 8 * KSC; i += kLnRowsThreads) gsum_all[i] = 0.f;
-    __syncthreads();
-    float *gsum = gsum_all + (wv * 4 + q) * (2 * 8 * KSC);
-    const long ntiles = (a.rows + 15) / 16;
-    const long stride = (long)gridDim.x * NW;
-    for (long tile = (long)blockIdx.x * NW + wv; tile < ntiles; tile += stride) {
-        const long t = tile * 16 + tok;
-        const bool ok = t < a.rows;
-        u32x4 ru[KSC], rd[KSC], rr[KSC];
-        load_rows<KSC>(a.u, t, a.rows, C, q, ru);
-        load_rows<KSC>(a.dout, t, a.rows, C, q, rd);
-        if (a.res) load_rows<KSC>(a.res, t, a.rows, C, q, rr);
-        uint32_t xu[KSC][4], xd[KSC][4];
-        tidy_rows<KSC>(C, q, ru, xu);
-        tidy_rows<KSC>(C, q, rd, xd);
-        int qq = q;
-        asm volatile("" : "+v"(qq));
-        // mean and 1 / sqrt(var + eps) as the forward kernels take them
-        float sum = 0.f;
+    const float inv = 1.f / (float)C;
+    const bool in = l + 32 * (NK - 1) < (C >> 1);
+    const long stride = (long)gridDim.x * kLnRowsWaves * 2 * R;
+    long t0 = ((long)blockIdx.x * kLnRowsWaves + wv) * 2 * R;
+    LnRows<NK, R> u, d, e;
+    auto load = [&](long t) {
+        u.load(a.u, t, a.rows, C, l, half);
+        d.load(a.dout, t, a.rows, C, l, half);
+        if (a.res) e.load(a.res, t, a.rows, C, l, half);
+    };
+    if (t0 < a.rows) load(t0);
+    float2 gam[NK], pg[NK], pb[NK];
 #pragma unroll
-        for (int p = 0; p < KSC; ++p)
+    for (int k = 0; k < NK; ++k) {
+        const int c = k + 1 < NK || in ? 2 * (l + 32 * k) : 0;
+        gam[k] = make_float2(bfv(a.gamma, c), bfv(a.gamma, c + 1));
+        pg[k] = pb[k] = make_float2(0.f, 0.f);
+    }
+    for (; t0 < a.rows; t0 += stride) {
+        uint32_t x[R][NK], y[R][NK], z[R][NK];
 #pragma unroll
-            for (int dw = 0; dw < 4; ++dw) sum += bf16_lo(xu[p][dw]) + bf16_hi(xu[p][dw]);
-        const float mean = qgroup_sum(sum) / (float)C;
-        float dev = 0.f, s1 = 0.f, s2 = 0.f;
+        for (int r = 0; r < R; ++r)
 #pragma unroll
-        for (int p = 0; p < KSC; ++p)
+            for (int k = 0; k < NK; ++k) {
+                const bool have = k + 1 < NK || in;
+                x[r][k] = have ? u.v[r][k] : 0u;
+                y[r][k] = have && t0 + 2 * r + half < a.rows ? d.v[r][k] : 0u; // (a row that is not there counts nowhere)
+                z[r][k] = a.res ? e.v[r][k] : 0u;
+            }
+        if (t0 + stride < a.rows) load(t0 + stride);
 #pragma unroll
-            for (int dw = 0; dw < 4; ++dw)
-                if (32 * p + 8 * qq + 2 * dw < C) {
-                    const float d0 = bf16_lo(xu[p][dw]) - mean, d1 = bf16_hi(xu[p][dw]) - mean;
-                    dev += d0 * d0 + d1 * d1;
-                }
-        const float rstd = rsqrtf(qgroup_sum(dev) / (float)C + a.eps);
+        for (int r = 0; r < R; ++r) {
+            const long t = t0 + 2 * r + half;
+            const float2 st = ln_row_stats<NK>(x[r], in, C, inv, a.eps);
+            float2 h[NK];
+            float s1 = 0.f, s2 = 0.f;
 #pragma unroll
-        for (int p = 0; p < KSC; ++p)
-#pragma unroll
-            for (int dw = 0; dw < 4; ++dw) {
-                const int c = 32 * p + 8 * qq + 2 * dw;
-                const bool in = c < C;
-                const float2 gm = *reinterpret_cast<const float2 *>(gam + c);
-                const float g0 = bf16_lo(xd[p][dw]) * gm.x, g1 = bf16_hi(xd[p][dw]) * gm.y;
-                const float h0 = in ? (bf16_lo(xu[p][dw]) - mean) * rstd : 0.f;
-                const float h1 = in ? (bf16_hi(xu[p][dw]) - mean) * rstd : 0.f;
+            for (int k = 0; k < NK; ++k) {
+                const float d0 = bf16_lo(y[r][k]), d1 = bf16_hi(y[r][k]), g0 = d0 * gam[k].x, g1 = d1 * gam[k].y;
+                h[k] = make_float2((bf16_lo(x[r][k]) - st.x) * st.y, (bf16_hi(x[r][k]) - st.x) * st.y);
+                pg[k].x += d0 * h[k].x;
+                pg[k].y += d1 * h[k].y;
+                pb[k].x += d0;
+                pb[k].y += d1;
                 s1 += g0 + g1;
-                s2 += g0 * h0 + g1 * h1;
+                s2 += g0 * h[k].x + g1 * h[k].y; // (beyond C the gradient is zero)
             }
-        s1 = qgroup_sum(s1) / (float)C;
-        s2 = qgroup_sum(s2) / (float)C;
-        uint32_t xr[KSC][4];
-        if (a.res) tidy_rows<KSC>(C, q, rr, xr);
+            s1 = over(half_sum(s1), (float)C, inv);
+            s2 = over(half_sum(s2), (float)C, inv);
+            if (t >= a.rows) continue;
 #pragma unroll
-        for (int p = 0; p < KSC; ++p) {
-            float pg[8], pb[8];
-            uint32_t duo[4];
-#pragma unroll
-            for (int dw = 0; dw < 4; ++dw) {
-                const int c = 32 * p + 8 * qq + 2 * dw;
-                const bool in = c < C;
-                const float2 gm = *reinterpret_cast<const float2 *>(gam + c);
-                const float d0 = bf16_lo(xd[p][dw]), d1 = bf16_hi(xd[p][dw]);
-                const float h0 = in ? (bf16_lo(xu[p][dw]) - mean) * rstd : 0.f;
-                const float h1 = in ? (bf16_hi(xu[p][dw]) - mean) * rstd : 0.f;
-                float o0 = rstd * (d0 * gm.x - s1 - h0 * s2), o1 = rstd * (d1 * gm.y - s1 - h1 * s2);
-                if (a.res) { o0 += bf16_lo(xr[p][dw]); o1 += bf16_hi(xr[p][dw]); }
-                duo[dw] = pack_bf16x2(o0, o1);
-                // (rows beyond the last one repeat the last one: they must not be counted)
-                pg[2 * dw] = ok ? d0 * h0 : 0.f; pg[2 * dw + 1] = ok ? d1 * h1 : 0.f;
-                pb[2 * dw] = ok ? d0 : 0.f; pb[2 * dw + 1] = ok ? d1 : 0.f;
-            }
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                pg[j] = row_sum_in_last_lane(pg[j]);
-                pb[j] = row_sum_in_last_lane(pb[j]);
-            }
-            store_piece<KSC>(a.du, t, ok, C, qq, p, duo);
-            if (tok == 15) { // the row's last lane adds the 16 rows' sums to the wave's own
-                float4 *ag = reinterpret_cast<float4 *>(gsum + 8 * p), *ab = reinterpret_cast<float4 *>(gsum + 8 * KSC + 8 * p);
-                const float4 a0 = ag[0], a1 = ag[1], b0 = ab[0], b1 = ab[1];
-                ag[0] = make_float4(a0.x + pg[0], a0.y + pg[1], a0.z + pg[2], a0.w + pg[3]);
-                ag[1] = make_float4(a1.x + pg[4], a1.y + pg[5], a1.z + pg[6], a1.w + pg[7]);
-                ab[0] = make_float4(b0.x + pb[0], b0.y + pb[1], b0.z + pb[2], b0.w + pb[3]);
-                ab[1] = make_float4(b1.x + pb[4], b1.y + pb[5], b1.z + pb[6], b1.w + pb[7]);
+            for (int k = 0; k < NK; ++k) {
+                if (k + 1 == NK && !in) continue;
+                float o0 = st.y * (bf16_lo(y[r][k]) * gam[k].x - s1 - h[k].x * s2), o1 = st.y * (bf16_hi(y[r][k]) * gam[k].y - s1 - h[k].y * s2);
+                if (a.res) { o0 += bf16_lo(z[r][k]); o1 += bf16_hi(z[r][k]); }
+                reinterpret_cast<uint32_t *>(a.du)[t * (C >> 1) + l + 32 * k] = pack_bf16x2(o0, o1);
             }
         }
     }
+    // the two halves of a wavefront, then the wavefronts
+    auto both = [](float v) {
+        const unsigned w = __float_as_uint(v);
+        const u32x2 r = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+        return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    };
+#pragma unroll
+    for (int k = 0; k < NK; ++k) {
+        const float2 g = make_float2(both(pg[k].x), both(pg[k].y)), b = make_float2(both(pb[k].x), both(pb[k].y));
+        if (half == 0) {
+            sums[wv][0][l + 32 * k] = g;
+            sums[wv][1][l + 32 * k] = b;
+        }
+    }
     __syncthreads();
-    for (int i = tid; i < 2 * 32 * KSC; i += kLnRowsThreads) {
-        const int which = i / (32 * KSC), c = i - which * (32 * KSC);
-        if (c >= C) continue;
-        const int p = c >> 5, cq = (c >> 3) & 3, j = c & 7;
+    for (int i = threadIdx.x; i < 2 * C; i += kLnRowsThreads) {
+        const int which = i >= C ? 1 : 0, c = i - which * C;
         float sum = 0.f;
 #pragma unroll
-        for (int w = 0; w < NW; ++w) sum += gsum_all[(w * 4 + cq) * (2 * 8 * KSC) + which * 8 * KSC + 8 * p + j];
-        a.part[(size_t)blockIdx.x * 2 * C + which * C + c] = sum;
+        for (int w = 0; w < kLnRowsWaves; ++w) sum += reinterpret_cast<const float *>(sums[w][which])[c];
+        a.part[(size_t)blockIdx.x * 2 * C + i] = sum;
     }
 }
 
@@ -1157,7 +1208,7 @@ int astl_mlp_wide_bwd_blocks(long rows)
 int ln_rows_bwd_blocks(long rows)
 {
     const long tiles = (rows + 15) / 16;
-    long blocks = (tiles + kLnRowsThreads / 64 - 1) / (kLnRowsThreads / 64);
+    long blocks = (tiles + kLnRowsWaves - 1) / kLnRowsWaves;
     const long cap = 4L * device_cu_count();
     if (blocks > cap) blocks = cap;
     return (int)(blocks < 1 ? 1 : blocks);
@@ -1167,21 +1218,20 @@ hipError_t launch_ln_rows_bwd(const LnRowsBwdArgs &a, hipStream_t s)
 {
     if (!ln_rows_supported(a.C) || a.rows <= 0 || !a.part) return hipErrorInvalidValue;
     const dim3 grid((unsigned)ln_rows_bwd_blocks(a.rows)), block(kLnRowsThreads);
-    if (a.C <= 128) hipLaunchKernelGGL(ln_rows_bwd_kernel<4>, grid, block, 0, s, a);
-    else hipLaunchKernelGGL(ln_rows_bwd_kernel<6>, grid, block, 0, s, a);
+    if (a.C <= 128) hipLaunchKernelGGL(ln_rows_bwd_kernel<2>, grid, block, 0, s, a);
+    else hipLaunchKernelGGL(ln_rows_bwd_kernel<3>, grid, block, 0, s, a);
     return hipGetLastError();
 }
 
 hipError_t launch_ln_rows_fwd(const LnRowsArgs &a, hipStream_t s)
 {
     if (!ln_rows_supported(a.C) || a.rows <= 0) return hipErrorInvalidValue;
-    const long tiles = (a.rows + 15) / 16;
-    long blocks = (tiles + kLnRowsThreads / 64 - 1) / (kLnRowsThreads / 64);
-    const long cap = 8L * device_cu_count(); // (eight workgroups of four waves per compute unit: one pass at 131072 rows)
+    long blocks = (a.rows + 2 * kLnRowsPairs * kLnRowsWaves - 1) / (2 * kLnRowsPairs * kLnRowsWaves);
+    const long cap = 8L * device_cu_count();
     if (blocks > cap) blocks = cap;
     const dim3 grid((unsigned)blocks), block(kLnRowsThreads);
-    if (a.C <= 128) hipLaunchKernelGGL(ln_rows_fwd_kernel<4>, grid, block, 0, s, a);
-    else hipLaunchKernelGGL(ln_rows_fwd_kernel<6>, grid, block, 0, s, a);
+    if (a.C <= 128) hipLaunchKernelGGL(ln_rows_fwd_kernel<2>, grid, block, 0, s, a);
+    else hipLaunchKernelGGL(ln_rows_fwd_kernel<3>, grid, block, 0, s, a);
     return hipGetLastError();
 }
 

@@ -238,6 +238,8 @@ def test_padding_edges_of_the_fused_mlp_tiles(C, hidden):
     dict(B=2, H=4, W=4, C=4, heads=2, groups=2, window=2, shift=1, dtype="bf16", hidden=4),
     dict(B=2, H=4, W=4, C=8, heads=2, groups=1, window=4, shift=2, dtype="f32", hidden=7),
     dict(B=1, H=8, W=8, C=20, heads=2, groups=2, window=4, shift=0, dtype="bf16", hidden=36),
+    dict(B=1, H=5, W=5, C=68, heads=2, groups=1, window=5, shift=2, dtype="bf16", hidden=32),   # 25 rows: half a pair
+    dict(B=1, H=7, W=21, C=132, heads=4, groups=1, window=7, shift=3, dtype="bf16", hidden=64), # 147
 ], ids=_id)
 def test_extreme_widths(case):
     """The widest supported map (256 channels), the narrowest fused one, an odd hidden width."""
