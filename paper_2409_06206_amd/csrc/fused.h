@@ -260,18 +260,22 @@ struct ReduceJob {
     int accumulate;
 };
 hipError_t launch_reduce_pair(const ReduceJob &a, const ReduceJob &b, hipStream_t s);
+// the same with a third, whose vectors are about as long as the first's
+hipError_t launch_reduce_three(const ReduceJob &a, const ReduceJob &b, const ReduceJob &c, hipStream_t s);
 
 // Wide layers (C = 180, two or three groups, 8x8 windows), backward of the attention and of the QKV
 // projection, group by group in reverse order (wide_bwd.hip): one launch with one wavefront per
 // window recomputes the group's q, k, v and probabilities and leaves d(q|k|v) in scratch and the
 // bias-table gradient as per-workgroup partial sums; a second launch turns d(q|k|v) into the
 // group's dx slice (the cascade gradient of the group before, Eq. 8) and its weight gradients.
-// d w_proj / d b_proj are not produced here.
+// d w_proj / d b_proj are not produced here.  The sums of the last group's weight gradients (sums[0]) and of the table
+// (sums[1]) are left to the caller; until they have run, only the first wide_bwd_free_bytes of the scratch are free.
 bool wide_bwd_supported(const Geom &g);
 size_t wide_bwd_ws_bytes(const Geom &g);
+size_t wide_bwd_free_bytes(const Geom &g);
 hipError_t launch_wide_bwd(const Geom &g, const bf16_t *x, const bf16_t *dy, const bf16_t *attn, const void *pack,
                            bf16_t *dx, float *dw_qkv, float *db_qkv, float *dtable, int accumulate, void *ws,
-                           hipStream_t s);
+                           ReduceJob (&sums)[2], hipStream_t s);
 
 bool fused_bwd_supported(const Geom &g);
 // Scratch of the fused backward: per-workgroup partial parameter gradients.

@@ -849,15 +849,18 @@ __global__ __launch_bounds__(1024) void reduce_partials_kernel(const float *__re
 }
 
 // Two sums in one launch: blocks [0, blocks1) take the second (one entry per load: the short vectors of a bias-table
-// gradient, of which there may be many, so these blocks start first), the others the first (V entries per load).
+// gradient, of which there may be many, so these blocks start first), the others the first (V entries per load); blocks2
+// blocks between them, if any, a third like the first.
 template <int V>
-__global__ __launch_bounds__(1024) void reduce_partials_pair_kernel(ReduceJob j0, int blocks1, ReduceJob j1)
+__global__ __launch_bounds__(1024) void reduce_partials_pair_kernel(ReduceJob j0, int blocks1, ReduceJob j1, int blocks2, ReduceJob j2)
 {
     __shared__ float red[32 * (32 * V + 1)];
     if ((int)blockIdx.x < blocks1)
         reduce_partials_block<1>(j1.part, j1.nparts, j1.n, j1.out, j1.accumulate, (int)blockIdx.x, red);
+    else if ((int)blockIdx.x < blocks1 + blocks2)
+        reduce_partials_block<V>(j2.part, j2.nparts, j2.n, j2.out, j2.accumulate, (int)blockIdx.x - blocks1, red);
     else
-        reduce_partials_block<V>(j0.part, j0.nparts, j0.n, j0.out, j0.accumulate, (int)blockIdx.x - blocks1, red);
+        reduce_partials_block<V>(j0.part, j0.nparts, j0.n, j0.out, j0.accumulate, (int)blockIdx.x - blocks1 - blocks2, red);
 }
 
 // d w_proj, d b_proj of wide layers: dY^T [A | 1] over plain token rows, 128 tokens per pass of a workgroup
@@ -1019,11 +1022,11 @@ struct GradOut {
 } // namespace
 
 // entries per load: two or four where every partial vector starts on such a boundary and enough workgroups
-// remain to fill the chip
+// remain to fill the chip (24570 entries, 256 vectors: 192 workgroups of four entries a load 7.9 us, 384 of two 8.8)
 static int reduce_width(const float *part, int n)
 {
     const uintptr_t at = reinterpret_cast<uintptr_t>(part);
-    if (n % 4 == 0 && at % 16 == 0 && n >= 200 * 128) return 4;
+    if (n % 4 == 0 && at % 16 == 0 && n >= 180 * 128) return 4;
     if (n % 2 == 0 && at % 8 == 0 && n >= 200 * 64) return 2;
     return 1;
 }
@@ -1039,19 +1042,22 @@ hipError_t launch_reduce(const float *part, int nparts, int n, const ReduceOut &
     return hipGetLastError();
 }
 
-hipError_t launch_reduce_pair(const ReduceJob &a, const ReduceJob &b, hipStream_t s)
+hipError_t launch_reduce_three(const ReduceJob &a, const ReduceJob &b, const ReduceJob &c, hipStream_t s)
 {
     KernelTimer kt(K_REDUCE, s);
-    const int v = reduce_width(a.part, a.n);
-    const int blocks0 = (a.n + 32 * v - 1) / (32 * v), blocks1 = (b.n + 31) / 32;
-    const dim3 grid(blocks0 + blocks1);
+    int v = reduce_width(a.part, a.n);
+    if (c.n > 0 && reduce_width(c.part, c.n) < v) v = reduce_width(c.part, c.n);
+    const int blocks0 = (a.n + 32 * v - 1) / (32 * v), blocks1 = (b.n + 31) / 32, blocks2 = (c.n + 32 * v - 1) / (32 * v);
+    const dim3 grid(blocks0 + blocks1 + blocks2);
     switch (v) {
-    case 4: hipLaunchKernelGGL(reduce_partials_pair_kernel<4>, grid, dim3(1024), 0, s, a, blocks1, b); break;
-    case 2: hipLaunchKernelGGL(reduce_partials_pair_kernel<2>, grid, dim3(1024), 0, s, a, blocks1, b); break;
-    default: hipLaunchKernelGGL(reduce_partials_pair_kernel<1>, grid, dim3(1024), 0, s, a, blocks1, b); break;
+    case 4: hipLaunchKernelGGL(reduce_partials_pair_kernel<4>, grid, dim3(1024), 0, s, a, blocks1, b, blocks2, c); break;
+    case 2: hipLaunchKernelGGL(reduce_partials_pair_kernel<2>, grid, dim3(1024), 0, s, a, blocks1, b, blocks2, c); break;
+    default: hipLaunchKernelGGL(reduce_partials_pair_kernel<1>, grid, dim3(1024), 0, s, a, blocks1, b, blocks2, c); break;
     }
     return hipGetLastError();
 }
+
+hipError_t launch_reduce_pair(const ReduceJob &a, const ReduceJob &b, hipStream_t s) { return launch_reduce_three(a, b, ReduceJob{}, s); }
 
 namespace {
 
@@ -1126,10 +1132,10 @@ template <class Cf, int I = 0> constexpr int max_partial()
     }
 }
 
-// d w_proj, d b_proj of a wide layer: the kernel, then the sum of its partials.
+// d w_proj, d b_proj of a wide layer: the kernel, then the sum of its partials, in the launch of `sums` where there are any.
 template <class Cf>
 hipError_t run_wproj_grad(const Geom &g, int grid, const bf16_t *dy, const bf16_t *attn, float *part, float *dw_proj,
-                          float *db_proj, int accumulate, hipStream_t s)
+                          float *db_proj, int accumulate, const ReduceJob *sums, hipStream_t s)
 {
     using P = WprojGradCfg<Cf>;
     constexpr size_t lds = P::LDS_BYTES;
@@ -1141,12 +1147,13 @@ hipError_t run_wproj_grad(const Geom &g, int grid, const bf16_t *dy, const bf16_
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    ReduceOut out{};
-    out.ptr[0] = dw_proj; out.begin[0] = 0;
-    out.ptr[1] = db_proj; out.begin[1] = Cf::C * Cf::C;
-    out.begin[2] = Cf::C * Cf::C + Cf::C;
-    out.nseg = 2;
-    return launch_reduce(part, grid, Cf::C * Cf::C + Cf::C, out, accumulate, s);
+    ReduceJob j{};
+    j.part = part; j.nparts = grid; j.n = Cf::C * Cf::C + Cf::C; j.accumulate = accumulate;
+    j.out.ptr[0] = dw_proj; j.out.begin[0] = 0;
+    j.out.ptr[1] = db_proj; j.out.begin[1] = Cf::C * Cf::C;
+    j.out.begin[2] = Cf::C * Cf::C + Cf::C;
+    j.out.nseg = 2;
+    return sums ? launch_reduce_three(sums[0], sums[1], j, s) : launch_reduce(part, grid, j.n, j.out, accumulate, s);
 }
 
 template <class Cf>
@@ -1158,16 +1165,22 @@ hipError_t run_bwd(const Geom &g, const bf16_t *x, const bf16_t *dy, const bf16_
     float *part = static_cast<float *>(ws);
     const int grid = bwd_grid(g, device_cu_count());
     if constexpr (Cf::SPLIT) {
-        if (wide_bwd_supported(g)) { // (16-byte aligned tensors: the entry points check; the projection's gradient reuses the scratch afterwards)
-            hipError_t e = launch_wide_bwd(g, x, dy, attn, pack_, dx, dw_qkv, db_qkv, dtable, accumulate, ws, s);
+        if (wide_bwd_supported(g)) { // (16-byte aligned tensors: the entry points check)
+            ReduceJob sums[2];
+            hipError_t e = launch_wide_bwd(g, x, dy, attn, pack_, dx, dw_qkv, db_qkv, dtable, accumulate, ws, sums, s);
             if (e != hipSuccess) return e;
-            return run_wproj_grad<Cf>(g, grid, dy, attn, part, dw_proj, db_proj, accumulate, s);
+            // The projection's partial vectors take the place of d(q|k|v).  Where that is too small for them (few windows for
+            // the compute units) the sums before have to run first: a launch more.  (One launch for the last three sums and
+            // the wider loads of reduce_width: 32 images of 64x64, forward + backward, 340 -> 335 us.)
+            const bool fits = (size_t)grid * (Cf::C * Cf::C + Cf::C) * sizeof(float) <= wide_bwd_free_bytes(g);
+            if (!fits && (e = launch_reduce_pair(sums[0], sums[1], s)) != hipSuccess) return e;
+            return run_wproj_grad<Cf>(g, grid, dy, attn, part, dw_proj, db_proj, accumulate, fits ? sums : nullptr, s);
         }
     }
     const GradOut go{dw_qkv, db_qkv, dw_proj, db_proj, dtable, accumulate};
     hipError_t e = launch_chunks<Cf>(g, grid, x, dy, attn, pack, table, dx, part, go, s);
     if (e != hipSuccess) return e;
-    if constexpr (Cf::SPLIT) return run_wproj_grad<Cf>(g, grid, dy, attn, part, dw_proj, db_proj, accumulate, s);
+    if constexpr (Cf::SPLIT) return run_wproj_grad<Cf>(g, grid, dy, attn, part, dw_proj, db_proj, accumulate, nullptr, s);
     return hipSuccess;
 }
 

@@ -852,7 +852,7 @@ hipError_t run_group(const Geom &g, int grid, const bf16_t *x, const bf16_t *dy,
     out.begin[2] = W::L_END;
     out.nseg = 2;
     const int nparts = grid < (g.nW + 1) / 2 ? grid : (g.nW + 1) / 2;
-    if (GI == 0 && last) { // (the last group's sum shares a launch with the bias table's)
+    if (GI == 0 && last) { // (the last group's sum shares a launch with others)
         last->part = part; last->nparts = nparts; last->n = W::L_TOTAL; last->out = out; last->accumulate = accumulate;
         return hipSuccess;
     }
@@ -873,7 +873,8 @@ hipError_t run_groups(const Geom &g, int grid, const bf16_t *x, const bf16_t *dy
 
 template <class Cf>
 hipError_t run_wide_bwd(const Geom &g, const bf16_t *x, const bf16_t *dy, const bf16_t *attn, const uint8_t *pack,
-                        bf16_t *dx, float *dw_qkv, float *db_qkv, float *dtable, int accumulate, void *ws, hipStream_t s)
+                        bf16_t *dx, float *dw_qkv, float *db_qkv, float *dtable, int accumulate, void *ws, ReduceJob (&sums)[2],
+                        hipStream_t s)
 {
     using W = WideBwdCfg<Cf>;
     using Ws = WideBwdWs<Cf>;
@@ -884,7 +885,8 @@ hipError_t run_wide_bwd(const Geom &g, const bf16_t *x, const bf16_t *dy, const 
     uint8_t *cgf = base + Ws::dqkv_bytes(g) + Ws::part_bytes(g) + Ws::tbl_bytes(g);
     uint8_t *ffr = cgf + Ws::cg_bytes(g);
     const int grid = attn_grid(g, device_cu_count());
-    ReduceJob last{};
+    ReduceJob &last = sums[0], &tbl = sums[1];
+    last = tbl = ReduceJob{};
     hipError_t e = run_groups<Cf, Cf::G - 1>(g, grid, x, dy, attn, pack, dx, dw_qkv, db_qkv, accumulate, dqkv, part,
                                              tpart, cgf, ffr, &last, s);
     if (e != hipSuccess) return e;
@@ -893,9 +895,8 @@ hipError_t run_wide_bwd(const Geom &g, const bf16_t *x, const bf16_t *dy, const 
     out.begin[1] = Cf::HEADS * W::NTBL;
     out.nseg = 1;
     out.tbl_heads = Cf::HEADS; out.tbl_entries = W::NTBL; out.tbl_stride = Cf::HEADS; out.tbl_head0 = 0;
-    ReduceJob tbl{};
     tbl.part = tpart; tbl.nparts = grid; tbl.n = Cf::HEADS * W::NTBL; tbl.out = out; tbl.accumulate = accumulate;
-    return launch_reduce_pair(last, tbl, s);
+    return hipSuccess;
 }
 
 #define GSWA_WIDE_BWD_SHAPES(X) X(180, 6, 2) X(180, 6, 3)
@@ -928,14 +929,23 @@ size_t wide_bwd_ws_bytes(const Geom &g)
     return 0;
 }
 
+size_t wide_bwd_free_bytes(const Geom &g)
+{
+#define X(C_, H_, G_) \
+    if (g.C == C_ && g.heads == H_ && g.groups == G_) return WideBwdWs<FusedCfg<C_, H_, G_>>::dqkv_bytes(g);
+    GSWA_WIDE_BWD_SHAPES(X)
+#undef X
+    return 0;
+}
+
 hipError_t launch_wide_bwd(const Geom &g, const bf16_t *x, const bf16_t *dy, const bf16_t *attn, const void *pack,
                            bf16_t *dx, float *dw_qkv, float *db_qkv, float *dtable, int accumulate, void *ws,
-                           hipStream_t s)
+                           ReduceJob (&sums)[2], hipStream_t s)
 {
 #define X(C_, H_, G_)                                                                                            \
     if (g.C == C_ && g.heads == H_ && g.groups == G_)                                                            \
         return run_wide_bwd<FusedCfg<C_, H_, G_>>(g, x, dy, attn, static_cast<const uint8_t *>(pack), dx, dw_qkv, \
-                                                  db_qkv, dtable, accumulate, ws, s);
+                                                  db_qkv, dtable, accumulate, ws, sums, s);
     GSWA_WIDE_BWD_SHAPES(X)
 #undef X
     return hipErrorInvalidValue;

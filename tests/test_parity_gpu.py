@@ -69,6 +69,28 @@ def test_forced_staged_path_one_group_many_tokens(oracle, C, heads):
                       extra_flags=gswa.GSWA_FORCE_STAGED)
 
 
+@pytest.mark.parametrize("rows,cols", [(8, 113), (5, 181)])
+def test_last_sums_of_a_wide_backward_in_two_launches_and_in_one(oracle, rows, cols):
+    """904 and 905 windows of 180 channels, two groups: the projection's partial vectors (256 compute units) do not fit
+    the place of d(q|k|v), and just fill it, while the other sums still have to be taken; here all are added."""
+    import torch
+    from paper_2409_06206_amd import gswa, runner
+    H, W = 8 * rows, 8 * cols
+    x, dy, p = parity.make_inputs(1, H, W, 180, 6, 2, 8, "bf16", synth.LAYER_SEED0 + 3, "stress")
+    layer = runner.DeviceLayer(1, H, W, 180, 6, 2, 8, 4, "bf16", gswa.GSWA_ACCUM_WGRAD)
+    layer.set_params(p)
+    layer.set_inputs(x, dy)
+    for g in layer.grads.values():
+        g.fill_(0.5)
+    layer.forward()
+    layer.backward()
+    torch.cuda.synchronize()
+    got = layer.results()
+    want = parity.oracle_results(oracle, x, dy, p, 6, 2, 8, 4)
+    for k in parity.GRAD_NAMES:
+        assert parity.rel_err(got[k] - (0.5 if k != "dx" else 0.0), want[k]) <= parity.TOL["bf16"], k
+
+
 @pytest.mark.parametrize("accumulate", [False, True])
 @pytest.mark.parametrize("B,H,W", [(1, 64, 64), (1, 64, 72), (1, 64, 80), (3, 56, 72)])
 def test_one_group_of_a_wide_layer_sums_its_gradients_directly(oracle, B, H, W, accumulate):
