@@ -27,11 +27,11 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0
 # the launch kinds of that kernel), valid only for the kernel source they were taken on:
 # {(workload, groups, kernel): (source file, sha256 of it, bytes per launch)}
 MEASURED_TRAFFIC = {
-    ("c4", 2, "wide_attn_bwd"): ("wide_bwd.hip", "352693d517081ee0c33c35060cc3f2ac5a2649ebcfd12444c2cc316d892ad1e2", 229522842),
-    ("c3", 2, "wide_attn_bwd"): ("wide_bwd.hip", "352693d517081ee0c33c35060cc3f2ac5a2649ebcfd12444c2cc316d892ad1e2", 115178291),
-    ("c2", 2, "fused_bwd"): ("fused_bwd.hip", "045736001555f81e0501be67670f7af0f1ac71b801671cb1e812f83f53afcbf1", 74098790),
-    ("c5_m8", 2, "fused_fwd"): ("wide_fwd.hip", "98163ed852681e2c18862150cd6b51ab1f4d47b54d1aeb9a3572bef3389a5f4b", 238839398),
-    ("c5_m16", 2, "fused_fwd"): ("wide_fwd.hip", "98163ed852681e2c18862150cd6b51ab1f4d47b54d1aeb9a3572bef3389a5f4b", 240262861),
+    ("c4", 2, "wide_attn_bwd"): ("wide_bwd.hip", "542575f85bb32af15785402762cfeba8b0857aef2d9ed64e0e9316358bad860b", 229492499),
+    ("c3", 2, "wide_attn_bwd"): ("wide_bwd.hip", "542575f85bb32af15785402762cfeba8b0857aef2d9ed64e0e9316358bad860b", 115818984),
+    ("c2", 2, "fused_bwd"): ("fused_bwd.hip", "b02edb8e90f33d0b430c0c54ff57215565e8927ab397e0e61b9a7af641ac50bb", 74098978),
+    ("c5_m8", 2, "fused_fwd"): ("wide_fwd.hip", "3a045cb1571dda4b176ffd6295e73fed859232efe85b4d08bb43f1dd406cb3e9", 238957256),
+    ("c5_m16", 2, "fused_fwd"): ("wide_fwd.hip", "3a045cb1571dda4b176ffd6295e73fed859232efe85b4d08bb43f1dd406cb3e9", 239763192),
 }
 
 
