@@ -92,15 +92,15 @@ def test_last_sums_of_a_wide_backward_in_two_launches_and_in_one(oracle, rows, c
 
 
 @pytest.mark.parametrize("accumulate", [False, True])
-@pytest.mark.parametrize("B,H,W", [(1, 64, 64), (1, 64, 72), (1, 64, 80), (3, 56, 72)])
-def test_one_group_of_a_wide_layer_sums_its_gradients_directly(oracle, B, H, W, accumulate):
+@pytest.mark.parametrize("B,H,W,window", [(1, 64, 64, 8), (1, 64, 72, 8), (1, 64, 80, 8), (3, 56, 72, 8), (1, 72, 72, 12)])
+def test_one_group_of_a_wide_layer_sums_its_gradients_directly(oracle, B, H, W, window, accumulate):
     """180 channels, one group, from 4096 tokens on: weight gradients and the sum of the windows' bias-table gradients
-    (64 to 189 of them) in one launch, written or added; up to 73 windows the scratch holds one pack of weights, above
-    two.  Twice the same call: the same bits."""
+    (36 to 189 of them) in one launch, written or added; up to 73 8x8 windows the scratch holds one pack of weights,
+    above two.  Twice the same call: the same bits."""
     import torch
     from paper_2409_06206_amd import gswa, runner
-    x, dy, p = parity.make_inputs(B, H, W, 180, 6, 1, 8, "bf16", synth.LAYER_SEED0 + 2, "stress")
-    layer = runner.DeviceLayer(B, H, W, 180, 6, 1, 8, 4, "bf16", gswa.GSWA_ACCUM_WGRAD if accumulate else 0)
+    x, dy, p = parity.make_inputs(B, H, W, 180, 6, 1, window, "bf16", synth.LAYER_SEED0 + 2, "stress")
+    layer = runner.DeviceLayer(B, H, W, 180, 6, 1, window, 4, "bf16", gswa.GSWA_ACCUM_WGRAD if accumulate else 0)
     layer.set_params(p)
     layer.set_inputs(x, dy)
     start = 0.5 if accumulate else 0.0
@@ -112,7 +112,7 @@ def test_one_group_of_a_wide_layer_sums_its_gradients_directly(oracle, B, H, W, 
         layer.backward()
         torch.cuda.synchronize()
         runs.append({k: v.copy() for k, v in layer.results().items()})
-    want = parity.oracle_results(oracle, x, dy, p, 6, 1, 8, 4)
+    want = parity.oracle_results(oracle, x, dy, p, 6, 1, window, 4)
     for k in parity.GRAD_NAMES:
         assert (runs[0][k] == runs[1][k]).all(), k
         got = runs[0][k] - (start if k != "dx" else 0.0)
