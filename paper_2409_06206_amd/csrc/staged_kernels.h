@@ -43,6 +43,10 @@ bool linear_act_supported(const LinearArgs &a);
 // true when launch_linear<bf16_t> runs this call on the kernel that implements the LayerNorm of the operand
 bool linear_ln_supported(const LinearArgs &a);
 
+// 0 for t <= 0, 1 for t > 0, in one instruction: 2^160 t clamped to 0..1.  (The exponent takes the smallest subnormal, 2^-149,
+// past 1; no fp32 factor does, and 3.4e38 t, which stood here, is a fraction for t below 2.9e-39.)
+__device__ __forceinline__ float step01(float t) { return __builtin_amdgcn_fmed3f(__builtin_ldexpf(t, 160), 0.f, 1.f); }
+
 // Gaussian CDF Phi(t) and density phi(t): erf by the rational-times-exponential approximation
 // 7.1.26 of Abramowitz & Stegun (absolute error below 1.5e-7); exp(-t^2/2) serves both.
 __device__ __forceinline__ void gauss(float t, float &Phi, float &phi)
@@ -52,9 +56,9 @@ __device__ __forceinline__ void gauss(float t, float &Phi, float &phi)
     const float e = __builtin_amdgcn_exp2f(t * t * -0.72134752044448170f);
     const float k = __builtin_amdgcn_rcpf(fmaf(fabsf(t), 0.23164190f, 1.f));
     const float poly = ((((0.5307027145f * k - 0.7265760135f) * k + 0.7107068705f) * k - 0.142248368f) * k + 0.127414796f) * k;
-    // Phi = 1 - poly e for positive t, poly e for the others: |step(t) - poly e|, with the step a product clamped to 0..1
+    // Phi = 1 - poly e for positive t, poly e for the others: |step(t) - poly e|
     // (a comparison, a choice and a subtraction otherwise; fused into the next instruction the magnitude costs nothing)
-    Phi = fabsf(fmaf(-poly, e, __builtin_amdgcn_fmed3f(t * 3.4028234e38f, 0.f, 1.f)));
+    Phi = fabsf(fmaf(-poly, e, step01(t)));
     phi = 0.39894228040143268f * e;
 }
 
@@ -74,7 +78,7 @@ __device__ __forceinline__ float gauss_cdf(float t)
     s = fmaf(s, a, -4.59204906e-1f);
     s = fmaf(s, a, -1.15110572f);
     s = fmaf(s, a, -0.999999978f);
-    return fabsf(__builtin_amdgcn_fmed3f(t * 3.4028234e38f, 0.f, 1.f) - __builtin_amdgcn_exp2f(s)); // (as in gauss)
+    return fabsf(step01(t) - __builtin_amdgcn_exp2f(s)); // (as in gauss)
 }
 
 // GELU in its Gaussian-CDF form and its derivative Phi(t) + t phi(t)

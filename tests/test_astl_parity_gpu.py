@@ -204,6 +204,45 @@ def test_eps_enters_both_layer_norms(eps):
     parity.check_block(astl_oracle, eps=eps, **case)
 
 
+@pytest.mark.parametrize("case", [
+    SMALL[0],   # fp32, one workgroup per window
+    SMALL[7],   # narrow, fused MLP kernels
+    SMALL[10],  # 12x12 windows, one workgroup per window
+    SMALL[11],  # wide, streaming MLP kernels
+    # hidden 400: the GELU and its derivative in the linear maps of 4096 rows and more
+    dict(B=1, H=64, W=64, C=180, heads=6, groups=2, window=8, shift=4, dtype="bf16", hidden=400),
+], ids=_id)
+def test_gelu_derivative_at_subnormal_arguments(case):
+    """W1 = 0: the pre-activations are b1 alone, here zero, subnormal and the smallest normal numbers of either sign, where
+    GELU' is 1/2.  An argument whose derivative is lost shows as an entry of d b1 and a row of d W1 on their own scale."""
+    import torch
+    from paper_2409_06206_amd import runner
+    c = dict(case)
+    hidden, dtype = c.pop("hidden"), c.pop("dtype")
+    B, H, W, C, heads, groups, window, shift = (c[k] for k in ("B", "H", "W", "C", "heads", "groups", "window", "shift"))
+    dqk = c.get("dqk", 0)
+    p = synth.astl_params(C, heads, groups, window, hidden, synth.LAYER_SEED0, "stress", dqk)
+    least = 2.0 ** (-149 if dtype == "f32" else -133)
+    args = np.array([0.0, least, 2.0 ** -129, 2.0 ** -128, 1.25 * 2.0 ** -128, 2.0 ** -126, 1e-30, -0.0, -least, -2.0 ** -129, -1e-30])
+    p["w_fc1"] = np.zeros_like(p["w_fc1"])
+    p["b_fc1"] = args[np.arange(hidden) % args.size].astype(np.float32)
+    p = {k: synth.quantize(v, dtype) for k, v in p.items()}
+    assert (p["b_fc1"][:2] == args[:2]).all()
+    x, dy = (synth.quantize(a, dtype) for a in synth.activations(B, H, W, C, synth.ACT_SEED))
+    blk = runner.DeviceBlock(B, H, W, C, heads, groups, window, shift, dtype, hidden, dqk=dqk)
+    blk.set_params(p)
+    blk.set_inputs(x, dy)
+    blk.forward()
+    blk.backward()
+    torch.cuda.synchronize()
+    got = blk.results()
+    _, g = astl_oracle.backward(x, dy, p, heads=heads, groups=groups, window=window, shift=shift, dqk=dqk)
+    for k in ("b_fc1", "w_fc1"):
+        err = parity.rel_err(got["d" + k], g[k])
+        print(k, err, flush=True)
+        assert err <= parity.TOL[dtype], (k, err)
+
+
 def test_narrow_bf16_layers_take_the_fused_mlp_kernels():
     """The kernel timing aid names what ran: one fused launch per pass for the MLP half of a narrow
     bf16 layer, the per-step kernels otherwise (fp32, wide layers, forced)."""
