@@ -243,6 +243,43 @@ def test_gelu_derivative_at_subnormal_arguments(case):
         assert err <= parity.TOL[dtype], (k, err)
 
 
+@pytest.mark.parametrize("C,heads,hidden", [(180, 6, 360), (180, 6, 400), (68, 4, 32)])
+def test_layer_norm_of_a_row_whose_squares_overflow(C, heads, hidden):
+    """One token of alternating +-1e20: finite, but the sum of its squared distances is not (in fp32), 1/sqrt of it is zero and
+    the row of LN is beta.  In place of the token the oracle sees zeros, whose LN_1 is beta too; its output gradient is
+    zero, so that the MLP half, where the two differ, adds nothing to any gradient."""
+    import torch
+    from paper_2409_06206_amd import runner
+    B, H, W, window = 1, 8, 16, 8
+    p = {k: synth.quantize(v, "bf16") for k, v in synth.astl_params(C, heads, 1, window, hidden, synth.LAYER_SEED0, "stress").items()}
+    x, dy = (synth.quantize(a, "bf16") for a in synth.activations(B, H, W, C, synth.ACT_SEED))
+    at = (0, 3, 5)
+    rest = np.ones((B, H, W), dtype=bool)
+    rest[at] = False
+    x[at] = 1e20 * (1 - 2 * (np.arange(C) % 2))
+    x, dy[at] = synth.quantize(x, "bf16"), 0.0
+    blk = runner.DeviceBlock(B, H, W, C, heads, 1, window, 0, "bf16", hidden)
+    blk.set_params(p)
+    blk.set_inputs(x, dy)
+    blk.forward()
+    blk.backward()
+    torch.cuda.synchronize()
+    got = blk.results()
+    plain = x.copy()
+    plain[at] = 0.0
+    kw = dict(heads=heads, groups=1, window=window, shift=0)
+    want = {"y": astl_oracle.forward(plain, p, **kw)}
+    dx, g = astl_oracle.backward(plain, dy, p, **kw)
+    want.update({"dx": dx, **{"d" + k: v for k, v in g.items()}})
+    assert (got["y"][at] == x[at]).all()  # (attention and MLP are far below the last bit)
+    assert (got["dx"][at] == 0.0).all()
+    for t in (got, want):
+        t["y"], t["dx"] = t["y"][rest], t["dx"][rest]
+    errs = {k: parity.rel_err(got[k], want[k]) for k in want}
+    print(errs, flush=True)
+    assert all(e <= parity.TOL["bf16"] for e in errs.values()), errs
+
+
 def test_narrow_bf16_layers_take_the_fused_mlp_kernels():
     """The kernel timing aid names what ran: one fused launch per pass for the MLP half of a narrow
     bf16 layer, the per-step kernels otherwise (fp32, wide layers, forced)."""
