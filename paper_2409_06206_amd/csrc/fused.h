@@ -260,7 +260,7 @@ struct ReduceJob {
     int accumulate;
 };
 hipError_t launch_reduce_pair(const ReduceJob &a, const ReduceJob &b, hipStream_t s);
-// the same with a third, whose vectors are about as long as the first's
+// the same with a third (c.n == 0: none)
 hipError_t launch_reduce_three(const ReduceJob &a, const ReduceJob &b, const ReduceJob &c, hipStream_t s);
 
 // Wide layers (C = 180, two or three groups, 8x8 windows), backward of the attention and of the QKV

@@ -17,21 +17,30 @@ GRAD_NAMES = ("dx", "dw_qkv", "db_qkv", "dw_proj", "db_proj", "dtable")
 
 
 @contextlib.contextmanager
-def launched():
-    """Names of the kernels that the library launches inside the block (filled in when it ends without an error)."""
+def launch_counts():
+    """Launches of each kernel that the library launches inside the block, by name (filled in when it ends without an error)."""
     import torch
     from paper_2409_06206_amd import gswa
-    names = set()
+    counts = {}
     gswa.gswa_profile_enable(True)
     try:
         gswa.gswa_profile_collect()
-        yield names
+        yield counts
         torch.cuda.synchronize()
         got, dropped = gswa.gswa_profile_collect()
         assert dropped == 0
-        names.update(got)
+        counts.update({k: n for k, (_, n) in got.items()})
     finally:
         gswa.gswa_profile_enable(False)
+
+
+@contextlib.contextmanager
+def launched():
+    """Names of the kernels that the library launches inside the block (filled in when it ends without an error)."""
+    names = set()
+    with launch_counts() as counts:
+        yield names
+    names.update(counts)
 
 
 def rel_err(got, want):

@@ -69,24 +69,25 @@ def test_forced_staged_path_one_group_many_tokens(oracle, C, heads):
                       extra_flags=gswa.GSWA_FORCE_STAGED)
 
 
-@pytest.mark.parametrize("rows,cols", [(8, 113), (5, 181)])
-def test_last_sums_of_a_wide_backward_in_two_launches_and_in_one(oracle, rows, cols):
-    """904 and 905 windows of 180 channels, two groups: the projection's partial vectors (256 compute units) do not fit
-    the place of d(q|k|v), and just fill it, while the other sums still have to be taken; here all are added."""
-    import torch
+@pytest.mark.parametrize("groups,rows,cols,launches", [(2, 8, 113, 3), (2, 5, 181, 2), (3, 23, 59, 4), (3, 14, 97, 3)])
+def test_last_sums_of_a_wide_backward_in_two_launches_and_in_one(oracle, groups, rows, cols, launches):
+    """180 channels: with 904 windows and two groups, 1357 and three, the projection's partial vectors (256 compute units) do
+    not fit the place of d(q|k|v); with 905 and 1358 they just fill it, while the other sums still have to be taken (with
+    three groups the vectors of q|k|v are summed one entry a load, the projection's four); here all are added."""
     from paper_2409_06206_amd import gswa, runner
     H, W = 8 * rows, 8 * cols
-    x, dy, p = parity.make_inputs(1, H, W, 180, 6, 2, 8, "bf16", synth.LAYER_SEED0 + 3, "stress")
-    layer = runner.DeviceLayer(1, H, W, 180, 6, 2, 8, 4, "bf16", gswa.GSWA_ACCUM_WGRAD)
+    x, dy, p = parity.make_inputs(1, H, W, 180, 6, groups, 8, "bf16", synth.LAYER_SEED0 + 3, "stress")
+    layer = runner.DeviceLayer(1, H, W, 180, 6, groups, 8, 4, "bf16", gswa.GSWA_ACCUM_WGRAD)
     layer.set_params(p)
     layer.set_inputs(x, dy)
     for g in layer.grads.values():
         g.fill_(0.5)
     layer.forward()
-    layer.backward()
-    torch.cuda.synchronize()
+    with parity.launch_counts() as counts:
+        layer.backward()
+    assert counts["reduce_partials"] == launches, counts
     got = layer.results()
-    want = parity.oracle_results(oracle, x, dy, p, 6, 2, 8, 4)
+    want = parity.oracle_results(oracle, x, dy, p, 6, groups, 8, 4)
     for k in parity.GRAD_NAMES:
         assert parity.rel_err(got[k] - (0.5 if k != "dx" else 0.0), want[k]) <= parity.TOL["bf16"], k
 
