@@ -518,9 +518,14 @@ void fused_bwd_kernel(Geom g, const bf16_t *__restrict__ x,
                     for (int j = 0; j < 4; ++j)
                         if ((lastrow && rmask[kt]) || (lastcol && cmask[j])) st[kt][j] += kMask;
             }
-            float mx = max4f(st[0]);
+            // (one by one, not in threes as max5f takes them: behind the mask that quiets half as many operands again, 216
+            // for 144 in all instances.  32 images of 64x64, forward + backward, 1 / 2 / 3 / 6 groups: 161.8 / 129.4 /
+            // 138.6 / 128.8 us in threes, 161.2 / 128.4 / 137.5 / 128.2 so.)
+            float mx = -INFINITY;
 #pragma unroll
-            for (int kt = 1; kt < 4; ++kt) mx = max5f(mx, st[kt]);
+            for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) mx = fmaxf(mx, st[kt][j]);
             mx = qgroup_max(mx);
             const float mxl = mx * kLog2e;
             float sum = 0.f;

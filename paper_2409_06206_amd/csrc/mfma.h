@@ -56,16 +56,12 @@ __device__ __forceinline__ f32x4 mma32(uint4 a, uint4 b, f32x4 c)
                                                    __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
 }
 
-// Largest of two and three.  (fmaxf first quiets signalling NaNs, an instruction for each operand of which the compiler
-// knows nothing, like a product's result, which is never one: 36 of the 470 vector instructions of a 12x12 window's unit
-// of scores.  The instruction that remains treats quiet NaNs and infinities as before.)
-#pragma float_control(push)
-#pragma float_control(precise, off)
-__device__ __forceinline__ float max2f(float a, float b) { return __builtin_fmaxf(a, b); }
-__device__ __forceinline__ float max3f(float a, float b, float c) { return __builtin_fmaxf(__builtin_fmaxf(a, b), c); }
-#pragma float_control(pop)
-__device__ __forceinline__ float max4f(f32x4 v) { return max2f(max3f(v[0], v[1], v[2]), v[3]); }
-__device__ __forceinline__ float max5f(float m, f32x4 v) { return max3f(max3f(m, v[0], v[1]), v[2], v[3]); }
+// Largest entry of a score tile, and of a tile and the tiles before it.  (fmaxf first quiets signalling NaNs, an instruction of
+// its own for each operand of which the compiler knows nothing, like a product's result, which is never one.  How many of
+// them it can leave out depends on the order: with the running maximum and two entries at a time 216 remain in the 12x12
+// kernels of four heads, with the four of a tile first 864.)
+__device__ __forceinline__ float max4f(f32x4 v) { return fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])); }
+__device__ __forceinline__ float max5f(float m, f32x4 v) { return fmaxf(fmaxf(fmaxf(fmaxf(m, v[0]), v[1]), v[2]), v[3]); }
 
 // all-reduce over the four lanes that share l16 (q = 0..3), without touching LDS:
 // v_permlane16_swap(v, v) returns {rows 0,0,2,2 of v; rows 1,1,3,3 of v} (rows = 16 lanes), and
@@ -75,9 +71,9 @@ __device__ __forceinline__ float qgroup_max(float v)
 {
     const unsigned u = __float_as_uint(v);
     u32x2 r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-    const unsigned w = __float_as_uint(max2f(__uint_as_float(r[0]), __uint_as_float(r[1])));
+    const unsigned w = __float_as_uint(fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1])));
     r = __builtin_amdgcn_permlane32_swap(w, w, false, false);
-    return max2f(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 __device__ __forceinline__ float qgroup_sum(float v)
 {
