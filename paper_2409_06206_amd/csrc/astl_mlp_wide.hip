@@ -737,9 +737,11 @@ __global__ __launch_bounds__(kWideThreads) void astl_mlp_wide_bwd_kernel(WideMlp
             }
         };
 
-        // first unit of the round: see the forward kernel (the stores of the unit's own steps are younger than
-        // the row loads; leaving 2 KSC operations in flight then waits for as many of the row loads as there
-        // were stores, whichever way loads and stores are ordered among each other)
+        // First unit of the round (apart from the loop over the others, so that the compiler sees that the row loads are not
+        // in flight when that runs): the second unit is sent on its way into the other buffer, and BEHIND its loads the
+        // next round's rows.  A wave's vector-memory operations, loads and stores, are counted down in the order it issued
+        // them (the memory model of the compiler's AMDGPU guide): with 2 KSC of them outstanding all older ones are done,
+        // and behind the second unit's loads there are the 2 KSC row loads and the stores of this unit's steps.
         if (nu > 1) stream_unit(1, slot ^ 1);
         else if (more) stream_unit(0, slot ^ 1);
         if (more) {

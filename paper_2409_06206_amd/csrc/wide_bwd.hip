@@ -29,9 +29,9 @@ namespace {
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kMaskLog2 = -100.0f * kLog2e; // the additive -100 of the shift mask, in base-2 units
 
-// s_waitcnt immediate: everything in LDS, all vector-memory operations but the 12 youngest
+// s_waitcnt immediate: everything in LDS, all vector-memory operations but the N youngest
 // (vmcnt in bits 3:0 and 15:14, expcnt 6:4, lgkmcnt 11:8)
-constexpr int kWaitAllBut12 = 12 | (7 << 4);
+template <int N> constexpr int kWaitAllBut = (N & 15) | ((N >> 4) << 14) | (7 << 4);
 
 template <class Cf> struct WideBwdCfg {
     static constexpr int NWAVES = 4, NTHREADS = 64 * NWAVES;
@@ -61,6 +61,7 @@ template <class Cf> struct WideBwdCfg {
     static_assert(NWAVES == 4, "the table sums of four waves are added pairwise");
     // d(q|k|v) in scratch: fragment ((window * 4 + token tile) * HG + head of the group) * 3 + (q|k|v)
     static constexpr int FR_TILE = Cf::HG * 3;
+    static constexpr int HEAD_STORES = 4 * 3; // of a head of a window: four token tiles of q, k and v, 16 bytes a lane each
     // second kernel
     static constexpr int KS = Cf::KS;                  // K=32 steps over the group's channels, natural order
     static constexpr int CT = Cf::CG / 16 + 1;         // column tiles of d w_qkv, column CG carries the bias sums
@@ -352,6 +353,10 @@ __global__ __launch_bounds__(256, 1) void wide_attn_bwd_kernel(Geom g, const bf1
                     }
                 }
                 if (active) {
+                    // one store: token tile `tile` of d q, d k or d v of the head
+                    auto put = [&](int tile, int kind, f32x4 lo, f32x4 hi) {
+                        *reinterpret_cast<uint4 *>(dq_win + (size_t)((tile * HG + hl) * 3 + kind) * 1024) = cat(pack_bf16x4(lo), pack_bf16x4(hi));
+                    };
                     // ---- Q^T, K^T, V^T exactly as the forward computes them (rows = head features) ----
                     uint2 Qb[2][4], Kb[2][4], Vb[2][4];
                     // (the fragments of a K step are read under the products of the step before; vector instructions may cross
@@ -521,9 +526,7 @@ __global__ __launch_bounds__(256, 1) void wide_attn_bwd_kernel(Geom g, const bf1
                                 dSq[kt][ni] = transpose_tile(dSb[ni][kt], ident);
                             }
 #pragma unroll
-                        for (int ni = 0; ni < 2; ++ni)
-                            *reinterpret_cast<uint4 *>(dq_win + (size_t)(((2 * p2 + ni) * HG + hl) * 3 + 0) * 1024) =
-                                cat(pack_bf16x4(d0[ni]), pack_bf16x4(d1[ni]));
+                        for (int ni = 0; ni < 2; ++ni) put(2 * p2 + ni, 0, d0[ni], d1[ni]);
                         __builtin_amdgcn_sched_barrier(0);
                         // dK^T += Q^T dS, dV^T += dO^T P over the 32 queries of the pair
 #pragma unroll
@@ -537,17 +540,18 @@ __global__ __launch_bounds__(256, 1) void wide_attn_bwd_kernel(Geom g, const bf1
                     // dK = dS^T (q / sqrt(d)): the recomputed Q carries log2(e) / sqrt(d)
 #pragma unroll
                     for (int kt = 0; kt < 4; ++kt) {
-                        *reinterpret_cast<uint4 *>(dq_win + (size_t)((kt * HG + hl) * 3 + 1) * 1024) =
-                            cat(pack_bf16x4(dkT[0][kt] * (1.0f / kLog2e)), pack_bf16x4(dkT[1][kt] * (1.0f / kLog2e)));
-                        *reinterpret_cast<uint4 *>(dq_win + (size_t)((kt * HG + hl) * 3 + 2) * 1024) =
-                            cat(pack_bf16x4(dvT[0][kt]), pack_bf16x4(dvT[1][kt]));
+                        put(kt, 1, dkT[0][kt] * (1.0f / kLog2e), dkT[1][kt] * (1.0f / kLog2e));
+                        put(kt, 2, dvT[0][kt], dvT[1][kt]);
                     }
+                    // (the wait at the unit's end counts on them: two of dQ in each pair of query tiles, dK and dV of each key tile)
+                    static_assert(W::HEAD_STORES == 2 * 2 + 4 * 2, "stores behind the loads of the next unit");
                 }
             }
-            // The next unit has landed in LDS before any wave reads it.  Memory operations complete in the order they were
-            // issued: behind the unit's loads a wave with a window has issued at least the stores of dQ, dK and dV of the
-            // head, whose way to memory is nobody's to wait for.
-            if (u >= W::NAU && active) __builtin_amdgcn_s_waitcnt(kWaitAllBut12);
+            // The next unit has landed in LDS before any wave reads it.  A wave's vector-memory operations, loads and stores,
+            // are counted down in the order it issued them (the memory model of the compiler's AMDGPU guide): behind the unit's
+            // loads a wave with a window has issued at least the stores of dQ, dK and dV of the head, whose way to memory is
+            // nobody's to wait for.
+            if (u >= W::NAU && active) __builtin_amdgcn_s_waitcnt(kWaitAllBut<W::HEAD_STORES>);
             else __builtin_amdgcn_s_waitcnt(0);
             __syncthreads();
         });
