@@ -27,11 +27,11 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0
 # the launch kinds of that kernel), valid only for the kernel source they were taken on:
 # {(workload, groups, kernel): (source file, sha256 of it, bytes per launch)}
 MEASURED_TRAFFIC = {
-    ("c4", 2, "wide_attn_bwd"): ("wide_bwd.hip", "542575f85bb32af15785402762cfeba8b0857aef2d9ed64e0e9316358bad860b", 229492499),
-    ("c3", 2, "wide_attn_bwd"): ("wide_bwd.hip", "542575f85bb32af15785402762cfeba8b0857aef2d9ed64e0e9316358bad860b", 115818984),
-    ("c2", 2, "fused_bwd"): ("fused_bwd.hip", "b02edb8e90f33d0b430c0c54ff57215565e8927ab397e0e61b9a7af641ac50bb", 74098978),
-    ("c5_m8", 2, "fused_fwd"): ("wide_fwd.hip", "3a045cb1571dda4b176ffd6295e73fed859232efe85b4d08bb43f1dd406cb3e9", 238957256),
-    ("c5_m16", 2, "fused_fwd"): ("wide_fwd.hip", "3a045cb1571dda4b176ffd6295e73fed859232efe85b4d08bb43f1dd406cb3e9", 239763192),
+    ("c4", 2, "wide_attn_bwd"): ("wide_bwd.hip", "7dc5db26762dcc56b7331661ed9a3a0cb7d411d14a41421f728c37f162ace091", 229529042),
+    ("c3", 2, "wide_attn_bwd"): ("wide_bwd.hip", "7dc5db26762dcc56b7331661ed9a3a0cb7d411d14a41421f728c37f162ace091", 115213184),
+    ("c2", 2, "fused_bwd"): ("fused_bwd.hip", "ca3ca1676ede6e2a6cb842f95ffda0eea25f38097560e295b5d072b27277ac69", 74098582),
+    ("c5_m8", 2, "fused_fwd"): ("wide_fwd.hip", "3a045cb1571dda4b176ffd6295e73fed859232efe85b4d08bb43f1dd406cb3e9", 238968328),
+    ("c5_m16", 2, "fused_fwd"): ("wide_fwd.hip", "3a045cb1571dda4b176ffd6295e73fed859232efe85b4d08bb43f1dd406cb3e9", 240168888),
 }
 
 

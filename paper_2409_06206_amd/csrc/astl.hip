@@ -294,7 +294,7 @@ template <typename T, int V> hipError_t launch_ln_fwd_v(const LnArgs &a, const M
 template <typename T> hipError_t launch_ln_fwd(const LnArgs &a, hipStream_t s, const MlpReduceArgs *r = nullptr)
 {
     if constexpr (sizeof(T) == 2) {
-        // bf16 rows of 65 to 192 channels: the kernel with four lanes per row and whole tiles of loads in flight
+        // bf16 rows of 65 to 192 channels: the kernel with half a wavefront per row and the next rows' loads in flight
         // (whatever the number of rows: a band of a map must get the arithmetic the whole map gets)
         if (!r && ln_rows_supported(a.C)) {
             LnRowsArgs n{};
@@ -841,8 +841,8 @@ int backward_t(const astl_desc *d, const Plan &pl, const T *x, const T *dy, cons
     }
 
     // Eq. 4 backwards: the attention layer on LN_1(x) (recomputed), then LN_1 and the skip.  (Where the forward took LN_1
-    // inside another kernel, that one sums a row in another order: about one element of LN_1(x) in 150000 is one bf16
-    // step from the forward's.)
+    // inside another kernel, the attention's or the MLP's of the layer before, that one sums a row in another order: about
+    // one element of LN_1(x) in 160000 is one bf16 step from the forward's, counted over 400000 normal rows of 180.)
     LnArgs l1{};
     l1.u = x; l1.gamma = p->ln1_w; l1.beta = p->ln1_b; l1.out = xn; l1.rows = rows; l1.C = C; l1.eps = d->eps;
     // (the fused MLP backward's final sum rides in the same launch)

@@ -657,9 +657,8 @@ __global__ __launch_bounds__(64 * LinStream::NWV) void linear_stream_kernel(Line
     }
 }
 
-// Maps the streaming kernel takes: bf16 (checked by the caller), no second addend, activation or LayerNorm, at most
-// 576 output columns, dword-aligned rows, scratch for the pack - and a shape the kernel that keeps a whole weight
-// matrix in LDS does not take (a reduction longer than 384, or more than 192 columns).
+// Maps the streaming kernel can take: bf16 (checked by the caller), no second addend, activation or LayerNorm, 64 to 576
+// output columns, dword-aligned rows, scratch for the pack.
 static bool linear_stream_takes(const LinearArgs &a)
 {
     if (!a.scratch || a.a2 || a.act || a.ln_gamma) return false;
@@ -667,6 +666,8 @@ static bool linear_stream_takes(const LinearArgs &a)
     if ((a.lda1 & 1) || (reinterpret_cast<uintptr_t>(a.a1) & 3) || (reinterpret_cast<uintptr_t>(a.scratch) & 15)) return false;
     return a.scratch_bytes >= LinStream::pack_bytes(a.N, a.K);
 }
+// Maps it is chosen for by themselves: a shape the kernel that keeps a whole weight matrix in LDS does not take (a reduction
+// longer than 384, or more than 192 columns).
 static bool linear_stream_ok(const LinearArgs &a)
 {
     return !(a.K <= 384 && a.N <= 16 * LinStream::NT) && linear_stream_takes(a);
