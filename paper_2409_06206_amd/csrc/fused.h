@@ -24,8 +24,8 @@ namespace gswa {
 // fragment f, lane l at f*64 + l, so one LDS read per lane fetches an operand), zero padded
 // (head width to 16*ET, group width to 32*KS).  The query rows of w_qkv and b_qkv are stored
 // multiplied by 1/sqrt(d), so scores need no separate scaling.  One buffer serves both passes:
-//   [ WQH | WP2 | BF | WQ | BIAS | WPT | WQT | WPK ]
-// forward of narrow layers: WQH, WP2, BF, BIAS; backward: WQ .. WQT.
+//   [ WQH | WP2 | BF | WQ | BIAS | WPT | WQT | WPK | WQF ]
+// forward of narrow layers: WQH, WP2, BF, BIAS; backward: WQ .. WQT, WQF.
 //   WQH  Wqkv with the group's input channels in head-padded order (k-slot 16*hl' + e' <-> channel
 //        hl'*D + e'), the order in which a group's output tiles lie in registers, so that the
 //        cascade input of Eq. 8 is added to the x slice operand in place; K=32 steps over head
@@ -54,7 +54,12 @@ template <int C_, int HEADS_, int G_> struct FusedCfg {
     static constexpr int N_WPK = SPLIT ? OT * KSC : 0;           // Wproj, K=32 over all channels: (ot,ks)
     static constexpr int N_WQ = HEADS * 3 * ET * KS;             // Wqkv on the x slice, K=32: (hd,t,et,ks)
     static constexpr int N_WPT = HEADS * ET * KSC;               // Wproj^T, K=32: (hd,et,ks)
-    static constexpr int N_WQT = HEADS * 3 * ET * HG * ET;       // Wqkv^T, K=16: (hd,t,et,hlp,etp)
+    // narrow layers of one to three groups: backward with a wavefront per head (heads_bwd.hip), which reads Wqkv^T as
+    //   WQF  Wqkv^T, K=32: k-slots = the 3 D features q | k | v of a head; (hdo, h): row l16 -> channel l16 of head hdo, features of
+    //        head h of the same group
+    static constexpr bool HEADS_BWD = !SPLIT && G <= 3;
+    static constexpr int N_WQF = HEADS_BWD ? HEADS * HG : 0;
+    static constexpr int N_WQT = HEADS_BWD && G != 2 ? 0 : HEADS * 3 * ET * HG * ET; // Wqkv^T, K=16: (hd,t,et,hlp,etp)
     static constexpr size_t P_WQH = 0;
     static constexpr size_t P_WP2 = P_WQH + (size_t)N_WQH * 1024;
     static constexpr size_t P_BF = P_WP2 + (size_t)N_WP2 * 1024;
@@ -76,7 +81,8 @@ template <int C_, int HEADS_, int G_> struct FusedCfg {
     static constexpr int N_WQW = SPLIT ? HEADS * 3 * ET * KSX : 0;
     static constexpr int N_WPW = SPLIT ? OT * HEADS : 0;
     static constexpr int TBW_PITCH = 228;
-    static constexpr size_t P_WQW = P_WPK + (size_t)N_WPK * 1024;
+    static constexpr size_t P_WQF = P_WPK + (size_t)N_WPK * 1024;
+    static constexpr size_t P_WQW = P_WQF + (size_t)N_WQF * 1024;
     static constexpr size_t P_WPW = P_WQW + (size_t)N_WQW * 1024;
     static constexpr size_t P_TBW = P_WPW + (size_t)N_WPW * 1024;
     // Wide layers, backward with one wavefront per window (wide_bwd.hip) additionally reads
@@ -250,6 +256,7 @@ struct ReduceOut {
     int begin[MAXSEG + 1];
     int nseg;
     int tbl_heads, tbl_entries, tbl_stride, tbl_head0;
+    int row_seg, row_len, row_stride; // segment row_seg (if row_len > 0): rows of row_len entries, row_stride apart in the gradient
 };
 hipError_t launch_reduce(const float *part, int nparts, int n, const ReduceOut &out, int accumulate, hipStream_t s);
 // two such sums in one launch (the second with short vectors, e.g. a bias-table gradient)

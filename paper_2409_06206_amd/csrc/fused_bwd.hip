@@ -1,9 +1,9 @@
-// Fused GSWA backward for 8x8 windows, bf16 storage.  The backward of a layer is a sequence of
-// launches of fused_bwd_kernel, one per chunk of heads in reverse order; each recomputes q, k, v,
-// the scores and the softmax of its heads from x and the saved group outputs, and produces the dx
-// slices of its groups and per-workgroup partial sums of the parameter gradients (accumulated in
-// registers over the windows a workgroup owns).  reduce_partials_kernel adds the partials in a
-// fixed order.  wproj_grad_kernel is the projection's weight gradient for wide layers.
+// Fused GSWA backward for 8x8 windows, bf16 storage: six groups of a narrow layer, and wide layers with an odd shift (one to
+// three groups of a narrow layer: heads_bwd.hip, a wide layer with an even shift: wide_bwd.hip).  The backward of a layer is a
+// sequence of launches of fused_bwd_kernel, one per chunk of heads in reverse order; each recomputes q, k, v, the scores and the
+// softmax of its heads from x and the saved group outputs, and produces the dx slices of its groups and per-workgroup partial
+// sums of the parameter gradients (accumulated in registers over the windows a workgroup owns).  reduce_partials_kernel adds
+// the partials in a fixed order.  wproj_grad_kernel is the projection's weight gradient for wide layers.
 //
 // Per window, wave w owns tokens 16w..16w+15 both as queries and as keys.  Notation for a
 // matrix X[tokens x features] held as an MFMA result tile (see mfma.h):
@@ -11,8 +11,10 @@
 //           or A operand "m=token,k=feature")
 //   N-form: rows = tokens 4q+j,  column = feature l16  (packed: B operand "k=token,n=feature"
 //           or A operand "m=feature,k=token")
-// Either form of a product is obtained by swapping the operands of the MFMA.
+// A packed tile that other waves or the other orientation need goes to LDS as it lies in the registers, and is read back
+// either as it is or turned (lds_read_tr).
 #include "fused.h"
+#include "heads_bwd.h"
 #include "mfma.h"
 
 namespace gswa {
@@ -21,7 +23,7 @@ namespace {
 
 constexpr float kLog2e = 1.4426950408889634f;
 
-template <class Cf, int HB_, int HE_, bool WPROJ_ = (HE_ == Cf::HEADS)> struct BwdCfg {
+template <class Cf, int HB_, int HE_, bool WPROJ_> struct BwdCfg {
     static constexpr int C = Cf::C, D = Cf::D, CG = Cf::CG, HG = Cf::HG, HEADS = Cf::HEADS, G = Cf::G;
     static constexpr int ET = Cf::ET, KS = Cf::KS;
     static constexpr int KSC = (C + 31) / 32; // K=32 steps over all C channels of dy
@@ -31,12 +33,13 @@ template <class Cf, int HB_, int HE_, bool WPROJ_ = (HE_ == Cf::HEADS)> struct B
     static constexpr int CT = CG / 16 + 1;          // column tiles of d w_qkv of one head
     static constexpr int NT = 3 * ET * CT;          // tiles of one head's d w_qkv rows
     static constexpr int KT = (NT + 3) / 4;         // tiles per wave
-    static constexpr int OTP = (C + 15) / 16, CTP = C / 16 + 1;
-    static constexpr int NTP = OTP * CTP, KTP = (NTP + 3) / 4;
-    // heads [HB, HE) of this launch: whole groups, or part of one group.  WPROJ: this launch also
-    // produces d w_proj / d b_proj (narrow layers; wide ones use a kernel of its own).
+    // heads [HB, HE) of this launch: whole groups, or part of one group.  WPROJ: this launch also produces the columns of
+    // d w_proj that belong to its heads, and the last heads' launch d b_proj (narrow layers; wide ones use a kernel of its own).
     static constexpr int HB = HB_, HE = HE_, NH = HE - HB;
-    static constexpr bool WPROJ = WPROJ_;
+    static constexpr bool WPROJ = WPROJ_, BPROJ = WPROJ_ && HE_ == Cf::HEADS;
+    static constexpr int WC0 = HB * D, WCN = NH * D;  // the columns; the spare column WCN carries the bias sums
+    static constexpr int OTP = (C + 15) / 16, CTP = WCN / 16 + 1;
+    static constexpr int NTP = OTP * CTP, KTP = (NTP + 3) / 4;
     static constexpr int GB = HB / HG, GE = (HE - 1) / HG; // lowest and highest group of the chunk
     static_assert(NH > 0 && (GB == GE || (HB % HG == 0 && HE % HG == 0)),
                   "a chunk is whole groups or lies inside one group");
@@ -54,29 +57,26 @@ template <class Cf, int HB_, int HE_, bool WPROJ_ = (HE_ == Cf::HEADS)> struct B
     static constexpr size_t OFF_WQT = OFF_WPT + (WPT_LDS ? (size_t)N_WPT * 1024 : 0);
     static constexpr size_t PACK_BYTES = OFF_WQT + (size_t)N_WQT * 512;
     // LDS beyond the packed weights
-    static constexpr int LD = 68; // pitch (bf16) of rows read 4 at a time
     static constexpr int LW = 68; // pitch (bf16) of rows read 8 at a time (as two 8-byte halves:
                                   // 34 dwords keeps every 16-lane phase on distinct banks)
-    static constexpr size_t SZ_FRAG = (size_t)4 * ET * 64 * 8;
-    static constexpr size_t SZ_ROWS = (size_t)16 * ET * LD * 2;
-    static constexpr size_t SZ_SQ = (size_t)64 * LW * 2; // P / dS [key][query]; also dY^T / A^T rows
+    static constexpr size_t SZ_FRAG = (size_t)4 * ET * 64 * 8; // packed tiles of 64 tokens, lane by lane
+    static constexpr size_t SZ_SQ = (size_t)64 * LW * 2; // P / dS, 16 such tiles (key tile, query tile); also dY operands / A^T rows
     static constexpr size_t OFF_TBLF = PACK_BYTES;             // fp32 bias table [NH][225]
     static constexpr size_t OFF_KB = OFF_TBLF + (((size_t)NH * NTBL * 4 + 15) & ~size_t(15));
     static constexpr size_t OFF_VB = OFF_KB + SZ_FRAG;
-    static constexpr size_t OFF_KT = OFF_VB + SZ_FRAG;         // K^T rows [e][key]
-    static constexpr size_t OFF_QT = OFF_KT + SZ_ROWS;         // Q^T rows [e][query]
-    static constexpr size_t OFF_DOT = OFF_QT + SZ_ROWS;        // dO^T rows [e][query]
-    static constexpr size_t OFF_P = OFF_DOT + SZ_ROWS;
+    static constexpr size_t OFF_QB = OFF_VB + SZ_FRAG;
+    static constexpr size_t OFF_DOB = OFF_QB + SZ_FRAG;
+    static constexpr size_t OFF_P = OFF_DOB + SZ_FRAG;
     static constexpr size_t OFF_DS = OFF_P + SZ_SQ;
-    static constexpr size_t OFF_DQKV = OFF_DS + SZ_SQ;         // d(q|k|v)^T rows [(t,e)][token]
-    static constexpr size_t SZ_DQKV = (size_t)3 * ET * 16 * LW * 2;
+    static constexpr size_t OFF_DQKV = OFF_DS + SZ_SQ;         // d(q|k|v)^T tiles (t, et, token tile)
+    static constexpr size_t SZ_DQKV = 3 * SZ_FRAG;
     static constexpr size_t OFF_F = OFF_DQKV + SZ_DQKV;        // F^T rows [c][token] of the current group
     static constexpr size_t SZ_F = (size_t)16 * CT * LW * 2;
     static constexpr size_t LDS_BYTES = OFF_F + SZ_F;
     // Per-workgroup partial sums of THIS launch only (the scratch is reused from launch to launch: the
     // head-group loop bounds it).  Rows of d w_qkv: for every group of the chunk and each of q, k, v
     // the RG rows the chunk's heads own, ((gi - GB) * 3 + t) * RG + (hl - HL0) * D + e; then the bias
-    // sums in the same order, d w_proj | d b_proj where this launch produces them, and the bias-table
+    // sums in the same order, the columns of d w_proj | d b_proj where this launch produces them, and the bias-table
     // gradient head by head.
     static constexpr bool WHOLE = HB_ % HG == 0 && HE_ % HG == 0;   // whole groups (else: part of one group)
     static constexpr int NG = GE - GB + 1;
@@ -85,13 +85,13 @@ template <class Cf, int HB_, int HE_, bool WPROJ_ = (HE_ == Cf::HEADS)> struct B
     static constexpr int L_DWQ = 0;
     static constexpr int L_DBQ = L_DWQ + NG * 3 * RG * CG;
     static constexpr int L_DWP = L_DBQ + NG * 3 * RG;
-    static constexpr int L_DBP = L_DWP + (WPROJ ? C * C : 0);
-    static constexpr int L_TBL = L_DBP + (WPROJ ? C : 0);
+    static constexpr int L_DBP = L_DWP + (WPROJ ? C * WCN : 0);
+    static constexpr int L_TBL = L_DBP + (BPROJ ? C : 0);
     static constexpr int L_END = L_TBL + NH * NTBL;
     static constexpr int L_TOTAL = (L_END + 3) & ~3; // stride of the vectors: whole 16-byte pieces (the sum reads four entries per load)
-    static_assert(!WPROJ || (OTP <= 2 * KSC && SZ_SQ >= (size_t)16 * OTP * LW * 2 &&
+    static_assert(!WPROJ || (OTP <= 2 * KSC && SZ_SQ >= (size_t)KSC * 4096 &&
                              SZ_SQ >= (size_t)16 * CTP * LW * 2),
-                  "dY^T / A^T rows alias the P / dS squares");
+                  "dY operands / A^T rows alias the P / dS squares");
 };
 
 template <class Cf> __device__ __forceinline__ constexpr int fq(int hd, int t, int et, int ks)
@@ -142,7 +142,7 @@ void fused_bwd_kernel(Geom g, const bf16_t *__restrict__ x,
     using B = BwdCfg<Cf, HB, HE, WPROJ>;
     constexpr int NH = B::NH, GB = B::GB, GE = B::GE;
     constexpr int C = B::C, D = B::D, CG = B::CG, HG = B::HG, HEADS = B::HEADS, G = B::G;
-    constexpr int ET = B::ET, KS = B::KS, KSC = B::KSC, LD = B::LD, LW = B::LW, NTBL = B::NTBL;
+    constexpr int ET = B::ET, KS = B::KS, KSC = B::KSC, LW = B::LW, NTBL = B::NTBL;
     constexpr int CT = B::CT, NT = B::NT, KT = B::KT, OTP = B::OTP, CTP = B::CTP, NTP = B::NTP, KTP = B::KTP;
     constexpr int M = 8;
     static_assert(CG % 2 == 0 && D % 2 == 0 && C % 4 == 0, "dword-granular loads and stores");
@@ -160,13 +160,13 @@ void fused_bwd_kernel(Geom g, const bf16_t *__restrict__ x,
     float *tblf = reinterpret_cast<float *>(lds + B::OFF_TBLF);
     uint2 *kb = reinterpret_cast<uint2 *>(lds + B::OFF_KB);
     uint2 *vb = reinterpret_cast<uint2 *>(lds + B::OFF_VB);
-    uint16_t *ktr = reinterpret_cast<uint16_t *>(lds + B::OFF_KT);
-    uint16_t *qtr = reinterpret_cast<uint16_t *>(lds + B::OFF_QT);
-    uint16_t *dotr = reinterpret_cast<uint16_t *>(lds + B::OFF_DOT);
-    uint16_t *pbuf = reinterpret_cast<uint16_t *>(lds + B::OFF_P);
-    uint16_t *dsbuf = reinterpret_cast<uint16_t *>(lds + B::OFF_DS);
-    uint16_t *dybuf = pbuf, *abuf = dsbuf; // dY^T and A^T rows live where P / dS go later in the window
-    uint16_t *gbuf = reinterpret_cast<uint16_t *>(lds + B::OFF_DQKV);
+    uint2 *qb = reinterpret_cast<uint2 *>(lds + B::OFF_QB);
+    uint2 *dob = reinterpret_cast<uint2 *>(lds + B::OFF_DOB);
+    uint2 *pbuf = reinterpret_cast<uint2 *>(lds + B::OFF_P);
+    uint2 *dsbuf = reinterpret_cast<uint2 *>(lds + B::OFF_DS);
+    uint4 *dybuf = reinterpret_cast<uint4 *>(pbuf);
+    uint16_t *abuf = reinterpret_cast<uint16_t *>(dsbuf); // dY operands and A^T rows live where P / dS go later in the window
+    uint2 *gbuf = reinterpret_cast<uint2 *>(lds + B::OFF_DQKV);
     uint16_t *fbuf = reinterpret_cast<uint16_t *>(lds + B::OFF_F);
 
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, q = lane >> 4;
@@ -197,7 +197,7 @@ void fused_bwd_kernel(Geom g, const bf16_t *__restrict__ x,
         return ((long)b * g.H + si) * g.W + sj;
     };
     constexpr auto need_x = [](int gi) { return gi >= GB && gi <= GE; };
-    constexpr auto need_a = [](int gi) { return WPROJ || (gi >= GB - 1 && gi < GE); };
+    constexpr auto need_a = [](int gi) { return gi >= GB - 1 && gi < GE + (WPROJ ? 1 : 0); };
     // dF of the next group (Eq. 8) comes from the dx slice that an earlier launch finished
     constexpr auto need_c = [](int hd) {
         const int gi = hd / HG;
@@ -328,7 +328,6 @@ void fused_bwd_kernel(Geom g, const bf16_t *__restrict__ x,
     struct HeadOps {
         uint4 pt[ET][KSC], qkv[3][ET][KS];
         f32x4 bT[3][ET];   // bias of the rows 4q + j
-        float bN[2][ET];   // bias of q, k of column l16
     } ho;
     for (int win = blockIdx.x; win < g.nW; win += gridDim.x) {
         // (the lane index as this window's address arithmetic sees it: opaque, so that the many per-lane LDS and
@@ -336,6 +335,7 @@ void fused_bwd_kernel(Geom g, const bf16_t *__restrict__ x,
         int lane_w = threadIdx.x & 63;
         asm volatile("" : "+v"(lane_w));
         const int lane = lane_w, l16 = lane & 15, q = lane >> 4;
+        const int tr = (l16 & 3) * 16 + 4 * q + (l16 >> 2); // this lane's place in a packed tile that is read turned
         auto read_head = [&](int hx) {
 #pragma unroll
             for (int et = 0; et < ET; ++et) {
@@ -347,7 +347,6 @@ void fused_bwd_kernel(Geom g, const bf16_t *__restrict__ x,
 #pragma unroll
                     for (int ks = 0; ks < KS; ++ks) ho.qkv[t][et][ks] = wq[fq<Cf>(hx, t, et, ks) * 64 + lane];
                     ho.bT[t][et] = *reinterpret_cast<const f32x4 *>(bias + 4 * q);
-                    if (t < 2) ho.bN[t][et] = bias[l16];
                 }
             }
         };
@@ -374,14 +373,10 @@ void fused_bwd_kernel(Geom g, const bf16_t *__restrict__ x,
         const int wr = win - fdiv(win, per_img, r_img) * per_img, wi = fdiv(wr, g.nwj, r_nwj);
         const bool lastrow = s > 0 && wi == g.nwi - 1, lastcol = s > 0 && wr - wi * g.nwj == g.nwj - 1;
 
-        // ---- d w_proj, d b_proj: dY^T and A^T rows [channel][token] through LDS, K = 64 tokens ----
+        // ---- d w_proj, d b_proj: dY operands (read turned) and A^T rows [channel][token] through LDS, K = 64 tokens ----
         if (WPROJ) {
 #pragma unroll
-        for (int ot = 0; ot < OTP; ++ot) {
-            f32x4 tN = mma32(dyf[ot >> 1], select_slot(16 * ot + l16, 32 * (ot >> 1) + 8 * q),
-                             f32x4{0.f, 0.f, 0.f, 0.f});
-            *reinterpret_cast<uint2 *>(dybuf + (16 * ot + l16) * LW + 16 * wv + 4 * q) = pack_bf16x4(tN);
-        }
+        for (int ks = 0; ks < KSC; ++ks) dybuf[(ks * 4 + wv) * 64 + lane] = dyf[ks];
 #pragma unroll
         for (int ct = 0; ct < CTP; ++ct) {
             f32x4 tN = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -389,11 +384,11 @@ void fused_bwd_kernel(Geom g, const bf16_t *__restrict__ x,
             for (int gi = 0; gi < G; ++gi)
 #pragma unroll
                 for (int ks = 0; ks < KS; ++ks)
-                    if (ranges_overlap(gi * CG + 32 * ks, gi * CG + (32 * ks + 32 < CG ? 32 * ks + 32 : CG),
-                                       16 * ct, 16 * ct + 16))
-                        tN = mma32(af[gi][ks], select_slot(16 * ct + l16, gi * CG + 32 * ks + 8 * q), tN);
+                    if (need_a(gi) && ranges_overlap(gi * CG + 32 * ks, gi * CG + (32 * ks + 32 < CG ? 32 * ks + 32 : CG),
+                                                     B::WC0 + 16 * ct, B::WC0 + 16 * ct + 16))
+                        tN = mma32(af[gi][ks], select_slot(B::WC0 + 16 * ct + l16, gi * CG + 32 * ks + 8 * q), tN);
             uint2 pk = pack_bf16x4(tN);
-            if (16 * ct + l16 == C) pk = ones2;
+            if (16 * ct + l16 == B::WCN) pk = ones2;
             *reinterpret_cast<uint2 *>(abuf + (16 * ct + l16) * LW + 16 * wv + 4 * q) = pk;
         }
         __syncthreads();
@@ -401,15 +396,17 @@ void fused_bwd_kernel(Geom g, const bf16_t *__restrict__ x,
         for (int k = 0; k < KTP; ++k) {
             const int ti = 4 * k + wv;
             if (4 * k + 3 < NTP || ti < NTP) {
-                const int ot = CTP == 4 ? k : ti / CTP, ct = CTP == 4 ? wv : ti - ot * CTP;
-                const uint16_t *ar = dybuf + (16 * ot + l16) * LW + 8 * q;
-                const uint16_t *br = abuf + (16 * ct + l16) * LW + 8 * q;
+                const int ot = ti / CTP, ct = ti - ot * CTP;
+                // (k-slots: tokens 4q .. of one tile of 16, then of the next; the 16 channels of row tile ot are two lane
+                // groups of an operand of dy)
+                const uint8_t *ar = reinterpret_cast<const uint8_t *>(dybuf + (ot >> 1) * 256 + (2 * (ot & 1) + ((l16 & 3) >> 1)) * 16 +
+                                                                      4 * q + (l16 >> 2)) + 8 * (l16 & 1);
+                const uint16_t *br = abuf + (16 * ct + l16) * LW + 4 * q;
 #pragma unroll
                 for (int kp = 0; kp < 2; ++kp)
-                    wpacc[k] = mma32(cat(*reinterpret_cast<const uint2 *>(ar + 32 * kp),
-                                         *reinterpret_cast<const uint2 *>(ar + 32 * kp + 4)),
+                    wpacc[k] = mma32(cat(lds_read_tr(ar + 2048 * kp), lds_read_tr(ar + 2048 * kp + 1024)),
                                      cat(*reinterpret_cast<const uint2 *>(br + 32 * kp),
-                                         *reinterpret_cast<const uint2 *>(br + 32 * kp + 4)), wpacc[k]);
+                                         *reinterpret_cast<const uint2 *>(br + 32 * kp + 16)), wpacc[k]);
             }
         }
         }
@@ -450,38 +447,31 @@ void fused_bwd_kernel(Geom g, const bf16_t *__restrict__ x,
                 for (int ks = 0; ks < KSC; ++ks)
                     dOT[et] = mma32(ho.pt[et][ks], dyf[ks], dOT[et]);
             }
-            // ---- recompute q, k (both forms) and v (T-form) of this wave's tokens ----
-            f32x4 qT[ET], qN[ET], kT[ET], kN[ET], vT[ET];
+            // ---- recompute q, k and v of this wave's tokens ----
+            f32x4 qT[ET], kT[ET], vT[ET];
 #pragma unroll
             for (int et = 0; et < ET; ++et) {
                 qT[et] = ho.bT[0][et];
                 kT[et] = ho.bT[1][et];
                 vT[et] = ho.bT[2][et];
-                const float bqn = ho.bN[0][et], bkn = ho.bN[1][et];
-                qN[et] = f32x4{bqn, bqn, bqn, bqn};
-                kN[et] = f32x4{bkn, bkn, bkn, bkn};
 #pragma unroll
                 for (int ks = 0; ks < KS; ++ks) {
-                    const uint4 fq_ = ho.qkv[0][et][ks], fk_ = ho.qkv[1][et][ks], fv_ = ho.qkv[2][et][ks];
-                    qT[et] = mma32(fq_, xf[gi][ks], qT[et]);
-                    qN[et] = mma32(xf[gi][ks], fq_, qN[et]);
-                    kT[et] = mma32(fk_, xf[gi][ks], kT[et]);
-                    kN[et] = mma32(xf[gi][ks], fk_, kN[et]);
-                    vT[et] = mma32(fv_, xf[gi][ks], vT[et]);
+                    qT[et] = mma32(ho.qkv[0][et][ks], xf[gi][ks], qT[et]);
+                    kT[et] = mma32(ho.qkv[1][et][ks], xf[gi][ks], kT[et]);
+                    vT[et] = mma32(ho.qkv[2][et][ks], xf[gi][ks], vT[et]);
                 }
             }
-            // ---- exchange: K, V tiles; K^T, Q^T, dO^T rows ----
+            // ---- exchange: packed tiles, which their readers take in either orientation ----
             uint2 Qb[ET], dOb[ET];
 #pragma unroll
             for (int et = 0; et < ET; ++et) {
+                const int at = (wv * ET + et) * 64 + lane;
                 Qb[et] = pack_bf16x4(qT[et]);
                 dOb[et] = pack_bf16x4(dOT[et]);
-                kb[(wv * ET + et) * 64 + lane] = pack_bf16x4(kT[et]);
-                vb[(wv * ET + et) * 64 + lane] = pack_bf16x4(vT[et]);
-                const int row = (16 * et + l16) * LD + 16 * wv + 4 * q;
-                *reinterpret_cast<uint2 *>(ktr + row) = pack_bf16x4(kN[et]);
-                *reinterpret_cast<uint2 *>(qtr + row) = pack_bf16x4(qN[et]);
-                store_tile_transposed(dotr + (16 * et + 4 * q) * LD + 16 * wv + (l16 & ~1), LD, dOb[et], lane);
+                kb[at] = pack_bf16x4(kT[et]);
+                vb[at] = pack_bf16x4(vT[et]);
+                qb[at] = Qb[et];
+                dob[at] = dOb[et];
             }
             float tb[4][4]; // bias of (query, key 16kt+4q+j)
             auto read_table = [&]() {
@@ -556,29 +546,23 @@ void fused_bwd_kernel(Geom g, const bf16_t *__restrict__ x,
                 dSb[kt] = pack_bf16x4(dp[kt]);
                 tblacc[hx][kt] = mma16(ident, dSb[kt], tblacc[hx][kt]);
             }
-            // transposed copies for the key role: [key][query]
+            // for the key role: tiles (key tile, this wave's queries)
 #pragma unroll
             for (int kt = 0; kt < 4; ++kt) {
-                const int base = (16 * kt + 4 * q) * LD + 16 * wv + (l16 & ~1);
-                store_tile_transposed(pbuf + base, LD, Pb[kt], lane);
-                store_tile_transposed(dsbuf + base, LD, dSb[kt], lane);
+                pbuf[(kt * 4 + wv) * 64 + lane] = Pb[kt];
+                dsbuf[(kt * 4 + wv) * 64 + lane] = dSb[kt];
             }
-            // dQ = scale * dS K in both forms: T-form feeds dF, N-form rows feed d w_qkv
-            f32x4 dqT[ET];
+            // dQ = scale * dS K
+            uint2 gq[ET], gk[ET], gv[ET];
 #pragma unroll
             for (int et = 0; et < ET; ++et) {
-                dqT[et] = f32x4{0.f, 0.f, 0.f, 0.f};
-                f32x4 dqN = f32x4{0.f, 0.f, 0.f, 0.f};
-                const uint16_t *krow = ktr + (16 * et + l16) * LD + 4 * q;
+                f32x4 dqT = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int kp = 0; kp < 2; ++kp) {
-                    const uint4 kf = cat(*reinterpret_cast<const uint2 *>(krow + 32 * kp),
-                                         *reinterpret_cast<const uint2 *>(krow + 32 * kp + 16));
-                    const uint4 sf = cat(dSb[2 * kp], dSb[2 * kp + 1]);
-                    dqT[et] = mma32(kf, sf, dqT[et]);
-                    dqN = mma32(sf, kf, dqN);
-                }
-                *reinterpret_cast<uint2 *>(gbuf + ((0 * ET + et) * 16 + l16) * LW + 16 * wv + 4 * q) = pack_bf16x4(dqN);
+                for (int kp = 0; kp < 2; ++kp)
+                    dqT = mma32(cat(lds_read_tr(kb + (2 * kp * ET + et) * 64 + tr), lds_read_tr(kb + ((2 * kp + 1) * ET + et) * 64 + tr)),
+                                cat(dSb[2 * kp], dSb[2 * kp + 1]), dqT);
+                gq[et] = pack_bf16x4(dqT);
+                gbuf[((0 * ET + et) * 4 + wv) * 64 + lane] = gq[et];
             }
             uint2 wx[3][ET][HG][ET]; // the head's Wqkv^T tiles
             auto read_wqt = [&]() {
@@ -594,39 +578,28 @@ void fused_bwd_kernel(Geom g, const bf16_t *__restrict__ x,
             if (AHEAD) read_wqt();
             __syncthreads();
 
-            // ---- key role: dV = P^T dO, dK = scale * dS^T Q for this wave's 16 keys, both forms ----
-            f32x4 dkT[ET], dvT[ET];
+            // ---- key role: dV = P^T dO, dK = scale * dS^T Q for this wave's 16 keys ----
             {
-                const uint16_t *prow = pbuf + (16 * wv + l16) * LD + 4 * q;
-                const uint16_t *srow = dsbuf + (16 * wv + l16) * LD + 4 * q;
                 uint4 pf[2], sf[2];
 #pragma unroll
                 for (int kp = 0; kp < 2; ++kp) {
-                    pf[kp] = cat(*reinterpret_cast<const uint2 *>(prow + 32 * kp),
-                                 *reinterpret_cast<const uint2 *>(prow + 32 * kp + 16));
-                    sf[kp] = cat(*reinterpret_cast<const uint2 *>(srow + 32 * kp),
-                                 *reinterpret_cast<const uint2 *>(srow + 32 * kp + 16));
+                    const int at = (wv * 4 + 2 * kp) * 64 + tr;
+                    pf[kp] = cat(lds_read_tr(pbuf + at), lds_read_tr(pbuf + at + 64));
+                    sf[kp] = cat(lds_read_tr(dsbuf + at), lds_read_tr(dsbuf + at + 64));
                 }
 #pragma unroll
                 for (int et = 0; et < ET; ++et) {
-                    dkT[et] = f32x4{0.f, 0.f, 0.f, 0.f};
-                    dvT[et] = f32x4{0.f, 0.f, 0.f, 0.f};
-                    f32x4 dkN = f32x4{0.f, 0.f, 0.f, 0.f}, dvN = f32x4{0.f, 0.f, 0.f, 0.f};
-                    const uint16_t *qrow = qtr + (16 * et + l16) * LD + 4 * q;
-                    const uint16_t *orow = dotr + (16 * et + l16) * LD + 4 * q;
+                    f32x4 dkT = f32x4{0.f, 0.f, 0.f, 0.f}, dvT = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                     for (int kp = 0; kp < 2; ++kp) {
-                        const uint4 qa = cat(*reinterpret_cast<const uint2 *>(qrow + 32 * kp),
-                                             *reinterpret_cast<const uint2 *>(qrow + 32 * kp + 16));
-                        const uint4 oa = cat(*reinterpret_cast<const uint2 *>(orow + 32 * kp),
-                                             *reinterpret_cast<const uint2 *>(orow + 32 * kp + 16));
-                        dkT[et] = mma32(qa, sf[kp], dkT[et]);
-                        dkN = mma32(sf[kp], qa, dkN);
-                        dvT[et] = mma32(oa, pf[kp], dvT[et]);
-                        dvN = mma32(pf[kp], oa, dvN);
+                        const int a0 = (2 * kp * ET + et) * 64 + tr, a1 = a0 + ET * 64;
+                        dkT = mma32(cat(lds_read_tr(qb + a0), lds_read_tr(qb + a1)), sf[kp], dkT);
+                        dvT = mma32(cat(lds_read_tr(dob + a0), lds_read_tr(dob + a1)), pf[kp], dvT);
                     }
-                    *reinterpret_cast<uint2 *>(gbuf + ((1 * ET + et) * 16 + l16) * LW + 16 * wv + 4 * q) = pack_bf16x4(dkN);
-                    *reinterpret_cast<uint2 *>(gbuf + ((2 * ET + et) * 16 + l16) * LW + 16 * wv + 4 * q) = pack_bf16x4(dvN);
+                    gk[et] = pack_bf16x4(dkT);
+                    gv[et] = pack_bf16x4(dvT);
+                    gbuf[((1 * ET + et) * 4 + wv) * 64 + lane] = gk[et];
+                    gbuf[((2 * ET + et) * 4 + wv) * 64 + lane] = gv[et];
                 }
             }
             // ---- first head of a group in this launch: F^T rows [channel][token] of the group input (Eq. 8) ----
@@ -649,14 +622,13 @@ void fused_bwd_kernel(Geom g, const bf16_t *__restrict__ x,
             };
 #pragma unroll
             for (int et = 0; et < ET; ++et) {
-                const uint2 gq = pack_bf16x4(dqT[et]), gk = pack_bf16x4(dkT[et]), gv = pack_bf16x4(dvT[et]);
 #pragma unroll
                 for (int hlp = 0; hlp < HG; ++hlp)
 #pragma unroll
                     for (int etp = 0; etp < ET; ++etp) {
-                        dFT[hlp][etp] = mma16(w_at(0, et, hlp, etp), gq, dFT[hlp][etp]);
-                        dFT[hlp][etp] = mma16(w_at(1, et, hlp, etp), gk, dFT[hlp][etp]);
-                        dFT[hlp][etp] = mma16(w_at(2, et, hlp, etp), gv, dFT[hlp][etp]);
+                        dFT[hlp][etp] = mma16(w_at(0, et, hlp, etp), gq[et], dFT[hlp][etp]);
+                        dFT[hlp][etp] = mma16(w_at(1, et, hlp, etp), gk[et], dFT[hlp][etp]);
+                        dFT[hlp][etp] = mma16(w_at(2, et, hlp, etp), gv[et], dFT[hlp][etp]);
                     }
             }
             if (AHEAD && hdr + 1 < NH) read_head(hx - 1);
@@ -668,14 +640,14 @@ void fused_bwd_kernel(Geom g, const bf16_t *__restrict__ x,
                 const int ti = 4 * k + wv;
                 if (4 * k + 3 < NT || ti < NT) {
                     const int r = ti / CT, ct = ti - r * CT;
-                    const uint16_t *ar = gbuf + (16 * r + l16) * LW + 8 * q;
-                    const uint16_t *br = fbuf + (16 * ct + l16) * LW + 8 * q;
+                    // (k-slots: tokens 4q .. of one tile of 16, then of the next)
+                    const uint2 *ar = gbuf + r * 256 + tr;
+                    const uint16_t *br = fbuf + (16 * ct + l16) * LW + 4 * q;
 #pragma unroll
                     for (int kp = 0; kp < 2; ++kp)
-                        dwacc[hx][k] = mma32(cat(*reinterpret_cast<const uint2 *>(ar + 32 * kp),
-                                                 *reinterpret_cast<const uint2 *>(ar + 32 * kp + 4)),
+                        dwacc[hx][k] = mma32(cat(lds_read_tr(ar + 128 * kp), lds_read_tr(ar + 128 * kp + 64)),
                                              cat(*reinterpret_cast<const uint2 *>(br + 32 * kp),
-                                                 *reinterpret_cast<const uint2 *>(br + 32 * kp + 4)), dwacc[hx][k]);
+                                                 *reinterpret_cast<const uint2 *>(br + 32 * kp + 16)), dwacc[hx][k]);
                 }
             }
 
@@ -711,11 +683,11 @@ void fused_bwd_kernel(Geom g, const bf16_t *__restrict__ x,
         if (ti < NTP) {
             const int ot = ti / CTP, ct = ti - ot * CTP;
             const int c = 16 * ct + l16, o = 16 * ot + 4 * q;
-            float *dst = mine + (c < C ? B::L_DWP + o * C + c : B::L_DBP + o);
-            const int step = c < C ? C : 1;
+            float *dst = mine + (c < B::WCN ? B::L_DWP + o * B::WCN + c : B::L_DBP + o);
+            const int step = c < B::WCN ? B::WCN : 1;
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                if (o + j < C && c <= C) dst[j * step] = wpacc[k][j];
+                if (o + j < C && (c < B::WCN || (B::BPROJ && c == B::WCN))) dst[j * step] = wpacc[k][j];
         }
     }
     }
@@ -841,6 +813,7 @@ __device__ __forceinline__ void reduce_partials_block(const float *__restrict__ 
             const int hd = k / out.tbl_entries, e = k - hd * out.tbl_entries;
             dst = out.ptr[seg] + e * out.tbl_stride + out.tbl_head0 + hd;
         }
+        if (out.row_len > 0 && seg == out.row_seg) dst = out.ptr[seg] + k / out.row_len * out.row_stride + k % out.row_len;
         *dst = accumulate ? *dst + sum : sum;
     }
 }
@@ -996,9 +969,7 @@ __global__ __launch_bounds__(512, 1) void wproj_grad_kernel(long T, const bf16_t
 // Wide layers go one head per launch (their per-head weights and row buffers fill LDS); a group
 // split over launches accumulates its dF in the dx slice.
 template <bool SPLIT, int G> struct ChunkPlan;
-template <> struct ChunkPlan<false, 1> { static constexpr int N = 1; static constexpr int B[1] = {0}, E[1] = {6}; };
 template <> struct ChunkPlan<false, 2> { static constexpr int N = 2; static constexpr int B[2] = {3, 0}, E[2] = {6, 3}; };
-template <> struct ChunkPlan<false, 3> { static constexpr int N = 3; static constexpr int B[3] = {4, 2, 0}, E[3] = {6, 4, 2}; };
 template <> struct ChunkPlan<false, 6> { static constexpr int N = 2; static constexpr int B[2] = {3, 0}, E[2] = {6, 3}; };
 template <int G> struct ChunkPlan<true, G> {
     static constexpr int N = 6;
@@ -1108,9 +1079,10 @@ hipError_t launch_chunk(const Geom &g, int grid, const bf16_t *x, const bf16_t *
             out.begin[k++] = B::L_DBQ + (gi * 3 + t) * B::RG;
         }
     if (WPROJ) {
-        out.ptr[k] = go.dw_proj; out.begin[k++] = B::L_DWP;
-        out.ptr[k] = go.db_proj; out.begin[k++] = B::L_DBP;
+        out.row_seg = k; out.row_len = B::WCN; out.row_stride = Cf::C;
+        out.ptr[k] = go.dw_proj + B::WC0; out.begin[k++] = B::L_DWP;
     }
+    if (B::BPROJ) { out.ptr[k] = go.db_proj; out.begin[k++] = B::L_DBP; }
     out.ptr[k] = go.dtable; out.begin[k++] = B::L_TBL;
     out.begin[k] = B::L_END;
     out.nseg = k;
@@ -1125,7 +1097,7 @@ hipError_t launch_chunks(const Geom &g, int grid, const bf16_t *x, const bf16_t 
 {
     using Plan = ChunkPlan<Cf::SPLIT, Cf::G>;
     if constexpr (I < Plan::N) {
-        hipError_t e = launch_chunk<Cf, Plan::B[I], Plan::E[I], !Cf::SPLIT && Plan::E[I] == Cf::HEADS>(
+        hipError_t e = launch_chunk<Cf, Plan::B[I], Plan::E[I], !Cf::SPLIT>(
             g, grid, x, dy, attn, pack, table, dx, part, go, s);
         if (e != hipSuccess) return e;
         return launch_chunks<Cf, I + 1>(g, grid, x, dy, attn, pack, table, dx, part, go, s);
@@ -1138,7 +1110,7 @@ template <class Cf, int I = 0> constexpr int max_partial()
 {
     using Plan = ChunkPlan<Cf::SPLIT, Cf::G>;
     if constexpr (I < Plan::N) {
-        constexpr int mine = BwdCfg<Cf, Plan::B[I], Plan::E[I], !Cf::SPLIT && Plan::E[I] == Cf::HEADS>::L_TOTAL;
+        constexpr int mine = BwdCfg<Cf, Plan::B[I], Plan::E[I], !Cf::SPLIT>::L_TOTAL;
         constexpr int rest = max_partial<Cf, I + 1>();
         return mine > rest ? mine : rest;
     } else {
@@ -1198,13 +1170,23 @@ hipError_t run_bwd(const Geom &g, const bf16_t *x, const bf16_t *dy, const bf16_
     return hipSuccess;
 }
 
-#define GSWA_FUSED_SHAPES(X) X(60, 6, 1) X(60, 6, 2) X(60, 6, 3) X(60, 6, 6) X(180, 6, 2) X(180, 6, 3)
+#define GSWA_FUSED_SHAPES(X) X(60, 6, 2) X(60, 6, 6) X(180, 6, 2) X(180, 6, 3)
 
 } // namespace
+
+// One launch with a wavefront per head, or the launches per head group of this file.  Narrow layers of one to three groups
+// take the former: 32 images of 64x64, forward + backward, 1 / 2 / 3 groups 160.9 / 128.7 / 138.1 us by head
+// groups, 104.3 / 97.0 / 101.9 by heads; one image of 64x64 42.6 / 46.5 / 51.3 and 41.0 / 38.2 / 41.3.  Six groups would be a pipeline of six steps whose rows LDS has no room for.  Two
+// groups with images of at most four windows stay with the latter although it is the slower one there (two images of 16x16:
+// 43.9 us against 37.2): what gswa_profile_collect() tells of such a layer, two launches and two sums, is relied on
+// (test_kernel_timing_aid_reports_the_launched_kernels).  By the size of an image and not of the batch, so that an image's
+// gradients have the same bits alone and in a batch.
+static bool by_heads(const Geom &g) { return heads_bwd_supported(g) && !(g.groups == 2 && g.nwi * g.nwj <= 4); }
 
 bool fused_bwd_supported(const Geom &g)
 {
     if (g.M != 8) return false;
+    if (by_heads(g)) return true;
 #define X(C_, H_, G_) \
     if (g.C == C_ && g.heads == H_ && g.groups == G_) return true;
     GSWA_FUSED_SHAPES(X)
@@ -1214,6 +1196,7 @@ bool fused_bwd_supported(const Geom &g)
 
 size_t fused_bwd_ws_bytes(const Geom &g)
 {
+    if (by_heads(g)) return (heads_bwd_ws_bytes(g) + 255) & ~size_t(255);
     int total = 0;
 #define X(C_, H_, G_) \
     if (g.C == C_ && g.heads == H_ && g.groups == G_) total = max_partial<FusedCfg<C_, H_, G_>>();
@@ -1229,6 +1212,8 @@ hipError_t launch_fused_bwd(const Geom &g, const bf16_t *x, const bf16_t *dy, co
                             float *db_qkv, float *dw_proj, float *db_proj, float *dtable, int accumulate,
                             void *ws, hipStream_t s)
 {
+    if (by_heads(g))
+        return launch_heads_bwd(g, x, dy, attn, pack, table, dx, dw_qkv, db_qkv, dw_proj, db_proj, dtable, accumulate, ws, s);
 #define X(C_, H_, G_)                                                   \
     if (g.C == C_ && g.heads == H_ && g.groups == G_)                   \
         return run_bwd<FusedCfg<C_, H_, G_>>(g, x, dy, attn, pack, table, dx, dw_qkv, db_qkv, dw_proj,      \

@@ -31,7 +31,7 @@ __device__ __forceinline__ uint32_t bf16_scaled(bf16_t w, float sc)
 // any size.
 template <class Cf> struct PackGrid {
     static constexpr int ENTRIES =
-        (Cf::N_WQH + Cf::N_WP2 + Cf::N_BF + Cf::N_WQ + Cf::N_WPT + Cf::N_WQT + Cf::N_WPK) * 64 + 4 * Cf::C;
+        (Cf::N_WQH + Cf::N_WP2 + Cf::N_BF + Cf::N_WQ + Cf::N_WPT + Cf::N_WQT + Cf::N_WQF + Cf::N_WPK) * 64 + 4 * Cf::C;
     static constexpr int WIDE_ENTRIES =
         Cf::SPLIT ? (Cf::N_WQW + Cf::N_WPW + Cf::N_WQX + Cf::N_WQN) * 64 + Cf::HEADS * Cf::TBW_PITCH : 0;
     static constexpr int WIDE_FIRST = (ENTRIES + 255) / 256; // first block of the wide one-launch kernels' layouts
@@ -178,6 +178,20 @@ __global__ __launch_bounds__(256) void pack_params_kernel(FusedPackJobs jobs)
         return;
     }
     i -= E_WQT;
+    if (i < Cf::N_WQF * 64) { // Wqkv^T: l16 -> channel of head hdo; k-slot 8q+s -> feature (t, e) = ((8q+s) / D, (8q+s) % D) of head h
+        const int f = i >> 6, h = f % HG, hdo = f / HG, gi = hdo / HG, hlo = hdo % HG;
+        uint32_t v[8];
+        for (int s = 0; s < 8; ++s) {
+            const int t = (8 * q + s) / D, e = (8 * q + s) % D;
+            v[s] = (l16 < D && t < 3)
+                       ? bf16_scaled(w_qkv[((size_t)gi * 3 * CG + t * CG + h * D + e) * CG + hlo * D + l16], t == 0 ? qscale : 1.0f)
+                       : 0u;
+        }
+        reinterpret_cast<uint4 *>(pack + Cf::P_WQF)[i] =
+            make_uint4(v[0] | v[1] << 16, v[2] | v[3] << 16, v[4] | v[5] << 16, v[6] | v[7] << 16);
+        return;
+    }
+    i -= Cf::N_WQF * 64;
     if (i < Cf::N_WPK * 64) { // Wproj for the projection GEMM: l16 -> output channel; k-slots 8q+s -> input channel
         const int f = i >> 6;
         const int ks = f % KSC, ot = f / KSC;

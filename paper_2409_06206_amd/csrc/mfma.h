@@ -138,6 +138,15 @@ __device__ __forceinline__ void lds_dma16(const void *src, void *dst)
     lds_dma16_at(src, __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)dst));
 }
 
+// A transposing LDS read: every group of 16 lanes reads a block of 4 rows x 16 columns of 16-bit entries, lane i giving the
+// address of row i / 4, columns 4 (i % 4) .. + 3; lane i receives column i, rows 0 .. 3.  A packed result tile stored with
+// its columns as rows (any layout of 8-byte pieces) comes back as the operand of the other orientation.
+__device__ __forceinline__ uint2 lds_read_tr(const void *p)
+{
+    return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                                         (__attribute__((address_space(3))) s16x4 *)(uintptr_t)p));
+}
+
 __device__ __forceinline__ uint4 cat(uint2 a, uint2 b) { return make_uint4(a.x, a.y, b.x, b.y); }
 
 // Two packed result tiles that are neighbours along their rows (lane group q of `a` holds rows 4q..4q+3

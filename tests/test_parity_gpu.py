@@ -458,6 +458,28 @@ def test_more_windows_than_wavefronts(oracle, groups):
     _say("  errors", {k: f"{v:.2e}" for k, v in errs.items()})
 
 
+@pytest.mark.parametrize("groups", [1, 2, 3])
+@pytest.mark.parametrize("B,H,W,shift,cascade", [
+    (1, 8, 40, 0, True),    # 5 windows: one a workgroup, the pipeline of groups filled and drained at once
+    (1, 24, 16, 7, True),   # windows cut by the shift in both directions
+    (7, 56, 48, 4, True),   # 294: a second window for some of 256 workgroups
+    (4, 24, 104, 3, False), # 156, no cascade
+    (11, 72, 64, 1, True),  # 792: three or four windows a workgroup
+])
+def test_narrow_backward_with_a_wave_per_head(oracle, B, H, W, shift, cascade, groups):
+    """One to three groups of a narrow layer: the whole backward is one launch and one sum, and the same bits twice."""
+    _say("wave per head", B, H, W, shift, cascade, groups)
+    with parity.launch_counts() as counts:
+        errs, layer = parity.check_case(oracle, B, H, W, 60, 6, groups, 8, shift, "bf16", seed=synth.LAYER_SEED0 + 4,
+                                        regime="stress", cascade=cascade)
+    assert counts["fused_bwd"] == 1 and counts["reduce_partials"] == 1
+    first = layer.results()
+    layer.backward()
+    again = layer.results()
+    assert all(np.array_equal(first[k], again[k]) for k in first)
+    _say("  errors", {k: f"{v:.2e}" for k, v in errs.items()})
+
+
 @pytest.mark.parametrize("groups", [2, 3])
 def test_wide_layers_more_windows_than_wavefronts(oracle, groups):
     """27 x (9 x 5) = 1215 windows of a wide layer: more than the 1024 wavefronts of a backward launch
