@@ -26,10 +26,11 @@ hipError_t launch_astl_mlp_wide_pack(int C, int hidden, const MlpPackJob *jobs, 
 struct NarrowMlpPack {
     static constexpr int FT = 8, KSF = 4, W2 = 1024, FLOATS = 2048, SRC_FLOATS = 4096;
     static constexpr size_t LDS_BYTES = (size_t)FLOATS * 16 + 192 * 4;
-    // into LDS, by n threads
-    static __device__ __forceinline__ void stage(uint4 *dst, const uint4 *src, int tid, int n)
+    static_assert(FLOATS % 1024 == 0, "whole pieces of 16 waves");
+    // what stands behind the fragments: the first 48 threads copy it
+    static __device__ __forceinline__ void stage_floats(uint4 *dst, const uint4 *src, int tid)
     {
-        for (int i = tid; i < FLOATS + 48; i += n) dst[i] = src[i < FLOATS ? i : i + SRC_FLOATS - FLOATS];
+        if (tid >= 0 && tid < 48) dst[FLOATS + tid] = src[SRC_FLOATS + tid];
     }
 };
 

@@ -251,7 +251,6 @@ template <class Cf, bool LAYER> struct Wave4FwdCfg {
     static constexpr size_t OFF_COPY = (size_t)16 * Cf::C;
     static constexpr size_t OFF_WQH = OFF_COPY + Cf::P_WQH, OFF_WP2 = OFF_COPY + Cf::P_WP2, OFF_BF = OFF_COPY + Cf::P_BF;
     static constexpr size_t COPY_BYTES = Cf::P_WQ;
-    static constexpr int COPY_IT = (int)((COPY_BYTES / 16 + NTHREADS - 1) / NTHREADS);
     // whole layer: LN_1's (gamma, beta) in head-padded order [HEADS][16], W1, W2 fragments and the MLP's biases
     static constexpr size_t OFF_LN = OFF_COPY + COPY_BYTES;
     static constexpr size_t OFF_MLP = OFF_LN + (LAYER ? (size_t)Cf::HEADS * 16 * 8 : 0);
@@ -654,27 +653,39 @@ __global__ __launch_bounds__(1024) void wave4_fwd_kernel(Geom g, const bf16_t *_
         load_first();
     }
 
-    // ---- set-up: packed weights, bias operands and linear biases into LDS (unrolled, so that the
-    // loads of a thread are all in flight together); the workgroups start at different offsets
-    // so that they do not all ask for the same cache lines at once ----
+    // ---- set-up: packed weights, bias operands and linear biases into LDS, written there by the loads themselves; the
+    // workgroups start at different offsets so that they do not all ask for the same cache lines at once.  The MLP's
+    // weights are not waited for here but in front of the last heads.  (99 windows: 9.0 k clocks of a layer's 27.5 k were
+    // set-up, three trips to memory one after the other.) ----
     {
-        constexpr int N16 = (int)(W::COPY_BYTES / 16);
-        const int rot = (int)((blockIdx.x * 5u) % (unsigned)W::COPY_IT);
+        constexpr int N1K = (int)(W::COPY_BYTES / 1024), IT = (N1K + W::NWAVES - 1) / W::NWAVES;
+        static_assert(W::COPY_BYTES % 1024 == 0 && W::OFF_COPY % 16 == 0, "whole pieces of a wave");
+        const int rot = (int)((blockIdx.x * 5u) % (unsigned)N1K);
 #pragma unroll
-        for (int k = 0; k < W::COPY_IT; ++k) {
-            int kk = k + rot;
-            if (kk >= W::COPY_IT) kk -= W::COPY_IT;
-            const int i = kk * NTHREADS + tid;
-            if (i < N16) reinterpret_cast<uint4 *>(lds + W::OFF_COPY)[i] = reinterpret_cast<const uint4 *>(pack)[i];
+        for (int k = 0; k < IT; ++k) {
+            int f = k * W::NWAVES + wv;
+            if (f < N1K) {
+                f += rot;
+                if (f >= N1K) f -= N1K;
+                lds_dma16(pack + (size_t)f * 1024 + 16 * lane, lds + W::OFF_COPY + (size_t)f * 1024);
+            }
         }
         if (tid < C)
             reinterpret_cast<uint4 *>(lds + W::OFF_BIAS)[tid] = reinterpret_cast<const uint4 *>(pack + Cf::P_BIAS)[tid];
         if constexpr (LAYER) {
-            NarrowMlpPack::stage(reinterpret_cast<uint4 *>(lds + W::OFF_MLP), la.mlp, tid, NTHREADS);
-            if (tid < HEADS * 16) {
-                const int e = tid & 15, c = (tid >> 4) * D + e;
-                reinterpret_cast<float2 *>(lds + W::OFF_LN)[tid] =
-                    e < D ? make_float2(to_f32(la.ln1_w[c]), to_f32(la.ln1_b[c])) : make_float2(0.f, 0.f);
+            if (tid >= 512 && tid < 512 + HEADS * 16) {
+                const int i = tid - 512, e = i & 15, c = (i >> 4) * D + (e < D ? e : 0);
+                const float w = to_f32(la.ln1_w[c]), b = to_f32(la.ln1_b[c]);
+                reinterpret_cast<float2 *>(lds + W::OFF_LN)[i] = e < D ? make_float2(w, b) : make_float2(0.f, 0.f);
+            }
+            NarrowMlpPack::stage_floats(reinterpret_cast<uint4 *>(lds + W::OFF_MLP), la.mlp, tid - 256);
+        }
+        __builtin_amdgcn_s_waitcnt(0);
+        if constexpr (LAYER) {
+#pragma unroll
+            for (int k = 0; k < NarrowMlpPack::FLOATS / 64 / W::NWAVES; ++k) {
+                const int f = k * W::NWAVES + wv;
+                lds_dma16(la.mlp + f * 64 + lane, lds + W::OFF_MLP + (size_t)f * 1024);
             }
         }
     }
@@ -814,6 +825,7 @@ __global__ __launch_bounds__(1024) void wave4_fwd_kernel(Geom g, const bf16_t *_
                     }
                 }
             }
+            if (LAYER && h0 + HB == HEADS && round == 0) __builtin_amdgcn_s_waitcnt(0); // (the MLP's weights)
             __syncthreads();
             if (active) {
 #pragma unroll
