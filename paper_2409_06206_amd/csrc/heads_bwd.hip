@@ -85,9 +85,11 @@ constexpr bool overlap(int a0, int a1, int b0, int b1) { return a0 < b1 && b0 < 
 // What bounds it: six heads on four SIMD units, so two units issue the steps of two heads, 12.5 k clocks a window where a head
 // alone takes 10 k (four query tiles of 1.6 k, 3 k before and 1 k behind them); most of a tile is the chain products -> softmax
 // -> products.  Against launches per head group with a window in four waves and three barriers a head: 32 images of 64x64, 60
-// channels, forward + backward, 1 / 2 / 3 groups 160.9 / 128.7 / 138.1 -> 104.3 / 97.0 / 101.9 us.  On the way there, two groups:
+// channels, forward + backward, 1 / 2 / 3 groups 160.9 / 128.7 / 138.1 -> 99.6 / 91.9 / 96.6 us.  On the way there, two groups:
 // turned reads in place of products with the identity 107.9 -> 108.0 (fewer instructions, more waits), every read in front of
-// the first write 104.1, dF of the first group on waves 6 and 7 102.7, d(q|k|v) in 32 features a head instead of 3 x 16 97.0.
+// the first write 104.1, dF of the first group on waves 6 and 7 102.7, d(q|k|v) in 32 features a head instead of 3 x 16 97.0.  Then the ends: set-up in one trip
+// to memory and the table's diagonals with all reads in flight (8.4 -> 6.8 k and 17.5 -> 7.5 k clocks of 130 k): 91.9; one image of
+// 64x64 38.2 -> 32.3.
 template <class Cf>
 __global__ __launch_bounds__(HeadsCfg<Cf>::THREADS, 2) void heads_bwd_kernel(Geom g, const bf16_t *__restrict__ x,
                                                                             const bf16_t *__restrict__ dy,
@@ -117,19 +119,31 @@ __global__ __launch_bounds__(HeadsCfg<Cf>::THREADS, 2) void heads_bwd_kernel(Geo
     const int cnt = (g.nW - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x; // windows blockIdx.x + m gridDim.x, m < cnt
 
     const int hw = wv - HEADS;
-    // ---- set-up: weights and biases to LDS, the table to where the first d(q|k|v) go later ----
+    // ---- set-up: weights, biases and the table to LDS, all loads in flight together ----
     auto setup = [&](int tid) {
-        constexpr int TH = P::THREADS;
-        auto copy = [&](size_t dst, size_t src, int n) { // 16-byte pieces
-            for (int i = tid; i < n; i += TH) reinterpret_cast<uint4 *>(lds + dst)[i] = reinterpret_cast<const uint4 *>(pack + src)[i];
-        };
-        copy(P::OFF_WPT, Cf::P_WPT, (int)(P::SZ_WPT / 16));
-        for (int i = tid; i < HEADS * 48; i += TH) {
-            const int e = i % 16, t = i / 16 % 3, hd = i / 48;
-            const float v = reinterpret_cast<const float *>(pack + Cf::P_BIAS)[hd / HG * 3 * CG + t * CG + hd % HG * D + (e < D ? e : 0)];
-            reinterpret_cast<float *>(lds + P::OFF_BIAS)[i] = e < D ? v : 0.f;
+        constexpr int TH = P::THREADS, NW = TH / 64, N1K = (int)(P::SZ_WPT / 1024), N_T = P::NTBL * HEADS / 2;
+        constexpr int I_T = (N_T + TH - 1) / TH;
+        static_assert(P::NTBL * HEADS % 2 == 0 && HEADS * 48 <= TH && P::SZ_WPT % 1024 == 0, "set-up in whole pieces");
+        const int lane = tid & 63;
+#pragma unroll
+        for (int k = 0; k < (N1K + NW - 1) / NW; ++k) {
+            const int f = k * NW + wv;
+            if (f < N1K) lds_dma16(pack + Cf::P_WPT + (size_t)f * 1024 + 16 * lane, lds + P::OFF_WPT + (size_t)f * 1024);
         }
-        for (int i = tid; i < P::NTBL * HEADS; i += TH) tbl[i] = table[i];
+        const int i = tid < HEADS * 48 ? tid : 0, e = i % 16, t = i / 16 % 3, hd = i / 48;
+        const float v = reinterpret_cast<const float *>(pack + Cf::P_BIAS)[hd / HG * 3 * CG + t * CG + hd % HG * D + (e < D ? e : 0)];
+        uint16_t tv[I_T][2];
+#pragma unroll
+        for (int k = 0; k < I_T; ++k) {
+            const int at = k * TH + tid < N_T ? k * TH + tid : N_T - 1;
+            tv[k][0] = table[2 * at].bits;
+            tv[k][1] = table[2 * at + 1].bits;
+        }
+        if (tid < HEADS * 48) reinterpret_cast<float *>(lds + P::OFF_BIAS)[i] = e < D ? v : 0.f;
+#pragma unroll
+        for (int k = 0; k < I_T; ++k)
+            if (k * TH + tid < N_T) reinterpret_cast<uint32_t *>(tbl)[k * TH + tid] = tv[k][0] | (uint32_t)tv[k][1] << 16;
+        __builtin_amdgcn_s_waitcnt(0);
     };
     // Wqkv^T tiles of group gn for the channels of its head hlp, a token tile of its dF (d(q|k|v) of the group's first head at
     // `src`, this lane's piece), and that tile's place in dx
@@ -195,9 +209,9 @@ __global__ __launch_bounds__(HeadsCfg<Cf>::THREADS, 2) void heads_bwd_kernel(Geo
             }
         };
         f32x4 wpacc[OTP][CTP];
-        // window m: its operands to LDS, its share of d w_proj | d b_proj
+        // window m: its operands to LDS; then its share of d w_proj | d b_proj
+        uint4 dyf[2][KSC], af[2][G][KS];
         auto stage = [&](int m) {
-            uint4 dyf[2][KSC], af[2][G][KS];
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
                 const int tt = 2 * hw + i;
@@ -229,6 +243,8 @@ __global__ __launch_bounds__(HeadsCfg<Cf>::THREADS, 2) void heads_bwd_kernel(Geo
                 if (q == 0) tokb[(m % P::TOK_SLOTS) * 64 + 16 * tt + l16] = rtok[i];
             }
             if (tid == 64 * HEADS) flagb[m % P::TOK_SLOTS] = rflag;
+        };
+        auto project = [&] {
             // dY^T and [A | 1]^T of the two token tiles, K = 32 tokens
             uint4 aN[CTP];
 #pragma unroll
@@ -268,10 +284,12 @@ __global__ __launch_bounds__(HeadsCfg<Cf>::THREADS, 2) void heads_bwd_kernel(Geo
         stage(0);
         if (cnt > 1) load_rows(1);
         __syncthreads();
+        project();
         for (int n = 0; n < cnt + G; ++n) {
             if (n + 1 < cnt) {
                 stage(n + 1);
                 if (n + 2 < cnt) load_rows(n + 2);
+                project();
             }
             // dF of the first group, whose heads were done with window n - G in the step before
             if (n >= G) {
@@ -570,19 +588,27 @@ __global__ __launch_bounds__(HeadsCfg<Cf>::THREADS, 2) void heads_bwd_kernel(Geo
             for (int j = 0; j < 4; ++j) mat[(dl * 16 + 4 * q + j) * P::TP + l16] = tblacc[dl][j];
     }
     __syncthreads();
-    // the entry of offsets (dr, dc): query rows and columns r, c of a tile pair with key row r - dr + 2 (dl - 3) ...
+    // The entry of offset (dr, dc) of a query from its key: in tiles of two window rows the query's row is rq, the key's rk,
+    // with rq - rk - dr = 2 (dl - 3), which two of the four pairs fulfil; eight columns each, all reads in flight.
     const float *mat = fold + hd * P::NDLT * 16 * P::TP;
-    for (int e = le; e < P::NTBL; e += 64) {
-        const int dr = e / (2 * M - 1) - (M - 1), dc = e % (2 * M - 1) - (M - 1);
+#pragma unroll
+    for (int k = 0; k < (P::NTBL + 63) / 64; ++k) {
+        const int e = 64 * k + le < P::NTBL ? 64 * k + le : P::NTBL - 1;
+        const int dr = e / (2 * M - 1) - (M - 1), dc = e % (2 * M - 1) - (M - 1), odd = dr & 1;
         float a = 0.f;
 #pragma unroll
-        for (int rr = 0; rr < 4; ++rr) { // query row, key row inside their tiles of two rows
-            const int rq = rr >> 1, rk = rr & 1, d2 = rq - rk - dr; // = 2 (dl - 3)
-            if (d2 & 1 || d2 < -6 || d2 > 6) continue;
-            const float *t = mat + ((d2 / 2 + 3) * 16 + 8 * rk) * P::TP + 8 * rq;
-            for (int c = dc > 0 ? dc : 0; c < (dc < 0 ? M + dc : M); ++c) a += t[(c - dc) * P::TP + c];
+        for (int i = 0; i < 2; ++i) {
+            const int rq = odd ? 1 - i : i, rk = i, d2 = rq - rk - dr;
+            const bool ok = d2 >= -6 && d2 <= 6;
+            const float *t = mat + (((ok ? d2 / 2 : 0) + 3) * 16 + 8 * rk) * P::TP + 8 * rq;
+#pragma unroll
+            for (int c = 0; c < M; ++c) {
+                const int ck = c - dc;
+                const float v = t[(ck < 0 ? 0 : ck >= M ? M - 1 : ck) * P::TP + c];
+                a += ok && ck >= 0 && ck < M ? v : 0.f;
+            }
         }
-        mine[P::L_TBL + hd * P::NTBL + e] = a;
+        if (64 * k + le < P::NTBL) mine[P::L_TBL + hd * P::NTBL + e] = a;
     }
 }
 
