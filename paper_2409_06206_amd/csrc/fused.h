@@ -97,7 +97,12 @@ template <int C_, int HEADS_, int G_> struct FusedCfg {
     //        log2(e)/sqrt(d) as in WQW: the backward recomputes q, k, v from 16-byte row pieces
     static constexpr int N_WQN = SPLIT ? N_WQ : 0;
     static constexpr size_t P_WQN = P_WQX + (size_t)N_WQX * 1024;
-    static constexpr size_t P_END = P_WQN + (size_t)N_WQN * 1024;
+    //   WQY  Wqkv^T for dF by heads (wide_heads_bwd.hip), K=32: k-slots = the 3 D features q | k | v of a head in KF steps;
+    //        (hdo, et, h, ks): row l16 -> channel 16 et + l16 of head hdo, features of head h of the same group
+    static constexpr bool WIDE_HEADS = SPLIT && HG == 3;
+    static constexpr int KF = (3 * D + 31) / 32, N_WQY = WIDE_HEADS ? HEADS * ET * HG * KF : 0;
+    static constexpr size_t P_WQY = P_WQN + (size_t)N_WQN * 1024;
+    static constexpr size_t P_END = P_WQY + (size_t)N_WQY * 1024;
 };
 
 // True when a fused forward instantiation exists for this geometry (bf16 only).
@@ -143,7 +148,7 @@ hipError_t launch_fused_fwd(const Geom &g, const bf16_t *x, const bf16_t *w_qkv,
 // ---------------------------------------------------------------------------------------
 // Parameter packing for this kernel (layout: FusedCfg, WQW / WPW / TBW)
 // ---------------------------------------------------------------------------------------
-// (entry i of the (N_WQW + N_WPW + N_WQX + N_WQN) * 64 + HEADS * TBW_PITCH of the wide layout; run by the extra
+// (entry i of the (N_WQW + N_WPW + N_WQX + N_WQN + N_WQY) * 64 + HEADS * TBW_PITCH of the wide layout; run by the extra
 // blocks of the parameter-packing launch)
 template <class Cf>
 __device__ __forceinline__ void wide_pack_entry(int i, const bf16_t *__restrict__ w_qkv,
@@ -234,6 +239,23 @@ __device__ __forceinline__ void wide_pack_entry(int i, const bf16_t *__restrict_
         }
         reinterpret_cast<uint4 *>(pack + Cf::P_WQN)[i] =
             make_uint4(v[0] | v[1] << 16, v[2] | v[3] << 16, v[4] | v[5] << 16, v[6] | v[7] << 16);
+        return;
+    }
+    i -= Cf::N_WQN * 64;
+    if (i < Cf::N_WQY * 64) { // Wqkv^T by heads: row l16 -> channel 16 et + l16 of head hdo, k-slots -> feature (t, e) of head h
+        int f = i >> 6;
+        const int ks = f % Cf::KF; f /= Cf::KF;
+        const int h = f % HG; f /= HG;
+        const int et = f % ET, hdo = f / ET, gi = hdo / HG, hlo = hdo % HG, c = 16 * et + (i & 15);
+        uint32_t v[8];
+        for (int s = 0; s < 8; ++s) {
+            const int u = 32 * ks + 8 * ((i >> 4) & 3) + s, t = u / D, e = u - t * D;
+            float w = 0.f;
+            if (c < D && t < 3) w = to_f32(w_qkv[((size_t)gi * 3 * CG + t * CG + h * D + e) * CG + hlo * D + c]) * (t == 0 ? 1.0f / sqrtf((float)D) : 1.0f);
+            v[s] = f32_to_bf16_bits(w);
+        }
+        reinterpret_cast<uint4 *>(pack + Cf::P_WQY)[i] =
+            make_uint4(v[0] | v[1] << 16, v[2] | v[3] << 16, v[4] | v[5] << 16, v[6] | v[7] << 16);
     }
 }
 
@@ -281,7 +303,7 @@ bool wide_bwd_supported(const Geom &g);
 size_t wide_bwd_ws_bytes(const Geom &g);
 size_t wide_bwd_free_bytes(const Geom &g);
 hipError_t launch_wide_bwd(const Geom &g, const bf16_t *x, const bf16_t *dy, const bf16_t *attn, const void *pack,
-                           bf16_t *dx, float *dw_qkv, float *db_qkv, float *dtable, int accumulate, void *ws,
+                           const bf16_t *table, bf16_t *dx, float *dw_qkv, float *db_qkv, float *dtable, int accumulate, void *ws,
                            ReduceJob (&sums)[2], hipStream_t s);
 
 bool fused_bwd_supported(const Geom &g);

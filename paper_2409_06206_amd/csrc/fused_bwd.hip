@@ -1153,7 +1153,7 @@ hipError_t run_bwd(const Geom &g, const bf16_t *x, const bf16_t *dy, const bf16_
     if constexpr (Cf::SPLIT) {
         if (wide_bwd_supported(g)) { // (16-byte aligned tensors: the entry points check)
             ReduceJob sums[2];
-            hipError_t e = launch_wide_bwd(g, x, dy, attn, pack_, dx, dw_qkv, db_qkv, dtable, accumulate, ws, sums, s);
+            hipError_t e = launch_wide_bwd(g, x, dy, attn, pack_, table, dx, dw_qkv, db_qkv, dtable, accumulate, ws, sums, s);
             if (e != hipSuccess) return e;
             // The projection's partial vectors take the place of d(q|k|v).  Where that is too small for them (few windows for
             // the compute units) the sums before have to run first: a launch more.  (One launch for the last three sums and

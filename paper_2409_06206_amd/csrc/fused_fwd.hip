@@ -33,7 +33,7 @@ template <class Cf> struct PackGrid {
     static constexpr int ENTRIES =
         (Cf::N_WQH + Cf::N_WP2 + Cf::N_BF + Cf::N_WQ + Cf::N_WPT + Cf::N_WQT + Cf::N_WQF + Cf::N_WPK) * 64 + 4 * Cf::C;
     static constexpr int WIDE_ENTRIES =
-        Cf::SPLIT ? (Cf::N_WQW + Cf::N_WPW + Cf::N_WQX + Cf::N_WQN) * 64 + Cf::HEADS * Cf::TBW_PITCH : 0;
+        Cf::SPLIT ? (Cf::N_WQW + Cf::N_WPW + Cf::N_WQX + Cf::N_WQN + Cf::N_WQY) * 64 + Cf::HEADS * Cf::TBW_PITCH : 0;
     static constexpr int WIDE_FIRST = (ENTRIES + 255) / 256; // first block of the wide one-launch kernels' layouts
     static constexpr int BLOCKS = WIDE_FIRST + (WIDE_ENTRIES + 255) / 256;
 };
