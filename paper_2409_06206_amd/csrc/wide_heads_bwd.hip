@@ -183,6 +183,7 @@ __global__ __launch_bounds__(WideHeadsCfg<Cf>::THREADS, 1) void wide_heads_bwd_k
         __syncthreads();
         __syncthreads();
         for (int m = 0; m < cnt; ++m) {
+            __builtin_amdgcn_s_sleep(24); // (1.5 k clocks: the heads' own loads of this window go first)
             if (m + 1 < cnt) load_rows(m + 1);
             __syncthreads();
             if (m + 1 < cnt) stage(m + 1);
