@@ -335,78 +335,113 @@ __global__ __launch_bounds__(WideHeadsCfg<Cf>::THREADS, 1) void wide_heads_bwd_k
             for (int et = 0; et < 2; ++et)
 #pragma unroll
                 for (int kt = 0; kt < 4; ++kt) dk[et][kt] = dv[et][kt] = zero;
+            // two tiles of queries at a time, every stage for both: two chains that fill each other's waits
 #pragma unroll
-            for (int qt = 0; qt < 4; ++qt) {
-                turn[8 * 64 + lane] = Qb[0][qt];
-                turn[9 * 64 + lane] = Qb[1][qt];
-                turn[10 * 64 + lane] = dOb[0][qt];
-                turn[11 * 64 + lane] = dOb[1][qt];
-                f32x4 st[4], dp[4];
-                const uint4 qop = cat(Qb[0][qt], Qb[1][qt]), oop = cat(dOb[0][qt], dOb[1][qt]);
+            for (int p2 = 0; p2 < 2; ++p2) {
+                uint4 qn[2], on[2];
 #pragma unroll
-                for (int kt = 0; kt < 4; ++kt) {
-                    st[kt] = mma32(cat(Kb[0][kt], Kb[1][kt]), qop, bias_t[kt - qt + 3]);
-                    dp[kt] = mma32(cat(Vb[0][kt], Vb[1][kt]), oop, zero);
-                }
-                if (MASK) {
-                    const bool qr = 2 * qt + (l16 >> 3) >= M - s, qc = (l16 & 7) >= M - s;
+                for (int i = 0; i < 4; ++i) turn[(8 + i) * 64 + lane] = Qb[i / 2][2 * p2 + i % 2];
+#pragma unroll
+                for (int et = 0; et < 2; ++et) qn[et] = cat(lds_read_tr(turn + (8 + 2 * et) * 64 + tr), lds_read_tr(turn + (9 + 2 * et) * 64 + tr));
+#pragma unroll
+                for (int i = 0; i < 4; ++i) turn[(8 + i) * 64 + lane] = dOb[i / 2][2 * p2 + i % 2];
+#pragma unroll
+                for (int et = 0; et < 2; ++et) on[et] = cat(lds_read_tr(turn + (8 + 2 * et) * 64 + tr), lds_read_tr(turn + (9 + 2 * et) * 64 + tr));
+                f32x4 st[2][4], dp[2][4];
+#pragma unroll
+                for (int ni = 0; ni < 2; ++ni) {
+                    const int qt = 2 * p2 + ni;
+                    const uint4 qop = cat(Qb[0][qt], Qb[1][qt]), oop = cat(dOb[0][qt], dOb[1][qt]);
 #pragma unroll
                     for (int kt = 0; kt < 4; ++kt) {
-                        const bool row = (flags & 1) && qr != (2 * kt + (q >> 1) >= M - s);
-#pragma unroll
-                        for (int j = 0; j < 4; ++j)
-                            st[kt][j] += row || ((flags & 2) && qc != (4 * (q & 1) + j >= M - s)) ? kMask : 0.f;
+                        st[ni][kt] = mma32(cat(Kb[0][kt], Kb[1][kt]), qop, bias_t[kt - qt + 3]);
+                        dp[ni][kt] = mma32(cat(Vb[0][kt], Vb[1][kt]), oop, zero);
                     }
                 }
-                float mx = max4f(st[0]);
+                if (MASK) {
 #pragma unroll
-                for (int kt = 1; kt < 4; ++kt) mx = max5f(mx, st[kt]);
-                const float mxl = qgroup_max(mx) * kLog2e;
-                f32x4 sum4, del4;
+                    for (int ni = 0; ni < 2; ++ni) {
+                        const bool qr = 2 * (2 * p2 + ni) + (l16 >> 3) >= M - s, qc = (l16 & 7) >= M - s;
 #pragma unroll
-                for (int kt = 0; kt < 4; ++kt) {
+                        for (int kt = 0; kt < 4; ++kt) {
+                            const bool row = (flags & 1) && qr != (2 * kt + (q >> 1) >= M - s);
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) st[kt][j] = __builtin_amdgcn_exp2f(fmaf(st[kt][j], kLog2e, -mxl));
-                    sum4 = kt == 0 ? st[0] : sum4 + st[kt];
-                    if (kt == 0) del4 = st[0] * dp[0];
-                    else
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) del4[j] = fmaf(st[kt][j], dp[kt][j], del4[j]);
+                            for (int j = 0; j < 4; ++j)
+                                st[ni][kt][j] += row || ((flags & 2) && qc != (4 * (q & 1) + j >= M - s)) ? kMask : 0.f;
+                        }
+                    }
                 }
-                const float inv = recip(qgroup_sum((sum4[0] + sum4[1]) + (sum4[2] + sum4[3])));
-                const float delta = inv * qgroup_sum((del4[0] + del4[1]) + (del4[2] + del4[3]));
-                uint2 dSb[4];
+                float mxl[2], inv[2], delta[2];
 #pragma unroll
-                for (int kt = 0; kt < 4; ++kt) {
-                    st[kt] *= inv;
-                    turn[kt * 64 + lane] = pack_bf16x4(st[kt]);
+                for (int ni = 0; ni < 2; ++ni) {
+                    float mx = max4f(st[ni][0]);
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) dp[kt][j] = st[kt][j] * (dp[kt][j] - delta);
-                    dSb[kt] = pack_bf16x4(dp[kt]);
-                    turn[(4 + kt) * 64 + lane] = dSb[kt];
-                }
-                uint2 qn[2], on[2], pn[4], sn[4];
-#pragma unroll
-                for (int et = 0; et < 2; ++et) {
-                    qn[et] = lds_read_tr(turn + (8 + et) * 64 + tr);
-                    on[et] = lds_read_tr(turn + (10 + et) * 64 + tr);
+                    for (int kt = 1; kt < 4; ++kt) mx = max5f(mx, st[ni][kt]);
+                    mxl[ni] = mx;
                 }
 #pragma unroll
-                for (int kt = 0; kt < 4; ++kt) {
-                    pn[kt] = lds_read_tr(turn + kt * 64 + tr);
-                    sn[kt] = lds_read_tr(turn + (4 + kt) * 64 + tr);
+                for (int ni = 0; ni < 2; ++ni) mxl[ni] = qgroup_max(mxl[ni]) * kLog2e;
+#pragma unroll
+                for (int ni = 0; ni < 2; ++ni) {
+                    f32x4 sum4, del4;
+#pragma unroll
+                    for (int kt = 0; kt < 4; ++kt) {
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) st[ni][kt][j] = __builtin_amdgcn_exp2f(fmaf(st[ni][kt][j], kLog2e, -mxl[ni]));
+                        sum4 = kt == 0 ? st[ni][0] : sum4 + st[ni][kt];
+                        if (kt == 0) del4 = st[ni][0] * dp[ni][0];
+                        else
+#pragma unroll
+                            for (int j = 0; j < 4; ++j) del4[j] = fmaf(st[ni][kt][j], dp[ni][kt][j], del4[j]);
+                    }
+                    inv[ni] = (sum4[0] + sum4[1]) + (sum4[2] + sum4[3]);
+                    delta[ni] = (del4[0] + del4[1]) + (del4[2] + del4[3]);
                 }
 #pragma unroll
-                for (int kt = 0; kt < 4; ++kt) tblacc[kt - qt + 3] = mma16(ident, dSb[kt], tblacc[kt - qt + 3]);
+                for (int ni = 0; ni < 2; ++ni) inv[ni] = recip(qgroup_sum(inv[ni]));
 #pragma unroll
-                for (int et = 0; et < 2; ++et)
-                    put(0, et, qt, mma32(cat(KT[et][2], KT[et][3]), cat(dSb[2], dSb[3]), mma32(cat(KT[et][0], KT[et][1]), cat(dSb[0], dSb[1]), zero)));
+                for (int ni = 0; ni < 2; ++ni) delta[ni] = inv[ni] * qgroup_sum(delta[ni]);
+                uint2 dSb[2][4], pn[2][4];
+#pragma unroll
+                for (int ni = 0; ni < 2; ++ni)
+#pragma unroll
+                    for (int kt = 0; kt < 4; ++kt) {
+                        st[ni][kt] *= inv[ni];
+                        turn[(ni * 4 + kt) * 64 + lane] = pack_bf16x4(st[ni][kt]);
+                    }
+#pragma unroll
+                for (int ni = 0; ni < 2; ++ni)
+#pragma unroll
+                    for (int kt = 0; kt < 4; ++kt) {
+                        pn[ni][kt] = lds_read_tr(turn + (ni * 4 + kt) * 64 + tr);
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) dp[ni][kt][j] = st[ni][kt][j] * (dp[ni][kt][j] - delta[ni]);
+                        dSb[ni][kt] = pack_bf16x4(dp[ni][kt]);
+                    }
+#pragma unroll
+                for (int ni = 0; ni < 2; ++ni)
+#pragma unroll
+                    for (int kt = 0; kt < 4; ++kt) turn[(ni * 4 + kt) * 64 + lane] = dSb[ni][kt];
+#pragma unroll
+                for (int ni = 0; ni < 2; ++ni)
+#pragma unroll
+                    for (int kt = 0; kt < 4; ++kt) tblacc[kt - 2 * p2 - ni + 3] = mma16(ident, dSb[ni][kt], tblacc[kt - 2 * p2 - ni + 3]);
+                uint2 sn[2][4];
+#pragma unroll
+                for (int ni = 0; ni < 2; ++ni)
+#pragma unroll
+                    for (int kt = 0; kt < 4; ++kt) sn[ni][kt] = lds_read_tr(turn + (ni * 4 + kt) * 64 + tr);
+#pragma unroll
+                for (int ni = 0; ni < 2; ++ni)
+#pragma unroll
+                    for (int et = 0; et < 2; ++et)
+                        put(0, et, 2 * p2 + ni, mma32(cat(KT[et][2], KT[et][3]), cat(dSb[ni][2], dSb[ni][3]), mma32(cat(KT[et][0], KT[et][1]), cat(dSb[ni][0], dSb[ni][1]), zero)));
 #pragma unroll
                 for (int et = 0; et < 2; ++et)
 #pragma unroll
                     for (int kt = 0; kt < 4; ++kt) {
-                        dv[et][kt] = mma16(on[et], pn[kt], dv[et][kt]);
-                        dk[et][kt] = mma16(qn[et], sn[kt], dk[et][kt]);
+                        dv[et][kt] = mma32(on[et], cat(pn[0][kt], pn[1][kt]), dv[et][kt]);
+                        dk[et][kt] = mma32(qn[et], cat(sn[0][kt], sn[1][kt]), dk[et][kt]);
                     }
             }
         };
