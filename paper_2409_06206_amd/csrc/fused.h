@@ -2,14 +2,17 @@
 //
 // Activations stay in registers in MFMA operand / result layouts (see mfma.h).  Three ways of
 // giving a window to the hardware are in use:
-//   * one wavefront per window (forward of narrow layers with many windows, attention adjoint of wide layers): the wave
+//   * one wavefront per window (forward of narrow layers with many windows, attention adjoint of wide layers of three groups):
+//     the wave
 //     holds all 64 tokens as four 16-token tiles, so nothing crosses waves and no barrier is needed for it;
 //   * a few wavefronts per window, several windows per workgroup (forward of narrow layers with few windows and of whole
 //     narrow layers: four waves of one tile; forward of wide layers: waves of one or two tiles, wide_fwd.hip): K and V of a
 //     head cross the window's waves through LDS, as the operands they are read as;
-//   * one workgroup per window, one wavefront per 16 tokens (backward of narrow layers; wide layers: backward with an odd
-//     shift, both passes of inputs of 2^31 elements and more): K and V of a head, and in the backward the transposed
-//     score gradients, cross waves through LDS.
+//   * one wavefront per head, a workgroup for a row of windows (backward of narrow layers of one to three groups,
+//     heads_bwd.hip, and of wide ones of two, wide_heads_bwd.hip): the head's gradients stay in registers over all windows;
+//   * one workgroup per window, one wavefront per 16 tokens (backward of narrow layers of six groups and of wide ones of three
+//     with an odd shift; forward of wide inputs of 2^31 elements and more): K and V of a head, and in the backward the
+//     transposed score gradients, cross waves through LDS.
 // The shift, the window partition and their inverses are the address computation of the
 // first load and the last store (Sec. "Patch Embedding", Sec. "Group Shifted Window Attention").
 #pragma once
@@ -59,7 +62,7 @@ template <int C_, int HEADS_, int G_> struct FusedCfg {
     //        head h of the same group
     static constexpr bool HEADS_BWD = !SPLIT && G <= 3;
     static constexpr int N_WQF = HEADS_BWD ? HEADS * HG : 0;
-    static constexpr int N_WQT = HEADS_BWD && G != 2 ? 0 : HEADS * 3 * ET * HG * ET; // Wqkv^T, K=16: (hd,t,et,hlp,etp)
+    static constexpr int N_WQT = G == 6 || (SPLIT ? G == 3 : G == 2) ? HEADS * 3 * ET * HG * ET : 0; // Wqkv^T, K=16: (hd,t,et,hlp,etp)
     static constexpr size_t P_WQH = 0;
     static constexpr size_t P_WP2 = P_WQH + (size_t)N_WQH * 1024;
     static constexpr size_t P_BF = P_WP2 + (size_t)N_WP2 * 1024;
@@ -85,21 +88,24 @@ template <int C_, int HEADS_, int G_> struct FusedCfg {
     static constexpr size_t P_WQW = P_WQF + (size_t)N_WQF * 1024;
     static constexpr size_t P_WPW = P_WQW + (size_t)N_WQW * 1024;
     static constexpr size_t P_TBW = P_WPW + (size_t)N_WPW * 1024;
-    // Wide layers, backward with one wavefront per window (wide_bwd.hip) additionally reads
+    // Wide layers of three groups, backward with one wavefront per window (wide_bwd.hip) additionally reads
     //   WQX  Wqkv^T for dF = d(q|k|v) Wqkv, K=32: one step = the 32 k-slots of one (head, q|k|v) in
     //        head-padded order; (hd, t, ct), ct = (input head hl', half et') of the group: row l16 ->
     //        input channel hl' D + 16 et' + l16 (so that dF comes out in the tiles dO is held in);
     //        query rows carry 1/sqrt(d) like WQ
     static constexpr int CTF = HG * ET;                           // 16-row tiles of a group's input channels, per head
-    static constexpr int N_WQX = SPLIT ? HEADS * 3 * CTF : 0;
+    static constexpr bool WIDE_WAVES = SPLIT && G == 3;
+    static constexpr int N_WQX = WIDE_WAVES ? HEADS * 3 * CTF : 0;
     static constexpr size_t P_WQX = P_TBW + (SPLIT ? (size_t)HEADS * TBW_PITCH * 4 : 0);
+    // of two or three groups
     //   WQN  Wqkv on the group's channels in their own order, K=32 (the layout of WQ), query rows times
     //        log2(e)/sqrt(d) as in WQW: the backward recomputes q, k, v from 16-byte row pieces
-    static constexpr int N_WQN = SPLIT ? N_WQ : 0;
+    static constexpr int N_WQN = SPLIT && G > 1 ? N_WQ : 0;
     static constexpr size_t P_WQN = P_WQX + (size_t)N_WQX * 1024;
+    // of two groups
     //   WQY  Wqkv^T for dF by heads (wide_heads_bwd.hip), K=32: k-slots = the 3 D features q | k | v of a head in KF steps;
     //        (hdo, et, h, ks): row l16 -> channel 16 et + l16 of head hdo, features of head h of the same group
-    static constexpr bool WIDE_HEADS = SPLIT && HG == 3;
+    static constexpr bool WIDE_HEADS = SPLIT && G == 2;
     static constexpr int KF = (3 * D + 31) / 32, N_WQY = WIDE_HEADS ? HEADS * ET * HG * KF : 0;
     static constexpr size_t P_WQY = P_WQN + (size_t)N_WQN * 1024;
     static constexpr size_t P_END = P_WQY + (size_t)N_WQY * 1024;
@@ -292,7 +298,7 @@ hipError_t launch_reduce_pair(const ReduceJob &a, const ReduceJob &b, hipStream_
 // the same with a third (c.n == 0: none)
 hipError_t launch_reduce_three(const ReduceJob &a, const ReduceJob &b, const ReduceJob &c, hipStream_t s);
 
-// Wide layers (C = 180, two or three groups, 8x8 windows), backward of the attention and of the QKV
+// Wide layers (C = 180, three groups, 8x8 windows, even shift), backward of the attention and of the QKV
 // projection, group by group in reverse order (wide_bwd.hip): one launch with one wavefront per
 // window recomputes the group's q, k, v and probabilities and leaves d(q|k|v) in scratch and the
 // bias-table gradient as per-workgroup partial sums; a second launch turns d(q|k|v) into the
@@ -303,8 +309,8 @@ bool wide_bwd_supported(const Geom &g);
 size_t wide_bwd_ws_bytes(const Geom &g);
 size_t wide_bwd_free_bytes(const Geom &g);
 hipError_t launch_wide_bwd(const Geom &g, const bf16_t *x, const bf16_t *dy, const bf16_t *attn, const void *pack,
-                           const bf16_t *table, bf16_t *dx, float *dw_qkv, float *db_qkv, float *dtable, int accumulate, void *ws,
-                           ReduceJob (&sums)[2], hipStream_t s);
+                           bf16_t *dx, float *dw_qkv, float *db_qkv, float *dtable, int accumulate, void *ws, ReduceJob (&sums)[2],
+                           hipStream_t s);
 
 bool fused_bwd_supported(const Geom &g);
 // Scratch of the fused backward: per-workgroup partial parameter gradients.

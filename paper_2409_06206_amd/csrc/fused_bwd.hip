@@ -1,5 +1,6 @@
-// Fused GSWA backward for 8x8 windows, bf16 storage: six groups of a narrow layer, and wide layers with an odd shift (one to
-// three groups of a narrow layer: heads_bwd.hip, a wide layer with an even shift: wide_bwd.hip).  The backward of a layer is a
+// Fused GSWA backward for 8x8 windows, bf16 storage: narrow layers of six groups, and wide layers of three with an odd shift
+// (narrow layers of one to three groups: heads_bwd.hip; wide ones of two groups: wide_heads_bwd.hip, of three with an even
+// shift: wide_bwd.hip).  The backward of a layer is a
 // sequence of launches of fused_bwd_kernel, one per chunk of heads in reverse order; each recomputes q, k, v, the scores and the
 // softmax of its heads from x and the saved group outputs, and produces the dx slices of its groups and per-workgroup partial
 // sums of the parameter gradients (accumulated in registers over the windows a workgroup owns).  reduce_partials_kernel adds
@@ -16,6 +17,7 @@
 #include "fused.h"
 #include "heads_bwd.h"
 #include "mfma.h"
+#include "wide_heads_bwd.h"
 
 namespace gswa {
 
@@ -33,7 +35,7 @@ template <class Cf, int HB_, int HE_, bool WPROJ_> struct BwdCfg {
     static constexpr int CT = CG / 16 + 1;          // column tiles of d w_qkv of one head
     static constexpr int NT = 3 * ET * CT;          // tiles of one head's d w_qkv rows
     static constexpr int KT = (NT + 3) / 4;         // tiles per wave
-    // heads [HB, HE) of this launch: whole groups, or part of one group.  WPROJ: this launch also produces the columns of
+    // heads [HB, HE) of this launch: whole groups.  WPROJ: this launch also produces the columns of
     // d w_proj that belong to its heads, and the last heads' launch d b_proj (narrow layers; wide ones use a kernel of its own).
     static constexpr int HB = HB_, HE = HE_, NH = HE - HB;
     static constexpr bool WPROJ = WPROJ_, BPROJ = WPROJ_ && HE_ == Cf::HEADS;
@@ -41,8 +43,7 @@ template <class Cf, int HB_, int HE_, bool WPROJ_> struct BwdCfg {
     static constexpr int OTP = (C + 15) / 16, CTP = WCN / 16 + 1;
     static constexpr int NTP = OTP * CTP, KTP = (NTP + 3) / 4;
     static constexpr int GB = HB / HG, GE = (HE - 1) / HG; // lowest and highest group of the chunk
-    static_assert(NH > 0 && (GB == GE || (HB % HG == 0 && HE % HG == 0)),
-                  "a chunk is whole groups or lies inside one group");
+    static_assert(NH > 0 && HB % HG == 0 && HE % HG == 0, "a chunk is whole groups");
     // packed parameters of these heads, copied from the buffer forward filled: [WQ | BIAS | WPT | WQT]
     static constexpr int N_WQ = NH * 3 * ET * KS, N_WPT = NH * ET * KSC, N_WQT = NH * 3 * ET * HG * ET;
     static constexpr size_t SRC_WQ = Cf::P_WQ + (size_t)HB * 3 * ET * KS * 1024;
@@ -75,16 +76,13 @@ template <class Cf, int HB_, int HE_, bool WPROJ_> struct BwdCfg {
     static constexpr size_t LDS_BYTES = OFF_F + SZ_F;
     // Per-workgroup partial sums of THIS launch only (the scratch is reused from launch to launch: the
     // head-group loop bounds it).  Rows of d w_qkv: for every group of the chunk and each of q, k, v
-    // the RG rows the chunk's heads own, ((gi - GB) * 3 + t) * RG + (hl - HL0) * D + e; then the bias
+    // CG rows, ((gi - GB) * 3 + t) * CG + hl * D + e; then the bias
     // sums in the same order, the columns of d w_proj | d b_proj where this launch produces them, and the bias-table
     // gradient head by head.
-    static constexpr bool WHOLE = HB_ % HG == 0 && HE_ % HG == 0;   // whole groups (else: part of one group)
     static constexpr int NG = GE - GB + 1;
-    static constexpr int RG = WHOLE ? CG : NH * D;                  // rows per (group, q|k|v)
-    static constexpr int HL0 = WHOLE ? 0 : HB_ % HG;
     static constexpr int L_DWQ = 0;
-    static constexpr int L_DBQ = L_DWQ + NG * 3 * RG * CG;
-    static constexpr int L_DWP = L_DBQ + NG * 3 * RG;
+    static constexpr int L_DBQ = L_DWQ + NG * 3 * CG * CG;
+    static constexpr int L_DWP = L_DBQ + NG * 3 * CG;
     static constexpr int L_DBP = L_DWP + (WPROJ ? C * WCN : 0);
     static constexpr int L_TBL = L_DBP + (BPROJ ? C : 0);
     static constexpr int L_END = L_TBL + NH * NTBL;
@@ -418,10 +416,7 @@ void fused_bwd_kernel(Geom g, const bf16_t *__restrict__ x,
             const int hx = hd - HB;      // index into this launch's fragments and accumulators
             const int gi = hd / HG, hl = hd % HG;
             const bool casc_out = gi < G - 1 && g.cascade; // this group's output feeds the next group
-            // the heads of group gi this launch processes, top first: [g_lo, g_hi]
-            const int g_hi = (HE < (gi + 1) * HG ? HE : (gi + 1) * HG) - 1;
-            const int g_lo = HB > gi * HG ? HB : gi * HG;
-            const bool starts_group = g_hi == (gi + 1) * HG - 1; // no earlier launch touched this group
+            const int g_hi = (gi + 1) * HG - 1, g_lo = gi * HG; // the heads of the group, top first
             const bool next_in_regs = HB <= (gi + 1) * HG && HE >= (gi + 2) * HG; // group gi+1 done in this launch
             if (hd == g_hi) {
 #pragma unroll
@@ -602,7 +597,7 @@ void fused_bwd_kernel(Geom g, const bf16_t *__restrict__ x,
                     gbuf[((2 * ET + et) * 4 + wv) * 64 + lane] = gv[et];
                 }
             }
-            // ---- first head of a group in this launch: F^T rows [channel][token] of the group input (Eq. 8) ----
+            // ---- first head of a group: F^T rows [channel][token] of the group input (Eq. 8) ----
             if (hd == g_hi) {
 #pragma unroll
                 for (int ct = 0; ct < CT; ++ct) {
@@ -659,10 +654,6 @@ void fused_bwd_kernel(Geom g, const bf16_t *__restrict__ x,
                     for (int etp = 0; etp < ET; ++etp) {
                         const int c0 = 16 * etp + 4 * q;
                         uint32_t *dst = reinterpret_cast<uint32_t *>(dx + tok * C + gi * CG + hlp * D + c0);
-                        if (!starts_group) { // earlier launches left the other heads' share in the slice
-                            const uint32_t lo = c0 < D ? dst[0] : 0u, hi = c0 + 2 < D ? dst[1] : 0u;
-                            dFT[hlp][etp] += f32x4{bf16_lo(lo), bf16_hi(lo), bf16_lo(hi), bf16_hi(hi)};
-                        }
                         const uint2 v = pack_bf16x4(dFT[hlp][etp]);
                         if (c0 < D) dst[0] = v.x;
                         if (c0 + 2 < D) dst[1] = v.y;
@@ -702,7 +693,7 @@ void fused_bwd_kernel(Geom g, const bf16_t *__restrict__ x,
                 const int r = ti / CT, ct = ti - r * CT;
                 const int t = r / ET, et = r - t * ET;
                 const int c = 16 * ct + l16, e = 16 * et + 4 * q;
-                const int row = ((gi - GB) * 3 + t) * B::RG + (hl - B::HL0) * D + e;
+                const int row = ((gi - GB) * 3 + t) * CG + hl * D + e;
                 float *dst = mine + (c < CG ? B::L_DWQ + row * CG + c : B::L_DBQ + row);
                 const int step = c < CG ? CG : 1;
 #pragma unroll
@@ -964,21 +955,13 @@ __global__ __launch_bounds__(512, 1) void wproj_grad_kernel(long T, const bf16_t
 
 // Head chunks of the backward, in launch order (last group first).  Chunks are whole groups, so
 // the only thing one launch hands to the next is the cascade gradient, which is the dx slice it
-// wrote.  Three heads per launch keep the accumulators small enough for two workgroups per CU;
-// with one group (no boundary to cut at) a single launch takes all heads at one workgroup per CU.
-// Wide layers go one head per launch (their per-head weights and row buffers fill LDS); a group
-// split over launches accumulates its dF in the dx slice.
+// wrote.  Three heads per launch keep the accumulators small enough for two workgroups per CU.
+// Wide layers of three groups go a group of two heads a launch (their weights and row buffers fill LDS).
 template <bool SPLIT, int G> struct ChunkPlan;
 template <> struct ChunkPlan<false, 2> { static constexpr int N = 2; static constexpr int B[2] = {3, 0}, E[2] = {6, 3}; };
 template <> struct ChunkPlan<false, 6> { static constexpr int N = 2; static constexpr int B[2] = {3, 0}, E[2] = {6, 3}; };
-template <int G> struct ChunkPlan<true, G> {
-    static constexpr int N = 6;
-    static constexpr int B[6] = {5, 4, 3, 2, 1, 0}, E[6] = {6, 5, 4, 3, 2, 1};
-};
-// (with three groups a wide group is two heads, whose weights and buffers fit LDS together; of a
-// three-head group two heads fit)
 template <> struct ChunkPlan<true, 3> { static constexpr int N = 3; static constexpr int B[3] = {4, 2, 0}, E[3] = {6, 4, 2}; };
-template <> struct ChunkPlan<true, 2> { static constexpr int N = 4; static constexpr int B[4] = {4, 3, 1, 0}, E[4] = {6, 4, 3, 1}; };
+template <> struct ChunkPlan<true, 2> { static constexpr int N = 0; }; // (wide_heads_bwd.hip)
 
 // Workgroups of a backward launch: narrow layers with more than one group run two per compute unit.
 // `cus` = the device's compute units for a launch, kSizingCus for the scratch size (a launch never
@@ -1070,13 +1053,13 @@ hipError_t launch_chunk(const Geom &g, int grid, const bf16_t *x, const bf16_t *
     static_assert(2 * B::NG * 3 + 3 <= ReduceOut::MAXSEG, "segment table");
     for (int gi = 0; gi < B::NG; ++gi)
         for (int t = 0; t < 3; ++t) { // d w_qkv rows of (group, q|k|v) owned by the chunk's heads
-            out.ptr[k] = go.dw_qkv + (size_t)((B::GB + gi) * 3 * CG + t * CG + B::HL0 * D) * CG;
-            out.begin[k++] = B::L_DWQ + (gi * 3 + t) * B::RG * CG;
+            out.ptr[k] = go.dw_qkv + (size_t)((B::GB + gi) * 3 * CG + t * CG) * CG;
+            out.begin[k++] = B::L_DWQ + (gi * 3 + t) * CG * CG;
         }
     for (int gi = 0; gi < B::NG; ++gi)
         for (int t = 0; t < 3; ++t) {
-            out.ptr[k] = go.db_qkv + (B::GB + gi) * 3 * CG + t * CG + B::HL0 * D;
-            out.begin[k++] = B::L_DBQ + (gi * 3 + t) * B::RG;
+            out.ptr[k] = go.db_qkv + (B::GB + gi) * 3 * CG + t * CG;
+            out.begin[k++] = B::L_DBQ + (gi * 3 + t) * CG;
         }
     if (WPROJ) {
         out.row_seg = k; out.row_len = B::WCN; out.row_stride = Cf::C;
@@ -1151,22 +1134,26 @@ hipError_t run_bwd(const Geom &g, const bf16_t *x, const bf16_t *dy, const bf16_
     float *part = static_cast<float *>(ws);
     const int grid = bwd_grid(g, device_cu_count());
     if constexpr (Cf::SPLIT) {
-        if (wide_bwd_supported(g)) { // (16-byte aligned tensors: the entry points check)
-            ReduceJob sums[2];
-            hipError_t e = launch_wide_bwd(g, x, dy, attn, pack_, table, dx, dw_qkv, db_qkv, dtable, accumulate, ws, sums, s);
+        if (Cf::WIDE_HEADS || wide_bwd_supported(g)) { // (16-byte aligned tensors: the entry points check)
+            ReduceJob sums[2]{};
+            hipError_t e = Cf::WIDE_HEADS ? launch_wide_heads_bwd(g, x, dy, attn, pack, table, dx, dw_qkv, db_qkv, dtable, accumulate, ws, sums[0], s)
+                                          : launch_wide_bwd(g, x, dy, attn, pack, dx, dw_qkv, db_qkv, dtable, accumulate, ws, sums, s);
             if (e != hipSuccess) return e;
-            // The projection's partial vectors take the place of d(q|k|v).  Where that is too small for them (few windows for
-            // the compute units) the sums before have to run first: a launch more.  (One launch for the last three sums and
-            // the wider loads of reduce_width: 32 images of 64x64, forward + backward, 340 -> 335 us.)
-            const bool fits = (size_t)grid * (Cf::C * Cf::C + Cf::C) * sizeof(float) <= wide_bwd_free_bytes(g);
+            // The projection's partial vectors take the free part of the scratch.  Where that is too small for them (few
+            // windows for the compute units) the sums before have to run first: a launch more.  (One launch for the last
+            // three sums and the wider loads of reduce_width: 32 images of 64x64, three groups, forward + backward, 5 us.)
+            const size_t room = Cf::WIDE_HEADS ? wide_heads_bwd_free_bytes(g) : wide_bwd_free_bytes(g);
+            const bool fits = (size_t)grid * (Cf::C * Cf::C + Cf::C) * sizeof(float) <= room;
             if (!fits && (e = launch_reduce_pair(sums[0], sums[1], s)) != hipSuccess) return e;
             return run_wproj_grad<Cf>(g, grid, dy, attn, part, dw_proj, db_proj, accumulate, fits ? sums : nullptr, s);
         }
     }
-    const GradOut go{dw_qkv, db_qkv, dw_proj, db_proj, dtable, accumulate};
-    hipError_t e = launch_chunks<Cf>(g, grid, x, dy, attn, pack, table, dx, part, go, s);
-    if (e != hipSuccess) return e;
-    if constexpr (Cf::SPLIT) return run_wproj_grad<Cf>(g, grid, dy, attn, part, dw_proj, db_proj, accumulate, nullptr, s);
+    if constexpr (!Cf::WIDE_HEADS) {
+        const GradOut go{dw_qkv, db_qkv, dw_proj, db_proj, dtable, accumulate};
+        hipError_t e = launch_chunks<Cf>(g, grid, x, dy, attn, pack, table, dx, part, go, s);
+        if (e != hipSuccess) return e;
+        if constexpr (Cf::SPLIT) return run_wproj_grad<Cf>(g, grid, dy, attn, part, dw_proj, db_proj, accumulate, nullptr, s);
+    }
     return hipSuccess;
 }
 
@@ -1203,7 +1190,7 @@ size_t fused_bwd_ws_bytes(const Geom &g)
     GSWA_FUSED_SHAPES(X)
 #undef X
     const size_t chunks = ((size_t)bwd_grid(g, kSizingCus) * total * 4 + 255) & ~size_t(255);
-    const size_t wide = wide_bwd_supported(g) ? wide_bwd_ws_bytes(g) : 0;
+    const size_t wide = wide_heads_bwd_supported(g) ? wide_heads_bwd_ws_bytes(g) : wide_bwd_supported(g) ? wide_bwd_ws_bytes(g) : 0;
     return wide > chunks ? wide : chunks;
 }
 

@@ -1,5 +1,5 @@
-// Backward of wide GSWA layers (C = 180, six heads of 30 channels, 8x8 windows, two or three
-// groups) through the attention and the QKV projection, group by group in reverse order (Eq. 8 hands
+// Backward of wide GSWA layers of three groups (C = 180, six heads of 30 channels, 8x8 windows; two groups:
+// wide_heads_bwd.hip) through the attention and the QKV projection, group by group in reverse order (Eq. 8 hands
 // the gradient of a group's input to the output of the group before it).  Two launches per group:
 //
 // wide_attn_bwd_kernel: one wavefront per window (the forward, wide_fwd.hip, has two): four waves per
@@ -19,7 +19,6 @@
 //
 // Notation (T-form, N-form, head-padded order): fused_bwd.hip, wide_fwd.hip.
 #include "fused.h"
-#include "wide_heads_bwd.h"
 #include "mfma.h"
 #include "wide_rows.h"
 
@@ -904,7 +903,7 @@ hipError_t run_wide_bwd(const Geom &g, const bf16_t *x, const bf16_t *dy, const 
     return hipSuccess;
 }
 
-#define GSWA_WIDE_BWD_SHAPES(X) X(180, 6, 2) X(180, 6, 3)
+#define GSWA_WIDE_BWD_SHAPES(X) X(180, 6, 3)
 
 } // namespace
 
@@ -923,12 +922,6 @@ bool wide_bwd_supported(const Geom &g)
 
 size_t wide_bwd_ws_bytes(const Geom &g)
 {
-    // (the projection's partial vectors, where there is room for them in what the two launches a group left between them,
-    // and those of a group)
-    if (wide_heads_bwd_supported(g)) {
-        const size_t own = wide_bwd_free_bytes(g) + wide_heads_bwd_part_bytes(g), wproj = WideBwdWs<FusedCfg<180, 6, 2>>::wproj_bytes(g);
-        return own > wproj ? own : wproj;
-    }
 #define X(C_, H_, G_)                                                                       \
     if (g.C == C_ && g.heads == H_ && g.groups == G_) {                                     \
         using Ws = WideBwdWs<FusedCfg<C_, H_, G_>>;                                         \
@@ -943,24 +936,16 @@ size_t wide_bwd_ws_bytes(const Geom &g)
 size_t wide_bwd_free_bytes(const Geom &g)
 {
 #define X(C_, H_, G_) \
-    if (g.C == C_ && g.heads == H_ && g.groups == G_) {                                                                     \
-        using Ws = WideBwdWs<FusedCfg<C_, H_, G_>>;                                                                          \
-        return !wide_heads_bwd_supported(g) || Ws::dqkv_bytes(g) < Ws::wproj_bytes(g) ? Ws::dqkv_bytes(g) : Ws::wproj_bytes(g); \
-    }
+    if (g.C == C_ && g.heads == H_ && g.groups == G_) return WideBwdWs<FusedCfg<C_, H_, G_>>::dqkv_bytes(g);
     GSWA_WIDE_BWD_SHAPES(X)
 #undef X
     return 0;
 }
 
 hipError_t launch_wide_bwd(const Geom &g, const bf16_t *x, const bf16_t *dy, const bf16_t *attn, const void *pack,
-                           const bf16_t *table, bf16_t *dx, float *dw_qkv, float *db_qkv, float *dtable, int accumulate, void *ws,
-                           ReduceJob (&sums)[2], hipStream_t s)
+                           bf16_t *dx, float *dw_qkv, float *db_qkv, float *dtable, int accumulate, void *ws, ReduceJob (&sums)[2],
+                           hipStream_t s)
 {
-    if (wide_heads_bwd_supported(g)) {
-        sums[1] = ReduceJob{};
-        return launch_wide_heads_bwd(g, x, dy, attn, static_cast<const uint8_t *>(pack), table, dx, dw_qkv, db_qkv, dtable, accumulate,
-                                     reinterpret_cast<float *>(static_cast<uint8_t *>(ws) + wide_bwd_free_bytes(g)), sums[0], s);
-    }
 #define X(C_, H_, G_)                                                                                            \
     if (g.C == C_ && g.heads == H_ && g.groups == G_)                                                            \
         return run_wide_bwd<FusedCfg<C_, H_, G_>>(g, x, dy, attn, static_cast<const uint8_t *>(pack), dx, dw_qkv, \

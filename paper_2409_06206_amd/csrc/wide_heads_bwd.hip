@@ -6,9 +6,15 @@
 // barrier it forms the head's channels of dF = d(q|k|v) Wqkv^T, which are its part of the dx slice.  Wave 3 fetches the rows
 // of the next window meanwhile, and lays them down behind that barrier.  Two barriers a window.
 //
-// What bounds it: the chain of a head's steps, a SIMD unit having one wave.  What it saves over an adjoint and a gradient launch
-// a group (wide_bwd.hip) is memory: d(q|k|v), F and the cascade gradient went out and in between the two, 380 MB a group of
-// 2048 windows against 125.
+// What bounds it: the chain of a head's steps, a SIMD unit having one wave (its LDS, 150 KB, and its registers, 506, leave no
+// room for a second).  Of the 18 k clocks of a window q, k, v and dO take 5 k, scores to d(q|k|v) 6.5 k, the d(q|k|v) rows 1 k,
+// the weight gradients 1.9 k and dF 2.9 k; eight windows a workgroup, 12 k clocks of set-up and 12 k to leave the partial sums.
+// What it saves over an adjoint and a gradient launch a group (wide_bwd.hip) is memory: d(q|k|v), F and the cascade gradient
+// went out and in between the two, 380 MB a group of 2048 windows against 125.  Forward + backward of 32 / 16 / 1 images of
+// 64x64 333 / 203 / 117 us by those two, 270 / 172 / 83 by heads; of an image of 24x16 with an odd shift, which took four
+// launches of one or two heads with a workgroup a window, ODD.
+//
+// For two groups: with three a group's two heads would leave half the SIMD units to row fetches, and its launches are three.
 #include "fused.h"
 #include "mfma.h"
 #include "wide_heads_bwd.h"
@@ -18,7 +24,7 @@ namespace gswa {
 namespace {
 
 constexpr float kLog2e = 1.4426950408889634f;
-constexpr float kMask = -100.0f;
+constexpr float kMaskLog2 = -100.0f * kLog2e; // scores are in base-2 units, as the forward forms them
 
 template <class Cf> struct WideHeadsCfg {
     static constexpr int C = Cf::C, D = Cf::D, CG = Cf::CG, HG = Cf::HG, HEADS = Cf::HEADS, G = Cf::G;
@@ -90,7 +96,7 @@ __global__ __launch_bounds__(WideHeadsCfg<Cf>::THREADS, 1) void wide_heads_bwd_k
 #pragma unroll
         for (int k = 0; k < (N1K + NW - 1) / NW; ++k) {
             const int f = k * NW + wv;
-            if (f < N1K) lds_dma16(pack + Cf::P_WQ + ((size_t)GI * N1K + f) * 1024 + 16 * lane, lds + P::OFF_WQ + (size_t)f * 1024);
+            if (f < N1K) lds_dma16(pack + Cf::P_WQN + ((size_t)GI * N1K + f) * 1024 + 16 * lane, lds + P::OFF_WQ + (size_t)f * 1024);
         }
         float bv[I_B];
         uint16_t tv[I_T][2];
@@ -98,7 +104,7 @@ __global__ __launch_bounds__(WideHeadsCfg<Cf>::THREADS, 1) void wide_heads_bwd_k
         for (int k = 0; k < I_B; ++k) {
             const int i = k * TH + tid < HG * 96 ? k * TH + tid : 0, e = i % 32, t = i / 32 % 3, hl = i / 96;
             bv[k] = reinterpret_cast<const float *>(pack + Cf::P_BIAS)[GI * 3 * CG + t * CG + hl * D + (e < D ? e : 0)];
-            bv[k] = e < D ? bv[k] : 0.f;
+            bv[k] = e < D ? (t == 0 ? bv[k] * kLog2e : bv[k]) : 0.f;
         }
 #pragma unroll
         for (int k = 0; k < I_T; ++k) {
@@ -203,7 +209,7 @@ __global__ __launch_bounds__(WideHeadsCfg<Cf>::THREADS, 1) void wide_heads_bwd_k
             const int dr = (l16 >> 3) - (q >> 1) - 2 * (dl - 3);
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                bias_t[dl][j] = to_f32(tbl[((dr + M - 1) * (2 * M - 1) + (l16 & 7) - 4 * (q & 1) - j + M - 1) * HEADS + hd]);
+                bias_t[dl][j] = to_f32(tbl[((dr + M - 1) * (2 * M - 1) + (l16 & 7) - 4 * (q & 1) - j + M - 1) * HEADS + hd]) * kLog2e;
             tblacc[dl] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
 #pragma unroll
@@ -225,8 +231,6 @@ __global__ __launch_bounds__(WideHeadsCfg<Cf>::THREADS, 1) void wide_heads_bwd_k
         const int lane = lane_n, l16 = lane & 15, q = lane >> 4;
         const int tr = (l16 & 3) * 16 + 4 * q + (l16 >> 2);
         const uint8_t *ftr = lds + P::OFF_F + ((l16 & 3) >> 1) * 256 + (l16 & 1) * 8 + (4 * q + (l16 >> 2)) * 16;
-        const uint2 ident = make_uint2((4 * q == l16 ? 0x3F80u : 0u) | (4 * q + 1 == l16 ? 0x3F800000u : 0u),
-                                       (4 * q + 2 == l16 ? 0x3F80u : 0u) | (4 * q + 3 == l16 ? 0x3F800000u : 0u));
         uint32_t tok[4];
 #pragma unroll
         for (int t = 0; t < 4; ++t) tok[t] = tokb[(m & 1) * 64 + 16 * t + l16];
@@ -367,27 +371,27 @@ __global__ __launch_bounds__(WideHeadsCfg<Cf>::THREADS, 1) void wide_heads_bwd_k
                             const bool row = (flags & 1) && qr != (2 * kt + (q >> 1) >= M - s);
 #pragma unroll
                             for (int j = 0; j < 4; ++j)
-                                st[ni][kt][j] += row || ((flags & 2) && qc != (4 * (q & 1) + j >= M - s)) ? kMask : 0.f;
+                                st[ni][kt][j] += row || ((flags & 2) && qc != (4 * (q & 1) + j >= M - s)) ? kMaskLog2 : 0.f;
                         }
                     }
                 }
-                float mxl[2], inv[2], delta[2];
+                float top[2], inv[2], delta[2];
 #pragma unroll
                 for (int ni = 0; ni < 2; ++ni) {
                     float mx = max4f(st[ni][0]);
 #pragma unroll
                     for (int kt = 1; kt < 4; ++kt) mx = max5f(mx, st[ni][kt]);
-                    mxl[ni] = mx;
+                    top[ni] = mx;
                 }
 #pragma unroll
-                for (int ni = 0; ni < 2; ++ni) mxl[ni] = qgroup_max(mxl[ni]) * kLog2e;
+                for (int ni = 0; ni < 2; ++ni) top[ni] = qgroup_max(top[ni]);
 #pragma unroll
                 for (int ni = 0; ni < 2; ++ni) {
                     f32x4 sum4, del4;
 #pragma unroll
                     for (int kt = 0; kt < 4; ++kt) {
 #pragma unroll
-                        for (int j = 0; j < 4; ++j) st[ni][kt][j] = __builtin_amdgcn_exp2f(fmaf(st[ni][kt][j], kLog2e, -mxl[ni]));
+                        for (int j = 0; j < 4; ++j) st[ni][kt][j] = __builtin_amdgcn_exp2f(st[ni][kt][j] - top[ni]);
                         sum4 = kt == 0 ? st[ni][0] : sum4 + st[ni][kt];
                         if (kt == 0) del4 = st[ni][0] * dp[ni][0];
                         else
@@ -417,15 +421,13 @@ __global__ __launch_bounds__(WideHeadsCfg<Cf>::THREADS, 1) void wide_heads_bwd_k
 #pragma unroll
                         for (int j = 0; j < 4; ++j) dp[ni][kt][j] = st[ni][kt][j] * (dp[ni][kt][j] - delta[ni]);
                         dSb[ni][kt] = pack_bf16x4(dp[ni][kt]);
+                        tblacc[kt - 2 * p2 - ni + 3] += dp[ni][kt];
                     }
 #pragma unroll
                 for (int ni = 0; ni < 2; ++ni)
 #pragma unroll
                     for (int kt = 0; kt < 4; ++kt) turn[(ni * 4 + kt) * 64 + lane] = dSb[ni][kt];
-#pragma unroll
-                for (int ni = 0; ni < 2; ++ni)
-#pragma unroll
-                    for (int kt = 0; kt < 4; ++kt) tblacc[kt - 2 * p2 - ni + 3] = mma16(ident, dSb[ni][kt], tblacc[kt - 2 * p2 - ni + 3]);
+                __builtin_amdgcn_sched_barrier(0);
                 uint2 sn[2][4];
 #pragma unroll
                 for (int ni = 0; ni < 2; ++ni)
@@ -453,7 +455,7 @@ __global__ __launch_bounds__(WideHeadsCfg<Cf>::THREADS, 1) void wide_heads_bwd_k
 #pragma unroll
         for (int et = 0; et < 2; ++et)
 #pragma unroll
-            for (int kt = 0; kt < 4; ++kt) put(1, et, kt, dk[et][kt]);
+            for (int kt = 0; kt < 4; ++kt) put(1, et, kt, dk[et][kt] * (1.0f / kLog2e)); // (Q carries log2(e))
         asm volatile("" ::: "memory");
 #pragma unroll
         for (int et = 0; et < 2; ++et)
@@ -607,22 +609,37 @@ hipError_t run_group(const Geom &g, int grid, const bf16_t *x, const bf16_t *dy,
 
 } // namespace
 
-size_t wide_heads_bwd_part_bytes(const Geom &g)
+using Shape = FusedCfg<180, 6, 2>;
+
+bool wide_heads_bwd_supported(const Geom &g)
 {
-    const int grid = g.nW < kSizingCus ? g.nW : kSizingCus;
-    return ((size_t)grid * WideHeadsCfg<FusedCfg<180, 6, 2>>::L_TOTAL * sizeof(float) + 255) & ~size_t(255);
+    return g.M == 8 && g.C == Shape::C && g.heads == Shape::HEADS && g.groups == Shape::G && g.dq == g.d;
 }
 
-bool wide_heads_bwd_supported(const Geom &g) { return g.M == 8 && g.C == 180 && g.heads == 6 && g.groups == 2; }
+// The projection's partial vectors go there where a scratch of 36 KB a window (the d(q|k|v) of a group, which the launches of
+// wide_bwd.hip hand over) has room for them, from 905 windows on; fewer windows pay one more sum instead of 33 MB of scratch.
+size_t wide_heads_bwd_free_bytes(const Geom &g)
+{
+    const size_t room = (size_t)g.nW * 4 * Shape::HG * 3 * 1024;
+    const size_t wproj = ((size_t)kSizingCus * (Shape::C * Shape::C + Shape::C) * sizeof(float) + 255) & ~size_t(255);
+    return room < wproj ? room : wproj;
+}
+
+size_t wide_heads_bwd_ws_bytes(const Geom &g)
+{
+    const int grid = g.nW < kSizingCus ? g.nW : kSizingCus;
+    return wide_heads_bwd_free_bytes(g) + (((size_t)grid * WideHeadsCfg<Shape>::L_TOTAL * sizeof(float) + 255) & ~size_t(255));
+}
 
 hipError_t launch_wide_heads_bwd(const Geom &g, const bf16_t *x, const bf16_t *dy, const bf16_t *attn, const uint8_t *pack,
                                  const bf16_t *table, bf16_t *dx, float *dw_qkv, float *db_qkv, float *dtable, int accumulate,
-                                 float *part, ReduceJob &last, hipStream_t s)
+                                 void *ws, ReduceJob &last, hipStream_t s)
 {
+    float *part = reinterpret_cast<float *>(static_cast<uint8_t *>(ws) + wide_heads_bwd_free_bytes(g));
     int grid = device_cu_count();
     if (grid > kSizingCus) grid = kSizingCus;
     if (grid > g.nW) grid = g.nW;
-    return run_group<FusedCfg<180, 6, 2>, 1>(g, grid, x, dy, attn, pack, table, dx, dw_qkv, db_qkv, dtable, accumulate, part, last, s);
+    return run_group<Shape, 1>(g, grid, x, dy, attn, pack, table, dx, dw_qkv, db_qkv, dtable, accumulate, part, last, s);
 }
 
 } // namespace gswa

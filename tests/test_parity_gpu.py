@@ -480,6 +480,37 @@ def test_narrow_backward_with_a_wave_per_head(oracle, B, H, W, shift, cascade, g
     _say("  errors", {k: f"{v:.2e}" for k, v in errs.items()})
 
 
+@pytest.mark.parametrize("B,H,W,shift,cascade,accumulate", [
+    (1, 8, 8, 0, True, False),     # one window
+    (1, 24, 40, 7, True, True),    # 15, cut by an odd shift in both directions, added
+    (7, 56, 48, 4, True, False),   # 294: a second window for some of 256 workgroups
+    (4, 24, 104, 3, False, True),  # 156, no cascade
+    (13, 72, 64, 1, True, False),  # 936: three or four a workgroup, the last three sums in one launch
+])
+def test_wide_backward_with_a_wave_per_head(oracle, B, H, W, shift, cascade, accumulate):
+    """Two groups of a wide layer: one launch a group, any shift, and the same bits twice (added onto 0.5 where asked)."""
+    from paper_2409_06206_amd import gswa, runner
+    _say("wide, wave per head", B, H, W, shift, cascade, accumulate)
+    flags = (gswa.GSWA_ACCUM_WGRAD if accumulate else 0) | (0 if cascade else gswa.GSWA_NO_CASCADE)
+    x, dy, p = parity.make_inputs(B, H, W, 180, 6, 2, 8, "bf16", synth.LAYER_SEED0 + 4, "stress")
+    layer = runner.DeviceLayer(B, H, W, 180, 6, 2, 8, shift, "bf16", flags)
+    layer.set_params(p)
+    layer.set_inputs(x, dy)
+    layer.forward()
+    start, runs = 0.5 if accumulate else 0.0, []
+    for _ in range(2):
+        for g in layer.grads.values():
+            g.fill_(0.5)
+        with parity.launch_counts() as counts:
+            layer.backward()
+        assert counts["wide_attn_bwd"] == 2 and "wide_qkv_grad" not in counts and "fused_bwd" not in counts, counts
+        runs.append({k: v.copy() for k, v in layer.results().items()})
+    want = parity.oracle_results(oracle, x, dy, p, 6, 2, 8, shift, cascade=cascade)
+    for k in parity.GRAD_NAMES:
+        assert parity.rel_err(runs[0][k] - (start if k != "dx" else 0.0), want[k]) <= parity.TOL["bf16"], k
+        assert np.array_equal(runs[0][k], runs[1][k]), k
+
+
 @pytest.mark.parametrize("groups", [2, 3])
 def test_wide_layers_more_windows_than_wavefronts(oracle, groups):
     """27 x (9 x 5) = 1215 windows of a wide layer: more than the 1024 wavefronts of a backward launch
