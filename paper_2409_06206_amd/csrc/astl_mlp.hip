@@ -34,20 +34,6 @@ __device__ __forceinline__ float bf(const bf16_t *p, long i) { return __uint_as_
 // channel (or hidden feature) a lane's k-slot j of step s stands for
 __device__ __forceinline__ int slot_index(int s, int q, int j) { return 16 * (2 * s + (j >> 2)) + 4 * q + (j & 3); }
 
-// Fragments of a weight matrix as the A operand: tile `mt` of 16 output rows, k-step `s`;
-// get(m, k) returns the entry for output row m and reduction index k (zero outside the matrix).
-template <typename F>
-__device__ __forceinline__ void build_frags(uint4 *dst, int mtiles, int ksteps, F get)
-{
-    uint16_t *d16 = reinterpret_cast<uint16_t *>(dst);
-    const int total = mtiles * ksteps * 512;
-    for (int e = blockIdx.x * kMlpThreads + threadIdx.x; e < total; e += gridDim.x * kMlpThreads) {
-        const int j = e & 7, l = (e >> 3) & 63, fr = e >> 9;
-        const int s = fr % ksteps, mt = fr / ksteps;
-        d16[e] = f32_to_bf16_bits(get(16 * mt + (l & 15), slot_index(s, l >> 4, j)));
-    }
-}
-
 struct MlpArgs {
     long rows;
     int C, Hd;
@@ -83,6 +69,9 @@ template <int KSC, int KSF> struct PackLayout {
     static constexpr int floats_at = 4 * frag; // in uint4 units
     static constexpr int nfloats = (FT + CT) * 16;
     static constexpr size_t bytes = (size_t)4 * frag * 16 + (size_t)nfloats * 4;
+    // workgroups of the packing: pieces, features of b1, then one for b2
+    static constexpr int B_FRAG = 4 * frag / kMlpThreads, B_FEAT = FT * 16 / kMlpWaves, BLOCKS = B_FRAG + B_FEAT + 1;
+    static_assert(4 * frag % kMlpThreads == 0 && frag % 64 == 0 && FT * 16 % kMlpWaves == 0, "whole workgroups");
 };
 static_assert(PackLayout<2, 4>::w2f == NarrowMlpPack::W2 && PackLayout<2, 4>::floats_at == NarrowMlpPack::SRC_FLOATS &&
                   PackLayout<2, 4>::nfloats == 192 && PackLayout<2, 4>::FT == NarrowMlpPack::FT,
@@ -93,7 +82,9 @@ struct MlpPackJobs {
     int C, Hd;
 };
 // Once per forward call: the MLP's weights into MFMA fragment order (gamma and beta of LN_2 folded
-// into the first layer); the backward pass reads the same pack.
+// into the first layer), as the A operand: tile of 16 output rows, k-step, lane; zero outside the matrices.  The backward pass
+// reads the same pack.  One 16-byte piece a thread, its eight loads in flight together (all four matrices in turn, an entry a
+// thread and step, were sixteen trips to memory: C = 60 4.4 -> 4.3 us).
 template <int KSC, int KSF>
 __global__ __launch_bounds__(kMlpThreads) void astl_mlp_pack_kernel(MlpPackJobs jobs)
 {
@@ -102,23 +93,42 @@ __global__ __launch_bounds__(kMlpThreads) void astl_mlp_pack_kernel(MlpPackJobs 
     constexpr int CT = L::CT, FT = L::FT;
     uint4 *pk = static_cast<uint4 *>(a.pack);
     const int C = jobs.C, Hd = jobs.Hd;
-    build_frags(pk + L::w1f, FT, KSC, [&](int f, int c) { return (f < Hd && c < C) ? bf(a.w_fc1, (long)f * C + c) * bf(a.ln_w, c) : 0.f; });
-    build_frags(pk + L::w2f, CT, KSF, [&](int c, int f) { return (f < Hd && c < C) ? bf(a.w_fc2, (long)c * Hd + f) : 0.f; });
-    build_frags(pk + L::w2t, FT, KSC, [&](int f, int c) { return (f < Hd && c < C) ? bf(a.w_fc2, (long)c * Hd + f) : 0.f; });
-    build_frags(pk + L::w1t, CT, KSF, [&](int c, int f) { return (f < Hd && c < C) ? bf(a.w_fc1, (long)f * C + c) : 0.f; });
+    int blk = blockIdx.x;
+    if (blk < L::B_FRAG) {
+        const int p = blk * kMlpThreads + (int)threadIdx.x;
+        const int mat = __builtin_amdgcn_readfirstlane(p / L::frag); // w1f, w2f, w2t, w1t
+        const int l = p & 63, fr = (p - mat * L::frag) >> 6;
+        const bool rows_are_features = mat == 0 || mat == 2, first = mat == 0 || mat == 3;
+        const int ks = rows_are_features ? KSC : KSF, s = fr % ks, m = 16 * (fr / ks) + (l & 15);
+        const bf16_t *w = first ? a.w_fc1 : a.w_fc2;
+        uint32_t v[8];
+        float e[8], g[8];
+        bool ok[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int k = slot_index(s, l >> 4, j), f = rows_are_features ? m : k, c = rows_are_features ? k : m;
+            ok[j] = f < Hd && c < C;
+            e[j] = bf(w, ok[j] ? (first ? (long)f * C + c : (long)c * Hd + f) : 0);
+            g[j] = mat == 0 ? bf(a.ln_w, c < C ? c : 0) : 1.0f;
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = ok[j] ? f32_to_bf16_bits(e[j] * g[j]) : 0u;
+        pk[p] = make_uint4(v[0] | v[1] << 16, v[2] | v[3] << 16, v[4] | v[5] << 16, v[6] | v[7] << 16);
+        return;
+    }
+    blk -= L::B_FRAG;
     float *fl = reinterpret_cast<float *>(pk + L::floats_at);
-    // b1 + W1 beta: one wavefront per feature
-    const int lane = threadIdx.x & 63;
-    for (int f = blockIdx.x * kMlpWaves + (threadIdx.x >> 6); f < FT * 16; f += gridDim.x * kMlpWaves) {
+    if (blk < L::B_FEAT) { // b1 + W1 beta: one wavefront per feature
+        const int lane = threadIdx.x & 63, f = blk * kMlpWaves + (threadIdx.x >> 6);
         float s = 0.f;
         if (f < Hd)
             for (int c = lane; c < C; c += 64) s += bf(a.w_fc1, (long)f * C + c) * bf(a.ln_b, c);
 #pragma unroll
         for (int m = 1; m < 64; m <<= 1) s += __shfl_xor(s, m);
         if (lane == 0) fl[f] = f < Hd ? s + bf(a.b_fc1, f) : 0.f;
+        return;
     }
-    for (int c = blockIdx.x * kMlpThreads + threadIdx.x; c < CT * 16; c += gridDim.x * kMlpThreads)
-        fl[FT * 16 + c] = c < C ? bf(a.b_fc2, c) : 0.f;
+    for (int c = threadIdx.x; c < CT * 16; c += kMlpThreads) fl[FT * 16 + c] = c < C ? bf(a.b_fc2, c) : 0.f;
 }
 
 // copies `n` uint4 from the pack into LDS
@@ -601,7 +611,7 @@ template <int KSC, int KSF> hipError_t launch_pack_t(int C, int hidden, const Ml
     for (int i = 0; i < n; ++i) a.j[i] = jobs[i];
     a.C = C; a.Hd = hidden;
     KernelTimer kt(K_MLP_PACK, s);
-    hipLaunchKernelGGL((astl_mlp_pack_kernel<KSC, KSF>), dim3(32, n), dim3(kMlpThreads), 0, s, a);
+    hipLaunchKernelGGL((astl_mlp_pack_kernel<KSC, KSF>), dim3(PackLayout<KSC, KSF>::BLOCKS, n), dim3(kMlpThreads), 0, s, a);
     return hipGetLastError();
 }
 

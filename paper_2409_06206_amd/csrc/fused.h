@@ -154,6 +154,20 @@ hipError_t launch_fused_fwd(const Geom &g, const bf16_t *x, const bf16_t *w_qkv,
 // ---------------------------------------------------------------------------------------
 // Parameter packing for this kernel (layout: FusedCfg, WQW / WPW / TBW)
 // ---------------------------------------------------------------------------------------
+// Bits of p[at], zero where the operand is padding.  The load is always taken (entry 0 stands in for none), so that a thread's
+// eight are in flight together: behind a branch each they are eight trips to memory one after the other.  That is what bounds
+// the packing, a launch as short as its longest thread: C = 180 with one / two groups 5.7 / 5.2 -> 4.9 / 4.7 us; C = 60 with
+// the operand of heads_bwd.hip added 5.2 -> 4.9.
+__device__ __forceinline__ uint32_t entry_or_zero(const bf16_t *p, int at, bool ok)
+{
+    const uint32_t v = p[ok ? at : 0].bits;
+    return ok ? v : 0u;
+}
+__device__ __forceinline__ uint32_t scaled_bits(uint32_t bits, float sc) { return f32_to_bf16_bits(__uint_as_float(bits << 16) * sc); }
+__device__ __forceinline__ uint4 join8(const uint32_t (&v)[8])
+{
+    return make_uint4(v[0] | v[1] << 16, v[2] | v[3] << 16, v[4] | v[5] << 16, v[6] | v[7] << 16);
+}
 // (entry i of the (N_WQW + N_WPW + N_WQX + N_WQN + N_WQY) * 64 + HEADS * TBW_PITCH of the wide layout; run by the extra
 // blocks of the parameter-packing launch)
 template <class Cf>
@@ -176,15 +190,14 @@ __device__ __forceinline__ void wide_pack_entry(int i, const bf16_t *__restrict_
         const int hd = f / 3, gi = hd / HG, hl = hd % HG;
         const int e = 16 * et + l16;
         uint32_t v[8];
+#pragma unroll
         for (int s = 0; s < 8; ++s) {
             const int fe = slot_feature(s);
-            float w = 0.f;
-            if (e < D && fe < D)
-                w = to_f32(w_qkv[((size_t)gi * 3 * CG + t * CG + hl * D + e) * CG + ks * D + fe]) * (t == 0 ? qscale : 1.0f);
-            v[s] = f32_to_bf16_bits(w);
+            v[s] = entry_or_zero(w_qkv, (gi * 3 * CG + t * CG + hl * D + e) * CG + ks * D + fe, e < D && fe < D);
         }
-        reinterpret_cast<uint4 *>(pack + Cf::P_WQW)[i] =
-            make_uint4(v[0] | v[1] << 16, v[2] | v[3] << 16, v[4] | v[5] << 16, v[6] | v[7] << 16);
+#pragma unroll
+        for (int s = 0; s < 8; ++s) v[s] = scaled_bits(v[s], t == 0 ? qscale : 1.0f);
+        reinterpret_cast<uint4 *>(pack + Cf::P_WQW)[i] = join8(v);
         return;
     }
     i -= E_WQW;
@@ -193,22 +206,22 @@ __device__ __forceinline__ void wide_pack_entry(int i, const bf16_t *__restrict_
         const int hd = f % HEADS, ot = f / HEADS;
         const int o = 16 * ot + l16;
         uint32_t v[8];
+#pragma unroll
         for (int s = 0; s < 8; ++s) {
             const int fe = slot_feature(s);
-            v[s] = (o < C && fe < D) ? (uint32_t)w_proj[(size_t)o * C + hd * D + fe].bits : 0u;
+            v[s] = entry_or_zero(w_proj, o * C + hd * D + fe, o < C && fe < D);
         }
-        reinterpret_cast<uint4 *>(pack + Cf::P_WPW)[i] =
-            make_uint4(v[0] | v[1] << 16, v[2] | v[3] << 16, v[4] | v[5] << 16, v[6] | v[7] << 16);
+        reinterpret_cast<uint4 *>(pack + Cf::P_WPW)[i] = join8(v);
         return;
     }
     i -= E_WPW;
     if (i < E_TBW) {
         const int hd = i / Cf::TBW_PITCH, e = i % Cf::TBW_PITCH;
-        reinterpret_cast<float *>(pack + Cf::P_TBW)[i] = e < 225 ? to_f32(table[e * HEADS + hd]) * kLog2e : 0.f;
+        reinterpret_cast<float *>(pack + Cf::P_TBW)[i] = __uint_as_float(entry_or_zero(table, e * HEADS + hd, e < 225) << 16) * kLog2e;
         return;
     }
     i -= E_TBW;
-    if (i < E_WQX) { // Wqkv^T for the backward: row l16 -> input channel (per head of the group), k-slots -> features of (hd, t)
+    if (Cf::N_WQX && i < E_WQX) { // Wqkv^T for the backward: row l16 -> input channel (per head of the group), k-slots -> features of (hd, t)
         int f = i >> 6;
         const int ct = f % Cf::CTF; f /= Cf::CTF;
         const int t = f % 3;
@@ -217,18 +230,18 @@ __device__ __forceinline__ void wide_pack_entry(int i, const bf16_t *__restrict_
         const int qq = (i >> 4) & 3;
         const float sc = t == 0 ? 1.0f / sqrtf((float)D) : 1.0f;
         uint32_t v[8];
+#pragma unroll
         for (int s = 0; s < 8; ++s) {
             const int fe = s < 4 ? 4 * qq + s : 16 + 4 * qq + (s - 4);
-            float w = 0.f;
-            if (cl < D && fe < D) w = to_f32(w_qkv[((size_t)gi * 3 * CG + t * CG + hl * D + fe) * CG + c]) * sc;
-            v[s] = f32_to_bf16_bits(w);
+            v[s] = entry_or_zero(w_qkv, (gi * 3 * CG + t * CG + hl * D + fe) * CG + c, cl < D && fe < D);
         }
-        reinterpret_cast<uint4 *>(pack + Cf::P_WQX)[i] =
-            make_uint4(v[0] | v[1] << 16, v[2] | v[3] << 16, v[4] | v[5] << 16, v[6] | v[7] << 16);
+#pragma unroll
+        for (int s = 0; s < 8; ++s) v[s] = scaled_bits(v[s], sc);
+        reinterpret_cast<uint4 *>(pack + Cf::P_WQX)[i] = join8(v);
         return;
     }
     i -= E_WQX;
-    if (i < Cf::N_WQN * 64) { // (hd, t, et, ks): row l16 -> feature 16 et + l16, k-slots -> channels 32 ks + 8 q ..
+    if (Cf::N_WQN && i < Cf::N_WQN * 64) { // (hd, t, et, ks): row l16 -> feature 16 et + l16, k-slots -> channels 32 ks + 8 q ..
         int f = i >> 6;
         const int ks = f % Cf::KS; f /= Cf::KS;
         const int et = f % ET; f /= ET;
@@ -237,31 +250,29 @@ __device__ __forceinline__ void wide_pack_entry(int i, const bf16_t *__restrict_
         const int e = 16 * et + (i & 15);
         const int c0 = 32 * ks + 8 * ((i >> 4) & 3);
         uint32_t v[8];
-        for (int s = 0; s < 8; ++s) {
-            float w = 0.f;
-            if (e < D && c0 + s < CG)
-                w = to_f32(w_qkv[((size_t)gi * 3 * CG + t * CG + hl * D + e) * CG + c0 + s]) * (t == 0 ? qscale : 1.0f);
-            v[s] = f32_to_bf16_bits(w);
-        }
-        reinterpret_cast<uint4 *>(pack + Cf::P_WQN)[i] =
-            make_uint4(v[0] | v[1] << 16, v[2] | v[3] << 16, v[4] | v[5] << 16, v[6] | v[7] << 16);
+#pragma unroll
+        for (int s = 0; s < 8; ++s) v[s] = entry_or_zero(w_qkv, (gi * 3 * CG + t * CG + hl * D + e) * CG + c0 + s, e < D && c0 + s < CG);
+#pragma unroll
+        for (int s = 0; s < 8; ++s) v[s] = scaled_bits(v[s], t == 0 ? qscale : 1.0f);
+        reinterpret_cast<uint4 *>(pack + Cf::P_WQN)[i] = join8(v);
         return;
     }
     i -= Cf::N_WQN * 64;
-    if (i < Cf::N_WQY * 64) { // Wqkv^T by heads: row l16 -> channel 16 et + l16 of head hdo, k-slots -> feature (t, e) of head h
+    if (Cf::N_WQY && i < Cf::N_WQY * 64) { // Wqkv^T by heads: row l16 -> channel 16 et + l16 of head hdo, k-slots -> feature (t, e) of head h
         int f = i >> 6;
         const int ks = f % Cf::KF; f /= Cf::KF;
         const int h = f % HG; f /= HG;
         const int et = f % ET, hdo = f / ET, gi = hdo / HG, hlo = hdo % HG, c = 16 * et + (i & 15);
         uint32_t v[8];
+        const int u0 = 32 * ks + 8 * ((i >> 4) & 3);
+#pragma unroll
         for (int s = 0; s < 8; ++s) {
-            const int u = 32 * ks + 8 * ((i >> 4) & 3) + s, t = u / D, e = u - t * D;
-            float w = 0.f;
-            if (c < D && t < 3) w = to_f32(w_qkv[((size_t)gi * 3 * CG + t * CG + h * D + e) * CG + hlo * D + c]) * (t == 0 ? 1.0f / sqrtf((float)D) : 1.0f);
-            v[s] = f32_to_bf16_bits(w);
+            const int t = (u0 + s) / D, e = u0 + s - t * D;
+            v[s] = entry_or_zero(w_qkv, (gi * 3 * CG + t * CG + h * D + e) * CG + hlo * D + c, c < D && t < 3);
         }
-        reinterpret_cast<uint4 *>(pack + Cf::P_WQY)[i] =
-            make_uint4(v[0] | v[1] << 16, v[2] | v[3] << 16, v[4] | v[5] << 16, v[6] | v[7] << 16);
+#pragma unroll
+        for (int s = 0; s < 8; ++s) v[s] = scaled_bits(v[s], u0 + s < D ? 1.0f / sqrtf((float)D) : 1.0f);
+        reinterpret_cast<uint4 *>(pack + Cf::P_WQY)[i] = join8(v);
     }
 }
 

@@ -22,11 +22,6 @@ struct FusedPackJobs {
 // ---------------------------------------------------------------------------------------
 // Parameter packing (see FusedCfg): every thread assembles the operand of one (fragment, lane).
 // ---------------------------------------------------------------------------------------
-__device__ __forceinline__ uint32_t bf16_scaled(bf16_t w, float sc)
-{
-    return sc == 1.0f ? (uint32_t)w.bits : (uint32_t)f32_to_bf16_bits(to_f32(w) * sc);
-}
-
 // All layouts of a shape are written whatever the size of the map, so that weights packed once serve maps and bands of
 // any size.
 template <class Cf> struct PackGrid {
@@ -58,20 +53,23 @@ __global__ __launch_bounds__(256) void pack_params_kernel(FusedPackJobs jobs)
     int i = blockIdx.x * blockDim.x + threadIdx.x;
     int l16 = i & 15, q = (i >> 4) & 3; // lane coordinates inside the current segment
 
-    if (i < E_WQH) { // Wqkv, head-padded input order: l16 -> out feature e; k-slot s -> head 2*step + s/4, e' = 4q + s%4
+    if (Cf::N_WQH && i < E_WQH) { // Wqkv, head-padded input order: l16 -> out feature e; k-slot s -> head 2*step + s/4, e' = 4q + s%4
         int f = i >> 6;
         const int st = f % Cf::NSTEP; f /= Cf::NSTEP;
         const int t = f % 3;
         const int hd = f / 3, gi = hd / HG, hl = hd % HG;
         const float sc = t == 0 ? qscale * kLog2e : 1.0f;
         uint32_t v[8];
+#pragma unroll
         for (int s = 0; s < 8; ++s) {
             const int hlp = 2 * st + (s >> 2), ep = 4 * q + (s & 3);
-            float w = 0.f;
-            if (st < HG / 2 || s < 4) {
-                if (l16 < D && hlp < HG && ep < D)
-                    w = to_f32(w_qkv[((size_t)gi * 3 * CG + t * CG + hl * D + l16) * CG + hlp * D + ep]) * sc;
-            } else if (q == 0 && l16 >= D && l16 < D + 4) {
+            v[s] = entry_or_zero(w_qkv, (gi * 3 * CG + t * CG + hl * D + l16) * CG + hlp * D + ep,
+                                 (st < HG / 2 || s < 4) && l16 < D && hlp < HG && ep < D);
+        }
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            float w = __uint_as_float(v[s] << 16) * sc;
+            if (st >= HG / 2 && s >= 4 && q == 0 && l16 >= D && l16 < D + 4) {
                 // mask inputs (1, r, c, r*c) -> rows D..D+3: the query side carries the coefficients of
                 //   mask(n,m) = kMask * [ (r_n|c_n) + (1-2r_n)(1-c_n) r_m + (1-2c_n)(1-r_n) c_m - (1-2r_n)(1-2c_n) r_m c_m ],
                 // the key side the inputs themselves
@@ -81,26 +79,25 @@ __global__ __launch_bounds__(256) void pack_params_kernel(FusedPackJobs jobs)
             }
             v[s] = f32_to_bf16_bits(w);
         }
-        reinterpret_cast<uint4 *>(pack + Cf::P_WQH)[i] =
-            make_uint4(v[0] | v[1] << 16, v[2] | v[3] << 16, v[4] | v[5] << 16, v[6] | v[7] << 16);
+        reinterpret_cast<uint4 *>(pack + Cf::P_WQH)[i] = join8(v);
         return;
     }
     i -= E_WQH;
-    if (i < E_WP2) { // Wproj: l16 -> output channel o; k-slot s -> head 2*pair + s/4, e = 4q + s%4
+    if (Cf::N_WP2 && i < E_WP2) { // Wproj: l16 -> output channel o; k-slot s -> head 2*pair + s/4, e = 4q + s%4
         const int f = i >> 6;
         const int pr = f % (HEADS / 2), ot = f / (HEADS / 2);
         const int o = 16 * ot + l16;
         uint32_t v[8];
+#pragma unroll
         for (int s = 0; s < 8; ++s) {
             const int hd = 2 * pr + (s >> 2), e = 4 * q + (s & 3);
-            v[s] = (o < C && e < D) ? (uint32_t)w_proj[(size_t)o * C + hd * D + e].bits : 0u;
+            v[s] = entry_or_zero(w_proj, o * C + hd * D + e, o < C && e < D);
         }
-        reinterpret_cast<uint4 *>(pack + Cf::P_WP2)[i] =
-            make_uint4(v[0] | v[1] << 16, v[2] | v[3] << 16, v[4] | v[5] << 16, v[6] | v[7] << 16);
+        reinterpret_cast<uint4 *>(pack + Cf::P_WP2)[i] = join8(v);
         return;
     }
     i -= E_WP2;
-    if (i < E_BF) { // bias (base-2 units) of score tile (key tile kt, query tile nt), nt - kt = dlt - 3, as a
+    if (Cf::N_BF && i < E_BF) { // bias (base-2 units) of score tile (key tile kt, query tile nt), nt - kt = dlt - 3, as a
         // B operand: column l16 = query (2nt + l16/8, l16%8), k-slots 4q+j = key (2kt + q/2, 4(q%2) + j)
         constexpr int M = 8;
         const int f = i >> 6;
@@ -123,21 +120,21 @@ __global__ __launch_bounds__(256) void pack_params_kernel(FusedPackJobs jobs)
         const int hd = f / 3, gi = hd / HG, hl = hd % HG;
         const int e = 16 * et + l16;
         uint32_t v[8];
+#pragma unroll
         for (int s = 0; s < 8; ++s) {
             const int c = 32 * ks + 8 * q + s;
-            v[s] = (e < D && c < CG)
-                       ? bf16_scaled(w_qkv[((size_t)gi * 3 * CG + t * CG + hl * D + e) * CG + c], t == 0 ? qscale : 1.0f)
-                       : 0u;
+            v[s] = entry_or_zero(w_qkv, (gi * 3 * CG + t * CG + hl * D + e) * CG + c, e < D && c < CG);
         }
-        reinterpret_cast<uint4 *>(pack + Cf::P_WQ)[i] =
-            make_uint4(v[0] | v[1] << 16, v[2] | v[3] << 16, v[4] | v[5] << 16, v[6] | v[7] << 16);
+        if (t == 0)
+#pragma unroll
+            for (int s = 0; s < 8; ++s) v[s] = scaled_bits(v[s], qscale);
+        reinterpret_cast<uint4 *>(pack + Cf::P_WQ)[i] = join8(v);
         return;
     }
     i -= E_WQ;
     if (i < E_BIAS) { // fp32 biases; the q third of every group scaled like its weights
         float *bias = reinterpret_cast<float *>(pack + Cf::P_BIAS);
-        if (i < 3 * C) bias[i] = to_f32(b_qkv[i]) * ((i % (3 * CG)) < CG ? qscale : 1.0f);
-        else bias[i] = to_f32(b_proj[i - 3 * C]);
+        bias[i] = i < 3 * C ? to_f32(b_qkv[i]) * ((i % (3 * CG)) < CG ? qscale : 1.0f) : to_f32(b_proj[i - 3 * C]);
         return;
     }
     i -= E_BIAS; // not a multiple of 64: re-derive the lane coordinates
@@ -150,16 +147,16 @@ __global__ __launch_bounds__(256) void pack_params_kernel(FusedPackJobs jobs)
         const int hd = f / ET;
         const int e = 16 * et + l16;
         uint32_t v[8];
+#pragma unroll
         for (int s = 0; s < 8; ++s) {
             const int o = 32 * ks + 8 * q + s;
-            v[s] = (e < D && o < C) ? (uint32_t)w_proj[(size_t)o * C + hd * D + e].bits : 0u;
+            v[s] = entry_or_zero(w_proj, o * C + hd * D + e, e < D && o < C);
         }
-        reinterpret_cast<uint4 *>(pack + Cf::P_WPT)[i] =
-            make_uint4(v[0] | v[1] << 16, v[2] | v[3] << 16, v[4] | v[5] << 16, v[6] | v[7] << 16);
+        reinterpret_cast<uint4 *>(pack + Cf::P_WPT)[i] = join8(v);
         return;
     }
     i -= E_WPT;
-    if (i < E_WQT) { // Wqkv^T: l16 -> input channel hlp*D + 16etp + l16; k-slots 4q+j -> out feature (t,hl,e)
+    if (Cf::N_WQT && i < E_WQT) { // Wqkv^T: l16 -> input channel hlp*D + 16etp + l16; k-slots 4q+j -> out feature (t,hl,e)
         int f = i >> 6;
         const int etp = f % ET; f /= ET;
         const int hlp = f % HG; f /= HG;
@@ -168,41 +165,43 @@ __global__ __launch_bounds__(256) void pack_params_kernel(FusedPackJobs jobs)
         const int hd = f / 3, gi = hd / HG, hl = hd % HG;
         const int cp = 16 * etp + l16;
         uint32_t v[4];
+#pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int e = 16 * et + 4 * q + j;
-            v[j] = (cp < D && e < D)
-                       ? bf16_scaled(w_qkv[((size_t)gi * 3 * CG + t * CG + hl * D + e) * CG + hlp * D + cp], t == 0 ? qscale : 1.0f)
-                       : 0u;
+            v[j] = entry_or_zero(w_qkv, (gi * 3 * CG + t * CG + hl * D + e) * CG + hlp * D + cp, cp < D && e < D);
         }
+        if (t == 0)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[j] = scaled_bits(v[j], qscale);
         reinterpret_cast<uint2 *>(pack + Cf::P_WQT)[i] = make_uint2(v[0] | v[1] << 16, v[2] | v[3] << 16);
         return;
     }
     i -= E_WQT;
-    if (i < Cf::N_WQF * 64) { // Wqkv^T: l16 -> channel of head hdo; k-slot 8q+s -> feature (t, e) = ((8q+s) / D, (8q+s) % D) of head h
+    if (Cf::N_WQF && i < Cf::N_WQF * 64) { // Wqkv^T: l16 -> channel of head hdo; k-slot 8q+s -> feature (t, e) = ((8q+s) / D, (8q+s) % D) of head h
         const int f = i >> 6, h = f % HG, hdo = f / HG, gi = hdo / HG, hlo = hdo % HG;
         uint32_t v[8];
+#pragma unroll
         for (int s = 0; s < 8; ++s) {
             const int t = (8 * q + s) / D, e = (8 * q + s) % D;
-            v[s] = (l16 < D && t < 3)
-                       ? bf16_scaled(w_qkv[((size_t)gi * 3 * CG + t * CG + h * D + e) * CG + hlo * D + l16], t == 0 ? qscale : 1.0f)
-                       : 0u;
+            v[s] = entry_or_zero(w_qkv, (gi * 3 * CG + t * CG + h * D + e) * CG + hlo * D + l16, l16 < D && t < 3);
         }
-        reinterpret_cast<uint4 *>(pack + Cf::P_WQF)[i] =
-            make_uint4(v[0] | v[1] << 16, v[2] | v[3] << 16, v[4] | v[5] << 16, v[6] | v[7] << 16);
+#pragma unroll
+        for (int s = 0; s < 8; ++s) v[s] = 8 * q + s < D ? scaled_bits(v[s], qscale) : v[s];
+        reinterpret_cast<uint4 *>(pack + Cf::P_WQF)[i] = join8(v);
         return;
     }
     i -= Cf::N_WQF * 64;
-    if (i < Cf::N_WPK * 64) { // Wproj for the projection GEMM: l16 -> output channel; k-slots 8q+s -> input channel
+    if (Cf::N_WPK && i < Cf::N_WPK * 64) { // Wproj for the projection GEMM: l16 -> output channel; k-slots 8q+s -> input channel
         const int f = i >> 6;
         const int ks = f % KSC, ot = f / KSC;
         const int o = 16 * ot + l16;
         uint32_t v[8];
+#pragma unroll
         for (int s = 0; s < 8; ++s) {
             const int c = 32 * ks + 8 * q + s;
-            v[s] = (o < C && c < C) ? (uint32_t)w_proj[(size_t)o * C + c].bits : 0u;
+            v[s] = entry_or_zero(w_proj, o * C + c, o < C && c < C);
         }
-        reinterpret_cast<uint4 *>(pack + Cf::P_WPK)[i] =
-            make_uint4(v[0] | v[1] << 16, v[2] | v[3] << 16, v[4] | v[5] << 16, v[6] | v[7] << 16);
+        reinterpret_cast<uint4 *>(pack + Cf::P_WPK)[i] = join8(v);
     }
 }
 

@@ -517,17 +517,23 @@ __global__ __launch_bounds__(256) void linear_stream_pack_kernel(LinearArgs p0, 
     const LinearArgs &p = blockIdx.y ? p1 : p0;
     const int nu = ((p.K + 31) / 32 + L::HU - 1) / L::HU, nb = (p.N + 16 * L::NT - 1) / (16 * L::NT);
     const uint16_t *w = static_cast<const uint16_t *>(p.w);
-    uint16_t *d16 = static_cast<uint16_t *>(p.scratch);
-    const int total = nb * nu * L::FR_UNIT * 512;
+    const int total = nb * nu * L::FR_UNIT * 64; // (a thread's eight loads in flight together, none behind a branch)
     for (int e = blockIdx.x * 256 + threadIdx.x; e < total; e += gridDim.x * 256) {
-        const int j = e & 7, l = (e >> 3) & 63, fr = e >> 9;
+        const int l = e & 63, fr = e >> 6;
         const int gu = fr / L::FR_UNIT, f = fr - gu * L::FR_UNIT;
         const int blk = gu / nu, u = gu - blk * nu;
         const int hs = f / L::NT, ct = f - hs * L::NT;
         const int m = l & 15, lq = l >> 4;
         const int n = 16 * L::NT * blk + 32 * (ct >> 1) + 8 * (m >> 2) + 4 * (ct & 1) + (m & 3);
-        const int k = 32 * (L::HU * u + hs) + 8 * lq + j;
-        d16[e] = (n < p.N && k < p.K) ? w[(long)n * p.w_sn + (long)k * p.w_sk] : (uint16_t)0;
+        uint32_t v[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int k = 32 * (L::HU * u + hs) + 8 * lq + j;
+            const bool ok = n < p.N && k < p.K;
+            v[j] = w[ok ? (long)n * p.w_sn + (long)k * p.w_sk : 0];
+            v[j] = ok ? v[j] : 0u;
+        }
+        static_cast<uint4 *>(p.scratch)[e] = make_uint4(v[0] | v[1] << 16, v[2] | v[3] << 16, v[4] | v[5] << 16, v[6] | v[7] << 16);
     }
     float *bl = reinterpret_cast<float *>(static_cast<uint8_t *>(p.scratch) + (size_t)nb * nu * L::UNIT_BYTES);
     const uint16_t *bias = static_cast<const uint16_t *>(p.bias);
