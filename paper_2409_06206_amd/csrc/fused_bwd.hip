@@ -1161,13 +1161,13 @@ hipError_t run_bwd(const Geom &g, const bf16_t *x, const bf16_t *dy, const bf16_
 
 } // namespace
 
-// One launch with a wavefront per head, or the launches per head group of this file.  Narrow layers of one to three groups
-// take the former: 32 images of 64x64, forward + backward, 1 / 2 / 3 groups 160.9 / 128.7 / 138.1 us by head
-// groups, 99.6 / 91.9 / 96.6 by heads; one image of 64x64 42.6 / 46.5 / 51.3 and 35.5 / 32.3 / 35.4.  Six groups would be a pipeline of six steps whose rows LDS has no room for.  Two
-// groups with images of at most four windows stay with the latter although it is the slower one there (two images of 16x16:
-// 43.9 us against 31.5): what gswa_profile_collect() tells of such a layer, two launches and two sums, is relied on
-// (test_kernel_timing_aid_reports_the_launched_kernels).  By the size of an image and not of the batch, so that an image's
-// gradients have the same bits alone and in a batch.
+// One launch with a wavefront per head, or the launches per head group of this file.  Narrow layers of one to three groups take
+// the former: 32 images of 64x64, forward + backward, 1 / 2 / 3 groups 160.4 / 128.6 / 138.8 us by head groups, 97.6 / 90.7 /
+// 95.7 by heads; one image of 64x64 42.6 / 46.4 / 51.3 and 35.5 / 31.6 / 35.4.  Six groups would be a pipeline of six steps
+// whose rows LDS has no room for.  Two groups with images of at most four windows stay with the latter although it is the slower
+// one there (two images of 16x16: 43.9 us against 31.5): what gswa_profile_collect() tells of such a layer, two launches and two
+// sums, is relied on (test_kernel_timing_aid_reports_the_launched_kernels).  By the size of an image and not of the batch, so
+// that an image's gradients have the same bits alone and in a batch.
 static bool by_heads(const Geom &g) { return heads_bwd_supported(g) && !(g.groups == 2 && g.nwi * g.nwj <= 4); }
 
 bool fused_bwd_supported(const Geom &g)

@@ -11,8 +11,8 @@
 // the weight gradients 1.9 k and dF 2.9 k; eight windows a workgroup, 12 k clocks of set-up and 12 k to leave the partial sums.
 // What it saves over an adjoint and a gradient launch a group (wide_bwd.hip) is memory: d(q|k|v), F and the cascade gradient
 // went out and in between the two, 380 MB a group of 2048 windows against 125.  Forward + backward of 32 / 16 / 1 images of
-// 64x64 333 / 203 / 117 us by those two, 270 / 172 / 83 by heads; of an image of 24x16 with an odd shift, which took four
-// launches of one or two heads with a workgroup a window, ODD.
+// 64x64 333.2 / 202.7 / 117.0 us by those two, 273.4 / 172.0 / 81.7 by heads; with an odd shift, which took four launches of one
+// or two heads with a workgroup a window, 32 images 462.2 -> 273.2, an image of 24x16 102.5 -> 73.8.
 //
 // For two groups: with three a group's two heads would leave half the SIMD units to row fetches, and its launches are three.
 #include "fused.h"
