@@ -525,8 +525,17 @@ def test_wide_layers_more_windows_than_wavefronts(oracle, groups):
 @pytest.mark.parametrize("shift", [2, 3, 6])
 def test_wide_layers_other_shifts(oracle, shift):
     """Shifts other than half a window: even ones split the last window column's rows at a
-    16-byte boundary (the streamed backward), odd ones take the per-chunk kernels."""
+    16-byte boundary, odd ones do not."""
     parity.check_case(oracle, 1, 24, 16, 180, 6, 2, 8, shift, "bf16", regime="stress")
+
+
+@pytest.mark.parametrize("B,H,W,shift", [(1, 8, 8, 0), (1, 24, 16, 3), (5, 56, 64, 7)])
+def test_three_groups_of_a_wide_layer_odd_shifts(oracle, B, H, W, shift):
+    """Three groups: an odd shift takes a launch of whole groups a head pair, any other the streamed backward; one window, six,
+    and more than one a workgroup."""
+    with parity.launch_counts() as counts:
+        parity.check_case(oracle, B, H, W, 180, 6, 3, 8, shift, "bf16", regime="stress")
+    assert (counts.get("fused_bwd", 0), counts.get("wide_attn_bwd", 0)) == ((3, 0) if shift % 2 else (0, 3)), counts
 
 
 @pytest.mark.parametrize("regime", ["init", "stress"])
