@@ -276,12 +276,14 @@ def test_narrow_forward_in_four_waves_and_in_one(oracle, groups, shift):
         assert parity.rel_err(kept[k], w) <= parity.TOL["bf16"], k
 
 
-def test_kernel_timing_aid_reports_the_launched_kernels():
-    """gswa_profile_*: per-kernel HIP-event totals for one forward + backward."""
+@pytest.mark.parametrize("groups", [2, 6])
+def test_kernel_timing_aid_reports_the_launched_kernels(groups):
+    """gswa_profile_*: per-kernel HIP-event totals for one forward + backward, the launches of a kernel added up (the backward
+    of six groups is two launches with a sum behind each)."""
     import torch
     from paper_2409_06206_amd import gswa, runner
-    x, dy, p = parity.make_inputs(2, 16, 16, 60, 6, 2, 8, "bf16", synth.LAYER_SEED0, "init")
-    layer = runner.DeviceLayer(2, 16, 16, 60, 6, 2, 8, 4, "bf16")
+    x, dy, p = parity.make_inputs(2, 16, 16, 60, 6, groups, 8, "bf16", synth.LAYER_SEED0, "init")
+    layer = runner.DeviceLayer(2, 16, 16, 60, 6, groups, 8, 4, "bf16")
     layer.set_params(p)
     layer.set_inputs(x, dy)
     gswa.gswa_profile_enable(True)
@@ -294,7 +296,9 @@ def test_kernel_timing_aid_reports_the_launched_kernels():
         gswa.gswa_profile_enable(False)
     torch.cuda.synchronize()
     assert dropped == 0
-    assert res["fused_fwd"][1] == 1 and res["fused_bwd"][1] == 2 and res["reduce_partials"][1] == 2  # one sum per head-group launch
+    assert res["fused_fwd"][1] == 1 and res["fused_bwd"][1] == res["reduce_partials"][1] >= 1  # one sum per launch
+    if groups == 6:
+        assert res["fused_bwd"][1] == 2
     assert all(ms > 0 for ms, _ in res.values())
     layer.forward()
     assert gswa.gswa_profile_collect()[0] == {}
