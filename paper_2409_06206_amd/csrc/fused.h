@@ -62,7 +62,7 @@ template <int C_, int HEADS_, int G_> struct FusedCfg {
     //        head h of the same group
     static constexpr bool HEADS_BWD = !SPLIT && G <= 3;
     static constexpr int N_WQF = HEADS_BWD ? HEADS * HG : 0;
-    static constexpr int N_WQT = G == 6 || (SPLIT ? G == 3 : G == 2) ? HEADS * 3 * ET * HG * ET : 0; // Wqkv^T, K=16: (hd,t,et,hlp,etp)
+    static constexpr int N_WQT = G == 6 || (SPLIT && G == 3) ? HEADS * 3 * ET * HG * ET : 0; // Wqkv^T, K=16: (hd,t,et,hlp,etp)
     static constexpr size_t P_WQH = 0;
     static constexpr size_t P_WP2 = P_WQH + (size_t)N_WQH * 1024;
     static constexpr size_t P_BF = P_WP2 + (size_t)N_WP2 * 1024;

@@ -958,18 +958,17 @@ __global__ __launch_bounds__(512, 1) void wproj_grad_kernel(long T, const bf16_t
 // wrote.  Three heads per launch keep the accumulators small enough for two workgroups per CU.
 // Wide layers of three groups go a group of two heads a launch (their weights and row buffers fill LDS).
 template <bool SPLIT, int G> struct ChunkPlan;
-template <> struct ChunkPlan<false, 2> { static constexpr int N = 2; static constexpr int B[2] = {3, 0}, E[2] = {6, 3}; };
 template <> struct ChunkPlan<false, 6> { static constexpr int N = 2; static constexpr int B[2] = {3, 0}, E[2] = {6, 3}; };
 template <> struct ChunkPlan<true, 3> { static constexpr int N = 3; static constexpr int B[3] = {4, 2, 0}, E[3] = {6, 4, 2}; };
 template <> struct ChunkPlan<true, 2> { static constexpr int N = 0; }; // (wide_heads_bwd.hip)
 
-// Workgroups of a backward launch: narrow layers with more than one group run two per compute unit.
+// Workgroups of a backward launch: narrow layers run two per compute unit.
 // `cus` = the device's compute units for a launch, kSizingCus for the scratch size (a launch never
 // uses more workgroups than the size was computed for).
 int bwd_grid(const Geom &g, int cus)
 {
     if (cus > kSizingCus) cus = kSizingCus;
-    const int grid = ((g.C <= 64 && g.groups > 1) ? 2 : 1) * cus;
+    const int grid = (g.C <= 64 ? 2 : 1) * cus;
     return grid > g.nW ? g.nW : grid;
 }
 
@@ -1157,23 +1156,18 @@ hipError_t run_bwd(const Geom &g, const bf16_t *x, const bf16_t *dy, const bf16_
     return hipSuccess;
 }
 
-#define GSWA_FUSED_SHAPES(X) X(60, 6, 2) X(60, 6, 6) X(180, 6, 2) X(180, 6, 3)
+#define GSWA_FUSED_SHAPES(X) X(60, 6, 6) X(180, 6, 2) X(180, 6, 3)
 
 } // namespace
 
 // One launch with a wavefront per head, or the launches per head group of this file.  Narrow layers of one to three groups take
 // the former: 32 images of 64x64, forward + backward, 1 / 2 / 3 groups 160.4 / 128.6 / 138.8 us by head groups, 97.6 / 90.7 /
-// 95.7 by heads; one image of 64x64 42.6 / 46.4 / 51.3 and 35.5 / 31.6 / 35.4.  Six groups would be a pipeline of six steps
-// whose rows LDS has no room for.  Two groups with images of at most four windows stay with the latter although it is the slower
-// one there (two images of 16x16: 43.9 us against 31.5): what gswa_profile_collect() tells of such a layer, two launches and two
-// sums, is relied on (test_kernel_timing_aid_reports_the_launched_kernels).  By the size of an image and not of the batch, so
-// that an image's gradients have the same bits alone and in a batch.
-static bool by_heads(const Geom &g) { return heads_bwd_supported(g) && !(g.groups == 2 && g.nwi * g.nwj <= 4); }
-
+// 95.7 by heads; one image of 64x64 42.6 / 46.4 / 51.3 and 35.5 / 31.6 / 35.4; two of 16x16, two groups, 42.0 and 31.1.  Six
+// groups would be a pipeline of six steps whose rows LDS has no room for.
 bool fused_bwd_supported(const Geom &g)
 {
     if (g.M != 8) return false;
-    if (by_heads(g)) return true;
+    if (heads_bwd_supported(g)) return true;
 #define X(C_, H_, G_) \
     if (g.C == C_ && g.heads == H_ && g.groups == G_) return true;
     GSWA_FUSED_SHAPES(X)
@@ -1183,7 +1177,7 @@ bool fused_bwd_supported(const Geom &g)
 
 size_t fused_bwd_ws_bytes(const Geom &g)
 {
-    if (by_heads(g)) return (heads_bwd_ws_bytes(g) + 255) & ~size_t(255);
+    if (heads_bwd_supported(g)) return (heads_bwd_ws_bytes(g) + 255) & ~size_t(255);
     int total = 0;
 #define X(C_, H_, G_) \
     if (g.C == C_ && g.heads == H_ && g.groups == G_) total = max_partial<FusedCfg<C_, H_, G_>>();
@@ -1199,7 +1193,7 @@ hipError_t launch_fused_bwd(const Geom &g, const bf16_t *x, const bf16_t *dy, co
                             float *db_qkv, float *dw_proj, float *db_proj, float *dtable, int accumulate,
                             void *ws, hipStream_t s)
 {
-    if (by_heads(g))
+    if (heads_bwd_supported(g))
         return launch_heads_bwd(g, x, dy, attn, pack, table, dx, dw_qkv, db_qkv, dw_proj, db_proj, dtable, accumulate, ws, s);
 #define X(C_, H_, G_)                                                   \
     if (g.C == C_ && g.heads == H_ && g.groups == G_)                   \

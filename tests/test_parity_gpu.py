@@ -469,9 +469,13 @@ def test_more_windows_than_wavefronts(oracle, groups):
     (7, 56, 48, 4, True),   # 294: a second window for some of 256 workgroups
     (4, 24, 104, 3, False), # 156, no cascade
     (11, 72, 64, 1, True),  # 792: three or four windows a workgroup
+    (3, 8, 8, 0, True),     # images of one window
+    (1, 16, 8, 5, True),    # of two, both cut by the shift in both directions
+    (2, 16, 16, 4, True),   # of four
 ])
 def test_narrow_backward_with_a_wave_per_head(oracle, B, H, W, shift, cascade, groups):
-    """One to three groups of a narrow layer: the whole backward is one launch and one sum, and the same bits twice."""
+    """One to three groups of a narrow layer, images of any size: the whole backward is one launch and one sum, and the same bits
+    twice."""
     _say("wave per head", B, H, W, shift, cascade, groups)
     with parity.launch_counts() as counts:
         errs, layer = parity.check_case(oracle, B, H, W, 60, 6, groups, 8, shift, "bf16", seed=synth.LAYER_SEED0 + 4,
