@@ -15,6 +15,10 @@
 // or two heads with a workgroup a window, 32 images 462.2 -> 273.2, an image of 24x16 102.5 -> 73.8.
 //
 // For two groups: with three a group's two heads would leave half the SIMD units to row fetches, and its launches are three.
+//
+// Inputs of any size.  q, k, v and the scores come from the operands of the one-launch forward, log2(e) / sqrt(d) in the query
+// rows.  From 2^31 elements on the forward is another one with 1 / sqrt(d) there: q is rounded once in either, but not to the
+// same values (as with three groups and an odd shift, where the backward is the one with 1 / sqrt(d), fused_bwd.hip).
 #include "fused.h"
 #include "mfma.h"
 #include "wide_heads_bwd.h"
@@ -24,7 +28,7 @@ namespace gswa {
 namespace {
 
 constexpr float kLog2e = 1.4426950408889634f;
-constexpr float kMaskLog2 = -100.0f * kLog2e; // scores are in base-2 units, as the forward forms them
+constexpr float kMaskLog2 = -100.0f * kLog2e; // scores are in base-2 units, as the one-launch forward forms them
 
 template <class Cf> struct WideHeadsCfg {
     static constexpr int C = Cf::C, D = Cf::D, CG = Cf::CG, HG = Cf::HG, HEADS = Cf::HEADS, G = Cf::G;

@@ -250,6 +250,49 @@ def test_wide_forward_of_2_31_elements_and_more(window, shift, groups):
             assert err <= parity.TOL["bf16"], (i, r, err)
 
 
+@pytest.mark.parametrize("shift", [4, 3])
+def test_wide_backward_of_2_31_elements_and_more(shift):
+    """Two groups: one kernel takes the backward of inputs of any size.  Every image's input gradient against the image alone,
+    and the parameter gradients against the sum over the images, at the tolerance of two organisations of the same layer (the
+    forward of such inputs is another one, so the group outputs that both passes of the backward start from are rounded
+    differently)."""
+    import torch
+    from paper_2409_06206_amd import gswa, runner
+    B, H, W, C = 8, 1008, 1504, 180
+    assert (B - 1) * H * W * C < 1 << 31 <= B * H * W * C
+    _say("case", shift)
+    _, _, p = parity.make_inputs(1, 8, 8, C, 6, 2, 8, "bf16", synth.LAYER_SEED0 + 7, "stress")
+    one = runner.DeviceLayer(1, H, W, C, 6, 2, 8, shift, "bf16", gswa.GSWA_ACCUM_WGRAD)
+    one.set_params(p)
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(2)
+    x, dy = (torch.randn((B, H, W, C), generator=gen, device="cuda:0", dtype=torch.bfloat16) for _ in range(2))
+    desc = gswa.make_desc(B, H, W, C, 6, 2, 8, shift, "bf16")
+    saved_bytes, fwd_bytes, bwd_bytes = gswa.gswa_query_bytes(desc)
+    ws = torch.full((max(fwd_bytes, bwd_bytes),), 255, dtype=torch.uint8, device="cuda:0")  # (NaN where nothing is written)
+    saved = torch.full((saved_bytes,), 255, dtype=torch.uint8, device="cuda:0")
+    y, dx = torch.empty_like(x), torch.full_like(x, float("nan"))
+    names = ("w_qkv", "b_qkv", "w_proj", "b_proj", "table")
+    args = [one.params[k] for k in names]
+    grads = [torch.full_like(one.grads[k], float("nan")) for k in names]
+    gswa.gswa_forward(desc, x, *args, y, saved, ws)
+    with parity.launch_counts() as counts:
+        gswa.gswa_backward(desc, x, dy, *args, saved, dx, *grads, ws)
+    assert counts["wide_attn_bwd"] == 2 and "fused_bwd" not in counts, counts
+    for g in one.grads.values():
+        g.zero_()
+    for i in range(B):
+        one.x, one.dy = x[i:i + 1], dy[i:i + 1]
+        one.forward()
+        one.backward()
+        top = float(one.dx.abs().max())
+        for r in range(0, H, 16):
+            err = float((dx[i, r:r + 16].float() - one.dx[0, r:r + 16].float()).abs().max()) / top
+            assert err <= parity.TOL["bf16"], (i, r, err)
+    for k, g in zip(names, grads):
+        assert parity.rel_err(runner.to_host(g), runner.to_host(one.grads[k])) <= parity.TOL["bf16"], k
+
+
 @pytest.mark.parametrize("groups", [1, 2, 3, 6])
 @pytest.mark.parametrize("shift", [0, 3])
 def test_narrow_forward_in_four_waves_and_in_one(oracle, groups, shift):
