@@ -52,10 +52,7 @@ template <class Cf, int HB_, int HE_, bool WPROJ_> struct BwdCfg {
     static constexpr size_t OFF_WQ = 0;
     static constexpr size_t OFF_BIAS = OFF_WQ + (size_t)N_WQ * 1024;
     static constexpr size_t OFF_WPT = OFF_BIAS + (size_t)NH * 3 * ET * 64; // fp32 b_qkv [head][q, k, v][16 ET]
-    // two heads of a wide three-head group fit LDS only without the Wproj^T fragments: those are
-    // then read from the packed buffer in memory (12 reads per wave, window and head)
-    static constexpr bool WPT_LDS = !(Cf::SPLIT && NH > 1 && Cf::HG == 3);
-    static constexpr size_t OFF_WQT = OFF_WPT + (WPT_LDS ? (size_t)N_WPT * 1024 : 0);
+    static constexpr size_t OFF_WQT = OFF_WPT + (size_t)N_WPT * 1024;
     static constexpr size_t PACK_BYTES = OFF_WQT + (size_t)N_WQT * 512;
     // LDS beyond the packed weights
     static constexpr int LW = 68; // pitch (bf16) of rows read 8 at a time (as two 8-byte halves:
@@ -125,9 +122,9 @@ constexpr bool ranges_overlap(int a0, int a1, int b0, int b1) { return a0 < b1 &
 // long, and a CU holds two workgroups: a read that is waited for where it is used costs more than its products.  So the
 // next window's rows are loaded a head before the window ends, in pieces of 16 bytes; a head's weights, biases (whole
 // padded tiles) and bias-table entries are read in front of the barrier before their use; the set-up's loads are all in
-// flight together; the table gradient of as many heads as LDS takes is folded at once.  fwd + bwd, 32 images of 64x64,
-// 60 channels: two groups 142.4 -> 127.0 us, one 198 -> 159, three 155 -> 135, six 143 -> 126.5; one image of 64x64
-// 58.8 -> 46.1; 180 channels with an odd shift, 8 images: two groups 230 -> 182, three 180 -> 143.
+// flight together; the table gradient of as many heads as LDS takes is folded at once.  fwd + bwd, 60 channels, six groups,
+// 32 images of 64x64: 143 -> 126.5 us, with packed tiles read turned 118.8; 180 channels, three groups, odd shift, 8 images:
+// 180 -> 143.
 template <class Cf, int HB, int HE, bool WPROJ>
 __global__ __launch_bounds__(256, (BwdCfg<Cf, HB, HE, WPROJ>::LDS_BYTES <= 80 * 1024 ? 2 : 1))
 void fused_bwd_kernel(Geom g, const bf16_t *__restrict__ x,
@@ -141,7 +138,7 @@ void fused_bwd_kernel(Geom g, const bf16_t *__restrict__ x,
     constexpr int NH = B::NH, GB = B::GB, GE = B::GE;
     constexpr int C = B::C, D = B::D, CG = B::CG, HG = B::HG, HEADS = B::HEADS, G = B::G;
     constexpr int ET = B::ET, KS = B::KS, KSC = B::KSC, LW = B::LW, NTBL = B::NTBL;
-    constexpr int CT = B::CT, NT = B::NT, KT = B::KT, OTP = B::OTP, CTP = B::CTP, NTP = B::NTP, KTP = B::KTP;
+    constexpr int CT = B::CT, NT = B::NT, KT = B::KT, CTP = B::CTP, NTP = B::NTP, KTP = B::KTP;
     constexpr int M = 8;
     static_assert(CG % 2 == 0 && D % 2 == 0 && C % 4 == 0, "dword-granular loads and stores");
     // The shift mask, exactly as the forward kernel of the same layer adds it: -100 for wide layers;
@@ -151,8 +148,7 @@ void fused_bwd_kernel(Geom g, const bf16_t *__restrict__ x,
 
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     const uint4 *wq = reinterpret_cast<const uint4 *>(lds + B::OFF_WQ);
-    const uint4 *wpt = B::WPT_LDS ? reinterpret_cast<const uint4 *>(lds + B::OFF_WPT)
-                                  : reinterpret_cast<const uint4 *>(pack + B::SRC_WPT);
+    const uint4 *wpt = reinterpret_cast<const uint4 *>(lds + B::OFF_WPT);
     const uint2 *wqt = reinterpret_cast<const uint2 *>(lds + B::OFF_WQT);
     const float *bqkv = reinterpret_cast<const float *>(lds + B::OFF_BIAS);
     float *tblf = reinterpret_cast<float *>(lds + B::OFF_TBLF);
@@ -258,7 +254,7 @@ void fused_bwd_kernel(Geom g, const bf16_t *__restrict__ x,
         constexpr int N_QT = (int)((B::PACK_BYTES - B::OFF_WQT) / 16), N_T = NTBL * NH, N_B = NH * 3 * ET * 16;
         constexpr int I_Q = (N_Q + 255) / 256, I_PT = (N_PT + 255) / 256, I_QT = (N_QT + 255) / 256, I_T = (N_T + 255) / 256;
         constexpr int I_B = (N_B + 255) / 256;
-        uint4 vq[I_Q], vpt[I_PT > 0 ? I_PT : 1], vqt[I_QT];
+        uint4 vq[I_Q], vpt[I_PT], vqt[I_QT];
         uint16_t vt[I_T];
         float vb[I_B];
         // (threads behind a part's end copy its last piece once more: under a condition each load would sit, and be
@@ -1046,7 +1042,7 @@ hipError_t launch_chunk(const Geom &g, int grid, const bf16_t *x, const bf16_t *
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    constexpr int CG = Cf::CG, D = Cf::D;
+    constexpr int CG = Cf::CG;
     ReduceOut out{};
     int k = 0;
     static_assert(2 * B::NG * 3 + 3 <= ReduceOut::MAXSEG, "segment table");

@@ -582,7 +582,7 @@ __global__ __launch_bounds__(1024) void wave4_fwd_kernel(Geom g, const bf16_t *_
     using W = Wave4FwdCfg<Cf, LAYER>;
     constexpr int C = Cf::C, D = Cf::D, CG = Cf::CG, HG = Cf::HG, HEADS = Cf::HEADS;
     constexpr int OT = Cf::OT, NSTEP = Cf::NSTEP, NDLT = Cf::NDLT, WPW = W::WPW, HB = W::HB, TW = 1;
-    constexpr int M = 8, NTHREADS = W::NTHREADS;
+    constexpr int M = 8;
     static_assert(Cf::ET == 1 && D + 4 <= 16, "one 16-row tile per head with four spare rows");
     static_assert(CG % 2 == 0 && D % 2 == 0 && C % 4 == 0 && HEADS % 2 == 0, "dword-granular loads and stores");
 
