@@ -151,6 +151,15 @@ hipError_t launch_fused_fwd(const Geom &g, const bf16_t *x, const bf16_t *w_qkv,
                             bf16_t *y, bf16_t *attn_out, void *pack, int training, bool packed, const FusedLn &ln,
                             hipStream_t s);
 
+// a / d with rd = 1 / d in fp32 and a fix-up: exact for operands below 2^24, a fraction of the cost of an integer division
+__device__ __forceinline__ int quotient(int a, int d, float rd)
+{
+    int qt = (int)((float)a * rd);
+    qt += (qt + 1) * d <= a ? 1 : 0;
+    qt -= qt * d > a ? 1 : 0;
+    return qt;
+}
+
 // ---------------------------------------------------------------------------------------
 // Parameter packing for this kernel (layout: FusedCfg, WQW / WPW / TBW)
 // ---------------------------------------------------------------------------------------

@@ -172,19 +172,12 @@ void fused_bwd_kernel(Geom g, const bf16_t *__restrict__ x,
     const int per_img = g.nwi * g.nwj;
     const int rn = 2 * wv + (l16 >> 3), cn = l16 & 7;
     const int s = g.shift;
-    // window -> (image, window row, window column): quotients through a float reciprocal with a fix-up
-    // (exact for operands below 2^24), a fraction of the cost of the integer divisions
+    // window -> (image, window row, window column)
     const float r_img = 1.0f / (float)per_img, r_nwj = 1.0f / (float)g.nwj;
-    auto fdiv = [](int a, int d, float rd) {
-        int qt = (int)((float)a * rd);
-        qt += (qt + 1) * d <= a ? 1 : 0;
-        qt -= qt * d > a ? 1 : 0;
-        return qt;
-    };
     auto token_of = [&](int win) {
-        const int b = fdiv(win, per_img, r_img);
+        const int b = quotient(win, per_img, r_img);
         const int wr = win - b * per_img;
-        const int wi = fdiv(wr, g.nwj, r_nwj), wj = wr - wi * g.nwj;
+        const int wi = quotient(wr, g.nwj, r_nwj), wj = wr - wi * g.nwj;
         int si = wi * M + rn + s, sj = wj * M + cn + s;
         if (si >= g.H) si -= g.H;
         if (sj >= g.W) sj -= g.W;
@@ -364,7 +357,7 @@ void fused_bwd_kernel(Geom g, const bf16_t *__restrict__ x,
                 }
         }
         const long tok = token_of(win);
-        const int wr = win - fdiv(win, per_img, r_img) * per_img, wi = fdiv(wr, g.nwj, r_nwj);
+        const int wr = win - quotient(win, per_img, r_img) * per_img, wi = quotient(wr, g.nwj, r_nwj);
         const bool lastrow = s > 0 && wi == g.nwi - 1, lastcol = s > 0 && wr - wi * g.nwj == g.nwj - 1;
 
         // ---- d w_proj, d b_proj: dY operands (read turned) and A^T rows [channel][token] through LDS, K = 64 tokens ----

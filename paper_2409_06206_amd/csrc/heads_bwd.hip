@@ -12,9 +12,8 @@
 // pipeline, group g one window behind group g + 1, with one barrier per window.
 //
 // T-form, N-form and the operand conventions: fused_bwd.hip, mfma.h.
-#include "fused.h"
 #include "heads_bwd.h"
-#include "mfma.h"
+#include "heads_common.h"
 
 namespace gswa {
 
@@ -73,13 +72,6 @@ template <class Cf> struct HeadsCfg {
     static constexpr int L_TBL = L_DBP + C, L_END = L_TBL + HEADS * NTBL, L_TOTAL = (L_END + 3) & ~3;
 };
 
-// 1 / x for a sum of exponentials (1 .. 64): the hardware's estimate and a Newton step, within 1 ulp of the quotient
-__device__ __forceinline__ float recip(float x)
-{
-    const float r = __builtin_amdgcn_rcpf(x);
-    return fmaf(fmaf(-x, r, 1.0f), r, r);
-}
-
 constexpr bool overlap(int a0, int a1, int b0, int b1) { return a0 < b1 && b0 < a1; }
 
 // What bounds it: six heads on four SIMD units, so two units issue the steps of two heads, 12.5 k clocks a window where a head
@@ -121,9 +113,8 @@ __global__ __launch_bounds__(HeadsCfg<Cf>::THREADS, 2) void heads_bwd_kernel(Geo
     const int hw = wv - HEADS;
     // ---- set-up: weights, biases and the table to LDS, all loads in flight together ----
     auto setup = [&](int tid) {
-        constexpr int TH = P::THREADS, NW = TH / 64, N1K = (int)(P::SZ_WPT / 1024), N_T = P::NTBL * HEADS / 2;
-        constexpr int I_T = (N_T + TH - 1) / TH;
-        static_assert(P::NTBL * HEADS % 2 == 0 && HEADS * 48 <= TH && P::SZ_WPT % 1024 == 0, "set-up in whole pieces");
+        constexpr int TH = P::THREADS, NW = TH / 64, N1K = (int)(P::SZ_WPT / 1024);
+        static_assert(HEADS * 48 <= TH && P::SZ_WPT % 1024 == 0, "set-up in whole pieces");
         const int lane = tid & 63;
 #pragma unroll
         for (int k = 0; k < (N1K + NW - 1) / NW; ++k) {
@@ -132,17 +123,10 @@ __global__ __launch_bounds__(HeadsCfg<Cf>::THREADS, 2) void heads_bwd_kernel(Geo
         }
         const int i = tid < HEADS * 48 ? tid : 0, e = i % 16, t = i / 16 % 3, hd = i / 48;
         const float v = reinterpret_cast<const float *>(pack + Cf::P_BIAS)[hd / HG * 3 * CG + t * CG + hd % HG * D + (e < D ? e : 0)];
-        uint16_t tv[I_T][2];
-#pragma unroll
-        for (int k = 0; k < I_T; ++k) {
-            const int at = k * TH + tid < N_T ? k * TH + tid : N_T - 1;
-            tv[k][0] = table[2 * at].bits;
-            tv[k][1] = table[2 * at + 1].bits;
-        }
+        TableCopy<P::NTBL * HEADS, TH> tc;
+        tc.fetch(table, tid);
         if (tid < HEADS * 48) reinterpret_cast<float *>(lds + P::OFF_BIAS)[i] = e < D ? v : 0.f;
-#pragma unroll
-        for (int k = 0; k < I_T; ++k)
-            if (k * TH + tid < N_T) reinterpret_cast<uint32_t *>(tbl)[k * TH + tid] = tv[k][0] | (uint32_t)tv[k][1] << 16;
+        tc.store(tbl, tid);
         __builtin_amdgcn_s_waitcnt(0);
     };
     // Wqkv^T tiles of group gn for the channels of its head hlp, a token tile of its dF (d(q|k|v) of the group's first head at
@@ -176,19 +160,13 @@ __global__ __launch_bounds__(HeadsCfg<Cf>::THREADS, 2) void heads_bwd_kernel(Geo
         // ---- rows (waves 6 and 7): token tiles 2 hw and 2 hw + 1 of a window ----
         const int per_img = g.nwi * g.nwj;
         const float r_img = 1.0f / (float)per_img, r_nwj = 1.0f / (float)g.nwj;
-        auto fdiv = [](int a, int d, float rd) { // (exact for operands below 2^24)
-            int qt = (int)((float)a * rd);
-            qt += (qt + 1) * d <= a ? 1 : 0;
-            qt -= qt * d > a ? 1 : 0;
-            return qt;
-        };
         uint4 rx[2][G][KS], ra[2][G][KS], rdy[2][KSC]; // as loaded: partial pieces still unshifted
         uint32_t rtok[2];
         int rflag = 0;
         auto load_rows = [&](int m) {
             const int win = (int)blockIdx.x + m * (int)gridDim.x;
-            const int b = fdiv(win, per_img, r_img), wr = win - b * per_img;
-            const int wi = fdiv(wr, g.nwj, r_nwj), wj = wr - wi * g.nwj;
+            const int b = quotient(win, per_img, r_img), wr = win - b * per_img;
+            const int wi = quotient(wr, g.nwj, r_nwj), wj = wr - wi * g.nwj;
             rflag = s > 0 ? (wi == g.nwi - 1 ? 1 : 0) | (wj == g.nwj - 1 ? 2 : 0) : 0;
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
@@ -226,18 +204,8 @@ __global__ __launch_bounds__(HeadsCfg<Cf>::THREADS, 2) void heads_bwd_kernel(Geo
                     for (int ks = 0; ks < KS; ++ks) {
                         af[i][gi][ks] = piece4<CG>(ra[i][gi][ks], 32 * ks, q);
                         uint4 f = piece4<CG>(rx[i][gi][ks], 32 * ks, q);
-                        // Eq. 8: F = x slice + previous group's output, rounded to bf16 as the forward kernels round it
-                        if (gi > 0 && g.cascade) {
-                            const uint4 a = af[i][gi > 0 ? gi - 1 : 0][ks];
-                            f.x = add_bf16x2(f.x, a.x);
-                            f.y = add_bf16x2(f.y, a.y);
-                            f.z = add_bf16x2(f.z, a.z);
-                            f.w = add_bf16x2(f.w, a.w);
-                        }
-                        if (ks == CG / 32) { // the slot behind the channels: 1 for the bias sums, against zeros in the weights
-                            uint32_t &w = (CG % 8 / 2) == 0 ? f.x : (CG % 8 / 2) == 1 ? f.y : (CG % 8 / 2) == 2 ? f.z : f.w;
-                            w = q == CG % 32 / 8 ? w | 0x3f80u : w;
-                        }
+                        if (gi > 0 && g.cascade) f = add_bf16x8(f, af[i][gi > 0 ? gi - 1 : 0][ks]);
+                        f = with_bias_slot<CG>(f, ks, q);
                         if (lane < P::FL) fb[(((P::f_first(gi) + m % P::f_slots(gi)) * KS + ks) * 4 + tt) * P::FL + lane] = f;
                     }
                 if (q == 0) tokb[(m % P::TOK_SLOTS) * 64 + 16 * tt + l16] = rtok[i];
@@ -588,26 +556,11 @@ __global__ __launch_bounds__(HeadsCfg<Cf>::THREADS, 2) void heads_bwd_kernel(Geo
             for (int j = 0; j < 4; ++j) mat[(dl * 16 + 4 * q + j) * P::TP + l16] = tblacc[dl][j];
     }
     __syncthreads();
-    // The entry of offset (dr, dc) of a query from its key: in tiles of two window rows the query's row is rq, the key's rk,
-    // with rq - rk - dr = 2 (dl - 3), which two of the four pairs fulfil; eight columns each, all reads in flight.
     const float *mat = fold + hd * P::NDLT * 16 * P::TP;
 #pragma unroll
     for (int k = 0; k < (P::NTBL + 63) / 64; ++k) {
         const int e = 64 * k + le < P::NTBL ? 64 * k + le : P::NTBL - 1;
-        const int dr = e / (2 * M - 1) - (M - 1), dc = e % (2 * M - 1) - (M - 1), odd = dr & 1;
-        float a = 0.f;
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int rq = odd ? 1 - i : i, rk = i, d2 = rq - rk - dr;
-            const bool ok = d2 >= -6 && d2 <= 6;
-            const float *t = mat + (((ok ? d2 / 2 : 0) + 3) * 16 + 8 * rk) * P::TP + 8 * rq;
-#pragma unroll
-            for (int c = 0; c < M; ++c) {
-                const int ck = c - dc;
-                const float v = t[(ck < 0 ? 0 : ck >= M ? M - 1 : ck) * P::TP + c];
-                a += ok && ck >= 0 && ck < M ? v : 0.f;
-            }
-        }
+        const float a = table_entry<P::TP>(mat, e);
         if (64 * k + le < P::NTBL) mine[P::L_TBL + hd * P::NTBL + e] = a;
     }
 }

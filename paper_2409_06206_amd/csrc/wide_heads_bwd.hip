@@ -19,8 +19,7 @@
 // Inputs of any size.  q, k, v and the scores come from the operands of the one-launch forward, log2(e) / sqrt(d) in the query
 // rows.  From 2^31 elements on the forward is another one with 1 / sqrt(d) there: q is rounded once in either, but not to the
 // same values (as with three groups and an odd shift, where the backward is the one with 1 / sqrt(d), fused_bwd.hip).
-#include "fused.h"
-#include "mfma.h"
+#include "heads_common.h"
 #include "wide_heads_bwd.h"
 
 namespace gswa {
@@ -59,12 +58,6 @@ template <class Cf> struct WideHeadsCfg {
     static constexpr int L_TOTAL = (L_END + 3) & ~3;
 };
 
-__device__ __forceinline__ float recip(float x) // as heads_bwd.hip
-{
-    const float r = __builtin_amdgcn_rcpf(x);
-    return fmaf(fmaf(-x, r, 1.0f), r, r);
-}
-
 template <class Cf, int GI>
 __global__ __launch_bounds__(WideHeadsCfg<Cf>::THREADS, 1) void wide_heads_bwd_kernel(Geom g, const bf16_t *__restrict__ x,
                                                                                      const bf16_t *__restrict__ dy,
@@ -94,7 +87,7 @@ __global__ __launch_bounds__(WideHeadsCfg<Cf>::THREADS, 1) void wide_heads_bwd_k
 
     // ---- set-up: weights, biases and the table to LDS, all loads in flight together ----
     auto setup = [&](int tid) {
-        constexpr int TH = P::THREADS, NW = TH / 64, N1K = (int)(P::SZ_WQ / 1024), N_T = P::NTBL * HEADS / 2, I_T = (N_T + TH - 1) / TH;
+        constexpr int TH = P::THREADS, NW = TH / 64, N1K = (int)(P::SZ_WQ / 1024);
         constexpr int I_B = (HG * 96 + TH - 1) / TH;
         const int lane = tid & 63;
 #pragma unroll
@@ -103,25 +96,18 @@ __global__ __launch_bounds__(WideHeadsCfg<Cf>::THREADS, 1) void wide_heads_bwd_k
             if (f < N1K) lds_dma16(pack + Cf::P_WQN + ((size_t)GI * N1K + f) * 1024 + 16 * lane, lds + P::OFF_WQ + (size_t)f * 1024);
         }
         float bv[I_B];
-        uint16_t tv[I_T][2];
+        TableCopy<P::NTBL * HEADS, TH> tc;
 #pragma unroll
         for (int k = 0; k < I_B; ++k) {
             const int i = k * TH + tid < HG * 96 ? k * TH + tid : 0, e = i % 32, t = i / 32 % 3, hl = i / 96;
             bv[k] = reinterpret_cast<const float *>(pack + Cf::P_BIAS)[GI * 3 * CG + t * CG + hl * D + (e < D ? e : 0)];
             bv[k] = e < D ? (t == 0 ? bv[k] * kLog2e : bv[k]) : 0.f;
         }
-#pragma unroll
-        for (int k = 0; k < I_T; ++k) {
-            const int at = k * TH + tid < N_T ? k * TH + tid : N_T - 1;
-            tv[k][0] = table[2 * at].bits;
-            tv[k][1] = table[2 * at + 1].bits;
-        }
+        tc.fetch(table, tid);
 #pragma unroll
         for (int k = 0; k < I_B; ++k)
             if (k * TH + tid < HG * 96) reinterpret_cast<float *>(lds + P::OFF_BIAS)[k * TH + tid] = bv[k];
-#pragma unroll
-        for (int k = 0; k < I_T; ++k)
-            if (k * TH + tid < N_T) reinterpret_cast<uint32_t *>(tbl)[k * TH + tid] = tv[k][0] | (uint32_t)tv[k][1] << 16;
+        tc.store(tbl, tid);
         __builtin_amdgcn_s_waitcnt(0);
     };
 
@@ -131,19 +117,13 @@ __global__ __launch_bounds__(WideHeadsCfg<Cf>::THREADS, 1) void wide_heads_bwd_k
         const int lane = lane_h, l16 = lane & 15, q = lane >> 4;
         const int per_img = g.nwi * g.nwj;
         const float r_img = 1.0f / (float)per_img, r_nwj = 1.0f / (float)g.nwj;
-        auto fdiv = [](int a, int d, float rd) { // (exact for operands below 2^24)
-            int qt = (int)((float)a * rd);
-            qt += (qt + 1) * d <= a ? 1 : 0;
-            qt -= qt * d > a ? 1 : 0;
-            return qt;
-        };
         uint4 rx[4][KS], ra[4][KS], rdy[4][KSC]; // as loaded: partial pieces still unshifted
         uint32_t rtok[4];
         int rflag = 0;
         auto load_rows = [&](int m) {
             const int win = (int)blockIdx.x + m * (int)gridDim.x;
-            const int b = fdiv(win, per_img, r_img), wr = win - b * per_img;
-            const int wi = fdiv(wr, g.nwj, r_nwj), wj = wr - wi * g.nwj;
+            const int b = quotient(win, per_img, r_img), wr = win - b * per_img;
+            const int wi = quotient(wr, g.nwj, r_nwj), wj = wr - wi * g.nwj;
             rflag = s > 0 ? (wi == g.nwi - 1 ? 1 : 0) | (wj == g.nwj - 1 ? 2 : 0) : 0;
             int sj = wj * M + (l16 & 7) + s;
             if (sj >= g.W) sj -= g.W;
@@ -170,17 +150,8 @@ __global__ __launch_bounds__(WideHeadsCfg<Cf>::THREADS, 1) void wide_heads_bwd_k
 #pragma unroll
                 for (int ks = 0; ks < KS; ++ks) {
                     uint4 f = piece4<CG>(rx[t][ks], 32 * ks, q);
-                    if (casc_in) { // Eq. 8, rounded as the forward kernels round it
-                        const uint4 a = piece4<CG>(ra[t][ks], 32 * ks, q);
-                        f.x = add_bf16x2(f.x, a.x);
-                        f.y = add_bf16x2(f.y, a.y);
-                        f.z = add_bf16x2(f.z, a.z);
-                        f.w = add_bf16x2(f.w, a.w);
-                    }
-                    if (ks == CG / 32) { // the slot behind the channels: 1 for the bias sums, against zeros in the weights
-                        uint32_t &w = (CG % 8 / 2) == 0 ? f.x : (CG % 8 / 2) == 1 ? f.y : (CG % 8 / 2) == 2 ? f.z : f.w;
-                        w = q == CG % 32 / 8 ? w | 0x3f80u : w;
-                    }
+                    if (casc_in) f = add_bf16x8(f, piece4<CG>(ra[t][ks], 32 * ks, q));
+                    f = with_bias_slot<CG>(f, ks, q);
                     fb[(ks * 4 + t) * 64 + lane] = f;
                 }
                 if (q == 0) tokb[(m & 1) * 64 + 16 * t + l16] = rtok[t];
@@ -561,24 +532,10 @@ __global__ __launch_bounds__(WideHeadsCfg<Cf>::THREADS, 1) void wide_heads_bwd_k
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    // (entries of the table: as in heads_bwd.hip)
 #pragma unroll
     for (int k = 0; k < (P::NTBL + 63) / 64; ++k) {
         const int e = 64 * k + lane < P::NTBL ? 64 * k + lane : P::NTBL - 1;
-        const int dr = e / (2 * M - 1) - (M - 1), dc = e % (2 * M - 1) - (M - 1), odd = dr & 1;
-        float a = 0.f;
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int rq = odd ? 1 - i : i, rk = i, d2 = rq - rk - dr;
-            const bool ok = d2 >= -6 && d2 <= 6;
-            const float *t = mat + (((ok ? d2 / 2 : 0) + 3) * 16 + 8 * rk) * P::TP + 8 * rq;
-#pragma unroll
-            for (int c = 0; c < M; ++c) {
-                const int ck = c - dc;
-                const float v = t[(ck < 0 ? 0 : ck >= M ? M - 1 : ck) * P::TP + c];
-                a += ok && ck >= 0 && ck < M ? v : 0.f;
-            }
-        }
+        const float a = table_entry<P::TP>(mat, e);
         if (64 * k + lane < P::NTBL) mine[P::L_TBL + hl * P::NTBL + e] = a;
     }
 }
