@@ -104,14 +104,15 @@ typedef struct gswa_desc {
  *                  adds over the copies; one launch sums them at the end) and, for bf16 layers with
  *                  64- or 144-token windows, one bias-table gradient per window.
  *                  GSWA_PATH_WINDOW: at least one gradient vector for each of up to 256 workgroups.
- *                  Fused path: one partial parameter-gradient vector per workgroup of ONE head-group
- *                  launch (each launch is followed by the fixed-order sum of its partials, and the next
- *                  reuses the buffer), so this size does not grow with the group count.  Layers of
- *                  180 channels with two or three groups and 8x8 windows additionally pass ONE
- *                  group's intermediate gradients (d(q|k|v), the group's input and its gradient, as
- *                  matrix-core operand fragments) from the attention kernel to the kernel that forms
- *                  dx and the weight gradients: about 7.6 Cg bytes per token, falling with the group
- *                  count.
+ *                  Fused path: one partial parameter-gradient vector per workgroup of ONE launch
+ *                  (60 channels: of all head groups, or with six of three; 180: of one group.  Each
+ *                  launch is followed by the fixed-order sum of its partials, and the next reuses the
+ *                  buffer), so this size does not grow with the group count.  Layers of 180 channels
+ *                  with 8x8 windows: two groups add the projection's vectors, up to 36 KB a window;
+ *                  three, with an even shift, pass ONE group's intermediate gradients (d(q|k|v), the
+ *                  group's input and its gradient, as matrix-core operand fragments) from the
+ *                  attention kernel to the kernel that forms dx and the weight gradients: about
+ *                  7.6 Cg bytes per token.
  * Which path serves a layer, and every size, depends only on desc (shape, dtype, flags), not on the
  * device.
  * Any output pointer may be NULL.  All sizes are multiples of 256.

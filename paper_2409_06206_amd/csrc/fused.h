@@ -1,10 +1,9 @@
 // Fused per-window GSWA kernels (bf16 storage, MFMA arithmetic).
 //
-// Activations stay in registers in MFMA operand / result layouts (see mfma.h).  Three ways of
+// Activations stay in registers in MFMA operand / result layouts (see mfma.h).  Four ways of
 // giving a window to the hardware are in use:
 //   * one wavefront per window (forward of narrow layers with many windows, attention adjoint of wide layers of three groups):
-//     the wave
-//     holds all 64 tokens as four 16-token tiles, so nothing crosses waves and no barrier is needed for it;
+//     the wave holds all 64 tokens as four 16-token tiles, so nothing crosses waves and no barrier is needed for it;
 //   * a few wavefronts per window, several windows per workgroup (forward of narrow layers with few windows and of whole
 //     narrow layers: four waves of one tile; forward of wide layers: waves of one or two tiles, wide_fwd.hip): K and V of a
 //     head cross the window's waves through LDS, as the operands they are read as;
@@ -164,9 +163,8 @@ __device__ __forceinline__ int quotient(int a, int d, float rd)
 // Parameter packing for this kernel (layout: FusedCfg, WQW / WPW / TBW)
 // ---------------------------------------------------------------------------------------
 // Bits of p[at], zero where the operand is padding.  The load is always taken (entry 0 stands in for none), so that a thread's
-// eight are in flight together: behind a branch each they are eight trips to memory one after the other.  That is what bounds
-// the packing, a launch as short as its longest thread: C = 180 with one / two groups 5.7 / 5.2 -> 4.9 / 4.7 us; C = 60 with
-// the operand of heads_bwd.hip added 5.2 -> 4.9.
+// eight are in flight together: behind a branch each they are eight trips to memory one after the other, which bounds a launch
+// this short (C = 180, one / two groups, 5.7 / 5.2 us; with this 4.9 / 4.7).
 __device__ __forceinline__ uint32_t entry_or_zero(const bf16_t *p, int at, bool ok)
 {
     const uint32_t v = p[ok ? at : 0].bits;

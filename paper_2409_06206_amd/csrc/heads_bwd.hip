@@ -77,11 +77,8 @@ constexpr bool overlap(int a0, int a1, int b0, int b1) { return a0 < b1 && b0 < 
 // What bounds it: six heads on four SIMD units, so two units issue the steps of two heads, 12.5 k clocks a window where a head
 // alone takes 10 k (four query tiles of 1.6 k, 3 k before and 1 k behind them); most of a tile is the chain products -> softmax
 // -> products.  Against launches per head group with a window in four waves and three barriers a head: 32 images of 64x64, 60
-// channels, forward + backward, 1 / 2 / 3 groups 160.4 / 128.6 / 138.8 -> 97.6 / 90.7 / 95.7 us.  On the way there, two groups:
-// turned reads in place of products with the identity 107.9 -> 108.0 (fewer instructions, more waits), every read in front of
-// the first write 104.1, dF of the first group on waves 6 and 7 102.7, d(q|k|v) in 32 features a head instead of 3 x 16 97.0.  Then the ends: set-up in one trip
-// to memory and the table's diagonals with all reads in flight (8.4 -> 6.8 k and 17.5 -> 7.5 k clocks of 130 k): 91.9; one image of
-// 64x64 38.2 -> 32.3.
+// channels, forward + backward, 1 / 2 / 3 groups 160.4 / 128.6 / 138.8 -> 97.6 / 90.7 / 95.7 us; one image, two groups, 46.4 ->
+// 31.6.
 template <class Cf>
 __global__ __launch_bounds__(HeadsCfg<Cf>::THREADS, 2) void heads_bwd_kernel(Geom g, const bf16_t *__restrict__ x,
                                                                             const bf16_t *__restrict__ dy,

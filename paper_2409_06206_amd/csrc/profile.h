@@ -18,7 +18,7 @@ enum KernelId {
     K_QKV_WGRAD,    // d w_qkv, d b_qkv of one group
     K_PACK_FWD,     // parameters into MFMA fragment order (once per forward call, both passes use it)
     K_FUSED_FWD,    // whole forward layer, one launch
-    K_FUSED_BWD,    // dx and partial parameter gradients of one head chunk
+    K_FUSED_BWD,    // dx and partial parameter gradients of a narrow layer, or of one chunk of heads
     K_REDUCE,       // per-workgroup partial sums -> parameter gradients
     K_ATTN_CHUNK_FWD, // split forward: attention of one head chunk
     K_PROJ_GEMM,    // split forward: output projection (Eq. 7)

@@ -10,9 +10,9 @@
 // room for a second).  Of the 18 k clocks of a window q, k, v and dO take 5 k, scores to d(q|k|v) 6.5 k, the d(q|k|v) rows 1 k,
 // the weight gradients 1.9 k and dF 2.9 k; eight windows a workgroup, 12 k clocks of set-up and 12 k to leave the partial sums.
 // What it saves over an adjoint and a gradient launch a group (wide_bwd.hip) is memory: d(q|k|v), F and the cascade gradient
-// went out and in between the two, 380 MB a group of 2048 windows against 125.  Forward + backward of 32 / 16 / 1 images of
-// 64x64 333.2 / 202.7 / 117.0 us by those two, 273.4 / 172.0 / 81.7 by heads; with an odd shift, which took four launches of one
-// or two heads with a workgroup a window, 32 images 462.2 -> 273.2, an image of 24x16 102.5 -> 73.8.
+// went out and in between the two, 380 MB a group of 2048 windows against 184 (94 are what the method needs).  Forward + backward
+// of 32 / 16 / 1 images of 64x64 333.2 / 202.7 / 117.0 us by those two, 273.4 / 172.0 / 81.7 by heads; with an odd shift, which
+// took four launches of one or two heads with a workgroup a window, 32 images 462.2 -> 273.2, an image of 24x16 102.5 -> 73.8.
 //
 // For two groups: with three a group's two heads would leave half the SIMD units to row fetches, and its launches are three.
 //
@@ -164,7 +164,11 @@ __global__ __launch_bounds__(WideHeadsCfg<Cf>::THREADS, 1) void wide_heads_bwd_k
         __syncthreads();
         __syncthreads();
         for (int m = 0; m < cnt; ++m) {
-            __builtin_amdgcn_s_sleep(24); // (1.5 k clocks: the heads' own loads of this window go first)
+            // The heads' own loads of this window go first: they are waited for at once, these rows a window later.  (Sleeping
+            // 0 / 6 / 12 / 24 / 48 / 96, 64 clocks each, of a window's 18 k: 32 images of 64x64, forward + backward, 273.9 /
+            // 271.4 / 270.5 / 269.1 / 268.7 / 269.2 us, 16 images 168.6 / 167.4 / 167.4 / 165.9 / 165.4 / 166.1; eight and fewer,
+            // with one or two windows a workgroup, within their noise.)
+            __builtin_amdgcn_s_sleep(24);
             if (m + 1 < cnt) load_rows(m + 1);
             __syncthreads();
             if (m + 1 < cnt) stage(m + 1);

@@ -309,7 +309,7 @@ def test_reproducible_mode_is_a_valid_flag_and_sizes_its_scratch():
 def test_fused_path_memory_does_not_grow_with_the_group_count():
     """Default (fused) path at the benchmark's narrow and wide shapes: saved state plus scratch is
     non-increasing in the group count -- the scratch holds the partial parameter gradients of one
-    head-group launch at a time, which shrink with the group."""
+    launch at a time, which shrink with the group."""
     for shape, groups in (((32, 64, 64, 60), (1, 2, 3, 6)), ((16, 64, 64, 180), (2, 3))):
         B, H, W, C = shape
         prev = None

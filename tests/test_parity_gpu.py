@@ -72,8 +72,8 @@ def test_forced_staged_path_one_group_many_tokens(oracle, C, heads):
 @pytest.mark.parametrize("groups,rows,cols,launches", [(2, 8, 113, 3), (2, 5, 181, 2), (3, 23, 59, 4), (3, 14, 97, 3)])
 def test_last_sums_of_a_wide_backward_in_two_launches_and_in_one(oracle, groups, rows, cols, launches):
     """180 channels: with 904 windows and two groups, 1357 and three, the projection's partial vectors (256 compute units) do
-    not fit the place of d(q|k|v); with 905 and 1358 they just fill it, while the other sums still have to be taken (with
-    three groups the vectors of q|k|v are summed one entry a load, the projection's four); here all are added."""
+    not fit the part of the scratch that is free by then; with 905 and 1358 they just do, while the other sums still have
+    to be taken (with three groups the vectors of q|k|v are summed one entry a load, the projection's four); here all are added."""
     from paper_2409_06206_amd import gswa, runner
     H, W = 8 * rows, 8 * cols
     x, dy, p = parity.make_inputs(1, H, W, 180, 6, groups, 8, "bf16", synth.LAYER_SEED0 + 3, "stress")
@@ -564,7 +564,8 @@ def test_wide_backward_with_a_wave_per_head(oracle, B, H, W, shift, cascade, acc
 
 @pytest.mark.parametrize("groups", [2, 3])
 def test_wide_layers_more_windows_than_wavefronts(oracle, groups):
-    """27 x (9 x 5) = 1215 windows of a wide layer: more than the 1024 wavefronts of a backward launch
+    """27 x (9 x 5) = 1215 windows of a wide layer.  Two groups: four or five windows for each of 256 workgroups of a backward
+    launch.  Three groups: more than the 1024 wavefronts of a backward launch
     on 256 compute units (a ragged second round), an odd number of windows (the kernel that takes
     them in pairs is left with one), odd window counts per image, shifted."""
     _say("many windows, wide", groups)
