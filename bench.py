@@ -27,9 +27,9 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0
 # the launch kinds of that kernel), valid only for the kernel source they were taken on:
 # {(workload, groups, kernel): (source file, sha256 of it, bytes per launch)}
 MEASURED_TRAFFIC = {
-    ("c4", 2, "wide_attn_bwd"): ("wide_heads_bwd.hip", "16a12853915bf7e2f5a8e94c52c63371cd3fbcb50961ef0ba7b9661ced631d5e", 183652040),
-    ("c3", 2, "wide_attn_bwd"): ("wide_heads_bwd.hip", "16a12853915bf7e2f5a8e94c52c63371cd3fbcb50961ef0ba7b9661ced631d5e", 105754336),
-    ("c2", 2, "fused_bwd"): ("heads_bwd.hip", "e3e0280be8e19c2ff4442d5383cdf1313648c1136b59f261eabc92734ee4fd60", 83200420),
+    ("c4", 2, "wide_attn_bwd"): ("wide_heads_bwd.hip", "f6b1824ffaf83fad5a1eb6588b6b0f114998ecf7eb4ceb94cee4cf8926f7fabb", 183646560),
+    ("c3", 2, "wide_attn_bwd"): ("wide_heads_bwd.hip", "f6b1824ffaf83fad5a1eb6588b6b0f114998ecf7eb4ceb94cee4cf8926f7fabb", 105748640),
+    ("c2", 2, "fused_bwd"): ("heads_bwd.hip", "bc19b2a2bbede7fb774c67230933e7ec8a4cd5a3ca53ecf66f79562abd3589ad", 83340036),
     ("c5_m8", 2, "fused_fwd"): ("wide_fwd.hip", "3a045cb1571dda4b176ffd6295e73fed859232efe85b4d08bb43f1dd406cb3e9", 238968328),
     ("c5_m16", 2, "fused_fwd"): ("wide_fwd.hip", "3a045cb1571dda4b176ffd6295e73fed859232efe85b4d08bb43f1dd406cb3e9", 240168888),
 }
